@@ -192,8 +192,7 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
  * grads:  host array [n_params] of device pointers, float32 or bfloat16 per
  *         grad_dtype, same shapes; read only.
  * Asynchronous on `stream` (except refresh steps under SHAMPOO_ROOT_NEWTON, see
- * root_method, and a call that follows a change of the params / grads pointers, which first
- * waits for `stream`: the tables it sends replace those an earlier call may still be copying).
+ * root_method).
  * With bf16 gradients the factor update of the first steps, while a factor has summed fewer than
  * four times as many gradient columns as it has rows, adds up in float64 (the later ones in the
  * float32 accumulators of the matrix cores): a root taken from such a young factor weights its

@@ -1,4 +1,5 @@
-"""ctypes binding of libshampoo.so: the same entry points as include/shampoo.h.
+"""ctypes binding of libshampoo.so: the same entry points as include/shampoo.h
+(the tensors of a step go through _marshal.so, csrc/marshal.cpp).
 
 Argument marshalling only -- every step of the optimizer runs in the HIP
 kernels of the library.  PyTorch is used for device memory and streams.
@@ -204,29 +205,14 @@ class Shampoo:
         with torch.cuda.device(self.device):
             _check(lib().shampoo_create(ctypes.byref(self.cfg), ctypes.c_void_p(self.workspace.data_ptr()),
                                         nbytes, _stream_ptr(), ctypes.byref(self.handle)))
-        self._n = len(self.shapes)
-        self._pw = (ctypes.c_void_p * self._n)()
-        self._pg = (ctypes.c_void_p * self._n)()
+        from . import _marshal
+        self._marshal = _marshal
+        self._stepper = _marshal.make(ctypes.cast(lib().shampoo_step, ctypes.c_void_p).value, self.handle.value, device,
+                                      grad_dtype == GRAD_BF16, self.shapes)
 
     def step(self, params, grads, lr, step):
         """params / grads: lists of contiguous CUDA tensors (float32 / float32-or-bfloat16)."""
-        import torch
-        gdt = torch.bfloat16 if self.grad_dtype == GRAD_BF16 else torch.float32
-        if len(params) != self._n or len(grads) != self._n:
-            raise ValueError("one parameter and one gradient tensor per declared parameter")
-        for i in range(self._n):
-            w, g = params[i], grads[i]
-            if not (w.is_cuda and g.is_cuda and w.device == self.device and g.device == self.device):
-                raise ValueError(f"parameter {i}: tensors must live on {self.device}")
-            if w.dtype != torch.float32 or g.dtype != gdt:
-                raise ValueError(f"parameter {i}: parameters are float32, gradients {gdt}")
-            if not (w.is_contiguous() and g.is_contiguous()):
-                raise ValueError(f"parameter {i}: tensors must be contiguous")
-            if tuple(w.shape) != tuple(self.shapes[i]) or tuple(g.shape) != tuple(self.shapes[i]):
-                raise ValueError(f"parameter {i}: shape differs from the one given at creation")
-            self._pw[i] = w.data_ptr()
-            self._pg[i] = g.data_ptr()
-        _check(lib().shampoo_step(self.handle, self._pw, self._pg, lr, step, _stream_ptr()))
+        _check(self._marshal.step(self._stepper, params, grads, lr, step) if self.handle else -1)
 
     def get(self, param, block, which):
         import torch
@@ -280,6 +266,7 @@ class Shampoo:
 
     def destroy(self):
         if self.handle:
+            self._stepper = None
             lib().shampoo_destroy(self.handle)
             self.handle = ctypes.c_void_p()
 
@@ -290,6 +277,9 @@ class Shampoo:
             pass
 
 
+# The stand-alone calls take their workspace from torch's allocator and give it back on return,
+# while the work is still queued: the allocator hands freed memory to later work of the same
+# stream only, and the library's helper streams have joined that stream by then.
 def shampoo_root_inverse(a, epsilon, r, want_lambda=False, want_failed=False):
     """a: CUDA float32 tensor [batch, n, n] (symmetric).  Returns X [batch, n, n]
     (and eigenvalues [batch, n], failure flags [batch] on request)."""
@@ -308,7 +298,6 @@ def shampoo_root_inverse(a, epsilon, r, want_lambda=False, want_failed=False):
             ctypes.c_void_p(lam.data_ptr()) if lam is not None else None,
             ctypes.c_void_p(failed.data_ptr()) if failed is not None else None,
             ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr()))
-        torch.cuda.current_stream().synchronize()   # ws is released on return
     res = [x]
     if want_lambda:
         res.append(lam)
@@ -341,7 +330,6 @@ def shampoo_root_inverse_warm(a, epsilon, r, qt, start):
             ctypes.c_void_p(lam.data_ptr()), ctypes.c_void_p(failed.data_ptr()), ctypes.c_void_p(qt.data_ptr()),
             1 if start else 0, ctypes.c_void_p(sweeps.data_ptr()), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
             _stream_ptr()))
-        torch.cuda.current_stream().synchronize()   # ws is released on return
     return x, lam, failed, sweeps
 
 
@@ -391,7 +379,6 @@ def shampoo_root_inverse_newton(a, epsilon, p, tolerance=1e-6, max_iterations=10
             ctypes.c_void_p(iters.data_ptr()) if iters is not None else None,
             ctypes.c_void_p(failed.data_ptr()) if failed is not None else None,
             ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr()))
-        torch.cuda.current_stream().synchronize()   # ws is released on return
     res = [x]
     if want_iterations:
         res.append(iters)

@@ -369,6 +369,19 @@ __global__ __launch_bounds__(EW_THREADS) void prep_kernel(const PrepArgs g) {
   }
 }
 
+// Parameter and gradient pointers of one step, passed by value (the 4 KB of a kernel's arguments
+// hold 240 pairs) and written to the tables that the other kernels read.
+constexpr int POINTER_SET = 240;
+struct PointerSet {
+  void **w_table, **g_table;
+  int32_t count;
+  void *w[POINTER_SET], *g[POINTER_SET];
+};
+__global__ __launch_bounds__(256) void pointer_table_kernel(const PointerSet p) {
+  const int i = threadIdx.x;
+  if (i < p.count) { p.w_table[i] = p.w[i]; p.g_table[i] = p.g[i]; }
+}
+
 __global__ __launch_bounds__(256) void fill_kernel(float *p, float v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = v;
