@@ -1,0 +1,509 @@
+// Root inverse of matrices of n <= 128 without eigenvectors, one workgroup per matrix.
+//
+//   A = Q T Q^T        Householder reduction to tridiagonal form, float64, A in registers
+//   F = f(T)           f(x) = (x - min(lambda_min, 0) + eps)^-r as a sum of inverses of shifted T
+//                      (root_rational.h): two recurrences per shift, one product chain per row
+//   X = Q F Q^T        the same reflectors in reverse order, float64, F in registers
+//
+// The LDS Jacobi solver (eigh_jacobi.h) does the same job in about eight sweeps of 127 rounds with
+// two barriers and a pass over the matrix each; here there are 2 x 126 reflections.  It still serves
+// callers that want the eigenvalues, and exponents that root_rational.h has no fit for.
+//
+// What bounds it: the latency of a reflection (barriers, wavefront reductions) and its LDS reads.
+// The matrix itself stays out of LDS: a thread owns rows rg + RG a and columns cl + 16 b (cyclic,
+// so that the shrinking part stays spread over all threads), only the vectors of a reflection go
+// through LDS, and partial row sums meet across the 16 lanes of a DPP row.  At n = 128: 4 wavefronts,
+// 128 registers of matrix per lane, 80 KB of LDS, two workgroups per CU.
+//
+// Accuracy: T comes from a float64 reduction, so eigenvalues move by about 1e-16 of the largest, as
+// in the float64 Jacobi; the reflectors are kept as float32 for the way back (orthogonal to 1e-7,
+// like accumulated float32 rotations) and the terms of F are float32.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "eigh_jacobi.h"      // SmallRootArgs, rcp_newton
+#include "root_rational.h"
+
+namespace shampoo {
+
+// The smallest eigenvalue is bisected to float64 accuracy and its eigenvector handled apart from
+// the rational sum when it is negative (then f there is exactly eps^-r) or below this fraction of
+// the largest: a float64 reduction resolves lambda to 1e-16 of the largest, so that at 2^-32 the
+// argument of f still holds to 1e-6.
+constexpr double TRI_DEFLATE_BELOW = 0x1p-32;
+constexpr double TRI_LOWEST = 0x1p-48;       // the widest range of the rational sum
+constexpr int TRI_CHUNK = 16;                // columns of F handed from their makers to their owners at a time
+
+// element of another lane of the same 16
+template <int CTRL>
+__device__ __forceinline__ double dpp_fetch(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141, DPP_MIRROR16 = 0x140;
+
+__device__ __forceinline__ double row16_sum(double x) {
+  x += dpp_fetch<DPP_XOR1>(x);
+  x += dpp_fetch<DPP_XOR2>(x);
+  x += dpp_fetch<DPP_MIRROR8>(x);
+  return x + dpp_fetch<DPP_MIRROR16>(x);
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+// sum over the 64 lanes, the same bits in all of them
+__device__ __forceinline__ double wave64_sum(double x) {
+  x = row16_sum(x);
+  return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
+}
+
+// Sums of RB values over 16 lanes, the values split among the lanes on the way: lane cl ends with
+// value row16_slot<RB>(cl).  Each step sends the half that the other side keeps.
+template <int RB> __device__ __forceinline__ int row16_slot(int cl) {
+  return RB == 4 ? (((cl >> 3) & 1) * 2 + ((cl >> 2) & 1)) : (((cl >> 3) & 1) * 4 + ((cl >> 2) & 1) * 2 + ((cl >> 1) & 1));
+}
+template <int RB> __device__ __forceinline__ double row16_sums(const double (&v)[RB], int cl) {
+  static_assert(RB == 4 || RB == 8, "4 or 8 values");
+  double h[RB / 2];
+  const bool b3 = (cl & 8) != 0, b2 = (cl & 4) != 0, b1 = (cl & 2) != 0;
+#pragma unroll
+  for (int i = 0; i < RB / 2; ++i) {
+    const double keep = b3 ? v[RB / 2 + i] : v[i], send = b3 ? v[i] : v[RB / 2 + i];
+    h[i] = keep + dpp_fetch<DPP_MIRROR16>(send);
+  }
+  double q[RB / 4];
+#pragma unroll
+  for (int i = 0; i < RB / 4; ++i) {
+    const double keep = b2 ? h[RB / 4 + i] : h[i], send = b2 ? h[i] : h[RB / 4 + i];
+    q[i] = keep + dpp_fetch<DPP_MIRROR8>(send);
+  }
+  double x = q[0];
+  if (RB == 8) {
+    const double keep = b1 ? q[RB / 4 - 1] : q[0], send = b1 ? q[0] : q[RB / 4 - 1];
+    x = keep + dpp_fetch<DPP_XOR2>(send);
+  } else {
+    x += dpp_fetch<DPP_XOR2>(x);
+  }
+  return x + dpp_fetch<DPP_XOR1>(x);
+}
+
+// f(BlockIndex<0>()), ..., f(BlockIndex<COUNT - 1>()): a loop whose index is a constant in the body
+template <int I> struct BlockIndex { static constexpr int value = I; };
+template <int COUNT, int I = 0, typename F> __device__ __forceinline__ void for_each_block(F &&f) {
+  if constexpr (I < COUNT) { f(BlockIndex<I>()); for_each_block<COUNT, I + 1>(f); }
+}
+
+// All pivots of T - sigma positive, i.e. sigma < lambda_min
+__device__ __forceinline__ bool tri_above(const double *d, const double *e, int n, double sigma) {
+  double piv = d[0] - sigma;
+  bool ok = piv > 0.0;
+  for (int i = 1; i < n; ++i) {
+    piv = d[i] - sigma - e[i - 1] * e[i - 1] * rcp_newton(piv);
+    ok = ok && piv > 0.0;
+  }
+  return ok;
+}
+
+template <int N> struct TriShared {
+  double d[N], e[N], v1[N];                  // T; the eigenvector handled by itself
+  double beta[N];                            // reflector k: 2 / v.v, or 0 where there is none
+  union {
+    struct {
+      union {
+        struct { double x[3][N], p[2][N]; } step;             // vectors of the current reflection
+        struct { double slot[N * RAT_MAX_POLES]; float chunk[TRI_CHUNK][N]; } fun;
+      };
+      float vs[(N - 1) * (N - 2) / 2];       // reflector k: entries k + 2 .. n - 1 (entry k + 1 is 1)
+    };
+    float out[N][N + 1];
+  };
+  double bound[2];                           // bracket of the smallest eigenvalue
+  int count;
+  unsigned char dec[N];                      // row k is coupled to no other
+};
+
+// N: the largest n; NT threads = 16 lanes along the columns x RG row groups
+template <int N, int NT>
+__global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const SmallRootArgs g, const RatTable table) {
+  constexpr int RG = NT / 16, RB = N / RG, CB = N / 16;
+  constexpr int PQ = RAT_MAX_POLES / 2, PQ_STEP = 6;      // two lanes share a row of F: poles per lane, taken 6 at a time
+  static_assert(NT == 2 * N && PQ % PQ_STEP == 0, "two lanes per row");
+  if (g.only && g.only[blockIdx.x] == 0) return;
+  __shared__ __align__(16) TriShared<N> sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & 15, rg = tid >> 4;
+  const int b = blockIdx.x, n = g.n;
+  const float *a = g.a + (int64_t)b * g.a_stride;
+
+  // ---- load (symmetrised), find what is not finite and the rows that stand alone ----
+  double A[RB][CB];
+  int bad = 0;
+  for (int i = wave; i < n; i += NT / 64)
+    for (int j = lane; j < n; j += 64) {
+      const float v = a[(int64_t)i * n + j];
+      if (!(fabsf(v) <= 3.0e38f)) bad = 1;
+      sh.out[i][j] = v;
+    }
+  for (int i = tid; i < N; i += NT) sh.dec[i] = 1;
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < RB; ++p) {
+    const int r = rg + RG * p, ri = min(r, n - 1);
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+      const int c = cl + 16 * q, ci = min(c, n - 1);
+      const double v = (double)g.scale * (0.5 * ((double)sh.out[ri][ci] + (double)sh.out[ci][ri]));
+      A[p][q] = (r < n && c < n) ? v : 0.0;
+      any = any || (r != c && A[p][q] != 0.0);
+    }
+    if (any) sh.dec[r] = 0;
+  }
+  bad = __syncthreads_or(bad);
+  if (bad) {   // Sec. 3.2.3: keep the previous root
+    if (tid == 0) {
+      if (g.failed) g.failed[b] = 1;
+      if (g.fail_count) atomicAdd(g.fail_count, 1ull);
+    }
+    return;
+  }
+  // A row that is coupled to no other is an eigenvector by itself: its entry of the result is f of
+  // its diagonal entry, and it takes part in the reduction with a diagonal entry from inside the
+  // spectrum of the rest, where it changes neither end of it.
+#pragma unroll
+  for (int p = 0; p < RB; ++p)
+#pragma unroll
+    for (int q = 0; q < CB; ++q)
+      if (rg + RG * p == cl + 16 * q) sh.step.x[0][rg + RG * p] = A[p][q];
+  __syncthreads();
+  double dec_min = 1.0e300, fill = -1.0e300;
+  for (int i = lane; i < n; i += 64) {
+    const double v = sh.step.x[0][i];
+    if (sh.dec[i]) dec_min = fmin(dec_min, v); else fill = fmax(fill, v);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { dec_min = fmin(dec_min, __shfl_xor(dec_min, off, 64)); fill = fmax(fill, __shfl_xor(fill, off, 64)); }
+  const bool coupled = fill > -1.0e300;
+  if (!coupled) fill = 1.0;
+#pragma unroll
+  for (int p = 0; p < RB; ++p)
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+      const int r = rg + RG * p, c = cl + 16 * q;
+      if (r == c && r < n && sh.dec[r]) A[p][q] = fill;
+    }
+  __syncthreads();
+
+  // ---- reduction ----
+  auto offs = [n](int k) { return k * (n - 2) - k * (k - 1) / 2 - (k + 2); };   // entry i of reflector k: vs[offs(k) + i]
+  // Columns 16 KQ .. 16 KQ + 15: the blocks left of and above them are finished and drop out of the
+  // code (the whole similarity transform is applied to the others: what it does to finished rows and
+  // columns inside them is to turn them into T).
+  auto reduce16 = [&](auto kq) {
+    constexpr int KQ = decltype(kq)::value, P0 = 16 * KQ / RG, P1 = 16 * KQ / RG + 16 / RG;   // row blocks P0 .. P1 - 1: rows 16 KQ .. 16 KQ + 15
+    for (int k = 16 * KQ; k < min(16 * KQ + 16, n - 1); ++k) {
+      double *xb = sh.step.x[k & 1], *pb = sh.step.p[0];
+      if (cl == (k & 15)) {
+#pragma unroll
+        for (int p = P0; p < RB; ++p) {
+          const int r = rg + RG * p;
+          xb[r] = (p >= P1 || r > k) ? A[p][KQ] : 0.0;
+          if (p < P1 && r == k) sh.d[k] = A[p][KQ];
+        }
+      }
+      if (KQ > 0 && (k & 15) < 2) for (int i = tid; i < 16 * KQ; i += NT) xb[i] = 0.0;      // what the blocks before left there
+      __syncthreads();
+      double s2 = 0.0;
+#pragma unroll
+      for (int h = 0; h < (N + 63) / 64; ++h) {
+        const int i = lane + 64 * h;
+        if (N % 64 == 0 || i < N) { const double v = xb[i]; if (i != k + 1) s2 += v * v; }
+      }
+      s2 = wave64_sum(s2);
+      const double x0 = xb[k + 1];
+      if (!(s2 > 0.0)) {       // nothing to reflect
+        if (tid == 0) { sh.beta[k] = 0.0; sh.e[k] = x0; }
+        for (int i = tid; i < n; i += NT) if (i > k + 1) sh.vs[offs(k) + i] = 0.f;
+        continue;
+      }
+      const double nn = x0 * x0 + s2, norm = nn * rsqrt_newton(nn);
+      const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, beta = rcp_newton(norm * fabs(v0));
+      double vc[CB], part[RB];
+#pragma unroll
+      for (int p = P0; p < RB; ++p) part[p] = 0.0;
+#pragma unroll
+      for (int q = KQ; q < CB; ++q) {
+        vc[q] = xb[cl + 16 * q];
+        if (q < KQ + 2 && cl + 16 * q == k + 1) vc[q] = v0;
+#pragma unroll
+        for (int p = P0; p < RB; ++p) part[p] += A[p][q] * vc[q];
+      }
+#pragma unroll
+      for (int p = 0; p < P0; ++p) part[p] = 0.0;
+      pb[rg + RG * row16_slot<RB>(cl)] = beta * row16_sums<RB>(part, cl);
+      {
+        const double inv = rcp_newton(v0);
+        if (tid == 0) { sh.beta[k] = beta * v0 * v0; sh.e[k] = alpha; }
+        for (int i = tid; i < n; i += NT) if (i > k + 1) sh.vs[offs(k) + i] = (float)(xb[i] * inv);
+      }
+      __syncthreads();
+      double vp = 0.0;
+#pragma unroll
+      for (int h = 0; h < (N + 63) / 64; ++h) {
+        const int i = lane + 64 * h;
+        if (N % 64 == 0 || i < N) vp += (i == k + 1 ? v0 : xb[i]) * pb[i];
+      }
+      const double K = 0.5 * beta * wave64_sum(vp);
+      double vr[RB], qr[RB];
+#pragma unroll
+      for (int p = P0; p < RB; ++p) {
+        vr[p] = xb[rg + RG * p];
+        if (p < P1 + 16 / RG && rg + RG * p == k + 1) vr[p] = v0;
+        qr[p] = pb[rg + RG * p] - K * vr[p];
+      }
+#pragma unroll
+      for (int q = KQ; q < CB; ++q) {
+        const double qc = pb[cl + 16 * q] - K * vc[q];
+#pragma unroll
+        for (int p = P0; p < RB; ++p) A[p][q] -= vr[p] * qc + qr[p] * vc[q];
+      }
+    }
+  };
+  for_each_block<CB>(reduce16);
+#pragma unroll
+  for (int p = 0; p < RB; ++p)
+#pragma unroll
+    for (int q = 0; q < CB; ++q)
+      if (rg + RG * p == n - 1 && cl + 16 * q == n - 1) sh.d[n - 1] = A[p][q];
+  __syncthreads();
+
+  // ---- bounds of the spectrum, smallest eigenvalue ----
+  const double eps = (double)g.epsilon, r_exp = (double)g.r;
+  double hi = -1.0e300, amax = 0.0;
+  for (int i = lane; i < n; i += 64) {
+    const double off = (i > 0 ? fabs(sh.e[i - 1]) : 0.0) + (i < n - 1 ? fabs(sh.e[i]) : 0.0);
+    hi = fmax(hi, sh.d[i] + off);
+    amax = fmax(amax, fabs(sh.d[i]) + off);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { hi = fmax(hi, __shfl_xor(hi, off, 64)); amax = fmax(amax, __shfl_xor(amax, off, 64)); }
+  if (wave == 0) {
+    // a ladder of shifts, one per lane: 0, amax 2^-48 ... amax 2^-1, and downwards -2 amax 2^-56 ... -2 amax
+    const double sigma = lane == 0 ? 0.0 : lane <= 48 ? ldexp(amax, lane - 49) : -2.0 * ldexp(amax, 4 * (lane - 63));
+    const unsigned long long up = __ballot(tri_above(sh.d, sh.e, n, sigma));
+    const int cnt = __popcll(up & ((1ull << 49) - 1));
+    if (lane == 0) {
+      double lo_b, hi_b;
+      if (cnt > 0) {
+        lo_b = cnt == 1 ? 0.0 : ldexp(amax, cnt - 1 - 49);
+        hi_b = cnt == 49 ? hi : ldexp(amax, cnt - 49);
+      } else {
+        int l = 49;
+        while (l < 63 && !((up >> l) & 1)) ++l;
+        lo_b = -2.0 * ldexp(amax, 4 * (l - 63));
+        hi_b = l == 49 ? 0.0 : -2.0 * ldexp(amax, 4 * (l - 1 - 63));
+      }
+      sh.bound[0] = lo_b; sh.bound[1] = hi_b; sh.count = cnt;
+    }
+  }
+  __syncthreads();
+  double lam = sh.bound[0], lam_up = sh.bound[1];
+  const bool deflate = coupled && (sh.count == 0 || lam + eps < TRI_DEFLATE_BELOW * (hi + eps));
+  if (deflate) {
+    for (int round = 0; round < 12 && lam_up - lam > 0x1p-53 * amax; ++round) {
+      const double step = (lam_up - lam) / (NT + 1);
+      const int c = __syncthreads_count(tri_above(sh.d, sh.e, n, lam + step * (tid + 1)));
+      const double base = lam;
+      lam = base + step * c;
+      if (c < NT) lam_up = base + step * (c + 1);
+    }
+  }
+  const double lam_min = coupled ? fmin(lam, dec_min) : dec_min;
+  const double shift = fmin(lam_min, 0.0);
+  // without deflation lam is a lower bound within a factor of two, and only a bound is needed
+  const double f_min = pow((lam_min - shift) + eps, -r_exp);
+  if (!(f_min <= 3.0e38)) {   // not representable: keep the previous root
+    if (tid == 0) {
+      if (g.failed) g.failed[b] = 1;
+      if (g.fail_count) atomicAdd(g.fail_count, 1ull);
+    }
+    return;
+  }
+  if (tid == 0 && g.failed) g.failed[b] = 0;
+  const double base = eps - shift, top = hi + base;
+  double low = fmax(lam + base, TRI_LOWEST * top);
+  const int cls = rat_class(low, top), np = rat_poles(cls);
+  low = ldexp(top, -4 * (cls + 1));
+  double *slot = sh.fun.slot;
+  if (deflate && tid == 0) {
+    // the eigenvector of lam by inverse iteration just below it
+    const double sg = lam - 0x1p-50 * amax;
+    double *piv = slot, *z = sh.v1;
+    double pv = sh.d[0] - sg;
+    piv[0] = 1.0 / pv;
+    for (int i = 1; i < n; ++i) { pv = sh.d[i] - sg - sh.e[i - 1] * sh.e[i - 1] * piv[i - 1]; piv[i] = 1.0 / (pv > 0x1p-60 * amax ? pv : 0x1p-60 * amax); }
+    for (int i = n; i < N; ++i) z[i] = 0.0;
+    for (int i = 0; i < n; ++i) z[i] = 1.0 + 0.25 * (double)((i * 2654435761u) >> 24) * 0x1p-8;
+    for (int it = 0; it < 4; ++it) {
+      double zz = z[0];
+      for (int i = 1; i < n; ++i) { zz = z[i] - sh.e[i - 1] * piv[i - 1] * zz; z[i] = zz; }
+      zz = z[n - 1] * piv[n - 1];
+      z[n - 1] = zz;
+      double s2 = zz * zz;
+      for (int i = n - 2; i >= 0; --i) { zz = piv[i] * (z[i] - sh.e[i] * zz); z[i] = zz; s2 += zz * zz; }
+      const double inv = 1.0 / sqrt(s2);
+      for (int i = 0; i < n; ++i) z[i] *= inv;
+    }
+  }
+  __syncthreads();
+
+  // ---- F = sum_j w_j (T + sigma_j)^-1: pivots from the top, diagonal of the inverse from the bottom ----
+  // slot (i, j): first 1 / pivot, then (-e_i / pivot, w_j G_ii) as float32
+  const int half = ((np + 1) / 2 + PQ_STEP - 1) / PQ_STEP * PQ_STEP;     // poles per lane of a row, the last ones with weight 0
+  if (tid < 2 * half) {
+    const bool real = tid < np;
+    const double sg = real ? base + low * exp(rat_log_pole(cls, tid)) : amax + top;
+    const double wj = real ? table.w[rat_offset(cls) + tid] * pow(low, 1.0 - r_exp) : 0.0;
+    double inv = rcp_newton(sh.d[0] + sg);
+    slot[tid] = inv;
+    for (int i = 1; i < n; ++i) {
+      inv = rcp_newton(sh.d[i] + sg - sh.e[i - 1] * sh.e[i - 1] * inv);
+      slot[i * RAT_MAX_POLES + tid] = inv;
+    }
+    double G = inv, next = n > 1 ? slot[(n - 2) * RAT_MAX_POLES + tid] : 0.0;
+    reinterpret_cast<float2 *>(slot)[(n - 1) * RAT_MAX_POLES + tid] = make_float2(0.f, (float)(wj * G));
+    for (int i = n - 2; i >= 0; --i) {
+      const double pi = next, k = sh.e[i] * pi;
+      if (i > 0) next = slot[(i - 1) * RAT_MAX_POLES + tid];
+      G = pi + k * k * G;
+      reinterpret_cast<float2 *>(slot)[i * RAT_MAX_POLES + tid] = make_float2((float)-k, (float)(wj * G));
+    }
+  }
+  __syncthreads();
+  // d has served: f of the rows that stand alone goes there
+  for (int i = tid; i < n; i += NT)
+    if (sh.dec[i]) sh.d[i] = pow(((double)g.scale * (double)a[(int64_t)i * n + i] - shift) + eps, -r_exp);
+  // Row l of F runs from its diagonal entry to the left: G_{l,i} = -(e_i / pivot_i) G_{l,i+1}, every
+  // pole by itself, two lanes sharing the poles of a row.  A lane's values are zero until its row begins.
+  {
+    const int l = tid >> 1;
+    float val[PQ];
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) val[q] = 0.f;
+    const float4 *sl = reinterpret_cast<const float4 *>(slot + (tid & 1) * half);
+    for (int ch = (n - 1) / TRI_CHUNK; ch >= 0; --ch) {
+      if (32 * wave + 31 >= ch * TRI_CHUNK)      // a wavefront holds 32 rows
+        for (int i = min(n, (ch + 1) * TRI_CHUNK) - 1; i >= ch * TRI_CHUNK; --i) {
+          float acc = 0.f;
+#pragma unroll
+          for (int q0 = 0; q0 < PQ; q0 += PQ_STEP)
+            if (q0 < half) {
+#pragma unroll
+              for (int q = q0; q < q0 + PQ_STEP; q += 2) {
+                const float4 s = sl[i * (RAT_MAX_POLES / 2) + q / 2];
+                val[q] = l == i ? s.y : val[q] * s.x;
+                val[q + 1] = l == i ? s.w : val[q + 1] * s.z;
+                acc += val[q] + val[q + 1];
+              }
+            }
+          acc += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc), DPP_XOR1, 0xf, 0xf, true));
+          if ((tid & 1) == 0) sh.fun.chunk[i - ch * TRI_CHUNK][l] = acc;
+        }
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < RB; ++p)
+#pragma unroll
+        for (int q = 0; q < CB; ++q)
+          if (min(RG * p / 16, q) == ch) {       // all of its rows and columns lie in one 16 x 16 block
+            const int r = rg + RG * p, c = cl + 16 * q, mn = min(r, c), mx = max(r, c);
+            A[p][q] = mx < n ? (double)sh.fun.chunk[mn % TRI_CHUNK][mx] : 0.0;
+          }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int p = 0; p < RB; ++p)
+#pragma unroll
+      for (int q = 0; q < CB; ++q)
+        if (rg + RG * p >= n || cl + 16 * q >= n) A[p][q] = 0.0;
+  }
+
+  // ---- F <- F - v q^T - q v^T with p = beta F v, q = p - (beta v.p + add) / 2 v ----
+  // beta = 2 / v.v, add = 0: the reflection H F H;  |v| = 1, beta = 1, add = f: the part of F along
+  // v is replaced by f.  v (in xb): zero below index k0.
+  // v of the next reflection is put in place on the way (three buffers: a wavefront may be one step ahead).
+  auto place = [&](double *xb, int k) {
+    const float *v = sh.vs + offs(k);
+    for (int i = tid; i < N; i += NT) xb[i] = i == k + 1 ? 1.0 : (i > k + 1 && i < n) ? (double)v[i] : 0.0;
+  };
+  // KQ: v is zero in front of element 16 KQ.
+  auto rank2 = [&](auto kq, const double *xb, double *pb, double beta, double add, double *xnext, int knext) {
+    constexpr int KQ = decltype(kq)::value, P0 = 16 * KQ / RG;
+    double vc[CB], part[RB];
+#pragma unroll
+    for (int p = 0; p < RB; ++p) part[p] = 0.0;
+#pragma unroll
+    for (int q = KQ; q < CB; ++q) {
+      vc[q] = xb[cl + 16 * q];
+#pragma unroll
+      for (int p = 0; p < RB; ++p) part[p] += A[p][q] * vc[q];
+    }
+    pb[rg + RG * row16_slot<RB>(cl)] = beta * row16_sums<RB>(part, cl);
+    if (knext >= 0) place(xnext, knext);
+    __syncthreads();
+    double vp = 0.0;
+#pragma unroll
+    for (int h = 0; h < (N + 63) / 64; ++h) {
+      const int i = lane + 64 * h;
+      if (N % 64 == 0 || i < N) vp += xb[i] * pb[i];
+    }
+    const double K = 0.5 * (beta * wave64_sum(vp) + add);
+    double vr[RB], qr[RB];
+#pragma unroll
+    for (int p = 0; p < RB; ++p) {
+      vr[p] = p >= P0 ? xb[rg + RG * p] : 0.0;
+      qr[p] = p >= P0 ? pb[rg + RG * p] - K * vr[p] : pb[rg + RG * p];
+    }
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+      const double qc = q >= KQ ? pb[cl + 16 * q] - K * vc[q] : pb[cl + 16 * q];
+#pragma unroll
+      for (int p = 0; p < RB; ++p) {
+        if (q >= KQ && p >= P0) A[p][q] -= vr[p] * qc + qr[p] * vc[q];
+        else if (q >= KQ) A[p][q] -= qr[p] * vc[q];
+        else if (p >= P0) A[p][q] -= vr[p] * qc;
+      }
+    }
+  };
+  int turn = 0;
+  if (n > 2) place(sh.step.x[0], n - 3);
+  if (deflate) rank2(BlockIndex<0>(), sh.v1, sh.step.p[1], 1.0, pow((lam - shift) + eps, -r_exp), nullptr, -1);
+  __syncthreads();
+  for_each_block<CB>([&](auto rev) {
+    constexpr int KQ = CB - 1 - decltype(rev)::value;
+    for (int k = min(n - 3, 16 * KQ + 14); k >= max(0, 16 * KQ - 1); --k) {       // k + 1 in 16 KQ .. 16 KQ + 15
+      const int nxt = turn == 2 ? 0 : turn + 1;
+      rank2(BlockIndex<KQ>(), sh.step.x[turn], sh.step.p[k & 1], sh.beta[k], 0.0, sh.step.x[nxt], k - 1);
+      turn = nxt;
+    }
+  });
+  __syncthreads();
+
+  // ---- out: the lower triangle and its mirror image carry the same bits ----
+#pragma unroll
+  for (int p = 0; p < RB; ++p)
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+      const int r = rg + RG * p, c = cl + 16 * q;
+      if (r < n && c <= r) {
+        double v = A[p][q];
+        if (sh.dec[r] || sh.dec[c]) v = r == c ? sh.d[r] : 0.0;
+        sh.out[r][c] = (float)v;
+      }
+    }
+  __syncthreads();
+  float *x = g.x + (int64_t)b * g.x_stride;
+  for (int i = wave; i < n; i += NT / 64)
+    for (int j = lane; j < n; j += 64) x[(int64_t)i * n + j] = i >= j ? sh.out[i][j] : sh.out[j][i];
+}
+
+}  // namespace shampoo

@@ -23,6 +23,7 @@
 #include "gemm_f16x2.h"
 #include "gemm_mfma.h"
 #include "newton_root.h"
+#include "root_tridiag.h"
 #include "syrk_bf16.h"
 #include "tensor_blocks.h"
 
@@ -656,6 +657,15 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
     g.x = x; g.x_stride = (int64_t)n * n;
     g.lambda = lambda; g.failed = failed_user; g.fail_count = fail_count;
     g.n = n; g.epsilon = eps; g.r = r; g.scale = scale; g.only = only;
+    // without eigenvectors where nobody asks for eigenvalues and the exponent has a rational fit
+    RatTable table;
+    if (!lambda && rat_table(r, table)) {
+      if (n <= 32) hipLaunchKernelGGL((rootinv_tridiag_kernel<32, 64>), dim3(batch), dim3(64), 0, s, g, table);
+      else if (n <= 64) hipLaunchKernelGGL((rootinv_tridiag_kernel<64, 128>), dim3(batch), dim3(128), 0, s, g, table);
+      else hipLaunchKernelGGL((rootinv_tridiag_kernel<128, 256>), dim3(batch), dim3(256), 0, s, g, table);
+      HIP_TRY(hipGetLastError());
+      return SHAMPOO_OK;
+    }
     const size_t lds = rootinv_small_lds_bytes(n);
     if (n <= 64) {
       HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(rootinv_small_kernel<256>),
