@@ -1,0 +1,1022 @@
+// Root inverse of matrices of 128 < n <= 2048 without eigenvectors, batched.
+//
+//   A = Q B Q^T       blocked Householder reduction to a symmetric band matrix B of 32-wide blocks, in
+//                     float64 on the fp64 matrix cores: per panel a QR factorisation (one workgroup per
+//                     matrix, panel in registers), Z = W V, Y = Z T - V (T^T V^T Z T) / 2 and
+//                     W <- W - V Y^T - Y V^T
+//   F = f(B)          f(x) = (x - min(lambda_min, 0) + eps)^-r as a sum of inverses of B + sigma_j
+//                     (root_rational.h).  B is block tridiagonal, so an inverse is one elimination along
+//                     the blocks (a wavefront per matrix and shift), and every block row of it runs from
+//                     its diagonal block to the left by one 32 x 32 product per block
+//   X = Q F Q^T       the same reflectors from both sides, last panel first, float32 matrix cores
+//
+// The block Jacobi solver (eigh_jacobi.h) needs 10 ... 13 sweeps of 6 n^3 multiply-adds for the
+// eigenvectors; this takes about 2 n^3 for the reduction, 1 n^3 for F and 2 n^3 on the way back, and
+// nothing in it iterates except the bisection of a negative or tiny smallest eigenvalue.  Jacobi
+// still serves callers that want eigenvalues or keep eigenvectors between calls, larger matrices, and
+// exponents without a rational fit.
+//
+// Accuracy: the reduction is backward stable in float64 (eigenvalues move by 1e-16 of the largest, as
+// in the float64 sweeps), the inverses are float64; F, the reflectors of the way back and its products
+// are float32, like the accumulated rotations and the reconstruction of the Jacobi path.
+//
+// Layouts of v_mfma_f64_16x16x4_f64: lane l supplies A(l % 16, l / 16) and B(l / 16, l % 16), element v
+// of the result is D(l / 16 + 4 v, l % 16); v_mfma_f32_16x16x4_f32: the same operands, D(4 (l / 16) + v,
+// l % 16).  The order of k inside a sum is free, so a result can be the B operand of the next product as
+// it stands (step v takes the rows that element v holds), and a symmetric one the A operand too.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "root_rational.h"
+#include "root_tridiag.h"
+
+namespace shampoo {
+
+constexpr int BAND = 32;                 // block size: half bandwidth of B
+constexpr int BAND_MAX_N = 2048;
+constexpr int BAND_SHIFTS = 32;          // shifts tried per round of the bisection
+constexpr int BAND_ROUNDS = 12;          // 33^11 covers 2^53
+constexpr int BAND_ROWS = 128;           // rows per workgroup of the panel products
+constexpr int BAND_COLS = 128;           // columns per workgroup of the rank-64 update
+
+typedef double band_d4 __attribute__((ext_vector_type(4)));
+typedef float band_f4 __attribute__((ext_vector_type(4)));
+
+struct BandMeta {
+  double dec_min, hi, amax;              // smallest diagonal entry of the rows that stand alone; bounds of the spectrum of B
+  double lo[2], up[2];                   // bracket of the smallest eigenvalue of B, by parity of the round
+  double base, low, shift, f1, lam;      // eps - shift; lower end of the rational sum's range; min(lambda_min, 0); f(lam); lambda_min of B
+  int32_t skip;                          // 0: go on; 1: failed; 2: not asked for
+  int32_t coupled, cls, poles, deflate;
+  int32_t active[2];                     // bisection still running, by parity of the round
+};
+
+struct BandArgs {
+  const float *a; int32_t n, np, nb;     // input [n][n]; padded size, number of blocks
+  float eps, r, scale;
+  float *x; int32_t *failed_user; unsigned long long *fail_count; const int32_t *only;
+  BandMeta *meta;
+  double *w;        // [np][np]: the matrix being reduced
+  float *f;         // [np][np], in the memory of w: F, then X
+  double *vp, *z, *y, *t, *part;         // current panel: V, Z, Y [np][32], T [32][32], partial sums of V^T Z [np / 128][32][32]
+  float *zf, *yf, *partf;                // the same arrays on the way back
+  float *vall, *tall;                    // all panels: V [nb - 1][np][32], T [nb - 1][32][32]
+  double *dblk, *cblk;                   // B: diagonal blocks [nb][32][32], transposed sub-diagonal blocks [nb][32][32]
+  double *kf, *gf;                       // per pole and block: -K^T (A operand order) and weight * G (D order), [36][nb][1024]
+  double *v1;                            // [np]: eigenvector handled by itself
+  int32_t *ok;                           // [2][BAND_SHIFTS]: verdicts of the bisection, by parity of the round
+  int32_t *dec;                          // [np]: row is coupled to no other
+};
+// from the arrays of matrix 0 of the batch to those of matrix b (failed_user and only stay: they are indexed)
+__host__ __device__ inline void band_select(BandArgs &g, int b) {
+  const int64_t np = g.np, nb = g.nb;
+  g.a += (int64_t)b * g.n * g.n; g.x += (int64_t)b * g.n * g.n;
+  g.meta += b;
+  g.w += b * np * np; g.f += b * np * np * 2;
+  g.vp += b * np * BAND; g.z += b * np * BAND; g.y += b * np * BAND; g.t += (int64_t)b * 1024;
+  const int64_t parts = (np + BAND_ROWS - 1) / BAND_ROWS;
+  g.part += b * parts * 1024;
+  g.zf += b * np * BAND * 2; g.yf += b * np * BAND * 2; g.partf += b * parts * 2048;
+  g.vall += b * np * np; g.tall += b * nb * 1024;
+  g.dblk += b * nb * 1024; g.cblk += b * nb * 1024;
+  g.kf += b * nb * 1024 * RAT_MAX_POLES; g.gf += b * nb * 1024 * RAT_MAX_POLES;
+  g.v1 += b * np; g.ok += b * 2 * BAND_SHIFTS; g.dec += b * np;
+}
+
+__device__ __forceinline__ band_d4 band_mfma(double a, double b, band_d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ band_f4 band_mfma(float a, float b, band_f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+template <typename T> struct BandVec;
+template <> struct BandVec<double> { typedef band_d4 type; static __device__ __forceinline__ int row(int lg, int v) { return lg + 4 * v; } };
+template <> struct BandVec<float> { typedef band_f4 type; static __device__ __forceinline__ int row(int lg, int v) { return 4 * lg + v; } };
+
+// ---------------------------------------------------------------------------
+// W = pad(sym(scale A)); which rows stand alone.  grid (np / 32, batch), 256 threads
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void band_init_kernel(BandArgs g) {
+  __shared__ float Xs[BAND][BAND + 1], Ys[BAND][BAND + 1];
+  __shared__ int coupled[BAND];
+  const int b = blockIdx.y, br = blockIdx.x, tid = threadIdx.x, r = tid >> 3, c4 = (tid & 7) * 4;
+  const int32_t *only = g.only;
+  band_select(g, b);
+  if (only && only[b] == 0) {
+    if (br == 0 && tid == 0) g.meta->skip = 2;
+    return;
+  }
+  const int n = g.n, np = g.np;
+  if (tid < BAND) coupled[tid] = 0;
+  const int gi = br * BAND + r;
+  int bad = 0, any = 0;
+  for (int bc = 0; bc < g.nb; ++bc) {
+    const int yi = bc * BAND + r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int xj = bc * BAND + c4 + e, yj = br * BAND + c4 + e;
+      const float x = (gi < n && xj < n) ? g.a[(int64_t)gi * n + xj] : 0.f;
+      const float y = (yi < n && yj < n) ? g.a[(int64_t)yi * n + yj] : 0.f;
+      if (!(fabsf(x) <= 3.0e38f)) bad = 1;
+      Xs[r][c4 + e] = x;
+      Ys[r][c4 + e] = y;
+    }
+    __syncthreads();
+    double v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (double)g.scale * (0.5 * ((double)Xs[r][c4 + e] + (double)Ys[c4 + e][r]));
+      if (gi != bc * BAND + c4 + e && v[e] != 0.0) any = 1;
+    }
+    double2 *dst = reinterpret_cast<double2 *>(g.w + (int64_t)gi * np + bc * BAND + c4);
+    dst[0] = make_double2(v[0], v[1]); dst[1] = make_double2(v[2], v[3]);
+    __syncthreads();
+  }
+  if (any) coupled[r] = 1;
+  if (bad) g.meta->skip = 1;
+  __syncthreads();
+  if (tid < BAND) g.dec[br * BAND + tid] = coupled[tid] ? 0 : 1;
+}
+
+// A row that is coupled to no other is an eigenvector by itself: its entry of the result is f of its
+// diagonal entry.  It goes through the reduction, like the padding, with a diagonal entry from inside
+// the spectrum of the rest.  grid (batch), 256 threads
+__global__ __launch_bounds__(256) void band_alone_kernel(BandArgs g) {
+  __shared__ double red[2][4];
+  band_select(g, blockIdx.x);
+  if (g.meta->skip) return;
+  const int tid = threadIdx.x, n = g.n, np = g.np;
+  double dmin = 1.0e300, fill = -1.0e300;
+  for (int i = tid; i < n; i += 256) {
+    const double v = g.w[(int64_t)i * np + i];
+    if (g.dec[i]) dmin = fmin(dmin, v); else fill = fmax(fill, v);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { dmin = fmin(dmin, __shfl_xor(dmin, off, 64)); fill = fmax(fill, __shfl_xor(fill, off, 64)); }
+  if ((tid & 63) == 0) { red[0][tid >> 6] = dmin; red[1][tid >> 6] = fill; }
+  __syncthreads();
+  dmin = fmin(fmin(red[0][0], red[0][1]), fmin(red[0][2], red[0][3]));
+  fill = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
+  const bool coupled = fill > -1.0e300;
+  if (!coupled) fill = 1.0;
+  for (int i = tid; i < np; i += 256)
+    if (i >= n || g.dec[i]) g.w[(int64_t)i * np + i] = fill;
+  if (tid == 0) { g.meta->dec_min = dmin; g.meta->coupled = coupled ? 1 : 0; }
+}
+
+// ---------------------------------------------------------------------------
+// QR of panel k (rows 32 (k + 1) ... np - 1 of columns 32 k ... 32 k + 31): V, T, R; and D_k as it now is.
+// One workgroup of 16 wavefronts per matrix, 16 columns at a time: lane (c = l % 16, ph = l / 16) of
+// wavefront w holds rows 4 (16 t + w) + ph of column c, t < TT, so that the entry of the pivot column of
+// a row reaches the row's 16 columns by a DPP broadcast, and the entries are MFMA operands as they lie.
+// Per column one barrier; bound by the vector instructions of the two passes over the registers
+// (about 9 per register), i.e. by the one CU that a matrix has here: 30 us for a panel of 1024 rows.
+// The other matrices of the batch run beside it, other sub-chunks' products too.
+// ---------------------------------------------------------------------------
+template <int J> __device__ __forceinline__ double row16_bcast(double x) { return dpp_fetch<0x150 + J>(x); }
+
+struct BandQrShared {
+  double red[2][16][16], prow[2][16], tau[BAND];
+  double big[16][256];                   // one 16 x 16 tile per wavefront
+  double s[16][17], t[2][16][17], g01[16][17];
+};
+
+template <int TT>
+__global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) {
+  __shared__ BandQrShared sh;
+  band_select(g, blockIdx.x);
+  if (g.meta->skip) return;
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, ph = lane >> 4;
+  const int r0 = (k + 1) * BAND, m = np - r0;
+  g.dblk[(int64_t)k * 1024 + tid] = g.w[(int64_t)(k * BAND + (tid >> 5)) * np + k * BAND + (tid & 31)];
+  if (m <= 0) return;
+  const int tt = (m + 63) / 64;
+  const int rel0 = 4 * w + ph;           // row of register t: rel0 + 64 t
+  double *vp = g.vp + (int64_t)r0 * BAND;
+  float *va = g.vall + ((int64_t)k * np + r0) * BAND;
+  double P[TT];
+  int buf = 0;
+
+  // sum over the wavefronts of a 16 x 16 tile held as MFMA results: to sum[i][j]
+  auto tile_sum = [&](band_d4 acc, double (*sum)[17]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sh.big[w][(ph + 4 * v) * 16 + c] = acc[v];
+    __syncthreads();
+    if (tid < 256) {
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s += sh.big[i][tid];
+      sum[tid >> 4][tid & 15] = s;
+    }
+    __syncthreads();
+  };
+
+  for (int h = 0; h < 2; ++h) {
+    {
+      const double *src = g.w + (int64_t)r0 * np + k * BAND + 16 * h + c;
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        P[t] = 0.0;
+        if (t < tt) { const int rel = rel0 + 64 * t; if (rel < m) P[t] = src[(int64_t)rel * np]; }
+      }
+    }
+    if (h == 1) {                        // the reflectors of the first 16 columns:  C <- C - V0 (T0^T V0^T C)
+      band_d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+        if (t < tt) {
+          const int rel = rel0 + 64 * t;
+          acc = band_mfma(rel < m ? vp[(int64_t)rel * BAND + c] : 0.0, P[t], acc);
+        }
+      tile_sum(acc, sh.s);
+      double e = 0.0;
+      if (tid < 256) for (int l = 0; l <= (tid >> 4); ++l) e += sh.t[0][l][tid >> 4] * sh.s[l][tid & 15];
+      __syncthreads();
+      if (tid < 256) sh.s[tid >> 4][tid & 15] = e;
+      __syncthreads();
+      double sw[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sw[i] = sh.s[i][c];
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+        if (t < tt) {
+          const int rel = rel0 + 64 * t;
+          const double v = rel < m ? vp[(int64_t)rel * BAND + c] : 0.0;
+          double p = P[t];
+          for_each_block<16>([&](auto i) { p -= row16_bcast<decltype(i)::value>(v) * sw[decltype(i)::value]; });
+          P[t] = p;
+        }
+    }
+    for_each_block<16>([&](auto jj) {
+      constexpr int J = decltype(jj)::value;
+      const int pr = 16 * h + J;         // pivot row
+      double dot = 0.0;
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+        if (t < tt) {
+          double x = row16_bcast<J>(P[t]);
+          if (t == 0) x = rel0 > pr ? x : 0.0;
+          dot += x * P[t];
+        }
+      dot += __shfl_xor(dot, 16, 64);
+      dot += __shfl_xor(dot, 32, 64);
+      if (lane < 16) sh.red[buf][w][c] = dot;
+      if (rel0 == pr) sh.prow[buf][c] = P[0];
+      __syncthreads();
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s += sh.red[buf][i][c];
+      const double sj = row16_bcast<J>(s), x0 = sh.prow[buf][J], pc = sh.prow[buf][c];
+      buf ^= 1;
+      double tau = 0.0;
+      if (sj > 0.0) {
+        const double nn = sj + x0 * x0, rn = rsqrt_newton(nn), norm = nn * rn;
+        const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, inv = rcp_newton(v0);
+        tau = fabs(v0) * rn;
+        const double wc = c > J ? tau * (s * inv + pc) : 0.0;
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+          if (t < tt) {
+            double v = row16_bcast<J>(P[t]) * inv;
+            if (t == 0) v = rel0 > pr ? v : rel0 == pr ? 1.0 : 0.0;
+            const double p = P[t] - v * wc;
+            if (t == 0) P[t] = c != J ? p : rel0 > pr ? v : rel0 == pr ? alpha : P[t];
+            else P[t] = c != J ? p : v;
+          }
+      }
+      if (tid == 0) sh.tau[pr] = tau;
+    });
+    // R (rows up to the pivot's) and V out; what is left in P is V
+    if (rel0 < BAND) g.cblk[(int64_t)k * 1024 + (16 * h + c) * BAND + rel0] = rel0 <= 16 * h + c ? P[0] : 0.0;
+    P[0] = rel0 > 16 * h + c ? P[0] : rel0 == 16 * h + c ? 1.0 : 0.0;
+    band_d4 acc = {0.0, 0.0, 0.0, 0.0}, acc01 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+      if (t < tt) {
+        const int rel = rel0 + 64 * t;
+        if (h == 1) acc01 = band_mfma(rel < m ? vp[(int64_t)rel * BAND + c] : 0.0, P[t], acc01);
+        acc = band_mfma(P[t], P[t], acc);
+        if (rel < m) {
+          vp[(int64_t)rel * BAND + 16 * h + c] = P[t];
+          va[(int64_t)rel * BAND + 16 * h + c] = (float)P[t];
+        }
+      }
+    tile_sum(acc, sh.s);
+    // T of these 16 columns: T[i][j] = -tau_j sum_{i <= l < j} T[i][l] (v_l . v_j); lane i holds row i
+    if (w == 0) {
+      double T[16];
+      for_each_block<16>([&](auto jc) {
+        constexpr int J = decltype(jc)::value;
+        const double tj = sh.tau[16 * h + J];
+        double e = 0.0;
+#pragma unroll
+        for (int l = 0; l < J; ++l) e += T[l] * sh.s[l][J];
+        T[J] = c == J ? tj : c < J ? -tj * e : 0.0;
+      });
+      if (lane < 16) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sh.t[h][c][j] = T[j];
+      }
+    }
+    __syncthreads();
+    if (h == 1) tile_sum(acc01, sh.g01);
+  }
+  // T = [T0, -T0 (V0^T V1) T1; 0, T1]
+  double e = 0.0;
+  const int i = tid >> 4, j = tid & 15;
+  if (tid < 256) for (int l = 0; l <= j; ++l) e += sh.g01[i][l] * sh.t[1][l][j];
+  __syncthreads();
+  if (tid < 256) sh.s[i][j] = e;
+  __syncthreads();
+  if (tid < 256) {
+    e = 0.0;
+    for (int l = i; l < 16; ++l) e -= sh.t[0][i][l] * sh.s[l][j];
+    double *t = g.t;
+    float *ta = g.tall + (int64_t)k * 1024;
+    auto put = [&](int row, int col, double v) { t[row * BAND + col] = v; ta[row * BAND + col] = (float)v; };
+    put(i, j, sh.t[0][i][j]); put(i, 16 + j, e); put(16 + i, j, 0.0); put(16 + i, 16 + j, sh.t[1][i][j]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The panel products of both directions.  T = double: the reduction, W22 <- H^T W22 H with
+// H = I - V T V^T on rows and columns r0 ... np - 1.  T = float: the way back, F <- H F H^T, where the
+// rows in front of r0 take part in the columns behind it.
+// ---------------------------------------------------------------------------
+template <typename T> struct BandPanel { T *w; const T *v; T *z, *y, *part; const T *t; int row0, r0; };
+template <typename T> __device__ __forceinline__ BandPanel<T> band_panel(const BandArgs &g, int k);
+template <> __device__ __forceinline__ BandPanel<double> band_panel<double>(const BandArgs &g, int k) {
+  return {g.w, g.vp, g.z, g.y, g.part, g.t, (k + 1) * BAND, (k + 1) * BAND};
+}
+template <> __device__ __forceinline__ BandPanel<float> band_panel<float>(const BandArgs &g, int k) {
+  return {g.f, g.vall + (int64_t)k * g.np * BAND, g.zf, g.yf, g.partf, g.tall + (int64_t)k * 1024, 0, (k + 1) * BAND};
+}
+
+// Z = W[:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
+// grid (ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows.  Memory bound (every element of W is
+// read once for 64 multiply-adds); a lane reads 4 consecutive k of its row.
+template <typename T>
+__global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
+  typedef typename BandVec<T>::type V4;
+  __shared__ T red[4][1024];
+  band_select(g, blockIdx.y);
+  if (g.meta->skip) return;
+  const BandPanel<T> p = band_panel<T>(g, k);
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
+  V4 m1[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) m1[i][j] = (V4){0, 0, 0, 0};
+  if (base < np) {
+    V4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = (V4){0, 0, 0, 0};
+    const T *wr[2] = {p.w + (int64_t)(base + li) * np + 4 * lg, p.w + (int64_t)(base + 16 + li) * np + 4 * lg};
+    const T *vr = p.v + (int64_t)(4 * lg) * BAND + li;
+#pragma unroll 2
+    for (int k0 = p.r0; k0 < np; k0 += 16) {
+      const V4 a0 = *reinterpret_cast<const V4 *>(wr[0] + k0), a1 = *reinterpret_cast<const V4 *>(wr[1] + k0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const T b0 = vr[(int64_t)(k0 + q) * BAND], b1 = vr[(int64_t)(k0 + q) * BAND + 16];
+        acc[0][0] = band_mfma(a0[q], b0, acc[0][0]); acc[0][1] = band_mfma(a0[q], b1, acc[0][1]);
+        acc[1][0] = band_mfma(a1[q], b0, acc[1][0]); acc[1][1] = band_mfma(a1[q], b1, acc[1][1]);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = base + 16 * rt + BandVec<T>::row(lg, v);
+        p.z[(int64_t)row * BAND + li] = acc[rt][0][v];
+        p.z[(int64_t)row * BAND + 16 + li] = acc[rt][1][v];
+        if (base >= p.r0) {
+          const T v0 = p.v[(int64_t)row * BAND + li], v1 = p.v[(int64_t)row * BAND + 16 + li];
+          m1[0][0] = band_mfma(v0, acc[rt][0][v], m1[0][0]); m1[0][1] = band_mfma(v0, acc[rt][1][v], m1[0][1]);
+          m1[1][0] = band_mfma(v1, acc[rt][0][v], m1[1][0]); m1[1][1] = band_mfma(v1, acc[rt][1][v], m1[1][1]);
+        }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[w][(16 * i + BandVec<T>::row(lg, v)) * BAND + 16 * j + li] = m1[i][j][v];
+  __syncthreads();
+  for (int e = tid; e < 1024; e += 256) p.part[(int64_t)blockIdx.x * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+}
+
+// Y = Z T' - V (T'^T M T') / 2 with M = V^T Z; T' = T, on the way back T^T.  grid and threads as above
+template <typename T>
+__global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
+  typedef typename BandVec<T>::type V4;
+  __shared__ T M[BAND][BAND + 1], Tm[BAND][BAND + 1], S[BAND][BAND + 1];
+  band_select(g, blockIdx.y);
+  if (g.meta->skip) return;
+  const BandPanel<T> p = band_panel<T>(g, k);
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
+  constexpr bool BACK = sizeof(T) == 4;
+  for (int e = tid; e < 1024; e += 256) {
+    T s = 0;
+    for (int q = 0; q < (int)gridDim.x; ++q) s += p.part[(int64_t)q * 1024 + e];
+    M[e >> 5][e & 31] = s;
+    if (BACK) Tm[e & 31][e >> 5] = p.t[e]; else Tm[e >> 5][e & 31] = p.t[e];
+  }
+  __syncthreads();
+  const int ti = 16 * (w >> 1), tj = 16 * (w & 1);
+  V4 acc = {0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < 8; ++s) acc = band_mfma(M[ti + li][4 * s + lg], Tm[4 * s + lg][tj + li], acc);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) M[ti + BandVec<T>::row(lg, v)][tj + li] = acc[v];
+  __syncthreads();
+  acc = (V4){0, 0, 0, 0};
+#pragma unroll
+  for (int s = 0; s < 8; ++s) acc = band_mfma(Tm[4 * s + lg][ti + li], M[4 * s + lg][tj + li], acc);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) S[ti + BandVec<T>::row(lg, v)][tj + li] = acc[v];
+  __syncthreads();
+  if (base >= np) return;
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    V4 zt[2], vs[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { zt[j] = (V4){0, 0, 0, 0}; vs[j] = (V4){0, 0, 0, 0}; }
+#pragma unroll
+    for (int kk = 0; kk < BAND; kk += 16) {
+      const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + kk + 4 * lg;
+      const V4 za = *reinterpret_cast<const V4 *>(p.z + at);
+      V4 va = {0, 0, 0, 0};
+      if (base >= p.r0) va = *reinterpret_cast<const V4 *>(p.v + at);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int kq = kk + 4 * lg + q;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          zt[j] = band_mfma(za[q], Tm[kq][16 * j + li], zt[j]);
+          vs[j] = band_mfma(va[q], S[kq][16 * j + li], vs[j]);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        p.y[(int64_t)(base + 16 * rt + BandVec<T>::row(lg, v)) * BAND + 16 * j + li] = zt[j][v] - (T)0.5 * vs[j][v];
+  }
+}
+
+// W <- W - V Y^T - Y V^T on rows row0 ..., columns row0 ... (without the corner in front of r0 on the way
+// back).  grid (ceil((np - row0) / 128), ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows, which
+// keep their rows of V and Y in registers and walk along the columns together, 16 at a time.
+template <typename T>
+__global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int k) {
+  typedef typename BandVec<T>::type V4;
+  band_select(g, blockIdx.z);
+  if (g.meta->skip) return;
+  const BandPanel<T> p = band_panel<T>(g, k);
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
+  if (base >= np) return;
+  const bool inner = base >= p.r0;        // V has these rows
+  int c0 = p.row0 + BAND_COLS * blockIdx.y;
+  const int c1 = min(c0 + BAND_COLS, np);
+  if (!inner) c0 = max(c0, p.r0);
+  if (c0 >= c1) return;
+  V4 va[2][2], ya[2][2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + 16 * kk + 4 * lg;
+      ya[rt][kk] = *reinterpret_cast<const V4 *>(p.y + at);
+      va[rt][kk] = (V4){0, 0, 0, 0};
+      if (inner) va[rt][kk] = *reinterpret_cast<const V4 *>(p.v + at);
+    }
+  for (int c = c0; c < c1; c += 16) {
+    T *dst = p.w + (int64_t)base * np + c + li;
+    T old[2][4];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) old[rt][v] = dst[(int64_t)(16 * rt + BandVec<T>::row(lg, v)) * np];
+    V4 acc[2];
+    acc[0] = (V4){0, 0, 0, 0}; acc[1] = (V4){0, 0, 0, 0};
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int64_t at = (int64_t)(c + li) * BAND + 16 * kk + 4 * lg;
+      if (inner) {
+        const V4 yb = *reinterpret_cast<const V4 *>(p.y + at);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(va[rt][kk][q], yb[q], acc[rt]);
+      }
+      if (c >= p.r0) {
+        const V4 vb = *reinterpret_cast<const V4 *>(p.v + at);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(ya[rt][kk][q], vb[q], acc[rt]);
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dst[(int64_t)(16 * rt + BandVec<T>::row(lg, v)) * np] = old[rt][v] - acc[rt][v];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The block tridiagonal matrix
+// ---------------------------------------------------------------------------
+// Gershgorin bounds of B.  grid (batch), 256 threads
+__global__ __launch_bounds__(256) void band_bounds_kernel(BandArgs g) {
+  __shared__ double red[2][4];
+  band_select(g, blockIdx.x);
+  if (g.meta->skip) return;
+  const int tid = threadIdx.x, np = g.np;
+  double hi = -1.0e300, amax = 0.0;
+  for (int i = tid; i < np; i += 256) {
+    const int blk = i >> 5, r = i & 31;
+    const double *d = g.dblk + (int64_t)blk * 1024 + r * BAND;
+    double off = 0.0;
+    for (int c = 0; c < BAND; ++c) if (c != r) off += fabs(d[c]);
+    if (blk > 0) for (int c = 0; c < BAND; ++c) off += fabs(g.cblk[(int64_t)(blk - 1) * 1024 + c * BAND + r]);
+    if (blk + 1 < g.nb) for (int c = 0; c < BAND; ++c) off += fabs(g.cblk[(int64_t)blk * 1024 + r * BAND + c]);
+    hi = fmax(hi, d[r] + off);
+    amax = fmax(amax, fabs(d[r]) + off);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { hi = fmax(hi, __shfl_xor(hi, off, 64)); amax = fmax(amax, __shfl_xor(amax, off, 64)); }
+  if ((tid & 63) == 0) { red[0][tid >> 6] = hi; red[1][tid >> 6] = amax; }
+  __syncthreads();
+  if (tid == 0) {
+    g.meta->hi = fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
+    g.meta->amax = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
+  }
+}
+
+// Position of element (i, k) of -K^T in its stored order (A operand: lane l holds (l % 16, l / 16 + 4 v))
+// and of element (r, c) of a block in result order.
+__device__ __forceinline__ int band_a_index(int i, int k) { return ((((i >> 4) * 2 + (k >> 4)) * 4 + ((k & 15) >> 2)) << 6) + ((k & 3) << 4) + (i & 15); }
+__device__ __forceinline__ int band_d_index(int r, int c) { return ((((r >> 4) * 2 + (c >> 4)) * 4 + ((r & 15) >> 2)) << 6) + ((r & 3) << 4) + (c & 15); }
+
+// One block of the elimination, all of it in the registers of one wavefront as MFMA results:
+//     M  pivot block (D_i + sigma I less what the blocks before took away)   ->  -M^-1
+//     K  R^T, R the block that couples i + 1 to i                            ->  K^T = M^-1 R^T
+//     S  D_i+1                                                                ->  D_i+1 - R M^-1 R^T
+// by 32 pivots of the sweep operator on [M R^T; R S].  S is eliminated pivot by pivot (the stable
+// Cholesky way); formed as a product with M^-1 it would lose the condition number of M in accuracy,
+// which for a pivot block with a few large eigenvalues and many tiny ones is everything.
+// row: 64 doubles of LDS.  Returns whether all pivots were positive.
+struct BandElim {
+  double M[2][2][4], K[2][2][4], S[2][2][4];
+  static __device__ __forceinline__ void load(double (&x)[2][2][4], const double *d, int li, int lg) {
+    const double *p = d + lg * BAND + li;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[ti][tj][v] = p[(16 * ti + 4 * v) * BAND + 16 * tj];
+  }
+  __device__ __forceinline__ void begin(const double *d, int li, int lg) { load(S, d, li, lg); }
+  // d, rt: D_i+1 and R^T, row-major; last: there is no next block
+  __device__ __forceinline__ bool step(const double *d, const double *rt, bool last, double sigma, double tiny, double *row, int li, int lg) {
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) M[ti][tj][v] = S[ti][tj][v] + (ti == tj && lg + 4 * v == li ? sigma : 0.0);
+    if (!last) { load(K, rt, li, lg); load(S, d, li, lg); }
+    bool ok = true;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+#pragma unroll 1
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const int p = 16 * ti + 4 * v + r4;
+          if (lg == r4) {
+            row[li] = M[ti][0][v]; row[16 + li] = M[ti][1][v];
+            row[32 + li] = K[ti][0][v]; row[48 + li] = K[ti][1][v];
+          }
+          __syncthreads();
+          double pv = row[p];
+          if (!(pv > 0.0)) ok = false;
+          if (!(pv > tiny)) pv = tiny;
+          const double inv = rcp_newton(pv);
+          const double c0 = row[li], c1 = row[16 + li], k0 = row[32 + li], k1 = row[48 + li];
+          double f[2][4], h[2][4];
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { f[t][u] = row[16 * t + lg + 4 * u] * inv; h[t][u] = row[32 + 16 * t + lg + 4 * u] * inv; }
+          __syncthreads();
+          const bool mine = li == 4 * v + r4;
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              M[t][0][u] -= f[t][u] * c0;
+              M[t][1][u] -= f[t][u] * c1;
+              if (mine) M[t][ti][u] = f[t][u];
+              K[t][0][u] -= f[t][u] * k0;
+              K[t][1][u] -= f[t][u] * k1;
+              S[t][0][u] -= h[t][u] * k0;
+              S[t][1][u] -= h[t][u] * k1;
+            }
+          if (lg == r4) {
+            M[ti][0][v] = c0 * inv; M[ti][1][v] = c1 * inv;
+            if (mine) M[ti][ti][v] = -inv;
+            K[ti][0][v] = k0 * inv; K[ti][1][v] = k1 * inv;
+          }
+        }
+      }
+    return ok;
+  }
+};
+
+// Round `round` of the search for the smallest eigenvalue: wavefront s tells whether B - shift_s is
+// positive definite.  Round 0: a ladder of shifts over all magnitudes; later rounds divide the bracket,
+// where the eigenvalue is negative or so small that float64 resolves it only by itself.
+// grid (BAND_SHIFTS, batch), one wavefront
+__device__ __forceinline__ double band_ladder(int s, double amax) {   // 0, amax 2^-48 ... 2^-3, -amax 2^-55 ... 2
+  return s == 0 ? 0.0 : s <= 16 ? ldexp(amax, 3 * s - 51) : -2.0 * ldexp(amax, 4 * (s - 31));
+}
+__device__ __forceinline__ void band_bracket(const BandArgs &g, int round, double &lo, double &up, int &active) {
+  // what round - 1 has left behind: its own bracket and its verdicts
+  const BandMeta &m = *g.meta;
+  const int32_t *ok = g.ok + ((round - 1) & 1) * BAND_SHIFTS;
+  if (round == 1) {
+    int cnt = 0;
+    while (cnt <= 16 && ok[cnt]) ++cnt;
+    if (cnt > 0) {
+      lo = band_ladder(cnt - 1, m.amax);
+      up = cnt <= 16 ? band_ladder(cnt, m.amax) : m.hi;
+    } else {
+      int s = 17;
+      while (s < 31 && !ok[s]) ++s;
+      lo = band_ladder(s, m.amax);
+      up = s == 17 ? 0.0 : band_ladder(s - 1, m.amax);
+    }
+    active = m.coupled && (cnt == 0 || lo + (double)g.eps < TRI_DEFLATE_BELOW * (m.hi + (double)g.eps)) ? 1 : 0;
+  } else {
+    lo = m.lo[(round - 1) & 1]; up = m.up[(round - 1) & 1]; active = m.active[(round - 1) & 1];
+    if (active) {
+      int cnt = 0;
+      while (cnt < BAND_SHIFTS && ok[cnt]) ++cnt;
+      const double step = (up - lo) / (BAND_SHIFTS + 1);
+      up = cnt < BAND_SHIFTS ? lo + step * (cnt + 1) : up;
+      lo = lo + step * cnt;
+      if (!(up - lo > 0x1p-53 * m.amax)) active = 0;
+    }
+  }
+}
+__global__ __launch_bounds__(64) void band_probe_kernel(BandArgs g, const int round) {
+  __shared__ double row[2 * BAND];
+  const int s = blockIdx.x;
+  band_select(g, blockIdx.y);
+  if (g.meta->skip) return;
+  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
+  double sigma;
+  if (round == 0) {
+    sigma = band_ladder(s, g.meta->amax);
+  } else {
+    double lo, up;
+    int active;
+    band_bracket(g, round, lo, up, active);
+    if (s == 0 && lane == 0) { g.meta->lo[round & 1] = lo; g.meta->up[round & 1] = up; g.meta->active[round & 1] = active; }
+    if (!active) return;
+    sigma = lo + (up - lo) / (BAND_SHIFTS + 1) * (s + 1);
+  }
+  BandElim e;
+  bool ok = true;
+  e.begin(g.dblk, li, lg);
+  for (int i = 0; i < g.nb && ok; ++i)
+    ok = e.step(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == g.nb, -sigma, 1.0e-290, row, li, lg);
+  if (lane == 0) g.ok[(round & 1) * BAND_SHIFTS + s] = ok ? 1 : 0;
+}
+
+// Range, poles and exceptions of every matrix.  One thread per matrix
+__global__ void band_plan_kernel(BandArgs g, const int batch) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= batch) return;
+  int32_t *failed_user = g.failed_user;
+  band_select(g, b);
+  BandMeta &m = *g.meta;
+  if (m.skip == 2) return;
+  if (m.skip == 0) {
+    double lo, up;
+    int active;
+    band_bracket(g, BAND_ROUNDS, lo, up, active);
+    const double eps = (double)g.eps, r = (double)g.r;
+    const double lam_min = m.coupled ? fmin(lo, m.dec_min) : m.dec_min;
+    m.shift = fmin(lam_min, 0.0);
+    m.lam = lo;
+    if (!(pow((lam_min - m.shift) + eps, -r) <= 3.0e38)) m.skip = 1;
+    m.base = eps - m.shift;
+    const double top = m.hi + m.base, low = fmax(lo + m.base, TRI_LOWEST * top);
+    m.deflate = m.coupled && low < TRI_DEFLATE_BELOW * top ? 1 : 0;
+    m.cls = rat_class(low, top);
+    m.poles = rat_poles(m.cls);
+    m.low = ldexp(top, -4 * (m.cls + 1));
+    m.f1 = pow((lo - m.shift) + eps, -r);
+  }
+  if (failed_user) failed_user[b] = m.skip ? 1 : 0;
+  if (m.skip && g.fail_count) atomicAdd(g.fail_count, 1ull);
+}
+
+// Eliminates B + sigma_j from the first block to the last, then forms the diagonal blocks of the inverse
+// from the last to the first.  One wavefront per matrix and pole: grid (RAT_MAX_POLES, batch).  Bound by the
+// latency of 32 pivots per block.  Pole 0 also iterates for the eigenvector that is handled by itself.
+__global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTable table) {
+  __shared__ double row[2 * BAND];
+  __shared__ double z[BAND_MAX_N + BAND];
+  const int pole = blockIdx.x;
+  band_select(g, blockIdx.y);
+  const BandMeta m = *g.meta;
+  if (m.skip || pole >= m.poles) return;
+  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4, nb = g.nb;
+  const double sigma = m.base + m.low * exp(rat_log_pole(m.cls, pole));
+  const double wj = table.w[rat_offset(m.cls) + pole] * pow(m.low, 1.0 - (double)g.r);
+  double *kf = g.kf + (int64_t)pole * nb * 1024, *gf = g.gf + (int64_t)pole * nb * 1024;
+  BandElim e;
+  e.begin(g.dblk, li, lg);
+  for (int i = 0; i < nb; ++i) {
+    e.step(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == nb, sigma, 0x1p-60 * m.amax, row, li, lg);
+    double *go = gf + (int64_t)i * 1024;
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) go[((ti * 2 + tj) * 4 + v) * 64 + lane] = -e.M[ti][tj][v];
+    if (i + 1 < nb) {
+      double *ko = kf + (int64_t)i * 1024;
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) ko[band_a_index(16 * ti + lg + 4 * v, 16 * tj + li)] = -e.K[ti][tj][v];
+    }
+  }
+  __syncthreads();
+  if (pole == 0 && m.deflate) {
+    // x <- (B + sigma_0)^-1 x:  z_i+1 = x_i+1 - K_i z_i,  x_i = pivot_i^-1 z_i - K_i^T x_i+1
+    const int a = lane & 31, k0 = 16 * (lane >> 5);
+    for (int i = lane; i < g.np; i += 64) z[i] = 1.0 + 0.25 * (double)(((unsigned)i * 2654435761u) >> 24) * 0x1p-8;
+    __syncthreads();
+    for (int it = 0; it < 5; ++it) {
+      for (int i = 0; i + 1 < nb; ++i) {
+        const double *ko = kf + (int64_t)i * 1024;
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s += ko[band_a_index(k0 + q, a)] * z[BAND * i + k0 + q];
+        s += __shfl_xor(s, 32, 64);
+        if (lane < 32) z[BAND * (i + 1) + a] += s;
+        __syncthreads();
+      }
+      double nrm = 0.0;
+      for (int i = nb - 1; i >= 0; --i) {
+        const double *go = gf + (int64_t)i * 1024, *ko = kf + (int64_t)i * 1024;
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s += go[band_d_index(a, k0 + q)] * z[BAND * i + k0 + q];
+        if (i + 1 < nb) {
+#pragma unroll
+          for (int q = 0; q < 16; ++q) s += ko[band_a_index(a, k0 + q)] * z[BAND * (i + 1) + k0 + q];
+        }
+        s += __shfl_xor(s, 32, 64);
+        __syncthreads();
+        if (lane < 32) z[BAND * i + a] = s;
+        __syncthreads();
+        nrm += lane < 32 ? s * s : 0.0;
+      }
+      nrm = rsqrt_newton(wave64_sum(nrm));
+      for (int i = lane; i < g.np; i += 64) z[i] *= nrm;
+      __syncthreads();
+    }
+    for (int i = lane; i < g.np; i += 64) g.v1[i] = z[i];
+  }
+  // G_i = pivot_i^-1 + K_i^T G_i+1 K_i
+  double G[2][2][4];
+  for (int i = nb - 1; i >= 0; --i) {
+    double *go = gf + (int64_t)i * 1024;
+    double P[2][2][4];
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) P[ti][tj][v] = go[((ti * 2 + tj) * 4 + v) * 64 + lane];
+    if (i + 1 < nb) {
+      const double *ko = kf + (int64_t)i * 1024;
+      double kn[2][2][4];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) kn[ti][tk][v] = ko[((ti * 2 + tk) * 4 + v) * 64 + lane];
+      band_d4 H[2][2];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) {
+          H[ti][tj] = (band_d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) H[ti][tj] = band_mfma(G[tk][ti][v], kn[tj][tk][v], H[ti][tj]);
+        }
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) {
+          band_d4 acc = {P[ti][tj][0], P[ti][tj][1], P[ti][tj][2], P[ti][tj][3]};
+#pragma unroll
+          for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc = band_mfma(kn[ti][tk][v], H[tk][tj][v], acc);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) G[ti][tj][v] = acc[v];
+        }
+    } else {
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) G[ti][tj][v] = P[ti][tj][v];
+    }
+#pragma unroll
+    for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+      for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) go[((ti * 2 + tj) * 4 + v) * 64 + lane] = wj * G[ti][tj][v];
+  }
+}
+
+// Block row l of F = sum_j w_j (B + sigma_j)^-1: per pole G_{l,i} = -G_{l,i+1} K_i, held transposed, so that
+// a product's result is the next one's operand; the poles are dealt over 8 wavefronts, which meet in
+// LDS once per block.  grid (nb, batch), 512 threads; the longest rows first.
+template <int PW>
+__global__ __launch_bounds__(512, 2) void band_rows_kernel(BandArgs g) {
+  __shared__ float red[2][8][1024];
+  band_select(g, blockIdx.y);
+  const int poles = g.meta->poles;
+  if (g.meta->skip || (poles + 7) / 8 != PW) return;
+  const int np = g.np, nb = g.nb, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l = nb - 1 - blockIdx.x;
+  double gt[PW][2][2][4];                // [pole][rows 16 h ...][tile of columns][v]
+#pragma unroll
+  for (int p = 0; p < PW; ++p) {
+    const int j = w + 8 * p;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          gt[p][h][ti][v] = j < poles ? g.gf[((int64_t)j * nb + l) * 1024 + ((ti * 2 + h) * 4 + v) * 64 + lane] : 0.0;
+  }
+  for (int i = l; i >= 0; --i) {
+    if (i < l) {
+#pragma unroll
+      for (int p = 0; p < PW; ++p) {
+        const int j = w + 8 * p;
+        if (j < poles) {
+          const double *ko = g.kf + ((int64_t)j * nb + i) * 1024 + lane;
+          double kn[2][2][4];
+#pragma unroll
+          for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+            for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) kn[ti][tk][v] = ko[((ti * 2 + tk) * 4 + v) * 64];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            band_d4 acc[2];
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti) {
+              acc[ti] = (band_d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+              for (int tk = 0; tk < 2; ++tk)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[ti] = band_mfma(kn[ti][tk][v], gt[p][h][tk][v], acc[ti]);
+            }
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) gt[p][h][ti][v] = acc[ti][v];
+          }
+        }
+      }
+    }
+    float *out = red[i & 1][w];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double s = 0.0;
+#pragma unroll
+          for (int p = 0; p < PW; ++p) s += gt[p][h][ti][v];
+          out[((h * 2 + ti) * 4 + v) * 64 + lane] = (float)s;
+        }
+    __syncthreads();
+    for (int e = tid; e < 1024; e += 512) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += red[i & 1][q][e];
+      const int el = e & 63, v = (e >> 6) & 3, ti = (e >> 8) & 1, h = e >> 9;
+      const int r = 16 * h + (el & 15), c = 16 * ti + (el >> 4) + 4 * v;
+      g.f[(int64_t)(BAND * l + r) * np + BAND * i + c] = s;
+      if (i < l) g.f[(int64_t)(BAND * i + c) * np + BAND * l + r] = s;
+    }
+  }
+}
+
+// The part of F along v1 becomes f1:  F <- F - v q^T - q v^T,  q = F v - (v.F v + f1) / 2 v.
+// First kernel: y = F v;  grid (np / 32, batch), 256 threads.  Second: the update; grid (np / 32, batch).
+__global__ __launch_bounds__(256) void band_fv_kernel(BandArgs g) {
+  band_select(g, blockIdx.y);
+  if (g.meta->skip || !g.meta->deflate) return;
+  const int np = g.np, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int r = blockIdx.x * BAND + w; r < (int)(blockIdx.x + 1) * BAND; r += 4) {
+    double s = 0.0;
+    for (int c = lane; c < np; c += 64) s += (double)g.f[(int64_t)r * np + c] * g.v1[c];
+    s = wave64_sum(s);
+    if (lane == 0) g.z[r] = s;
+  }
+}
+__global__ __launch_bounds__(256) void band_deflate_kernel(BandArgs g) {
+  __shared__ double red[4];
+  band_select(g, blockIdx.y);
+  if (g.meta->skip || !g.meta->deflate) return;
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  double s = 0.0;
+  for (int c = tid; c < np; c += 256) s += g.z[c] * g.v1[c];
+  s = wave64_sum(s);
+  if (lane == 0) red[w] = s;
+  __syncthreads();
+  const double K = 0.5 * ((red[0] + red[1]) + (red[2] + red[3]) + g.meta->f1);
+  for (int r = blockIdx.x * BAND + w; r < (int)(blockIdx.x + 1) * BAND; r += 4) {
+    const double vr = g.v1[r], qr = g.z[r] - K * vr;
+    for (int c = lane; c < np; c += 64) {
+      const double vc = g.v1[c], qc = g.z[c] - K * vc;
+      g.f[(int64_t)r * np + c] = (float)((double)g.f[(int64_t)r * np + c] - (vr * qc + qr * vc));
+    }
+  }
+}
+
+// x from the lower triangle of F, mirrored; the rows that stand alone.  grid (pairs of 32 x 32 tiles, batch), 256 threads
+__global__ __launch_bounds__(256) void band_out_kernel(BandArgs g) {
+  __shared__ float tile[BAND][BAND + 1];
+  const int b = blockIdx.y;
+  band_select(g, b);
+  if (g.meta->skip) return;
+  const int n = g.n, np = g.np, tid = threadIdx.x;
+  int bi = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+  while ((bi + 1) * (bi + 2) / 2 <= (int)blockIdx.x) ++bi;
+  while (bi * (bi + 1) / 2 > (int)blockIdx.x) --bi;
+  const int bj = blockIdx.x - bi * (bi + 1) / 2;
+  const int r = tid >> 3, c4 = (tid & 7) * 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = bi * BAND + r, j = bj * BAND + c4 + e;
+    float v = g.f[(int64_t)i * np + j];
+    if (i < n && j < n && (g.dec[i] || g.dec[j]))
+      v = i == j ? (float)pow(((double)g.scale * (double)g.a[(int64_t)i * n + i] - g.meta->shift) + (double)g.eps, -(double)g.r) : 0.f;
+    tile[r][c4 + e] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int c = c4 + e;
+    const int i = bi * BAND + r, j = bj * BAND + c;
+    if (i < n && j < n) g.x[(int64_t)i * n + j] = (bi == bj && c > r) ? tile[c][r] : tile[r][c];
+    const int mi = bj * BAND + r, mj = bi * BAND + c;
+    if (bi != bj && mi < n && mj < n) g.x[(int64_t)mi * n + mj] = tile[c][r];
+  }
+}
+
+// meta and flags start at zero.  One thread per matrix
+__global__ void band_clear_kernel(BandArgs g, const int batch) {
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= batch) return;
+  band_select(g, b);
+  g.meta->skip = 0;
+  g.meta->active[0] = g.meta->active[1] = 0;
+}
+
+}  // namespace shampoo

@@ -23,6 +23,7 @@
 #include "gemm_f16x2.h"
 #include "gemm_mfma.h"
 #include "newton_root.h"
+#include "root_band.h"
 #include "root_tridiag.h"
 #include "syrk_bf16.h"
 #include "tensor_blocks.h"
@@ -359,7 +360,38 @@ int check_plan(const Plan &p) {
 // ---------------------------------------------------------------------------
 constexpr int CONGRUENCE_PANEL = 256;   // columns of T = A Qt^T formed at a time (warm start)
 
+// Workspace of the band reduction (root_band.h) for chunks of matrices.
+constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30;
+struct BandLayout {
+  int32_t np = 0, nb = 0, chunk = 0;
+  size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
+         off_kf = 0, off_gf = 0, off_v1 = 0, off_ok = 0, off_dec = 0, off_meta = 0;
+  size_t bytes = 0;
+};
+BandLayout band_layout(int n, int batch) {
+  BandLayout e;
+  if (n > BAND_MAX_N) return e;
+  e.np = (n + BAND - 1) / BAND * BAND; e.nb = e.np / BAND;
+  const size_t np = e.np, blk = (size_t)e.nb * BAND * BAND, parts = (np + BAND_ROWS - 1) / BAND_ROWS;
+  auto place = [&](size_t chunk) {
+    size_t off = 0;
+    auto take = [&](size_t per) { const size_t at = off; off += align_up(per * chunk); return at; };
+    e.off_w = take(np * np * 8); e.off_vall = take(np * np * 4);
+    e.off_vp = take(np * BAND * 8); e.off_z = take(np * BAND * 8); e.off_y = take(np * BAND * 8);
+    e.off_t = take(BAND * BAND * 8); e.off_part = take(parts * BAND * BAND * 8); e.off_tall = take(blk * 4);
+    e.off_dblk = take(blk * 8); e.off_cblk = take(blk * 8);
+    e.off_kf = take(blk * 8 * RAT_MAX_POLES); e.off_gf = take(blk * 8 * RAT_MAX_POLES);
+    e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_meta = take(sizeof(BandMeta));
+    e.chunk = (int32_t)chunk;
+    e.bytes = off;
+  };
+  place(1);
+  place(std::max<size_t>(1, std::min<size_t>({(size_t)batch, (size_t)32768, BAND_CHUNK_BYTES / e.bytes})));
+  return e;
+}
+
 struct EigLayout {
+  BandLayout band;         // bytes = 0: not available
   int32_t np = 0, chunk = 0;
   bool warm = false;       // block solver: room for the float64 panel of the congruence W = Qt A Qt^T
   size_t off_w = 0, off_qt = 0, off_j = 0, off_ident = 0, off_j16 = 0, off_rot = 0, off_dmax = 0, off_failed = 0, off_f = 0, off_t = 0;
@@ -407,6 +439,9 @@ EigLayout eig_layout(int n, int batch, size_t budget = EIG_CHUNK_BYTES, size_t h
   if (hard_cap) {
     while (e.bytes > hard_cap && e.chunk > 1) { --e.chunk; eig_offsets(e); }
     if (e.bytes > hard_cap) e.bytes = 0;
+  } else {
+    e.band = band_layout(n, batch);
+    e.bytes = std::max(e.bytes, e.band.bytes);
   }
   return e;
 }
@@ -642,6 +677,120 @@ struct BlockSolve {
   }
 };
 
+// One sub-chunk of the band reduction: matrices [first, first + cnt) of a chunk, all of its work on one
+// stream.  Enqueued panel by panel, so that the caller can interleave sub-chunks: while one is in a QR
+// factorisation, which uses one CU per matrix, the others' products fill the chip.
+struct BandSolve {
+  BandArgs g; int cnt; hipStream_t s; const RatTable *table;
+  int begin() {
+    hipLaunchKernelGGL(band_clear_kernel, dim3((cnt + 255) / 256), dim3(256), 0, s, g, cnt);
+    hipLaunchKernelGGL(band_init_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(band_alone_kernel, dim3(cnt), dim3(256), 0, s, g);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
+  template <typename T> void products(int k, int rows) {
+    const unsigned rb = (rows + BAND_ROWS - 1) / BAND_ROWS, cb = (rows + BAND_COLS - 1) / BAND_COLS;
+    hipLaunchKernelGGL(band_z_kernel<T>, dim3(rb, cnt), dim3(256), 0, s, g, k);
+    hipLaunchKernelGGL(band_y_kernel<T>, dim3(rb, cnt), dim3(256), 0, s, g, k);
+    hipLaunchKernelGGL(band_update_kernel<T>, dim3(rb, cb, cnt), dim3(256), 0, s, g, k);
+  }
+  int forward(int k) {
+    const int m = g.np - (k + 1) * BAND;
+    if (m <= 512) hipLaunchKernelGGL(band_qr_kernel<8>, dim3(cnt), dim3(1024), 0, s, g, k);
+    else if (m <= 1024) hipLaunchKernelGGL(band_qr_kernel<16>, dim3(cnt), dim3(1024), 0, s, g, k);
+    else hipLaunchKernelGGL(band_qr_kernel<32>, dim3(cnt), dim3(1024), 0, s, g, k);
+    if (m > 0) products<double>(k, m);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
+  int function() {
+    hipLaunchKernelGGL(band_bounds_kernel, dim3(cnt), dim3(256), 0, s, g);
+    for (int round = 0; round < BAND_ROUNDS; ++round)
+      hipLaunchKernelGGL(band_probe_kernel, dim3(BAND_SHIFTS, cnt), dim3(64), 0, s, g, round);
+    hipLaunchKernelGGL(band_plan_kernel, dim3((cnt + 63) / 64), dim3(64), 0, s, g, cnt);
+    hipLaunchKernelGGL(band_factor_kernel, dim3(RAT_MAX_POLES, cnt), dim3(64), 0, s, g, *table);
+    hipLaunchKernelGGL(band_rows_kernel<2>, dim3(g.nb, cnt), dim3(512), 0, s, g);
+    hipLaunchKernelGGL(band_rows_kernel<3>, dim3(g.nb, cnt), dim3(512), 0, s, g);
+    hipLaunchKernelGGL(band_rows_kernel<4>, dim3(g.nb, cnt), dim3(512), 0, s, g);
+    hipLaunchKernelGGL(band_rows_kernel<5>, dim3(g.nb, cnt), dim3(512), 0, s, g);
+    hipLaunchKernelGGL(band_fv_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(band_deflate_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
+  int back(int k) {
+    products<float>(k, g.np);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
+  int finish() {
+    hipLaunchKernelGGL(band_out_kernel, dim3(g.nb * (g.nb + 1) / 2, cnt), dim3(256), 0, s, g);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
+};
+
+// Forks the helper streams off s and joins them again.
+int aux_fork(AuxStreams *aux, int subs, hipStream_t s) {
+  if (subs <= 1) return SHAMPOO_OK;
+  HIP_TRY(hipEventRecord(aux->fork, s));
+  for (int k = 1; k < subs; ++k) HIP_TRY(hipStreamWaitEvent(aux->stream[k - 1], aux->fork, 0));
+  return SHAMPOO_OK;
+}
+int aux_join(AuxStreams *aux, int subs, hipStream_t s) {
+  for (int k = 1; k < subs; ++k) {
+    HIP_TRY(hipEventRecord(aux->join[k - 1], aux->stream[k - 1]));
+    HIP_TRY(hipStreamWaitEvent(s, aux->join[k - 1], 0));
+  }
+  return SHAMPOO_OK;
+}
+
+int band_root_batched(const float *a, int n, int batch, float eps, float r, float scale, float *x, int32_t *failed_user,
+                      unsigned long long *fail_count, unsigned char *ws, const BandLayout &e, hipStream_t s, AuxStreams *aux,
+                      const int32_t *only, const RatTable &table) {
+  int rc;
+  for (int b0 = 0; b0 < batch; b0 += e.chunk) {
+    const int cb = std::min(e.chunk, batch - b0);
+    const int subs = aux ? std::min(JAC_STREAMS, cb) : 1;
+    if ((rc = aux_fork(aux, subs, s))) return rc;
+    BandArgs base{};
+    base.a = a + (int64_t)b0 * n * n; base.n = n; base.np = e.np; base.nb = e.nb;
+    base.eps = eps; base.r = r; base.scale = scale; base.x = x + (int64_t)b0 * n * n; base.fail_count = fail_count;
+    base.meta = reinterpret_cast<BandMeta *>(ws + e.off_meta);
+    base.w = reinterpret_cast<double *>(ws + e.off_w); base.f = reinterpret_cast<float *>(ws + e.off_w);
+    base.vp = reinterpret_cast<double *>(ws + e.off_vp); base.t = reinterpret_cast<double *>(ws + e.off_t);
+    base.z = reinterpret_cast<double *>(ws + e.off_z); base.zf = reinterpret_cast<float *>(ws + e.off_z);
+    base.y = reinterpret_cast<double *>(ws + e.off_y); base.yf = reinterpret_cast<float *>(ws + e.off_y);
+    base.part = reinterpret_cast<double *>(ws + e.off_part); base.partf = reinterpret_cast<float *>(ws + e.off_part);
+    base.vall = reinterpret_cast<float *>(ws + e.off_vall); base.tall = reinterpret_cast<float *>(ws + e.off_tall);
+    base.dblk = reinterpret_cast<double *>(ws + e.off_dblk); base.cblk = reinterpret_cast<double *>(ws + e.off_cblk);
+    base.kf = reinterpret_cast<double *>(ws + e.off_kf); base.gf = reinterpret_cast<double *>(ws + e.off_gf);
+    base.v1 = reinterpret_cast<double *>(ws + e.off_v1);
+    base.ok = reinterpret_cast<int32_t *>(ws + e.off_ok); base.dec = reinterpret_cast<int32_t *>(ws + e.off_dec);
+    BandSolve solve[JAC_STREAMS];
+    int first = 0;
+    for (int k = 0; k < subs; ++k) {
+      BandSolve &v = solve[k];
+      v.g = base; v.cnt = cb / subs + (k < cb % subs ? 1 : 0); v.table = &table;
+      v.s = k == 0 ? s : aux->stream[k - 1];
+      band_select(v.g, first);
+      v.g.failed_user = failed_user ? failed_user + b0 + first : nullptr;
+      v.g.only = only ? only + b0 + first : nullptr;
+      first += v.cnt;
+    }
+    for (int k = 0; k < subs; ++k) if ((rc = solve[k].begin())) return rc;
+    for (int p = 0; p < e.nb; ++p)
+      for (int k = 0; k < subs; ++k) if ((rc = solve[k].forward(p))) return rc;
+    for (int k = 0; k < subs; ++k) if ((rc = solve[k].function())) return rc;
+    for (int p = e.nb - 2; p >= 0; --p)
+      for (int k = 0; k < subs; ++k) if ((rc = solve[k].back(p))) return rc;
+    for (int k = 0; k < subs; ++k) if ((rc = solve[k].finish())) return rc;
+    if ((rc = aux_join(aux, subs, s))) return rc;
+  }
+  return SHAMPOO_OK;
+}
+
 // X_i = rootinv(scale * A_i) for a batch of dense n x n matrices.  ws: eig_layout(n, >= chunk) region.
 // aux: helper streams for the sub-chunks of the block solver (the caller owns them and
 // serialises their use), or nullptr.
@@ -685,14 +834,14 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
   // different phases overlap on the same CUs.
   // aux == nullptr: everything on the caller's stream.
   if (aux && !aux->ready()) aux = nullptr;
+  RatTable table;
+  if (!lambda && !warm.qt && e.band.bytes && rat_table(r, table))
+    return band_root_batched(a, n, batch, eps, r, scale, x, failed_user, fail_count, ws, e.band, s, aux, only, table);
   const int n_sub = aux ? JAC_STREAMS : 1;
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {
     const int cb = std::min(e.chunk, batch - b0);
     const int subs = std::min(n_sub, cb);
-    if (subs > 1) {
-      HIP_TRY(hipEventRecord(aux->fork, s));
-      for (int k = 1; k < subs; ++k) HIP_TRY(hipStreamWaitEvent(aux->stream[k - 1], aux->fork, 0));
-    }
+    if (const int rc = aux_fork(aux, subs, s)) return rc;
     BlockSolve solve[JAC_STREAMS];
     int first = 0;
     for (int k = 0; k < subs; ++k) {
@@ -715,11 +864,7 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
         if (const int rc = solve[k].sweep()) return rc;
     for (int k = 0; k < subs; ++k)
       if (const int rc = solve[k].finish()) return rc;
-    if (subs > 1)
-      for (int k = 1; k < subs; ++k) {
-        HIP_TRY(hipEventRecord(aux->join[k - 1], aux->stream[k - 1]));
-        HIP_TRY(hipStreamWaitEvent(s, aux->join[k - 1], 0));
-      }
+    if (const int rc = aux_join(aux, subs, s)) return rc;
   }
   return SHAMPOO_OK;
 }

@@ -1,4 +1,4 @@
-"""Roots asked for without eigenvalues (csrc/root_tridiag.h) against the fp64 oracle, at the edges of
+"""Roots asked for without eigenvalues (csrc/root_tridiag.h, csrc/root_band.h) against the fp64 oracle, at the edges of
 the kernels' size classes and on every kind of spectrum that is handled by a branch of its own."""
 import numpy as np
 import pytest
@@ -50,22 +50,38 @@ def test_small_sizes(n):
     check(n, 0.25)
 
 
+@pytest.mark.parametrize("n", [129, 160, 161, 255, 288, 544, 1056])
+def test_band_sizes(n):
+    check(n, 0.25)
+
+
+@pytest.mark.parametrize("n,kinds", [(2048, ("low",)), (2017, ("single",))])
+def test_largest_band_sizes(n, kinds):
+    check(n, 0.25, kinds)
+
+
+def test_exponents_of_the_band_path():
+    for r in (1 / 6, 0.5):
+        check(200, r)
+
+
 @pytest.mark.parametrize("r", [1 / 6, 1 / 3, 0.5])
 def test_exponents(r):
     check(72, r)
 
 
-def test_non_finite_and_unrepresentable_matrices_keep_their_output():
+@pytest.mark.parametrize("n", [48, 160])
+def test_non_finite_matrices_keep_their_output(n):
     import ctypes
     import torch
-    a = np.stack([matrix("well", 48, np.random.default_rng(5))] * 3)
+    a = np.stack([matrix("well", n, np.random.default_rng(5))] * 3)
     a[1, 7, 9] = a[1, 9, 7] = np.nan
     dev = torch.from_numpy(a).cuda()
     x = torch.full_like(dev, 7.0)
     failed = torch.zeros(3, dtype=torch.int32, device="cuda")
-    ws = torch.empty(B.lib().shampoo_root_inverse_workspace_bytes(48, 3), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(B.lib().shampoo_root_inverse_workspace_bytes(n, 3), dtype=torch.uint8, device="cuda")
     p = lambda t: ctypes.c_void_p(t.data_ptr())
-    rc = B.lib().shampoo_root_inverse(p(dev), 48, 3, 1e-12, 0.25, p(x), None, p(failed), p(ws), ws.numel(),
+    rc = B.lib().shampoo_root_inverse(p(dev), n, 3, 1e-12, 0.25, p(x), None, p(failed), p(ws), ws.numel(),
                                       ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert rc == 0 and failed.tolist() == [0, 1, 0]
     assert bool((x[1] == 7.0).all()) and bool((x[0] != 7.0).all())
