@@ -69,6 +69,7 @@ struct GemmArgs {
   const int32_t *skip;          // per batch entry: nonzero = leave C untouched, or nullptr
   float *norm_partial;          // EPI_STORE_NORM: [batch][tiles] sums of squares of the stored tile
   int32_t tiles_m, tiles_n, tiles;  // tiles = tiles per batch entry (triangular count for SYRK)
+  int32_t tile0;                // EPI_SYRK: the first of them (rows of tiles in front of it stay as they are)
   int32_t batch;
 };
 
@@ -221,11 +222,12 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
   const int tile = logical - b * g.tiles;
   int ti, tj;
   if (EPI == EPI_SYRK) {
-    // lower-triangular tile index: tile = ti (ti + 1) / 2 + tj, tj <= ti
-    ti = (int)((sqrtf(8.f * (float)tile + 1.f) - 1.f) * 0.5f);
-    while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
-    while (ti * (ti + 1) / 2 > tile) --ti;
-    tj = tile - ti * (ti + 1) / 2;
+    // lower-triangular tile index: t = ti (ti + 1) / 2 + tj, tj <= ti
+    const int t = tile + g.tile0;
+    ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+    while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+    while (ti * (ti + 1) / 2 > t) --ti;
+    tj = t - ti * (ti + 1) / 2;
   } else {
     ti = tile / g.tiles_n;
     tj = tile - ti * g.tiles_n;
@@ -340,7 +342,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = ibase + e;
-          float v = g.alpha * acc[mi][ni][4 * q + e];
+          float v = ACC64 && EPI != EPI_SYRK ? (float)(g.alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0])
+                                             : g.alpha * acc[mi][ni][4 * q + e];
           if (i < g.M && j < g.N) {
             if (EPI == EPI_SYRK) {
               // only the lower triangle is computed; its mirror image is written with the

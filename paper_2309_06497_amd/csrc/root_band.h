@@ -8,7 +8,10 @@
 //                     (root_rational.h).  B is block tridiagonal, so an inverse is one elimination along
 //                     the blocks (a wavefront per matrix and shift), and every block row of it runs from
 //                     its diagonal block to the left by one 32 x 32 product per block
-//   X = Q F Q^T       the same reflectors from both sides, last panel first, float32 matrix cores
+//   X = Q F Q^T       the same reflectors from both sides, last panel first, four panels at a time as one
+//                     block reflector of 128 columns: on the way back all of them are known, and a pass over
+//                     F then costs 128 multiply-adds per element read instead of 32.  Products with the
+//                     batched float32 GEMM (gemm_mfma.h)
 //
 // The block Jacobi solver (eigh_jacobi.h) needs 10 ... 13 sweeps of 6 n^3 multiply-adds for the
 // eigenvectors; this takes about 2 n^3 for the reduction, 1 n^3 for F and 2 n^3 on the way back, and
@@ -27,6 +30,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "gemm_mfma.h"
 #include "root_rational.h"
 #include "root_tridiag.h"
 
@@ -38,6 +42,9 @@ constexpr int BAND_SHIFTS = 32;          // shifts tried per round of the bisect
 constexpr int BAND_ROUNDS = 12;          // 33^11 covers 2^53
 constexpr int BAND_ROWS = 128;           // rows per workgroup of the panel products
 constexpr int BAND_COLS = 128;           // columns per workgroup of the rank-64 update
+constexpr int BAND_GROUP = 4;            // panels per block reflector of the way back
+constexpr int BAND_GW = BAND_GROUP * BAND;   // its columns
+constexpr int BAND_PLD = 3 * BAND_GW;    // row of its work array: Z, later Y | V | Y
 
 typedef double band_d4 __attribute__((ext_vector_type(4)));
 typedef float band_f4 __attribute__((ext_vector_type(4)));
@@ -59,14 +66,23 @@ struct BandArgs {
   double *w;        // [np][np]: the matrix being reduced
   float *f;         // [np][np], in the memory of w: F, then X
   double *vp, *z, *y, *t, *part;         // current panel: V, Z, Y [np][32], T [32][32], partial sums of V^T Z [np / 128][32][32]
-  float *zf, *yf, *partf;                // the same arrays on the way back
-  float *vall, *tall;                    // all panels: V [nb - 1][np][32], T [nb - 1][32][32]
+  float *vall, *tall;                    // all panels: V [np][np], panel k in columns 32 k ...; T [nb - 1][32][32]
   double *dblk, *cblk;                   // B: diagonal blocks [nb][32][32], transposed sub-diagonal blocks [nb][32][32]
   double *kf, *gf;                       // per pole and block: -K^T (A operand order) and weight * G (D order), [36][nb][1024]
   double *v1;                            // [np]: eigenvector handled by itself
   int32_t *ok;                           // [2][BAND_SHIFTS]: verdicts of the bisection, by parity of the round
   int32_t *dec;                          // [np]: row is coupled to no other
+  int32_t *skip;                         // meta->skip != 0, back to back for the products of the way back
 };
+// Arrays of the way back, in the memory of kf and gf, which nothing reads any more by then: the work array
+// [np][BAND_PLD] of a group of panels; [T^T; -T M T^T / 2] as a [256][128] matrix; T [groups][128][128].
+__host__ __device__ inline float *band_p(const BandArgs &g) { return reinterpret_cast<float *>(g.kf); }
+__host__ __device__ inline float *band_ts(const BandArgs &g) { return reinterpret_cast<float *>(g.gf); }
+__host__ __device__ inline float *band_tg(const BandArgs &g) { return band_ts(g) + 2 * BAND_GW * BAND_GW; }
+__host__ __device__ inline int64_t band_p_stride(const BandArgs &g) { return (int64_t)g.nb * 1024 * RAT_MAX_POLES * 2; }   // matrix to matrix, floats
+// room for them: 1536 of 9216 bytes per row, and (2 + groups) 64 KB of 9216 bytes per row from 5 blocks on
+static_assert(BAND_PLD * 4 <= 32 * 8 * RAT_MAX_POLES && (2 + 2) * BAND_GW * BAND_GW * 4 <= 5 * 1024 * 8 * RAT_MAX_POLES, "way back");
+
 // from the arrays of matrix 0 of the batch to those of matrix b (failed_user and only stay: they are indexed)
 __host__ __device__ inline void band_select(BandArgs &g, int b) {
   const int64_t np = g.np, nb = g.nb;
@@ -76,18 +92,15 @@ __host__ __device__ inline void band_select(BandArgs &g, int b) {
   g.vp += b * np * BAND; g.z += b * np * BAND; g.y += b * np * BAND; g.t += (int64_t)b * 1024;
   const int64_t parts = (np + BAND_ROWS - 1) / BAND_ROWS;
   g.part += b * parts * 1024;
-  g.zf += b * np * BAND * 2; g.yf += b * np * BAND * 2; g.partf += b * parts * 2048;
   g.vall += b * np * np; g.tall += b * nb * 1024;
   g.dblk += b * nb * 1024; g.cblk += b * nb * 1024;
   g.kf += b * nb * 1024 * RAT_MAX_POLES; g.gf += b * nb * 1024 * RAT_MAX_POLES;
-  g.v1 += b * np; g.ok += b * 2 * BAND_SHIFTS; g.dec += b * np;
+  g.v1 += b * np; g.ok += b * 2 * BAND_SHIFTS; g.dec += b * np; g.skip += b;
 }
 
 __device__ __forceinline__ band_d4 band_mfma(double a, double b, band_d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 __device__ __forceinline__ band_f4 band_mfma(float a, float b, band_f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-template <typename T> struct BandVec;
-template <> struct BandVec<double> { typedef band_d4 type; static __device__ __forceinline__ int row(int lg, int v) { return lg + 4 * v; } };
-template <> struct BandVec<float> { typedef band_f4 type; static __device__ __forceinline__ int row(int lg, int v) { return 4 * lg + v; } };
+__device__ __forceinline__ int band_row(int lg, int v) { return lg + 4 * v; }   // of element v of a band_d4
 
 // ---------------------------------------------------------------------------
 // W = pad(sym(scale A)); which rows stand alone.  grid (np / 32, batch), 256 threads
@@ -104,6 +117,10 @@ __global__ __launch_bounds__(256) void band_init_kernel(BandArgs g) {
   }
   const int n = g.n, np = g.np;
   if (tid < BAND) coupled[tid] = 0;
+  {                                      // rows above a panel's first are zero in V
+    float4 *v = reinterpret_cast<float4 *>(g.vall + (int64_t)br * BAND * np);
+    for (int e = tid; e < BAND * np / 4; e += 256) v[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
   const int gi = br * BAND + r;
   int bad = 0, any = 0;
   for (int bc = 0; bc < g.nb; ++bc) {
@@ -189,7 +206,7 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
   const int tt = (m + 63) / 64;
   const int rel0 = 4 * w + ph;           // row of register t: rel0 + 64 t
   double *vp = g.vp + (int64_t)r0 * BAND;
-  float *va = g.vall + ((int64_t)k * np + r0) * BAND;
+  float *va = g.vall + (int64_t)r0 * np + k * BAND;
   double P[TT];
   int buf = 0;
 
@@ -294,7 +311,7 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
         acc = band_mfma(P[t], P[t], acc);
         if (rel < m) {
           vp[(int64_t)rel * BAND + 16 * h + c] = P[t];
-          va[(int64_t)rel * BAND + 16 * h + c] = (float)P[t];
+          va[(int64_t)rel * np + 16 * h + c] = (float)P[t];
         }
       }
     tile_sum(acc, sh.s);
@@ -335,50 +352,38 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
 }
 
 // ---------------------------------------------------------------------------
-// The panel products of both directions.  T = double: the reduction, W22 <- H^T W22 H with
-// H = I - V T V^T on rows and columns r0 ... np - 1.  T = float: the way back, F <- H F H^T, where the
-// rows in front of r0 take part in the columns behind it.
+// The panel products of the reduction: W22 <- H^T W22 H with H = I - V T V^T on rows and columns
+// r0 ... np - 1, r0 = 32 (k + 1).
 // ---------------------------------------------------------------------------
-template <typename T> struct BandPanel { T *w; const T *v; T *z, *y, *part; const T *t; int row0, r0; };
-template <typename T> __device__ __forceinline__ BandPanel<T> band_panel(const BandArgs &g, int k);
-template <> __device__ __forceinline__ BandPanel<double> band_panel<double>(const BandArgs &g, int k) {
-  return {g.w, g.vp, g.z, g.y, g.part, g.t, (k + 1) * BAND, (k + 1) * BAND};
-}
-template <> __device__ __forceinline__ BandPanel<float> band_panel<float>(const BandArgs &g, int k) {
-  return {g.f, g.vall + (int64_t)k * g.np * BAND, g.zf, g.yf, g.partf, g.tall + (int64_t)k * 1024, 0, (k + 1) * BAND};
-}
-
 // Z = W[:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
 // grid (ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows.  Memory bound (every element of W is
 // read once for 64 multiply-adds); a lane reads 4 consecutive k of its row.
-template <typename T>
 __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
-  typedef typename BandVec<T>::type V4;
-  __shared__ T red[4][1024];
+  __shared__ double red[4][1024];
   band_select(g, blockIdx.y);
   if (g.meta->skip) return;
-  const BandPanel<T> p = band_panel<T>(g, k);
+  const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
-  V4 m1[2][2];
+  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
+  band_d4 m1[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) m1[i][j] = (V4){0, 0, 0, 0};
+    for (int j = 0; j < 2; ++j) m1[i][j] = (band_d4){0, 0, 0, 0};
   if (base < np) {
-    V4 acc[2][2];
+    band_d4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (V4){0, 0, 0, 0};
-    const T *wr[2] = {p.w + (int64_t)(base + li) * np + 4 * lg, p.w + (int64_t)(base + 16 + li) * np + 4 * lg};
-    const T *vr = p.v + (int64_t)(4 * lg) * BAND + li;
+      for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0, 0, 0, 0};
+    const double *wr[2] = {g.w + (int64_t)(base + li) * np + 4 * lg, g.w + (int64_t)(base + 16 + li) * np + 4 * lg};
+    const double *vr = g.vp + (int64_t)(4 * lg) * BAND + li;
 #pragma unroll 2
-    for (int k0 = p.r0; k0 < np; k0 += 16) {
-      const V4 a0 = *reinterpret_cast<const V4 *>(wr[0] + k0), a1 = *reinterpret_cast<const V4 *>(wr[1] + k0);
+    for (int k0 = r0; k0 < np; k0 += 16) {
+      const band_d4 a0 = *reinterpret_cast<const band_d4 *>(wr[0] + k0), a1 = *reinterpret_cast<const band_d4 *>(wr[1] + k0);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const T b0 = vr[(int64_t)(k0 + q) * BAND], b1 = vr[(int64_t)(k0 + q) * BAND + 16];
+        const double b0 = vr[(int64_t)(k0 + q) * BAND], b1 = vr[(int64_t)(k0 + q) * BAND + 16];
         acc[0][0] = band_mfma(a0[q], b0, acc[0][0]); acc[0][1] = band_mfma(a0[q], b1, acc[0][1]);
         acc[1][0] = band_mfma(a1[q], b0, acc[1][0]); acc[1][1] = band_mfma(a1[q], b1, acc[1][1]);
       }
@@ -387,11 +392,11 @@ __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = base + 16 * rt + BandVec<T>::row(lg, v);
-        p.z[(int64_t)row * BAND + li] = acc[rt][0][v];
-        p.z[(int64_t)row * BAND + 16 + li] = acc[rt][1][v];
-        if (base >= p.r0) {
-          const T v0 = p.v[(int64_t)row * BAND + li], v1 = p.v[(int64_t)row * BAND + 16 + li];
+        const int row = base + 16 * rt + band_row(lg, v);
+        g.z[(int64_t)row * BAND + li] = acc[rt][0][v];
+        g.z[(int64_t)row * BAND + 16 + li] = acc[rt][1][v];
+        if (base >= r0) {
+          const double v0 = g.vp[(int64_t)row * BAND + li], v1 = g.vp[(int64_t)row * BAND + 16 + li];
           m1[0][0] = band_mfma(v0, acc[rt][0][v], m1[0][0]); m1[0][1] = band_mfma(v0, acc[rt][1][v], m1[0][1]);
           m1[1][0] = band_mfma(v1, acc[rt][0][v], m1[1][0]); m1[1][1] = band_mfma(v1, acc[rt][1][v], m1[1][1]);
         }
@@ -402,55 +407,52 @@ __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[w][(16 * i + BandVec<T>::row(lg, v)) * BAND + 16 * j + li] = m1[i][j][v];
+      for (int v = 0; v < 4; ++v) red[w][(16 * i + band_row(lg, v)) * BAND + 16 * j + li] = m1[i][j][v];
   __syncthreads();
-  for (int e = tid; e < 1024; e += 256) p.part[(int64_t)blockIdx.x * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+  for (int e = tid; e < 1024; e += 256) g.part[(int64_t)blockIdx.x * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
-// Y = Z T' - V (T'^T M T') / 2 with M = V^T Z; T' = T, on the way back T^T.  grid and threads as above
-template <typename T>
+// Y = Z T - V (T^T M T) / 2 with M = V^T Z.  grid and threads as above
 __global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
-  typedef typename BandVec<T>::type V4;
-  __shared__ T M[BAND][BAND + 1], Tm[BAND][BAND + 1], S[BAND][BAND + 1];
+  __shared__ double M[BAND][BAND + 1], Tm[BAND][BAND + 1], S[BAND][BAND + 1];
   band_select(g, blockIdx.y);
   if (g.meta->skip) return;
-  const BandPanel<T> p = band_panel<T>(g, k);
+  const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
-  constexpr bool BACK = sizeof(T) == 4;
+  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
   for (int e = tid; e < 1024; e += 256) {
-    T s = 0;
-    for (int q = 0; q < (int)gridDim.x; ++q) s += p.part[(int64_t)q * 1024 + e];
+    double s = 0.0;
+    for (int q = 0; q < (int)gridDim.x; ++q) s += g.part[(int64_t)q * 1024 + e];
     M[e >> 5][e & 31] = s;
-    if (BACK) Tm[e & 31][e >> 5] = p.t[e]; else Tm[e >> 5][e & 31] = p.t[e];
+    Tm[e >> 5][e & 31] = g.t[e];
   }
   __syncthreads();
   const int ti = 16 * (w >> 1), tj = 16 * (w & 1);
-  V4 acc = {0, 0, 0, 0};
+  band_d4 acc = {0, 0, 0, 0};
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc = band_mfma(M[ti + li][4 * s + lg], Tm[4 * s + lg][tj + li], acc);
   __syncthreads();
 #pragma unroll
-  for (int v = 0; v < 4; ++v) M[ti + BandVec<T>::row(lg, v)][tj + li] = acc[v];
+  for (int v = 0; v < 4; ++v) M[ti + band_row(lg, v)][tj + li] = acc[v];
   __syncthreads();
-  acc = (V4){0, 0, 0, 0};
+  acc = (band_d4){0, 0, 0, 0};
 #pragma unroll
   for (int s = 0; s < 8; ++s) acc = band_mfma(Tm[4 * s + lg][ti + li], M[4 * s + lg][tj + li], acc);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) S[ti + BandVec<T>::row(lg, v)][tj + li] = acc[v];
+  for (int v = 0; v < 4; ++v) S[ti + band_row(lg, v)][tj + li] = acc[v];
   __syncthreads();
   if (base >= np) return;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
-    V4 zt[2], vs[2];
+    band_d4 zt[2], vs[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) { zt[j] = (V4){0, 0, 0, 0}; vs[j] = (V4){0, 0, 0, 0}; }
+    for (int j = 0; j < 2; ++j) { zt[j] = (band_d4){0, 0, 0, 0}; vs[j] = (band_d4){0, 0, 0, 0}; }
 #pragma unroll
     for (int kk = 0; kk < BAND; kk += 16) {
       const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + kk + 4 * lg;
-      const V4 za = *reinterpret_cast<const V4 *>(p.z + at);
-      V4 va = {0, 0, 0, 0};
-      if (base >= p.r0) va = *reinterpret_cast<const V4 *>(p.v + at);
+      const band_d4 za = *reinterpret_cast<const band_d4 *>(g.z + at);
+      band_d4 va = {0, 0, 0, 0};
+      if (base >= r0) va = *reinterpret_cast<const band_d4 *>(g.vp + at);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int kq = kk + 4 * lg + q;
@@ -465,58 +467,56 @@ __global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        p.y[(int64_t)(base + 16 * rt + BandVec<T>::row(lg, v)) * BAND + 16 * j + li] = zt[j][v] - (T)0.5 * vs[j][v];
+        g.y[(int64_t)(base + 16 * rt + band_row(lg, v)) * BAND + 16 * j + li] = zt[j][v] - 0.5 * vs[j][v];
   }
 }
 
 // W <- W - V Y^T - Y V^T on rows row0 ..., columns row0 ... (without the corner in front of r0 on the way
 // back).  grid (ceil((np - row0) / 128), ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows, which
 // keep their rows of V and Y in registers and walk along the columns together, 16 at a time.
-template <typename T>
 __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int k) {
-  typedef typename BandVec<T>::type V4;
   band_select(g, blockIdx.z);
   if (g.meta->skip) return;
-  const BandPanel<T> p = band_panel<T>(g, k);
+  const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = p.row0 + BAND_ROWS * blockIdx.x + BAND * w;
+  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
   if (base >= np) return;
-  const bool inner = base >= p.r0;        // V has these rows
-  int c0 = p.row0 + BAND_COLS * blockIdx.y;
+  const bool inner = base >= r0;        // V has these rows
+  int c0 = r0 + BAND_COLS * blockIdx.y;
   const int c1 = min(c0 + BAND_COLS, np);
-  if (!inner) c0 = max(c0, p.r0);
+  if (!inner) c0 = max(c0, r0);
   if (c0 >= c1) return;
-  V4 va[2][2], ya[2][2];
+  band_d4 va[2][2], ya[2][2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + 16 * kk + 4 * lg;
-      ya[rt][kk] = *reinterpret_cast<const V4 *>(p.y + at);
-      va[rt][kk] = (V4){0, 0, 0, 0};
-      if (inner) va[rt][kk] = *reinterpret_cast<const V4 *>(p.v + at);
+      ya[rt][kk] = *reinterpret_cast<const band_d4 *>(g.y + at);
+      va[rt][kk] = (band_d4){0, 0, 0, 0};
+      if (inner) va[rt][kk] = *reinterpret_cast<const band_d4 *>(g.vp + at);
     }
   for (int c = c0; c < c1; c += 16) {
-    T *dst = p.w + (int64_t)base * np + c + li;
-    T old[2][4];
+    double *dst = g.w + (int64_t)base * np + c + li;
+    double old[2][4];
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) old[rt][v] = dst[(int64_t)(16 * rt + BandVec<T>::row(lg, v)) * np];
-    V4 acc[2];
-    acc[0] = (V4){0, 0, 0, 0}; acc[1] = (V4){0, 0, 0, 0};
+      for (int v = 0; v < 4; ++v) old[rt][v] = dst[(int64_t)(16 * rt + band_row(lg, v)) * np];
+    band_d4 acc[2];
+    acc[0] = (band_d4){0, 0, 0, 0}; acc[1] = (band_d4){0, 0, 0, 0};
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const int64_t at = (int64_t)(c + li) * BAND + 16 * kk + 4 * lg;
       if (inner) {
-        const V4 yb = *reinterpret_cast<const V4 *>(p.y + at);
+        const band_d4 yb = *reinterpret_cast<const band_d4 *>(g.y + at);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
           for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(va[rt][kk][q], yb[q], acc[rt]);
       }
-      if (c >= p.r0) {
-        const V4 vb = *reinterpret_cast<const V4 *>(p.v + at);
+      if (c >= r0) {
+        const band_d4 vb = *reinterpret_cast<const band_d4 *>(g.vp + at);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int 
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dst[(int64_t)(16 * rt + BandVec<T>::row(lg, v)) * np] = old[rt][v] - acc[rt][v];
+      for (int v = 0; v < 4; ++v) dst[(int64_t)(16 * rt + band_row(lg, v)) * np] = old[rt][v] - acc[rt][v];
   }
 }
 
@@ -710,7 +710,7 @@ __global__ void band_plan_kernel(BandArgs g, const int batch) {
   int32_t *failed_user = g.failed_user;
   band_select(g, b);
   BandMeta &m = *g.meta;
-  if (m.skip == 2) return;
+  if (m.skip == 2) { *g.skip = 1; return; }
   if (m.skip == 0) {
     double lo, up;
     int active;
@@ -728,6 +728,7 @@ __global__ void band_plan_kernel(BandArgs g, const int batch) {
     m.low = ldexp(top, -4 * (m.cls + 1));
     m.f1 = pow((lo - m.shift) + eps, -r);
   }
+  *g.skip = m.skip ? 1 : 0;
   if (failed_user) failed_user[b] = m.skip ? 1 : 0;
   if (m.skip && g.fail_count) atomicAdd(g.fail_count, 1ull);
 }
@@ -977,6 +978,164 @@ __global__ __launch_bounds__(256) void band_deflate_kernel(BandArgs g) {
       g.f[(int64_t)r * np + c] = (float)((double)g.f[(int64_t)r * np + c] - (vr * qc + qr * vc));
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// The way back: F <- H F H^T for H = I - V T V^T of a group of 4 panels, as
+//     Z = F V,  Y = Z T^T - V (T M T^T) / 2 with M = V^T Z,  F <- F - Y V^T - V Y^T
+// The first, the second and the last product are launches of gemm_mfma_kernel on the work array
+// [Z V] and [Y V], [V Y]; the last computes the tiles on and below the diagonal and mirrors them.
+// 64 matrices of 1024, kernel time summed over four streams: 23.7 ms one panel at a time, 16 ms so (64
+// refreshed factors: 19.5 -> 18.1 ms in all); groups of 4 because T and M of 128 columns still fit LDS.
+// ---------------------------------------------------------------------------
+// T of the groups: T of two neighbours is [T1, -T1 (V1^T V2) T2; 0, T2].  grid (groups, batch), 16
+// wavefronts that share the rows of the 6 products V_a^T V_b; all groups of all matrices in one launch.
+__global__ __launch_bounds__(1024) void band_group_t_kernel(BandArgs g) {
+  __shared__ float red[16][1024], T[BAND_GW][BAND_GW + 1];
+  band_select(g, blockIdx.y);
+  if (g.meta->skip) return;
+  const int np = g.np, q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int panels = min(BAND_GROUP, g.nb - 1 - BAND_GROUP * q);
+  band_f4 acc[6][2][2];
+#pragma unroll
+  for (int e = 0; e < 6; ++e)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[e][i][j] = (band_f4){0.f, 0.f, 0.f, 0.f};
+  const float *v = g.vall + BAND_GW * q + li;
+  for (int r = (BAND_GROUP * q + 1) * BAND + 4 * w; r < np; r += 64) {
+    float x[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = t < 2 * panels ? v[(int64_t)(r + lg) * np + 16 * t] : 0.f;
+    int e = 0;
+#pragma unroll
+    for (int b = 1; b < 4; ++b)
+#pragma unroll
+      for (int a = 0; a < b; ++a, ++e)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[e][i][j] = band_mfma(x[2 * a + i], x[2 * b + j], acc[e][i][j]);
+  }
+  int e = 0;
+#pragma unroll
+  for (int b = 1; b < 4; ++b)
+#pragma unroll
+    for (int a = 0; a < b; ++a, ++e) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) red[w][(16 * i + 4 * lg + u) * BAND + 16 * j + li] = acc[e][i][j][u];
+      __syncthreads();
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s += red[k][tid];
+      T[BAND * a + (tid >> 5)][BAND * b + (tid & 31)] = s;
+      T[BAND * b + (tid >> 5)][BAND * a + (tid & 31)] = 0.f;
+      __syncthreads();
+    }
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+    T[BAND * a + (tid >> 5)][BAND * a + (tid & 31)] = a < panels ? g.tall[(int64_t)(BAND_GROUP * q + a) * 1024 + tid] : 0.f;
+  __syncthreads();
+  float *u = red[0];                     // [h][h]: (V1^T V2) T2
+  for (int h = BAND; h < BAND_GW; h *= 2)
+    for (int o = 0; o < BAND_GW; o += 2 * h) {
+      for (int x = tid; x < h * h; x += 1024) {
+        const int i = x / h, j = x % h;
+        float s = 0.f;
+        for (int k = 0; k <= j; ++k) s += T[o + i][o + h + k] * T[o + h + k][o + h + j];
+        u[x] = s;
+      }
+      __syncthreads();
+      for (int x = tid; x < h * h; x += 1024) {
+        const int i = x / h, j = x % h;
+        float s = 0.f;
+        for (int k = i; k < h; ++k) s += T[o + i][o + k] * u[k * h + j];
+        T[o + i][o + h + j] = -s;
+      }
+      __syncthreads();
+    }
+  float *out = band_tg(g) + (int64_t)q * BAND_GW * BAND_GW;
+  for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x / BAND_GW][x % BAND_GW];
+}
+
+// V of group q into the work array (Y = false), or Y into its second place.  grid (np / 8, batch), 256 threads
+template <bool Y>
+__global__ __launch_bounds__(256) void band_stage_kernel(BandArgs g, const int q) {
+  band_select(g, blockIdx.y);
+  if (g.meta->skip) return;
+  const int row = blockIdx.x * 8 + (threadIdx.x >> 5), c = (threadIdx.x & 31) * 4;
+  float *p = band_p(g) + (int64_t)row * BAND_PLD;
+  if (Y) {
+    *reinterpret_cast<float4 *>(p + 2 * BAND_GW + c) = *reinterpret_cast<const float4 *>(p + c);
+  } else {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (BAND_GW * q + c < g.np) v = *reinterpret_cast<const float4 *>(g.vall + (int64_t)row * g.np + BAND_GW * q + c);
+    *reinterpret_cast<float4 *>(p + BAND_GW + c) = v;
+  }
+}
+
+// M = V^T Z and [T^T; -T M T^T / 2].  grid (batch), 16 wavefronts of 32 x 32 results each; one workgroup per
+// matrix, since the second product needs all of the first: 15 us for 1024 rows.
+__global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
+  __shared__ float M[BAND_GW][BAND_GW + 1], T[BAND_GW][BAND_GW + 1];
+  band_select(g, blockIdx.x);
+  if (g.meta->skip) return;
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int i0 = 32 * (w >> 2), j0 = 32 * (w & 3);
+  const float *tg = band_tg(g) + (int64_t)q * BAND_GW * BAND_GW;
+  for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) T[x / BAND_GW][x % BAND_GW] = tg[x];
+  band_f4 acc[2][2];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = (band_f4){0.f, 0.f, 0.f, 0.f};
+  };
+  auto product = [&](float a0, float a1, float b0, float b1) {
+    acc[0][0] = band_mfma(a0, b0, acc[0][0]); acc[0][1] = band_mfma(a0, b1, acc[0][1]);
+    acc[1][0] = band_mfma(a1, b0, acc[1][0]); acc[1][1] = band_mfma(a1, b1, acc[1][1]);
+  };
+  clear();
+  const float *p = band_p(g) + (int64_t)lg * BAND_PLD + li;
+  for (int r = (BAND_GROUP * q + 1) * BAND; r < np; r += BAND)
+#pragma unroll
+    for (int t = 0; t < BAND; t += 4) {
+      const float *z = p + (int64_t)(r + t) * BAND_PLD, *v = z + BAND_GW;
+      product(v[i0], v[i0 + 16], z[j0], z[j0 + 16]);
+    }
+  auto put = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) M[i0 + 16 * i + 4 * lg + u][j0 + 16 * j + li] = acc[i][j][u];
+  };
+  put();
+  __syncthreads();
+  clear();
+#pragma unroll 8
+  for (int s = 0; s < BAND_GW / 4; ++s) product(M[i0 + li][4 * s + lg], M[i0 + 16 + li][4 * s + lg], T[j0 + li][4 * s + lg], T[j0 + 16 + li][4 * s + lg]);
+  __syncthreads();
+  put();
+  __syncthreads();
+  clear();
+#pragma unroll 8
+  for (int s = 0; s < BAND_GW / 4; ++s) product(T[i0 + li][4 * s + lg], T[i0 + 16 + li][4 * s + lg], M[4 * s + lg][j0 + li], M[4 * s + lg][j0 + 16 + li]);
+  float *out = band_ts(g);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        out[(BAND_GW + i0 + 16 * i + 4 * lg + u) * BAND_GW + j0 + 16 * j + li] = -0.5f * acc[i][j][u];
+  for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x % BAND_GW][x / BAND_GW];
 }
 
 // x from the lower triangle of F, mirrored; the rows that stand alone.  grid (pairs of 32 x 32 tiles, batch), 256 threads

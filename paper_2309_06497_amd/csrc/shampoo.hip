@@ -365,7 +365,7 @@ constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30;
 struct BandLayout {
   int32_t np = 0, nb = 0, chunk = 0;
   size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
-         off_kf = 0, off_gf = 0, off_v1 = 0, off_ok = 0, off_dec = 0, off_meta = 0;
+         off_kf = 0, off_gf = 0, off_v1 = 0, off_ok = 0, off_dec = 0, off_skip = 0, off_meta = 0;
   size_t bytes = 0;
 };
 BandLayout band_layout(int n, int batch) {
@@ -381,7 +381,7 @@ BandLayout band_layout(int n, int batch) {
     e.off_t = take(BAND * BAND * 8); e.off_part = take(parts * BAND * BAND * 8); e.off_tall = take(blk * 4);
     e.off_dblk = take(blk * 8); e.off_cblk = take(blk * 8);
     e.off_kf = take(blk * 8 * RAT_MAX_POLES); e.off_gf = take(blk * 8 * RAT_MAX_POLES);
-    e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_meta = take(sizeof(BandMeta));
+    e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_skip = take(4); e.off_meta = take(sizeof(BandMeta));
     e.chunk = (int32_t)chunk;
     e.bytes = off;
   };
@@ -689,18 +689,17 @@ struct BandSolve {
     HIP_TRY(hipGetLastError());
     return SHAMPOO_OK;
   }
-  template <typename T> void products(int k, int rows) {
-    const unsigned rb = (rows + BAND_ROWS - 1) / BAND_ROWS, cb = (rows + BAND_COLS - 1) / BAND_COLS;
-    hipLaunchKernelGGL(band_z_kernel<T>, dim3(rb, cnt), dim3(256), 0, s, g, k);
-    hipLaunchKernelGGL(band_y_kernel<T>, dim3(rb, cnt), dim3(256), 0, s, g, k);
-    hipLaunchKernelGGL(band_update_kernel<T>, dim3(rb, cb, cnt), dim3(256), 0, s, g, k);
-  }
   int forward(int k) {
     const int m = g.np - (k + 1) * BAND;
     if (m <= 512) hipLaunchKernelGGL(band_qr_kernel<8>, dim3(cnt), dim3(1024), 0, s, g, k);
     else if (m <= 1024) hipLaunchKernelGGL(band_qr_kernel<16>, dim3(cnt), dim3(1024), 0, s, g, k);
     else hipLaunchKernelGGL(band_qr_kernel<32>, dim3(cnt), dim3(1024), 0, s, g, k);
-    if (m > 0) products<double>(k, m);
+    if (m > 0) {
+      const unsigned rb = (m + BAND_ROWS - 1) / BAND_ROWS, cb = (m + BAND_COLS - 1) / BAND_COLS;
+      hipLaunchKernelGGL(band_z_kernel, dim3(rb, cnt), dim3(256), 0, s, g, k);
+      hipLaunchKernelGGL(band_y_kernel, dim3(rb, cnt), dim3(256), 0, s, g, k);
+      hipLaunchKernelGGL(band_update_kernel, dim3(rb, cb, cnt), dim3(256), 0, s, g, k);
+    }
     HIP_TRY(hipGetLastError());
     return SHAMPOO_OK;
   }
@@ -716,11 +715,42 @@ struct BandSolve {
     hipLaunchKernelGGL(band_rows_kernel<5>, dim3(g.nb, cnt), dim3(512), 0, s, g);
     hipLaunchKernelGGL(band_fv_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
     hipLaunchKernelGGL(band_deflate_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(band_group_t_kernel, dim3(groups(), cnt), dim3(1024), 0, s, g);
     HIP_TRY(hipGetLastError());
     return SHAMPOO_OK;
   }
-  int back(int k) {
-    products<float>(k, g.np);
+  int groups() const { return (g.nb - 1 + BAND_GROUP - 1) / BAND_GROUP; }
+  int back(int q) {
+    const int np = g.np, r0 = (BAND_GROUP * q + 1) * BAND, tiles = (np + BM - 1) / BM;
+    float *p = band_p(g);
+    const int64_t pstride = band_p_stride(g);
+    // Z sums over up to 2048 values of k: 64 at a time in float32, those sums in float64 (error of the root at
+    // n = 1024: 2.5e-6 -> 2.2e-6; the shorter sums of Y and F gain 0.2e-6 for 5 % of the time, and stay)
+    constexpr int FLUSH = 4;
+    int rc;
+    hipLaunchKernelGGL(band_stage_kernel<false>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
+    GemmArgs z{};                        // Z = F V
+    z.a.base = g.f + r0; z.a.batch_stride = (int64_t)np * np * 2; z.a.ld = np;
+    z.b.base = p + (int64_t)r0 * BAND_PLD + BAND_GW; z.b.batch_stride = pstride; z.b.ld = BAND_PLD;
+    z.c = p; z.c_batch_stride = pstride; z.ldc = BAND_PLD;
+    z.M = np; z.N = BAND_GW; z.K = np - r0; z.alpha_d = 1.0; z.skip = g.skip;
+    z.tiles_m = z.tiles = tiles; z.tiles_n = 1; z.batch = cnt;
+    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, FLUSH>(z, s))) return rc;
+    hipLaunchKernelGGL(band_s_kernel, dim3(cnt), dim3(1024), 0, s, g, q);
+    // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them
+    GemmArgs y = z;
+    y.a = Operand{p, pstride, BAND_PLD, 0};
+    y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
+    y.K = 2 * BAND_GW; y.alpha = 1.f;
+    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>(y, s))) return rc;
+    hipLaunchKernelGGL(band_stage_kernel<true>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
+    GemmArgs u = z;                      // F <- F - [Y V] [V Y]^T; V has no rows in front of r0
+    u.a = y.a;
+    u.b = Operand{p + BAND_GW, pstride, BAND_PLD, 0};
+    u.c = g.f; u.c_batch_stride = (int64_t)np * np * 2; u.ldc = np;
+    u.N = np; u.K = 2 * BAND_GW; u.alpha = -1.f; u.beta = 1.f;
+    u.tiles_n = tiles; u.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; u.tiles = tiles * (tiles + 1) / 2 - u.tile0;
+    if ((rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(u, s))) return rc;
     HIP_TRY(hipGetLastError());
     return SHAMPOO_OK;
   }
@@ -760,9 +790,8 @@ int band_root_batched(const float *a, int n, int batch, float eps, float r, floa
     base.meta = reinterpret_cast<BandMeta *>(ws + e.off_meta);
     base.w = reinterpret_cast<double *>(ws + e.off_w); base.f = reinterpret_cast<float *>(ws + e.off_w);
     base.vp = reinterpret_cast<double *>(ws + e.off_vp); base.t = reinterpret_cast<double *>(ws + e.off_t);
-    base.z = reinterpret_cast<double *>(ws + e.off_z); base.zf = reinterpret_cast<float *>(ws + e.off_z);
-    base.y = reinterpret_cast<double *>(ws + e.off_y); base.yf = reinterpret_cast<float *>(ws + e.off_y);
-    base.part = reinterpret_cast<double *>(ws + e.off_part); base.partf = reinterpret_cast<float *>(ws + e.off_part);
+    base.z = reinterpret_cast<double *>(ws + e.off_z); base.y = reinterpret_cast<double *>(ws + e.off_y);
+    base.part = reinterpret_cast<double *>(ws + e.off_part); base.skip = reinterpret_cast<int32_t *>(ws + e.off_skip);
     base.vall = reinterpret_cast<float *>(ws + e.off_vall); base.tall = reinterpret_cast<float *>(ws + e.off_tall);
     base.dblk = reinterpret_cast<double *>(ws + e.off_dblk); base.cblk = reinterpret_cast<double *>(ws + e.off_cblk);
     base.kf = reinterpret_cast<double *>(ws + e.off_kf); base.gf = reinterpret_cast<double *>(ws + e.off_gf);
@@ -783,8 +812,8 @@ int band_root_batched(const float *a, int n, int batch, float eps, float r, floa
     for (int p = 0; p < e.nb; ++p)
       for (int k = 0; k < subs; ++k) if ((rc = solve[k].forward(p))) return rc;
     for (int k = 0; k < subs; ++k) if ((rc = solve[k].function())) return rc;
-    for (int p = e.nb - 2; p >= 0; --p)
-      for (int k = 0; k < subs; ++k) if ((rc = solve[k].back(p))) return rc;
+    for (int q = solve[0].groups() - 1; q >= 0; --q)
+      for (int k = 0; k < subs; ++k) if ((rc = solve[k].back(q))) return rc;
     for (int k = 0; k < subs; ++k) if ((rc = solve[k].finish())) return rc;
     if ((rc = aux_join(aux, subs, s))) return rc;
   }
