@@ -71,6 +71,7 @@ struct GemmArgs {
   int32_t tiles_m, tiles_n, tiles;  // tiles = tiles per batch entry (triangular count for SYRK)
   int32_t tile0;                // EPI_SYRK: the first of them (rows of tiles in front of it stay as they are)
   int32_t batch;
+  int32_t ksplit, krange;       // EPI_SYRK, ksplit > 1: batch entry b is the range b % ksplit, of krange values of k, of operand b / ksplit
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
@@ -240,13 +241,22 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
   const int wm = wave >> 1, wn = wave & 1;
   const int row0 = ti * BM, col0 = tj * BN;
 
-  int lda, ldb;
-  const TA *pa = operand_ptr<TA>(g.a, g.desc, g.ptr_table, b, lda);
-  const TB *pb = operand_ptr<TB>(g.b, g.desc, g.ptr_table, b, ldb);
+  int lda, ldb, entry = b, K = g.K, kfirst = 0;
+  if (EPI == EPI_SYRK && g.ksplit > 1) {
+    entry = b / g.ksplit;
+    kfirst = (b - entry * g.ksplit) * g.krange;
+    K = min(g.krange, g.K - kfirst);
+  }
+  const TA *pa = operand_ptr<TA>(g.a, g.desc, g.ptr_table, entry, lda);
+  const TB *pb = operand_ptr<TB>(g.b, g.desc, g.ptr_table, entry, ldb);
+  if (EPI == EPI_SYRK) {
+    pa += AO == K_CONTIG ? (int64_t)kfirst : (int64_t)kfirst * lda;
+    pb += BO == K_CONTIG ? (int64_t)kfirst : (int64_t)kfirst * ldb;
+  }
   TileLoader<AO, TA> la;
   TileLoader<BO, TB> lb;
-  la.init(pa + (AO == K_CONTIG ? (int64_t)row0 * lda : (int64_t)row0), lda, g.M - row0, g.K);
-  lb.init(pb + (BO == K_CONTIG ? (int64_t)col0 * ldb : (int64_t)col0), ldb, g.N - col0, g.K);
+  la.init(pa + (AO == K_CONTIG ? (int64_t)row0 * lda : (int64_t)row0), lda, g.M - row0, K);
+  lb.init(pb + (BO == K_CONTIG ? (int64_t)col0 * ldb : (int64_t)col0), ldb, g.N - col0, K);
   const float *ks = KSCALE ? g.kscale + (int64_t)b * g.kscale_stride : nullptr;
 
   floatx16 acc[2][2];
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
         for (int v = 0; v < 16; ++v) acc64[ACC64 ? i : 0][ACC64 ? j : 0][ACC64 ? v : 0] = 0.0;
   }
 
-  const int nk = (g.K + BK - 1) / BK;
+  const int nk = (K + BK - 1) / BK;
   la.fetch(0, tid);
   lb.fetch(0, tid);
   if (KSCALE) la.scale(ks, 0, tid);

@@ -1300,30 +1300,39 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
 
   // Tensor parameters (Sec. 2.3): the step works on block-contiguous copies of their gradient
   // and of the parameter itself; the pointer tables on the device name those copies.
-  auto tensor_copy_args = [&](int i) {
+  TensorCopySet copies{};
+  int copy_wgs = 0;
+  auto send_copies = [&](bool scatter) {
+    if (copies.count == 0) return;
+    if (scatter) hipLaunchKernelGGL(tensor_block_copy_kernel<true>, dim3((unsigned)copy_wgs), dim3(256), 0, s, copies);
+    else hipLaunchKernelGGL(tensor_block_copy_kernel<false>, dim3((unsigned)copy_wgs), dim3(256), 0, s, copies);
+    copies.count = 0; copy_wgs = 0;
+  };
+  auto add_copy = [&](int i, void *tensor, void *copy, int bytes, bool scatter) {
     const PShape &ps = p.pshape[i];
     TensorCopyArgs ta{};
+    ta.tensor = tensor; ta.copy = copy; ta.bytes = bytes;
     ta.D1 = ps.d[0]; ta.D2 = ps.d[1]; ta.D3 = ps.d[2]; ta.D4 = ps.d[3]; ta.b = c.block_size;
     ta.k2n = (int32_t)((ps.d[1] + c.block_size - 1) / c.block_size);
     ta.k3n = (int32_t)((ps.d[2] + c.block_size - 1) / c.block_size);
     ta.k4n = (int32_t)((ps.d[3] + c.block_size - 1) / c.block_size);
-    return ta;
-  };
-  auto tensor_copy_grid = [&](int i) {
-    const int64_t per = std::min<int64_t>(c.block_size, p.pshape[i].d[0]) * std::min<int64_t>(c.block_size, p.pshape[i].d[1]) *
-                        std::min<int64_t>(c.block_size, p.pshape[i].d[2]) * std::min<int64_t>(c.block_size, p.pshape[i].d[3]);
-    return dim3((unsigned)p.param_blocks[i].size(), (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (per + 2047) / 2048)));
+    const int64_t per = std::min<int64_t>(c.block_size, ps.d[0]) * std::min<int64_t>(c.block_size, ps.d[1]) *
+                        std::min<int64_t>(c.block_size, ps.d[2]) * std::min<int64_t>(c.block_size, ps.d[3]);
+    ta.chunks = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, (per + 2047) / 2048));
+    const int64_t wgs = (int64_t)ta.chunks * (int64_t)p.param_blocks[i].size();
+    if (copies.count == TENSOR_COPY_SET || copy_wgs + wgs > ((int64_t)1 << 30)) send_copies(scatter);
+    ta.first = copy_wgs;
+    copy_wgs += (int)wgs;
+    copies.t[copies.count++] = ta;
   };
   if (o->has_tensor) {
     StageTimer t(o, SHAMPOO_STAGE_GRAFT, s);
     for (int i = 0; i < c.n_params; ++i) {
       if (p.pshape[i].kind != P_TENSOR) continue;
-      TensorCopyArgs ta = tensor_copy_args(i);
-      ta.tensor_in = o->last_g[i]; ta.copy_out = ws + o->off_Gb[i];
-      hipLaunchKernelGGL((tensor_block_copy_kernel<GT, false>), tensor_copy_grid(i), dim3(256), 0, s, ta);
-      ta.tensor_in = o->last_w[i]; ta.copy_out = ws + o->off_Wb[i];
-      hipLaunchKernelGGL((tensor_block_copy_kernel<float, false>), tensor_copy_grid(i), dim3(256), 0, s, ta);
+      add_copy(i, const_cast<void *>(o->last_g[i]), ws + o->off_Gb[i], (int)sizeof(GT), false);
+      add_copy(i, o->last_w[i], ws + o->off_Wb[i], 4, false);
     }
+    send_copies(false);
     HIP_TRY(hipGetLastError());
   }
 
@@ -1361,6 +1370,27 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     xs.s_g = reinterpret_cast<float *>(ws + b.off_s_g); xs.inv_g2 = reinterpret_cast<float *>(ws + b.off_inv_g2);
     xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
     hipLaunchKernelGGL(x2_scales_kernel, dim3(b.count), dim3(64), 0, s, xs);
+  };
+  // Tensor blocks: the Gram matrix of an unfolding d x N / d is a tile or a few per block over a long k, which
+  // leaves most of the CUs idle.  k is cut into ranges of at least 64 until there are about four workgroups per
+  // CU; their Gram matrices go through T (it holds m n values per block, splits d^2 of them are needed) and are
+  // added in float64.  The blocks of ResNet-50, most of them 128 x 1152 twice: 706 us whole, 200 + 66 us cut.
+  auto split_gram = [&](const Bucket &b, GemmArgs &g) {
+    const int64_t most = std::min<int64_t>((int64_t)b.m * b.n / ((int64_t)g.M * g.M), g.K / 64);
+    const int64_t want = (1024 + (int64_t)g.tiles * g.batch - 1) / ((int64_t)g.tiles * g.batch);
+    if (std::min(want, most) <= 1) return 1;
+    g.krange = (int32_t)((g.K / std::min(want, most) + BK - 1) / BK * BK);
+    g.ksplit = (g.K + g.krange - 1) / g.krange;
+    if (g.ksplit <= 1) { g.ksplit = 0; return 1; }
+    g.c = T; g.batch *= g.ksplit;
+    g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0;
+    return (int)g.ksplit;
+  };
+  auto reduce_gram = [&](size_t off_factor, int d, int splits, int count) {
+    GramReduceArgs gr;
+    gr.partial = T; gr.factor = reinterpret_cast<float *>(ws + off_factor); gr.d = d; gr.splits = splits;
+    gr.alpha = alpha; gr.beta = beta;
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(((int64_t)d * d + 255) / 256), count), dim3(256), 0, s, gr);
   };
   for (auto &b : p.buckets) {
     if (fused(b)) continue;
@@ -1441,8 +1471,14 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
         g.M = b.m; g.N = b.m; g.K = b.n;
         g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
+        const int sp = b.t3 ? split_gram(b, g) : 1;
         rc = launch_gemm<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
         if (rc) return rc;
+        if (sp > 1) {
+          reduce_gram(b.off_L, b.m, sp, b.count);
+          g.ksplit = 0; g.batch = b.count;
+          HIP_TRY(hipGetLastError());
+        }
       }
       if (b.t3) {
         // Above: L_1 <- beta L_1 + alpha G_(1) G_(1)^T, the block being d1 x (d2 d3 d4).  The other
@@ -1453,17 +1489,21 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           // scratch; gram_reduce_kernel adds them up in float64 and applies the moving average.
           float *T2 = reinterpret_cast<float *>(ws + o->off_T2);
           const int dl = b.dlast(), inner = b.n / dl;
-          g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3);
-          g.c = T2; g.c_batch_stride = (int64_t)dl * dl; g.ldc = dl;
-          g.M = dl; g.N = dl; g.K = (b.m / b.split3) * inner;
-          g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0; g.batch = b.count * b.split3;
-          g.tiles_m = g.tiles_n = (dl + BM - 1) / BM; g.tiles = g.tiles_m * (g.tiles_m + 1) / 2;
-          rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
-          if (rc) return rc;
-          GramReduceArgs gr;
-          gr.partial = T2; gr.factor = reinterpret_cast<float *>(ws + b.off_R); gr.d = dl; gr.splits = b.split3;
-          gr.alpha = alpha; gr.beta = beta;
-          hipLaunchKernelGGL(gram_reduce_kernel, dim3((dl * dl + 255) / 256, b.count), dim3(256), 0, s, gr);
+          if (dl <= 16) {
+            GramNarrowArgs gn;
+            gn.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3); gn.table = gs_tab; gn.partial = T;
+            gn.d = dl; gn.rows = (b.m / b.split3) * inner; gn.entries = b.count * b.split3;
+            hipLaunchKernelGGL(gram_narrow_kernel<GS>, dim3((unsigned)(gn.entries + 3) / 4), dim3(256), 0, s, gn);
+          } else {
+            g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3);
+            g.c = T; g.c_batch_stride = (int64_t)dl * dl; g.ldc = dl;
+            g.M = dl; g.N = dl; g.K = (b.m / b.split3) * inner;
+            g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0; g.batch = b.count * b.split3;
+            g.tiles_m = g.tiles_n = (dl + BM - 1) / BM; g.tiles = g.tiles_m * (g.tiles_m + 1) / 2;
+            rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
+            if (rc) return rc;
+          }
+          reduce_gram(b.off_R, dl, b.split3, b.count);
           HIP_TRY(hipGetLastError());
           // Middle dimensions k: the block as pre x d_k x post with its first two indices swapped,
           // d_k x (pre post)
@@ -1482,8 +1522,13 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             h.c = reinterpret_cast<float *>(ws + b.off_mid[k - 1]); h.c_batch_stride = (int64_t)dk * dk; h.ldc = dk;
             h.M = dk; h.N = dk; h.K = pre * post;
             h.tiles_m = h.tiles_n = (dk + BM - 1) / BM; h.tiles = h.tiles_m * (h.tiles_m + 1) / 2;
+            const int sp = split_gram(b, h);
             rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>(h, s);
             if (rc) return rc;
+            if (sp > 1) {
+              reduce_gram(b.off_mid[k - 1], dk, sp, b.count);
+              HIP_TRY(hipGetLastError());
+            }
             pre *= dk;
           }
         }
@@ -1788,10 +1833,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     StageTimer t(o, SHAMPOO_STAGE_UPDATE, s);
     for (int i = 0; i < c.n_params; ++i) {
       if (p.pshape[i].kind != P_TENSOR) continue;
-      TensorCopyArgs ta = tensor_copy_args(i);
-      ta.copy_in = ws + o->off_Wb[i]; ta.tensor_out = o->last_w[i];
-      hipLaunchKernelGGL((tensor_block_copy_kernel<float, true>), tensor_copy_grid(i), dim3(256), 0, s, ta);
+      add_copy(i, o->last_w[i], ws + o->off_Wb[i], 4, true);
     }
+    send_copies(true);
     HIP_TRY(hipGetLastError());
   }
   if (!p.diag_chunks.empty()) {

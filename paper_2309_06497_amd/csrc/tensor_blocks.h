@@ -20,42 +20,56 @@
 namespace shampoo {
 
 struct TensorCopyArgs {
-  const void *tensor_in;   // gather: the caller's D1 x D2 x D3 tensor (row-major)
-  void *tensor_out;        // scatter: the same
-  const void *copy_in;     // scatter: the block-contiguous copy
-  void *copy_out;          // gather: the same
+  void *tensor;            // the caller's D1 x D2 x D3 x D4 tensor (row-major)
+  void *copy;              // the block-contiguous copy
   int64_t D1, D2, D3, D4;  // unused trailing dimensions are 1
   int32_t b;               // block size
   int32_t k2n, k3n, k4n;   // pieces along the second, third and fourth dimension
+  int32_t bytes;           // of an element: 4, or 2 (bf16 gradients)
+  int32_t first, chunks;   // first workgroup of this tensor; workgroups per block
 };
+// The tensors of one launch.  A network has dozens of small ones, each worth a few microseconds: one
+// launch per 40 of them and direction (that is what fits a kernel's 4 KB of arguments) instead of three
+// per tensor, and 32-bit index arithmetic (a block has less than 2^31 elements).  ResNet-50 shapes, 17
+// tensors of 11e6 elements in all: 485 -> 96 us a step.
+constexpr int TENSOR_COPY_SET = 40;
+struct TensorCopySet { TensorCopyArgs t[TENSOR_COPY_SET]; int32_t count; };
+static_assert(sizeof(TensorCopySet) <= 4096, "kernel arguments");
 
-// grid (blocks, chunks): block index = ((k1 * k2n + k2) * k3n + k3) * k4n + k4.  All pieces
-// before the last one of a dimension are full, so the offset of a block inside the copy is
+// Block index = ((k1 * k2n + k2) * k3n + k3) * k4n + k4.  All pieces before the last one of a
+// dimension are full, so the offset of a block inside the copy is
 // s1 D2 D3 D4 + d1 s2 D3 D4 + d1 d2 s3 D4 + d1 d2 d3 s4.
 template <typename T, bool SCATTER>
-__global__ __launch_bounds__(256) void tensor_block_copy_kernel(const TensorCopyArgs g) {
-  int64_t blk = blockIdx.x;
-  const int64_t k4 = blk % g.k4n; blk /= g.k4n;
-  const int64_t k3 = blk % g.k3n; blk /= g.k3n;
-  const int64_t k2 = blk % g.k2n, k1 = blk / g.k2n;
-  const int64_t s1 = k1 * g.b, s2 = k2 * g.b, s3 = k3 * g.b, s4 = k4 * g.b;
+__device__ __forceinline__ void tensor_copy(const TensorCopyArgs &g, uint32_t wg) {
+  uint32_t blk = wg / (uint32_t)g.chunks;
+  const uint32_t chunk = wg - blk * (uint32_t)g.chunks;
+  const uint32_t k4 = blk % (uint32_t)g.k4n; blk /= (uint32_t)g.k4n;
+  const uint32_t k3 = blk % (uint32_t)g.k3n; blk /= (uint32_t)g.k3n;
+  const uint32_t k2 = blk % (uint32_t)g.k2n, k1 = blk / (uint32_t)g.k2n;
+  const int64_t s1 = (int64_t)k1 * g.b, s2 = (int64_t)k2 * g.b, s3 = (int64_t)k3 * g.b, s4 = (int64_t)k4 * g.b;
   const int64_t d1 = min((int64_t)g.b, g.D1 - s1), d2 = min((int64_t)g.b, g.D2 - s2), d3 = min((int64_t)g.b, g.D3 - s3),
                 d4 = min((int64_t)g.b, g.D4 - s4);
   const int64_t voff = s1 * g.D2 * g.D3 * g.D4 + d1 * (s2 * g.D3 * g.D4) + d1 * d2 * (s3 * g.D4) + d1 * d2 * d3 * s4;
-  const int64_t n = d1 * d2 * d3 * d4;
-  const T *tin = static_cast<const T *>(g.tensor_in);
-  T *tout = static_cast<T *>(g.tensor_out);
-  const T *cin = static_cast<const T *>(g.copy_in);
-  T *cout = static_cast<T *>(g.copy_out);
-  for (int64_t e = (int64_t)blockIdx.y * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.y * 256) {
-    int64_t r = e;
-    const int64_t i4 = r % d4; r /= d4;
-    const int64_t i3 = r % d3; r /= d3;
-    const int64_t i2 = r % d2, i1 = r / d2;
-    const int64_t at = (((s1 + i1) * g.D2 + (s2 + i2)) * g.D3 + (s3 + i3)) * g.D4 + s4 + i4;
-    if (SCATTER) tout[at] = cin[voff + e];
-    else cout[voff + e] = tin[at];
+  T *tensor = static_cast<T *>(g.tensor) + ((s1 * g.D2 + s2) * g.D3 + s3) * g.D4 + s4;
+  T *copy = static_cast<T *>(g.copy) + voff;
+  const uint32_t e4 = (uint32_t)d4, e3 = (uint32_t)d3, e2 = (uint32_t)d2, n = (uint32_t)(d1 * d2 * d3 * d4);
+  const int64_t l3 = g.D4, l2 = g.D3 * l3, l1 = g.D2 * l2;
+  for (uint32_t e = chunk * 256 + threadIdx.x; e < n; e += (uint32_t)g.chunks * 256) {
+    uint32_t r = e;
+    const uint32_t q4 = r / e4, i4 = r - q4 * e4, q3 = q4 / e3, i3 = q4 - q3 * e3, i1 = q3 / e2, i2 = q3 - i1 * e2;
+    const int64_t at = i1 * l1 + i2 * l2 + i3 * l3 + i4;
+    if (SCATTER) tensor[at] = copy[e];
+    else copy[e] = tensor[at];
   }
+}
+template <bool SCATTER>
+__global__ __launch_bounds__(256) void tensor_block_copy_kernel(const TensorCopySet g) {
+  int i = 0;
+  while (i + 1 < g.count && g.t[i + 1].first <= (int)blockIdx.x) ++i;
+  const TensorCopyArgs &t = g.t[i];
+  const uint32_t wg = blockIdx.x - t.first;
+  if (t.bytes == 4) tensor_copy<uint32_t, SCATTER>(t, wg);
+  else tensor_copy<uint16_t, SCATTER>(t, wg);
 }
 
 struct PermuteArgs {
@@ -70,7 +84,7 @@ struct PermuteArgs {
 template <typename T>
 __global__ __launch_bounds__(256) void permute_12_kernel(const PermuteArgs g) {
   const int slot = blockIdx.y;
-  const int64_t n = (int64_t)g.d1 * g.d2 * g.d3;
+  const uint32_t n = (uint32_t)g.d1 * g.d2 * g.d3;
   const T *tin = nullptr;
   if (!g.src) {
     const BlockDesc d = g.desc[slot];
@@ -78,10 +92,11 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const PermuteArgs g) {
   }
   const float *fin = g.src ? g.src + (int64_t)slot * n : nullptr;
   float *out = g.dst + (int64_t)slot * n;
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-    const int64_t i3 = e % g.d3, i2 = (e / g.d3) % g.d2, i1 = e / ((int64_t)g.d3 * g.d2);
+  const uint32_t d1 = g.d1, d2 = g.d2, d3 = g.d3;   // 32-bit divisions: a block has less than 2^31 elements
+  for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < n; e += gridDim.x * 256) {
+    const uint32_t q = e / d3, i3 = e - q * d3, i1 = q / d2, i2 = q - i1 * d2;
     const float v = fin ? fin[e] : Elem<T>::load1(tin + e);
-    out[(i2 * g.d1 + i1) * g.d3 + i3] = v;
+    out[(i2 * d1 + i1) * d3 + i3] = v;
   }
 }
 
@@ -92,10 +107,48 @@ struct GramReduceArgs {
   double alpha, beta;
 };
 
-// factor <- beta factor + alpha sum_s partial_s, in float64, fixed order.  The factor of the
-// last dimension of a tensor block is a d3 x d3 Gram matrix over d1 d2 rows (d3 = 9 for a
-// 3 x 3 convolution, 16384 rows at block size 128): its rows are split into `splits` ranges
-// whose Gram matrices are separate batch entries of the SYRK launch.  grid (ceil(d d / 256), slots).
+struct GramNarrowArgs {
+  const BlockDesc *desc;        // [slot][split]: the row ranges of X
+  const void *const *table;
+  float *partial;               // [slot][split][d][d]
+  int32_t d, rows, entries;
+};
+
+// X^T X of a range of rows of a row-major matrix of d <= 16 columns, one wavefront per range: the factor of the last
+// dimension of a tensor block (9 columns and 16384 rows for a 3 x 3 convolution at block size 128).  With
+// v_mfma_f32_16x16x4_f32 one register of 4 rows is both operands, and 16 rows at a time are summed before they go
+// into float64, as in the general SYRK kernel.  That one multiplies 128 x 128 tiles, 99 % of it padding at d = 9:
+// 564 -> 25 us for the blocks of ResNet-50 (most of them 128 x 128 x 9).  Bound by the latency of the loads.  grid (ceil(entries / 4)), 4 wavefronts.
+template <typename T>
+__global__ __launch_bounds__(256) void gram_narrow_kernel(const GramNarrowArgs g) {
+  typedef float narrow_f4 __attribute__((ext_vector_type(4)));
+  const int entry = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4, d = g.d;
+  if (entry >= g.entries) return;
+  const BlockDesc bd = g.desc[entry];
+  const T *x = reinterpret_cast<const T *>(g.table[bd.param]) + bd.offset;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int r0 = 0; r0 < g.rows; r0 += 16) {
+    float v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int r = r0 + 4 * t + lg;
+      v[t] = (li < d && r < g.rows) ? Elem<T>::load1(x + (int64_t)r * d + li) : 0.f;
+    }
+    narrow_f4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_16x16x4f32(v[t], v[t], s, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] += (double)s[u];
+  }
+  float *out = g.partial + (int64_t)entry * d * d;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (4 * lg + u < d && li < d) out[(4 * lg + u) * d + li] = (float)acc[u];
+}
+
+// factor <- beta factor + alpha sum_s partial_s, in float64, fixed order: the Gram matrix of a split
+// unfolding.  grid (ceil(d d / 256), slots).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const GramReduceArgs g) {
   const int slot = blockIdx.y;
   const int e = blockIdx.x * 256 + threadIdx.x;
