@@ -114,8 +114,9 @@ typedef struct {
                              for `stream` once per batch of factors                          */
   float newton_tolerance; /* stop when ||M_k - I||_inf < this; 0 selects 1e-6 (Sec. 3.2.1)     */
   int32_t newton_max_iterations; /* iteration cap, <= 1000; 0 selects 100                     */
-  int32_t precond_matrix_cores; /* SHAMPOO_MATRIX_CORES_AUTO (default): with bf16 gradients and blocks
-                             whose shape and alignment allow it, Lbar G Rbar runs on the fp16 matrix
+  int32_t precond_matrix_cores; /* SHAMPOO_MATRIX_CORES_AUTO (default): for blocks whose shape and
+                             alignment allow it (float32 or filtered gradients: also more than 128
+                             rows and columns), Lbar G Rbar runs on the fp16 matrix
                              cores from float32 operands split into two fp16 planes each, scaled
                              per block by a power of two (three exact products accumulated in
                              float32: float32 accuracy at 3/16 of the float32-MFMA time; elements

@@ -10,6 +10,8 @@
 // float32 product.  A bf16 operand (the gradient) is one exact fp16 term after scaling, which
 // leaves two products.  The fp16 matrix cores run 16x faster than the float32 ones, so three
 // products cost 3/16 of the float32-MFMA time (two: 1/8), with the same float32 accumulation.
+// Float32 directions (float32 gradients, filtered or shifted ones) take two planes of G^T, made
+// by split2h_transpose_kernel.
 // (Three bf16 terms per value would need no scaling, but six products and half as many more
 // operand bytes; this kernel is bound by operand delivery, so bytes decide.)
 //
@@ -26,7 +28,7 @@
 // step writes its result T directly as two planes.  C[i][j] = alpha * sum_k A[i][k] * B[j][k]:
 // both operands are read along k (row-major A; B given transposed, or symmetric).  The two
 // products of Sec. 2.3 of the paper have that form:
-//   T = Lbar G       A = Lbar (two planes)   B = G^T (the scaled fp16 transpose of the block, one plane)
+//   T = Lbar G       A = Lbar (two planes)   B = G^T (the scaled fp16 transpose of the block: one plane, or two of a float32 block)
 //   P = T Rbar       A = T (two planes)      B = Rbar (symmetric, two planes)
 //
 // Tile TM x 256 per workgroup of 4 wavefronts, one workgroup per CU: TM = 256 with 128 x 128 per
@@ -133,6 +135,54 @@ __global__ __launch_bounds__(256) void split2h_kernel(const float *in, const flo
   uint16_t h, l;
   split2h(in[i] * sc, h, l);
   out[i] = h; out[count + i] = l;
+}
+
+struct SplitTransposeArgs {
+  const BlockDesc *desc;
+  const void *const *g_table;
+  uint16_t *out; int64_t plane_stride;   // [plane][slot][n][m]
+  const float *scale;                    // [slot] s_G
+  int32_t m, n;
+};
+// The two fp16 terms of s_G G_block, transposed.  Reads 4 and writes 4 bytes per element, 16 bytes per lane on both
+// sides; the transposition happens in LDS (rows of 65 words: the 64 lanes of a read hit 64 banks).  Requires
+// m % 8 == 0, n % 8 == 0 and 16-byte aligned rows.  grid (ceil(n / 64), ceil(m / 64), blocks), 256 threads.
+__global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTransposeArgs g) {
+  __shared__ float tile[64][65];
+  const BlockDesc d = g.desc[blockIdx.z];
+  const float *src = reinterpret_cast<const float *>(g.g_table[d.param]) + d.offset;
+  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64, tid = threadIdx.x;
+  const float sc = g.scale[blockIdx.z];
+  float4 v[4];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    const int i = i0 + 16 * h + (tid >> 4), j = j0 + (tid & 15) * 4;
+    v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < g.m && j < g.n) v[h] = *reinterpret_cast<const float4 *>(src + (int64_t)i * d.ld + j);
+  }
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    float *t = &tile[16 * h + (tid >> 4)][(tid & 15) * 4];
+    t[0] = v[h].x * sc; t[1] = v[h].y * sc; t[2] = v[h].z * sc; t[3] = v[h].w * sc;
+  }
+  __syncthreads();
+  uint16_t *dst = g.out + (int64_t)blockIdx.z * g.m * g.n;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int x = tid + 256 * q, jr = x >> 3, c = (x & 7) * 8, i = i0 + c, j = j0 + jr;
+    if (j >= g.n || i >= g.m) continue;
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint16_t h0, l0, h1, l1;
+      split2h(tile[c + 2 * e][jr], h0, l0);
+      split2h(tile[c + 2 * e + 1][jr], h1, l1);
+      hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+      lo[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    }
+    *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.m + i) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    *reinterpret_cast<uint4 *>(dst + g.plane_stride + (int64_t)j * g.m + i) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+  }
 }
 
 // Scales of the fp16 operands of one bucket and step, all powers of two.  The gradient block

@@ -1065,10 +1065,13 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
       t2_elems = std::max(t2_elems, B * m * n);
     }
     b.off_P = take(B * m * n * 4);
-    // bf16 gradients: the preconditioning products run on the fp16 matrix cores from
-    // operands kept split in two scaled fp16 planes
-    b.planes = c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2 && !use_b1 &&
-               c->precond_matrix_cores != SHAMPOO_MATRIX_CORES_FP32;
+    // the preconditioning products run on the fp16 matrix cores from operands kept split in two
+    // scaled fp16 planes.  Float32 directions also have to be split in every step, and blocks of
+    // one 128-wide tile leave half of the 256-wide one idle: they keep the float32 matrix cores there.
+    // 96 blocks of 1024, both products: 3.9 ms on the float32 matrix cores, 1.2 + 0.14 (split) so, error
+    // of Lbar G Rbar 8.3e-7 and 5.3e-7; filtered gradients, blocks of 512 and 488: 1.75 and 0.72 + 0.09 ms
+    const bool dir32 = c->grad_dtype != SHAMPOO_GRAD_BF16 || use_l2 || use_b1;
+    b.planes = b.bf16_mfma && c->precond_matrix_cores != SHAMPOO_MATRIX_CORES_FP32 && (!dir32 || (b.m > BM && b.n > BN));
     if (b.planes) {
       b.off_Linv2h = take(B * m * m * 4);
       b.off_Rinv2h = take(B * n * n * 4);
@@ -1090,7 +1093,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
     t_elems = std::max(t_elems, B * m * n);   // float32, or two fp16 planes
-    if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
+    if (b.planes && dir32) b.off_Gt = take(B * m * n * 4);
+    else if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
     const bool warm = c->warm_start_roots != 0 && c->root_method == SHAMPOO_ROOT_EIGH;
@@ -1737,11 +1741,12 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         HIP_TRY(hipGetLastError());
         ssh_count = b.geom.chunks;
       }
-    } else if (use_shampoo && sizeof(GD) == 2 && sizeof(GS) == 2 && b.planes && o->ptrs_aligned16) {
-      // bf16 gradients: both products on the fp16 matrix cores, float32-accurate through
-      // two-plane splits of the float32 operands (Lbar, T, Rbar), each scaled by a power of two
-      // into the fp16 range; the gradient is one fp16 plane (exact: 8 significant bits).
-      // B operands are read along k: G^T is the scaled fp16 transpose made for the factor update.
+    } else if (use_shampoo && b.planes && o->ptrs_aligned16) {
+      // Both products on the fp16 matrix cores, float32-accurate through two-plane splits of the
+      // float32 operands (Lbar, T, Rbar), each scaled by a power of two into the fp16 range.  A bf16
+      // gradient is one fp16 plane (exact: 8 significant bits), the scaled transpose made for the factor
+      // update; a float32 one (or a filtered or shifted one) is split here, into the same place.
+      // B operands are read along k.
       const int tm128 = (b.m + 127) / 128, x2_tn = (b.n + X2_TN - 1) / X2_TN;
       // tiles of 256 rows (half the operand traffic per multiply) unless padding the rows to
       // 256 would add more than an eighth to the work
@@ -1755,19 +1760,25 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       const int64_t t_plane = (int64_t)b.count * b.m * b.n;
       {
       StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      if (refresh) launch_x2_scales(b);   // the roots, and with them their scales, have just changed
+      if (refresh || sizeof(GD) == 4) launch_x2_scales(b);   // on a refresh the roots, and with them their scales, have just changed
+      if constexpr (sizeof(GD) == 4) {
+        SplitTransposeArgs st;
+        st.desc = desc; st.g_table = gd_tab; st.out = reinterpret_cast<uint16_t *>(ws + b.off_Gt); st.plane_stride = t_plane;
+        st.scale = reinterpret_cast<const float *>(ws + b.off_s_g); st.m = b.m; st.n = b.n;
+        hipLaunchKernelGGL(split2h_transpose_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, st);
+      }
       GemmX2Args g{};
       g.a = reinterpret_cast<const uint16_t *>(ws + b.off_Linv2h);
       g.a_plane_stride = (int64_t)b.count * b.m * b.m; g.a_batch_stride = (int64_t)b.m * b.m; g.lda = b.m;
-      g.b = reinterpret_cast<const uint16_t *>(ws + b.off_Gt); g.b_plane_stride = 0;
+      g.b = reinterpret_cast<const uint16_t *>(ws + b.off_Gt); g.b_plane_stride = sizeof(GD) == 4 ? t_plane : 0;
       g.b_batch_stride = (int64_t)b.m * b.n; g.ldb = b.m;
       g.c2 = T2h; g.c2_plane_stride = t_plane; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
       g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.out_scale = reinterpret_cast<const float *>(ws + b.off_t_scale);
       g.tiles_m = h_tm; g.tiles_n = x2_tn; g.batch = b.count;
       if (tall)
-        hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, sizeof(GD) == 4 ? 2 : 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
       else
-        hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, sizeof(GD) == 4 ? 2 : 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
       }
       StageTimer t2(o, SHAMPOO_STAGE_PRECOND2, s);
       GemmX2Args h{};

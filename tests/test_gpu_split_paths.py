@@ -1,8 +1,10 @@
-"""Tensor blocks whose Gram matrices are formed in ranges, against the oracle (bars of test_gpu_parity.py)."""
+"""Tensor blocks whose Gram matrices are formed in ranges, and float32 gradients as two fp16 planes, against the
+oracle (bars of test_gpu_parity.py)."""
+import numpy as np
 import pytest
 
 from paper_2309_06497_amd import workloads as wl
-from test_gpu_parity import TensorPair
+from test_gpu_parity import Pair, TensorPair
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +26,31 @@ def test_more_tensors_than_one_copy_launch_holds():
     for t in range(2):
         p.step(wl.gaussian_grads(shapes, 72, t, 1e-2), 0.01, t)
         p.check(t)
+
+
+@pytest.mark.parametrize("name,sigma,eps,span", [("tiny", 1e-15, 1e-30, False), ("huge", 1e10, 1e20, False), ("rows", 1e-3, 1e-9, True)])
+def test_float32_gradients_on_the_fp16_matrix_cores(name, sigma, eps, span):
+    """Blocks with ragged tiles and ragged k (136 = 128 + 8, 264 = 256 + 8, k % 32 of 8, 16 and 24) whose gradients
+    are tiny, huge, or span six decades from row to row, and a zero block: factors, products, directions."""
+    shapes = [(256, 384), (392, 144), (152, 264)]
+    p = Pair(shapes, 256, 0.999, 1, eps=eps, eps_g=sigma * 1e-7)
+    for t in range(3):
+        g = wl.gaussian_grads(shapes, 73, t, sigma)
+        if span:
+            for x in g:
+                x *= (10.0 ** (-6.0 * np.arange(x.shape[0]) / x.shape[0]))[:, None].astype(np.float32)
+            g[0][:, 256:] = 0.0
+        p.step(g, 0.01, t)
+        worst, _ = p.check(t)
+        assert worst["gemm"] <= 2e-5, worst
+    for w in p.w_gpu:
+        assert np.isfinite(w.cpu().numpy()).all()
+
+
+def test_filtered_gradients_on_the_fp16_matrix_cores():
+    shapes = [(256, 384), (392, 144), (152, 264)]
+    for bf16 in (False, True):
+        p = Pair(shapes, 256, 0.999, 1, bf16=bf16, beta1=0.9, weight_decay=0.05, bias_correction=True, grafting="adam")
+        for t in range(3):
+            p.step(wl.gaussian_grads(shapes, 74, t, 1e-2), 0.01, t)
+            p.check(t)
