@@ -99,13 +99,15 @@ __device__ __forceinline__ void split2h(float x, uint16_t &h, uint16_t &l) {
 }
 
 // stats[2 b] = max |x_ij|, stats[2 b + 1] = max_i sum_j |x_ij| of the n x n matrix b.
-// grid (batch), 256 threads.
+// grid (batch, parts of the rows), 256 threads; stats start at zero (values are not negative, so that their
+// bits order like integers and the result does not depend on the order).  One workgroup per matrix read the 192
+// roots of two transformer layers at 0.45 TB/s, 1.7 ms of a refresh.
 __global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float *stats, int n) {
   __shared__ float red[8];
   const float *p = x + (int64_t)blockIdx.x * n * n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float mx = 0.f, rs = 0.f;
-  for (int i = wave; i < n; i += 4) {
+  for (int i = 4 * blockIdx.y + wave; i < n; i += 4 * gridDim.y) {
     float sum = 0.f;
     for (int j = lane; j < n; j += 64) {
       const float v = fabsf(p[(int64_t)i * n + j]);
@@ -121,20 +123,23 @@ __global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float
   if (lane == 0) { red[wave] = mx; red[4 + wave] = rs; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    stats[2 * blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    stats[2 * blockIdx.x + 1] = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+    int *out = reinterpret_cast<int *>(stats + 2 * blockIdx.x);
+    atomicMax(out, __float_as_int(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
+    atomicMax(out + 1, __float_as_int(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]))));
   }
 }
 
 // out[plane][i] = the two fp16 terms of s_b in[i], s_b = pow2_scale_f16(stats[2 b]) for the
-// matrix b = i / per that element i belongs to
+// matrix b that element i belongs to; per, its elements, is a multiple of 64.  grid (batch, ceil(per / 1024)), 256 threads.
 __global__ __launch_bounds__(256) void split2h_kernel(const float *in, const float *stats, uint16_t *out, int64_t per, int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= count) return;
-  const float sc = pow2_scale_f16(stats[2 * (i / per)]);
-  uint16_t h, l;
-  split2h(in[i] * sc, h, l);
-  out[i] = h; out[count + i] = l;
+  const int64_t e = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4, i = blockIdx.x * per + e;
+  if (e >= per) return;
+  const float sc = pow2_scale_f16(stats[2 * blockIdx.x]);
+  const float4 x = *reinterpret_cast<const float4 *>(in + i);
+  ushort4 h, l;
+  split2h(x.x * sc, h.x, l.x); split2h(x.y * sc, h.y, l.y); split2h(x.z * sc, h.z, l.z); split2h(x.w * sc, h.w, l.w);
+  *reinterpret_cast<ushort4 *>(out + i) = h;
+  *reinterpret_cast<ushort4 *>(out + count + i) = l;
 }
 
 struct SplitTransposeArgs {

@@ -1164,15 +1164,18 @@ struct StageTimer {
 int split_roots(shampoo_opt *o, hipStream_t s) {
   for (auto &b : o->plan.buckets) {
     if (!b.planes) continue;
-    const int64_t nl = (int64_t)b.count * b.m * b.m, nr = (int64_t)b.count * b.n * b.n;
     const float *Li = reinterpret_cast<const float *>(o->ws + b.off_Linv), *Ri = reinterpret_cast<const float *>(o->ws + b.off_Rinv);
     float *stat_l = reinterpret_cast<float *>(o->ws + b.off_stat_l), *stat_r = reinterpret_cast<float *>(o->ws + b.off_stat_r);
-    hipLaunchKernelGGL(matrix_stats_kernel, dim3(b.count), dim3(256), 0, s, Li, stat_l, b.m);
-    hipLaunchKernelGGL(matrix_stats_kernel, dim3(b.count), dim3(256), 0, s, Ri, stat_r, b.n);
-    hipLaunchKernelGGL(split2h_kernel, dim3((unsigned)((nl + 255) / 256)), dim3(256), 0, s,
-                       Li, stat_l, reinterpret_cast<uint16_t *>(o->ws + b.off_Linv2h), (int64_t)b.m * b.m, nl);
-    hipLaunchKernelGGL(split2h_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s,
-                       Ri, stat_r, reinterpret_cast<uint16_t *>(o->ws + b.off_Rinv2h), (int64_t)b.n * b.n, nr);
+    for (int side = 0; side < 2; ++side) {
+      const int n = side == 0 ? b.m : b.n;
+      const float *x = side == 0 ? Li : Ri;
+      float *stat = side == 0 ? stat_l : stat_r;
+      const int64_t per = (int64_t)n * n;
+      if (const int rc = launch_fill(stat, 0.f, 2 * (int64_t)b.count, s)) return rc;
+      hipLaunchKernelGGL(matrix_stats_kernel, dim3(b.count, std::max(1, std::min(32, n / 32))), dim3(256), 0, s, x, stat, n);
+      hipLaunchKernelGGL(split2h_kernel, dim3(b.count, (unsigned)((per + 1023) / 1024)), dim3(256), 0, s,
+                         x, stat, reinterpret_cast<uint16_t *>(o->ws + (side == 0 ? b.off_Linv2h : b.off_Rinv2h)), per, (int64_t)b.count * per);
+    }
     HIP_TRY(hipGetLastError());
   }
   return SHAMPOO_OK;
