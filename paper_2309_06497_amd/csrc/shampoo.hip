@@ -970,7 +970,7 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
     HIP_TRY(hipGetLastError());
     for (int k = 0; k <= max_iter; ++k) {
       g.k = k; g.M = M; g.X = X; g.T = T;
-      hipLaunchKernelGGL(newton_prep_kernel, dim3(n, cb), dim3(256), 0, s, g);
+      hipLaunchKernelGGL(newton_prep_kernel, dim3((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb), dim3(256), 0, s, g);
       hipLaunchKernelGGL(newton_check_kernel, dim3((cb + 255) / 256), dim3(256), 0, s, g, cb);
       HIP_TRY(hipGetLastError());
       // matrices whose iteration ended at this k hand their X over now: afterwards the X / M
@@ -980,7 +980,7 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
       fa.done = g.done; fa.failed = g.failed; fa.failed_out = failed_user ? failed_user + b0 : nullptr;
       fa.fail_count = fail_count;
       fa.iters = g.iters; fa.iters_out = iters_user ? iters_user + b0 : nullptr; fa.n = n; fa.k = k;
-      hipLaunchKernelGGL(newton_finish_kernel, dim3(n, cb), dim3(256), 0, s, fa);
+      hipLaunchKernelGGL(newton_finish_kernel, dim3((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb), dim3(256), 0, s, fa);
       HIP_TRY(hipGetLastError());
       if (k == max_iter) break;
       // T^p by repeated squaring, X' = X T, M' = T^p M
