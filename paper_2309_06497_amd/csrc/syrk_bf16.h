@@ -35,6 +35,14 @@
 // workgroup barrier of the loop is the bare s_barrier: the loads of later slabs stay in
 // flight across it.
 //
+// SPLIT: the factor update for float32 gradients.  X is kept as three scaled fp16 planes, s x = h + l + m (11 + 11
+// bits and the rest of the 24), and x x' as the six products h m' + m h' + l l' + h l' + l h' + h h', what is
+// left out being below 2^-32.  (Two planes and three products leave an error of 2^-23 in every x, which shows:
+// 8e-8 in the factor instead of 6e-8.)  Every 32 values of k are six slabs, one per product, summed in float32 with the
+// large product last (two roundings of full size), and go into float64 after the sixth.  Both factors of 96 blocks of 1024: 3.6 ms on
+// the float32 matrix cores, 2.1 ms so (660 TFLOP/s of fp16 products) and 0.15 ms for the planes; error of the factor
+// against float64 6.0e-8 and 5.0e-8 (one gradient), 5.0e-8 and 5.1e-8 (three).
+//
 // Only the tiles on and below the diagonal of tiles are computed and written; the mirror image
 // is left to mirror_upper_tiles_kernel: nothing in a step reads the tiles above the diagonal,
 // only the refresh and the state query do.
@@ -58,6 +66,7 @@ struct SyrkBf16Args {
   float *c; int64_t c_batch_stride; int32_t ldc;
   int32_t M, K;              // C is M x M
   double alpha, beta;
+  int64_t plane_stride;      // SPLIT: from plane to plane (h, l, m), elements
   const float *x_scale2;     // [batch] X holds fp16 values s x: 1 / s^2, applied with alpha (nullptr: X is bf16)
   int32_t tiles;             // lower-triangular tile count per batch entry
   int32_t batch;
@@ -77,8 +86,8 @@ __device__ __forceinline__ floatx16 syrk_mfma(floatx16 acc, const u32x4 &a0, con
 // Requires: operand base 16-byte aligned, ld % 8 == 0, K % 8 == 0 (checked by the host).
 // F16: the operand holds fp16 values (the scaled transpose of a bf16 block: products of two
 // such values are exact in float32 as well) and the fp16 matrix-core instruction is used.
-// ACC64: float64 accumulators, see the head of this file.
-template <bool F16, bool ACC64>
+// ACC64: float64 accumulators; SPLIT: three planes; see the head of this file.
+template <bool F16, bool ACC64, bool SPLIT = false>
 __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(const SyrkBf16Args g) {
   __shared__ __align__(128) unsigned char smem[SYRK_STAGES * SYRK_STAGE];   // the k-step addresses below differ by an XOR
   const int total = g.tiles * g.batch;
@@ -118,10 +127,15 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
   }
   // A tile on the diagonal multiplies a row panel by itself: only the B slab is loaded, and
   // the A operand is read from it as well.
-  const bool diag = ti == tj;
-  auto issue = [&](int stage, int k0) {
-    const char *ga = uniform_ptr(xa + k0);
-    const char *gb = uniform_ptr(xb + k0);
+  // With three planes the two operands of a product differ, but for two of the six.
+  static_assert(!SPLIT || (F16 && ACC64), "three planes");
+  const bool diag = !SPLIT && ti == tj;
+  // product `ph` of three planes: planes (0, 2) (2, 0) (1, 1) (0, 1) (1, 0) (0, 0)
+  auto plane_a = [&](int ph) { return SPLIT ? (ph == 1 ? 2 : ph == 2 || ph == 4 ? 1 : 0) * g.plane_stride : (int64_t)0; };
+  auto plane_b = [&](int ph) { return SPLIT ? (ph == 0 ? 2 : ph == 2 || ph == 3 ? 1 : 0) * g.plane_stride : (int64_t)0; };
+  auto issue = [&](int stage, int ph, int k0) {
+    const char *ga = uniform_ptr(xa + k0 + plane_a(ph));
+    const char *gb = uniform_ptr(xb + k0 + plane_b(ph));
     unsigned char *sa = smem + stage * SYRK_STAGE, *sb = sa + SYRK_SLAB;
 #pragma unroll
     for (int t = 0; t < PER_WAVE; ++t) {
@@ -150,12 +164,14 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
       }
 
   const int nk = g.K / SBK;                      // full slabs; K % SBK values of k remain
-  if (nk > 0) issue(0, 0);
-  if (nk > 1) issue(1, SBK);
+  constexpr int NP = SPLIT ? 6 : 1;              // products, each with slabs of its own
+  const int ns = NP * nk;
+  if (ns > 0) issue(0, 0, 0);
+  if (ns > 1) issue(1, 1, SPLIT ? 0 : SBK);
   u32x4 oa[2][2], ob[2][2];                      // [i or j][k step]
   // The eight operand reads of the slab in stage S, then the eight MFMAs of the wavefront's four
   // 32 x 32 tiles (the two of one tile four instructions apart).
-#define SYRK_SLAB_PRODUCT(S)                                                              \
+#define SYRK_SLAB_PRODUCT(S, PH)                                                          \
   {                                                                                       \
     LDS_DS_READ_B128(oa[0][0], la0, (S) * SYRK_STAGE);                                        \
     LDS_DS_READ_B128(ob[0][0], lb0, (S) * SYRK_STAGE + SYRK_SLAB);                            \
@@ -178,11 +194,11 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
     acc[1][0] = syrk_mfma<F16>(acc[1][0], oa[1][1], ob[0][1]);                            \
     acc[1][1] = syrk_mfma<F16>(acc[1][1], oa[1][1], ob[1][1]);                            \
     LDS_SCHED_BARRIER();                                                                  \
-    if constexpr (ACC64) {                                                                \
+    if (ACC64 && (!SPLIT || (PH) == 5)) {                                                 \
       _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_)                                    \
         _Pragma("unroll") for (int j_ = 0; j_ < 2; ++j_)                                  \
           _Pragma("unroll") for (int v_ = 0; v_ < 16; ++v_) {                             \
-            acc64[i_][j_][v_] += (double)acc[i_][j_][v_];                                 \
+            if constexpr (ACC64) acc64[i_][j_][v_] += (double)acc[i_][j_][v_];            \
             acc[i_][j_][v_] = 0.f;                                                        \
           }                                                                               \
     }                                                                                     \
@@ -193,30 +209,41 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
     // stage, while the first full slabs are on their way.
     const int k0 = nk * SBK;
 #pragma unroll
-    for (int t = 0; t < PER_WAVE; ++t) {
-      const int q = wave * PER_WAVE + t;
-      const bool kin = k0 + chunk_k[t] < g.K;      // K % 8 == 0: a chunk is entirely in or out
-      const uint4 va = kin ? *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(xa + k0) + offa[t]) : make_uint4(0, 0, 0, 0);
-      const uint4 vb = kin ? *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(xb + k0) + offb[t]) : make_uint4(0, 0, 0, 0);
-      *reinterpret_cast<uint4 *>(smem + (SYRK_STAGES - 1) * SYRK_STAGE + q * 1024 + lane * 16) = va;
-      *reinterpret_cast<uint4 *>(smem + (SYRK_STAGES - 1) * SYRK_STAGE + SYRK_SLAB + q * 1024 + lane * 16) = vb;
+    for (int ph = 0; ph < NP; ++ph) {
+      const uint16_t *pa = xa + k0 + plane_a(ph), *pb = xb + k0 + plane_b(ph);
+      if (ph > 0) __syncthreads();
+#pragma unroll
+      for (int t = 0; t < PER_WAVE; ++t) {
+        const int q = wave * PER_WAVE + t;
+        const bool kin = k0 + chunk_k[t] < g.K;      // K % 8 == 0: a chunk is entirely in or out
+        const uint4 va = kin ? *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(pa) + offa[t]) : make_uint4(0, 0, 0, 0);
+        const uint4 vb = kin ? *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(pb) + offb[t]) : make_uint4(0, 0, 0, 0);
+        *reinterpret_cast<uint4 *>(smem + (SYRK_STAGES - 1) * SYRK_STAGE + q * 1024 + lane * 16) = va;
+        *reinterpret_cast<uint4 *>(smem + (SYRK_STAGES - 1) * SYRK_STAGE + SYRK_SLAB + q * 1024 + lane * 16) = vb;
+      }
+      __syncthreads();
+      SYRK_SLAB_PRODUCT(SYRK_STAGES - 1, ph);
     }
-    __syncthreads();
-    SYRK_SLAB_PRODUCT(SYRK_STAGES - 1);
   }
   // Slab kt is multiplied while slabs kt + 1 and kt + 2 are on their way.
 #define SYRK_WAIT(N) { if (diag) { LDS_DMA_WAIT_VM((N) * PER_WAVE); } else { LDS_DMA_WAIT_VM((N) * PW); } }
-#define SYRK_STEP(S, NEXT, KT)                                                            \
+#define SYRK_STEP(S, NEXT, PH)                                                            \
   {                                                                                       \
-    if ((KT) + 1 < nk) SYRK_WAIT(1) else SYRK_WAIT(0)                                     \
+    const int q_ = kt + (PH);                                                             \
+    if (q_ + 1 < ns) SYRK_WAIT(1) else SYRK_WAIT(0)                                       \
     __builtin_amdgcn_s_barrier();                                                         \
-    if ((KT) + 2 < nk) issue(NEXT, ((KT) + 2) * SBK);                                     \
-    if ((KT) < nk) SYRK_SLAB_PRODUCT(S);                                                  \
+    if (q_ + 2 < ns) issue(NEXT, ((PH) + 2) % 6, (SPLIT ? (q_ + 2) / 6 : q_ + 2) * SBK);  \
+    if (q_ < ns) SYRK_SLAB_PRODUCT(S, PH);                                                \
   }
-  for (int kt = 0; kt < nk; kt += 3) {
-    SYRK_STEP(0, 2, kt);
-    SYRK_STEP(1, 0, kt + 1);
-    SYRK_STEP(2, 1, kt + 2);
+  for (int kt = 0; kt < ns; kt += SPLIT ? 6 : 3) {
+    SYRK_STEP(0, 2, 0);
+    SYRK_STEP(1, 0, 1);
+    SYRK_STEP(2, 1, 2);
+    if constexpr (SPLIT) {
+      SYRK_STEP(0, 2, 3);
+      SYRK_STEP(1, 0, 4);
+      SYRK_STEP(2, 1, 5);
+    }
   }
   LDS_DMA_WAIT_VM(0);
 
@@ -224,7 +251,8 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
   // accumulators, rows of 32 consecutive floats per half wavefront.  A tile on the diagonal is
   // stored whole: its elements (i, j) and (j, i) are the same products summed in the same order
   // by the matrix cores, from the same old values, so they carry the same bits and the factor
-  // stays exactly symmetric.  The tiles above the diagonal are mirror_upper_tiles_kernel's.
+  // stays exactly symmetric; with three planes the order differs, and its upper half is the mirror image of
+  // the lower.  The tiles above the diagonal are mirror_upper_tiles_kernel's.
   float *c = g.c + (int64_t)b * g.c_batch_stride;
   const int ldc = g.ldc;
   const double alpha = g.x_scale2 ? g.alpha * (double)g.x_scale2[b] : g.alpha;
@@ -259,7 +287,12 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
         double sum;
         if constexpr (ACC64) sum = acc64[mi][ni][v]; else sum = (double)acc[mi][ni][v];
         const float x = (float)(alpha * sum + g.beta * (double)old[ni][v]);
-        if (i < g.M && j < g.M) __builtin_nontemporal_store(x, c + (int64_t)i * ldc + j);
+        if constexpr (SPLIT) {
+          if (i < g.M && j < g.M && (ti != tj || j <= i)) {
+            __builtin_nontemporal_store(x, c + (int64_t)i * ldc + j);
+            if (ti == tj && j < i) c[(int64_t)j * ldc + i] = x;
+          }
+        } else if (i < g.M && j < g.M) __builtin_nontemporal_store(x, c + (int64_t)i * ldc + j);
       }
     }
   }
