@@ -130,11 +130,11 @@ __global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float
 }
 
 // out[plane][i] = the two fp16 terms of s_b in[i], s_b = pow2_scale_f16(stats[2 b]) for the
-// matrix b that element i belongs to; per, its elements, is a multiple of 64.  grid (batch, ceil(per / 1024)), 256 threads.
+// matrix b that element i belongs to; per, its elements, is a multiple of 64.  grid (ceil(per / 1024), batch), 256 threads.
 __global__ __launch_bounds__(256) void split2h_kernel(const float *in, const float *stats, uint16_t *out, int64_t per, int64_t count) {
-  const int64_t e = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4, i = blockIdx.x * per + e;
+  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, i = blockIdx.y * per + e;
   if (e >= per) return;
-  const float sc = pow2_scale_f16(stats[2 * blockIdx.x]);
+  const float sc = pow2_scale_f16(stats[2 * blockIdx.y]);
   const float4 x = *reinterpret_cast<const float4 *>(in + i);
   ushort4 h, l;
   split2h(x.x * sc, h.x, l.x); split2h(x.y * sc, h.y, l.y); split2h(x.z * sc, h.z, l.z); split2h(x.w * sc, h.w, l.w);
