@@ -355,8 +355,8 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
 // The panel products of the reduction: W22 <- H^T W22 H with H = I - V T V^T on rows and columns
 // r0 ... np - 1, r0 = 32 (k + 1).
 // ---------------------------------------------------------------------------
-// Z = W[:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
-// grid (ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows.  Memory bound (every element of W is
+// Z = W[r0:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
+// grid (ceil((np - r0) / 128), batch), 4 wavefronts of 32 rows.  Memory bound (every element of W is
 // read once for 64 multiply-adds); a lane reads 4 consecutive k of its row.
 __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
   __shared__ double red[4][1024];
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
         const int row = base + 16 * rt + band_row(lg, v);
         g.z[(int64_t)row * BAND + li] = acc[rt][0][v];
         g.z[(int64_t)row * BAND + 16 + li] = acc[rt][1][v];
-        if (base >= r0) {
+        {
           const double v0 = g.vp[(int64_t)row * BAND + li], v1 = g.vp[(int64_t)row * BAND + 16 + li];
           m1[0][0] = band_mfma(v0, acc[rt][0][v], m1[0][0]); m1[0][1] = band_mfma(v0, acc[rt][1][v], m1[0][1]);
           m1[1][0] = band_mfma(v1, acc[rt][0][v], m1[1][0]); m1[1][1] = band_mfma(v1, acc[rt][1][v], m1[1][1]);
@@ -451,8 +451,7 @@ __global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
     for (int kk = 0; kk < BAND; kk += 16) {
       const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + kk + 4 * lg;
       const band_d4 za = *reinterpret_cast<const band_d4 *>(g.z + at);
-      band_d4 va = {0, 0, 0, 0};
-      if (base >= r0) va = *reinterpret_cast<const band_d4 *>(g.vp + at);
+      const band_d4 va = *reinterpret_cast<const band_d4 *>(g.vp + at);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int kq = kk + 4 * lg + q;
@@ -471,9 +470,10 @@ __global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
   }
 }
 
-// W <- W - V Y^T - Y V^T on rows row0 ..., columns row0 ... (without the corner in front of r0 on the way
-// back).  grid (ceil((np - row0) / 128), ceil((np - row0) / 128), batch), 4 wavefronts of 32 rows, which
-// keep their rows of V and Y in registers and walk along the columns together, 16 at a time.
+// W <- W - V Y^T - Y V^T on rows and columns r0 ....  grid (ceil((np - r0) / 128), ceil((np - r0) / 128), batch), 4
+// wavefronts of 32 rows, which keep their rows of V and Y in registers and walk along the columns together, 16 at a
+// time.  Memory bound, 3.3 TB/s for 64 matrices of 1024.  Blocks below the diagonal only, with their mirror images stored
+// from the same registers, took 1 % off 16 matrices of 2048 and added 0.4 % to 64 of 1024: not kept.
 __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int k) {
   band_select(g, blockIdx.z);
   if (g.meta->skip) return;
@@ -481,11 +481,7 @@ __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int 
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
   if (base >= np) return;
-  const bool inner = base >= r0;        // V has these rows
-  int c0 = r0 + BAND_COLS * blockIdx.y;
-  const int c1 = min(c0 + BAND_COLS, np);
-  if (!inner) c0 = max(c0, r0);
-  if (c0 >= c1) return;
+  const int c0 = r0 + BAND_COLS * blockIdx.y, c1 = min(c0 + BAND_COLS, np);
   band_d4 va[2][2], ya[2][2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
@@ -493,8 +489,7 @@ __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int 
     for (int kk = 0; kk < 2; ++kk) {
       const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + 16 * kk + 4 * lg;
       ya[rt][kk] = *reinterpret_cast<const band_d4 *>(g.y + at);
-      va[rt][kk] = (band_d4){0, 0, 0, 0};
-      if (inner) va[rt][kk] = *reinterpret_cast<const band_d4 *>(g.vp + at);
+      va[rt][kk] = *reinterpret_cast<const band_d4 *>(g.vp + at);
     }
   for (int c = c0; c < c1; c += 16) {
     double *dst = g.w + (int64_t)base * np + c + li;
@@ -508,20 +503,15 @@ __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int 
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const int64_t at = (int64_t)(c + li) * BAND + 16 * kk + 4 * lg;
-      if (inner) {
-        const band_d4 yb = *reinterpret_cast<const band_d4 *>(g.y + at);
+      const band_d4 yb = *reinterpret_cast<const band_d4 *>(g.y + at), vb = *reinterpret_cast<const band_d4 *>(g.vp + at);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(va[rt][kk][q], yb[q], acc[rt]);
-      }
-      if (c >= r0) {
-        const band_d4 vb = *reinterpret_cast<const band_d4 *>(g.vp + at);
+        for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(va[rt][kk][q], yb[q], acc[rt]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-          for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(ya[rt][kk][q], vb[q], acc[rt]);
-      }
+        for (int rt = 0; rt < 2; ++rt) acc[rt] = band_mfma(ya[rt][kk][q], vb[q], acc[rt]);
     }
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
@@ -573,6 +563,9 @@ __device__ __forceinline__ int band_d_index(int r, int c) { return ((((r >> 4) *
 // Cholesky way); formed as a product with M^-1 it would lose the condition number of M in accuracy,
 // which for a pivot block with a few large eigenvalues and many tiny ones is everything.
 // row: 64 doubles of LDS.  Returns whether all pivots were positive.
+// INVERSE = false: only that answer and S.  The rows that pivots have left behind are not turned into an inverse,
+// and of the symmetric M and S only the three tiles on and above the diagonal are kept up: 32 instead of 48
+// multiply-adds per lane and pivot; bisection of 16 matrices of 2048 11.3 -> 8.8 ms of kernel time, their roots 44.2 -> 42.8.
 struct BandElim {
   double M[2][2][4], K[2][2][4], S[2][2][4];
   static __device__ __forceinline__ void load(double (&x)[2][2][4], const double *d, int li, int lg) {
@@ -586,6 +579,7 @@ struct BandElim {
   }
   __device__ __forceinline__ void begin(const double *d, int li, int lg) { load(S, d, li, lg); }
   // d, rt: D_i+1 and R^T, row-major; last: there is no next block
+  template <bool INVERSE = true>
   __device__ __forceinline__ bool step(const double *d, const double *rt, bool last, double sigma, double tiny, double *row, int li, int lg) {
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
@@ -602,8 +596,10 @@ struct BandElim {
 #pragma unroll 1
         for (int r4 = 0; r4 < 4; ++r4) {
           const int p = 16 * ti + 4 * v + r4;
+          const int t0 = INVERSE ? 0 : ti;   // tiles of rows in front of it are done with
           if (lg == r4) {
-            row[li] = M[ti][0][v]; row[16 + li] = M[ti][1][v];
+            if (t0 == 0) row[li] = M[ti][0][v];
+            row[16 + li] = M[ti][1][v];
             row[32 + li] = K[ti][0][v]; row[48 + li] = K[ti][1][v];
           }
           __syncthreads();
@@ -611,27 +607,29 @@ struct BandElim {
           if (!(pv > 0.0)) ok = false;
           if (!(pv > tiny)) pv = tiny;
           const double inv = rcp_newton(pv);
-          const double c0 = row[li], c1 = row[16 + li], k0 = row[32 + li], k1 = row[48 + li];
+          const double c0 = t0 == 0 ? row[li] : 0.0, c1 = row[16 + li], k0 = row[32 + li], k1 = row[48 + li];
           double f[2][4], h[2][4];
 #pragma unroll
           for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { f[t][u] = row[16 * t + lg + 4 * u] * inv; h[t][u] = row[32 + 16 * t + lg + 4 * u] * inv; }
+            for (int u = 0; u < 4; ++u) { f[t][u] = t >= t0 ? row[16 * t + lg + 4 * u] * inv : 0.0; h[t][u] = row[32 + 16 * t + lg + 4 * u] * inv; }
           __syncthreads();
           const bool mine = li == 4 * v + r4;
 #pragma unroll
           for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-              M[t][0][u] -= f[t][u] * c0;
-              M[t][1][u] -= f[t][u] * c1;
-              if (mine) M[t][ti][u] = f[t][u];
-              K[t][0][u] -= f[t][u] * k0;
-              K[t][1][u] -= f[t][u] * k1;
-              S[t][0][u] -= h[t][u] * k0;
+              if (t >= t0) {
+                if (INVERSE || t == 0) M[t][0][u] -= f[t][u] * c0;
+                M[t][1][u] -= f[t][u] * c1;
+                if (INVERSE && mine) M[t][ti][u] = f[t][u];
+                K[t][0][u] -= f[t][u] * k0;
+                K[t][1][u] -= f[t][u] * k1;
+              }
+              if (INVERSE || t == 0) S[t][0][u] -= h[t][u] * k0;
               S[t][1][u] -= h[t][u] * k1;
             }
-          if (lg == r4) {
+          if (INVERSE && lg == r4) {
             M[ti][0][v] = c0 * inv; M[ti][1][v] = c1 * inv;
             if (mine) M[ti][ti][v] = -inv;
             K[ti][0][v] = k0 * inv; K[ti][1][v] = k1 * inv;
@@ -699,7 +697,7 @@ __global__ __launch_bounds__(64) void band_probe_kernel(BandArgs g, const int ro
   bool ok = true;
   e.begin(g.dblk, li, lg);
   for (int i = 0; i < g.nb && ok; ++i)
-    ok = e.step(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == g.nb, -sigma, 1.0e-290, row, li, lg);
+    ok = e.step<false>(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == g.nb, -sigma, 1.0e-290, row, li, lg);
   if (lane == 0) g.ok[(round & 1) * BAND_SHIFTS + s] = ok ? 1 : 0;
 }
 
