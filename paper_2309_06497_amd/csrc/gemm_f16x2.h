@@ -147,6 +147,7 @@ struct SplitTransposeArgs {
   const void *const *g_table;
   uint16_t *out; int64_t plane_stride;   // [plane][slot][n][m]
   uint16_t *rows;                        // the same not transposed, [plane][slot][m][n] (nullptr: not wanted, and no third plane either)
+  uint16_t *out_m, *rows_m;              // the third planes
   const float *scale;                    // [slot] s_G
   int32_t m, n;
 };
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTrans
   }
   __syncthreads();
   const bool three = g.rows != nullptr;
-  auto put = [&](uint16_t *dst, const float (&x)[8]) {
+  auto put = [&](uint16_t *dst, uint16_t *dst_m, const float (&x)[8]) {
     uint32_t hi[4], lo[4], rest[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTrans
     }
     *reinterpret_cast<uint4 *>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     *reinterpret_cast<uint4 *>(dst + g.plane_stride) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    if (three) *reinterpret_cast<uint4 *>(dst + 2 * g.plane_stride) = make_uint4(rest[0], rest[1], rest[2], rest[3]);
+    if (three) *reinterpret_cast<uint4 *>(dst_m) = make_uint4(rest[0], rest[1], rest[2], rest[3]);
   };
   const int64_t block = (int64_t)blockIdx.z * g.m * g.n;
 #pragma unroll
@@ -202,12 +203,14 @@ __global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTrans
     if (j0 + r < g.n && i0 + c < g.m) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[e] = tile[c + e][r];
-      put(g.out + block + (int64_t)(j0 + r) * g.m + i0 + c, t);
+      const int64_t at = block + (int64_t)(j0 + r) * g.m + i0 + c;
+      put(g.out + at, g.out_m + at, t);
     }
     if (g.rows && i0 + r < g.m && j0 + c < g.n) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[e] = tile[r][c + e];
-      put(g.rows + block + (int64_t)(i0 + r) * g.n + j0 + c, t);
+      const int64_t at = block + (int64_t)(i0 + r) * g.n + j0 + c;
+      put(g.rows + at, g.rows_m + at, t);
     }
   }
 }

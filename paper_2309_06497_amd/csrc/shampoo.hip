@@ -85,7 +85,10 @@ struct Bucket {
   size_t off_QtL = 0, off_QtR = 0;   // warm start: eigenvectors of the previous refresh, [count][np][np] float32
   size_t off_Gt = 0;     // 16-bit transpose of the bucket's gradient blocks (bf16, or scaled fp16 where the fp16 products follow), made by the factor update and
                          // read again by the first preconditioning product of the same step
-  size_t off_Gp = 0;     // float32 gradients that feed the factors and the directions: three fp16 planes of the block as it lies
+  // float32 gradients that feed the factors and the directions: three fp16 planes of the block both ways round for
+  // the factor update.  Two of the transpose stay in Gt; two of the block as it lies are in T, and both third
+  // ones in P, which the products write later in the same step
+  bool split_factor = false;
   bool planes = false;
   EwGeom geom;
   int32_t tiles_m, tiles_n;
@@ -1100,11 +1103,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
     t_elems = std::max(t_elems, B * m * n);   // float32, or two fp16 planes
-    if (b.planes && dir32) {
-      // filtered directions: two planes; else the gradient feeds the factors too: three planes, both ways round
-      b.off_Gt = take(B * m * n * (use_b1 ? 4 : 6));
-      if (!use_b1) b.off_Gp = take(B * m * n * 6);
-    }
+    b.split_factor = b.planes && dir32 && !use_b1;   // the directions' gradient feeds the factors too
+    if (b.planes && dir32) b.off_Gt = take(B * m * n * 4);
     else if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
@@ -1415,7 +1415,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     SplitTransposeArgs st;
     st.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); st.g_table = gd_tab;
     st.out = reinterpret_cast<uint16_t *>(ws + b.off_Gt); st.plane_stride = (int64_t)b.count * b.m * b.n;
-    st.rows = b.off_Gp ? reinterpret_cast<uint16_t *>(ws + b.off_Gp) : nullptr;
+    const bool three = b.split_factor && use_shampoo;
+    st.rows = three ? reinterpret_cast<uint16_t *>(T) : nullptr;
+    st.out_m = reinterpret_cast<uint16_t *>(ws + b.off_P); st.rows_m = st.out_m + st.plane_stride;
     st.scale = reinterpret_cast<const float *>(ws + b.off_s_g); st.m = b.m; st.n = b.n;
     hipLaunchKernelGGL(split2h_transpose_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, st);
   };
@@ -1479,18 +1481,21 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         }
       }
       HIP_TRY(hipGetLastError());
-    } else if (sizeof(GS) == 4 && b.off_Gp && o->ptrs_aligned16) {
-      // float32 gradients: both factors from three fp16 planes, of which the preconditioning products take two
+    } else if (sizeof(GS) == 4 && b.split_factor && use_shampoo && o->ptrs_aligned16) {
+      // float32 gradients: both factors from three fp16 planes, of which the preconditioning products take two.
+      // (While only grafting is on, P is not written and keeps what the state query shows: float32 matrix cores.)
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
       launch_x2_scales(b);
       launch_split_transpose(b);
       o->upper_stale[&b - p.buckets.data()] = 1;
       SyrkBf16Args sa{};
       sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
-      sa.plane_stride = (int64_t)b.count * b.m * b.n; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
+      const uint16_t *Gt = reinterpret_cast<const uint16_t *>(ws + b.off_Gt), *Gm = reinterpret_cast<const uint16_t *>(ws + b.off_P);
+      sa.plane_l = (int64_t)b.count * b.m * b.n; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
       for (int side = 0; side < 2; ++side) {
         const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
-        sa.a.base = ws + (side == 0 ? b.off_Gp : b.off_Gt); sa.a.batch_stride = (int64_t)b.m * b.n;
+        const uint16_t *x = side == 0 ? reinterpret_cast<const uint16_t *>(T) : Gt;
+        sa.a.base = x; sa.plane_m = (side == 0 ? Gm + sa.plane_l : Gm) - x; sa.a.batch_stride = (int64_t)b.m * b.n;
         sa.a.ld = sa.K = side == 0 ? b.n : b.m;
         sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)); sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = dim;
         sa.M = dim; sa.tiles = tiles * (tiles + 1) / 2;
@@ -1802,7 +1807,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       const int64_t t_plane = (int64_t)b.count * b.m * b.n;
       {
       StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      const bool split = sizeof(GD) == 4 && !b.off_Gp;   // not yet split, and not yet scaled, for the factor update
+      const bool split = sizeof(GD) == 4 && !b.split_factor;   // not yet split, and not yet scaled, for the factor update
       if (refresh || split) launch_x2_scales(b);   // on a refresh the roots, and with them their scales, have just changed
       if (split) launch_split_transpose(b);
       GemmX2Args g{};

@@ -66,7 +66,7 @@ struct SyrkBf16Args {
   float *c; int64_t c_batch_stride; int32_t ldc;
   int32_t M, K;              // C is M x M
   double alpha, beta;
-  int64_t plane_stride;      // SPLIT: from plane to plane (h, l, m), elements
+  int64_t plane_l, plane_m;  // SPLIT: from the plane of the h to those of the l and of the m, elements
   const float *x_scale2;     // [batch] X holds fp16 values s x: 1 / s^2, applied with alpha (nullptr: X is bf16)
   int32_t tiles;             // lower-triangular tile count per batch entry
   int32_t batch;
@@ -131,8 +131,8 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
   static_assert(!SPLIT || (F16 && ACC64), "three planes");
   const bool diag = !SPLIT && ti == tj;
   // product `ph` of three planes: planes (0, 2) (2, 0) (1, 1) (0, 1) (1, 0) (0, 0)
-  auto plane_a = [&](int ph) { return SPLIT ? (ph == 1 ? 2 : ph == 2 || ph == 4 ? 1 : 0) * g.plane_stride : (int64_t)0; };
-  auto plane_b = [&](int ph) { return SPLIT ? (ph == 0 ? 2 : ph == 2 || ph == 3 ? 1 : 0) * g.plane_stride : (int64_t)0; };
+  auto plane_a = [&](int ph) { return SPLIT ? (ph == 1 ? g.plane_m : ph == 2 || ph == 4 ? g.plane_l : 0) : (int64_t)0; };
+  auto plane_b = [&](int ph) { return SPLIT ? (ph == 0 ? g.plane_m : ph == 2 || ph == 3 ? g.plane_l : 0) : (int64_t)0; };
   auto issue = [&](int stage, int ph, int k0) {
     const char *ga = uniform_ptr(xa + k0 + plane_a(ph));
     const char *gb = uniform_ptr(xb + k0 + plane_b(ph));
