@@ -22,6 +22,7 @@
 #include "elementwise.h"
 #include "gemm_f16x2.h"
 #include "gemm_mfma.h"
+#include "gram_split.h"
 #include "newton_root.h"
 #include "root_band.h"
 #include "root_tridiag.h"
@@ -1389,17 +1390,12 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
     hipLaunchKernelGGL(x2_scales_kernel, dim3(b.count), dim3(64), 0, s, xs);
   };
-  // Tensor blocks: the Gram matrix of an unfolding d x N / d is a tile or a few per block over a long k, which
-  // leaves most of the CUs idle.  k is cut into ranges of at least 64 until there are about four workgroups per
-  // CU; their Gram matrices go through T (it holds m n values per block, splits d^2 of them are needed) and are
-  // added in float64.  The blocks of ResNet-50, most of them 128 x 1152 twice: 706 us whole, 200 + 66 us cut.
+  // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through T: it holds
+  // the m n values of every block of the bucket.
   auto split_gram = [&](const Bucket &b, GemmArgs &g) {
-    const int64_t most = std::min<int64_t>((int64_t)b.m * b.n / ((int64_t)g.M * g.M), g.K / 64);
-    const int64_t want = (1024 + (int64_t)g.tiles * g.batch - 1) / ((int64_t)g.tiles * g.batch);
-    if (std::min(want, most) <= 1) return 1;
-    g.krange = (int32_t)((g.K / std::min(want, most) + BK - 1) / BK * BK);
-    g.ksplit = (g.K + g.krange - 1) / g.krange;
-    if (g.ksplit <= 1) { g.ksplit = 0; return 1; }
+    const GramSplit sp = gram_split(g.K, (int64_t)b.m * b.n / ((int64_t)g.M * g.M), (int64_t)g.tiles * g.batch, BK);
+    if (sp.ranges <= 1) return 1;
+    g.ksplit = sp.ranges; g.krange = sp.range;
     g.c = T; g.batch *= g.ksplit;
     g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0;
     return (int)g.ksplit;

@@ -20,6 +20,17 @@ def test_last_dimension_around_the_narrow_gram_kernel(last, bf16):
         p.check(t)
 
 
+@pytest.mark.parametrize("shape,b", [((72, 64, 3, 3), 128), ((128, 100, 3, 3), 128), ((128, 96, 5, 5), 128), ((144, 64, 3, 3), 256)])
+def test_long_unfoldings_that_the_ranges_do_not_divide(shape, b):
+    """One block that is the largest of its set, so that the scratch is no larger than its own m n; the number of
+    ranges is bounded by that scratch, and k is no multiple of it."""
+    shapes = [shape]
+    p = TensorPair(shapes, b, 0.99, 2)
+    for t in range(2):
+        p.step(wl.gaussian_grads(shapes, 75, t, 1e-2), 0.01, t)
+        p.check(t)
+
+
 def test_more_tensors_than_one_copy_launch_holds():
     shapes = [(3, 5, 7), (4, 6, 2), (5, 5, 5)] * 9 + [(6, 7)]
     p = TensorPair(shapes, 6, 0.99, 1)
