@@ -146,13 +146,10 @@ struct SplitTransposeArgs {
   const BlockDesc *desc;
   const void *const *g_table;
   uint16_t *out; int64_t plane_stride;   // [plane][slot][n][m]
-  uint16_t *rows;                        // the same not transposed, [plane][slot][m][n] (nullptr: not wanted, and no third plane either)
-  uint16_t *out_m, *rows_m;              // the third planes
   const float *scale;                    // [slot] s_G
   int32_t m, n;
 };
-// The two fp16 terms of s_G G_block, transposed; where the block also feeds the factors (syrk_bf16.h) three terms,
-// h + l + m = s_G G to 24 bits, transposed and as they lie.  Reads 4 and writes 4 (12) bytes per element, 16 bytes per lane on both
+// The two fp16 terms of s_G G_block, transposed.  Reads 4 and writes 4 bytes per element, 16 bytes per lane on both
 // sides; the transposition happens in LDS (rows of 65 words: the 64 lanes of a read hit 64 banks).  Requires
 // m % 8 == 0, n % 8 == 0 and 16-byte aligned rows.  grid (ceil(n / 64), ceil(m / 64), blocks), 256 threads.
 __global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTransposeArgs g) {
@@ -174,44 +171,22 @@ __global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTrans
     t[0] = v[h].x * sc; t[1] = v[h].y * sc; t[2] = v[h].z * sc; t[3] = v[h].w * sc;
   }
   __syncthreads();
-  const bool three = g.rows != nullptr;
-  auto put = [&](uint16_t *dst, uint16_t *dst_m, const float (&x)[8]) {
-    uint32_t hi[4], lo[4], rest[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint16_t h[2], l[2], r[2];
-#pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        const float y = x[2 * e + f];
-        split2h(y, h[f], l[f]);
-        const float left = (y - (float)__builtin_bit_cast(_Float16, h[f])) - (float)__builtin_bit_cast(_Float16, l[f]);
-        r[f] = __builtin_bit_cast(uint16_t, (_Float16)left);
-      }
-      hi[e] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-      lo[e] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
-      rest[e] = (uint32_t)r[0] | ((uint32_t)r[1] << 16);
-    }
-    *reinterpret_cast<uint4 *>(dst) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *reinterpret_cast<uint4 *>(dst + g.plane_stride) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    if (three) *reinterpret_cast<uint4 *>(dst_m) = make_uint4(rest[0], rest[1], rest[2], rest[3]);
-  };
-  const int64_t block = (int64_t)blockIdx.z * g.m * g.n;
+  uint16_t *dst = g.out + (int64_t)blockIdx.z * g.m * g.n;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    const int x = tid + 256 * q, r = x >> 3, c = (x & 7) * 8;
-    float t[8];
-    if (j0 + r < g.n && i0 + c < g.m) {
+    const int x = tid + 256 * q, jr = x >> 3, c = (x & 7) * 8, i = i0 + c, j = j0 + jr;
+    if (j >= g.n || i >= g.m) continue;
+    uint32_t hi[4], lo[4];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = tile[c + e][r];
-      const int64_t at = block + (int64_t)(j0 + r) * g.m + i0 + c;
-      put(g.out + at, g.out_m + at, t);
+    for (int e = 0; e < 4; ++e) {
+      uint16_t h0, l0, h1, l1;
+      split2h(tile[c + 2 * e][jr], h0, l0);
+      split2h(tile[c + 2 * e + 1][jr], h1, l1);
+      hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+      lo[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
     }
-    if (g.rows && i0 + r < g.m && j0 + c < g.n) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = tile[r][c + e];
-      const int64_t at = block + (int64_t)(i0 + r) * g.n + j0 + c;
-      put(g.rows + at, g.rows_m + at, t);
-    }
+    *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.m + i) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    *reinterpret_cast<uint4 *>(dst + g.plane_stride + (int64_t)j * g.m + i) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
   }
 }
 

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/shampoo.h"
+#include "bf16_planes.h"
 #include "block_step_small.h"
 #include "congruence_f64.h"
 #include "diag_shampoo.h"
@@ -86,10 +87,10 @@ struct Bucket {
   size_t off_QtL = 0, off_QtR = 0;   // warm start: eigenvectors of the previous refresh, [count][np][np] float32
   size_t off_Gt = 0;     // 16-bit transpose of the bucket's gradient blocks (bf16, or scaled fp16 where the fp16 products follow), made by the factor update and
                          // read again by the first preconditioning product of the same step
-  // float32 gradients that feed the factors and the directions: three fp16 planes of the block both ways round for
-  // the factor update.  Two of the transpose stay in Gt; two of the block as it lies are in T, and both third
-  // ones in P, which the products write later in the same step
+  // float32 gradients that feed the factors and the directions: three bf16 planes of the block both ways round for
+  // the factor update, of the transpose in Gt3, of the block as it lies in T, which the products write later in the same step
   bool split_factor = false;
+  size_t off_Gt3 = 0;
   bool planes = false;
   EwGeom geom;
   int32_t tiles_m, tiles_n;
@@ -1059,7 +1060,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   const size_t offG1tab = take((size_t)c->n_params * sizeof(void *));
   const size_t offGftab = take((size_t)c->n_params * sizeof(void *));
   const size_t offPrep = (use_l2 || use_b1) ? take(std::max<size_t>(1, p.prep_chunks.size()) * sizeof(DiagChunk)) : 0;
-  size_t t_elems = 0, t2_elems = 0, eig_bytes = 0, max_count = 1;
+  size_t t_bytes = 0, t2_elems = 0, eig_bytes = 0, max_count = 1;
   std::vector<EigLayout> eL, eR, eM[2];
   for (auto &b : p.buckets) {
     const size_t B = b.count, m = b.m, n = b.n;
@@ -1103,8 +1104,9 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_sshp = take(B * ssh_parts * 4);
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
-    t_elems = std::max(t_elems, B * m * n);   // float32, or two fp16 planes
     b.split_factor = b.planes && dir32 && !use_b1;   // the directions' gradient feeds the factors too
+    t_bytes = std::max(t_bytes, B * m * n * (b.split_factor ? 6 : 4));   // float32, two fp16 planes or three bf16 planes
+    if (b.split_factor) b.off_Gt3 = take(B * m * n * 6);
     if (b.planes && dir32) b.off_Gt = take(B * m * n * 4);
     else if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
@@ -1123,7 +1125,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
                                              std::max(eM[0].back().bytes, eM[1].back().bytes)));
     max_count = std::max(max_count, (size_t)b.count);
   }
-  const size_t offT = take(t_elems * 4);
+  const size_t offT = take(t_bytes);
   const size_t offT2 = t2_elems ? take(t2_elems * 4) : 0;
   std::vector<size_t> offGb(c->n_params, 0), offWb(c->n_params, 0);
   bool has_tensor = false;
@@ -1411,9 +1413,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     SplitTransposeArgs st;
     st.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); st.g_table = gd_tab;
     st.out = reinterpret_cast<uint16_t *>(ws + b.off_Gt); st.plane_stride = (int64_t)b.count * b.m * b.n;
-    const bool three = b.split_factor && use_shampoo;
-    st.rows = three ? reinterpret_cast<uint16_t *>(T) : nullptr;
-    st.out_m = reinterpret_cast<uint16_t *>(ws + b.off_P); st.rows_m = st.out_m + st.plane_stride;
     st.scale = reinterpret_cast<const float *>(ws + b.off_s_g); st.m = b.m; st.n = b.n;
     hipLaunchKernelGGL(split2h_transpose_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, st);
   };
@@ -1478,25 +1477,27 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       }
       HIP_TRY(hipGetLastError());
     } else if (sizeof(GS) == 4 && b.split_factor && use_shampoo && o->ptrs_aligned16) {
-      // float32 gradients: both factors from three fp16 planes, of which the preconditioning products take two.
-      // (While only grafting is on, P is not written and keeps what the state query shows: float32 matrix cores.)
+      // float32 gradients: both factors from three bf16 planes
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
       launch_x2_scales(b);
       launch_split_transpose(b);
+      BlockPlanesArgs bp;
+      bp.desc = desc; bp.g_table = gs_tab; bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g); bp.m = b.m; bp.n = b.n;
+      bp.cols = reinterpret_cast<uint16_t *>(ws + b.off_Gt3); bp.rows = reinterpret_cast<uint16_t *>(T);
+      bp.plane_stride = (int64_t)b.count * b.m * b.n;
+      hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, bp);
       o->upper_stale[&b - p.buckets.data()] = 1;
       SyrkBf16Args sa{};
       sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
-      const uint16_t *Gt = reinterpret_cast<const uint16_t *>(ws + b.off_Gt), *Gm = reinterpret_cast<const uint16_t *>(ws + b.off_P);
-      sa.plane_l = (int64_t)b.count * b.m * b.n; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
+      sa.plane = bp.plane_stride; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
       for (int side = 0; side < 2; ++side) {
         const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
-        const uint16_t *x = side == 0 ? reinterpret_cast<const uint16_t *>(T) : Gt;
-        sa.a.base = x; sa.plane_m = (side == 0 ? Gm + sa.plane_l : Gm) - x; sa.a.batch_stride = (int64_t)b.m * b.n;
+        sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;
         sa.a.ld = sa.K = side == 0 ? b.n : b.m;
         sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)); sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = dim;
         sa.M = dim; sa.tiles = tiles * (tiles + 1) / 2;
         const int64_t per = ((int64_t)sa.tiles * sa.batch + NUM_XCD - 1) / NUM_XCD;
-        hipLaunchKernelGGL((syrk_bf16_kernel<true, true, true>), dim3((unsigned)(per * NUM_XCD)), dim3(GEMM_THREADS), 0, s, sa);
+        hipLaunchKernelGGL((syrk_bf16_kernel<false, true, true>), dim3((unsigned)(per * NUM_XCD)), dim3(GEMM_THREADS), 0, s, sa);
       }
       HIP_TRY(hipGetLastError());
     } else {

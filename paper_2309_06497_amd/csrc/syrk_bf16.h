@@ -35,13 +35,13 @@
 // workgroup barrier of the loop is the bare s_barrier: the loads of later slabs stay in
 // flight across it.
 //
-// SPLIT: the factor update for float32 gradients.  X is kept as three scaled fp16 planes, s x = h + l + m (11 + 11
-// bits and the rest of the 24), and x x' as the six products h m' + m h' + l l' + h l' + l h' + h h', what is
-// left out being below 2^-32.  (Two planes and three products leave an error of 2^-23 in every x, which shows:
-// 8e-8 in the factor instead of 6e-8.)  Every 32 values of k are six slabs, one per product, summed in float32 with the
-// large product last (two roundings of full size), and go into float64 after the sixth.  Both factors of 96 blocks of 1024: 3.6 ms on
-// the float32 matrix cores, 2.1 ms so (660 TFLOP/s of fp16 products) and 0.15 ms for the planes; error of the factor
-// against float64 6.0e-8 and 5.0e-8 (one gradient), 5.0e-8 and 5.1e-8 (three).
+// SPLIT: the factor update for float32 gradients.  X is kept as three bf16 planes (bf16_planes.h), which hold its 24
+// bits at any size of an element, and x x' as the six products h m' + m h' + l l' + h l' + l h' + h h'.  (Two planes and
+// three products leave an error of 2^-16 in every x.)  Every 32 values of k are six slabs, one per product, summed in
+// float32 with the large product last (two roundings of full size), and go into float64 after the sixth.
+// Both factors of 96 blocks of 1024: 3.6 ms on the float32 matrix cores, 2.3 ms so with the planes.  Error of the factor
+// against float64 6.0e-8 and 4.6e-8 (one gradient), 5.0e-8 and 4.9e-8 (three); of a row 10^-8 of the largest, by its own
+// norm, 2.6e-9 and 1.9e-9 an element.
 //
 // Only the tiles on and below the diagonal of tiles are computed and written; the mirror image
 // is left to mirror_upper_tiles_kernel: nothing in a step reads the tiles above the diagonal,
@@ -66,8 +66,8 @@ struct SyrkBf16Args {
   float *c; int64_t c_batch_stride; int32_t ldc;
   int32_t M, K;              // C is M x M
   double alpha, beta;
-  int64_t plane_l, plane_m;  // SPLIT: from the plane of the h to those of the l and of the m, elements
-  const float *x_scale2;     // [batch] X holds fp16 values s x: 1 / s^2, applied with alpha (nullptr: X is bf16)
+  int64_t plane;             // SPLIT: from a plane to the next, elements
+  const float *x_scale2;     // [batch] X holds values s x: 1 / s^2, applied with alpha (nullptr: X itself)
   int32_t tiles;             // lower-triangular tile count per batch entry
   int32_t batch;
 };
@@ -128,11 +128,11 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
   // A tile on the diagonal multiplies a row panel by itself: only the B slab is loaded, and
   // the A operand is read from it as well.
   // With three planes the two operands of a product differ, but for two of the six.
-  static_assert(!SPLIT || (F16 && ACC64), "three planes");
+  static_assert(!SPLIT || (!F16 && ACC64), "three planes");
   const bool diag = !SPLIT && ti == tj;
   // product `ph` of three planes: planes (0, 2) (2, 0) (1, 1) (0, 1) (1, 0) (0, 0)
-  auto plane_a = [&](int ph) { return SPLIT ? (ph == 1 ? g.plane_m : ph == 2 || ph == 4 ? g.plane_l : 0) : (int64_t)0; };
-  auto plane_b = [&](int ph) { return SPLIT ? (ph == 0 ? g.plane_m : ph == 2 || ph == 3 ? g.plane_l : 0) : (int64_t)0; };
+  auto plane_a = [&](int ph) { return SPLIT ? (ph == 1 ? 2 : ph == 2 || ph == 4 ? 1 : 0) * g.plane : (int64_t)0; };
+  auto plane_b = [&](int ph) { return SPLIT ? (ph == 0 ? 2 : ph == 2 || ph == 3 ? 1 : 0) * g.plane : (int64_t)0; };
   auto issue = [&](int stage, int ph, int k0) {
     const char *ga = uniform_ptr(xa + k0 + plane_a(ph));
     const char *gb = uniform_ptr(xb + k0 + plane_b(ph));

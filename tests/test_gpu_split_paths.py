@@ -1,8 +1,9 @@
-"""Tensor blocks whose Gram matrices are formed in ranges, and float32 gradients as two fp16 planes, against the
-oracle (bars of test_gpu_parity.py)."""
+"""Tensor blocks whose Gram matrices are formed in ranges, and float32 gradients split into planes, against the
+oracle (bars of test_gpu_parity.py) and, element by element, against float64."""
 import numpy as np
 import pytest
 
+from paper_2309_06497_amd import binding as B
 from paper_2309_06497_amd import workloads as wl
 from test_gpu_parity import Pair, TensorPair
 
@@ -37,6 +38,34 @@ def test_more_tensors_than_one_copy_launch_holds():
     for t in range(2):
         p.step(wl.gaussian_grads(shapes, 72, t, 1e-2), 0.01, t)
         p.check(t)
+
+
+@pytest.mark.parametrize("shape,decades", [((256, 384), (8, 0)), ((392, 144), (0, 12)), ((152, 264), (10, 10))])
+def test_small_rows_and_columns_keep_their_accuracy_in_the_factors(shape, decades):
+    """Rows (columns) that are many decades below the largest: every element of a factor, measured by the norms of the
+    two rows it is a product of.  Bound: 2^-24 for the float32 it is stored in; the matrix cores add up 32 values of
+    k in 12 steps, 12 x 2^-24 of their share at worst; 2^-24 for the products left out: 14 x 2^-24, once per gradient."""
+    import torch
+    m, n = shape
+    beta = float(np.float32(0.999))
+    opt = B.Shampoo([shape], 512, 0.999, 1e-12, 0.25, 1000, 0)
+    w = [torch.zeros(shape, device="cuda")]
+    L, R = np.zeros((m, m)), np.zeros((n, n))
+    steps = 2
+    for t in range(steps):
+        g = np.random.default_rng(80 + t).standard_normal(shape) * 1e-3
+        g *= 10.0 ** (-decades[0] * np.arange(m) / m)[:, None] * 10.0 ** (-decades[1] * np.arange(n) / n)[None, :]
+        g = g.astype(np.float32)
+        opt.step(w, [torch.from_numpy(g).cuda()], 0.0, t)
+        g = g.astype(np.float64)
+        L = beta * L + (1.0 - beta) * g @ g.T
+        R = beta * R + (1.0 - beta) * g.T @ g
+    for which, want in ((B.GET_L, L), (B.GET_R, R)):
+        got = opt.get(0, 0, which).cpu().numpy()
+        d = np.sqrt(np.diag(want))
+        err = np.abs(got - want) / np.outer(d, d)
+        assert np.array_equal(got, got.T)
+        assert err.max() <= 14 * steps * 2.0 ** -24, (which, err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
 @pytest.mark.parametrize("name,sigma,eps,span", [("tiny", 1e-15, 1e-30, False), ("huge", 1e10, 1e20, False), ("rows", 1e-3, 1e-9, True)])
