@@ -88,9 +88,9 @@ struct Bucket {
   size_t off_Gt = 0;     // 16-bit transpose of the bucket's gradient blocks (bf16, or scaled fp16 where the fp16 products follow), made by the factor update and
                          // read again by the first preconditioning product of the same step
   // float32 gradients that feed the factors and the directions: three bf16 planes of the block both ways round for
-  // the factor update, of the transpose in Gt3, of the block as it lies in T, which the products write later in the same step
+  // the factor update, in T, of so many blocks at a time
   bool split_factor = false;
-  size_t off_Gt3 = 0;
+  int32_t plane_chunk = 0;
   bool planes = false;
   EwGeom geom;
   int32_t tiles_m, tiles_n;
@@ -1048,6 +1048,10 @@ struct shampoo_opt {
 
 namespace {
 
+// Planes of float32 gradients live only as long as the products that read them: those of 170 blocks of 1024 x 1024
+// at a time (both ways round 12 bytes per element), which is 24 tiles per CU of each product.
+constexpr size_t PLANE_BYTES = (size_t)2 << 30;
+
 size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t r = off; off += align_up(bytes); return r; };
@@ -1105,8 +1109,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
     b.split_factor = b.planes && dir32 && !use_b1;   // the directions' gradient feeds the factors too
-    t_bytes = std::max(t_bytes, B * m * n * (b.split_factor ? 6 : 4));   // float32, two fp16 planes or three bf16 planes
-    if (b.split_factor) b.off_Gt3 = take(B * m * n * 6);
+    t_bytes = std::max(t_bytes, B * m * n * 4);   // float32, or two fp16 planes
+    if (b.split_factor) t_bytes = std::max(t_bytes, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
     if (b.planes && dir32) b.off_Gt = take(B * m * n * 4);
     else if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
@@ -1126,6 +1130,11 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     max_count = std::max(max_count, (size_t)b.count);
   }
   const size_t offT = take(t_bytes);
+  for (auto &b : p.buckets) {            // even shares
+    if (!b.split_factor) continue;
+    const int64_t most = std::min<int64_t>(b.count, (int64_t)(t_bytes / ((size_t)12 * b.m * b.n))), passes = (b.count + most - 1) / most;
+    b.plane_chunk = (int32_t)((b.count + passes - 1) / passes);
+  }
   const size_t offT2 = t2_elems ? take(t2_elems * 4) : 0;
   std::vector<size_t> offGb(c->n_params, 0), offWb(c->n_params, 0);
   bool has_tensor = false;
@@ -1481,23 +1490,27 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
       launch_x2_scales(b);
       launch_split_transpose(b);
-      BlockPlanesArgs bp;
-      bp.desc = desc; bp.g_table = gs_tab; bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g); bp.m = b.m; bp.n = b.n;
-      bp.cols = reinterpret_cast<uint16_t *>(ws + b.off_Gt3); bp.rows = reinterpret_cast<uint16_t *>(T);
-      bp.plane_stride = (int64_t)b.count * b.m * b.n;
-      hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, bp);
       o->upper_stale[&b - p.buckets.data()] = 1;
-      SyrkBf16Args sa{};
-      sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
-      sa.plane = bp.plane_stride; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
-      for (int side = 0; side < 2; ++side) {
-        const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
-        sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;
-        sa.a.ld = sa.K = side == 0 ? b.n : b.m;
-        sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)); sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = dim;
-        sa.M = dim; sa.tiles = tiles * (tiles + 1) / 2;
-        const int64_t per = ((int64_t)sa.tiles * sa.batch + NUM_XCD - 1) / NUM_XCD;
-        hipLaunchKernelGGL((syrk_bf16_kernel<false, true, true>), dim3((unsigned)(per * NUM_XCD)), dim3(GEMM_THREADS), 0, s, sa);
+      for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
+        const int cnt = std::min(b.plane_chunk, b.count - b0);
+        BlockPlanesArgs bp;
+        bp.desc = desc + b0; bp.g_table = gs_tab; bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g) + b0; bp.m = b.m; bp.n = b.n;
+        bp.plane_stride = (int64_t)cnt * b.m * b.n;
+        bp.cols = reinterpret_cast<uint16_t *>(T); bp.rows = bp.cols + 3 * bp.plane_stride;
+        hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, cnt), dim3(256), 0, s, bp);
+        SyrkBf16Args sa{};
+        sa.alpha = alpha; sa.beta = beta; sa.batch = cnt;
+        sa.plane = bp.plane_stride; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2) + b0;
+        for (int side = 0; side < 2; ++side) {
+          const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
+          sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;
+          sa.a.ld = sa.K = side == 0 ? b.n : b.m;
+          sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = sa.M = dim;
+          sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)) + b0 * sa.c_batch_stride;
+          sa.tiles = tiles * (tiles + 1) / 2;
+          const int64_t per = ((int64_t)sa.tiles * sa.batch + NUM_XCD - 1) / NUM_XCD;
+          hipLaunchKernelGGL((syrk_bf16_kernel<false, true, true>), dim3((unsigned)(per * NUM_XCD)), dim3(GEMM_THREADS), 0, s, sa);
+        }
       }
       HIP_TRY(hipGetLastError());
     } else {

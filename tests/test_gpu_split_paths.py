@@ -68,6 +68,27 @@ def test_small_rows_and_columns_keep_their_accuracy_in_the_factors(shape, decade
         assert err.max() <= 14 * steps * 2.0 ** -24, (which, err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
+def test_more_blocks_than_the_planes_have_room_for():
+    """181 blocks of 1024 x 1024, whose planes are made for 91 and then for 90 at a time: the blocks at the edges of the two
+    parts, against float64 products of the same values."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    n, count = 1024, 181
+    opt = B.Shampoo([(n, n * count)], n, 0.999, 1e-12, 0.25, 1000, 0)
+    g = torch.randn(n, n * count, generator=gen, device="cuda") * torch.logspace(-4, -2, n * count, device="cuda")
+    opt.step([torch.zeros_like(g)], [g], 0.0, 0)
+    rel = lambda a, b: float((a.double() - b).norm() / b.norm())
+    alpha = 1.0 - float(np.float32(0.999))
+    for k in (0, 90, 91, 180):
+        blk = g[:, n * k:n * (k + 1)].double()
+        assert rel(opt.get(0, k, B.GET_L), alpha * blk @ blk.T) <= 1e-6, k
+        assert rel(opt.get(0, k, B.GET_R), alpha * blk.T @ blk) <= 1e-6, k
+        want = opt.get(0, k, B.GET_LINV).double() @ blk @ opt.get(0, k, B.GET_RINV).double()
+        assert rel(opt.get(0, k, B.GET_PSH), want) <= 2e-5, k
+    opt.destroy()
+
+
 @pytest.mark.parametrize("name,sigma,eps,span", [("tiny", 1e-15, 1e-30, False), ("huge", 1e10, 1e20, False), ("rows", 1e-3, 1e-9, True)])
 def test_float32_gradients_on_the_fp16_matrix_cores(name, sigma, eps, span):
     """Blocks with ragged tiles and ragged k (136 = 128 + 8, 264 = 256 + 8, k % 32 of 8, 16 and 24) whose gradients
