@@ -115,13 +115,15 @@ typedef struct {
   float newton_tolerance; /* stop when ||M_k - I||_inf < this; 0 selects 1e-6 (Sec. 3.2.1)     */
   int32_t newton_max_iterations; /* iteration cap, <= 1000; 0 selects 100                     */
   int32_t precond_matrix_cores; /* SHAMPOO_MATRIX_CORES_AUTO (default): for blocks whose shape and
-                             alignment allow it (float32 or filtered gradients: also more than 128
-                             rows and columns), Lbar G Rbar runs on the fp16 matrix
-                             cores from float32 operands split into two fp16 planes each, scaled
-                             per block by a power of two (three exact products accumulated in
+                             alignment allow it, Lbar G Rbar runs on the 16-bit matrix cores from split
+                             operands.  bf16 gradients: float32 operands as two fp16 planes each, scaled
+                             per block by a power of two (exact products accumulated in
                              float32: float32 accuracy at 3/16 of the float32-MFMA time; elements
                              below 2^-16 of a block's largest keep absolute, not relative,
-                             accuracy); SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA          */
+                             accuracy).  Float32 or filtered gradients, more than 128 rows and columns:
+                             three bf16 planes each, all 24 bits of every element, six products;
+                             the factor updates of float32 gradients take the same planes.
+                             SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA          */
   int32_t warm_start_roots; /* != 0: the eigendecomposition of a refresh starts from the eigenvectors of
                              the previous one (Sec. 3.2.1, 4.3: between refreshes a factor changes
                              little) instead of from the identity: W = Q^T L Q is formed (float64

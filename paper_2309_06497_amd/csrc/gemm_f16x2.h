@@ -10,10 +10,15 @@
 // float32 product.  A bf16 operand (the gradient) is one exact fp16 term after scaling, which
 // leaves two products.  The fp16 matrix cores run 16x faster than the float32 ones, so three
 // products cost 3/16 of the float32-MFMA time (two: 1/8), with the same float32 accumulation.
-// Float32 directions (float32 gradients, filtered or shifted ones) take two planes of G^T, made
-// by split2h_transpose_kernel.
-// (Three bf16 terms per value would need no scaling, but six products and half as many more
-// operand bytes; this kernel is bound by operand delivery, so bytes decide.)
+// (Three bf16 terms per value hold all 24 bits at any size, but take six products and half as many more
+// operand bytes; a bf16 gradient has no more than 8 bits to lose.)
+//
+// Float32 directions (float32 gradients, filtered or shifted ones) take three bf16 planes of every operand
+// (bf16_planes.h): there the small rows of G carry 24 bits of their own, which fp16 planes under one scale per block
+// would cut.  The product of the h planes has accumulators of its own, so that only it is rounded at full size.
+// Lbar G Rbar of 96 blocks of 1024: 3.8 ms on the float32 matrix cores, 2.2 ms so, planes of G and all (1.2 ms with two fp16
+// planes); error against the float64 product of the same roots 8.2e-7 and 2.8e-7, of a row 10^-8 of the largest 6.5e-7 and
+// 2.5e-7 of its own norm (3.7e-4 with two fp16 planes).
 //
 // Scaling.  Each matrix has one scale, chosen from a bound on its largest element so that the
 // scaled values stay below 2^14 (pow2_scale_f16): elements down to 2^-16 of the bound keep both
@@ -51,6 +56,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "bf16_planes.h"
 #include "gemm_mfma.h"
 #include "lds_dma.h"
 
@@ -63,14 +69,14 @@ constexpr int X2_B_SLAB = X2_TN * X2_BK * 2;   // bytes of one plane of the B sl
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // X2_STORE_NORM: float32 result and per-tile sums of squares; X2_STORE_SPLIT: the result as
-// two fp16 planes
+// two fp16 planes, or three bf16 ones where the operands have three
 enum { X2_STORE_NORM = 0, X2_STORE_SPLIT = 1 };
 
 struct GemmX2Args {
-  const uint16_t *a; int64_t a_plane_stride, a_batch_stride; int32_t lda;   // [plane][batch][M][K] fp16
-  const uint16_t *b; int64_t b_plane_stride, b_batch_stride; int32_t ldb;   // [plane][batch][N][K] fp16
+  const uint16_t *a; int64_t a_plane_stride, a_batch_stride; int32_t lda;   // [plane][batch][M][K] fp16 or bf16
+  const uint16_t *b; int64_t b_plane_stride, b_batch_stride; int32_t ldb;   // [plane][batch][N][K] fp16 or bf16
   float *c;                // X2_STORE_NORM: [batch][M][N] float32
-  uint16_t *c2;            // X2_STORE_SPLIT: [plane][batch][M][N] fp16
+  uint16_t *c2;            // X2_STORE_SPLIT: [plane][batch][M][N] fp16 or bf16
   int64_t c2_plane_stride;
   int64_t c_batch_stride; int32_t ldc;
   int32_t M, N, K;
@@ -129,64 +135,24 @@ __global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float
   }
 }
 
-// out[plane][i] = the two fp16 terms of s_b in[i], s_b = pow2_scale_f16(stats[2 b]) for the
+// out[plane][i] = the two fp16 or three bf16 terms of s_b in[i], s_b = pow2_scale_f16(stats[2 b]) for the
 // matrix b that element i belongs to; per, its elements, is a multiple of 64.  grid (ceil(per / 1024), batch), 256 threads.
-__global__ __launch_bounds__(256) void split2h_kernel(const float *in, const float *stats, uint16_t *out, int64_t per, int64_t count) {
+template <bool THREE>
+__global__ __launch_bounds__(256) void split_roots_kernel(const float *in, const float *stats, uint16_t *out, int64_t per, int64_t count) {
   const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, i = blockIdx.y * per + e;
   if (e >= per) return;
   const float sc = pow2_scale_f16(stats[2 * blockIdx.y]);
   const float4 x = *reinterpret_cast<const float4 *>(in + i);
-  ushort4 h, l;
-  split2h(x.x * sc, h.x, l.x); split2h(x.y * sc, h.y, l.y); split2h(x.z * sc, h.z, l.z); split2h(x.w * sc, h.w, l.w);
-  *reinterpret_cast<ushort4 *>(out + i) = h;
-  *reinterpret_cast<ushort4 *>(out + count + i) = l;
-}
-
-struct SplitTransposeArgs {
-  const BlockDesc *desc;
-  const void *const *g_table;
-  uint16_t *out; int64_t plane_stride;   // [plane][slot][n][m]
-  const float *scale;                    // [slot] s_G
-  int32_t m, n;
-};
-// The two fp16 terms of s_G G_block, transposed.  Reads 4 and writes 4 bytes per element, 16 bytes per lane on both
-// sides; the transposition happens in LDS (rows of 65 words: the 64 lanes of a read hit 64 banks).  Requires
-// m % 8 == 0, n % 8 == 0 and 16-byte aligned rows.  grid (ceil(n / 64), ceil(m / 64), blocks), 256 threads.
-__global__ __launch_bounds__(256) void split2h_transpose_kernel(const SplitTransposeArgs g) {
-  __shared__ float tile[64][65];
-  const BlockDesc d = g.desc[blockIdx.z];
-  const float *src = reinterpret_cast<const float *>(g.g_table[d.param]) + d.offset;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64, tid = threadIdx.x;
-  const float sc = g.scale[blockIdx.z];
-  float4 v[4];
+  if constexpr (THREE) {
+    uint16_t q[4][3];
+    split3b(x.x * sc, q[0]); split3b(x.y * sc, q[1]); split3b(x.z * sc, q[2]); split3b(x.w * sc, q[3]);
 #pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const int i = i0 + 16 * h + (tid >> 4), j = j0 + (tid & 15) * 4;
-    v[h] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < g.m && j < g.n) v[h] = *reinterpret_cast<const float4 *>(src + (int64_t)i * d.ld + j);
-  }
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    float *t = &tile[16 * h + (tid >> 4)][(tid & 15) * 4];
-    t[0] = v[h].x * sc; t[1] = v[h].y * sc; t[2] = v[h].z * sc; t[3] = v[h].w * sc;
-  }
-  __syncthreads();
-  uint16_t *dst = g.out + (int64_t)blockIdx.z * g.m * g.n;
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int x = tid + 256 * q, jr = x >> 3, c = (x & 7) * 8, i = i0 + c, j = j0 + jr;
-    if (j >= g.n || i >= g.m) continue;
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint16_t h0, l0, h1, l1;
-      split2h(tile[c + 2 * e][jr], h0, l0);
-      split2h(tile[c + 2 * e + 1][jr], h1, l1);
-      hi[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-      lo[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-    }
-    *reinterpret_cast<uint4 *>(dst + (int64_t)j * g.m + i) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    *reinterpret_cast<uint4 *>(dst + g.plane_stride + (int64_t)j * g.m + i) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    for (int t = 0; t < 3; ++t) *reinterpret_cast<ushort4 *>(out + t * count + i) = make_ushort4(q[0][t], q[1][t], q[2][t], q[3][t]);
+  } else {
+    ushort4 h, l;
+    split2h(x.x * sc, h.x, l.x); split2h(x.y * sc, h.y, l.y); split2h(x.z * sc, h.z, l.z); split2h(x.w * sc, h.w, l.w);
+    *reinterpret_cast<ushort4 *>(out + i) = h;
+    *reinterpret_cast<ushort4 *>(out + count + i) = l;
   }
 }
 
@@ -247,19 +213,28 @@ __global__ __launch_bounds__(64) void x2_scales_kernel(const X2ScaleArgs g) {
                                                              __builtin_bit_cast(f16x8, B_[j_]), acc[i_][j_], 0, 0, 0); \
   }
 
-// TM x 256 workgroup tile of wavefront tiles WM x 128.  NB: planes of B (2, or 1 for the scaled
-// gradient); A always has two.
+// The same with bf16 planes (two 32-row tiles of A): 8 MFMAs into ACC
+#define X3_GROUP(ACC, A_, B_)                                                                             \
+  {                                                                                                       \
+    _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_)                                                      \
+      _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_)                                                    \
+        ACC[i_][j_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A_[i_]),         \
+                                                              __builtin_bit_cast(bf16x8, B_[j_]), ACC[i_][j_], 0, 0, 0); \
+  }
+
+// TM x 256 workgroup tile of wavefront tiles WM x 128.  NB: planes of B: 1 (the scaled gradient) or 2 fp16 ones
+// against two of A, or three bf16 planes of both.
 template <int TM, int WM, int NB, int EPI>
 __global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const GemmX2Args g) {
   static_assert((TM == 128 && WM == 64) || (TM == 256 && (WM == 64 || WM == 128)), "wavefront tiles of 64 or 128 rows");
-  static_assert(NB == 1 || NB == 2, "planes of B");
-  constexpr int NA = 2;
+  static_assert(NB == 1 || NB == 2 || (NB == 3 && TM == 128), "planes of B");
+  constexpr int NA = NB == 3 ? 3 : 2;
   constexpr int MI = WM / 32;                  // 32-row MFMA tiles per wavefront
   constexpr int NW = TM / WM * 2;              // wavefronts, as TM / WM x 2
   constexpr int AL = TM / (16 * NW);           // 1 KiB pieces of an A plane slab that one wavefront loads
   constexpr int BL = 16 / NW;                  // and of a B plane slab
   constexpr int A_SLAB = TM * X2_BK * 2;       // bytes of one plane of the A slab
-  // TM = 128: 48 KB (2 + 2 planes), 32 KB (2 + 1); TM = 256: 64 KB (2 + 2), 48 KB (2 + 1)
+  // TM = 128: 72 KB (3 + 3 planes), 48 KB (2 + 2), 32 KB (2 + 1); TM = 256: 64 KB (2 + 2), 48 KB (2 + 1)
   constexpr int STAGE = NA * A_SLAB + NB * X2_B_SLAB;
   constexpr int NST = STAGE > 49152 ? 2 : 3;
   static_assert(NST * STAGE <= 147456, "LDS");
@@ -333,6 +308,18 @@ __global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const Gemm
   // step; ay / by0 the h planes at the second k step, whose l planes go into the registers that
   // b1 and a[0] have left by then
   u32x4 a[2][MI], b0[4], b1[4], ay[1][MI], by0[4];
+  // three planes: of A and B at the first k step, into whose l and m registers those of the second go as they become
+  // free; the h planes at the second; and the accumulators of all products but h h'
+  u32x4 a3[3][2], b3[3][4], ah[2], bh[4];
+  floatx16 rest[NB == 3 ? 2 : 1][NB == 3 ? 4 : 1];
+  if constexpr (NB == 3) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) rest[i][j][v] = 0.f;
+  }
 
   // One 1 KiB piece of the next slab: the loads are spread between the MFMA groups, so that a
   // wavefront never queues more than the texture path takes at once (a wavefront stalled on
@@ -349,7 +336,47 @@ __global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const Gemm
     for (int s = 0; s < NA; ++s) ga[s] = uniform_ptr(pa + s * g.a_plane_stride + k0);
 #pragma unroll
     for (int u = 0; u < NB; ++u) gb[u] = uniform_ptr(pb + u * g.b_plane_stride + k0);
-    if constexpr (NB == 1) {
+    if constexpr (NB == 3) {
+      // planes (h, l, m) of both operands: h h', then h l', l h', l l', h m', m h' per k step.  Not more than 16 reads are on
+      // their way at a time; the wait counts are the reads issued after the ones waited for (2 per A plane, 4 per B plane)
+#define X3_RD_A(D, S, LA) { X2_DS_READ(D[0], LA, (S) * A_SLAB); X2_DS_READ(D[1], LA, (S) * A_SLAB + 2048); }
+#define X3_WAIT_A(N, A_) asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(A_[0]), "+v"(A_[1]) :: "memory")
+#define X3_WAIT_B(N, B_) asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(B_[0]), "+v"(B_[1]), "+v"(B_[2]), "+v"(B_[3]) :: "memory")
+#define X3_WAIT_AB(N, A_, B_) asm volatile("s_waitcnt lgkmcnt(" #N ")" : "+v"(A_[0]), "+v"(A_[1]), "+v"(B_[0]), "+v"(B_[1]), "+v"(B_[2]), "+v"(B_[3]) :: "memory")
+      X3_RD_A(a3[0], 0, la); X2_RD_B(b3[0], 0, lb); X2_RD_B(b3[1], 1, lb); X3_RD_A(a3[1], 1, la); X2_RD_B(b3[2], 2, lb);
+      X2_SB();
+      X3_WAIT_AB(10, a3[0], b3[0]); X2_SB();            // outstanding: bl al bm
+      X3_GROUP(acc, a3[0], b3[0]); X3_RD_A(a3[2], 2, la);
+      if (feed) { X2_DMA_A(0, 0); X2_DMA_A(0, 1); } X2_SB();
+      X3_WAIT_B(8, b3[1]); X2_SB();                     // al bm am
+      X3_GROUP(rest, a3[0], b3[1]); if (feed) { X2_DMA_A(1, 0); X2_DMA_A(1, 1); } X2_SB();
+      X3_WAIT_A(6, a3[1]); X2_SB();                     // bm am
+      X3_GROUP(rest, a3[1], b3[0]); X3_RD_A(ah, 0, la1); X2_RD_B(bh, 0, lb1);
+      if (feed) { X2_DMA_A(2, 0); X2_DMA_A(2, 1); } X2_SB();
+      X3_GROUP(rest, a3[1], b3[1]); if (feed) { X2_DMA_B(0, 0); X2_DMA_B(0, 1); } X2_SB();
+      X3_WAIT_B(8, b3[2]); X2_SB();                     // am ah' bh'
+      X3_GROUP(rest, a3[0], b3[2]); X2_RD_B(b3[1], 1, lb1); X3_RD_A(a3[1], 1, la1);   // bl', al'
+      if (feed) { X2_DMA_B(0, 2); X2_DMA_B(0, 3); } X2_SB();
+      X3_WAIT_A(12, a3[2]); X2_SB();                    // ah' bh' bl' al'
+      X3_GROUP(rest, a3[2], b3[0]); X2_RD_B(b3[2], 2, lb1);   // bm'
+      if (feed) { X2_DMA_B(1, 0); X2_DMA_B(1, 1); } X2_SB();
+      X3_WAIT_AB(10, ah, bh); X2_SB();                  // bl' al' bm'
+      X3_GROUP(acc, ah, bh); X3_RD_A(a3[2], 2, la1);    // am'
+      if (feed) { X2_DMA_B(1, 2); X2_DMA_B(1, 3); } X2_SB();
+      X3_WAIT_B(8, b3[1]); X2_SB();                     // al' bm' am'
+      X3_GROUP(rest, ah, b3[1]); if (feed) { X2_DMA_B(2, 0); X2_DMA_B(2, 1); } X2_SB();
+      X3_WAIT_A(6, a3[1]); X2_SB();                     // bm' am'
+      X3_GROUP(rest, a3[1], bh); if (feed) { X2_DMA_B(2, 2); X2_DMA_B(2, 3); } X2_SB();
+      X3_GROUP(rest, a3[1], b3[1]); X2_SB();
+      X3_WAIT_B(2, b3[2]); X2_SB();                     // am'
+      X3_GROUP(rest, ah, b3[2]); X2_SB();
+      X3_WAIT_A(0, a3[2]); X2_SB();
+      X3_GROUP(rest, a3[2], bh); X2_SB();
+#undef X3_RD_A
+#undef X3_WAIT_A
+#undef X3_WAIT_B
+#undef X3_WAIT_AB
+    } else if constexpr (NB == 1) {
       // planes (h, l) of A against the single plane of B; the wait counts are the reads issued
       // after the ones waited for (MI per A plane, 4 per B plane)
       X2_RD_A(a, 0, 0, la); X2_RD_B(b0, 0, lb); X2_RD_A(a, 1, 1, la);
@@ -445,9 +472,16 @@ __global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const Gemm
       for (int v = 0; v < 16; ++v) {
         const int i = row0 + wm * WM + mi * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
         if (i < g.M && j < g.N) {
-          const float x = alpha * acc[mi][ni][v];
+          float sum = acc[mi][ni][v];
+          if constexpr (NB == 3) sum += rest[mi][ni][v];
+          const float x = alpha * sum;
           const int64_t at = (int64_t)b * g.c_batch_stride + (int64_t)i * g.ldc + j;
-          if (EPI == X2_STORE_SPLIT) {
+          if constexpr (EPI == X2_STORE_SPLIT && NB == 3) {
+            uint16_t q[3];
+            split3b(x, q);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) g.c2[t * g.c2_plane_stride + at] = q[t];
+          } else if constexpr (EPI == X2_STORE_SPLIT) {
             uint16_t h, l;
             split2h(x, h, l);
             g.c2[at] = h; g.c2[g.c2_plane_stride + at] = l;

@@ -80,18 +80,19 @@ struct Bucket {
   int32_t m, n, count;
   // byte offsets into the workspace
   size_t off_L, off_R, off_Linv, off_Rinv, off_P, off_desc, off_sgp, off_sshp, off_scale, off_norms;
-  // bf16 gradients, bf16_mfma buckets: both roots as two scaled fp16 planes, what the scales
+  // bf16_mfma buckets: both roots as two scaled fp16 planes, or three bf16 ones, what the scales
   // are made from (matrix_stats_kernel of both roots, max |G| per piece of a block) and the
   // scales themselves
-  size_t off_Linv2h = 0, off_Rinv2h = 0, off_stat_l = 0, off_stat_r = 0, off_gmaxp = 0, off_s_g = 0, off_inv_g2 = 0, off_t_scale = 0, off_inv_ts = 0;
+  size_t off_Linvp = 0, off_Rinvp = 0, off_stat_l = 0, off_stat_r = 0, off_gmaxp = 0, off_s_g = 0, off_inv_g2 = 0, off_t_scale = 0, off_inv_ts = 0;
   size_t off_QtL = 0, off_QtR = 0;   // warm start: eigenvectors of the previous refresh, [count][np][np] float32
   size_t off_Gt = 0;     // 16-bit transpose of the bucket's gradient blocks (bf16, or scaled fp16 where the fp16 products follow), made by the factor update and
                          // read again by the first preconditioning product of the same step
-  // float32 gradients that feed the factors and the directions: three bf16 planes of the block both ways round for
-  // the factor update, in T, of so many blocks at a time
-  bool split_factor = false;
-  int32_t plane_chunk = 0;
   bool planes = false;
+  // three: float32 directions, from three bf16 planes of every operand; split_factor: of float32 gradients that feed the
+  // factors too, which then take the planes of the block both ways round.  Planes of a block live in T, of
+  // plane_chunk blocks at a time: cols, the transpose, and behind it rows, the block as it lies, or T = Lbar G
+  bool three = false, split_factor = false;
+  int32_t plane_chunk = 0;
   EwGeom geom;
   int32_t tiles_m, tiles_n;
   bool bf16_mfma;   // shapes, offsets and leading dimensions allow the bf16 matrix-core factor update
@@ -1049,7 +1050,7 @@ struct shampoo_opt {
 namespace {
 
 // Planes of float32 gradients live only as long as the products that read them: those of 170 blocks of 1024 x 1024
-// at a time (both ways round 12 bytes per element), which is 24 tiles per CU of each product.
+// at a time (both ways round, or the transpose and T, 12 bytes per element), which is 24 tiles per CU of a factor update.
 constexpr size_t PLANE_BYTES = (size_t)2 << 30;
 
 size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
@@ -1082,15 +1083,16 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     }
     b.off_P = take(B * m * n * 4);
     // the preconditioning products run on the fp16 matrix cores from operands kept split in two
-    // scaled fp16 planes.  Float32 directions also have to be split in every step, and blocks of
-    // one 128-wide tile leave half of the 256-wide one idle: they keep the float32 matrix cores there.
-    // 96 blocks of 1024, both products: 3.9 ms on the float32 matrix cores, 1.2 + 0.14 (split) so, error
-    // of Lbar G Rbar 8.3e-7 and 5.3e-7; filtered gradients, blocks of 512 and 488: 1.75 and 0.72 + 0.09 ms
+    // scaled fp16 planes, float32 directions on the bf16 ones from three planes.  These also have to be split in every
+    // step, and blocks of one 128-wide tile leave half of the 256-wide one idle: they keep the float32 matrix cores there.
+    // Both products of 2^25 elements in blocks of 1024, 512, 256, 192 and 144: 1.28, 0.68, 0.38, 0.51 and 0.65 ms on the float32
+    // matrix cores, 0.70, 0.43, 0.32, 0.40 and 0.66 so; just above 256 columns, 0.81 and 0.83 (264 x 264).
     const bool dir32 = c->grad_dtype != SHAMPOO_GRAD_BF16 || use_l2 || use_b1;
     b.planes = b.bf16_mfma && c->precond_matrix_cores != SHAMPOO_MATRIX_CORES_FP32 && (!dir32 || (b.m > BM && b.n > BN));
+    b.three = b.planes && dir32;
     if (b.planes) {
-      b.off_Linv2h = take(B * m * m * 4);
-      b.off_Rinv2h = take(B * n * n * 4);
+      b.off_Linvp = take(B * m * m * (b.three ? 6 : 4));
+      b.off_Rinvp = take(B * n * n * (b.three ? 6 : 4));
       b.off_stat_l = take(B * 8);
       b.off_stat_r = take(B * 8);
       b.off_gmaxp = take(B * b.geom.chunks * 4);
@@ -1108,11 +1110,10 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_sshp = take(B * ssh_parts * 4);
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
-    b.split_factor = b.planes && dir32 && !use_b1;   // the directions' gradient feeds the factors too
+    b.split_factor = b.three && !use_b1;   // the directions' gradient feeds the factors too
     t_bytes = std::max(t_bytes, B * m * n * 4);   // float32, or two fp16 planes
-    if (b.split_factor) t_bytes = std::max(t_bytes, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
-    if (b.planes && dir32) b.off_Gt = take(B * m * n * 4);
-    else if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
+    if (b.three) t_bytes = std::max(t_bytes, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
+    if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
     const bool warm = c->warm_start_roots != 0 && c->root_method == SHAMPOO_ROOT_EIGH;
@@ -1131,7 +1132,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   }
   const size_t offT = take(t_bytes);
   for (auto &b : p.buckets) {            // even shares
-    if (!b.split_factor) continue;
+    if (!b.three) continue;
     const int64_t most = std::min<int64_t>(b.count, (int64_t)(t_bytes / ((size_t)12 * b.m * b.n))), passes = (b.count + most - 1) / most;
     b.plane_chunk = (int32_t)((b.count + passes - 1) / passes);
   }
@@ -1196,8 +1197,10 @@ int split_roots(shampoo_opt *o, hipStream_t s) {
       const int64_t per = (int64_t)n * n;
       if (const int rc = launch_fill(stat, 0.f, 2 * (int64_t)b.count, s)) return rc;
       hipLaunchKernelGGL(matrix_stats_kernel, dim3(b.count, std::max(1, std::min(32, n / 32))), dim3(256), 0, s, x, stat, n);
-      hipLaunchKernelGGL(split2h_kernel, dim3((unsigned)((per + 1023) / 1024), b.count), dim3(256), 0, s,
-                         x, stat, reinterpret_cast<uint16_t *>(o->ws + (side == 0 ? b.off_Linv2h : b.off_Rinv2h)), per, (int64_t)b.count * per);
+      uint16_t *out = reinterpret_cast<uint16_t *>(o->ws + (side == 0 ? b.off_Linvp : b.off_Rinvp));
+      const dim3 grid((unsigned)((per + 1023) / 1024), b.count);
+      if (b.three) hipLaunchKernelGGL(split_roots_kernel<true>, grid, dim3(256), 0, s, x, stat, out, per, (int64_t)b.count * per);
+      else hipLaunchKernelGGL(split_roots_kernel<false>, grid, dim3(256), 0, s, x, stat, out, per, (int64_t)b.count * per);
     }
     HIP_TRY(hipGetLastError());
   }
@@ -1417,16 +1420,20 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     gr.alpha = alpha; gr.beta = beta;
     hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(((int64_t)d * d + 255) / 256), count), dim3(256), 0, s, gr);
   };
-  // the planes of a bucket's float32 direction gradients, after launch_x2_scales
-  auto launch_split_transpose = [&](const Bucket &b) {
-    SplitTransposeArgs st;
-    st.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); st.g_table = gd_tab;
-    st.out = reinterpret_cast<uint16_t *>(ws + b.off_Gt); st.plane_stride = (int64_t)b.count * b.m * b.n;
-    st.scale = reinterpret_cast<const float *>(ws + b.off_s_g); st.m = b.m; st.n = b.n;
-    hipLaunchKernelGGL(split2h_transpose_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, st);
+  // the planes of blocks [b0, b0 + cnt) of a bucket's float32 gradients, after launch_x2_scales
+  auto launch_block_planes = [&](const Bucket &b, int b0, int cnt, bool rows) {
+    BlockPlanesArgs bp;
+    bp.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc) + b0; bp.g_table = gd_tab;
+    bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g) + b0; bp.m = b.m; bp.n = b.n;
+    bp.plane_stride = (int64_t)cnt * b.m * b.n;
+    bp.cols = reinterpret_cast<uint16_t *>(T); bp.rows = rows ? bp.cols + 3 * bp.plane_stride : nullptr;
+    hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, cnt), dim3(256), 0, s, bp);
+    return bp;
   };
+  const Bucket *cols_in_T = nullptr;     // whose planes of the transpose are all in T, from the factor update on
   for (auto &b : p.buckets) {
     if (fused(b)) continue;
+    cols_in_T = nullptr;
     const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
     // grafting state and norm first: the same pass finds max |G| of every block, which scales
     // the fp16 planes of this step's first product
@@ -1489,15 +1496,11 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       // float32 gradients: both factors from three bf16 planes
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
       launch_x2_scales(b);
-      launch_split_transpose(b);
       o->upper_stale[&b - p.buckets.data()] = 1;
+      if (b.plane_chunk == b.count) cols_in_T = &b;
       for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
         const int cnt = std::min(b.plane_chunk, b.count - b0);
-        BlockPlanesArgs bp;
-        bp.desc = desc + b0; bp.g_table = gs_tab; bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g) + b0; bp.m = b.m; bp.n = b.n;
-        bp.plane_stride = (int64_t)cnt * b.m * b.n;
-        bp.cols = reinterpret_cast<uint16_t *>(T); bp.rows = bp.cols + 3 * bp.plane_stride;
-        hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, cnt), dim3(256), 0, s, bp);
+        const BlockPlanesArgs bp = launch_block_planes(b, b0, cnt, true);
         SyrkBf16Args sa{};
         sa.alpha = alpha; sa.beta = beta; sa.batch = cnt;
         sa.plane = bp.plane_stride; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2) + b0;
@@ -1697,6 +1700,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     float *P = reinterpret_cast<float *>(ws + b.off_P);
     float *scale = reinterpret_cast<float *>(ws + b.off_scale);
     if (fused(b)) continue;
+    if (cols_in_T != &b) cols_in_T = nullptr;   // this bucket writes T first
     int ssh_count = b.tiles_m * b.tiles_n;
     if (use_shampoo && b.t3) {
       // P = G x_1 Lbar_1 x_2 Lbar_2 ... x_w Lbar_w (Sec. 2.3).  Mode 1 on the block as
@@ -1799,54 +1803,55 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         ssh_count = b.geom.chunks;
       }
     } else if (use_shampoo && b.planes && o->ptrs_aligned16) {
-      // Both products on the fp16 matrix cores, float32-accurate through two-plane splits of the
-      // float32 operands (Lbar, T, Rbar), each scaled by a power of two into the fp16 range.  A bf16
+      // Both products on the fp16 or bf16 matrix cores, float32-accurate through splits of the
+      // float32 operands, each scaled by a power of two.  A bf16
       // gradient is one fp16 plane (exact: 8 significant bits), the scaled transpose made for the factor
-      // update; a float32 one (or a filtered or shifted one) is split here, into the same place.
-      // B operands are read along k.
+      // update, against two of Lbar, T and Rbar; a float32 one (or a filtered or shifted one) is split here into three bf16
+      // planes, against three of the others.  B operands are read along k.
+      constexpr bool THREE = sizeof(GD) == 4;
       const int tm128 = (b.m + 127) / 128, x2_tn = (b.n + X2_TN - 1) / X2_TN;
-      // tiles of 256 rows (half the operand traffic per multiply) unless padding the rows to
-      // 256 would add more than an eighth to the work
+      // tiles of 256 rows (half the operand traffic per multiply; three planes do not leave room for them) unless
+      // padding the rows to 256 would add more than an eighth to the work
       // and unless there are too few of them to give every CU one
       const int tm256 = (b.m + 255) / 256;
-      const bool tall = tm256 * 256 * 8 <= tm128 * 128 * 9 && (int64_t)tm256 * x2_tn * b.count >= 256;
+      const bool tall = !THREE && tm256 * 256 * 8 <= tm128 * 128 * 9 && (int64_t)tm256 * x2_tn * b.count >= 256;
       const int h_tm = tall ? tm256 : tm128;
-      const int64_t per_h = ((int64_t)h_tm * x2_tn * b.count + NUM_XCD - 1) / NUM_XCD;
       ssh_count = h_tm * x2_tn;
-      uint16_t *T2h = reinterpret_cast<uint16_t *>(T);
-      const int64_t t_plane = (int64_t)b.count * b.m * b.n;
-      {
-      StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      const bool split = sizeof(GD) == 4 && !b.split_factor;   // not yet split, and not yet scaled, for the factor update
-      if (refresh || split) launch_x2_scales(b);   // on a refresh the roots, and with them their scales, have just changed
-      if (split) launch_split_transpose(b);
-      GemmX2Args g{};
-      g.a = reinterpret_cast<const uint16_t *>(ws + b.off_Linv2h);
-      g.a_plane_stride = (int64_t)b.count * b.m * b.m; g.a_batch_stride = (int64_t)b.m * b.m; g.lda = b.m;
-      g.b = reinterpret_cast<const uint16_t *>(ws + b.off_Gt); g.b_plane_stride = sizeof(GD) == 4 ? t_plane : 0;
-      g.b_batch_stride = (int64_t)b.m * b.n; g.ldb = b.m;
-      g.c2 = T2h; g.c2_plane_stride = t_plane; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
-      g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.out_scale = reinterpret_cast<const float *>(ws + b.off_t_scale);
-      g.tiles_m = h_tm; g.tiles_n = x2_tn; g.batch = b.count;
-      if (tall)
-        hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, sizeof(GD) == 4 ? 2 : 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
-      else
-        hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, sizeof(GD) == 4 ? 2 : 1, X2_STORE_SPLIT>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, g);
+      // on a refresh the roots, and with them their scales, have just changed; filtered gradients have not been scaled yet
+      if (refresh || (THREE && !b.split_factor)) launch_x2_scales(b);
+      const int step_blocks = THREE ? b.plane_chunk : b.count;
+      for (int b0 = 0; b0 < b.count; b0 += step_blocks) {
+        const int cnt = std::min(step_blocks, b.count - b0);
+        const int64_t mn = (int64_t)b.m * b.n, plane = cnt * mn;
+        const dim3 grid((unsigned)(((int64_t)h_tm * x2_tn * cnt + NUM_XCD - 1) / NUM_XCD * NUM_XCD));
+        uint16_t *Tp = reinterpret_cast<uint16_t *>(T) + (THREE ? 3 * plane : 0);
+        {
+          StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
+          GemmX2Args g{};
+          g.a_plane_stride = (int64_t)b.count * b.m * b.m; g.a_batch_stride = (int64_t)b.m * b.m; g.lda = b.m;
+          g.a = reinterpret_cast<const uint16_t *>(ws + b.off_Linvp) + b0 * g.a_batch_stride;
+          if constexpr (THREE) g.b = cols_in_T == &b ? reinterpret_cast<const uint16_t *>(T) : launch_block_planes(b, b0, cnt, false).cols;
+          else g.b = reinterpret_cast<const uint16_t *>(ws + b.off_Gt);
+          g.b_plane_stride = THREE ? plane : 0; g.b_batch_stride = mn; g.ldb = b.m;
+          g.c2 = Tp; g.c2_plane_stride = plane; g.c_batch_stride = mn; g.ldc = b.n;
+          g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.out_scale = reinterpret_cast<const float *>(ws + b.off_t_scale) + b0;
+          g.tiles_m = h_tm; g.tiles_n = x2_tn; g.batch = cnt;
+          if (tall) hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>), grid, dim3(256), 0, s, g);
+          else hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, THREE ? 3 : 1, X2_STORE_SPLIT>), grid, dim3(256), 0, s, g);
+        }
+        StageTimer t2(o, SHAMPOO_STAGE_PRECOND2, s);
+        GemmX2Args h{};
+        h.a = Tp; h.a_plane_stride = plane; h.a_batch_stride = mn; h.lda = b.n;
+        h.b_plane_stride = (int64_t)b.count * b.n * b.n; h.b_batch_stride = (int64_t)b.n * b.n; h.ldb = b.n;
+        h.b = reinterpret_cast<const uint16_t *>(ws + b.off_Rinvp) + b0 * h.b_batch_stride;
+        h.c = P + b0 * mn; h.c_batch_stride = mn; h.ldc = b.n;
+        h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.out_scale = reinterpret_cast<const float *>(ws + b.off_inv_ts) + b0;
+        h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp) + (int64_t)b0 * ssh_count;
+        h.tiles_m = h_tm; h.tiles_n = x2_tn; h.batch = cnt;
+        if (tall) hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>), grid, dim3(256), 0, s, h);
+        else hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, THREE ? 3 : 2, X2_STORE_NORM>), grid, dim3(256), 0, s, h);
+        HIP_TRY(hipGetLastError());
       }
-      StageTimer t2(o, SHAMPOO_STAGE_PRECOND2, s);
-      GemmX2Args h{};
-      h.a = T2h; h.a_plane_stride = t_plane; h.a_batch_stride = (int64_t)b.m * b.n; h.lda = b.n;
-      h.b = reinterpret_cast<const uint16_t *>(ws + b.off_Rinv2h);
-      h.b_plane_stride = (int64_t)b.count * b.n * b.n; h.b_batch_stride = (int64_t)b.n * b.n; h.ldb = b.n;
-      h.c = P; h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
-      h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.out_scale = reinterpret_cast<const float *>(ws + b.off_inv_ts);
-      h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
-      h.tiles_m = h_tm; h.tiles_n = x2_tn; h.batch = b.count;
-      if (tall)
-        hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, h);
-      else
-        hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, 2, X2_STORE_NORM>), dim3((unsigned)(per_h * NUM_XCD)), dim3(256), 0, s, h);
-      HIP_TRY(hipGetLastError());
     } else if (use_shampoo) {
       {
       StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);

@@ -41,10 +41,12 @@ def test_more_tensors_than_one_copy_launch_holds():
 
 
 @pytest.mark.parametrize("shape,decades", [((256, 384), (8, 0)), ((392, 144), (0, 12)), ((152, 264), (10, 10))])
-def test_small_rows_and_columns_keep_their_accuracy_in_the_factors(shape, decades):
-    """Rows (columns) that are many decades below the largest: every element of a factor, measured by the norms of the
-    two rows it is a product of.  Bound: 2^-24 for the float32 it is stored in; the matrix cores add up 32 values of
-    k in 12 steps, 12 x 2^-24 of their share at worst; 2^-24 for the products left out: 14 x 2^-24, once per gradient."""
+def test_small_rows_and_columns_keep_their_accuracy(shape, decades):
+    """Rows (columns) that are many decades below the largest.  Every element of a factor, measured by the norms of the
+    two rows it is a product of: 2^-24 for the float32 it is stored in; the matrix cores add up 32 values of
+    k in 12 steps, 12 x 2^-24 of their share at worst; 2^-24 for the products left out: 14 x 2^-24, once per gradient.
+    Every element of Lbar G Rbar, measured by |Lbar| |G| |Rbar|: a rounding per 16 values of k in both products, and
+    in each 2^-24 for the products left out, for the last sum and for the result."""
     import torch
     m, n = shape
     beta = float(np.float32(0.999))
@@ -66,6 +68,11 @@ def test_small_rows_and_columns_keep_their_accuracy_in_the_factors(shape, decade
         err = np.abs(got - want) / np.outer(d, d)
         assert np.array_equal(got, got.T)
         assert err.max() <= 14 * steps * 2.0 ** -24, (which, err.max(), np.unravel_index(err.argmax(), err.shape))
+    Li, Ri = (opt.get(0, 0, which).cpu().numpy().astype(np.float64) for which in (B.GET_LINV, B.GET_RINV))
+    P = opt.get(0, 0, B.GET_PSH).cpu().numpy()
+    err = np.abs(P - Li @ g @ Ri) / (np.abs(Li) @ np.abs(g) @ np.abs(Ri))
+    steps_of = lambda k: 2 * -(-k // 32)
+    assert err.max() <= (steps_of(m) + steps_of(n) + 6) * 2.0 ** -24, (err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
 def test_more_blocks_than_the_planes_have_room_for():
@@ -90,7 +97,7 @@ def test_more_blocks_than_the_planes_have_room_for():
 
 
 @pytest.mark.parametrize("name,sigma,eps,span", [("tiny", 1e-15, 1e-30, False), ("huge", 1e10, 1e20, False), ("rows", 1e-3, 1e-9, True)])
-def test_float32_gradients_on_the_fp16_matrix_cores(name, sigma, eps, span):
+def test_float32_gradients_in_planes(name, sigma, eps, span):
     """Blocks with ragged tiles and ragged k (136 = 128 + 8, 264 = 256 + 8, k % 32 of 8, 16 and 24) whose gradients
     are tiny, huge, or span six decades from row to row, and a zero block: factors, products, directions."""
     shapes = [(256, 384), (392, 144), (152, 264)]
@@ -108,7 +115,7 @@ def test_float32_gradients_on_the_fp16_matrix_cores(name, sigma, eps, span):
         assert np.isfinite(w.cpu().numpy()).all()
 
 
-def test_filtered_gradients_on_the_fp16_matrix_cores():
+def test_filtered_gradients_in_planes():
     shapes = [(256, 384), (392, 144), (152, 264)]
     for bf16 in (False, True):
         p = Pair(shapes, 256, 0.999, 1, bf16=bf16, beta1=0.9, weight_decay=0.05, bias_correction=True, grafting="adam")
