@@ -168,7 +168,7 @@ struct X2ScaleArgs {
   const float *gmax_partial; int32_t parts;   // [batch][parts] max |G| per piece of the block
   const float *stat_l, *stat_r;               // matrix_stats_kernel of Lbar, Rbar
   float c1;
-  float *s_g, *inv_g2, *t_scale, *inv_ts;     // [batch] s_G, 1 / s_G^2, s_T / (s_L s_G), 1 / (s_T s_R)
+  float *s_g, *t_scale, *inv_ts;              // [batch] s_G, s_T / (s_L s_G), 1 / (s_T s_R)
 };
 __global__ __launch_bounds__(64) void x2_scales_kernel(const X2ScaleArgs g) {
   const int b = blockIdx.x, lane = threadIdx.x;
@@ -182,7 +182,6 @@ __global__ __launch_bounds__(64) void x2_scales_kernel(const X2ScaleArgs g) {
     const float sl = pow2_scale_f16(g.stat_l[2 * b]);
     const float sr = pow2_scale_f16(g.stat_r[2 * b]);
     g.s_g[b] = sg;
-    g.inv_g2[b] = (1.f / sg) * (1.f / sg);
     g.t_scale[b] = (st / sl) / sg;
     g.inv_ts[b] = (1.f / st) * (1.f / sr);
   }

@@ -83,7 +83,7 @@ struct Bucket {
   // bf16_mfma buckets: both roots as two scaled fp16 planes, or three bf16 ones, what the scales
   // are made from (matrix_stats_kernel of both roots, max |G| per piece of a block) and the
   // scales themselves
-  size_t off_Linvp = 0, off_Rinvp = 0, off_stat_l = 0, off_stat_r = 0, off_gmaxp = 0, off_s_g = 0, off_inv_g2 = 0, off_t_scale = 0, off_inv_ts = 0;
+  size_t off_Linvp = 0, off_Rinvp = 0, off_stat_l = 0, off_stat_r = 0, off_gmaxp = 0, off_s_g = 0, off_t_scale = 0, off_inv_ts = 0;
   size_t off_QtL = 0, off_QtR = 0;   // warm start: eigenvectors of the previous refresh, [count][np][np] float32
   size_t off_Gt = 0;     // 16-bit transpose of the bucket's gradient blocks (bf16, or scaled fp16 where the fp16 products follow), made by the factor update and
                          // read again by the first preconditioning product of the same step
@@ -1097,7 +1097,6 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
       b.off_stat_r = take(B * 8);
       b.off_gmaxp = take(B * b.geom.chunks * 4);
       b.off_s_g = take(B * 4);
-      b.off_inv_g2 = take(B * 4);
       b.off_t_scale = take(B * 4);
       b.off_inv_ts = take(B * 4);
     }
@@ -1400,7 +1399,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     xs.gmax_partial = reinterpret_cast<const float *>(ws + b.off_gmaxp); xs.parts = b.geom.chunks;
     xs.stat_l = reinterpret_cast<const float *>(ws + b.off_stat_l); xs.stat_r = reinterpret_cast<const float *>(ws + b.off_stat_r);
     xs.c1 = c1;
-    xs.s_g = reinterpret_cast<float *>(ws + b.off_s_g); xs.inv_g2 = reinterpret_cast<float *>(ws + b.off_inv_g2);
+    xs.s_g = reinterpret_cast<float *>(ws + b.off_s_g);
     xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
     hipLaunchKernelGGL(x2_scales_kernel, dim3(b.count), dim3(64), 0, s, xs);
   };
@@ -1483,7 +1482,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         const int per = (int)((total + NUM_XCD - 1) / NUM_XCD);
         const bool young = young_factor(step, b.m, b.n);
         if (x2) {
-          sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2);
+          sa.x_scale = reinterpret_cast<const float *>(ws + b.off_s_g);
           if (young) hipLaunchKernelGGL((syrk_bf16_kernel<true, true>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
           else hipLaunchKernelGGL((syrk_bf16_kernel<true, false>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
         } else {
@@ -1503,7 +1502,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         const BlockPlanesArgs bp = launch_block_planes(b, b0, cnt, true);
         SyrkBf16Args sa{};
         sa.alpha = alpha; sa.beta = beta; sa.batch = cnt;
-        sa.plane = bp.plane_stride; sa.x_scale2 = reinterpret_cast<const float *>(ws + b.off_inv_g2) + b0;
+        sa.plane = bp.plane_stride; sa.x_scale = bp.scale;
         for (int side = 0; side < 2; ++side) {
           const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
           sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;

@@ -67,7 +67,7 @@ struct SyrkBf16Args {
   int32_t M, K;              // C is M x M
   double alpha, beta;
   int64_t plane;             // SPLIT: from a plane to the next, elements
-  const float *x_scale2;     // [batch] X holds values s x: 1 / s^2, applied with alpha (nullptr: X itself)
+  const float *x_scale;      // [batch] X holds values s x; 1 / s^2 is applied with alpha (nullptr: X itself)
   int32_t tiles;             // lower-triangular tile count per batch entry
   int32_t batch;
 };
@@ -255,7 +255,8 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
   // the lower.  The tiles above the diagonal are mirror_upper_tiles_kernel's.
   float *c = g.c + (int64_t)b * g.c_batch_stride;
   const int ldc = g.ldc;
-  const double alpha = g.x_scale2 ? g.alpha * (double)g.x_scale2[b] : g.alpha;
+  // s is up to 2^100, its square in float64
+  const double inv_s = g.x_scale ? 1.0 / (double)g.x_scale[b] : 1.0, alpha = g.alpha * (inv_s * inv_s);
   // The old values of half a quadrant (32 x 64) are requested before any of them is used,
   // from clamped (always valid) addresses so that the loads are unconditional: one memory
   // round trip per half instead of one per element.

@@ -75,6 +75,18 @@ def test_small_rows_and_columns_keep_their_accuracy(shape, decades):
     assert err.max() <= (steps_of(m) + steps_of(n) + 6) * 2.0 ** -24, (err.max(), np.unravel_index(err.argmax(), err.shape))
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+def test_factors_of_very_small_gradients(bf16):
+    """Gradients of 3e-20: their scale is 2^76, its square is beyond float32, the factors (2e-37 a gradient) are not."""
+    shapes = [(256, 384)]
+    p = Pair(shapes, 512, 1.0, 1000, eps=1e-30, eps_g=1e-30, bf16=bf16)
+    for t in range(3):
+        p.step(wl.gaussian_grads(shapes, 76, t, 3e-20), 0.01, t)
+    for which, want in ((B.GET_L, p.ora.L), (B.GET_R, p.ora.R)):
+        got = p.gpu.get(0, 0, which).cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - want[0][0]) <= 1e-5 * np.linalg.norm(want[0][0])
+
+
 def test_more_blocks_than_the_planes_have_room_for():
     """181 blocks of 1024 x 1024, whose planes are made for 91 and then for 90 at a time: the blocks at the edges of the two
     parts, against float64 products of the same values."""
