@@ -71,7 +71,8 @@ struct GemmArgs {
   int32_t tiles_m, tiles_n, tiles;  // tiles = tiles per batch entry (triangular count for SYRK)
   int32_t tile0;                // EPI_SYRK: the first of them (rows of tiles in front of it stay as they are)
   int32_t batch;
-  int32_t ksplit, krange;       // EPI_SYRK, ksplit > 1: batch entry b is the range b % ksplit, of krange values of k, of operand b / ksplit
+  int32_t ksplit, krange;       // EPI_SYRK, ksplit > 1: batch entry b is the range b % ksplit, of krange values of k, of operand b / ksplit;
+  double *c64;                  // its plain sum goes here, in float64 like c (ACC64 kernels)
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
       // would cost one memory round trip per element instead of one per tile.
       float old[EPI == EPI_SYRK ? 16 : 1];
       if (EPI == EPI_SYRK) {
-        const bool need = ACC64 ? (g.beta_d != 0.0) : (g.beta != 0.f);
+        const bool need = ACC64 ? (g.beta_d != 0.0 && g.ksplit <= 1) : (g.beta != 0.f);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int i = row0 + wm * 64 + mi * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
@@ -360,6 +361,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmAr
               // same bits so the factor stays exactly symmetric
               if (j <= i) {
                 const float o = old[EPI == EPI_SYRK ? 4 * q + e : 0];
+                if (ACC64 && g.ksplit > 1) {
+                  double *c64 = g.c64 + (int64_t)b * g.c_batch_stride;
+                  const double sum = acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0];
+                  c64[(int64_t)i * ldc + j] = sum;
+                  if (j < i) c64[(int64_t)j * ldc + i] = sum;
+                  continue;
+                }
                 if (ACC64) v = (float)(g.alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0] + g.beta_d * (double)o);
                 else v += g.beta * o;
                 c[(int64_t)i * ldc + j] = v;

@@ -1110,7 +1110,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
     b.split_factor = b.three && !use_b1;   // the directions' gradient feeds the factors too
-    t_bytes = std::max(t_bytes, B * m * n * 4);   // float32, or two fp16 planes
+    t_bytes = std::max(t_bytes, B * m * n * (b.t3 ? 8 : 4));   // float32, two fp16 planes, or float64 sums (split_gram)
     if (b.three) t_bytes = std::max(t_bytes, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
     if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
@@ -1403,21 +1403,22 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
     hipLaunchKernelGGL(x2_scales_kernel, dim3(b.count), dim3(64), 0, s, xs);
   };
-  // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through T: it holds
-  // the m n values of every block of the bucket.
+  // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through T in float64, as
+  // the one sum is held: it has room for m n of them per block of the bucket.
   auto split_gram = [&](const Bucket &b, GemmArgs &g) {
     const GramSplit sp = gram_split(g.K, (int64_t)b.m * b.n / ((int64_t)g.M * g.M), (int64_t)g.tiles * g.batch, BK);
     if (sp.ranges <= 1) return 1;
     g.ksplit = sp.ranges; g.krange = sp.range;
-    g.c = T; g.batch *= g.ksplit;
-    g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0;
+    g.c64 = reinterpret_cast<double *>(T); g.batch *= g.ksplit;
     return (int)g.ksplit;
   };
-  auto reduce_gram = [&](size_t off_factor, int d, int splits, int count) {
+  auto reduce_gram = [&](size_t off_factor, int d, int splits, int count, bool f64) {
     GramReduceArgs gr;
     gr.partial = T; gr.factor = reinterpret_cast<float *>(ws + off_factor); gr.d = d; gr.splits = splits;
     gr.alpha = alpha; gr.beta = beta;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(((int64_t)d * d + 255) / 256), count), dim3(256), 0, s, gr);
+    const dim3 grid((unsigned)(((int64_t)d * d + 255) / 256), count);
+    if (f64) hipLaunchKernelGGL(gram_reduce_kernel<double>, grid, dim3(256), 0, s, gr);
+    else hipLaunchKernelGGL(gram_reduce_kernel<float>, grid, dim3(256), 0, s, gr);
   };
   // the planes of blocks [b0, b0 + cnt) of a bucket's float32 gradients, after launch_x2_scales
   auto launch_block_planes = [&](const Bucket &b, int b0, int cnt, bool rows) {
@@ -1538,7 +1539,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         rc = launch_gemm<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
         if (rc) return rc;
         if (sp > 1) {
-          reduce_gram(b.off_L, b.m, sp, b.count);
+          reduce_gram(b.off_L, b.m, sp, b.count, true);
           g.ksplit = 0; g.batch = b.count;
           HIP_TRY(hipGetLastError());
         }
@@ -1566,7 +1567,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
             if (rc) return rc;
           }
-          reduce_gram(b.off_R, dl, b.split3, b.count);
+          reduce_gram(b.off_R, dl, b.split3, b.count, false);
           HIP_TRY(hipGetLastError());
           // Middle dimensions k: the block as pre x d_k x post with its first two indices swapped,
           // d_k x (pre post)
@@ -1589,7 +1590,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>(h, s);
             if (rc) return rc;
             if (sp > 1) {
-              reduce_gram(b.off_mid[k - 1], dk, sp, b.count);
+              reduce_gram(b.off_mid[k - 1], dk, sp, b.count, true);
               HIP_TRY(hipGetLastError());
             }
             pre *= dk;

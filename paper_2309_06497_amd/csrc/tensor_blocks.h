@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const PermuteArgs g) {
 }
 
 struct GramReduceArgs {
-  const float *partial;   // [slot][splits][d][d]
+  const void *partial;    // [slot][splits][d][d]
   float *factor;          // [slot][d][d]
   int32_t d, splits;
   double alpha, beta;
@@ -149,12 +149,13 @@ __global__ __launch_bounds__(256) void gram_narrow_kernel(const GramNarrowArgs g
 
 // factor <- beta factor + alpha sum_s partial_s, in float64, fixed order: the Gram matrix of a split
 // unfolding.  grid (ceil(d d / 256), slots).
+template <typename T>
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const GramReduceArgs g) {
   const int slot = blockIdx.y;
   const int e = blockIdx.x * 256 + threadIdx.x;
   const int dd = g.d * g.d;
   if (e >= dd) return;
-  const float *p = g.partial + (int64_t)slot * g.splits * dd + e;
+  const T *p = static_cast<const T *>(g.partial) + (int64_t)slot * g.splits * dd + e;
   double acc = 0.0;
   for (int s = 0; s < g.splits; ++s) acc += (double)p[(int64_t)s * dd];
   float *f = g.factor + (int64_t)slot * dd + e;

@@ -32,6 +32,21 @@ def test_long_unfoldings_that_the_ranges_do_not_divide(shape, b):
         p.check(t)
 
 
+@pytest.mark.parametrize("dim,which", [(0, B.GET_L), (1, B.GET_L2)])
+def test_sums_of_the_ranges_are_kept_in_float64(dim, which):
+    """One inner product over 9 ranges of 128 values of k: 2^25 + 1 in the first one, -2^25 in the last.  Every 16 products
+    add up exactly in float32; 2^25 + 1 does not fit one."""
+    import torch
+    opt = B.Shampoo([(128, 128, 9)], 128, 1.0, 1e-12, 0.25, 1000, 1)
+    u = np.zeros((128, 1152), np.float32)
+    u[0] = 1.0
+    u[1, :16], u[1, 32], u[1, -16:] = 2.0 ** 21, 1.0, -2.0 ** 21
+    g = np.ascontiguousarray(np.moveaxis(u.reshape(128, 128, 9), 0, dim))
+    opt.step([torch.zeros(128, 128, 9, device="cuda")], [torch.from_numpy(g).cuda()], 0.0, 0)
+    F = opt.get(0, 0, which).cpu().numpy()
+    assert F[0, 0] == 1152.0 and F[0, 1] == 1.0 and F[1, 0] == 1.0
+
+
 def test_more_tensors_than_one_copy_launch_holds():
     shapes = [(3, 5, 7), (4, 6, 2), (5, 5, 5)] * 9 + [(6, 7)]
     p = TensorPair(shapes, 6, 0.99, 1)
