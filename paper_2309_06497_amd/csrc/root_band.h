@@ -20,8 +20,9 @@
 // exponents without a rational fit.
 //
 // Accuracy: the reduction is backward stable in float64 (eigenvalues move by 1e-16 of the largest, as
-// in the float64 sweeps), the inverses are float64; F, the reflectors of the way back and its products
-// are float32, like the accumulated rotations and the reconstruction of the Jacobi path.
+// in the float64 sweeps), the inverses are float64; F, the reflectors of the way back and the results of its products
+// are float32, like the accumulated rotations and the reconstruction of the Jacobi path, the sums in them float64 (but for
+// the update of F from n = 513 on).
 //
 // Layouts of v_mfma_f64_16x16x4_f64: lane l supplies A(l % 16, l / 16) and B(l / 16, l % 16), element v
 // of the result is D(l / 16 + 4 v, l % 16); v_mfma_f32_16x16x4_f32: the same operands, D(4 (l / 16) + v,
@@ -934,9 +935,10 @@ __global__ __launch_bounds__(512, 2) void band_rows_kernel(BandArgs g) {
         }
     __syncthreads();
     for (int e = tid; e < 1024; e += 512) {
-      float s = 0.f;
+      double sum = 0.0;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) s += red[i & 1][q][e];
+      for (int q = 0; q < 8; ++q) sum += (double)red[i & 1][q][e];
+      const float s = (float)sum;
       const int el = e & 63, v = (e >> 6) & 3, ti = (e >> 8) & 1, h = e >> 9;
       const int r = 16 * h + (el & 15), c = 16 * ti + (el >> 4) + 4 * v;
       g.f[(int64_t)(BAND * l + r) * np + BAND * i + c] = s;
@@ -1028,10 +1030,10 @@ __global__ __launch_bounds__(1024) void band_group_t_kernel(BandArgs g) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) red[w][(16 * i + 4 * lg + u) * BAND + 16 * j + li] = acc[e][i][j][u];
       __syncthreads();
-      float s = 0.f;
+      double s = 0.0;
 #pragma unroll
-      for (int k = 0; k < 16; ++k) s += red[k][tid];
-      T[BAND * a + (tid >> 5)][BAND * b + (tid & 31)] = s;
+      for (int k = 0; k < 16; ++k) s += (double)red[k][tid];
+      T[BAND * a + (tid >> 5)][BAND * b + (tid & 31)] = (float)s;
       T[BAND * b + (tid >> 5)][BAND * a + (tid & 31)] = 0.f;
       __syncthreads();
     }
@@ -1044,16 +1046,16 @@ __global__ __launch_bounds__(1024) void band_group_t_kernel(BandArgs g) {
     for (int o = 0; o < BAND_GW; o += 2 * h) {
       for (int x = tid; x < h * h; x += 1024) {
         const int i = x / h, j = x % h;
-        float s = 0.f;
-        for (int k = 0; k <= j; ++k) s += T[o + i][o + h + k] * T[o + h + k][o + h + j];
-        u[x] = s;
+        double s = 0.0;
+        for (int k = 0; k <= j; ++k) s += (double)T[o + i][o + h + k] * (double)T[o + h + k][o + h + j];
+        u[x] = (float)s;
       }
       __syncthreads();
       for (int x = tid; x < h * h; x += 1024) {
         const int i = x / h, j = x % h;
-        float s = 0.f;
-        for (int k = i; k < h; ++k) s += T[o + i][o + k] * u[k * h + j];
-        T[o + i][o + h + j] = -s;
+        double s = 0.0;
+        for (int k = i; k < h; ++k) s += (double)T[o + i][o + k] * (double)u[k * h + j];
+        T[o + i][o + h + j] = (float)-s;
       }
       __syncthreads();
     }
@@ -1078,7 +1080,8 @@ __global__ __launch_bounds__(256) void band_stage_kernel(BandArgs g, const int q
 }
 
 // M = V^T Z and [T^T; -T M T^T / 2].  grid (batch), 16 wavefronts of 32 x 32 results each; one workgroup per
-// matrix, since the second product needs all of the first: 15 us for 1024 rows.
+// matrix, since the second product needs all of the first (158 us for 32 matrices of 1024 beside 32 others).  On the fp64 matrix cores:
+// float32 sums here cost more accuracy than the roundings of everything else on the way back together, and 135 us.
 __global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
   __shared__ float M[BAND_GW][BAND_GW + 1], T[BAND_GW][BAND_GW + 1];
   band_select(g, blockIdx.x);
@@ -1087,14 +1090,14 @@ __global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
   const int i0 = 32 * (w >> 2), j0 = 32 * (w & 3);
   const float *tg = band_tg(g) + (int64_t)q * BAND_GW * BAND_GW;
   for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) T[x / BAND_GW][x % BAND_GW] = tg[x];
-  band_f4 acc[2][2];
+  band_d4 acc[2][2];
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (band_f4){0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0.0, 0.0, 0.0, 0.0};
   };
-  auto product = [&](float a0, float a1, float b0, float b1) {
+  auto product = [&](double a0, double a1, double b0, double b1) {
     acc[0][0] = band_mfma(a0, b0, acc[0][0]); acc[0][1] = band_mfma(a0, b1, acc[0][1]);
     acc[1][0] = band_mfma(a1, b0, acc[1][0]); acc[1][1] = band_mfma(a1, b1, acc[1][1]);
   };
@@ -1112,7 +1115,7 @@ __global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) M[i0 + 16 * i + 4 * lg + u][j0 + 16 * j + li] = acc[i][j][u];
+        for (int u = 0; u < 4; ++u) M[i0 + 16 * i + band_row(lg, u)][j0 + 16 * j + li] = (float)acc[i][j][u];
   };
   put();
   __syncthreads();
@@ -1132,7 +1135,7 @@ __global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        out[(BAND_GW + i0 + 16 * i + 4 * lg + u) * BAND_GW + j0 + 16 * j + li] = -0.5f * acc[i][j][u];
+        out[(BAND_GW + i0 + 16 * i + band_row(lg, u)) * BAND_GW + j0 + 16 * j + li] = (float)(-0.5 * acc[i][j][u]);
   for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x % BAND_GW][x / BAND_GW];
 }
 

@@ -731,9 +731,11 @@ struct BandSolve {
     const int np = g.np, r0 = (BAND_GROUP * q + 1) * BAND, tiles = (np + BM - 1) / BM;
     float *p = band_p(g);
     const int64_t pstride = band_p_stride(g);
-    // Z sums over up to 2048 values of k: 64 at a time in float32, those sums in float64 (error of the root at
-    // n = 1024: 2.5e-6 -> 2.2e-6; the shorter sums of Y and F gain 0.2e-6 for 5 % of the time, and stay)
-    constexpr int FLUSH = 4;
+    // The sums are what these products lose accuracy by: those of 32 values of k (Y: 16) go into float64.  Error of
+    // the root of a factor of one gradient at n = 160, 256, 1024: 1.4e-6, 1.4e-6, 1.9e-6 with float32 sums but in Z, 4.8e-7,
+    // 4.8e-7, 6.2e-7 so; block Jacobi 8.8e-7, 1.0e-6, 3.0e-6.  The update of F moves the root by a tenth of that and
+    // costs 4.5 % of the time of 64 matrices of 1024: float64 where the margin to Jacobi is small.
+    constexpr int FLUSH = 2, FLUSH_Y = 1;
     int rc;
     hipLaunchKernelGGL(band_stage_kernel<false>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
     GemmArgs z{};                        // Z = F V
@@ -748,16 +750,18 @@ struct BandSolve {
     GemmArgs y = z;
     y.a = Operand{p, pstride, BAND_PLD, 0};
     y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
-    y.K = 2 * BAND_GW; y.alpha = 1.f;
-    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>(y, s))) return rc;
+    y.K = 2 * BAND_GW;
+    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, FLUSH_Y>(y, s))) return rc;
     hipLaunchKernelGGL(band_stage_kernel<true>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
     GemmArgs u = z;                      // F <- F - [Y V] [V Y]^T; V has no rows in front of r0
     u.a = y.a;
     u.b = Operand{p + BAND_GW, pstride, BAND_PLD, 0};
     u.c = g.f; u.c_batch_stride = (int64_t)np * np * 2; u.ldc = np;
-    u.N = np; u.K = 2 * BAND_GW; u.alpha = -1.f; u.beta = 1.f;
+    u.N = np; u.K = 2 * BAND_GW; u.alpha = -1.f; u.beta = 1.f; u.alpha_d = -1.0; u.beta_d = 1.0;
     u.tiles_n = tiles; u.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; u.tiles = tiles * (tiles + 1) / 2 - u.tile0;
-    if ((rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(u, s))) return rc;
+    if (np <= 512) rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>(u, s);
+    else rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(u, s);
+    if (rc) return rc;
     HIP_TRY(hipGetLastError());
     return SHAMPOO_OK;
   }
@@ -876,8 +880,10 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
   // different phases overlap on the same CUs.
   // aux == nullptr: everything on the caller's stream.
   if (aux && !aux->ready()) aux = nullptr;
+  // Exponents above 0.4 up to n = 224 stay with Jacobi, which is the more accurate one there (r = 1/2, factors of one
+  // gradient, n = 129 ... 224: 3.4e-7 ... 4.4e-7 against 4.0e-7 ... 4.6e-7; the other way round from 256 on).
   RatTable table;
-  if (!lambda && !warm.qt && e.band.bytes && rat_table(r, table))
+  if (!lambda && !warm.qt && e.band.bytes && !(r > 0.4f && n <= 224) && rat_table(r, table))
     return band_root_batched(a, n, batch, eps, r, scale, x, failed_user, fail_count, ws, e.band, s, aux, only, table);
   const int n_sub = aux ? JAC_STREAMS : 1;
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {

@@ -65,6 +65,22 @@ def test_exponents_of_the_band_path():
         check(200, r)
 
 
+@pytest.mark.parametrize("n,r", [(160, 0.25), (160, 0.5), (224, 0.6), (256, 0.25), (256, 0.5), (480, 1 / 6), (512, 0.25), (544, 0.25), (1024, 0.25)])
+def test_no_less_accurate_than_with_eigenvectors(n, r):
+    """The same matrices with and without eigenvalues asked for, i.e. by block Jacobi and without eigenvectors: the error
+    of the latter, in the mean over the batch, is no larger."""
+    import torch
+    rng = np.random.default_rng(2000 + n)
+    for kind in ("single", "well", "low"):
+        a = np.stack([matrix(kind, n, rng) for _ in range(4)])
+        dev = torch.from_numpy(a).cuda()
+        x, ref = B.shampoo_root_inverse(dev, 1e-12, r).cpu().numpy(), B.shampoo_root_inverse(dev, 1e-12, r, True)[0].cpu().numpy()
+        want = np.stack([so.root_inverse(m, float(np.float32(1e-12)), float(np.float32(r)))[0] for m in a])
+        err, bar = (np.mean([np.linalg.norm(y[i] - want[i]) / np.linalg.norm(want[i]) for i in range(4)]) for y in (x, ref))
+        print(f"    n={n} r={r:.3f} {kind}: {err:.2e}, with eigenvectors {bar:.2e}", flush=True)
+        assert err <= bar * 1.05, (kind, err, bar)     # 5 %: the spread of the mean of four
+
+
 @pytest.mark.parametrize("r", [1 / 6, 1 / 3, 0.5])
 def test_exponents(r):
     check(72, r)
