@@ -46,6 +46,7 @@ constexpr int BAND_COLS = 128;           // columns per workgroup of the rank-64
 constexpr int BAND_GROUP = 4;            // panels per block reflector of the way back
 constexpr int BAND_GW = BAND_GROUP * BAND;   // its columns
 constexpr int BAND_PLD = 3 * BAND_GW;    // row of its work array: Z, later Y | V | Y
+constexpr int BAND_SLOTS = RAT_MAX_POLES + 1;   // eliminations of B + shift: one per pole and one for the eigenvector
 
 typedef double band_d4 __attribute__((ext_vector_type(4)));
 typedef float band_f4 __attribute__((ext_vector_type(4)));
@@ -69,7 +70,7 @@ struct BandArgs {
   double *vp, *z, *y, *t, *part;         // current panel: V, Z, Y [np][32], T [32][32], partial sums of V^T Z [np / 128][32][32]
   float *vall, *tall;                    // all panels: V [np][np], panel k in columns 32 k ...; T [nb - 1][32][32]
   double *dblk, *cblk;                   // B: diagonal blocks [nb][32][32], transposed sub-diagonal blocks [nb][32][32]
-  double *kf, *gf;                       // per pole and block: -K^T (A operand order) and weight * G (D order), [36][nb][1024]
+  double *kf, *gf;                       // per slot and block: -K^T (A operand order) and weight * G (D order), [BAND_SLOTS][nb][1024]
   double *v1;                            // [np]: eigenvector handled by itself
   int32_t *ok;                           // [2][BAND_SHIFTS]: verdicts of the bisection, by parity of the round
   int32_t *dec;                          // [np]: row is coupled to no other
@@ -80,9 +81,9 @@ struct BandArgs {
 __host__ __device__ inline float *band_p(const BandArgs &g) { return reinterpret_cast<float *>(g.kf); }
 __host__ __device__ inline float *band_ts(const BandArgs &g) { return reinterpret_cast<float *>(g.gf); }
 __host__ __device__ inline float *band_tg(const BandArgs &g) { return band_ts(g) + 2 * BAND_GW * BAND_GW; }
-__host__ __device__ inline int64_t band_p_stride(const BandArgs &g) { return (int64_t)g.nb * 1024 * RAT_MAX_POLES * 2; }   // matrix to matrix, floats
-// room for them: 1536 of 9216 bytes per row, and (2 + groups) 64 KB of 9216 bytes per row from 5 blocks on
-static_assert(BAND_PLD * 4 <= 32 * 8 * RAT_MAX_POLES && (2 + 2) * BAND_GW * BAND_GW * 4 <= 5 * 1024 * 8 * RAT_MAX_POLES, "way back");
+__host__ __device__ inline int64_t band_p_stride(const BandArgs &g) { return (int64_t)g.nb * 1024 * BAND_SLOTS * 2; }   // matrix to matrix, floats
+// room for them: 1536 of 9472 bytes per row, and (2 + groups) 64 KB of 9472 bytes per row from 5 blocks on
+static_assert(BAND_PLD * 4 <= 32 * 8 * BAND_SLOTS && (2 + 2) * BAND_GW * BAND_GW * 4 <= 5 * 1024 * 8 * BAND_SLOTS, "way back");
 
 // from the arrays of matrix 0 of the batch to those of matrix b (failed_user and only stay: they are indexed)
 __host__ __device__ inline void band_select(BandArgs &g, int b) {
@@ -95,7 +96,7 @@ __host__ __device__ inline void band_select(BandArgs &g, int b) {
   g.part += b * parts * 1024;
   g.vall += b * np * np; g.tall += b * nb * 1024;
   g.dblk += b * nb * 1024; g.cblk += b * nb * 1024;
-  g.kf += b * nb * 1024 * RAT_MAX_POLES; g.gf += b * nb * 1024 * RAT_MAX_POLES;
+  g.kf += b * nb * 1024 * BAND_SLOTS; g.gf += b * nb * 1024 * BAND_SLOTS;
   g.v1 += b * np; g.ok += b * 2 * BAND_SHIFTS; g.dec += b * np; g.skip += b;
 }
 
@@ -733,18 +734,21 @@ __global__ void band_plan_kernel(BandArgs g, const int batch) {
 }
 
 // Eliminates B + sigma_j from the first block to the last, then forms the diagonal blocks of the inverse
-// from the last to the first.  One wavefront per matrix and pole: grid (RAT_MAX_POLES, batch).  Bound by the
-// latency of 32 pivots per block.  Pole 0 also iterates for the eigenvector that is handled by itself.
+// from the last to the first.  One wavefront per matrix and pole: grid (BAND_SLOTS, batch).  Bound by the
+// latency of 32 pivots per block.  The last slot iterates for the eigenvector that is handled by itself, from just below
+// its eigenvalue: the smallest pole is near zero on the shifted axis, and where lambda_min is positive that is no nearer
+// to it than to the next eigenvalue.
 __global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTable table) {
   __shared__ double row[2 * BAND];
   __shared__ double z[BAND_MAX_N + BAND];
   const int pole = blockIdx.x;
   band_select(g, blockIdx.y);
   const BandMeta m = *g.meta;
-  if (m.skip || pole >= m.poles) return;
+  const bool vector = pole == RAT_MAX_POLES;
+  if (m.skip || (vector ? !m.deflate : pole >= m.poles)) return;
   const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4, nb = g.nb;
-  const double sigma = m.base + m.low * exp(rat_log_pole(m.cls, pole));
-  const double wj = table.w[rat_offset(m.cls) + pole] * pow(m.low, 1.0 - (double)g.r);
+  const double sigma = vector ? 0x1p-50 * m.amax - m.lam : m.base + m.low * exp(rat_log_pole(m.cls, pole));
+  const double wj = vector ? 0.0 : table.w[rat_offset(m.cls) + pole] * pow(m.low, 1.0 - (double)g.r);
   double *kf = g.kf + (int64_t)pole * nb * 1024, *gf = g.gf + (int64_t)pole * nb * 1024;
   BandElim e;
   e.begin(g.dblk, li, lg);
@@ -768,8 +772,8 @@ __global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTa
     }
   }
   __syncthreads();
-  if (pole == 0 && m.deflate) {
-    // x <- (B + sigma_0)^-1 x:  z_i+1 = x_i+1 - K_i z_i,  x_i = pivot_i^-1 z_i - K_i^T x_i+1
+  if (vector) {
+    // x <- (B + sigma)^-1 x:  z_i+1 = x_i+1 - K_i z_i,  x_i = pivot_i^-1 z_i - K_i^T x_i+1
     const int a = lane & 31, k0 = 16 * (lane >> 5);
     for (int i = lane; i < g.np; i += 64) z[i] = 1.0 + 0.25 * (double)(((unsigned)i * 2654435761u) >> 24) * 0x1p-8;
     __syncthreads();
@@ -804,6 +808,7 @@ __global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTa
       __syncthreads();
     }
     for (int i = lane; i < g.np; i += 64) g.v1[i] = z[i];
+    return;
   }
   // G_i = pivot_i^-1 + K_i^T G_i+1 K_i
   double G[2][2][4];

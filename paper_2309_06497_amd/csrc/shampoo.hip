@@ -387,7 +387,7 @@ BandLayout band_layout(int n, int batch) {
     e.off_vp = take(np * BAND * 8); e.off_z = take(np * BAND * 8); e.off_y = take(np * BAND * 8);
     e.off_t = take(BAND * BAND * 8); e.off_part = take(parts * BAND * BAND * 8); e.off_tall = take(blk * 4);
     e.off_dblk = take(blk * 8); e.off_cblk = take(blk * 8);
-    e.off_kf = take(blk * 8 * RAT_MAX_POLES); e.off_gf = take(blk * 8 * RAT_MAX_POLES);
+    e.off_kf = take(blk * 8 * BAND_SLOTS); e.off_gf = take(blk * 8 * BAND_SLOTS);
     e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_skip = take(4); e.off_meta = take(sizeof(BandMeta));
     e.chunk = (int32_t)chunk;
     e.bytes = off;
@@ -715,7 +715,7 @@ struct BandSolve {
     for (int round = 0; round < BAND_ROUNDS; ++round)
       hipLaunchKernelGGL(band_probe_kernel, dim3(BAND_SHIFTS, cnt), dim3(64), 0, s, g, round);
     hipLaunchKernelGGL(band_plan_kernel, dim3((cnt + 63) / 64), dim3(64), 0, s, g, cnt);
-    hipLaunchKernelGGL(band_factor_kernel, dim3(RAT_MAX_POLES, cnt), dim3(64), 0, s, g, *table);
+    hipLaunchKernelGGL(band_factor_kernel, dim3(BAND_SLOTS, cnt), dim3(64), 0, s, g, *table);
     hipLaunchKernelGGL(band_rows_kernel<2>, dim3(g.nb, cnt), dim3(512), 0, s, g);
     hipLaunchKernelGGL(band_rows_kernel<3>, dim3(g.nb, cnt), dim3(512), 0, s, g);
     hipLaunchKernelGGL(band_rows_kernel<4>, dim3(g.nb, cnt), dim3(512), 0, s, g);

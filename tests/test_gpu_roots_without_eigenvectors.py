@@ -65,6 +65,36 @@ def test_exponents_of_the_band_path():
         check(200, r)
 
 
+@pytest.mark.parametrize("n", [40, 128, 129, 160, 512, 1000])
+@pytest.mark.parametrize("lam", [(2e-10, 3e-10), (1e-10, 1.05e-10), (3e-11, 2e-10), (-2e-10, -1.9e-10), (-1e-10, 2e-11)])
+def test_smallest_eigenvalues_close_to_each_other(n, lam):
+    """A 2 x 2 block with two eigenvalues at 1e-10 of the largest, exact in float32, beside well-conditioned ones: the
+    smaller one is handled by itself and has to be told from the other.  1e-5 of the root as everywhere here; float64
+    resolves these eigenvalues (plus epsilon) to 1e-5 at worst."""
+    import torch
+    rng = np.random.default_rng(3000 + n)
+    g = rng.standard_normal((n, 4 * n)) / np.sqrt(20.0 * n)
+    a = (g @ g.T).astype(np.float32)
+    i, j = n // 3, n - 2
+    a[[i, j]] = 0.0
+    a[:, [i, j]] = 0.0
+    a[i, i] = a[j, j] = np.float32((lam[0] + lam[1]) / 2)
+    a[i, j] = a[j, i] = np.float32((lam[1] - lam[0]) / 2)
+    a = (a + a.T) / np.float32(2)
+    x = B.shampoo_root_inverse(torch.from_numpy(a[None]).cuda(), 1e-12, 0.25)[0].cpu().numpy()
+    # the oracle block by block: as a whole, float64 would move the small eigenvalues by as much as is tested here
+    pair, rest = np.ix_([i, j], [i, j]), np.ix_(np.setdiff1d(np.arange(n), [i, j]), np.setdiff1d(np.arange(n), [i, j]))
+    small = np.linalg.eigvalsh(a[pair].astype(np.float64))
+    eps = float(np.float32(1e-12)) - min(small[0], 0.0)
+    want = np.zeros((n, n))
+    for blk in (pair, rest):
+        l, q = np.linalg.eigh(a[blk].astype(np.float64))
+        want[blk] = (q * (l + eps) ** -0.25) @ q.T
+    err = np.linalg.norm(x - want) / np.linalg.norm(want)
+    print(f"    n={n} {lam}: {err:.1e}", flush=True)
+    assert err <= 1e-5, err
+
+
 @pytest.mark.parametrize("n,r", [(160, 0.25), (160, 0.5), (224, 0.6), (256, 0.25), (256, 0.5), (480, 1 / 6), (512, 0.25), (544, 0.25), (1024, 0.25)])
 def test_no_less_accurate_than_with_eigenvectors(n, r):
     """The same matrices with and without eigenvalues asked for, i.e. by block Jacobi and without eigenvectors: the error
