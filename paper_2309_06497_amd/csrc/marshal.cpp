@@ -2,13 +2,18 @@
 // tensors of a step (device, dtype, contiguity, shape) and hands their addresses to
 // shampoo_step on the current stream.  Ten attribute look-ups per tensor cost a millisecond in
 // Python on a few hundred parameters, more than the step itself; here they cost some tens of
-// nanoseconds per tensor.
+// nanoseconds per tensor.  What the tensor library throws (a tensor without storage, no device, no memory) leaves here
+// as the Python exception that the same call raises from Python.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
+#include <pybind11/pybind11.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 namespace {
@@ -31,11 +36,12 @@ void stepper_free(PyObject *cap) { delete static_cast<Stepper *>(PyCapsule_GetPo
 
 // make(address of shampoo_step, handle, device index, gradients are bf16, [shape tuples])
 PyObject *make(PyObject *, PyObject *args) {
+  HANDLE_TH_ERRORS
   unsigned long long fn, handle;
   int device, bf16;
   PyObject *shapes;
   if (!PyArg_ParseTuple(args, "KKipO!", &fn, &handle, &device, &bf16, &PyList_Type, &shapes)) return nullptr;
-  auto *s = new Stepper;
+  auto s = std::make_unique<Stepper>();
   s->fn = reinterpret_cast<StepFn>(fn);
   s->handle = reinterpret_cast<void *>(handle);
   s->device = c10::Device(c10::DeviceType::CUDA, static_cast<c10::DeviceIndex>(device));
@@ -45,7 +51,6 @@ PyObject *make(PyObject *, PyObject *args) {
     std::vector<int64_t> dims;
     for (Py_ssize_t k = 0; PyTuple_Check(t) && k < PyTuple_GET_SIZE(t); ++k) dims.push_back(PyLong_AsLongLong(PyTuple_GET_ITEM(t, k)));
     if (!PyTuple_Check(t) || PyErr_Occurred()) {
-      delete s;
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "shapes are tuples of integers");
       return nullptr;
     }
@@ -53,28 +58,32 @@ PyObject *make(PyObject *, PyObject *args) {
   }
   s->w.resize(s->shapes.size());
   s->g.resize(s->shapes.size());
-  PyObject *cap = PyCapsule_New(s, CAPSULE, stepper_free);
-  if (!cap) delete s;
+  PyObject *cap = PyCapsule_New(s.get(), CAPSULE, stepper_free);
+  if (cap) (void)s.release();
   return cap;
+  END_HANDLE_TH_ERRORS
 }
 
 // step(stepper, params, grads, lr, step number) -> return code of shampoo_step
 PyObject *step(PyObject *, PyObject *args) {
+  HANDLE_TH_ERRORS
   PyObject *cap, *params, *grads;
   float lr;
   long long t;
   if (!PyArg_ParseTuple(args, "OOOfL", &cap, &params, &grads, &lr, &t)) return nullptr;
   auto *s = static_cast<Stepper *>(PyCapsule_GetPointer(cap, CAPSULE));
   if (!s) return nullptr;
-  PyObject *ps = PySequence_Fast(params, "params is a sequence of tensors");
+  THPObjectPtr ps(PySequence_Fast(params, "params is a sequence of tensors"));
   if (!ps) return nullptr;
-  PyObject *gs = PySequence_Fast(grads, "grads is a sequence of tensors");
-  if (!gs) { Py_DECREF(ps); return nullptr; }
+  THPObjectPtr gs(PySequence_Fast(grads, "grads is a sequence of tensors"));
+  if (!gs) return nullptr;
   const Py_ssize_t n = static_cast<Py_ssize_t>(s->shapes.size());
-  bool ok = PySequence_Fast_GET_SIZE(ps) == n && PySequence_Fast_GET_SIZE(gs) == n;
-  if (!ok) PyErr_SetString(PyExc_ValueError, "one parameter and one gradient tensor per declared parameter");
-  for (Py_ssize_t i = 0; ok && i < n; ++i) {
-    PyObject *po = PySequence_Fast_GET_ITEM(ps, i), *go = PySequence_Fast_GET_ITEM(gs, i);
+  if (PySequence_Fast_GET_SIZE(ps.get()) != n || PySequence_Fast_GET_SIZE(gs.get()) != n) {
+    PyErr_SetString(PyExc_ValueError, "one parameter and one gradient tensor per declared parameter");
+    return nullptr;
+  }
+  for (Py_ssize_t i = 0; i < n; ++i) {
+    PyObject *po = PySequence_Fast_GET_ITEM(ps.get(), i), *go = PySequence_Fast_GET_ITEM(gs.get(), i);
     const char *bad = nullptr;
     if (!THPVariable_Check(po) || !THPVariable_Check(go)) {
       bad = "parameters and gradients are tensors";
@@ -88,18 +97,16 @@ PyObject *step(PyObject *, PyObject *args) {
       else if (w.sizes() != shape || g.sizes() != shape) bad = "shape differs from the one given at creation";
       else { s->w[i] = w.data_ptr(); s->g[i] = g.data_ptr(); }
     }
-    if (bad) { PyErr_Format(PyExc_ValueError, "parameter %zd: %s", i, bad); ok = false; }
+    if (bad) { PyErr_Format(PyExc_ValueError, "parameter %zd: %s", i, bad); return nullptr; }
   }
-  int rc = 0;
-  if (ok) {
-    void *stream = c10::hip::getCurrentHIPStream().stream();
-    Py_BEGIN_ALLOW_THREADS
+  void *stream = c10::hip::getCurrentHIPStream().stream();
+  int rc;
+  {
+    pybind11::gil_scoped_release no_gil;
     rc = s->fn(s->handle, s->w.data(), s->g.data(), lr, static_cast<int64_t>(t), stream);
-    Py_END_ALLOW_THREADS
   }
-  Py_DECREF(ps);
-  Py_DECREF(gs);
-  return ok ? PyLong_FromLong(rc) : nullptr;
+  return PyLong_FromLong(rc);
+  END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {{"make", make, METH_VARARGS, nullptr}, {"step", step, METH_VARARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
