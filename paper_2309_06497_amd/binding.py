@@ -290,7 +290,9 @@ def shampoo_root_inverse(a, epsilon, r, want_lambda=False, want_failed=False):
     x = torch.empty_like(a)
     lam = torch.empty((batch, n), dtype=torch.float32, device=a.device) if want_lambda else None
     failed = torch.zeros((batch,), dtype=torch.int32, device=a.device) if want_failed else None
-    nbytes = lib().shampoo_root_inverse_workspace_bytes(n, batch)
+    # with eigenvalues the call takes the solver of the warm start, which needs half as much
+    size = "shampoo_root_inverse_warm_workspace_bytes" if want_lambda and n > 128 else "shampoo_root_inverse_workspace_bytes"
+    nbytes = getattr(lib(), size)(n, batch)
     ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=a.device)
     with torch.cuda.device(a.device):
         _check(lib().shampoo_root_inverse(

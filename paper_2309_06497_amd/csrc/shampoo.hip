@@ -367,8 +367,18 @@ int check_plan(const Plan &p) {
 // ---------------------------------------------------------------------------
 constexpr int CONGRUENCE_PANEL = 256;   // columns of T = A Qt^T formed at a time (warm start)
 
-// Workspace of the band reduction (root_band.h) for chunks of matrices.
-constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30;
+// Whether roots of n x n matrices with exponent r can do without eigenvectors (root_band.h), where no caller asks for
+// them or for eigenvalues.  Exponents above 0.4 up to n = 224 stay with Jacobi, which is the more accurate one there
+// (r = 1/2, factors of one gradient, n = 129 ... 224: 3.4e-7 ... 4.4e-7 against 4.0e-7 ... 4.6e-7; the other way round from
+// 256 on).
+bool band_serves(int n, float r) {
+  RatTable table;
+  return n > JAC_SMALL_MAX && n <= BAND_MAX_N && !(r > 0.4f && n <= 224) && rat_table(r, table);
+}
+
+// Workspace of the band reduction for chunks of matrices: 33 MB for one of 1024, of which 20 are the eliminations
+// of all poles; 96 of them fit.  Block Jacobi takes half of it.
+constexpr size_t BAND_CHUNK_BYTES = EIG_CHUNK_BYTES;
 struct BandLayout {
   int32_t np = 0, nb = 0, chunk = 0;
   size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
@@ -428,9 +438,9 @@ void eig_offsets(EigLayout &e) {
 // budget: bytes that the W and Qt arrays of one chunk may take (the other arrays are small);
 // hard_cap != 0: the whole layout must fit into that many bytes (bytes = 0 in the result if
 // not even one matrix does).
-EigLayout eig_layout(int n, int batch, size_t budget = EIG_CHUNK_BYTES, size_t hard_cap = 0, bool warm = false) {
+// band: with room for the band reduction (callers that can take it: band_serves, no eigenvectors wanted).
+EigLayout eig_layout(int n, int batch, bool band, size_t budget = EIG_CHUNK_BYTES, size_t hard_cap = 0) {
   EigLayout e;
-  (void)warm;
   e.warm = n > JAC_SMALL_MAX;   // the float64 panel serves the warm start and the mixed-precision cold solve alike
   if (n <= JAC_SMALL_MAX) {     // LDS solver: no scratch in device memory
     e.chunk = batch;
@@ -446,7 +456,7 @@ EigLayout eig_layout(int n, int batch, size_t budget = EIG_CHUNK_BYTES, size_t h
   if (hard_cap) {
     while (e.bytes > hard_cap && e.chunk > 1) { --e.chunk; eig_offsets(e); }
     if (e.bytes > hard_cap) e.bytes = 0;
-  } else {
+  } else if (band) {
     e.band = band_layout(n, batch);
     e.bytes = std::max(e.bytes, e.band.bytes);
   }
@@ -880,10 +890,8 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
   // different phases overlap on the same CUs.
   // aux == nullptr: everything on the caller's stream.
   if (aux && !aux->ready()) aux = nullptr;
-  // Exponents above 0.4 up to n = 224 stay with Jacobi, which is the more accurate one there (r = 1/2, factors of one
-  // gradient, n = 129 ... 224: 3.4e-7 ... 4.4e-7 against 4.0e-7 ... 4.6e-7; the other way round from 256 on).
   RatTable table;
-  if (!lambda && !warm.qt && e.band.bytes && !(r > 0.4f && n <= 224) && rat_table(r, table))
+  if (!lambda && !warm.qt && e.band.bytes && band_serves(n, r) && rat_table(r, table))
     return band_root_batched(a, n, batch, eps, r, scale, x, failed_user, fail_count, ws, e.band, s, aux, only, table);
   const int n_sub = aux ? JAC_STREAMS : 1;
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {
@@ -1121,12 +1129,14 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
-    const bool warm = c->warm_start_roots != 0 && c->root_method == SHAMPOO_ROOT_EIGH;
-    eL.push_back(eig_layout(em, b.count, EIG_CHUNK_BYTES, 0, warm));
-    eR.push_back(eig_layout(en, b.count, EIG_CHUNK_BYTES, 0, warm));
+    const bool warm = c->warm_start_roots != 0 && c->root_method == SHAMPOO_ROOT_EIGH && !b.t3;   // tensor blocks start cold
+    const float r_exp = b.t3 ? 2.f * c->root_exponent / (float)b.modes : c->root_exponent;
+    auto eig = [&](int n_) { return eig_layout(n_, b.count, !warm && band_serves(n_, r_exp)); };
+    eL.push_back(eig(em));
+    eR.push_back(eig(en));
     if (warm && eL.back().np > 0) b.off_QtL = take(B * (size_t)eL.back().np * eL.back().np * 4);
     if (warm && eR.back().np > 0) b.off_QtR = take(B * (size_t)eR.back().np * eR.back().np * 4);
-    for (int k = 0; k < 2; ++k) eM[k].push_back(eig_layout(b.td[k + 1], b.count));
+    for (int k = 0; k < 2; ++k) eM[k].push_back(eig(b.td[k + 1]));
     // under coupled Newton the eigensolver is the fallback of the guard (Sec. 3.2.3): room for both
     if (c->root_method == SHAMPOO_ROOT_NEWTON)
       eig_bytes = std::max(eig_bytes, std::max(std::max(newton_layout(em, b.count).bytes, newton_layout(en, b.count).bytes),
@@ -2265,7 +2275,7 @@ int shampoo_destroy(shampoo_opt *o) {
 
 size_t shampoo_root_inverse_workspace_bytes(int32_t n, int32_t batch) {
   if (n < 1 || batch < 1 || n > MAX_BLOCK_SIZE) return 0;
-  return eig_layout(n, batch).bytes;
+  return eig_layout(n, batch, true).bytes;   // for every exponent, and whether eigenvalues are asked for or not
 }
 
 int shampoo_root_inverse(const float *a, int32_t n, int32_t batch, float epsilon, float r, float *x,
@@ -2274,7 +2284,7 @@ int shampoo_root_inverse(const float *a, int32_t n, int32_t batch, float epsilon
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > MAX_BLOCK_SIZE) return SHAMPOO_ERR_UNSUPPORTED;
   if (!(epsilon > 0.f) || !std::isfinite(epsilon) || !(r > 0.f) || !std::isfinite(r)) return SHAMPOO_ERR_HYPER;
-  const EigLayout e = eig_layout(n, batch);
+  const EigLayout e = eig_layout(n, batch, !lambda && band_serves(n, r));
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % ALIGN) != 0 || workspace_bytes < e.bytes)
     return SHAMPOO_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -2296,7 +2306,7 @@ int shampoo_root_inverse(const float *a, int32_t n, int32_t batch, float epsilon
 
 size_t shampoo_root_inverse_warm_workspace_bytes(int32_t n, int32_t batch) {
   if (n <= JAC_SMALL_MAX || batch < 1 || n > MAX_BLOCK_SIZE) return 0;
-  return eig_layout(n, batch, EIG_CHUNK_BYTES, 0, true).bytes;
+  return eig_layout(n, batch, false).bytes;
 }
 
 int shampoo_root_inverse_warm(const float *a, int32_t n, int32_t batch, float epsilon, float r, float *x,
@@ -2306,7 +2316,7 @@ int shampoo_root_inverse_warm(const float *a, int32_t n, int32_t batch, float ep
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > MAX_BLOCK_SIZE || n <= JAC_SMALL_MAX) return SHAMPOO_ERR_UNSUPPORTED;
   if (!(epsilon > 0.f) || !std::isfinite(epsilon) || !(r > 0.f) || !std::isfinite(r)) return SHAMPOO_ERR_HYPER;
-  const EigLayout e = eig_layout(n, batch, EIG_CHUNK_BYTES, 0, true);
+  const EigLayout e = eig_layout(n, batch, false);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % ALIGN) != 0 || workspace_bytes < e.bytes)
     return SHAMPOO_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(qt) % 16 != 0) return SHAMPOO_ERR_WORKSPACE;   // the kernels move it 16 bytes at a time
@@ -2333,7 +2343,7 @@ int shampoo_root_inverse_static(const float *a, int32_t n, int32_t batch, float 
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > SHAMPOO_STATIC_MAX_N) return SHAMPOO_ERR_UNSUPPORTED;
   if (!(epsilon > 0.f) || !std::isfinite(epsilon) || !(r > 0.f) || !std::isfinite(r)) return SHAMPOO_ERR_HYPER;
-  const EigLayout e = eig_layout(n, batch, SHAMPOO_STATIC_SCRATCH_BYTES, SHAMPOO_STATIC_SCRATCH_BYTES);
+  const EigLayout e = eig_layout(n, batch, false, SHAMPOO_STATIC_SCRATCH_BYTES, SHAMPOO_STATIC_SCRATCH_BYTES);
   if (e.bytes == 0 || e.bytes > SHAMPOO_STATIC_SCRATCH_BYTES) return SHAMPOO_ERR_UNSUPPORTED;
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));

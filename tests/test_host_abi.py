@@ -86,6 +86,30 @@ def test_workspace_holds_the_state_of_the_memory_rule():
     assert 35e9 < big < 60e9
 
 
+def test_workspace_of_callers_that_need_eigenvectors():
+    """The path without eigenvectors needs about twice the scratch of block Jacobi.  Callers that never take it -- warm
+    starts, eigenvalues, exponents without a rational fit -- have no room for it."""
+    L = B.lib()
+    plain, warm = L.shampoo_root_inverse_workspace_bytes(1024, 64), L.shampoo_root_inverse_warm_workspace_bytes(1024, 64)
+    jacobi = 64 * 1024 * 1024 * 12          # W in float64 and Q^T of every matrix, the rest is small
+    assert jacobi < warm < 1.3 * jacobi < plain < 2.8 * jacobi
+    # chunks: never more than the 3 GiB that bound W and Q^T (plus the small arrays)
+    assert L.shampoo_root_inverse_workspace_bytes(2048, 1000) < 1.3 * (3 << 30)
+    shapes = wl.transformer_shapes(2, 2048)
+    cold = B.shampoo_workspace_bytes(cfg_for(shapes, 1024))
+    vectors = 96 * 2 * 1024 * 1024 * 4
+    assert B.shampoo_workspace_bytes(cfg_for(shapes, 1024, warm_start_roots=True)) < cold + vectors - (1 << 30)
+    assert B.shampoo_workspace_bytes(cfg_for(shapes, 1024, root_exponent=0.9)) < cold - (1 << 30)
+    # tensor blocks start cold and keep no eigenvectors
+    tensors = [(512, 512, 3, 3)] * 4
+    assert B.shampoo_workspace_bytes(cfg_for(tensors, 512, warm_start_roots=True)) == B.shampoo_workspace_bytes(cfg_for(tensors, 512))
+    # checked before anything touches the GPU: what a call takes depends on what it asks for
+    ptr, ws = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x100000)
+    call = lambda lam, r, nbytes: L.shampoo_root_inverse(ptr, 1024, 64, 1e-12, r, ptr, lam, None, ws, nbytes, None)
+    assert call(None, 0.25, warm) == -4 and call(None, 0.25, plain - 1) == -4
+    assert call(ptr, 0.25, warm - 1) == -4 and call(None, 0.9, warm - 1) == -4
+
+
 @pytest.mark.parametrize("kw,code", [
     (dict(beta2=0.0), -3), (dict(beta2=1.5), -3), (dict(epsilon=0.0), -3), (dict(epsilon=-1.0), -3),
     (dict(root_exponent=0.0), -3), (dict(precondition_frequency=0), -3),
