@@ -284,7 +284,7 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
       const double sj = row16_bcast<J>(s), x0 = sh.prow[buf][J], pc = sh.prow[buf][c];
       buf ^= 1;
       double tau = 0.0;
-      if (sj > 0.0) {
+      if (sj > TRI_NO_COLUMN) {
         const double nn = sj + x0 * x0, rn = rsqrt_newton(nn), norm = nn * rn;
         const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, inv = rcp_newton(v0);
         tau = fabs(v0) * rn;
@@ -298,6 +298,9 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
             if (t == 0) P[t] = c != J ? p : rel0 > pr ? v : rel0 == pr ? alpha : P[t];
             else P[t] = c != J ? p : v;
           }
+      } else if (c == J) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t) if (t > 0 || rel0 > pr) P[t] = 0.0;
       }
       if (tid == 0) sh.tau[pr] = tau;
     });

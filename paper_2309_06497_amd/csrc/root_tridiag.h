@@ -32,6 +32,10 @@ namespace shampoo {
 // argument of f still holds to 1e-6.
 constexpr double TRI_DEFLATE_BELOW = 0x1p-32;
 constexpr double TRI_LOWEST = 0x1p-48;       // the widest range of the rational sum
+// A column (squared norm) that is too small to be reflected.  Where columns depend on each other, what a reflection
+// leaves of the next one is rounding, 1e-16 of it, and so on: after some ten of them its square is a denormal number with a
+// few bits, and a reflector made of it is not orthogonal.  1e-100 is far below the rounding of any float32 matrix.
+constexpr double TRI_NO_COLUMN = 1e-200;
 constexpr int TRI_CHUNK = 16;                // columns of F handed from their makers to their owners at a time
 
 // element of another lane of the same 16
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const SmallRootA
       }
       s2 = wave64_sum(s2);
       const double x0 = xb[k + 1];
-      if (!(s2 > 0.0)) {       // nothing to reflect
+      if (!(s2 > TRI_NO_COLUMN)) {       // nothing to reflect
         if (tid == 0) { sh.beta[k] = 0.0; sh.e[k] = x0; }
         for (int i = tid; i < n; i += NT) if (i > k + 1) sh.vs[offs(k) + i] = 0.f;
         continue;

@@ -65,6 +65,24 @@ def test_exponents_of_the_band_path():
         check(200, r)
 
 
+@pytest.mark.parametrize("n", [33, 64, 100, 128, 129, 136, 144, 151, 160, 169, 200, 256, 291, 390, 512, 700])
+def test_columns_that_depend_on_each_other(n):
+    """All rows and columns alike but for a ridge (none for the smallest: epsilon serves as one): within a panel every
+    reflection leaves 1e-16 of the next column, down to where squares are no longer numbers of full precision."""
+    import torch
+    scales = ((1.0, 1e-3), (0.37, 1e-3), (4.1e7, 1e-3), (2.5e-9, 0.0))
+    a = np.stack([(c * (np.ones((n, n)) + ridge * np.eye(n))).astype(np.float32) for c, ridge in scales])
+    x = B.shampoo_root_inverse(torch.from_numpy(a).cuda(), 1e-12, 0.25).cpu().numpy()
+    for i in range(4):
+        # J / n and I - J / n are the eigenprojections
+        diag, off = a[i, 0, 0].astype(np.float64), a[i, 0, 1].astype(np.float64)
+        eps, J = float(np.float32(1e-12)), np.full((n, n), 1.0 / n)
+        want = (diag - off + eps) ** -0.25 * (np.eye(n) - J) + (diag + (n - 1) * off + eps) ** -0.25 * J
+        err = np.linalg.norm(x[i] - want) / np.linalg.norm(want)
+        print(f"    n={n} {scales[i]}: {err:.1e}", flush=True)
+        assert err <= 1e-5, (scales[i], err)
+
+
 @pytest.mark.parametrize("n", [40, 128, 129, 160, 512, 1000])
 @pytest.mark.parametrize("lam", [(2e-10, 3e-10), (1e-10, 1.05e-10), (3e-11, 2e-10), (-2e-10, -1.9e-10), (-1e-10, 2e-11)])
 def test_smallest_eigenvalues_close_to_each_other(n, lam):
