@@ -232,14 +232,15 @@ EwGeom make_geom(int m, int n) {
 
 void make_plan(const shampoo_config *c, Plan &p) {
   const int64_t b = c->block_size;
-  // (m, n, diagonal sides | tensor, d2, d3, d4) -> bucket
-  std::map<std::tuple<int, int, int, int, int, int>, int> bucket_of;
+  // (m, n, diagonal sides | tensor, d2, d3, d4, order of the tensor) -> bucket; the order gives the root's exponent, also
+  // where a block has a single index along the last dimension
+  std::map<std::tuple<int, int, int, int, int, int, int>, int> bucket_of;
   p.param_blocks.assign(c->n_params, {});
   p.param_state_offset.assign(c->n_params, 0);
   p.pshape.assign(c->n_params, PShape());
   int64_t off = 0;
   auto bucket_for = [&](int m, int n, int flags, int d2, int d3, int d4, int modes) {
-    auto key = std::make_tuple(m, n, flags, d2, d3, d4);
+    auto key = std::make_tuple(m, n, flags, d2, d3, d4, modes);
     auto it = bucket_of.find(key);
     if (it == bucket_of.end()) {
       Bucket bk{};

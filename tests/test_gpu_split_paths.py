@@ -47,6 +47,14 @@ def test_sums_of_the_ranges_are_kept_in_float64(dim, which):
     assert F[0, 0] == 1152.0 and F[0, 1] == 1.0 and F[1, 0] == 1.0
 
 
+def test_tensors_of_different_order_whose_blocks_measure_the_same():
+    shapes = [(6, 8, 9), (6, 8, 9, 9), (6, 17, 9)]
+    p = TensorPair(shapes, 8, 0.99, 1)
+    for t in range(2):
+        p.step(wl.gaussian_grads(shapes, 77, t, 1e-1), 0.01, t)
+        p.check(t)
+
+
 def test_more_tensors_than_one_copy_launch_holds():
     shapes = [(3, 5, 7), (4, 6, 2), (5, 5, 5)] * 9 + [(6, 7)]
     p = TensorPair(shapes, 6, 0.99, 1)

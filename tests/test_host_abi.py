@@ -221,6 +221,17 @@ def test_planner_merges_small_dimensions_and_blocks_tensors():
     assert B.shampoo_workspace_bytes(cfg_for([(64, 64, 9)], 128)) > 2 * 4 * (64 * 64 * 2 + 81)
 
 
+def test_blocks_of_tensors_of_different_order_do_not_share_a_bucket():
+    """A block that is one index thick in the last dimension of an order-4 tensor measures the same as one of an order-3
+    tensor; its roots have another exponent and it has one factor more."""
+    shapes = [(6, 8, 9), (6, 8, 9, 9)]
+    for order in (shapes, shapes[::-1]):
+        t, nb = B.shampoo_plan(cfg_for(order, 8))
+        assert {int(r[5]) for r in t if r[0] == 0}.isdisjoint({int(r[5]) for r in t if r[0] == 1})
+        for r in t:
+            assert int(r[7]) == 4 | len(order[int(r[0])]) << 4
+
+
 @pytest.mark.parametrize("s,halves", [(2, 0), (6, 0), (64, 0), (128, 0), (4, 1), (16, 1), (64, 1),
                                       (4, 2), (8, 2), (12, 2), (32, 2), (64, 2), (256, 2)])
 def test_jacobi_pair_schedule_is_a_tournament(s, halves):
