@@ -160,7 +160,7 @@ int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap,
 
 /* Bytes of device workspace shampoo_create needs for cfg; 0 if cfg is invalid.  Beside the state (factors, roots,
  * A, M, the last direction) it holds scratch of the size of the largest bucket, scratch of the root refresh (at most
- * about 3 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66), and for blocks
+ * about 4 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66), and for blocks
  * whose products run on the 16-bit matrix cores a second copy of the roots: 4 bytes per element, 6 for float32
  * directions, whose planes take up to 2 GiB more. */
 size_t shampoo_workspace_bytes(const shampoo_config *cfg);
@@ -282,7 +282,7 @@ int shampoo_destroy(shampoo_opt *opt);
  * workspace: device, 256-byte aligned, at least
  *         shampoo_root_inverse_workspace_bytes(n, batch) bytes: what the faster path without
  *         eigenvectors takes (128 < n <= 2048; 33 MB a matrix at n = 1024, chunks of at most
- *         3 GiB).  Where lambda is given, shampoo_root_inverse_warm_workspace_bytes(n, batch)
+ *         4 GiB).  Where lambda is given, shampoo_root_inverse_warm_workspace_bytes(n, batch)
  *         are enough for n > 128 (half of it)
  * failed: device int32[batch] set to 1 where A_i or its spectrum is not
  *         finite (X_i is then left untouched), else 0; or NULL
