@@ -24,7 +24,7 @@
 // scaled values stay below 2^14 (pow2_scale_f16): elements down to 2^-16 of the bound keep both
 // terms normal, smaller ones lose relative but not absolute accuracy (error <= 2^-39 of the
 // bound).  Roots get their scale when they are split, after each refresh (matrix_stats_kernel,
-// split2h_kernel); the gradient block from max |G| found by the grafting pass of the same step;
+// split_roots_kernel); the gradient block from max |G| found by the grafting pass of the same step;
 // T = c1 Lbar G from the bound c1 ||Lbar||_inf max |G| (x2_scales_kernel).  All scales are
 // powers of two, so undoing them is exact.
 //

@@ -10,8 +10,8 @@
 // The poles are spaced evenly on a logarithmic axis, from e^-3 lo to e^4 hi; the weights are the
 // least-squares fit of the relative error over [lo, hi] (the Stieltjes integral of x^-r by the
 // trapezoidal rule on that axis, with its two infinite tails folded into the outermost weights).
-// With 7 + 0.866 ln(hi / lo) poles the relative error is below 1.2e-7 at r = 1/4, 2e-7 at r = 1/2 and
-// 4e-7 at r = 2/3; from about 3/4 on the poles would have to reach further down, and rat_table says no.
+// With 7 + 0.866 ln(hi / lo) poles the relative error is below 1.3e-7 at r = 1/4 and 2.3e-7 at r = 1/2.
+// rat_table accepts 4e-7, which is r <= 0.663 (2/3 would be 4.1e-7); above, the poles would have to reach further down.
 // hi / lo comes in classes of 2^4, 2^8, ... 2^48, so that a matrix pays for the spread that it has.
 #pragma once
 #include <cmath>

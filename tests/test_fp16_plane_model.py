@@ -1,9 +1,10 @@
-"""The arithmetic behind the fp16-plane products of the GPU path, checked in numpy on the CPU:
+"""The arithmetic behind the split products of the GPU path, checked in numpy on the CPU.  fp16 planes:
 a float32 matrix scaled by a power of two below 2^14 and split into two fp16 terms loses at most
 2^-22 of each element (or 2^-25 / scale absolutely, for elements far below the largest), the
 three products (h,h) (h,l) (l,h) accumulated in float32 reproduce the float64 product to
-float32 accuracy, and undoing the power-of-two scales is exact.  This is a model of the scheme,
-not of the kernel: no code is shared with the HIP path."""
+float32 accuracy, and undoing the power-of-two scales is exact.  bf16 planes: three of them are the
+float32 value, at any size, and the six products of the GPU path leave out 2^-24 at most.  This is a
+model of the scheme, not of the kernel: no code is shared with the HIP path."""
 import numpy as np
 import pytest
 
@@ -70,3 +71,34 @@ def test_a_scaled_bf16_gradient_is_one_exact_fp16_plane():
     exact = gh.astype(np.float64) / s == g.astype(np.float64)
     # 8 significant bits fit into 11; only elements below 2^-31 of the largest could round
     assert exact[np.abs(g) >= 2.0 ** -31 * np.abs(g).max()].all()
+
+
+def bf16(x):
+    """float32 rounded to bf16, to nearest even, as float32"""
+    u = x.view(np.uint32)
+    return ((u + np.uint32(0x7FFF) + ((u >> np.uint32(16)) & np.uint32(1))) & np.uint32(0xFFFF0000)).view(np.float32)
+
+
+def split3b(x):
+    h = bf16(x)
+    l = bf16(x - h)
+    return h, l, bf16(x - h - l)
+
+
+def test_three_bf16_planes_are_the_float32():
+    rng = np.random.default_rng(10)
+    x = rng.standard_normal(200000).astype(np.float32) * np.exp2(rng.uniform(-76.0, 14.0, 200000)).astype(np.float32)
+    x = np.concatenate([x, np.float32([0.0, 1.0, -1.0, 2.0 ** 14 - 2.0 ** -10, 1.0 + 2.0 ** -23, 1.0 - 2.0 ** -24, 2.0 ** -8 + 2.0 ** -31])])
+    h, l, m = split3b(x)
+    assert (h.astype(np.float64) + l.astype(np.float64) + m.astype(np.float64) == x.astype(np.float64)).all()
+    assert (np.abs(l) <= 2.0 ** -8 * np.abs(x)).all() and (np.abs(m) <= 2.0 ** -16 * np.abs(x)).all()
+
+
+def test_six_products_of_three_bf16_planes():
+    rng = np.random.default_rng(11)
+    x, y = (rng.uniform(1.0, 2.0, 200000).astype(np.float32) * np.exp2(rng.uniform(-60.0, 14.0, 200000)).astype(np.float32) for _ in range(2))
+    p, q = ([v.astype(np.float64) for v in split3b(z)] for z in (x, y))
+    six = p[0] * q[2] + p[2] * q[0] + p[1] * q[1] + p[0] * q[1] + p[1] * q[0] + p[0] * q[0]
+    want = x.astype(np.float64) * y.astype(np.float64)
+    err = np.abs(six - want) / want
+    assert err.max() <= 2.0 ** -24 and np.sqrt(np.mean(err ** 2)) <= 2.0 ** -26

@@ -134,7 +134,8 @@ def test_more_blocks_than_the_planes_have_room_for():
 @pytest.mark.parametrize("name,sigma,eps,span", [("tiny", 1e-15, 1e-30, False), ("huge", 1e10, 1e20, False), ("rows", 1e-3, 1e-9, True)])
 def test_float32_gradients_in_planes(name, sigma, eps, span):
     """Blocks with ragged tiles and ragged k (136 = 128 + 8, 264 = 256 + 8, k % 32 of 8, 16 and 24) whose gradients
-    are tiny, huge, or span six decades from row to row, and a zero block: factors, products, directions."""
+    are tiny, huge, or span six decades from row to row, and a zero block: factors, products, directions, by the norms of
+    whole blocks (test_small_rows_and_columns_keep_their_accuracy looks at the small rows by themselves)."""
     shapes = [(256, 384), (392, 144), (152, 264)]
     p = Pair(shapes, 256, 0.999, 1, eps=eps, eps_g=sigma * 1e-7)
     for t in range(3):
