@@ -75,6 +75,24 @@ __device__ __forceinline__ void store_f4(float *p, bool vec, int valid, const fl
   for (int e = 0; e < 4; ++e) if (e < valid) p[e] = v[e];
 }
 
+// Four consecutive elements at any address of the element type's alignment: global loads and stores of 8 and 16 bytes
+// need no alignment of their own.
+typedef float ew_float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t ew_ushort4u __attribute__((ext_vector_type(4), aligned(2)));
+template <typename GT>
+__device__ __forceinline__ void load_u4(const GT *p, float (&v)[4]) {
+  if constexpr (sizeof(GT) == 2) {
+    const ew_ushort4u x = *reinterpret_cast<const ew_ushort4u *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32(x[e]);
+  } else {
+    const ew_float4u x = *reinterpret_cast<const ew_float4u *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = x[e];
+  }
+}
+__device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reinterpret_cast<ew_float4u *>(p) = ew_float4u{v[0], v[1], v[2], v[3]}; }
+
 // grid: chunks * (blocks of the bucket) workgroups, chunk index fastest.
 // GS / GD: element types of the state-source and direction-source gradients.
 template <typename GS, typename GD>

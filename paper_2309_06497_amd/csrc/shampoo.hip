@@ -108,6 +108,8 @@ struct Bucket {
   size_t off_mid[2] = {0, 0}, off_midinv[2] = {0, 0}, off_desc3 = 0;
   int32_t split3 = 1;   // row ranges of the (N / d_last) x d_last unfolding whose Gram matrices are formed separately
   bool whole() const { return diagL || diagR; }
+  bool wide = false;   // of a parameter so wide that the bytes of a block's rows span more than 2^31
+  bool small() const { return m <= SB && n <= SB && !whole() && !t3 && !wide; }   // one workgroup per block (block_step_small.h)
   int32_t dlast() const { return modes > 1 ? td[modes - 1] : 1; }
   int32_t rdim() const { return t3 ? dlast() : n; }
   size_t l_elems() const { return diagL ? (size_t)m : (size_t)m * m; }
@@ -119,7 +121,8 @@ struct Plan {
   std::vector<std::vector<int32_t>> param_blocks;  // per parameter: indices into blocks (row-major)
   std::vector<int64_t> param_state_offset;         // element offset of each parameter in A / M
   std::vector<DiagChunk> diag_chunks;   // 1-D parameters
-  std::vector<DiagChunk> prep_chunks;   // 2-D parameters, flat (used by the l2 / filtering pre-pass)
+  std::vector<DiagChunk> prep_chunks;   // 2-D parameters, flat (used by the l2 / filtering pre-pass); the first n_prep_rest
+  int64_t n_prep_rest = 0;              // of them of parameters that are not made of small blocks only
   std::vector<PShape> pshape;           // per parameter
   int64_t total_elems = 0;
 };
@@ -337,7 +340,16 @@ void make_plan(const shampoo_config *c, Plan &p) {
     if (blk.tensor) continue;
     const int64_t ld = p.pshape[blk.param].cols;
     if (ld % 8 != 0 || (blk.row0 * ld + blk.col0) % 8 != 0) p.buckets[blk.bucket].bf16_mfma = false;
+    if (ld > (int64_t)1 << 22) p.buckets[blk.bucket].wide = true;
   }
+  auto only_small = [&](int32_t param) {
+    for (int32_t k : p.param_blocks[param]) if (!p.buckets[p.blocks[k].bucket].small()) return false;
+    return true;
+  };
+  std::vector<char> is_small(c->n_params);
+  for (int i = 0; i < c->n_params; ++i) is_small[i] = only_small(i);
+  p.n_prep_rest = std::stable_partition(p.prep_chunks.begin(), p.prep_chunks.end(), [&](const DiagChunk &d) { return !is_small[d.param]; }) -
+                  p.prep_chunks.begin();
   for (auto &bk : p.buckets) {
     if (bk.t3 && bk.modes >= 3) {
       // the factor of the last dimension sums over N / d_last rows into one small tile per
@@ -1033,6 +1045,8 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
 // ---------------------------------------------------------------------------
 // The optimizer object
 // ---------------------------------------------------------------------------
+enum : char { UPPER_FRESH = 0, UPPER_TILES_STALE = 1, UPPER_HALF_STALE = 2 };   // the tiles above the diagonal of tiles; all above the diagonal
+
 struct shampoo_opt {
   shampoo_config cfg;
   std::vector<int32_t> ndim;
@@ -1043,6 +1057,8 @@ struct shampoo_opt {
   // workspace offsets
   size_t off_G1 = 0, off_Gf = 0, off_g1tab = 0, off_gftab = 0, off_prep = 0, off_small = 0;
   int64_t n_small = 0;     // blocks of at most 128 x 128 (single-workgroup step kernel)
+  bool small_half = false; // all of them at most 64 x 64
+  int64_t n_prep_rest = 0; // of plan.prep_chunks, the first ones: parameters with other blocks too
   bool use_l2 = false, use_b1 = false;
   size_t off_A = 0, off_M = 0, off_T = 0, off_wtab = 0, off_gtab = 0, off_diag = 0, off_count = 0, off_eig = 0;
   std::vector<EigLayout> eig_L, eig_R, eig_mid[2];   // per bucket (eig_mid: the middle dimensions of tensor blocks)
@@ -1055,7 +1071,7 @@ struct shampoo_opt {
   std::vector<void *> last_w, last_g;    // the caller's pointers of the last step (what the device tables name)
   AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
-  std::vector<char> upper_stale;         // per bucket: the factors' tiles above the diagonal of tiles are out of date
+  std::vector<char> upper_stale;         // per bucket: which part of the factors is out of date (UPPER_*)
   int64_t last_step = -1;
   int64_t n_refresh = 0;
   bool timing = false;
@@ -1167,7 +1183,9 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   const size_t offG = take((size_t)c->n_params * sizeof(void *));
   const size_t offD = take(std::max<size_t>(1, p.diag_chunks.size()) * sizeof(DiagChunk));
   int64_t n_small = 0;
-  for (auto &b : p.buckets) if (b.m <= SB && b.n <= SB && !b.whole() && !b.t3) n_small += b.count;
+  bool small_half = true;
+  for (auto &b : p.buckets)
+    if (b.small()) { n_small += b.count; small_half = small_half && b.m <= SB_HALF && b.n <= SB_HALF; }
   const size_t offSmall = take(std::max<size_t>(1, (size_t)n_small) * sizeof(SmallBlock));
   const size_t offC = take(64);
   const size_t offNf = take(max_count * 4);
@@ -1177,7 +1195,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     o->off_G1 = offG1; o->off_Gf = offGf; o->off_g1tab = offG1tab; o->off_gftab = offGftab; o->off_prep = offPrep;
     o->use_l2 = use_l2; o->use_b1 = use_b1; o->off_wtab = offW; o->off_gtab = offG;
     o->off_diag = offD; o->off_count = offC; o->off_eig = offE;
-    o->off_small = offSmall; o->n_small = n_small;
+    o->off_small = offSmall; o->n_small = n_small; o->small_half = small_half; o->n_prep_rest = p.n_prep_rest;
     o->eig_L = eL; o->eig_R = eR; o->eig_mid[0] = eM[0]; o->eig_mid[1] = eM[1];
     o->upper_stale.assign(o->plan.buckets.size(), 0);
     o->off_nfail = offNf;
@@ -1252,21 +1270,23 @@ int newton_root_guarded(shampoo_opt *o, const float *F, int dim, int count, floa
                               &o->aux, flags);
 }
 
-// The bf16 factor update writes only the tiles on and below the diagonal of tiles; whoever
-// needs the whole symmetric factor (the refresh, the state query) completes it first.
+// The bf16 factor update writes only the tiles on and below the diagonal of tiles, the step of a small block in one
+// workgroup only the lower triangle; whoever needs the whole symmetric factor (the refresh, the state query) completes
+// it first.
 int complete_factors(shampoo_opt *o, size_t bucket, hipStream_t s) {
-  if (!o->upper_stale[bucket]) return SHAMPOO_OK;
+  if (o->upper_stale[bucket] == UPPER_FRESH) return SHAMPOO_OK;
   const Bucket &b = o->plan.buckets[bucket];
   const int dims[2] = {(int)b.m, (int)b.n};
   const size_t offs[2] = {b.off_L, b.off_R};
   for (int side = 0; side < 2; ++side) {
     const int n = dims[side], pieces = (n + 31) / 32;
-    if (n <= BM) continue;   // a single tile: nothing above the diagonal
+    const int all = o->upper_stale[bucket] == UPPER_HALF_STALE ? 1 : 0;
+    if (n <= (all ? 1 : BM)) continue;   // a single tile: nothing above the diagonal of tiles
     hipLaunchKernelGGL(mirror_upper_tiles_kernel, dim3(pieces, pieces, b.count), dim3(256), 0, s,
-                       reinterpret_cast<float *>(o->ws + offs[side]), (int64_t)n * n, n);
+                       reinterpret_cast<float *>(o->ws + offs[side]), (int64_t)n * n, n, all);
   }
   HIP_TRY(hipGetLastError());
-  o->upper_stale[bucket] = 0;
+  o->upper_stale[bucket] = UPPER_FRESH;
   return SHAMPOO_OK;
 }
 
@@ -1386,30 +1406,40 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     HIP_TRY(hipGetLastError());
   }
 
-  if ((o->use_l2 || o->use_b1) && !p.prep_chunks.empty()) {
+  // Blocks of at most 128 x 128 take the whole step in one workgroup (gradient block
+  // resident in LDS) whenever no refresh separates the factor update from the
+  // preconditioning (l2 weight decay and SGD grafting go stage by stage).
+  const bool small_ok = use_shampoo && !refresh && !o->use_l2 && !sgd && o->n_small > 0;
+  auto fused = [&](const Bucket &b) { return small_ok && b.small(); };
+  const int64_t n_prep = small_ok ? o->n_prep_rest : (int64_t)p.prep_chunks.size();
+  if ((o->use_l2 || o->use_b1) && n_prep > 0) {
     StageTimer t(o, SHAMPOO_STAGE_GRAFT, s);
     PrepArgs pa;
     pa.chunks = reinterpret_cast<const DiagChunk *>(ws + o->off_prep);
     pa.w_table = wtab; pa.g_table = gtab; pa.g1 = G1; pa.gf = Gf; pa.wd_l2 = wd_l2; pa.beta1 = c.beta1;
-    hipLaunchKernelGGL(prep_kernel<GT>, dim3((unsigned)p.prep_chunks.size()), dim3(EW_THREADS), 0, s, pa);
+    hipLaunchKernelGGL(prep_kernel<GT>, dim3((unsigned)n_prep), dim3(EW_THREADS), 0, s, pa);
     HIP_TRY(hipGetLastError());
   }
-  // Blocks of at most 128 x 128 take the whole step in one workgroup (gradient block
-  // resident in LDS) whenever no refresh separates the factor update from the
-  // preconditioning and the default heuristics are in force.
-  const bool small_ok = use_shampoo && !refresh && !o->use_l2 && !o->use_b1 && !sgd;
-  auto fused = [&](const Bucket &b) { return small_ok && b.m <= SB && b.n <= SB && !b.whole() && !b.t3; };
-  if (small_ok && o->n_small > 0) {
+  if (small_ok) {
     StageTimer t(o, SHAMPOO_STAGE_FUSED, s);
     SmallStepArgs f;
     f.blocks = reinterpret_cast<const SmallBlock *>(ws + o->off_small); f.ws = ws;
-    f.w_table = wtab; f.g_table = gtab; f.a_state = A; f.m_state = M;
+    f.w_table = wtab; f.g_table = gtab; f.a_state = A; f.m_state = M; f.gf_state = Gf;
     f.alpha_d = alpha; f.beta_d = beta;
     f.graft_eps = c.graft_epsilon; f.mu = c.momentum; f.lr = lr; f.wd_decoupled = wd_dec;
     f.nesterov = c.use_nesterov ? 1 : 0;
-    f.a_decay = a_decay; f.a_gain = a_gain; f.a_bc = a_bc;
-    hipLaunchKernelGGL(block_step_small_kernel<GT>, dim3((unsigned)o->n_small), dim3(SB_THREADS), 0, s, f);
+    f.a_decay = a_decay; f.a_gain = a_gain; f.a_bc = a_bc; f.beta1 = c.beta1; f.gd_scale = c1;
+    const dim3 grid((unsigned)o->n_small), block(SB_THREADS);
+    constexpr bool FILT_ONLY = sizeof(GT) == 2 && sizeof(GD) == 4;   // bf16 gradients with float directions are filtered
+    if (FILT_ONLY || Gf) {
+      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, true>), grid, block, 0, s, f);
+      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, true>), grid, block, 0, s, f);
+    } else {
+      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, false>), grid, block, 0, s, f);
+      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, false>), grid, block, 0, s, f);
+    }
     HIP_TRY(hipGetLastError());
+    for (size_t i = 0; i < p.buckets.size(); ++i) if (p.buckets[i].small()) o->upper_stale[i] = UPPER_HALF_STALE;
   }
   // scales of the fp16 operands of a bucket's preconditioning products (and of R's update)
   auto launch_x2_scales = [&](const Bucket &b) {
@@ -1479,7 +1509,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       hipLaunchKernelGGL(transpose_bf16_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, ta);
       SyrkBf16Args sa{};
       sa.desc = desc; sa.ptr_table = gs_tab; sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
-      o->upper_stale[&b - p.buckets.data()] = 1;   // the kernel writes the tiles on and below the diagonal only
+      // the kernel reads and writes the tiles on and below the diagonal, those on it whole
+      if (o->upper_stale[&b - p.buckets.data()] == UPPER_HALF_STALE && (rc = complete_factors(o, &b - p.buckets.data(), s))) return rc;
+      o->upper_stale[&b - p.buckets.data()] = UPPER_TILES_STALE;
       // L <- beta L + alpha G G^T
       sa.a.from_table = 1;
       sa.c = reinterpret_cast<float *>(ws + b.off_L); sa.c_batch_stride = (int64_t)b.m * b.m; sa.ldc = b.m;
@@ -1514,7 +1546,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       // float32 gradients: both factors from three bf16 planes
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
       launch_x2_scales(b);
-      o->upper_stale[&b - p.buckets.data()] = 1;
+      o->upper_stale[&b - p.buckets.data()] = UPPER_TILES_STALE;
       if (b.plane_chunk == b.count) cols_in_T = &b;
       for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
         const int cnt = std::min(b.plane_chunk, b.count - b0);
@@ -1536,7 +1568,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       HIP_TRY(hipGetLastError());
     } else {
       StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
-      o->upper_stale[&b - p.buckets.data()] = 0;   // these kernels read the lower triangle and write both
+      o->upper_stale[&b - p.buckets.data()] = UPPER_FRESH;   // these kernels read the lower triangle and write both
       GemmArgs g{};
       g.a.from_table = 1; g.b.from_table = 1;
       g.desc = desc; g.ptr_table = gs_tab;
@@ -2088,12 +2120,14 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
   if (o->n_small > 0) {
     // largest blocks first, so that the tail of the launch is made of the cheapest workgroups
     std::vector<SmallBlock> small;
+    std::vector<char> only_small(cfg->n_params, 1);
+    for (const Block &b : p.blocks) if (!p.buckets[b.bucket].small()) only_small[b.param] = 0;
     for (size_t i = 0; i < p.buckets.size(); ++i) {
       const Bucket &b = p.buckets[i];
-      if (b.m > SB || b.n > SB || b.whole() || b.t3) continue;
+      if (!b.small()) continue;
       for (int64_t k = 0; k < b.count; ++k) {
         SmallBlock sb;
-        sb.d = descs[i][k]; sb.m = b.m; sb.n = b.n;
+        sb.d = descs[i][k]; sb.m = b.m; sb.n = b.n; sb.filter = only_small[sb.d.param];
         sb.off_L = (int64_t)(b.off_L + (size_t)k * b.m * b.m * 4); sb.off_R = (int64_t)(b.off_R + (size_t)k * b.n * b.n * 4);
         sb.off_Linv = (int64_t)(b.off_Linv + (size_t)k * b.m * b.m * 4);
         sb.off_Rinv = (int64_t)(b.off_Rinv + (size_t)k * b.n * b.n * 4);

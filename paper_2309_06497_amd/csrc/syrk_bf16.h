@@ -302,13 +302,13 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
 #undef SYRK_WAIT
 #undef SYRK_SLAB_PRODUCT
 
-// C[i][j] = C[j][i] for every element whose tile (of BM x BM) lies above the diagonal of tiles:
-// completes a factor that syrk_bf16_kernel has updated.  grid (ceil(n / 32),
-// ceil(n / 32), batch), 256 threads; a 32 x 32 piece never straddles two tiles.
-__global__ __launch_bounds__(256) void mirror_upper_tiles_kernel(float *c, int64_t batch_stride, int n) {
+// C[i][j] = C[j][i] for every element whose tile (of BM x BM) lies above the diagonal of tiles, or, `all`, for every
+// element above the diagonal: completes a factor that syrk_bf16_kernel, or block_step_small_kernel, has updated.
+// grid (ceil(n / 32), ceil(n / 32), batch), 256 threads; a 32 x 32 piece never straddles two tiles.
+__global__ __launch_bounds__(256) void mirror_upper_tiles_kernel(float *c, int64_t batch_stride, int n, int all) {
   __shared__ float t[32][33];
   const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;     // destination piece (i0, j0)
-  if (i0 / BM >= j0 / BM) return;
+  if (all ? i0 > j0 : i0 / BM >= j0 / BM) return;
   float *m = c + (int64_t)blockIdx.z * batch_stride;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void mirror_upper_tiles_kernel(float *c, int64
 #pragma unroll
   for (int r = ty; r < 32; r += 8) {
     const int di = i0 + r, dj = j0 + tx;
-    if (di < n && dj < n) m[(int64_t)di * n + dj] = t[tx][r];
+    if (di < dj && dj < n) m[(int64_t)di * n + dj] = t[tx][r];
   }
 }
 
