@@ -18,8 +18,8 @@
 // five or six vector instructions an element) and a product is six v_mfma_f32_32x32x16_bf16, 192 cycles for 16 values of k
 // where the float32 matrix cores take 512; an unfiltered bf16 gradient is one term by itself.  The splitting and the
 // matrix cores then take about the same time, and together less than the memory traffic.  Sums of the
-// factors: those of 16 values of k start from zero, the small products first (one rounding of full size, against eight on
-// the float32 matrix cores), and go into float64; of a bf16 gradient 32 values of k.
+// factors: those of 32 values of k start from zero, the small products first (two roundings of full size, against sixteen on
+// the float32 matrix cores), and go into float64.
 // G is scaled by a power of two where its largest element is outside 2^-40 ... 2^40, so that no term underflows.
 //
 // One step of 512 blocks of 128 x 128, of ResNet-50 in blocks of 128, and of nine blocks of at most 64 x 64, float32 matrix
@@ -78,15 +78,25 @@ __device__ __forceinline__ float sb_reduce(float v, float *red, int tid) {
 typedef float sb_floatx8 __attribute__((ext_vector_type(8)));
 // x = h + l + m, eight elements (bf16_planes.h)
 struct SbTerms { bf16x8 h, l, m; };
+// two of them rounded, and what that leaves (written out: from vector conversions the compiler makes every one twice)
+__device__ __forceinline__ uint32_t sb_round2(float &x, float &y, bool left) {
+  typedef float pair __attribute__((ext_vector_type(2)));
+  typedef __bf16 bpair __attribute__((ext_vector_type(2)));
+  const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair{x, y}, bpair));
+  if (left) { x -= __uint_as_float(u << 16); y -= __uint_as_float(u & 0xffff0000u); }
+  return u;
+}
 template <bool ONE>      // ONE: x holds bf16 values
 __device__ __forceinline__ void sb_split(sb_floatx8 x, SbTerms &t) {
-  t.h = __builtin_convertvector(x, bf16x8);
-  if constexpr (!ONE) {
-    x -= __builtin_convertvector(t.h, sb_floatx8);
-    t.l = __builtin_convertvector(x, bf16x8);
-    x -= __builtin_convertvector(t.l, sb_floatx8);
-    t.m = __builtin_convertvector(x, bf16x8);
+  u32x4 h, l, m;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float a = x[2 * e], b = x[2 * e + 1];
+    h[e] = sb_round2(a, b, !ONE);
+    if constexpr (!ONE) { l[e] = sb_round2(a, b, true); m[e] = sb_round2(a, b, false); }
   }
+  t.h = __builtin_bit_cast(bf16x8, h);
+  if constexpr (!ONE) { t.l = __builtin_bit_cast(bf16x8, l); t.m = __builtin_bit_cast(bf16x8, m); }
 }
 __device__ __forceinline__ floatx16 sb_mfma(const bf16x8 &a, const bf16x8 &b, const floatx16 &c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -148,39 +158,49 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int v = 0; v < 16; ++v) old[t][v] = sb_get(f, at[t] + (8 * (v >> 2) + (v & 3)) * stride);
-  floatx16 acc[2];
   double sum[2][16];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { acc[t][v] = 0.f; sum[t][v] = 0.0; }
+    for (int v = 0; v < 16; ++v) sum[t][v] = 0.0;
   auto operand = [&](int first, int k) {
     return WHICH == 0 ? sb_row8<LD>(Gs, first + l32, k + 8 * khalf) : sb_col8<LD>(Gs, k + 8 * khalf, first + l32);
   };
-  auto tile = [&](int t, const SbTerms &a, const SbTerms &b) {
-    if constexpr (!ONE) {
-      acc[t] = sb_mfma(a.h, b.m, acc[t]);
-      acc[t] = sb_mfma(a.m, b.h, acc[t]);
-      acc[t] = sb_mfma(a.l, b.l, acc[t]);
-      acc[t] = sb_mfma(a.h, b.l, acc[t]);
-      acc[t] = sb_mfma(a.l, b.h, acc[t]);
-    }
-    acc[t] = sb_mfma(a.h, b.h, acc[t]);
+  auto small_products = [&](const SbTerms &a, const SbTerms &b, floatx16 c) {
+    c = sb_mfma(a.h, b.m, c);
+    c = sb_mfma(a.m, b.h, c);
+    c = sb_mfma(a.l, b.l, c);
+    c = sb_mfma(a.h, b.l, c);
+    return sb_mfma(a.l, b.h, c);
   };
+  // 32 values of k from zero accumulators (G is zero from K on): both sets of small products, then both h h'
 #pragma unroll 1
-  for (int k = 0; k < K; k += 16) {
-    SbTerms a, b0, b1;
-    sb_split<ONE>(operand(row0, k), a);
-    if (I == J) b0 = a; else sb_split<ONE>(operand(col0, k), b0);
-    if (two) { if (I == J + 1) b1 = a; else sb_split<ONE>(operand(col0 + 32, k), b1); }
-    tile(0, a, b0);
-    if (two) tile(1, a, b1);
-    if (!ONE || (k & 16) || k + 16 >= K) {
+  for (int k = 0; k < K; k += 32) {
+    floatx16 acc[2] = {};
+    bf16x8 ah[2], bh[2][2];
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { sum[t][v] += (double)acc[t][v]; acc[t][v] = 0.f; }
+    for (int s = 0; s < 2; ++s) {
+      SbTerms a, b0, b1;
+      sb_split<ONE>(operand(row0, k + 16 * s), a);
+      if (I == J) b0 = a; else sb_split<ONE>(operand(col0, k + 16 * s), b0);
+      ah[s] = a.h; bh[s][0] = b0.h;
+      if constexpr (!ONE) acc[0] = small_products(a, b0, acc[0]);
+      if (two) {
+        if (I == J + 1) b1 = a; else sb_split<ONE>(operand(col0 + 32, k + 16 * s), b1);
+        bh[s][1] = b1.h;
+        if constexpr (!ONE) acc[1] = small_products(a, b1, acc[1]);
+      }
     }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) acc[0] = sb_mfma(ah[s], bh[s][0], acc[0]);
+    if (two)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) acc[1] = sb_mfma(ah[s], bh[s][1], acc[1]);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[0][v] += (double)acc[0][v];
+    if (two)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[1][v] += (double)acc[1][v];
   }
   // of a tile on the diagonal the lower half
   const bool diag[2] = {I == J, I == J + 1};
@@ -417,19 +437,6 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
 #pragma unroll
     for (int s = 0; s < RING; ++s) request_r(s, 16 * s);
   }
-  // W and M are wanted after the next products: a word of each of their lines is asked for, so that they come from the
-  // caches then
-  float warm = 0.f;
-  if constexpr (TT > 1) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = (tid >> 2) + 64 * u, j = (tid & 3) * 32;
-      if (i < m && j < n) {
-        warm += wp[(int64_t)i * ld + j];
-        if (mp) warm += mp[(int64_t)i * ld + j];
-      }
-    }
-  }
   __syncthreads();        // every wavefront has finished reading G
   if (active) {
 #pragma unroll
@@ -498,7 +505,6 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
             if (row_of(x, v) < m && c0 + 32 * y + l32 < n) sp += p * p;
           }
   }
-  if constexpr (TT > 1) asm volatile("" :: "v"(warm));
   sp = sb_reduce(sp, red[3], tid);
   if (tid == 0) norms[1] = sp;
   if (!active) return;
