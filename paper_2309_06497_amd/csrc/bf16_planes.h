@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "group.h"
 
 namespace shampoo {
 
@@ -30,18 +31,23 @@ struct BlockPlanesArgs {
   uint16_t *cols; int64_t plane_stride;  // [plane][slot][n][m]
   uint16_t *rows;                        // the same not transposed, [plane][slot][m][n] (nullptr: not wanted)
   const float *scale;                    // [slot] s
-  int32_t m, n;
+  int32_t m, n, blocks;
+  __device__ __forceinline__ void globals() { to_global(desc, g_table, cols, rows, scale); }
 };
 // The planes of s G_block, transposed and as they lie: operands that are read along k.  Reads 4 and writes 6 (12)
 // bytes per element, 16 bytes per lane on both sides; the transposition happens in LDS (rows of 65 words: the 64 lanes
 // of a read hit 64 banks).  Requires m % 8 == 0, n % 8 == 0 and 16-byte aligned rows.
-// grid (ceil(n / 64), ceil(m / 64), blocks), 256 threads.
-__global__ __launch_bounds__(256) void block_planes_kernel(const BlockPlanesArgs g) {
+// Workgroups: ceil(n / 64) x ceil(m / 64) x blocks, in that order; 256 threads.
+__global__ __launch_bounds__(256) void block_planes_kernel(const Group<BlockPlanesArgs> grp) {
   __shared__ float tile[64][65];
-  const BlockDesc d = g.desc[blockIdx.z];
-  const float *src = reinterpret_cast<const float *>(g.g_table[d.param]) + d.offset;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64, tid = threadIdx.x;
-  const float sc = g.scale[blockIdx.z];
+  int wg;
+  const BlockPlanesArgs g = group_pick(grp, wg);
+  const int gx = (g.n + 63) / 64, gy = (g.m + 63) / 64, slot = wg / (gx * gy), ty = (wg - slot * gx * gy) / gx, tx = wg % gx;
+  if (slot >= g.blocks) return;
+  const BlockDesc d = g.desc[slot];
+  const float *src = global_ptr<const float>(g.g_table[d.param]) + d.offset;
+  const int i0 = ty * 64, j0 = tx * 64, tid = threadIdx.x;
+  const float sc = g.scale[slot];
   float4 v[4];
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
@@ -68,7 +74,7 @@ __global__ __launch_bounds__(256) void block_planes_kernel(const BlockPlanesArgs
 #pragma unroll
     for (int t = 0; t < 3; ++t) *reinterpret_cast<uint4 *>(dst + t * g.plane_stride) = make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
   };
-  const int64_t block = (int64_t)blockIdx.z * g.m * g.n;
+  const int64_t block = (int64_t)slot * g.m * g.n;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int x = tid + 256 * q, r = x >> 3, c = (x & 7) * 8;

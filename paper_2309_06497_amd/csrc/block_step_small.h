@@ -246,8 +246,8 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
   const int m = sbk.m, n = sbk.n;
   const BlockDesc d = sbk.d;
   float *norms = reinterpret_cast<float *>(g.ws + sbk.off_norms);
-  const GT *gp = reinterpret_cast<const GT *>(g.g_table[d.param]) + d.offset;
-  float *wp = reinterpret_cast<float *>(g.w_table[d.param]) + d.offset;
+  const GT *gp = global_ptr<const GT>(g.g_table[d.param]) + d.offset;
+  float *wp = global_ptr<float>(g.w_table[d.param]) + d.offset;
   float *ap = g.a_state + d.state_offset;
   float *mp = g.m_state ? g.m_state + d.state_offset : nullptr;
   float *fp = FILT ? g.gf_state + d.state_offset : nullptr;

@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "group.h"
 
 namespace shampoo {
 
@@ -33,7 +34,7 @@ struct EwArgs {
   float *sg_partial;             // [slot][chunks]
   float *gmax_partial;           // graft_kernel: [slot][chunks] max |G| of the chunk (nullptr: not wanted)
   const float *scale;            // [slot]
-  int32_t m, n;
+  int32_t m, n, blocks;
   EwGeom geom;
   float graft_eps, mu, lr;
   float gd_scale;                // direction gradients are multiplied by this (bias correction, 1 = off)
@@ -45,6 +46,7 @@ struct EwArgs {
   int32_t sgd_graft;             // P_graft = G (no grafting state) instead of AdaGrad
   int32_t same_src;              // g_table and gd_table are the same tensors
   int32_t graft_only;            // update_kernel: use -P_graft instead of scale * P
+  __device__ __forceinline__ void globals() { to_global(desc, w_table, g_table, gd_table, a_state, m_state, p, sg_partial, gmax_partial, scale); }
 };
 
 template <typename GT>
@@ -93,15 +95,18 @@ __device__ __forceinline__ void load_u4(const GT *p, float (&v)[4]) {
 }
 __device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reinterpret_cast<ew_float4u *>(p) = ew_float4u{v[0], v[1], v[2], v[3]}; }
 
-// grid: chunks * (blocks of the bucket) workgroups, chunk index fastest.
+// workgroups of a bucket: chunks * blocks, chunk index fastest.
 // GS / GD: element types of the state-source and direction-source gradients.
 template <typename GS, typename GD>
-__global__ __launch_bounds__(EW_THREADS) void graft_kernel(const EwArgs g) {
+__global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> grp) {
   __shared__ float red[EW_THREADS / 64];
-  const int slot = blockIdx.x / g.geom.chunks, chunk = blockIdx.x - slot * g.geom.chunks, tid = threadIdx.x;
+  int wg;
+  const EwArgs g = group_pick(grp, wg);
+  const int slot = wg / g.geom.chunks, chunk = wg - slot * g.geom.chunks, tid = threadIdx.x;
+  if (slot >= g.blocks) return;
   const BlockDesc d = g.desc[slot];
-  const GS *gp = reinterpret_cast<const GS *>(g.g_table[d.param]) + d.offset;
-  const GD *dp = reinterpret_cast<const GD *>(g.gd_table[d.param]) + d.offset;
+  const GS *gp = global_ptr<const GS>(g.g_table[d.param]) + d.offset;
+  const GD *dp = global_ptr<const GD>(g.gd_table[d.param]) + d.offset;
   float *ap = g.a_state + d.state_offset;
   const int ld = d.ld, n = g.n;
   const bool vec = ((ld & 3) == 0) && ((n & 3) == 0) && ((d.offset & 3) == 0) && ((d.state_offset & 3) == 0) &&
@@ -193,11 +198,16 @@ struct ScaleArgs {
   const float *ssh_partial; int32_t ssh_count; // per block
   float *scale;    // [blocks]
   float *norms;    // [blocks][2]
+  int32_t blocks;
+  __device__ __forceinline__ void globals() { to_global(sg_partial, ssh_partial, scale, norms); }
 };
 
 // One wavefront per block; fixed summation order, so results are reproducible.
-__global__ __launch_bounds__(64) void scale_kernel(const ScaleArgs g) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+__global__ __launch_bounds__(64) void scale_kernel(const Group<ScaleArgs> grp) {
+  int b;
+  const ScaleArgs g = group_pick(grp, b);
+  if (b >= g.blocks) return;
+  const int lane = threadIdx.x;
   double sg = 0.0, ssh = 0.0;
   for (int i = lane; i < g.sg_count; i += 64) sg += (double)g.sg_partial[(int64_t)b * g.sg_count + i];
   for (int i = lane; i < g.ssh_count; i += 64) ssh += (double)g.ssh_partial[(int64_t)b * g.ssh_count + i];
@@ -217,11 +227,14 @@ __global__ __launch_bounds__(64) void scale_kernel(const ScaleArgs g) {
 
 // GD: element type of the direction-source gradients (read only in the grafting-only phase).
 template <typename GD>
-__global__ __launch_bounds__(EW_THREADS) void update_kernel(const EwArgs g) {
-  const int slot = blockIdx.x / g.geom.chunks, chunk = blockIdx.x - slot * g.geom.chunks, tid = threadIdx.x;
+__global__ __launch_bounds__(EW_THREADS) void update_kernel(const Group<EwArgs> grp) {
+  int wg;
+  const EwArgs g = group_pick(grp, wg);
+  const int slot = wg / g.geom.chunks, chunk = wg - slot * g.geom.chunks, tid = threadIdx.x;
+  if (slot >= g.blocks) return;
   const BlockDesc d = g.desc[slot];
-  float *wp = reinterpret_cast<float *>(g.w_table[d.param]) + d.offset;
-  const GD *gp = reinterpret_cast<const GD *>(g.gd_table[d.param]) + d.offset;
+  float *wp = global_ptr<float>(g.w_table[d.param]) + d.offset;
+  const GD *gp = global_ptr<const GD>(g.gd_table[d.param]) + d.offset;
   float *ap = g.a_state + d.state_offset;
   float *mp = g.m_state ? g.m_state + d.state_offset : nullptr;
   const int ld = d.ld, n = g.n;
@@ -338,8 +351,8 @@ struct DiagArgs {
 template <typename GT>
 __global__ __launch_bounds__(EW_THREADS) void diag_kernel(const DiagArgs g) {
   const DiagChunk c = g.chunks[blockIdx.x];
-  float *w = reinterpret_cast<float *>(g.w_table[c.param]) + c.start;
-  const GT *gp = reinterpret_cast<const GT *>(g.g_table[c.param]) + c.start;
+  float *w = global_ptr<float>(g.w_table[c.param]) + c.start;
+  const GT *gp = global_ptr<const GT>(g.g_table[c.param]) + c.start;
   float *a = g.a_state + c.state_offset;
   float *m = g.m_state ? g.m_state + c.state_offset : nullptr;
   float *gf = g.gf_state ? g.gf_state + c.state_offset : nullptr;
@@ -375,8 +388,8 @@ struct PrepArgs {
 template <typename GT>
 __global__ __launch_bounds__(EW_THREADS) void prep_kernel(const PrepArgs g) {
   const DiagChunk c = g.chunks[blockIdx.x];
-  const float *w = reinterpret_cast<const float *>(g.w_table[c.param]) + c.start;
-  const GT *gp = reinterpret_cast<const GT *>(g.g_table[c.param]) + c.start;
+  const float *w = global_ptr<const float>(g.w_table[c.param]) + c.start;
+  const GT *gp = global_ptr<const GT>(g.g_table[c.param]) + c.start;
   for (int i = threadIdx.x; i < c.len; i += EW_THREADS) {
     float gv = Elem<GT>::load1(gp + i);
     if (g.g1) { gv += g.wd_l2 * w[i]; g.g1[c.state_offset + i] = gv; }

@@ -58,6 +58,7 @@
 #include <stdint.h>
 #include "bf16_planes.h"
 #include "gemm_mfma.h"
+#include "group.h"
 #include "lds_dma.h"
 
 namespace shampoo {
@@ -84,6 +85,7 @@ struct GemmX2Args {
   const float *out_scale;  // [batch] further factor on the result (a power of two; nullptr: none)
   float *norm_partial;     // X2_STORE_NORM: [batch][tiles] sums of squares of the stored tile
   int32_t tiles_m, tiles_n, batch;
+  __device__ __forceinline__ void globals() { to_global(a, b, c, c2, out_scale, norm_partial); }
 };
 
 // The power of two s that puts a bound on |x| just below 2^14 (s * bound in [2^13, 2^14)):
@@ -169,9 +171,14 @@ struct X2ScaleArgs {
   const float *stat_l, *stat_r;               // matrix_stats_kernel of Lbar, Rbar
   float c1;
   float *s_g, *t_scale, *inv_ts;              // [batch] s_G, s_T / (s_L s_G), 1 / (s_T s_R)
+  int32_t blocks;
+  __device__ __forceinline__ void globals() { to_global(gmax_partial, stat_l, stat_r, s_g, t_scale, inv_ts); }
 };
-__global__ __launch_bounds__(64) void x2_scales_kernel(const X2ScaleArgs g) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+__global__ __launch_bounds__(64) void x2_scales_kernel(const Group<X2ScaleArgs> grp) {
+  int b;
+  const X2ScaleArgs g = group_pick(grp, b);
+  if (b >= g.blocks) return;
+  const int lane = threadIdx.x;
   float gm = 0.f;
   for (int i = lane; i < g.parts; i += 64) gm = fmaxf(gm, g.gmax_partial[(int64_t)b * g.parts + i]);
 #pragma unroll
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(64) void x2_scales_kernel(const X2ScaleArgs g) {
 // TM x 256 workgroup tile of wavefront tiles WM x 128.  NB: planes of B: 1 (the scaled gradient) or 2 fp16 ones
 // against two of A, or three bf16 planes of both.
 template <int TM, int WM, int NB, int EPI>
-__global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const GemmX2Args g) {
+__global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const Group<GemmX2Args> grp) {
   static_assert((TM == 128 && WM == 64) || (TM == 256 && (WM == 64 || WM == 128)), "wavefront tiles of 64 or 128 rows");
   static_assert(NB == 1 || NB == 2 || (NB == 3 && TM == 128), "planes of B");
   constexpr int NA = NB == 3 ? 3 : 2;
@@ -240,9 +247,11 @@ __global__ __launch_bounds__(TM / WM * 128, 1) void gemm_f16x2_kernel(const Gemm
   constexpr int PW = AL * NA + BL * NB;        // loads per wavefront per slab
   __shared__ __align__(128) unsigned char smem[NST * STAGE];   // the k-step addresses below differ by an XOR
   __shared__ float red[NW];
+  int wg;
+  const GemmX2Args g = group_pick(grp, wg);
   const int tiles = g.tiles_m * g.tiles_n;
   const int total = tiles * g.batch;
-  const int logical = xcd_remap(blockIdx.x, total);
+  const int logical = xcd_remap(wg, total);
   if (logical >= total) return;
   const int b = logical / tiles;
   const int tile = logical - b * tiles;

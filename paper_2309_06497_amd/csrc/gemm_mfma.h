@@ -17,6 +17,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "group.h"
 
 namespace shampoo {
 
@@ -73,6 +74,7 @@ struct GemmArgs {
   int32_t batch;
   int32_t ksplit, krange;       // EPI_SYRK, ksplit > 1: batch entry b is the range b % ksplit, of krange values of k, of operand b / ksplit;
   double *c64;                  // its plain sum goes here, in float64 like c (ACC64 kernels)
+  __device__ __forceinline__ void globals() { to_global(a.base, b.base, c, desc, ptr_table, kscale, skip, norm_partial, c64); }
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
@@ -199,7 +201,7 @@ __device__ __forceinline__ const T *operand_ptr(const Operand &o, const BlockDes
   if (o.from_table) {
     const BlockDesc d = desc[b];
     ld = d.ld;
-    return reinterpret_cast<const T *>(table[d.param]) + d.offset;
+    return global_ptr<const T>(table[d.param]) + d.offset;
   }
   ld = o.ld;
   return reinterpret_cast<const T *>(o.base) + (int64_t)b * o.batch_stride;
@@ -212,13 +214,15 @@ __device__ __forceinline__ const T *operand_ptr(const Operand &o, const BlockDes
 // whose condition number is the square of G's, and a plain float32 running sum
 // over k would perturb its small eigenvalues by more than the parity budget.
 template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, int ACC64 = 0>
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const GemmArgs g) {
+__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
   __shared__ __align__(16) float As[2][BK][BM + LDS_PAD];
   __shared__ __align__(16) float Bs[2][BK][BN + LDS_PAD];
   __shared__ float red[4];
 
+  int wg;
+  const GemmArgs g = group_pick(grp, wg);
   const int total = g.tiles * g.batch;
-  const int logical = xcd_remap(blockIdx.x, total);
+  const int logical = xcd_remap(wg, total);
   if (logical >= total) return;
   const int b = logical / g.tiles;
   const int tile = logical - b * g.tiles;

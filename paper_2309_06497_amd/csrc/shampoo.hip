@@ -24,6 +24,7 @@
 #include "gemm_f16x2.h"
 #include "gemm_mfma.h"
 #include "gram_split.h"
+#include "group.h"
 #include "newton_root.h"
 #include "root_band.h"
 #include "root_tridiag.h"
@@ -93,6 +94,8 @@ struct Bucket {
   // plane_chunk blocks at a time: cols, the transpose, and behind it rows, the block as it lies, or T = Lbar G
   bool three = false, split_factor = false;
   int32_t plane_chunk = 0;
+  size_t off_t = 0, off_t2 = 0;   // this bucket's part of the scratch arrays T and T2
+  int32_t set = 0;                // buckets of a set are worked on together (their parts do not overlap)
   EwGeom geom;
   int32_t tiles_m, tiles_n;
   bool bf16_mfma;   // shapes, offsets and leading dimensions allow the bf16 matrix-core factor update
@@ -125,6 +128,7 @@ struct Plan {
   int64_t n_prep_rest = 0;              // of them of parameters that are not made of small blocks only
   std::vector<PShape> pshape;           // per parameter
   int64_t total_elems = 0;
+  int n_sets = 0;                       // of buckets (layout)
 };
 
 // Merging of small dimensions (Sec. 4.2.1) and the resulting kind of parameter.  Returns
@@ -477,15 +481,42 @@ EigLayout eig_layout(int n, int batch, bool band, size_t budget = EIG_CHUNK_BYTE
   return e;
 }
 
+// One launch of a kernel for the buckets added to it (group.h), or several where they are more than an argument table
+// holds.  Nothing is launched before flush: what the kernel reads may be written by a launch that is still to come.
+template <typename Args> struct Batch {
+  using Kernel = void (*)(const Group<Args>);
+  struct Entry { Args args; int64_t workgroups; };
+  Kernel kernel; int threads; hipStream_t s;
+  std::vector<Entry> entries;
+  Batch(Kernel k, int threads_, hipStream_t s_) : kernel(k), threads(threads_), s(s_) {}
+  int add(const Args &a, int64_t workgroups) {
+    if (workgroups > ((int64_t)1 << 30) - NUM_XCD) return SHAMPOO_ERR_UNSUPPORTED;
+    if (workgroups > 0) entries.push_back(Entry{a, (workgroups + NUM_XCD - 1) / NUM_XCD * NUM_XCD});
+    return SHAMPOO_OK;
+  }
+  int flush() {
+    Group<Args> g;
+    for (size_t at = 0; at < entries.size();) {
+      int64_t total = 0;
+      g.count = 0;
+      while (at < entries.size() && g.count < group_max<Args>() && total + entries[at].workgroups <= (int64_t)1 << 30) {
+        g.a[g.count] = entries[at].args;
+        g.first[g.count++] = (int32_t)total;
+        total += entries[at++].workgroups;
+      }
+      hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(threads), 0, s, g);
+      HIP_TRY(hipGetLastError());
+    }
+    entries.clear();
+    return SHAMPOO_OK;
+  }
+};
+
 template <int AO, int BO, typename TA, typename TB, int EPI, bool KS, int ACC64 = 0>
-int launch_gemm(GemmArgs &g, hipStream_t s) {
-  const int64_t total = (int64_t)g.tiles * g.batch;
-  if (total <= 0) return SHAMPOO_OK;
-  if (total > (int64_t)1 << 30) return SHAMPOO_ERR_UNSUPPORTED;
-  const int per = (int)((total + NUM_XCD - 1) / NUM_XCD);
-  hipLaunchKernelGGL((gemm_mfma_kernel<AO, BO, TA, TB, EPI, KS, ACC64>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, g);
-  HIP_TRY(hipGetLastError());
-  return SHAMPOO_OK;
+int launch_gemm(const GemmArgs &g, hipStream_t s) {
+  Batch<GemmArgs> one(gemm_mfma_kernel<AO, BO, TA, TB, EPI, KS, ACC64>, GEMM_THREADS, s);
+  if (const int rc = one.add(g, (int64_t)g.tiles * g.batch)) return rc;
+  return one.flush();
 }
 
 int launch_fill(float *p, float v, int64_t n, hipStream_t s) {
@@ -1084,6 +1115,9 @@ namespace {
 // Planes of float32 gradients live only as long as the products that read them: those of 170 blocks of 1024 x 1024
 // at a time (both ways round, or the transpose and T, 12 bytes per element), which is 24 tiles per CU of a factor update.
 constexpr size_t PLANE_BYTES = (size_t)2 << 30;
+// Scratch of the buckets that are worked on together: as much as the planes of one of them may take, so that the workspace
+// of a set of any size grows by no more than this.
+constexpr size_t SET_BYTES = (size_t)2 << 30;
 
 size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   size_t off = 0;
@@ -1097,7 +1131,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   const size_t offG1tab = take((size_t)c->n_params * sizeof(void *));
   const size_t offGftab = take((size_t)c->n_params * sizeof(void *));
   const size_t offPrep = (use_l2 || use_b1) ? take(std::max<size_t>(1, p.prep_chunks.size()) * sizeof(DiagChunk)) : 0;
-  size_t t_bytes = 0, t2_elems = 0, eig_bytes = 0, max_count = 1;
+  size_t eig_bytes = 0, max_count = 1;
+  std::vector<size_t> t_need;
   std::vector<EigLayout> eL, eR, eM[2];
   for (auto &b : p.buckets) {
     const size_t B = b.count, m = b.m, n = b.n;
@@ -1111,7 +1146,6 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
         b.off_midinv[k] = take(B * (size_t)b.td[k + 1] * b.td[k + 1] * 4);
       }
       b.off_desc3 = take(B * (size_t)b.split3 * sizeof(BlockDesc));
-      t2_elems = std::max(t2_elems, B * m * n);
     }
     b.off_P = take(B * m * n * 4);
     // the preconditioning products run on the fp16 matrix cores from operands kept split in two
@@ -1142,8 +1176,16 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
     b.split_factor = b.three && !use_b1;   // the directions' gradient feeds the factors too
-    t_bytes = std::max(t_bytes, B * m * n * (b.t3 ? 8 : 4));   // float32, two fp16 planes, or float64 sums (split_gram)
-    if (b.three) t_bytes = std::max(t_bytes, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
+    // float32 or two fp16 planes; tensor blocks: float64 sums of the ranges of k of two dimensions (split_gram), and float32
+    // ones of the last
+    size_t need = B * m * n * 4;
+    if (b.t3) need = B * m * n * 16 + (b.modes >= 3 ? B * b.split3 * b.dlast() * b.dlast() * 4 : 0);
+    if (b.three) need = std::max(need, std::min(B, std::max<size_t>(1, PLANE_BYTES / (12 * m * n))) * 12 * m * n);
+    if (b.three) {                       // even shares
+      const int64_t most = std::min<int64_t>(b.count, (int64_t)(need / (12 * m * n))), passes = (b.count + most - 1) / most;
+      b.plane_chunk = (int32_t)((b.count + passes - 1) / passes);
+    }
+    t_need.push_back(align_up(need));
     if (c->grad_dtype == SHAMPOO_GRAD_BF16 && b.bf16_mfma && !use_l2) b.off_Gt = take(B * m * n * 2);
     // a diagonalised side needs no eigensolver workspace (stand-in layout of a 1 x 1 problem)
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
@@ -1163,13 +1205,24 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
                                              std::max(eM[0].back().bytes, eM[1].back().bytes)));
     max_count = std::max(max_count, (size_t)b.count);
   }
-  const size_t offT = take(t_bytes);
-  for (auto &b : p.buckets) {            // even shares
-    if (!b.three) continue;
-    const int64_t most = std::min<int64_t>(b.count, (int64_t)(t_bytes / ((size_t)12 * b.m * b.n))), passes = (b.count + most - 1) / most;
-    b.plane_chunk = (int32_t)((b.count + passes - 1) / passes);
+  // Sets of buckets whose scratch fits side by side into what the largest bucket needs, or SET_BYTES
+  size_t t_bytes = 0, t2_bytes = 0;
+  {
+    const size_t room = std::max(SET_BYTES, t_need.empty() ? 0 : *std::max_element(t_need.begin(), t_need.end()));
+    size_t at = 0, at2 = 0;
+    int set = 0;
+    for (size_t i = 0; i < p.buckets.size(); ++i) {
+      Bucket &b = p.buckets[i];
+      if (at + t_need[i] > room) { ++set; at = 0; at2 = 0; }
+      b.set = set; b.off_t = at; b.off_t2 = at2;
+      at += t_need[i];
+      if (b.t3) at2 += align_up((size_t)b.count * b.m * b.n * 4);
+      t_bytes = std::max(t_bytes, at); t2_bytes = std::max(t2_bytes, at2);
+    }
+    p.n_sets = p.buckets.empty() ? 0 : set + 1;
   }
-  const size_t offT2 = t2_elems ? take(t2_elems * 4) : 0;
+  const size_t offT = take(t_bytes);
+  const size_t offT2 = t2_bytes ? take(t2_bytes) : 0;
   std::vector<size_t> offGb(c->n_params, 0), offWb(c->n_params, 0);
   bool has_tensor = false;
   for (int i = 0; i < c->n_params; ++i) {
@@ -1335,7 +1388,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   unsigned char *ws = o->ws;
   float *A = reinterpret_cast<float *>(ws + o->off_A);
   float *M = c.momentum > 0.f ? reinterpret_cast<float *>(ws + o->off_M) : nullptr;
-  float *T = reinterpret_cast<float *>(ws + o->off_T);
   float *G1 = o->use_l2 ? reinterpret_cast<float *>(ws + o->off_G1) : nullptr;
   float *Gf = o->use_b1 ? reinterpret_cast<float *>(ws + o->off_Gf) : nullptr;
   void *const *wtab = reinterpret_cast<void *const *>(ws + o->off_wtab);
@@ -1441,228 +1493,274 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     HIP_TRY(hipGetLastError());
     for (size_t i = 0; i < p.buckets.size(); ++i) if (p.buckets[i].small()) o->upper_stale[i] = UPPER_HALF_STALE;
   }
-  // scales of the fp16 operands of a bucket's preconditioning products (and of R's update)
-  auto launch_x2_scales = [&](const Bucket &b) {
-    X2ScaleArgs xs;
-    xs.gmax_partial = reinterpret_cast<const float *>(ws + b.off_gmaxp); xs.parts = b.geom.chunks;
-    xs.stat_l = reinterpret_cast<const float *>(ws + b.off_stat_l); xs.stat_r = reinterpret_cast<const float *>(ws + b.off_stat_r);
-    xs.c1 = c1;
-    xs.s_g = reinterpret_cast<float *>(ws + b.off_s_g);
-    xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
-    hipLaunchKernelGGL(x2_scales_kernel, dim3(b.count), dim3(64), 0, s, xs);
-  };
-  // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through T in float64, as
+  // ---- stage by stage.  Buckets are independent of one another, so that each stage is one launch for all of them
+  // (group.h); those of a set have their own parts of the scratch T, and sets follow one another.
+  auto bucket_t = [&](const Bucket &b) { return reinterpret_cast<float *>(ws + o->off_T + b.off_t); };
+  // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through `sums` in float64, as
   // the one sum is held: it has room for m n of them per block of the bucket.
-  auto split_gram = [&](const Bucket &b, GemmArgs &g) {
+  auto split_gram = [&](const Bucket &b, GemmArgs &g, double *sums) {
     const GramSplit sp = gram_split(g.K, (int64_t)b.m * b.n / ((int64_t)g.M * g.M), (int64_t)g.tiles * g.batch, BK);
     if (sp.ranges <= 1) return 1;
     g.ksplit = sp.ranges; g.krange = sp.range;
-    g.c64 = reinterpret_cast<double *>(T); g.batch *= g.ksplit;
+    g.c64 = sums; g.batch *= g.ksplit;
     return (int)g.ksplit;
   };
-  auto reduce_gram = [&](size_t off_factor, int d, int splits, int count, bool f64) {
+  auto reduce_gram = [&](Batch<GramReduceArgs> &to, const void *partial, size_t off_factor, int d, int splits, int count) {
     GramReduceArgs gr;
-    gr.partial = T; gr.factor = reinterpret_cast<float *>(ws + off_factor); gr.d = d; gr.splits = splits;
+    gr.partial = partial; gr.factor = reinterpret_cast<float *>(ws + off_factor); gr.d = d; gr.splits = splits; gr.blocks = count;
     gr.alpha = alpha; gr.beta = beta;
-    const dim3 grid((unsigned)(((int64_t)d * d + 255) / 256), count);
-    if (f64) hipLaunchKernelGGL(gram_reduce_kernel<double>, grid, dim3(256), 0, s, gr);
-    else hipLaunchKernelGGL(gram_reduce_kernel<float>, grid, dim3(256), 0, s, gr);
+    return to.add(gr, (((int64_t)d * d + 255) / 256) * count);
   };
-  // the planes of blocks [b0, b0 + cnt) of a bucket's float32 gradients, after launch_x2_scales
-  auto launch_block_planes = [&](const Bucket &b, int b0, int cnt, bool rows) {
+  // scales of the fp16 operands of a bucket's preconditioning products (and of R's update)
+  auto add_x2_scales = [&](Batch<X2ScaleArgs> &to, const Bucket &b) {
+    X2ScaleArgs xs;
+    xs.gmax_partial = reinterpret_cast<const float *>(ws + b.off_gmaxp); xs.parts = b.geom.chunks;
+    xs.stat_l = reinterpret_cast<const float *>(ws + b.off_stat_l); xs.stat_r = reinterpret_cast<const float *>(ws + b.off_stat_r);
+    xs.c1 = c1; xs.blocks = b.count;
+    xs.s_g = reinterpret_cast<float *>(ws + b.off_s_g);
+    xs.t_scale = reinterpret_cast<float *>(ws + b.off_t_scale); xs.inv_ts = reinterpret_cast<float *>(ws + b.off_inv_ts);
+    return to.add(xs, b.count);
+  };
+  // the planes of blocks [b0, b0 + cnt) of a bucket's float32 gradients, after add_x2_scales
+  auto planes_of = [&](const Bucket &b, int b0, int cnt, bool rows) {
     BlockPlanesArgs bp;
     bp.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc) + b0; bp.g_table = gd_tab;
-    bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g) + b0; bp.m = b.m; bp.n = b.n;
+    bp.scale = reinterpret_cast<const float *>(ws + b.off_s_g) + b0; bp.m = b.m; bp.n = b.n; bp.blocks = cnt;
     bp.plane_stride = (int64_t)cnt * b.m * b.n;
-    bp.cols = reinterpret_cast<uint16_t *>(T); bp.rows = rows ? bp.cols + 3 * bp.plane_stride : nullptr;
-    hipLaunchKernelGGL(block_planes_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, cnt), dim3(256), 0, s, bp);
+    bp.cols = reinterpret_cast<uint16_t *>(bucket_t(b)); bp.rows = rows ? bp.cols + 3 * bp.plane_stride : nullptr;
     return bp;
   };
-  const Bucket *cols_in_T = nullptr;     // whose planes of the transpose are all in T, from the factor update on
-  for (auto &b : p.buckets) {
-    if (fused(b)) continue;
-    cols_in_T = nullptr;
-    const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
+  auto planes_wgs = [](const Bucket &b, int cnt) { return (int64_t)((b.n + 63) / 64) * ((b.m + 63) / 64) * cnt; };
+  auto syrk_wgs = [](const SyrkBf16Args &g) { return (int64_t)g.tiles * g.batch; };
+  auto tensor_chunks = [](const Bucket &b) { return (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, ((int64_t)b.m * b.n + 2047) / 2048)); };
+  // how a bucket's factors are updated: fp16 / bf16 matrix cores, three bf16 planes, float32 matrix cores
+  enum { F_BF16, F_SPLIT, F_F32 };
+  auto factor_path = [&](const Bucket &b) {
+    if (sizeof(GS) == 2 && b.bf16_mfma && o->ptrs_aligned16) return F_BF16;
+    if (sizeof(GS) == 4 && b.split_factor && use_shampoo && o->ptrs_aligned16) return F_SPLIT;
+    return F_F32;
+  };
+  auto fill_ew = [&](EwArgs &e, const Bucket &b) {
+    e.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
+    e.m = b.m; e.n = b.n; e.blocks = b.count; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
+    e.sgd_graft = sgd; e.gd_scale = c1; e.a_decay = a_decay; e.a_gain = a_gain; e.a_bc = a_bc;
+  };
+  // the buckets of a set that go stage by stage
+  auto members = [&](int set) {
+    std::vector<Bucket *> v;
+    for (auto &b : p.buckets) if (b.set == set && !fused(b)) v.push_back(&b);
+    return v;
+  };
+  for (int set = 0; set < p.n_sets; ++set) {
+    const std::vector<Bucket *> todo = members(set);
+    if (todo.empty()) continue;
     // grafting state and norm first: the same pass finds max |G| of every block, which scales
     // the fp16 planes of this step's first product
     {
       StageTimer t(o, SHAMPOO_STAGE_GRAFT, s);
-      EwArgs e{};
-      e.desc = desc; e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
-      e.sg_partial = reinterpret_cast<float *>(ws + b.off_sgp);
-      e.m = b.m; e.n = b.n; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
-      e.sgd_graft = sgd; e.same_src = (gs_tab == gd_tab) ? 1 : 0; e.gd_scale = c1;
-      e.a_decay = a_decay; e.a_gain = a_gain; e.a_bc = a_bc;
-      if (b.planes) e.gmax_partial = reinterpret_cast<float *>(ws + b.off_gmaxp);
-      hipLaunchKernelGGL((graft_kernel<GS, GD>), dim3((unsigned)b.geom.chunks * b.count), dim3(EW_THREADS), 0, s, e);
-      HIP_TRY(hipGetLastError());
+      Batch<EwArgs> graft(graft_kernel<GS, GD>, EW_THREADS, s);
+      for (Bucket *b : todo) {
+        EwArgs e{};
+        fill_ew(e, *b);
+        e.sg_partial = reinterpret_cast<float *>(ws + b->off_sgp);
+        e.same_src = (gs_tab == gd_tab) ? 1 : 0;
+        if (b->planes) e.gmax_partial = reinterpret_cast<float *>(ws + b->off_gmaxp);
+        if ((rc = graft.add(e, (int64_t)b->geom.chunks * b->count))) return rc;
+      }
+      if ((rc = graft.flush())) return rc;
     }
-    if (sizeof(GS) == 2 && b.bf16_mfma && o->ptrs_aligned16) {
-      StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
-      // fp16 operands of this step's preconditioning products (and of R's update): their scales first
-      const bool x2 = sizeof(GD) == 2 && b.planes;
-      if (x2) launch_x2_scales(b);
-      uint16_t *Gt = reinterpret_cast<uint16_t *>(ws + b.off_Gt);
-      TransposeArgs ta;
-      ta.desc = desc; ta.g_table = gs_tab; ta.out = Gt; ta.m = b.m; ta.n = b.n;
-      ta.scale = x2 ? reinterpret_cast<const float *>(ws + b.off_s_g) : nullptr;
-      hipLaunchKernelGGL(transpose_bf16_kernel, dim3((b.n + 63) / 64, (b.m + 63) / 64, b.count), dim3(256), 0, s, ta);
-      SyrkBf16Args sa{};
-      sa.desc = desc; sa.ptr_table = gs_tab; sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
-      // the kernel reads and writes the tiles on and below the diagonal, those on it whole
-      if (o->upper_stale[&b - p.buckets.data()] == UPPER_HALF_STALE && (rc = complete_factors(o, &b - p.buckets.data(), s))) return rc;
-      o->upper_stale[&b - p.buckets.data()] = UPPER_TILES_STALE;
-      // L <- beta L + alpha G G^T
-      sa.a.from_table = 1;
-      sa.c = reinterpret_cast<float *>(ws + b.off_L); sa.c_batch_stride = (int64_t)b.m * b.m; sa.ldc = b.m;
-      sa.M = b.m; sa.K = b.n; sa.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
-      {
-        const int64_t total = (int64_t)sa.tiles * sa.batch;
-        const int per = (int)((total + NUM_XCD - 1) / NUM_XCD);
-        if (young_factor(step, b.n, b.m))
-          hipLaunchKernelGGL((syrk_bf16_kernel<false, true>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
-        else
-          hipLaunchKernelGGL((syrk_bf16_kernel<false, false>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
+    StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
+    // scales, then transposes and planes
+    {
+      Batch<X2ScaleArgs> scales(x2_scales_kernel, 64, s);
+      Batch<TransposeArgs> transposes(transpose_bf16_kernel, 256, s);
+      Batch<BlockPlanesArgs> planes(block_planes_kernel, 256, s);
+      for (Bucket *b : todo) {
+        const int path = factor_path(*b);
+        if ((path == F_BF16 && sizeof(GD) == 2 && b->planes) || path == F_SPLIT) if ((rc = add_x2_scales(scales, *b))) return rc;
       }
-      // R <- beta R + alpha (G^T)(G^T)^T
-      sa.a.from_table = 0; sa.a.base = Gt; sa.a.batch_stride = (int64_t)b.m * b.n; sa.a.ld = b.m;
-      sa.c = reinterpret_cast<float *>(ws + b.off_R); sa.c_batch_stride = (int64_t)b.n * b.n; sa.ldc = b.n;
-      sa.M = b.n; sa.K = b.m; sa.tiles = b.tiles_n * (b.tiles_n + 1) / 2;
-      {
-        const int64_t total = (int64_t)sa.tiles * sa.batch;
-        const int per = (int)((total + NUM_XCD - 1) / NUM_XCD);
-        const bool young = young_factor(step, b.m, b.n);
-        if (x2) {
-          sa.x_scale = reinterpret_cast<const float *>(ws + b.off_s_g);
-          if (young) hipLaunchKernelGGL((syrk_bf16_kernel<true, true>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
-          else hipLaunchKernelGGL((syrk_bf16_kernel<true, false>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
-        } else {
-          if (young) hipLaunchKernelGGL((syrk_bf16_kernel<false, true>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
-          else hipLaunchKernelGGL((syrk_bf16_kernel<false, false>), dim3(per * NUM_XCD), dim3(GEMM_THREADS), 0, s, sa);
+      if ((rc = scales.flush())) return rc;
+      for (Bucket *b : todo) {
+        const int path = factor_path(*b);
+        if (path == F_BF16) {
+          TransposeArgs ta;
+          ta.desc = reinterpret_cast<const BlockDesc *>(ws + b->off_desc); ta.g_table = gs_tab; ta.out = reinterpret_cast<uint16_t *>(ws + b->off_Gt);
+          ta.m = b->m; ta.n = b->n; ta.blocks = b->count;
+          ta.scale = sizeof(GD) == 2 && b->planes ? reinterpret_cast<const float *>(ws + b->off_s_g) : nullptr;
+          if ((rc = transposes.add(ta, planes_wgs(*b, b->count)))) return rc;
+        } else if (path == F_SPLIT && b->plane_chunk == b->count) {
+          if ((rc = planes.add(planes_of(*b, 0, b->count, true), planes_wgs(*b, b->count)))) return rc;
         }
       }
-      HIP_TRY(hipGetLastError());
-    } else if (sizeof(GS) == 4 && b.split_factor && use_shampoo && o->ptrs_aligned16) {
-      // float32 gradients: both factors from three bf16 planes
-      StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
-      launch_x2_scales(b);
-      o->upper_stale[&b - p.buckets.data()] = UPPER_TILES_STALE;
-      if (b.plane_chunk == b.count) cols_in_T = &b;
-      for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
-        const int cnt = std::min(b.plane_chunk, b.count - b0);
-        const BlockPlanesArgs bp = launch_block_planes(b, b0, cnt, true);
-        SyrkBf16Args sa{};
-        sa.alpha = alpha; sa.beta = beta; sa.batch = cnt;
-        sa.plane = bp.plane_stride; sa.x_scale = bp.scale;
-        for (int side = 0; side < 2; ++side) {
-          const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
-          sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;
-          sa.a.ld = sa.K = side == 0 ? b.n : b.m;
-          sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = sa.M = dim;
-          sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)) + b0 * sa.c_batch_stride;
-          sa.tiles = tiles * (tiles + 1) / 2;
-          const int64_t per = ((int64_t)sa.tiles * sa.batch + NUM_XCD - 1) / NUM_XCD;
-          hipLaunchKernelGGL((syrk_bf16_kernel<false, true, true>), dim3((unsigned)(per * NUM_XCD)), dim3(GEMM_THREADS), 0, s, sa);
-        }
-      }
-      HIP_TRY(hipGetLastError());
-    } else {
-      StageTimer t(o, SHAMPOO_STAGE_FACTOR, s);
-      o->upper_stale[&b - p.buckets.data()] = UPPER_FRESH;   // these kernels read the lower triangle and write both
-      GemmArgs g{};
-      g.a.from_table = 1; g.b.from_table = 1;
-      g.desc = desc; g.ptr_table = gs_tab;
-      g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
-      DiagFactorArgs df{};
-      df.desc = desc; df.g_table = gs_tab; df.a = beta; df.b = alpha; df.m = b.m; df.n = b.n;
-      if (b.diagL) {
-        // l_i <- beta l_i + alpha sum_j G_ij^2 (Sec. 4.2.3)
-        df.vec = reinterpret_cast<float *>(ws + b.off_L);
-        hipLaunchKernelGGL(diag_row_kernel<GS>, dim3((b.m + 3) / 4, b.count), dim3(256), 0, s, df);
-        HIP_TRY(hipGetLastError());
-      } else {
-        // L <- beta L + alpha G G^T
-        g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
-        g.M = b.m; g.N = b.m; g.K = b.n;
-        g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
-        const int sp = b.t3 ? split_gram(b, g) : 1;
-        rc = launch_gemm<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
-        if (rc) return rc;
-        if (sp > 1) {
-          reduce_gram(b.off_L, b.m, sp, b.count, true);
-          g.ksplit = 0; g.batch = b.count;
-          HIP_TRY(hipGetLastError());
-        }
-      }
-      if (b.t3) {
-        // Above: L_1 <- beta L_1 + alpha G_(1) G_(1)^T, the block being d1 x (d2 d3 d4).  The other
-        // dimensions exist only for a tensor of order three or four.
-        if (b.modes >= 3) {
-          // Last dimension: the block as (N / d_last) x d_last, read "rows along k".  Its rows
-          // are cut into split3 ranges, each a batch entry that leaves its Gram matrix in
-          // scratch; gram_reduce_kernel adds them up in float64 and applies the moving average.
-          float *T2 = reinterpret_cast<float *>(ws + o->off_T2);
-          const int dl = b.dlast(), inner = b.n / dl;
-          if (dl <= 16) {
-            GramNarrowArgs gn;
-            gn.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3); gn.table = gs_tab; gn.partial = T;
-            gn.d = dl; gn.rows = (b.m / b.split3) * inner; gn.entries = b.count * b.split3;
-            hipLaunchKernelGGL(gram_narrow_kernel<GS>, dim3((unsigned)(gn.entries + 3) / 4), dim3(256), 0, s, gn);
-          } else {
-            g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3);
-            g.c = T; g.c_batch_stride = (int64_t)dl * dl; g.ldc = dl;
-            g.M = dl; g.N = dl; g.K = (b.m / b.split3) * inner;
-            g.alpha = 1.f; g.beta = 0.f; g.alpha_d = 1.0; g.beta_d = 0.0; g.batch = b.count * b.split3;
-            g.tiles_m = g.tiles_n = (dl + BM - 1) / BM; g.tiles = g.tiles_m * (g.tiles_m + 1) / 2;
-            rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
-            if (rc) return rc;
-          }
-          reduce_gram(b.off_R, dl, b.split3, b.count, false);
-          HIP_TRY(hipGetLastError());
-          // Middle dimensions k: the block as pre x d_k x post with its first two indices swapped,
-          // d_k x (pre post)
-          int pre = b.m;
-          for (int k = 1; k + 1 < b.modes; ++k) {
-            const int dk = b.td[k], post = b.n / (pre / b.m * dk);
-            PermuteArgs pm{};
-            pm.desc = desc; pm.table = gs_tab; pm.dst = T2; pm.d1 = pre; pm.d2 = dk; pm.d3 = post;
-            const unsigned pchunks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, ((int64_t)b.m * b.n + 2047) / 2048));
-            hipLaunchKernelGGL(permute_12_kernel<GS>, dim3(pchunks, b.count), dim3(256), 0, s, pm);
-            HIP_TRY(hipGetLastError());
-            GemmArgs h{};
-            h.a.base = T2; h.a.batch_stride = (int64_t)b.m * b.n; h.a.ld = pre * post;
-            h.b = h.a;
-            h.alpha = (float)alpha; h.beta = (float)beta; h.alpha_d = alpha; h.beta_d = beta; h.batch = b.count;
-            h.c = reinterpret_cast<float *>(ws + b.off_mid[k - 1]); h.c_batch_stride = (int64_t)dk * dk; h.ldc = dk;
-            h.M = dk; h.N = dk; h.K = pre * post;
-            h.tiles_m = h.tiles_n = (dk + BM - 1) / BM; h.tiles = h.tiles_m * (h.tiles_m + 1) / 2;
-            const int sp = split_gram(b, h);
-            rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>(h, s);
-            if (rc) return rc;
-            if (sp > 1) {
-              reduce_gram(b.off_mid[k - 1], dk, sp, b.count, true);
-              HIP_TRY(hipGetLastError());
+      if ((rc = transposes.flush()) || (rc = planes.flush())) return rc;
+    }
+    // both factors of matrix blocks
+    {
+      Batch<SyrkBf16Args> plain(syrk_bf16_kernel<false, false>, GEMM_THREADS, s), plain64(syrk_bf16_kernel<false, true>, GEMM_THREADS, s),
+          half(syrk_bf16_kernel<true, false>, GEMM_THREADS, s), half64(syrk_bf16_kernel<true, true>, GEMM_THREADS, s),
+          split(syrk_bf16_kernel<false, true, true>, GEMM_THREADS, s);
+      Batch<GemmArgs> left(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
+          right(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s);
+      for (Bucket *bp : todo) {
+        Bucket &b = *bp;
+        const size_t index = &b - p.buckets.data();
+        const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
+        const int path = factor_path(b);
+        if (path == F_BF16) {
+          // the kernel reads and writes the tiles on and below the diagonal, those on it whole
+          if (o->upper_stale[index] == UPPER_HALF_STALE && (rc = complete_factors(o, index, s))) return rc;
+          o->upper_stale[index] = UPPER_TILES_STALE;
+          const bool x2 = sizeof(GD) == 2 && b.planes;
+          SyrkBf16Args sa{};
+          sa.desc = desc; sa.ptr_table = gs_tab; sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
+          // L <- beta L + alpha G G^T
+          sa.a.from_table = 1;
+          sa.c = reinterpret_cast<float *>(ws + b.off_L); sa.c_batch_stride = (int64_t)b.m * b.m; sa.ldc = b.m;
+          sa.M = b.m; sa.K = b.n; sa.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
+          if ((rc = (young_factor(step, b.n, b.m) ? plain64 : plain).add(sa, syrk_wgs(sa)))) return rc;
+          // R <- beta R + alpha (G^T)(G^T)^T
+          sa.a.from_table = 0; sa.a.base = ws + b.off_Gt; sa.a.batch_stride = (int64_t)b.m * b.n; sa.a.ld = b.m;
+          sa.c = reinterpret_cast<float *>(ws + b.off_R); sa.c_batch_stride = (int64_t)b.n * b.n; sa.ldc = b.n;
+          sa.M = b.n; sa.K = b.m; sa.tiles = b.tiles_n * (b.tiles_n + 1) / 2;
+          const bool young = young_factor(step, b.m, b.n);
+          if (x2) sa.x_scale = reinterpret_cast<const float *>(ws + b.off_s_g);
+          if ((rc = (x2 ? (young ? half64 : half) : (young ? plain64 : plain)).add(sa, syrk_wgs(sa)))) return rc;
+        } else if (path == F_SPLIT) {
+          // float32 gradients: both factors from three bf16 planes, of as many blocks at a time as T has room for
+          o->upper_stale[index] = UPPER_TILES_STALE;
+          for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
+            const int cnt = std::min(b.plane_chunk, b.count - b0);
+            const BlockPlanesArgs bp = planes_of(b, b0, cnt, true);
+            if (b.plane_chunk < b.count) {
+              Batch<BlockPlanesArgs> planes(block_planes_kernel, 256, s);
+              if ((rc = planes.add(bp, planes_wgs(b, cnt))) || (rc = planes.flush())) return rc;
             }
-            pre *= dk;
+            SyrkBf16Args sa{};
+            sa.alpha = alpha; sa.beta = beta; sa.batch = cnt;
+            sa.plane = bp.plane_stride; sa.x_scale = bp.scale;
+            for (int side = 0; side < 2; ++side) {
+              const int dim = side == 0 ? b.m : b.n, tiles = side == 0 ? b.tiles_m : b.tiles_n;
+              sa.a.base = side == 0 ? bp.rows : bp.cols; sa.a.batch_stride = (int64_t)b.m * b.n;
+              sa.a.ld = sa.K = side == 0 ? b.n : b.m;
+              sa.c_batch_stride = (int64_t)dim * dim; sa.ldc = sa.M = dim;
+              sa.c = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R)) + b0 * sa.c_batch_stride;
+              sa.tiles = tiles * (tiles + 1) / 2;
+              if ((rc = split.add(sa, syrk_wgs(sa)))) return rc;
+            }
+            if (b.plane_chunk < b.count && (rc = split.flush())) return rc;
+          }
+        } else if (!b.t3) {
+          o->upper_stale[index] = UPPER_FRESH;   // these kernels read the lower triangle and write both
+          GemmArgs g{};
+          g.a.from_table = 1; g.b.from_table = 1;
+          g.desc = desc; g.ptr_table = gs_tab;
+          g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
+          DiagFactorArgs df{};
+          df.desc = desc; df.g_table = gs_tab; df.a = beta; df.b = alpha; df.m = b.m; df.n = b.n;
+          if (b.diagL) {
+            // l_i <- beta l_i + alpha sum_j G_ij^2 (Sec. 4.2.3)
+            df.vec = reinterpret_cast<float *>(ws + b.off_L);
+            hipLaunchKernelGGL(diag_row_kernel<GS>, dim3((b.m + 3) / 4, b.count), dim3(256), 0, s, df);
+            HIP_TRY(hipGetLastError());
+          } else {
+            // L <- beta L + alpha G G^T
+            g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
+            g.M = b.m; g.N = b.m; g.K = b.n;
+            g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
+            if ((rc = left.add(g, (int64_t)g.tiles * g.batch))) return rc;
+          }
+          if (b.diagR) {
+            // r_j <- beta r_j + alpha sum_i G_ij^2, rows cut into segments whose partial sums go through T
+            df.vec = reinterpret_cast<float *>(ws + b.off_R);
+            df.partial = bucket_t(b); df.segs = b.col_segs; df.rows_per_seg = b.rows_per_seg;
+            hipLaunchKernelGGL(diag_col_partial_kernel<GS>, dim3((b.n + 255) / 256, b.col_segs, b.count), dim3(256), 0, s, df);
+            hipLaunchKernelGGL(diag_col_reduce_kernel, dim3((b.n + 255) / 256, b.count), dim3(256), 0, s, df);
+            HIP_TRY(hipGetLastError());
+          } else {
+            // R <- beta R + alpha G^T G
+            g.c = reinterpret_cast<float *>(ws + b.off_R); g.c_batch_stride = (int64_t)b.n * b.n; g.ldc = b.n;
+            g.M = b.n; g.N = b.n; g.K = b.m;
+            g.tiles_m = g.tiles_n = b.tiles_n; g.tiles = b.tiles_n * (b.tiles_n + 1) / 2;
+            if ((rc = right.add(g, (int64_t)g.tiles * g.batch))) return rc;
           }
         }
-      } else if (b.diagR) {
-        // r_j <- beta r_j + alpha sum_i G_ij^2, rows cut into segments whose partial sums go through T
-        df.vec = reinterpret_cast<float *>(ws + b.off_R);
-        df.partial = T; df.segs = b.col_segs; df.rows_per_seg = b.rows_per_seg;
-        hipLaunchKernelGGL(diag_col_partial_kernel<GS>, dim3((b.n + 255) / 256, b.col_segs, b.count), dim3(256), 0, s, df);
-        hipLaunchKernelGGL(diag_col_reduce_kernel, dim3((b.n + 255) / 256, b.count), dim3(256), 0, s, df);
-        HIP_TRY(hipGetLastError());
-      } else {
-        // R <- beta R + alpha G^T G
-        g.c = reinterpret_cast<float *>(ws + b.off_R); g.c_batch_stride = (int64_t)b.n * b.n; g.ldc = b.n;
-        g.M = b.n; g.N = b.n; g.K = b.m;
-        g.tiles_m = g.tiles_n = b.tiles_n; g.tiles = b.tiles_n * (b.tiles_n + 1) / 2;
-        rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>(g, s);
-        if (rc) return rc;
       }
+      for (Batch<SyrkBf16Args> *x : {&plain, &plain64, &half, &half64, &split}) if ((rc = x->flush())) return rc;
+      if ((rc = left.flush()) || (rc = right.flush())) return rc;
+    }
+    // Factors of tensor blocks.  First dimension: L_1 <- beta L_1 + alpha G_(1) G_(1)^T, the block being d1 x (d2 d3 d4).
+    // Last dimension: the block as (N / d_last) x d_last, read "rows along k"; its rows are cut into split3 ranges, each a
+    // batch entry that leaves its Gram matrix in scratch.  Middle dimensions k: the block as pre x d_k x post with its first
+    // two indices swapped, d_k x (pre post).  gram_reduce_kernel adds the ranges up in float64 and applies the moving average.
+    for (int mid = 0; mid < 2; ++mid) {
+      Batch<PermuteArgs> swaps(permute_12_kernel<GS>, 256, s);
+      Batch<GemmArgs> first(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
+          middle(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
+          last(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s);
+      Batch<GramNarrowArgs> narrow(gram_narrow_kernel<GS>, 256, s);
+      Batch<GramReduceArgs> reduce64(gram_reduce_kernel<double>, 256, s), reduce32(gram_reduce_kernel<float>, 256, s);
+      for (Bucket *bp : todo) {
+        Bucket &b = *bp;
+        if (!b.t3) continue;
+        const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
+        const int64_t mn = (int64_t)b.m * b.n;
+        // parts of the bucket's scratch: sums of the first dimension, of a middle one, of the last one
+        double *sums_l = reinterpret_cast<double *>(bucket_t(b)), *sums_m = sums_l + mn * b.count;
+        float *sums_r = reinterpret_cast<float *>(sums_m + mn * b.count), *swapped = reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2);
+        GemmArgs g{};
+        g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
+        if (mid == 0) {
+          o->upper_stale[&b - p.buckets.data()] = UPPER_FRESH;
+          g.a.from_table = 1; g.b.from_table = 1; g.desc = desc; g.ptr_table = gs_tab;
+          g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
+          g.M = b.m; g.N = b.m; g.K = b.n;
+          g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
+          const int sp = split_gram(b, g, sums_l);
+          if ((rc = first.add(g, (int64_t)g.tiles * g.batch))) return rc;
+          if (sp > 1 && (rc = reduce_gram(reduce64, sums_l, b.off_L, b.m, sp, b.count))) return rc;
+          if (b.modes >= 3) {
+            const int dl = b.dlast(), inner = b.n / dl;
+            if (dl <= 16) {
+              GramNarrowArgs gn;
+              gn.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3); gn.table = gs_tab; gn.partial = sums_r;
+              gn.d = dl; gn.rows = (b.m / b.split3) * inner; gn.entries = b.count * b.split3;
+              if ((rc = narrow.add(gn, (gn.entries + 3) / 4))) return rc;
+            } else {
+              GemmArgs r = g;
+              r.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3); r.ksplit = 0; r.c64 = nullptr;
+              r.c = sums_r; r.c_batch_stride = (int64_t)dl * dl; r.ldc = dl;
+              r.M = dl; r.N = dl; r.K = (b.m / b.split3) * inner;
+              r.alpha = 1.f; r.beta = 0.f; r.alpha_d = 1.0; r.beta_d = 0.0; r.batch = b.count * b.split3;
+              r.tiles_m = r.tiles_n = (dl + BM - 1) / BM; r.tiles = r.tiles_m * (r.tiles_m + 1) / 2;
+              if ((rc = last.add(r, (int64_t)r.tiles * r.batch))) return rc;
+            }
+            if ((rc = reduce_gram(reduce32, sums_r, b.off_R, dl, b.split3, b.count))) return rc;
+          }
+        }
+        if (mid + 2 < b.modes) {
+          const int pre = mid == 0 ? b.m : b.m * b.td[1], dk = b.td[mid + 1], post = (int)(mn / ((int64_t)pre * dk));
+          PermuteArgs pm{};
+          pm.desc = desc; pm.table = gs_tab; pm.dst = swapped; pm.d1 = pre; pm.d2 = dk; pm.d3 = post;
+          pm.chunks = tensor_chunks(b); pm.blocks = b.count;
+          if ((rc = swaps.add(pm, (int64_t)pm.chunks * b.count))) return rc;
+          GemmArgs h{};
+          h.a.base = swapped; h.a.batch_stride = mn; h.a.ld = pre * post;
+          h.b = h.a;
+          h.alpha = (float)alpha; h.beta = (float)beta; h.alpha_d = alpha; h.beta_d = beta; h.batch = b.count;
+          h.c = reinterpret_cast<float *>(ws + b.off_mid[mid]); h.c_batch_stride = (int64_t)dk * dk; h.ldc = dk;
+          h.M = dk; h.N = dk; h.K = pre * post;
+          h.tiles_m = h.tiles_n = (dk + BM - 1) / BM; h.tiles = h.tiles_m * (h.tiles_m + 1) / 2;
+          const int sp = split_gram(b, h, sums_m);
+          if ((rc = middle.add(h, (int64_t)h.tiles * h.batch))) return rc;
+          if (sp > 1 && (rc = reduce_gram(reduce64, sums_m, b.off_mid[mid], dk, sp, b.count))) return rc;
+        }
+      }
+      if ((rc = swaps.flush()) || (rc = first.flush()) || (rc = middle.flush()) || (rc = narrow.flush()) || (rc = last.flush()) ||
+          (rc = reduce64.flush()) || (rc = reduce32.flush()))
+        return rc;
     }
   }
+  const bool cols_in_t = p.n_sets == 1;     // planes of the transposes that the factor update has made are still there
   if (refresh) {
     StageTimer t(o, SHAMPOO_STAGE_ROOT, s);
     // Warm start: from the eigenvectors of the previous refresh, except at the first refresh and
@@ -1745,206 +1843,235 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     o->n_refresh++;
     if ((rc = split_roots(o, s))) return rc;
   }
-  for (auto &b : p.buckets) {
-    const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
-    float *P = reinterpret_cast<float *>(ws + b.off_P);
-    float *scale = reinterpret_cast<float *>(ws + b.off_scale);
-    if (fused(b)) continue;
-    if (cols_in_T != &b) cols_in_T = nullptr;   // this bucket writes T first
-    int ssh_count = b.tiles_m * b.tiles_n;
-    if (use_shampoo && b.t3) {
-      // P = G x_1 Lbar_1 x_2 Lbar_2 ... x_w Lbar_w (Sec. 2.3).  Mode 1 on the block as
-      // d1 x (d2 ... dw); a middle mode k on the block as pre x d_k x post: its first two
-      // indices are swapped, the product is the plain one on d_k x (pre post), and they are
-      // swapped back; the last mode on the block as (N / d_w) x d_w, with the norm epilogue.
-      StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      float *T2 = reinterpret_cast<float *>(ws + o->off_T2);
-      float *ssh = reinterpret_cast<float *>(ws + b.off_sshp);
-      const int64_t mn = (int64_t)b.m * b.n;
-      GemmArgs g{};
-      g.a.base = ws + b.off_Linv; g.a.batch_stride = (int64_t)b.m * b.m; g.a.ld = b.m;
-      g.b.from_table = 1; g.desc = desc; g.ptr_table = gd_tab;
-      g.c_batch_stride = mn; g.ldc = b.n;
-      g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.beta = 0.f;
-      g.tiles_m = b.tiles_m; g.tiles_n = b.tiles_n; g.tiles = b.tiles_m * b.tiles_n; g.batch = b.count;
-      if (b.modes == 1) {
-        g.c = P; g.norm_partial = ssh;
-        rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false>(g, s);
-        if (rc) return rc;
-      } else {
-        float *cur = T, *other = T2;
-        g.c = cur;
-        rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>(g, s);
-        if (rc) return rc;
-        const unsigned pchunks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (mn + 2047) / 2048));
-        int pre = b.m;
-        for (int k = 1; k + 1 < b.modes; ++k) {
-          const int dk = b.td[k], post = (int)(mn / ((int64_t)pre * dk));
-          PermuteArgs pm{};
-          pm.src = cur; pm.dst = other; pm.d1 = pre; pm.d2 = dk; pm.d3 = post;
-          hipLaunchKernelGGL(permute_12_kernel<float>, dim3(pchunks, b.count), dim3(256), 0, s, pm);
-          HIP_TRY(hipGetLastError());
-          GemmArgs h{};
-          h.a.base = ws + b.off_midinv[k - 1]; h.a.batch_stride = (int64_t)dk * dk; h.a.ld = dk;
-          h.b.base = other; h.b.batch_stride = mn; h.b.ld = pre * post;
-          h.c = cur; h.c_batch_stride = mn; h.ldc = pre * post;
-          h.M = dk; h.N = pre * post; h.K = dk; h.alpha = 1.f; h.beta = 0.f;
-          h.tiles_m = (h.M + BM - 1) / BM; h.tiles_n = (h.N + BN - 1) / BN; h.tiles = h.tiles_m * h.tiles_n; h.batch = b.count;
-          rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>(h, s);
-          if (rc) return rc;
-          pm.src = cur; pm.dst = other; pm.d1 = dk; pm.d2 = pre; pm.d3 = post;
-          hipLaunchKernelGGL(permute_12_kernel<float>, dim3(pchunks, b.count), dim3(256), 0, s, pm);
-          HIP_TRY(hipGetLastError());
-          std::swap(cur, other);
-          pre *= dk;
-        }
-        const int dl = b.dlast();
-        GemmArgs q{};
-        q.a.base = cur; q.a.batch_stride = mn; q.a.ld = dl;
-        q.b.base = ws + b.off_Rinv; q.b.batch_stride = (int64_t)dl * dl; q.b.ld = dl;
-        q.c = P; q.c_batch_stride = mn; q.ldc = dl;
-        q.M = (int)(mn / dl); q.N = dl; q.K = dl; q.alpha = 1.f; q.beta = 0.f;
-        q.tiles_m = (q.M + BM - 1) / BM; q.tiles_n = (q.N + BN - 1) / BN; q.tiles = q.tiles_m * q.tiles_n; q.batch = b.count;
-        q.norm_partial = ssh;
-        rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>(q, s);
-        if (rc) return rc;
-        ssh_count = q.tiles;
+  for (int set = 0; set < p.n_sets; ++set) {
+    const std::vector<Bucket *> todo = members(set);
+    if (todo.empty()) continue;
+    std::vector<int> ssh_count(todo.size());
+    if (use_shampoo) {
+      auto on_planes = [&](const Bucket &b) { return !b.t3 && !b.whole() && b.planes && o->ptrs_aligned16; };
+      constexpr bool THREE = sizeof(GD) == 4;
+      {
+        StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
+        // on a refresh the roots, and with them their scales, have just changed; filtered gradients have not been scaled yet
+        Batch<X2ScaleArgs> scales(x2_scales_kernel, 64, s);
+        Batch<BlockPlanesArgs> planes(block_planes_kernel, 256, s);
+        for (Bucket *b : todo)
+          if (on_planes(*b) && (refresh || (THREE && !b->split_factor)) && (rc = add_x2_scales(scales, *b))) return rc;
+        if ((rc = scales.flush())) return rc;
+        if (THREE)
+          for (Bucket *b : todo)
+            if (on_planes(*b) && b->plane_chunk == b->count && !(b->split_factor && cols_in_t) &&
+                (rc = planes.add(planes_of(*b, 0, b->count, false), planes_wgs(*b, b->count))))
+              return rc;
+        if ((rc = planes.flush())) return rc;
       }
-    } else if (use_shampoo && b.whole()) {
-      // diagonal Shampoo: a diagonalised side scales rows / columns instead of multiplying
-      StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      DiagScaleArgs ds{};
-      ds.desc = desc; ds.g_table = gd_tab; ds.m = b.m; ds.n = b.n; ds.geom = b.geom;
-      const float *dl = reinterpret_cast<const float *>(ws + b.off_Linv), *dr = reinterpret_cast<const float *>(ws + b.off_Rinv);
-      float *ssh = reinterpret_cast<float *>(ws + b.off_sshp);
-      const unsigned ew_grid = (unsigned)b.geom.chunks * b.count;
-      if (b.diagL && b.diagR) {
-        ds.dl = dl; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = c1;
-        hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
-        HIP_TRY(hipGetLastError());
-        ssh_count = b.geom.chunks;
-      } else if (b.diagL) {
-        // T = D_L G, then P = T Rbar with per-tile sums of squares
-        ds.dl = dl; ds.out = T; ds.alpha = c1;
-        hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
-        HIP_TRY(hipGetLastError());
-        GemmArgs h{};
-        h.a.base = T; h.a.batch_stride = (int64_t)b.m * b.n; h.a.ld = b.n;
-        h.b.base = ws + b.off_Rinv; h.b.batch_stride = (int64_t)b.n * b.n; h.b.ld = b.n;
-        h.c = P; h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
-        h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.beta = 0.f;
-        h.tiles_m = b.tiles_m; h.tiles_n = b.tiles_n; h.tiles = b.tiles_m * b.tiles_n; h.batch = b.count;
-        h.norm_partial = ssh;
-        rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>(h, s);
-        if (rc) return rc;
-      } else {
-        // T = Lbar G, then P = T D_R
+      // T = Lbar G, then P = T Rbar with partial sums of squares
+      Batch<GemmX2Args> tall1(gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>, 256, s), wide1(gemm_f16x2_kernel<128, 64, THREE ? 3 : 1, X2_STORE_SPLIT>, 256, s),
+          tall2(gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>, 256, s), wide2(gemm_f16x2_kernel<128, 64, THREE ? 3 : 2, X2_STORE_NORM>, 256, s);
+      Batch<GemmArgs> first(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>, GEMM_THREADS, s),
+          only(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false>, GEMM_THREADS, s),
+          second(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>, GEMM_THREADS, s);
+      auto gemm_wgs = [](const GemmArgs &g) { return (int64_t)g.tiles * g.batch; };
+      auto x2_wgs = [](const GemmX2Args &g) { return (int64_t)g.tiles_m * g.tiles_n * g.batch; };
+      // a block of m x n times its left root, and the other way round
+      auto left_product = [&](const Bucket &b, float *out) {
         GemmArgs g{};
+        // (Lbar symmetric: A(i,k) read as Lbar[k][i], contiguous in i)
         g.a.base = ws + b.off_Linv; g.a.batch_stride = (int64_t)b.m * b.m; g.a.ld = b.m;
-        g.b.from_table = 1; g.desc = desc; g.ptr_table = gd_tab;
-        g.c = T; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
+        g.b.from_table = 1; g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); g.ptr_table = gd_tab;
+        g.c = out; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
         g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.beta = 0.f;
         g.tiles_m = b.tiles_m; g.tiles_n = b.tiles_n; g.tiles = b.tiles_m * b.tiles_n; g.batch = b.count;
-        rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>(g, s);
-        if (rc) return rc;
-        ds.src = T; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = 1.f;
-        hipLaunchKernelGGL(diag_scale_kernel<float>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
-        HIP_TRY(hipGetLastError());
-        ssh_count = b.geom.chunks;
-      }
-    } else if (use_shampoo && b.planes && o->ptrs_aligned16) {
+        return g;
+      };
+      auto right_product = [&](const Bucket &b, const float *in) {
+        GemmArgs h{};
+        h.a.base = in; h.a.batch_stride = (int64_t)b.m * b.n; h.a.ld = b.n;
+        h.b.base = ws + b.off_Rinv; h.b.batch_stride = (int64_t)b.n * b.n; h.b.ld = b.n;
+        h.c = reinterpret_cast<float *>(ws + b.off_P); h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
+        h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.beta = 0.f;
+        h.tiles_m = b.tiles_m; h.tiles_n = b.tiles_n; h.tiles = b.tiles_m * b.tiles_n; h.batch = b.count;
+        h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
+        return h;
+      };
       // Both products on the fp16 or bf16 matrix cores, float32-accurate through splits of the
       // float32 operands, each scaled by a power of two.  A bf16
       // gradient is one fp16 plane (exact: 8 significant bits), the scaled transpose made for the factor
-      // update, against two of Lbar, T and Rbar; a float32 one (or a filtered or shifted one) is split here into three bf16
-      // planes, against three of the others.  B operands are read along k.
-      constexpr bool THREE = sizeof(GD) == 4;
-      const int tm128 = (b.m + 127) / 128, x2_tn = (b.n + X2_TN - 1) / X2_TN;
-      // tiles of 256 rows (half the operand traffic per multiply; three planes do not leave room for them) unless
-      // padding the rows to 256 would add more than an eighth to the work
-      // and unless there are too few of them to give every CU one
-      const int tm256 = (b.m + 255) / 256;
-      const bool tall = !THREE && tm256 * 256 * 8 <= tm128 * 128 * 9 && (int64_t)tm256 * x2_tn * b.count >= 256;
-      const int h_tm = tall ? tm256 : tm128;
-      ssh_count = h_tm * x2_tn;
-      // on a refresh the roots, and with them their scales, have just changed; filtered gradients have not been scaled yet
-      if (refresh || (THREE && !b.split_factor)) launch_x2_scales(b);
-      const int step_blocks = THREE ? b.plane_chunk : b.count;
-      for (int b0 = 0; b0 < b.count; b0 += step_blocks) {
-        const int cnt = std::min(step_blocks, b.count - b0);
+      // update, against two of Lbar, T and Rbar; a float32 one (or a filtered or shifted one) is split into three bf16
+      // planes, against three of the others.  B operands are read along k.  Tiles of 256 rows (half the operand traffic per
+      // multiply; three planes do not leave room for them) unless padding the rows to 256 would add more than an eighth to the
+      // work and unless there are too few of them to give every CU one.
+      struct X2Shape { bool tall; int tm, tn; };
+      auto x2_shape = [&](const Bucket &b) {
+        const int tm128 = (b.m + 127) / 128, tn = (b.n + X2_TN - 1) / X2_TN, tm256 = (b.m + 255) / 256;
+        const bool tall = !THREE && tm256 * 256 * 8 <= tm128 * 128 * 9 && (int64_t)tm256 * tn * b.count >= 256;
+        return X2Shape{tall, tall ? tm256 : tm128, tn};
+      };
+      auto x2_args = [&](const Bucket &b, int b0, int cnt, GemmX2Args &g, GemmX2Args &h) {
+        const X2Shape x = x2_shape(b);
         const int64_t mn = (int64_t)b.m * b.n, plane = cnt * mn;
-        const dim3 grid((unsigned)(((int64_t)h_tm * x2_tn * cnt + NUM_XCD - 1) / NUM_XCD * NUM_XCD));
-        uint16_t *Tp = reinterpret_cast<uint16_t *>(T) + (THREE ? 3 * plane : 0);
-        {
-          StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-          GemmX2Args g{};
-          g.a_plane_stride = (int64_t)b.count * b.m * b.m; g.a_batch_stride = (int64_t)b.m * b.m; g.lda = b.m;
-          g.a = reinterpret_cast<const uint16_t *>(ws + b.off_Linvp) + b0 * g.a_batch_stride;
-          if constexpr (THREE) g.b = cols_in_T == &b ? reinterpret_cast<const uint16_t *>(T) : launch_block_planes(b, b0, cnt, false).cols;
-          else g.b = reinterpret_cast<const uint16_t *>(ws + b.off_Gt);
-          g.b_plane_stride = THREE ? plane : 0; g.b_batch_stride = mn; g.ldb = b.m;
-          g.c2 = Tp; g.c2_plane_stride = plane; g.c_batch_stride = mn; g.ldc = b.n;
-          g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.out_scale = reinterpret_cast<const float *>(ws + b.off_t_scale) + b0;
-          g.tiles_m = h_tm; g.tiles_n = x2_tn; g.batch = cnt;
-          if (tall) hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>), grid, dim3(256), 0, s, g);
-          else hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, THREE ? 3 : 1, X2_STORE_SPLIT>), grid, dim3(256), 0, s, g);
-        }
-        StageTimer t2(o, SHAMPOO_STAGE_PRECOND2, s);
-        GemmX2Args h{};
+        uint16_t *Tp = reinterpret_cast<uint16_t *>(bucket_t(b)) + (THREE ? 3 * plane : 0);
+        g = GemmX2Args{};
+        g.a_plane_stride = (int64_t)b.count * b.m * b.m; g.a_batch_stride = (int64_t)b.m * b.m; g.lda = b.m;
+        g.a = reinterpret_cast<const uint16_t *>(ws + b.off_Linvp) + b0 * g.a_batch_stride;
+        g.b = THREE ? reinterpret_cast<const uint16_t *>(bucket_t(b)) : reinterpret_cast<const uint16_t *>(ws + b.off_Gt);
+        g.b_plane_stride = THREE ? plane : 0; g.b_batch_stride = mn; g.ldb = b.m;
+        g.c2 = Tp; g.c2_plane_stride = plane; g.c_batch_stride = mn; g.ldc = b.n;
+        g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.out_scale = reinterpret_cast<const float *>(ws + b.off_t_scale) + b0;
+        g.tiles_m = x.tm; g.tiles_n = x.tn; g.batch = cnt;
+        h = GemmX2Args{};
         h.a = Tp; h.a_plane_stride = plane; h.a_batch_stride = mn; h.lda = b.n;
         h.b_plane_stride = (int64_t)b.count * b.n * b.n; h.b_batch_stride = (int64_t)b.n * b.n; h.ldb = b.n;
         h.b = reinterpret_cast<const uint16_t *>(ws + b.off_Rinvp) + b0 * h.b_batch_stride;
-        h.c = P + b0 * mn; h.c_batch_stride = mn; h.ldc = b.n;
+        h.c = reinterpret_cast<float *>(ws + b.off_P) + b0 * mn; h.c_batch_stride = mn; h.ldc = b.n;
         h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.out_scale = reinterpret_cast<const float *>(ws + b.off_inv_ts) + b0;
-        h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp) + (int64_t)b0 * ssh_count;
-        h.tiles_m = h_tm; h.tiles_n = x2_tn; h.batch = cnt;
-        if (tall) hipLaunchKernelGGL((gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>), grid, dim3(256), 0, s, h);
-        else hipLaunchKernelGGL((gemm_f16x2_kernel<128, 64, THREE ? 3 : 2, X2_STORE_NORM>), grid, dim3(256), 0, s, h);
-        HIP_TRY(hipGetLastError());
-      }
-    } else if (use_shampoo) {
+        h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp) + (int64_t)b0 * x.tm * x.tn;
+        h.tiles_m = x.tm; h.tiles_n = x.tn; h.batch = cnt;
+      };
       {
-      StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
-      GemmArgs g{};
-      // T = Lbar G   (Lbar symmetric: A(i,k) read as Lbar[k][i], contiguous in i)
-      g.a.base = ws + b.off_Linv; g.a.batch_stride = (int64_t)b.m * b.m; g.a.ld = b.m;
-      g.b.from_table = 1; g.desc = desc; g.ptr_table = gd_tab;
-      g.c = T; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
-      g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.beta = 0.f;
-      g.tiles_m = b.tiles_m; g.tiles_n = b.tiles_n; g.tiles = b.tiles_m * b.tiles_n; g.batch = b.count;
-      rc = launch_gemm<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>(g, s);
-      if (rc) return rc;
+        StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
+        for (size_t i = 0; i < todo.size(); ++i) {
+          const Bucket &b = *todo[i];
+          float *T = bucket_t(b), *P = reinterpret_cast<float *>(ws + b.off_P), *ssh = reinterpret_cast<float *>(ws + b.off_sshp);
+          ssh_count[i] = b.tiles_m * b.tiles_n;
+          if (on_planes(b)) {
+            const X2Shape x = x2_shape(b);
+            ssh_count[i] = x.tm * x.tn;
+            if (THREE && b.plane_chunk < b.count) continue;      // below
+            GemmX2Args g, h;
+            x2_args(b, 0, b.count, g, h);
+            if ((rc = (x.tall ? tall1 : wide1).add(g, x2_wgs(g))) || (rc = (x.tall ? tall2 : wide2).add(h, x2_wgs(h)))) return rc;
+          } else if (b.t3) {
+            // P = G x_1 Lbar_1 x_2 Lbar_2 ... x_w Lbar_w (Sec. 2.3), the first product here
+            GemmArgs g = left_product(b, b.modes == 1 ? P : T);
+            if (b.modes == 1) { g.norm_partial = ssh; rc = only.add(g, gemm_wgs(g)); }
+            else rc = first.add(g, gemm_wgs(g));
+            if (rc) return rc;
+          } else if (b.whole()) {
+            // diagonal Shampoo: a diagonalised side scales rows / columns instead of multiplying
+            DiagScaleArgs ds{};
+            ds.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);  ds.g_table = gd_tab; ds.m = b.m; ds.n = b.n; ds.geom = b.geom;
+            const float *dl = reinterpret_cast<const float *>(ws + b.off_Linv), *dr = reinterpret_cast<const float *>(ws + b.off_Rinv);
+            const unsigned ew_grid = (unsigned)b.geom.chunks * b.count;
+            if (b.diagL && b.diagR) {
+              ds.dl = dl; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = c1;
+              hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
+              HIP_TRY(hipGetLastError());
+              ssh_count[i] = b.geom.chunks;
+            } else if (b.diagL) {
+              // T = D_L G, then P = T Rbar with per-tile sums of squares
+              ds.dl = dl; ds.out = T; ds.alpha = c1;
+              hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
+              HIP_TRY(hipGetLastError());
+              const GemmArgs h = right_product(b, T);
+              if ((rc = second.add(h, gemm_wgs(h)))) return rc;
+            } else {
+              // T = Lbar G, then P = T D_R
+              const GemmArgs g = left_product(b, T);
+              if ((rc = first.add(g, gemm_wgs(g))) || (rc = first.flush())) return rc;
+              ds.src = T; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = 1.f;
+              hipLaunchKernelGGL(diag_scale_kernel<float>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
+              HIP_TRY(hipGetLastError());
+              ssh_count[i] = b.geom.chunks;
+            }
+          } else {
+            const GemmArgs g = left_product(b, T), h = right_product(b, T);
+            if ((rc = first.add(g, gemm_wgs(g))) || (rc = second.add(h, gemm_wgs(h)))) return rc;
+          }
+        }
+        if ((rc = tall1.flush()) || (rc = wide1.flush()) || (rc = first.flush()) || (rc = only.flush())) return rc;
+        // A middle mode k of a tensor block, seen as pre x d_k x post: its first two
+        // indices are swapped, the product is the plain one on d_k x (pre post), and they are
+        // swapped back; then the last mode on the block as (N / d_w) x d_w.
+        std::vector<int> swapped(todo.size(), 0);       // the block is in the second scratch
+        for (int mid = 0; mid < 2; ++mid) {
+          Batch<PermuteArgs> there(permute_12_kernel<float>, 256, s), back(permute_12_kernel<float>, 256, s);
+          Batch<GemmArgs> products(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>, GEMM_THREADS, s);
+          for (size_t i = 0; i < todo.size(); ++i) {
+            const Bucket &b = *todo[i];
+            if (!b.t3 || mid + 2 >= b.modes) continue;
+            float *cur = bucket_t(b), *other = reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2);
+            if (swapped[i]) std::swap(cur, other);
+            const int64_t mn = (int64_t)b.m * b.n;
+            const int pre = mid == 0 ? b.m : b.m * b.td[1], dk = b.td[mid + 1], post = (int)(mn / ((int64_t)pre * dk));
+            PermuteArgs pm{};
+            pm.src = cur; pm.dst = other; pm.d1 = pre; pm.d2 = dk; pm.d3 = post; pm.chunks = tensor_chunks(b); pm.blocks = b.count;
+            if ((rc = there.add(pm, (int64_t)pm.chunks * b.count))) return rc;
+            GemmArgs h{};
+            h.a.base = ws + b.off_midinv[mid]; h.a.batch_stride = (int64_t)dk * dk; h.a.ld = dk;
+            h.b.base = other; h.b.batch_stride = mn; h.b.ld = pre * post;
+            h.c = cur; h.c_batch_stride = mn; h.ldc = pre * post;
+            h.M = dk; h.N = pre * post; h.K = dk; h.alpha = 1.f; h.beta = 0.f;
+            h.tiles_m = (h.M + BM - 1) / BM; h.tiles_n = (h.N + BN - 1) / BN; h.tiles = h.tiles_m * h.tiles_n; h.batch = b.count;
+            if ((rc = products.add(h, gemm_wgs(h)))) return rc;
+            pm.d1 = dk; pm.d2 = pre;
+            if ((rc = back.add(pm, (int64_t)pm.chunks * b.count))) return rc;
+            swapped[i] ^= 1;
+          }
+          if ((rc = there.flush()) || (rc = products.flush()) || (rc = back.flush())) return rc;
+        }
+        for (size_t i = 0; i < todo.size(); ++i) {
+          const Bucket &b = *todo[i];
+          if (!b.t3 || b.modes == 1) continue;
+          const int dl = b.dlast();
+          const int64_t mn = (int64_t)b.m * b.n;
+          GemmArgs q{};
+          q.a.base = swapped[i] ? reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2) : bucket_t(b); q.a.batch_stride = mn; q.a.ld = dl;
+          q.b.base = ws + b.off_Rinv; q.b.batch_stride = (int64_t)dl * dl; q.b.ld = dl;
+          q.c = reinterpret_cast<float *>(ws + b.off_P); q.c_batch_stride = mn; q.ldc = dl;
+          q.M = (int)(mn / dl); q.N = dl; q.K = dl; q.alpha = 1.f; q.beta = 0.f;
+          q.tiles_m = (q.M + BM - 1) / BM; q.tiles_n = (q.N + BN - 1) / BN; q.tiles = q.tiles_m * q.tiles_n; q.batch = b.count;
+          q.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
+          if ((rc = second.add(q, gemm_wgs(q)))) return rc;
+          ssh_count[i] = q.tiles;
+        }
       }
-      // P = T Rbar, with per-tile sums of squares
-      StageTimer t2(o, SHAMPOO_STAGE_PRECOND2, s);
-      GemmArgs h{};
-      h.a.base = T; h.a.batch_stride = (int64_t)b.m * b.n; h.a.ld = b.n;
-      h.b.base = ws + b.off_Rinv; h.b.batch_stride = (int64_t)b.n * b.n; h.b.ld = b.n;
-      h.c = P; h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
-      h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.beta = 0.f;
-      h.tiles_m = b.tiles_m; h.tiles_n = b.tiles_n; h.tiles = b.tiles_m * b.tiles_n; h.batch = b.count;
-      h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
-      rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>(h, s);
-      if (rc) return rc;
+      {
+        StageTimer t(o, SHAMPOO_STAGE_PRECOND2, s);
+        if ((rc = tall2.flush()) || (rc = wide2.flush()) || (rc = second.flush())) return rc;
+      }
+      // planes of more blocks than the scratch has room for: in passes
+      if (THREE)
+        for (Bucket *bp : todo) {
+          const Bucket &b = *bp;
+          if (!on_planes(b) || b.plane_chunk == b.count) continue;
+          for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
+            const int cnt = std::min(b.plane_chunk, b.count - b0);
+            GemmX2Args g, h;
+            x2_args(b, b0, cnt, g, h);
+            {
+              StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
+              Batch<BlockPlanesArgs> planes(block_planes_kernel, 256, s);
+              if ((rc = planes.add(planes_of(b, b0, cnt, false), planes_wgs(b, cnt))) || (rc = planes.flush())) return rc;
+              if ((rc = wide1.add(g, x2_wgs(g))) || (rc = wide1.flush())) return rc;
+            }
+            StageTimer t(o, SHAMPOO_STAGE_PRECOND2, s);
+            if ((rc = wide2.add(h, x2_wgs(h))) || (rc = wide2.flush())) return rc;
+          }
+        }
     }
     {
       StageTimer t(o, SHAMPOO_STAGE_UPDATE, s);
-      if (use_shampoo) {
-        ScaleArgs sa;
-        sa.sg_partial = reinterpret_cast<const float *>(ws + b.off_sgp); sa.sg_count = b.geom.chunks;
-        sa.ssh_partial = reinterpret_cast<const float *>(ws + b.off_sshp); sa.ssh_count = ssh_count;
-        sa.scale = scale; sa.norms = reinterpret_cast<float *>(ws + b.off_norms);
-        hipLaunchKernelGGL(scale_kernel, dim3(b.count), dim3(64), 0, s, sa);
+      Batch<ScaleArgs> scales(scale_kernel, 64, s);
+      Batch<EwArgs> updates(update_kernel<GD>, EW_THREADS, s);
+      for (size_t i = 0; i < todo.size(); ++i) {
+        const Bucket &b = *todo[i];
+        float *scale = reinterpret_cast<float *>(ws + b.off_scale);
+        if (use_shampoo) {
+          ScaleArgs sa;
+          sa.sg_partial = reinterpret_cast<const float *>(ws + b.off_sgp); sa.sg_count = b.geom.chunks;
+          sa.ssh_partial = reinterpret_cast<const float *>(ws + b.off_sshp); sa.ssh_count = ssh_count[i];
+          sa.scale = scale; sa.norms = reinterpret_cast<float *>(ws + b.off_norms); sa.blocks = b.count;
+          if ((rc = scales.add(sa, b.count))) return rc;
+        }
+        EwArgs e{};
+        fill_ew(e, b);
+        e.p = reinterpret_cast<float *>(ws + b.off_P); e.scale = scale;
+        e.wd_decoupled = wd_dec; e.nesterov = c.use_nesterov ? 1 : 0;
+        e.graft_only = use_shampoo ? 0 : 1;
+        if ((rc = updates.add(e, (int64_t)b.geom.chunks * b.count))) return rc;
       }
-      EwArgs e{};
-      e.desc = desc; e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
-      e.p = P; e.scale = scale;
-      e.m = b.m; e.n = b.n; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
-      e.wd_decoupled = wd_dec; e.nesterov = c.use_nesterov ? 1 : 0; e.sgd_graft = sgd; e.gd_scale = c1;
-      e.a_decay = a_decay; e.a_gain = a_gain; e.a_bc = a_bc;
-      e.graft_only = use_shampoo ? 0 : 1;
-      hipLaunchKernelGGL(update_kernel<GD>, dim3((unsigned)b.geom.chunks * b.count), dim3(EW_THREADS), 0, s, e);
-      HIP_TRY(hipGetLastError());
+      if ((rc = scales.flush()) || (rc = updates.flush())) return rc;
     }
   }
   if (o->has_tensor) {

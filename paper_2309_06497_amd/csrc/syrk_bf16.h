@@ -50,6 +50,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "group.h"
 #include "lds_dma.h"
 
 namespace shampoo {
@@ -70,6 +71,7 @@ struct SyrkBf16Args {
   const float *x_scale;      // [batch] X holds values s x; 1 / s^2 is applied with alpha (nullptr: X itself)
   int32_t tiles;             // lower-triangular tile count per batch entry
   int32_t batch;
+  __device__ __forceinline__ void globals() { to_global(a.base, desc, ptr_table, c, x_scale); }
 };
 
 typedef _Float16 syrk_f16x8 __attribute__((ext_vector_type(8)));
@@ -88,10 +90,12 @@ __device__ __forceinline__ floatx16 syrk_mfma(floatx16 acc, const u32x4 &a0, con
 // such values are exact in float32 as well) and the fp16 matrix-core instruction is used.
 // ACC64: float64 accumulators; SPLIT: three planes; see the head of this file.
 template <bool F16, bool ACC64, bool SPLIT = false>
-__global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(const SyrkBf16Args g) {
+__global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(const Group<SyrkBf16Args> grp) {
   __shared__ __align__(128) unsigned char smem[SYRK_STAGES * SYRK_STAGE];   // the k-step addresses below differ by an XOR
+  int wg;
+  const SyrkBf16Args g = group_pick(grp, wg);
   const int total = g.tiles * g.batch;
-  const int logical = xcd_remap(blockIdx.x, total);
+  const int logical = xcd_remap(wg, total);
   if (logical >= total) return;
   const int b = logical / g.tiles;
   const int tile = logical - b * g.tiles;
@@ -329,19 +333,24 @@ struct TransposeArgs {
   const void *const *g_table;
   uint16_t *out;             // [slot][n][m]
   const float *scale;        // [slot] nullptr: out is bf16 like the block; else out = fp16(scale * block)
-  int32_t m, n;
+  int32_t m, n, blocks;
+  __device__ __forceinline__ void globals() { to_global(desc, g_table, out, scale); }
 };
 
-// out[slot][j][i] = G_block[i][j] (bf16 bits, or fp16 bits of the scaled value).  grid (ceil(n/64), ceil(m/64), blocks), 256 threads.
+// out[slot][j][i] = G_block[i][j] (bf16 bits, or fp16 bits of the scaled value).  Workgroups: ceil(n / 64) x ceil(m / 64) x blocks; 256 threads.
 // Both sides move 16 bytes per lane (8 bf16 along the contiguous direction); the transposition
 // itself happens in LDS.  Requires m % 8 == 0, n % 8 == 0, 16-byte aligned rows on both sides
 // (the conditions of the bf16 matrix-core path, checked by the host).
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const TransposeArgs g) {
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(const Group<TransposeArgs> grp) {
   __shared__ uint16_t tile[64][66];
-  const BlockDesc d = g.desc[blockIdx.z];
-  const uint16_t *src = reinterpret_cast<const uint16_t *>(g.g_table[d.param]) + d.offset;
-  uint16_t *dst = g.out + (int64_t)blockIdx.z * g.m * g.n;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+  int wg;
+  const TransposeArgs g = group_pick(grp, wg);
+  const int gx = (g.n + 63) / 64, gy = (g.m + 63) / 64, slot = wg / (gx * gy), ty = (wg - slot * gx * gy) / gx, tx = wg % gx;
+  if (slot >= g.blocks) return;
+  const BlockDesc d = g.desc[slot];
+  const uint16_t *src = global_ptr<const uint16_t>(g.g_table[d.param]) + d.offset;
+  uint16_t *dst = g.out + (int64_t)slot * g.m * g.n;
+  const int i0 = ty * 64, j0 = tx * 64;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int idx = threadIdx.x + 256 * h, r = idx >> 3, c = (idx & 7) * 8;
@@ -350,7 +359,7 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const TransposeArgs
     if (i < g.m && j < g.n) v = *reinterpret_cast<const uint4 *>(src + (int64_t)i * d.ld + j);
     uint32_t w[4] = {v.x, v.y, v.z, v.w};
     if (g.scale) {      // uniform: bf16 -> scaled fp16 (exact unless it underflows: 8 significant bits go into 11)
-      const float sc = g.scale[blockIdx.z];
+      const float sc = g.scale[slot];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const _Float16 lo = (_Float16)(__uint_as_float(w[e] << 16) * sc), hi = (_Float16)(__uint_as_float(w[e] & 0xffff0000u) * sc);

@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "group.h"
 
 namespace shampoo {
 
@@ -78,22 +79,27 @@ struct PermuteArgs {
   const float *src;             // ... or a dense float32 array [slot][d1][d2][d3]
   float *dst;                   // [slot][d2][d1][d3]
   int32_t d1, d2, d3;
+  int32_t chunks, blocks;       // workgroups per block
+  __device__ __forceinline__ void globals() { to_global(desc, table, src, dst); }
 };
 
-// dst[slot][i2][i1][i3] = in[slot][i1][i2][i3].  grid (chunks, slots).
+// dst[slot][i2][i1][i3] = in[slot][i1][i2][i3].  Workgroups: chunks x blocks.
 template <typename T>
-__global__ __launch_bounds__(256) void permute_12_kernel(const PermuteArgs g) {
-  const int slot = blockIdx.y;
+__global__ __launch_bounds__(256) void permute_12_kernel(const Group<PermuteArgs> grp) {
+  int wg;
+  const PermuteArgs g = group_pick(grp, wg);
+  const int slot = wg / g.chunks, chunk = wg - slot * g.chunks;
+  if (slot >= g.blocks) return;
   const uint32_t n = (uint32_t)g.d1 * g.d2 * g.d3;
   const T *tin = nullptr;
   if (!g.src) {
     const BlockDesc d = g.desc[slot];
-    tin = reinterpret_cast<const T *>(g.table[d.param]) + d.offset;
+    tin = global_ptr<const T>(g.table[d.param]) + d.offset;
   }
   const float *fin = g.src ? g.src + (int64_t)slot * n : nullptr;
   float *out = g.dst + (int64_t)slot * n;
   const uint32_t d1 = g.d1, d2 = g.d2, d3 = g.d3;   // 32-bit divisions: a block has less than 2^31 elements
-  for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < n; e += gridDim.x * 256) {
+  for (uint32_t e = chunk * 256 + threadIdx.x; e < n; e += g.chunks * 256) {
     const uint32_t q = e / d3, i3 = e - q * d3, i1 = q / d2, i2 = q - i1 * d2;
     const float v = fin ? fin[e] : Elem<T>::load1(tin + e);
     out[(i2 * d1 + i1) * d3 + i3] = v;
@@ -103,8 +109,9 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const PermuteArgs g) {
 struct GramReduceArgs {
   const void *partial;    // [slot][splits][d][d]
   float *factor;          // [slot][d][d]
-  int32_t d, splits;
+  int32_t d, splits, blocks;
   double alpha, beta;
+  __device__ __forceinline__ void globals() { to_global(partial, factor); }
 };
 
 struct GramNarrowArgs {
@@ -112,20 +119,23 @@ struct GramNarrowArgs {
   const void *const *table;
   float *partial;               // [slot][split][d][d]
   int32_t d, rows, entries;
+  __device__ __forceinline__ void globals() { to_global(desc, table, partial); }
 };
 
 // X^T X of a range of rows of a row-major matrix of d <= 16 columns, one wavefront per range: the factor of the last
 // dimension of a tensor block (9 columns and 16384 rows for a 3 x 3 convolution at block size 128).  With
 // v_mfma_f32_16x16x4_f32 one register of 4 rows is both operands, and 16 rows at a time are summed before they go
 // into float64, as in the general SYRK kernel.  That one multiplies 128 x 128 tiles, 99 % of it padding at d = 9:
-// 564 -> 25 us for the blocks of ResNet-50 (most of them 128 x 128 x 9).  Bound by the latency of the loads.  grid (ceil(entries / 4)), 4 wavefronts.
+// 564 -> 25 us for the blocks of ResNet-50 (most of them 128 x 128 x 9).  Bound by the latency of the loads.  Workgroups: ceil(entries / 4), 4 wavefronts.
 template <typename T>
-__global__ __launch_bounds__(256) void gram_narrow_kernel(const GramNarrowArgs g) {
+__global__ __launch_bounds__(256) void gram_narrow_kernel(const Group<GramNarrowArgs> grp) {
   typedef float narrow_f4 __attribute__((ext_vector_type(4)));
-  const int entry = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4, d = g.d;
+  int wg;
+  const GramNarrowArgs g = group_pick(grp, wg);
+  const int entry = wg * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4, d = g.d;
   if (entry >= g.entries) return;
   const BlockDesc bd = g.desc[entry];
-  const T *x = reinterpret_cast<const T *>(g.table[bd.param]) + bd.offset;
+  const T *x = global_ptr<const T>(g.table[bd.param]) + bd.offset;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
   for (int r0 = 0; r0 < g.rows; r0 += 16) {
@@ -148,13 +158,14 @@ __global__ __launch_bounds__(256) void gram_narrow_kernel(const GramNarrowArgs g
 }
 
 // factor <- beta factor + alpha sum_s partial_s, in float64, fixed order: the Gram matrix of a split
-// unfolding.  grid (ceil(d d / 256), slots).
+// unfolding.  Workgroups: ceil(d d / 256) x blocks.
 template <typename T>
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const GramReduceArgs g) {
-  const int slot = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int dd = g.d * g.d;
-  if (e >= dd) return;
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const Group<GramReduceArgs> grp) {
+  int wg;
+  const GramReduceArgs g = group_pick(grp, wg);
+  const int dd = g.d * g.d, per = (dd + 255) / 256, slot = wg / per;
+  const int e = (wg - slot * per) * 256 + threadIdx.x;
+  if (slot >= g.blocks || e >= dd) return;
   const T *p = static_cast<const T *>(g.partial) + (int64_t)slot * g.splits * dd + e;
   double acc = 0.0;
   for (int s = 0; s < g.splits; ++s) acc += (double)p[(int64_t)s * dd];
