@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "lds_dma.h"
 #include "root_rational.h"
 #include "root_tridiag.h"
 
@@ -181,37 +182,102 @@ __global__ __launch_bounds__(256) void band_alone_kernel(BandArgs g) {
 
 // ---------------------------------------------------------------------------
 // QR of panel k (rows 32 (k + 1) ... np - 1 of columns 32 k ... 32 k + 31): V, T, R; and D_k as it now is.
-// One workgroup of 16 wavefronts per matrix, 16 columns at a time: lane (c = l % 16, ph = l / 16) of
-// wavefront w holds rows 4 (16 t + w) + ph of column c, t < TT, so that the entry of the pivot column of
-// a row reaches the row's 16 columns by a DPP broadcast, and the entries are MFMA operands as they lie.
-// Per column one barrier; bound by the vector instructions of the two passes over the registers
-// (about 9 per register), i.e. by the one CU that a matrix has here: 30 us for a panel of 1024 rows.
+// One workgroup of 8 wavefronts per matrix, 16 columns at a time: lane (c = l % 16, ph = l / 16) of
+// wavefront w holds rows 32 t + 4 w + ph of column c, t < TT, so that the entry of the pivot column of
+// a row reaches the row's 16 columns by a DPP broadcast, which a multiply-add takes as an operand: one instruction per
+// register for the scalar products of a column, one for the update.  So that the update is that simple, the pivot column
+// stays as it is and becomes the reflector, by one factor, when all 16 are done.  The entries are MFMA operands as they lie.
+// Per column one barrier.  Two wavefronts per SIMD: the panel of 2048 rows takes 128 of 256 registers (four
+// wavefronts with half as many rows each spilled up to 247 of 128).
+// 8 panels of 2048 rows beside 8 others: 287 us before, 118 so; 32 of 1024 rows 152 and 85 us.
 // The other matrices of the batch run beside it, other sub-chunks' products too.
 // ---------------------------------------------------------------------------
+constexpr int BAND_QR_WAVES = 8, BAND_QR_THREADS = 64 * BAND_QR_WAVES;
+
+// d[i] += (lane J of the row's x[i]) * x[i], i < 4.  A register that the DPP operand reads must not have been written by
+// the two instructions before.
+template <int J> __device__ __forceinline__ void row16_dot4(double (&d)[4], double x0, double x1, double x2, double x3) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %4, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %5, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %6, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %7, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+      : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3]) : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "n"(J));
+}
+// x[i] += (lane J of the row's y[i]) * q; y may be x itself
+template <int J> __device__ __forceinline__ void row16_update4(double &x0, double &x1, double &x2, double &x3, double q) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %0, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %1, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %3, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+      : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3) : "v"(q), "n"(J));
+}
+template <int J> __device__ __forceinline__ void row16_fma(double &x, double y, double q) {
+  asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(y), "v"(q), "n"(J));
+}
 template <int J> __device__ __forceinline__ double row16_bcast(double x) { return dpp_fetch<0x150 + J>(x); }
+// sum over the four lanes l % 16, in all of them
+__device__ __forceinline__ double rows_sum(double x) {
+  auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+  auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+  x = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+  hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// One element per lane and row block of a column of a row-major array: lane address and scalar step, in elements
+struct BandColumn {
+  __amdgpu_buffer_rsrc_t r;
+  int lane;
+  __device__ __forceinline__ BandColumn(const void *base, int lane_, int size)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(uniform_ptr(base)), 0, INT32_MAX, 0x00020000)), lane(lane_ * size) {}
+  __device__ __forceinline__ double get(int at) const {
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    const pair x = __builtin_amdgcn_raw_buffer_load_b64(r, lane, at * 8, 0);
+    return __hiloint2double((int)x[1], (int)x[0]);
+  }
+  __device__ __forceinline__ void put(int at, double v) const {
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(pair{(uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)}, r, lane, at * 8, 0);
+  }
+  __device__ __forceinline__ void put(int at, float v) const { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, lane, at * 4, 0); }
+};
 
 struct BandQrShared {
-  double red[2][16][16], prow[2][16], tau[BAND];
-  double big[16][256];                   // one 16 x 16 tile per wavefront
+  double red[2][BAND_QR_WAVES][16], prow[2][16], tau[BAND];
+  double big[BAND_QR_WAVES][256];        // one 16 x 16 tile per wavefront
   double s[16][17], t[2][16][17], g01[16][17];
 };
 
 template <int TT>
-__global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) {
+__global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(BandArgs g, const int k) {
+  static_assert(TT % 4 == 0, "registers by fours");
   __shared__ BandQrShared sh;
   band_select(g, blockIdx.x);
   if (g.meta->skip) return;
-  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, ph = lane >> 4;
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, ph = lane >> 4;
   const int r0 = (k + 1) * BAND, m = np - r0;
-  g.dblk[(int64_t)k * 1024 + tid] = g.w[(int64_t)(k * BAND + (tid >> 5)) * np + k * BAND + (tid & 31)];
+  for (int x = tid; x < 1024; x += BAND_QR_THREADS) g.dblk[(int64_t)k * 1024 + x] = g.w[(int64_t)(k * BAND + (x >> 5)) * np + k * BAND + (x & 31)];
   if (m <= 0) return;
-  const int tt = (m + 63) / 64;
-  const int rel0 = 4 * w + ph;           // row of register t: rel0 + 64 t
-  double *vp = g.vp + (int64_t)r0 * BAND;
-  float *va = g.vall + (int64_t)r0 * np + k * BAND;
+  const int tt = m / BAND;               // row blocks of 32: np is a multiple
+  const int rel0 = 4 * w + ph;           // row of register t: rel0 + 32 t
+  // The panel's columns in W, V and all of V: a lane's address, plus a scalar that steps from register to register (64 vector
+  // addresses, held over both halves, cost more registers than the panel)
+  const BandColumn wcol(g.w + (int64_t)r0 * np + k * BAND, rel0 * np + c, 8), vcol(g.vp + (int64_t)r0 * BAND, rel0 * BAND + c, 8),
+      acol(g.vall + (int64_t)r0 * np + k * BAND, rel0 * np + c, 4);
   double P[TT];
   int buf = 0;
 
+  // f(t) for the registers that hold rows, four of them in flight at a time (all loads ahead of all uses would take as many
+  // registers again)
+  auto by_fours = [&](auto f) {
+    for_each_block<TT>([&](auto t) {
+      if (decltype(t)::value < tt) f(t);
+      if constexpr (decltype(t)::value % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    });
+  };
   // sum over the wavefronts of a 16 x 16 tile held as MFMA results: to sum[i][j]
   auto tile_sum = [&](band_d4 acc, double (*sum)[17]) {
 #pragma unroll
@@ -220,29 +286,22 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
     if (tid < 256) {
       double s = 0.0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s += sh.big[i][tid];
+      for (int i = 0; i < BAND_QR_WAVES; ++i) s += sh.big[i][tid];
       sum[tid >> 4][tid & 15] = s;
     }
     __syncthreads();
   };
 
+#pragma unroll 1
   for (int h = 0; h < 2; ++h) {
-    {
-      const double *src = g.w + (int64_t)r0 * np + k * BAND + 16 * h + c;
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        P[t] = 0.0;
-        if (t < tt) { const int rel = rel0 + 64 * t; if (rel < m) P[t] = src[(int64_t)rel * np]; }
-      }
+    for (int t = 0; t < TT; ++t) {
+      P[t] = 0.0;
+      if (t < tt) P[t] = wcol.get(t * BAND * np + 16 * h);
     }
     if (h == 1) {                        // the reflectors of the first 16 columns:  C <- C - V0 (T0^T V0^T C)
       band_d4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int t = 0; t < TT; ++t)
-        if (t < tt) {
-          const int rel = rel0 + 64 * t;
-          acc = band_mfma(rel < m ? vp[(int64_t)rel * BAND + c] : 0.0, P[t], acc);
-        }
+      by_fours([&](auto t) { acc = band_mfma(vcol.get(decltype(t)::value * BAND * BAND), P[decltype(t)::value], acc); });
       tile_sum(acc, sh.s);
       double e = 0.0;
       if (tid < 256) for (int l = 0; l <= (tid >> 4); ++l) e += sh.t[0][l][tid >> 4] * sh.s[l][tid & 15];
@@ -251,36 +310,31 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
       __syncthreads();
       double sw[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sw[i] = sh.s[i][c];
-#pragma unroll
-      for (int t = 0; t < TT; ++t)
-        if (t < tt) {
-          const int rel = rel0 + 64 * t;
-          const double v = rel < m ? vp[(int64_t)rel * BAND + c] : 0.0;
-          double p = P[t];
-          for_each_block<16>([&](auto i) { p -= row16_bcast<decltype(i)::value>(v) * sw[decltype(i)::value]; });
-          P[t] = p;
-        }
+      for (int i = 0; i < 16; ++i) sw[i] = -sh.s[i][c];
+      by_fours([&](auto t) {
+        const double v = vcol.get(decltype(t)::value * BAND * BAND);
+        for_each_block<16>([&](auto i) { row16_fma<decltype(i)::value>(P[decltype(t)::value], v, sw[decltype(i)::value]); });
+      });
     }
+    double mine = 0.0;                   // the factor that makes a reflector of this lane's column
     for_each_block<16>([&](auto jj) {
       constexpr int J = decltype(jj)::value;
       const int pr = 16 * h + J;         // pivot row
-      double dot = 0.0;
+      double d[4] = {0.0, 0.0, 0.0, 0.0};
+      {
+        const double x = rel0 > pr ? P[0] : 0.0;
+        row16_dot4<J>(d, x, P[1], P[2], P[3]);
+      }
 #pragma unroll
-      for (int t = 0; t < TT; ++t)
-        if (t < tt) {
-          double x = row16_bcast<J>(P[t]);
-          if (t == 0) x = rel0 > pr ? x : 0.0;
-          dot += x * P[t];
-        }
-      dot += __shfl_xor(dot, 16, 64);
-      dot += __shfl_xor(dot, 32, 64);
+      for (int t = 4; t < TT; t += 4)
+        if (t < tt) row16_dot4<J>(d, P[t], P[t + 1], P[t + 2], P[t + 3]);
+      const double dot = rows_sum((d[0] + d[1]) + (d[2] + d[3]));
       if (lane < 16) sh.red[buf][w][c] = dot;
       if (rel0 == pr) sh.prow[buf][c] = P[0];
       __syncthreads();
       double s = 0.0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s += sh.red[buf][i][c];
+      for (int i = 0; i < BAND_QR_WAVES; ++i) s += sh.red[buf][i][c];
       const double sj = row16_bcast<J>(s), x0 = sh.prow[buf][J], pc = sh.prow[buf][c];
       buf ^= 1;
       double tau = 0.0;
@@ -288,37 +342,31 @@ __global__ __launch_bounds__(1024) void band_qr_kernel(BandArgs g, const int k) 
         const double nn = sj + x0 * x0, rn = rsqrt_newton(nn), norm = nn * rn;
         const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, inv = rcp_newton(v0);
         tau = fabs(v0) * rn;
-        const double wc = c > J ? tau * (s * inv + pc) : 0.0;
+        const double wc = c > J ? tau * (s * inv + pc) : 0.0, q = -(inv * wc);
+        if (c == J) mine = inv;
+        double x = rel0 > pr ? P[0] : 0.0;
+        const double x1 = x;
+        row16_fma<J>(x, x1, q);
+        P[0] = rel0 > pr ? x : rel0 == pr ? (c == J ? alpha : P[0] - wc) : P[0];
+        row16_update4<J>(x, P[1], P[2], P[3], q);      // x: not used any more
 #pragma unroll
-        for (int t = 0; t < TT; ++t)
-          if (t < tt) {
-            double v = row16_bcast<J>(P[t]) * inv;
-            if (t == 0) v = rel0 > pr ? v : rel0 == pr ? 1.0 : 0.0;
-            const double p = P[t] - v * wc;
-            if (t == 0) P[t] = c != J ? p : rel0 > pr ? v : rel0 == pr ? alpha : P[t];
-            else P[t] = c != J ? p : v;
-          }
-      } else if (c == J) {
-#pragma unroll
-        for (int t = 0; t < TT; ++t) if (t > 0 || rel0 > pr) P[t] = 0.0;
+        for (int t = 4; t < TT; t += 4)
+          if (t < tt) row16_update4<J>(P[t], P[t + 1], P[t + 2], P[t + 3], q);
       }
       if (tid == 0) sh.tau[pr] = tau;
     });
     // R (rows up to the pivot's) and V out; what is left in P is V
-    if (rel0 < BAND) g.cblk[(int64_t)k * 1024 + (16 * h + c) * BAND + rel0] = rel0 <= 16 * h + c ? P[0] : 0.0;
-    P[0] = rel0 > 16 * h + c ? P[0] : rel0 == 16 * h + c ? 1.0 : 0.0;
+    g.cblk[(int64_t)k * 1024 + (16 * h + c) * BAND + rel0] = rel0 <= 16 * h + c ? P[0] : 0.0;
+    P[0] = rel0 > 16 * h + c ? P[0] * mine : rel0 == 16 * h + c ? 1.0 : 0.0;
     band_d4 acc = {0.0, 0.0, 0.0, 0.0}, acc01 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int t = 0; t < TT; ++t)
-      if (t < tt) {
-        const int rel = rel0 + 64 * t;
-        if (h == 1) acc01 = band_mfma(rel < m ? vp[(int64_t)rel * BAND + c] : 0.0, P[t], acc01);
-        acc = band_mfma(P[t], P[t], acc);
-        if (rel < m) {
-          vp[(int64_t)rel * BAND + 16 * h + c] = P[t];
-          va[(int64_t)rel * np + 16 * h + c] = (float)P[t];
-        }
-      }
+    by_fours([&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      const double v = t > 0 ? P[t] * mine : P[0];
+      if (h == 1) acc01 = band_mfma(vcol.get(t * BAND * BAND), v, acc01);
+      acc = band_mfma(v, v, acc);
+      vcol.put(t * BAND * BAND + 16 * h, v);
+      acol.put(t * BAND * np + 16 * h, (float)v);
+    });
     tile_sum(acc, sh.s);
     // T of these 16 columns: T[i][j] = -tau_j sum_{i <= l < j} T[i][l] (v_l . v_j); lane i holds row i
     if (w == 0) {

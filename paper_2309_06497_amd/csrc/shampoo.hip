@@ -753,9 +753,10 @@ struct BandSolve {
   }
   int forward(int k) {
     const int m = g.np - (k + 1) * BAND;
-    if (m <= 512) hipLaunchKernelGGL(band_qr_kernel<8>, dim3(cnt), dim3(1024), 0, s, g, k);
-    else if (m <= 1024) hipLaunchKernelGGL(band_qr_kernel<16>, dim3(cnt), dim3(1024), 0, s, g, k);
-    else hipLaunchKernelGGL(band_qr_kernel<32>, dim3(cnt), dim3(1024), 0, s, g, k);
+    if (m <= 256) hipLaunchKernelGGL(band_qr_kernel<8>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
+    else if (m <= 512) hipLaunchKernelGGL(band_qr_kernel<16>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
+    else if (m <= 1024) hipLaunchKernelGGL(band_qr_kernel<32>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
+    else hipLaunchKernelGGL(band_qr_kernel<64>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
     if (m > 0) {
       const unsigned rb = (m + BAND_ROWS - 1) / BAND_ROWS, cb = (m + BAND_COLS - 1) / BAND_COLS;
       hipLaunchKernelGGL(band_z_kernel, dim3(rb, cnt), dim3(256), 0, s, g, k);
