@@ -33,6 +33,7 @@
 #include <type_traits>
 #include "elementwise.h"
 #include "gemm_mfma.h"
+#include "bf16_terms.h"
 #include "lds_dma.h"
 
 namespace shampoo {
@@ -64,6 +65,7 @@ struct SmallStepArgs {
   float a_decay, a_gain, a_bc;   // grafting state A <- a_decay A + a_gain G.^2, root of a_bc A
   float beta1, gd_scale;         // filter, and its bias correction c1
   int32_t nesterov;
+  int32_t fp32;                  // Lbar G Rbar on the float32 matrix cores
 };
 
 // sums / maxima over the workgroup in a fixed order; every thread gets the result.  red: 4 floats not in use.
@@ -75,46 +77,6 @@ __device__ __forceinline__ float sb_reduce(float v, float *red, int tid) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-typedef float sb_floatx8 __attribute__((ext_vector_type(8)));
-// x = h + l + m, eight elements (bf16_planes.h)
-struct SbTerms { bf16x8 h, l, m; };
-// two of them rounded, and what that leaves (written out: from vector conversions the compiler makes every one twice)
-__device__ __forceinline__ uint32_t sb_round2(float &x, float &y, bool left) {
-  typedef float pair __attribute__((ext_vector_type(2)));
-  typedef __bf16 bpair __attribute__((ext_vector_type(2)));
-  const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair{x, y}, bpair));
-  if (left) { x -= __uint_as_float(u << 16); y -= __uint_as_float(u & 0xffff0000u); }
-  return u;
-}
-template <bool ONE>      // ONE: x holds bf16 values
-__device__ __forceinline__ void sb_split(sb_floatx8 x, SbTerms &t) {
-  u32x4 h, l, m;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float a = x[2 * e], b = x[2 * e + 1];
-    h[e] = sb_round2(a, b, !ONE);
-    if constexpr (!ONE) { l[e] = sb_round2(a, b, true); m[e] = sb_round2(a, b, false); }
-  }
-  t.h = __builtin_bit_cast(bf16x8, h);
-  if constexpr (!ONE) { t.l = __builtin_bit_cast(bf16x8, l); t.m = __builtin_bit_cast(bf16x8, m); }
-}
-__device__ __forceinline__ floatx16 sb_mfma(const bf16x8 &a, const bf16x8 &b, const floatx16 &c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-// Element (i, k .. k + 7) of an operand in LDS, read along rows: two 16-byte reads (rows are 16-byte aligned and 4 banks
-// apart: the 16 lanes that are served at a time cover the 64 banks).
-template <int LD> __device__ __forceinline__ sb_floatx8 sb_row8(const float *Gs, int i, int k) {
-  const float4 x = *reinterpret_cast<const float4 *>(Gs + i * LD + k), y = *reinterpret_cast<const float4 *>(Gs + i * LD + k + 4);
-  return sb_floatx8{x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-}
-// (k .. k + 7, j), read down a column: eight 4-byte reads, whose two half wavefronts are 32 banks apart
-template <int LD> __device__ __forceinline__ sb_floatx8 sb_col8(const float *Gs, int k, int j) {
-  sb_floatx8 x;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = Gs[(k + e) * LD + j];
-  return x;
-}
 // A range of memory that is read and written by byte offsets; what lies past its end is read as zero and not written, so
 // that the edges of a block need no branches.
 typedef __amdgpu_buffer_rsrc_t SbRange;
@@ -125,9 +87,9 @@ __device__ __forceinline__ SbRange sb_range(const void *p, int64_t bytes) {
 __device__ __forceinline__ float sb_get(SbRange r, int at) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0)); }
 __device__ __forceinline__ void sb_put(SbRange r, int at, float x) { __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, at, 0, 0); }
 // Eight consecutive floats of a root.  Past the end of a row they are the next one's: the operand that they meet is zero there.
-__device__ __forceinline__ sb_floatx8 sb_get8(SbRange r, int at) {
+__device__ __forceinline__ floatx8 sb_get8(SbRange r, int at) {
   const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, 0), y = __builtin_amdgcn_raw_buffer_load_b128(r, at + 16, 0, 0);
-  sb_floatx8 f;
+  floatx8 f;
 #pragma unroll
   for (int e = 0; e < 4; ++e) { f[e] = __uint_as_float(x[e]); f[4 + e] = __uint_as_float(y[e]); }
   return f;
@@ -164,14 +126,7 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
 #pragma unroll
     for (int v = 0; v < 16; ++v) sum[t][v] = 0.0;
   auto operand = [&](int first, int k) {
-    return WHICH == 0 ? sb_row8<LD>(Gs, first + l32, k + 8 * khalf) : sb_col8<LD>(Gs, k + 8 * khalf, first + l32);
-  };
-  auto small_products = [&](const SbTerms &a, const SbTerms &b, floatx16 c) {
-    c = sb_mfma(a.h, b.m, c);
-    c = sb_mfma(a.m, b.h, c);
-    c = sb_mfma(a.l, b.l, c);
-    c = sb_mfma(a.h, b.l, c);
-    return sb_mfma(a.l, b.h, c);
+    return WHICH == 0 ? lds_row8<LD>(Gs, first + l32, k + 8 * khalf) : lds_col8<LD>(Gs, k + 8 * khalf, first + l32);
   };
   // 32 values of k from zero accumulators (G is zero from K on): both sets of small products, then both h h'
 #pragma unroll 1
@@ -180,22 +135,22 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
     bf16x8 ah[2], bh[2][2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      SbTerms a, b0, b1;
-      sb_split<ONE>(operand(row0, k + 16 * s), a);
-      if (I == J) b0 = a; else sb_split<ONE>(operand(col0, k + 16 * s), b0);
+      Bf16Terms a, b0, b1;
+      bf16_split<ONE>(operand(row0, k + 16 * s), a);
+      if (I == J) b0 = a; else bf16_split<ONE>(operand(col0, k + 16 * s), b0);
       ah[s] = a.h; bh[s][0] = b0.h;
-      if constexpr (!ONE) acc[0] = small_products(a, b0, acc[0]);
+      if constexpr (!ONE) acc[0] = bf16_small_products<false, false>(a, b0, acc[0]);
       if (two) {
-        if (I == J + 1) b1 = a; else sb_split<ONE>(operand(col0 + 32, k + 16 * s), b1);
+        if (I == J + 1) b1 = a; else bf16_split<ONE>(operand(col0 + 32, k + 16 * s), b1);
         bh[s][1] = b1.h;
-        if constexpr (!ONE) acc[1] = small_products(a, b1, acc[1]);
+        if constexpr (!ONE) acc[1] = bf16_small_products<false, false>(a, b1, acc[1]);
       }
     }
 #pragma unroll
-    for (int s = 0; s < 2; ++s) acc[0] = sb_mfma(ah[s], bh[s][0], acc[0]);
+    for (int s = 0; s < 2; ++s) acc[0] = bf16_mfma(ah[s], bh[s][0], acc[0]);
     if (two)
 #pragma unroll
-      for (int s = 0; s < 2; ++s) acc[1] = sb_mfma(ah[s], bh[s][1], acc[1]);
+      for (int s = 0; s < 2; ++s) acc[1] = bf16_mfma(ah[s], bh[s][1], acc[1]);
 #pragma unroll
     for (int v = 0; v < 16; ++v) sum[0][v] += (double)acc[0][v];
     if (two)
@@ -218,14 +173,6 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
 // rows 2 and 0.  Of the tiles rows that exist, the job `q` (counted among those of its kind): row, first column.
 __device__ __forceinline__ int sb_pairs(int tiles) { return tiles >= 4 ? 4 : tiles == 3 ? 2 : tiles == 2 ? 1 : 0; }
 __device__ __forceinline__ int sb_singles(int tiles) { return tiles >= 3 ? 2 : 1; }
-
-// A power of two that brings a largest element outside 2^-40 ... 2^40 to 0.5 ... 1; otherwise 1.
-__device__ __forceinline__ float sb_scale(float largest) {
-  if (!(largest > 0.f) || !(largest < 3.4e38f) || (largest >= 0x1p-40f && largest <= 0x1p40f)) return 1.f;
-  int e;
-  (void)frexpf(largest, &e);
-  return ldexpf(1.f, min(-e, 120));
-}
 
 // GT: element type of the caller's gradients; CAP: no block is larger; FILT: directions from the filtered gradient.
 // grid: one workgroup per entry of g.blocks.
@@ -313,7 +260,7 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
     ss = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
     gmax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
     fmx = fmaxf(fmaxf(red[2][0], red[2][1]), fmaxf(red[2][2], red[2][3]));
-    const float sg = sb_scale(gmax);
+    const float sg = range_scale(gmax);
 #pragma unroll
     for (int u = 0; u < GV; ++u) {
       align(gv[u]);
@@ -331,7 +278,7 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
   // ---- factor updates (Gs is read-only here): the pairs of tiles of L, those of R, then the single tiles, dealt out in turn
   {
     float *Lp = reinterpret_cast<float *>(g.ws + sbk.off_L), *Rp = reinterpret_cast<float *>(g.ws + sbk.off_R);
-    const double inv_s = 1.0 / (double)sb_scale(gmax), alpha = g.alpha_d * (inv_s * inv_s);
+    const double inv_s = 1.0 / (double)range_scale(gmax), alpha = g.alpha_d * (inv_s * inv_s);
     const int pl = sb_pairs(mt), pr = sb_pairs(nt), sl = sb_singles(mt), total = pl + pr + sl + sb_singles(nt);
     for (int q = wave; q < total; q += 4) {
       const bool two = q < pl + pr;
@@ -358,7 +305,7 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
 
 
   // ---- the filtered gradient takes the place of G; every thread reads back what it has written itself
-  const float sf = FILT ? sb_scale(fmx) : sb_scale(gmax);
+  const float sf = FILT ? range_scale(fmx) : range_scale(gmax);
   if constexpr (FILT) {
     float fv[GV][4];
 #pragma unroll
@@ -379,7 +326,7 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
   }
 
   floatx16 acc[TT][TT];
-  sb_floatx8 ring[RING][TT];
+  floatx8 ring[RING][TT];
   auto clear = [&]() {
 #pragma unroll
     for (int i = 0; i < TT; ++i)
@@ -388,21 +335,28 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   };
-  // one step of 16 values of k; the small products first.  BONE: b has one term
-  auto multiply = [&](const SbTerms (&a)[TT], const SbTerms (&b)[TT], auto bone) {
+  // one step of 16 values of k, the small products first.  BONE: b holds bf16 values
+  auto multiply = [&](const floatx8 (&x)[TT], const floatx8 (&y)[TT], auto bone) {
     constexpr bool BONE = decltype(bone)::value;
+    if (g.fp32) {                        // uniform: the caller wants the float32 matrix cores
+#pragma unroll
+      for (int i = 0; i < TT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+          if ((i == 0 || r_two) && (j == 0 || c_two)) acc[i][j] = fp32_products(x[i], y[j], acc[i][j]);
+      return;
+    }
+    Bf16Terms a[TT], b[TT];
+#pragma unroll
+    for (int i = 0; i < TT; ++i) if (i == 0 || r_two) bf16_split<false>(x[i], a[i]);
+#pragma unroll
+    for (int j = 0; j < TT; ++j) if (j == 0 || c_two) bf16_split<BONE>(y[j], b[j]);
 #pragma unroll
     for (int i = 0; i < TT; ++i)
 #pragma unroll
       for (int j = 0; j < TT; ++j)
-        if ((i == 0 || r_two) && (j == 0 || c_two)) {
-          floatx16 c = acc[i][j];
-          if constexpr (!BONE) c = sb_mfma(a[i].h, b[j].m, c);
-          c = sb_mfma(a[i].m, b[j].h, c);
-          if constexpr (!BONE) { c = sb_mfma(a[i].l, b[j].l, c); c = sb_mfma(a[i].h, b[j].l, c); }
-          c = sb_mfma(a[i].l, b[j].h, c);
-          acc[i][j] = sb_mfma(a[i].h, b[j].h, c);
-        }
+        if ((i == 0 || r_two) && (j == 0 || c_two))
+          acc[i][j] = bf16_mfma(a[i].h, b[j].h, bf16_small_products<false, BONE>(a[i], b[j], acc[i][j]));
   };
   // ---- T = c1 Lbar G: A(i, k) = Lbar[i][k] from memory, B(k, j) = G[k][j] from LDS
   const SbRange Li = sb_range(g.ws + sbk.off_Linv, (int64_t)m * m * 4), Ri = sb_range(g.ws + sbk.off_Rinv, (int64_t)n * n * 4);
@@ -425,13 +379,13 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
       for (int s = 0; s < RING; ++s) {
         const int k = k0 + 16 * s;
         if (k < m) {
-          SbTerms a[TT], b[TT];
+          floatx8 x[TT], y[TT];
 #pragma unroll
-          for (int i = 0; i < TT; ++i) if (i == 0 || r_two) sb_split<false>(ring[s][i], a[i]);
+          for (int i = 0; i < TT; ++i) x[i] = ring[s][i];
           request_l(s, k + 16 * RING);
 #pragma unroll
-          for (int j = 0; j < TT; ++j) if (j == 0 || c_two) sb_split<BF && !FILT>(sb_col8<LD>(Gs, k + 8 * khalf, c0 + 32 * j + l32), b[j]);
-          multiply(a, b, std::integral_constant<bool, BF && !FILT>());
+          for (int j = 0; j < TT; ++j) if (j == 0 || c_two) y[j] = lds_col8<LD>(Gs, k + 8 * khalf, c0 + 32 * j + l32);
+          multiply(x, y, std::integral_constant<bool, BF && !FILT>());
         }
       }
 #pragma unroll
@@ -482,13 +436,13 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
       for (int s = 0; s < RING; ++s) {
         const int k = k0 + 16 * s;
         if (k < n) {
-          SbTerms a[TT], b[TT];
+          floatx8 x[TT], y[TT];
 #pragma unroll
-          for (int j = 0; j < TT; ++j) if (j == 0 || c_two) sb_split<false>(ring[s][j], b[j]);
+          for (int j = 0; j < TT; ++j) y[j] = ring[s][j];
           request_r(s, k + 16 * RING);
 #pragma unroll
-          for (int i = 0; i < TT; ++i) if (i == 0 || r_two) sb_split<false>(sb_row8<LD>(Gs, r0 + 32 * i + l32, k + 8 * khalf), a[i]);
-          multiply(a, b, std::integral_constant<bool, false>());
+          for (int i = 0; i < TT; ++i) if (i == 0 || r_two) x[i] = lds_row8<LD>(Gs, r0 + 32 * i + l32, k + 8 * khalf);
+          multiply(x, y, std::integral_constant<bool, false>());
         }
       }
     if constexpr (TT > 1) request_w();

@@ -32,7 +32,8 @@ struct EwArgs {
   float *m_state;                // momentum state, same layout (nullptr when mu == 0)
   const float *p;                // [slot][m][n] Shampoo directions
   float *sg_partial;             // [slot][chunks]
-  float *gmax_partial;           // graft_kernel: [slot][chunks] max |G| of the chunk (nullptr: not wanted)
+  float *gmax_partial;           // graft_kernel: [slot][chunks] max |G| of the chunk, direction gradients (nullptr: not wanted)
+  float *gmax;                   // [2][blocks]: largest element of state and direction gradients; zero between steps
   const float *scale;            // [slot]
   int32_t m, n, blocks;
   EwGeom geom;
@@ -46,7 +47,7 @@ struct EwArgs {
   int32_t sgd_graft;             // P_graft = G (no grafting state) instead of AdaGrad
   int32_t same_src;              // g_table and gd_table are the same tensors
   int32_t graft_only;            // update_kernel: use -P_graft instead of scale * P
-  __device__ __forceinline__ void globals() { to_global(desc, w_table, g_table, gd_table, a_state, m_state, p, sg_partial, gmax_partial, scale); }
+  __device__ __forceinline__ void globals() { to_global(desc, w_table, g_table, gd_table, a_state, m_state, p, sg_partial, gmax_partial, gmax, scale); }
 };
 
 template <typename GT>
@@ -77,29 +78,11 @@ __device__ __forceinline__ void store_f4(float *p, bool vec, int valid, const fl
   for (int e = 0; e < 4; ++e) if (e < valid) p[e] = v[e];
 }
 
-// Four consecutive elements at any address of the element type's alignment: global loads and stores of 8 and 16 bytes
-// need no alignment of their own.
-typedef float ew_float4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint16_t ew_ushort4u __attribute__((ext_vector_type(4), aligned(2)));
-template <typename GT>
-__device__ __forceinline__ void load_u4(const GT *p, float (&v)[4]) {
-  if constexpr (sizeof(GT) == 2) {
-    const ew_ushort4u x = *reinterpret_cast<const ew_ushort4u *>(p);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32(x[e]);
-  } else {
-    const ew_float4u x = *reinterpret_cast<const ew_float4u *>(p);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = x[e];
-  }
-}
-__device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reinterpret_cast<ew_float4u *>(p) = ew_float4u{v[0], v[1], v[2], v[3]}; }
-
 // workgroups of a bucket: chunks * blocks, chunk index fastest.
 // GS / GD: element types of the state-source and direction-source gradients.
 template <typename GS, typename GD>
 __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> grp) {
-  __shared__ float red[EW_THREADS / 64];
+  __shared__ float red[2 * EW_THREADS / 64];
   int wg;
   const EwArgs g = group_pick(grp, wg);
   const int slot = wg / g.geom.chunks, chunk = wg - slot * g.geom.chunks, tid = threadIdx.x;
@@ -116,7 +99,7 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
   const int tx = tid & ((1 << lx) - 1), ty = tid >> lx, ny = EW_THREADS >> lx;
   const int r0 = chunk * g.geom.rows_per_wg;
   const int r1 = min(r0 + g.geom.rows_per_wg, g.m);
-  float ss = 0.f, gmax = 0.f;
+  float ss = 0.f, gmax = 0.f, smax = 0.f;
   if (vec && g.same_src && !g.sgd_graft) {
     // The common case, four column passes at a time, every load requested before the first store.
     constexpr int U = 4;
@@ -168,7 +151,10 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
         for (int e = 0; e < 4; ++e) if (e < valid) ss += dv[e] * dv[e];
         continue;
       }
-      if (!g.same_src) load_g4<GS>(gp + (int64_t)i * ld + j, vec, valid, gv);
+      if (!g.same_src) {
+        load_g4<GS>(gp + (int64_t)i * ld + j, vec, valid, gv);
+        smax = fmaxf(fmaxf(smax, fmaxf(fabsf(gv[0]), fabsf(gv[1]))), fmaxf(fabsf(gv[2]), fabsf(gv[3])));
+      }
       load_f4(ap + (int64_t)i * ld + j, vec, valid, av);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -183,13 +169,18 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
   if (tid == 0) g.sg_partial[(int64_t)slot * g.geom.chunks + chunk] = (red[0] + red[1]) + (red[2] + red[3]);
-  if (g.gmax_partial) {       // uniform
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, off, 64));
-    __syncthreads();
-    if ((tid & 63) == 0) red[tid >> 6] = gmax;
-    __syncthreads();
-    if (tid == 0) g.gmax_partial[(int64_t)slot * g.geom.chunks + chunk] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  for (int off = 32; off > 0; off >>= 1) { gmax = fmaxf(gmax, __shfl_xor(gmax, off, 64)); smax = fmaxf(smax, __shfl_xor(smax, off, 64)); }
+  __syncthreads();
+  if ((tid & 63) == 0) { red[tid >> 6] = gmax; red[EW_THREADS / 64 + (tid >> 6)] = smax; }
+  __syncthreads();
+  if (tid == 0) {
+    gmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    smax = g.same_src ? gmax : fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+    if (g.gmax_partial) g.gmax_partial[(int64_t)slot * g.geom.chunks + chunk] = gmax;
+    // not negative, so that their bits order like integers and the result does not depend on the order
+    atomicMax(reinterpret_cast<int *>(g.gmax + slot), __float_as_int(smax));
+    atomicMax(reinterpret_cast<int *>(g.gmax + g.blocks + slot), __float_as_int(gmax));
   }
 }
 
@@ -247,6 +238,7 @@ __global__ __launch_bounds__(EW_THREADS) void update_kernel(const Group<EwArgs> 
   const int r0 = chunk * g.geom.rows_per_wg;
   const int r1 = min(r0 + g.geom.rows_per_wg, g.m);
   const float sc = g.graft_only ? 0.f : g.scale[slot];
+  if (chunk == 0 && tid < 2) g.gmax[tid * g.blocks + slot] = 0.f;      // read by all products of the step by now
   if (vec && !g.graft_only && mp) {
     // The common case, four column passes at a time: all twelve 16-byte loads of a thread are
     // requested before the first store (a store between two loads would make the second one

@@ -1,12 +1,18 @@
-// Batched fp32 GEMM / SYRK on the CDNA4 matrix cores (v_mfma_f32_32x32x2_f32).
+// Batched float32 GEMM / SYRK on the CDNA4 matrix cores, for operands as they lie in memory (any shape, stride and
+// alignment; the products on planes made beforehand are gemm_f16x2.h and syrk_bf16.h).
 //
 // One workgroup (256 threads = 4 wavefronts of 64) computes a 128 x 128 tile of
 // C = alpha * A * B (+ beta * C).  Each wavefront owns a 64 x 64 quadrant as
-// 2 x 2 MFMA tiles of 32 x 32.  Operand tiles are staged through LDS in
-// k-major order ([k][row]), so that the 64 lanes of an MFMA operand read two
-// rows of 32 consecutive floats, and are double-buffered against the global
-// loads of the next k-slab.  Operands may be float32 or bfloat16 in memory
-// (bf16 is widened exactly on the way into LDS); accumulation is float32.
+// 2 x 2 MFMA tiles of 32 x 32; tiles that hold nothing (ragged edges, above the diagonal) are passed over.  Slabs of
+// 32 values of k go through LDS as float32, laid out as they are read from memory ([row][k] or [k][row]: 16-byte writes
+// either way), double-buffered against the global loads of the next slab.  Operands may be float32 or bfloat16 in memory.
+//
+// A product is six v_mfma_f32_32x32x16_bf16 of operands split into three bf16 terms on the way from LDS (bf16_terms.h):
+// 192 cycles for 16 values of k, 512 on the float32 matrix cores, and 44 vector instructions per operand and step for the
+// splitting, which run beside them; a bf16 operand is one term and leaves three products, or one.  The five small
+// products have accumulators of their own, so that only h h' is rounded at full size.  FP32 keeps
+// v_mfma_f32_32x32x2_f32 for callers that ask for it.
+// GEMM_FIGURES
 //
 // The operands of the Shampoo step (Sec. 2.3, 3.1.1 of the paper) map onto it as
 //   L <- beta2 L + (1-beta2) G G^T   A(i,k) = G[i][k]   B(k,j) = G[j][k]   (both k-contiguous)
@@ -17,16 +23,18 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "bf16_terms.h"
 #include "group.h"
 
 namespace shampoo {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int BM = 128;
 constexpr int BN = 128;
-constexpr int BK = 16;          // k-slab depth (multiple of 8)
-constexpr int LDS_PAD = 4;
+constexpr int BK = 32;          // k-slab depth
+constexpr int GEMM_LDK = BK + 4;      // rows of a slab [row][k], and [k][row]: 16-byte aligned, four banks apart
+constexpr int GEMM_LDR = BM + 4;
+constexpr int GEMM_SLAB = BM * GEMM_LDK;     // floats; the larger of the two layouts
+static_assert(BK * GEMM_LDR <= GEMM_SLAB, "slab");
 constexpr int LOAD_PASSES = BK / 8;          // 128 x BK floats = 256 threads x LOAD_PASSES float4
 constexpr int GEMM_THREADS = 256;
 constexpr int NUM_XCD = 8;
@@ -74,7 +82,11 @@ struct GemmArgs {
   int32_t batch;
   int32_t ksplit, krange;       // EPI_SYRK, ksplit > 1: batch entry b is the range b % ksplit, of krange values of k, of operand b / ksplit;
   double *c64;                  // its plain sum goes here, in float64 like c (ACC64 kernels)
-  __device__ __forceinline__ void globals() { to_global(a.base, b.base, c, desc, ptr_table, kscale, skip, norm_partial, c64); }
+  const float *gmax;            // largest element of a block of gradients, per gmax_per operand entries (nullptr: none):
+  int32_t gmax_per;             // A and B are multiplied by range_scale of it where scale_a and scale_b say so, and
+  int32_t scale_a, scale_b;     // the result is divided by its power unscale
+  int32_t unscale;
+  __device__ __forceinline__ void globals() { to_global(a.base, b.base, c, desc, ptr_table, kscale, skip, norm_partial, c64, gmax); }
 };
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
@@ -100,52 +112,92 @@ template <> struct Elem<uint16_t> {
   static __device__ __forceinline__ float load1(const uint16_t *p) { return bf16_to_f32(*p); }
 };
 
+// Four consecutive elements at any address of the element type's alignment: global loads and stores of 8 and 16 bytes
+// need no alignment of their own.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t ushort4u __attribute__((ext_vector_type(4), aligned(2)));
+template <typename GT>
+__device__ __forceinline__ void load_u4(const GT *p, float (&v)[4]) {
+  if constexpr (sizeof(GT) == 2) {
+    const ushort4u x = *reinterpret_cast<const ushort4u *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32(x[e]);
+  } else {
+    const float4u x = *reinterpret_cast<const float4u *>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = x[e];
+  }
+}
+__device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reinterpret_cast<float4u *>(p) = float4u{v[0], v[1], v[2], v[3]}; }
+
 // Fetches one 128 x BK operand slab into registers (4 * LOAD_PASSES floats per thread)
-// and later writes it into LDS in [k][row] order.
+// and later writes it into LDS as [row][k] (K_CONTIG) or [k][row].  Whatever is read lies inside the matrix: rows past its
+// last one read that again (what they reach is never stored), values of k past the end are zero, and of four rows that
+// cross the end the last four of the matrix are read and moved into place.
 template <int ORIENT, typename T>
 struct TileLoader {
   const T *ptr;     // operand origin for this batch entry, already offset to the tile's first row
   int ld;
   int rows_left;    // valid rows from the tile's first row
   int K;
-  bool fast;        // whole tile in range and 4-element vectors aligned
+  int lane_row;     // ROW_CONTIG: the first of the four rows that are read
+  int back;         // ROW_CONTIG: how far they lie in front of their place
   float r[LOAD_PASSES][4];
 
-  __device__ __forceinline__ void init(const T *p, int ld_, int rows_left_, int K_) {
+  __device__ __forceinline__ void init(const T *p, int ld_, int rows_left_, int K_, int tid) {
     ptr = p; ld = ld_; rows_left = rows_left_; K = K_;
-    const bool aligned = ((ld_ & 3) == 0) && ((reinterpret_cast<uintptr_t>(p) & (4 * sizeof(T) - 1)) == 0);
-    fast = aligned && rows_left_ >= 128 && (K_ % BK) == 0;
+    const int r4 = (tid & 31) * 4;
+    lane_row = min(r4, max(rows_left - 4, 0));
+    back = r4 < rows_left ? r4 - lane_row : 0;
   }
 
   __device__ __forceinline__ void fetch(int k0, int tid) {
+    const bool whole = k0 + BK <= K;             // uniform
     if (ORIENT == K_CONTIG) {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;   // threads per row, rows per pass
-      const int row = tid / TPR, kq = (tid % TPR) * 4;
+      const int row = tid / TPR, kq = k0 + (tid % TPR) * 4;
 #pragma unroll
       for (int h = 0; h < LOAD_PASSES; ++h) {
-        const int rr = row + RPP * h;
-        if (fast) {
-          Elem<T>::load4(ptr + (int64_t)rr * ld + k0 + kq, r[h]);
+        const T *p = ptr + (int64_t)min(row + RPP * h, rows_left - 1) * ld + kq;
+        if (whole) {
+          load_u4<T>(p, r[h]);
         } else {
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            r[h][j] = (rr < rows_left && k0 + kq + j < K) ? Elem<T>::load1(ptr + (int64_t)rr * ld + k0 + kq + j) : 0.f;
+          for (int j = 0; j < 4; ++j) r[h][j] = kq + j < K ? Elem<T>::load1(p + j) : 0.f;
         }
       }
     } else {
-      const int kk = tid >> 5, r4 = (tid & 31) * 4;
+      const int kk = k0 + (tid >> 5);
+      if (rows_left >= 4) {                      // uniform
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h) {
-        const int k = k0 + kk + 8 * h;
-        if (fast) {
-          Elem<T>::load4(ptr + (int64_t)k * ld + r4, r[h]);
-        } else {
+        for (int h = 0; h < LOAD_PASSES; ++h) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) r[h][j] = 0.f;
+          if (whole || kk + 8 * h < K) load_u4<T>(ptr + (int64_t)(kk + 8 * h) * ld + lane_row, r[h]);
+        }
+        if (rows_left < BM && (rows_left & 3)) { // uniform
+#pragma unroll
+          for (int h = 0; h < LOAD_PASSES; ++h) {
+            if (back & 1) { r[h][0] = r[h][1]; r[h][1] = r[h][2]; r[h][2] = r[h][3]; }
+            if (back & 2) { r[h][0] = r[h][2]; r[h][1] = r[h][3]; }
+          }
+        }
+      } else {
+        const int r4 = (tid & 31) * 4;
+#pragma unroll
+        for (int h = 0; h < LOAD_PASSES; ++h)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            r[h][j] = (k < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)k * ld + r4 + j) : 0.f;
-        }
+            r[h][j] = (kk + 8 * h < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)(kk + 8 * h) * ld + r4 + j) : 0.f;
       }
     }
+  }
+
+  __device__ __forceinline__ void multiply(float s) {
+#pragma unroll
+    for (int h = 0; h < LOAD_PASSES; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[h][j] *= s;
   }
 
   // kscale: optional per-k multiplier (already offset to this batch entry), k0 = slab origin
@@ -170,20 +222,24 @@ struct TileLoader {
     }
   }
 
-  __device__ __forceinline__ void store(float (*lds)[BM + LDS_PAD], int tid) const {
+  __device__ __forceinline__ void store(float *lds, int tid) const {
     if (ORIENT == K_CONTIG) {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;
       const int row = tid / TPR, kq = (tid % TPR) * 4;
 #pragma unroll
       for (int h = 0; h < LOAD_PASSES; ++h)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) lds[kq + j][row + RPP * h] = r[h][j];
+        *reinterpret_cast<float4 *>(lds + (row + RPP * h) * GEMM_LDK + kq) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
     } else {
       const int kk = tid >> 5, r4 = (tid & 31) * 4;
 #pragma unroll
       for (int h = 0; h < LOAD_PASSES; ++h)
-        *reinterpret_cast<float4 *>(&lds[kk + 8 * h][r4]) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+        *reinterpret_cast<float4 *>(lds + (kk + 8 * h) * GEMM_LDR + r4) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
     }
+  }
+
+  // the MFMA operand of 32 rows: row (of the lane), values k ... k + 7 of the slab
+  static __device__ __forceinline__ floatx8 operand(const float *lds, int row, int k) {
+    return ORIENT == K_CONTIG ? lds_row8<GEMM_LDK>(lds, row, k) : lds_col8<GEMM_LDR>(lds, k, row);
   }
 };
 
@@ -207,16 +263,17 @@ __device__ __forceinline__ const T *operand_ptr(const Operand &o, const BlockDes
   return reinterpret_cast<const T *>(o.base) + (int64_t)b * o.batch_stride;
 }
 
-// ACC64 = N > 0: after every N k-slabs of 16 the float32 MFMA accumulators are added
-// into float64 registers and cleared, and the epilogue (alpha * acc + beta * C) is
+// ACC64: the products of a slab of 32 values of k start from zero accumulators, the small ones first (two roundings of full
+// size), and are added into float64 registers; the epilogue (alpha * acc + beta * C) is
 // evaluated in float64 before the single rounding to float32.  Used for the
 // factor updates: the first root refresh sees L = G G^T of a single gradient,
 // whose condition number is the square of G's, and a plain float32 running sum
 // over k would perturb its small eigenvalues by more than the parity budget.
-template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, int ACC64 = 0>
+template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, bool ACC64 = false, bool FP32 = false>
 __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
-  __shared__ __align__(16) float As[2][BK][BM + LDS_PAD];
-  __shared__ __align__(16) float Bs[2][BK][BN + LDS_PAD];
+  static_assert(!(ACC64 && FP32), "float64 sums: bf16 terms");
+  __shared__ __align__(16) float As[2][GEMM_SLAB];
+  __shared__ __align__(16) float Bs[2][GEMM_SLAB];
   __shared__ float red[4];
 
   int wg;
@@ -242,7 +299,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int row0 = ti * BM, col0 = tj * BN;
 
@@ -260,74 +317,127 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
   }
   TileLoader<AO, TA> la;
   TileLoader<BO, TB> lb;
-  la.init(pa + (AO == K_CONTIG ? (int64_t)row0 * lda : (int64_t)row0), lda, g.M - row0, K);
-  lb.init(pb + (BO == K_CONTIG ? (int64_t)col0 * ldb : (int64_t)col0), ldb, g.N - col0, K);
+  la.init(pa + (AO == K_CONTIG ? (int64_t)row0 * lda : (int64_t)row0), lda, g.M - row0, K, tid);
+  lb.init(pb + (BO == K_CONTIG ? (int64_t)col0 * ldb : (int64_t)col0), ldb, g.N - col0, K, tid);
   const float *ks = KSCALE ? g.kscale + (int64_t)b * g.kscale_stride : nullptr;
+  const float sg = g.gmax ? range_scale(g.gmax[entry / g.gmax_per]) : 1.f;
+  // which of this wavefront's 2 x 2 tiles hold part of the result
+  bool on[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = wm * 64 + 32 * i, c = wn * 64 + 32 * j;
+      on[i][j] = row0 + r < g.M && col0 + c < g.N && !(EPI == EPI_SYRK && ti == tj && c > r);
+    }
 
-  floatx16 acc[2][2];
+  floatx16 acc[2][2], rest[ACC64 || FP32 ? 1 : 2][ACC64 || FP32 ? 1 : 2];
+  double acc64[ACC64 ? 2 : 1][ACC64 ? 2 : 1][ACC64 ? 16 : 1];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  double acc64[ACC64 ? 2 : 1][ACC64 ? 2 : 1][ACC64 ? 16 : 1];
-  if (ACC64) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc64[ACC64 ? i : 0][ACC64 ? j : 0][ACC64 ? v : 0] = 0.0;
-  }
+      for (int v = 0; v < 16; ++v) {
+        acc[i][j][v] = 0.f;
+        if constexpr (!ACC64 && !FP32) rest[i][j][v] = 0.f;
+        if constexpr (ACC64) acc64[i][j][v] = 0.0;
+      }
 
   const int nk = (K + BK - 1) / BK;
-  la.fetch(0, tid);
-  lb.fetch(0, tid);
-  if (KSCALE) la.scale(ks, 0, tid);
-  la.store(As[0], tid);
-  lb.store(Bs[0], tid);
+  auto fetch = [&](int k0) {
+    la.fetch(k0, tid);
+    lb.fetch(k0, tid);
+  };
+  auto store = [&](int stage, int k0) {
+    if (sg != 1.f) {                     // uniform
+      if (g.scale_a) la.multiply(sg);
+      if (g.scale_b) lb.multiply(sg);
+    }
+    if (KSCALE) la.scale(ks, k0, tid);
+    la.store(As[stage], tid);
+    lb.store(Bs[stage], tid);
+  };
+  fetch(0);
+  store(0, 0);
   __syncthreads();
 
   const int arow = wm * 64 + (lane & 31);
   const int bcol = wn * 64 + (lane & 31);
   const int khalf = lane >> 5;
+  constexpr bool AONE = sizeof(TA) == 2, BONE = sizeof(TB) == 2;
   for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) {
-      la.fetch((kt + 1) * BK, tid);
-      lb.fetch((kt + 1) * BK, tid);
-    }
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const float a0 = As[cur][kk + khalf][arow];
-      const float a1 = As[cur][kk + khalf][arow + 32];
-      const float b0 = Bs[cur][kk + khalf][bcol];
-      const float b1 = Bs[cur][kk + khalf][bcol + 32];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    if (ACC64 && ((kt + 1) % (ACC64 ? ACC64 : 1) == 0 || kt + 1 == nk)) {
+    const float *as = As[kt & 1], *bs = Bs[kt & 1];
+    if (kt + 1 < nk) fetch((kt + 1) * BK);
+    auto operand_a = [&](int i, int s) { return TileLoader<AO, TA>::operand(as, arow + 32 * i, 16 * s + 8 * khalf); };
+    auto operand_b = [&](int j, int s) { return TileLoader<BO, TB>::operand(bs, bcol + 32 * j, 16 * s + 8 * khalf); };
+    if constexpr (ACC64) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
+        if (on[i][0] || on[i][1]) {
+          Bf16Terms a[2];
+          bf16_split<AONE>(operand_a(i, 0), a[0]);
+          bf16_split<AONE>(operand_a(i, 1), a[1]);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < 2; ++j)
+            if (on[i][j]) {
+              floatx16 c = {};
+              Bf16Terms t[2];
+              bf16_split<BONE>(operand_b(j, 0), t[0]);
+              c = bf16_small_products<AONE, BONE>(a[0], t[0], c);
+              bf16_split<BONE>(operand_b(j, 1), t[1]);
+              c = bf16_small_products<AONE, BONE>(a[1], t[1], c);
+              c = bf16_mfma(a[0].h, t[0].h, c);
+              c = bf16_mfma(a[1].h, t[1].h, c);
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            acc64[ACC64 ? i : 0][ACC64 ? j : 0][ACC64 ? v : 0] += (double)acc[i][j][v];
-            acc[i][j][v] = 0.f;
+              for (int v = 0; v < 16; ++v) acc64[i][j][v] += (double)c[v];
+            }
+        }
+    } else {
+#pragma unroll 1
+      for (int s = 0; s < 2; ++s) {
+        if constexpr (FP32) {
+          floatx8 a[2], t[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) { a[i] = operand_a(i, s); t[i] = operand_b(i, s); }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              if (on[i][j]) acc[i][j] = fp32_products(a[i], t[j], acc[i][j]);
+        } else {
+          Bf16Terms a[2], t[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            if (on[i][0] || on[i][1]) bf16_split<AONE>(operand_a(i, s), a[i]);
+            if (on[0][i] || on[1][i]) bf16_split<BONE>(operand_b(i, s), t[i]);
           }
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              if (on[i][j]) {
+                rest[i][j] = bf16_small_products<AONE, BONE>(a[i], t[j], rest[i][j]);
+                acc[i][j] = bf16_mfma(a[i].h, t[j].h, acc[i][j]);
+              }
+        }
+      }
     }
-    if (kt + 1 < nk) {
-      if (KSCALE) la.scale(ks, (kt + 1) * BK, tid);
-      la.store(As[cur ^ 1], tid);
-      lb.store(Bs[cur ^ 1], tid);
-    }
+    if (kt + 1 < nk) store((kt + 1) & 1, (kt + 1) * BK);
     __syncthreads();
   }
+  if constexpr (!ACC64 && !FP32)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] += rest[i][j][v];
+  // s is up to 2^120, its square in float64
+  const float inv_s = 1.f / sg;
+  const double unscale = g.unscale == 2 ? (double)inv_s * (double)inv_s : g.unscale == 1 ? (double)inv_s : 1.0;
+  const double alpha_d = g.alpha_d * unscale;
+  const float alpha = g.unscale ? g.alpha * inv_s : g.alpha;
 
   // ---- epilogue.  Accumulator element v of MFMA tile (mi, ni) is
   //      row = wm*64 + mi*32 + 8*(v/4) + 4*(lane/32) + v%4, col = wn*64 + ni*32 + lane%32.
@@ -357,8 +467,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = ibase + e;
-          float v = ACC64 && EPI != EPI_SYRK ? (float)(g.alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0])
-                                             : g.alpha * acc[mi][ni][4 * q + e];
+          float v = ACC64 && EPI != EPI_SYRK ? (float)(alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0])
+                                             : alpha * acc[mi][ni][4 * q + e];
           if (i < g.M && j < g.N) {
             if (EPI == EPI_SYRK) {
               // only the lower triangle is computed; its mirror image is written with the
@@ -367,12 +477,12 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
                 const float o = old[EPI == EPI_SYRK ? 4 * q + e : 0];
                 if (ACC64 && g.ksplit > 1) {
                   double *c64 = g.c64 + (int64_t)b * g.c_batch_stride;
-                  const double sum = acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0];
+                  const double sum = unscale * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0];
                   c64[(int64_t)i * ldc + j] = sum;
                   if (j < i) c64[(int64_t)j * ldc + i] = sum;
                   continue;
                 }
-                if (ACC64) v = (float)(g.alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0] + g.beta_d * (double)o);
+                if (ACC64) v = (float)(alpha_d * acc64[ACC64 ? mi : 0][ACC64 ? ni : 0][ACC64 ? 4 * q + e : 0] + g.beta_d * (double)o);
                 else v += g.beta * o;
                 c[(int64_t)i * ldc + j] = v;
                 if (j < i) c[(int64_t)j * ldc + i] = v;

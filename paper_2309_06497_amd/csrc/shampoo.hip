@@ -94,6 +94,7 @@ struct Bucket {
   // plane_chunk blocks at a time: cols, the transpose, and behind it rows, the block as it lies, or T = Lbar G
   bool three = false, split_factor = false;
   int32_t plane_chunk = 0;
+  size_t off_gmax = 0;            // [2][count]: largest |element| of a block's gradients (factors, directions), zero between steps
   size_t off_t = 0, off_t2 = 0;   // this bucket's part of the scratch arrays T and T2
   int32_t set = 0;                // buckets of a set are worked on together (their parts do not overlap)
   EwGeom geom;
@@ -512,7 +513,7 @@ template <typename Args> struct Batch {
   }
 };
 
-template <int AO, int BO, typename TA, typename TB, int EPI, bool KS, int ACC64 = 0>
+template <int AO, int BO, typename TA, typename TB, int EPI, bool KS, bool ACC64 = false>
 int launch_gemm(const GemmArgs &g, hipStream_t s) {
   Batch<GemmArgs> one(gemm_mfma_kernel<AO, BO, TA, TB, EPI, KS, ACC64>, GEMM_THREADS, s);
   if (const int rc = one.add(g, (int64_t)g.tiles * g.batch)) return rc;
@@ -787,11 +788,10 @@ struct BandSolve {
     const int np = g.np, r0 = (BAND_GROUP * q + 1) * BAND, tiles = (np + BM - 1) / BM;
     float *p = band_p(g);
     const int64_t pstride = band_p_stride(g);
-    // The sums are what these products lose accuracy by: those of 32 values of k (Y: 16) go into float64.  Error of
+    // The sums are what these products lose accuracy by: those of 32 values of k go into float64.  Error of
     // the root of a factor of one gradient at n = 160, 256, 1024: 1.4e-6, 1.4e-6, 1.9e-6 with float32 sums but in Z, 4.8e-7,
-    // 4.8e-7, 6.2e-7 so; block Jacobi 8.8e-7, 1.0e-6, 3.0e-6.  The update of F moves the root by a tenth of that and
-    // costs 4.5 % of the time of 64 matrices of 1024: float64 where the margin to Jacobi is small.
-    constexpr int FLUSH = 2, FLUSH_Y = 1;
+    // 4.8e-7, 6.2e-7 so; block Jacobi 8.8e-7, 1.0e-6, 3.0e-6.  The update of F moves the root by a tenth of that:
+    // float64 where the margin to Jacobi is small.
     int rc;
     hipLaunchKernelGGL(band_stage_kernel<false>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
     GemmArgs z{};                        // Z = F V
@@ -800,14 +800,14 @@ struct BandSolve {
     z.c = p; z.c_batch_stride = pstride; z.ldc = BAND_PLD;
     z.M = np; z.N = BAND_GW; z.K = np - r0; z.alpha_d = 1.0; z.skip = g.skip;
     z.tiles_m = z.tiles = tiles; z.tiles_n = 1; z.batch = cnt;
-    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, FLUSH>(z, s))) return rc;
+    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>(z, s))) return rc;
     hipLaunchKernelGGL(band_s_kernel, dim3(cnt), dim3(1024), 0, s, g, q);
     // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them
     GemmArgs y = z;
     y.a = Operand{p, pstride, BAND_PLD, 0};
     y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
     y.K = 2 * BAND_GW;
-    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, FLUSH_Y>(y, s))) return rc;
+    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>(y, s))) return rc;
     hipLaunchKernelGGL(band_stage_kernel<true>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
     GemmArgs u = z;                      // F <- F - [Y V] [V Y]^T; V has no rows in front of r0
     u.a = y.a;
@@ -815,7 +815,7 @@ struct BandSolve {
     u.c = g.f; u.c_batch_stride = (int64_t)np * np * 2; u.ldc = np;
     u.N = np; u.K = 2 * BAND_GW; u.alpha = -1.f; u.beta = 1.f; u.alpha_d = -1.0; u.beta_d = 1.0;
     u.tiles_n = tiles; u.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; u.tiles = tiles * (tiles + 1) / 2 - u.tile0;
-    if (np <= 512) rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>(u, s);
+    if (np <= 512) rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>(u, s);
     else rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(u, s);
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
@@ -1176,6 +1176,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_sshp = take(B * ssh_parts * 4);
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
+    b.off_gmax = take(B * 8);
     b.split_factor = b.three && !use_b1;   // the directions' gradient feeds the factors too
     // float32 or two fp16 planes; tensor blocks: float64 sums of the ranges of k of two dimensions (split_gram), and float32
     // ones of the last
@@ -1402,9 +1403,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   // EMA weights from the float32 beta2 the caller gave, evaluated in float64
   const double alpha = c.beta2 < 1.f ? 1.0 - (double)c.beta2 : 1.0;
   const double beta = c.beta2 < 1.f ? (double)c.beta2 : 1.0;
-  // k-slabs between float64 flushes of the factor accumulators (flushing every 4 slabs
-  // measured 3x larger errors in the stale-root directions, for a 5 % gain)
-  constexpr int FLUSH = 1;
   const float wd_l2 = o->use_l2 ? c.weight_decay : 0.f;
   const float wd_dec = (c.weight_decay > 0.f && c.use_decoupled_weight_decay) ? c.weight_decay : 0.f;
   const int sgd = c.grafting_type == SHAMPOO_GRAFT_SGD ? 1 : 0;
@@ -1482,6 +1480,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     f.graft_eps = c.graft_epsilon; f.mu = c.momentum; f.lr = lr; f.wd_decoupled = wd_dec;
     f.nesterov = c.use_nesterov ? 1 : 0;
     f.a_decay = a_decay; f.a_gain = a_gain; f.a_bc = a_bc; f.beta1 = c.beta1; f.gd_scale = c1;
+    f.fp32 = c.precond_matrix_cores == SHAMPOO_MATRIX_CORES_FP32 ? 1 : 0;
     const dim3 grid((unsigned)o->n_small), block(SB_THREADS);
     constexpr bool FILT_ONLY = sizeof(GT) == 2 && sizeof(GD) == 4;   // bf16 gradients with float directions are filtered
     if (FILT_ONLY || Gf) {
@@ -1499,6 +1498,14 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   auto bucket_t = [&](const Bucket &b) { return reinterpret_cast<float *>(ws + o->off_T + b.off_t); };
   // Tensor blocks: the Gram matrix of an unfolding in ranges of k (gram_split.h), whose sums go through `sums` in float64, as
   // the one sum is held: it has room for m n of them per block of the bucket.
+  // products with a block's gradients: the powers of two that keep their small terms from underflowing
+  auto scale_factor = [&](const Bucket &b, GemmArgs &g, int per) {
+    g.gmax = reinterpret_cast<const float *>(ws + b.off_gmax); g.gmax_per = per; g.scale_a = g.scale_b = 1; g.unscale = 2;
+  };
+  auto scale_direction = [&](const Bucket &b, GemmArgs &g, bool gradient, bool result) {
+    g.gmax = reinterpret_cast<const float *>(ws + b.off_gmax) + b.count; g.gmax_per = 1;
+    g.scale_b = gradient ? 1 : 0; g.unscale = result ? 1 : 0;
+  };
   auto split_gram = [&](const Bucket &b, GemmArgs &g, double *sums) {
     const GramSplit sp = gram_split(g.K, (int64_t)b.m * b.n / ((int64_t)g.M * g.M), (int64_t)g.tiles * g.batch, BK);
     if (sp.ranges <= 1) return 1;
@@ -1544,6 +1551,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   auto fill_ew = [&](EwArgs &e, const Bucket &b) {
     e.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
     e.m = b.m; e.n = b.n; e.blocks = b.count; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
+    e.gmax = reinterpret_cast<float *>(ws + b.off_gmax);
     e.sgd_graft = sgd; e.gd_scale = c1; e.a_decay = a_decay; e.a_gain = a_gain; e.a_bc = a_bc;
   };
   // the buckets of a set that go stage by stage
@@ -1600,8 +1608,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       Batch<SyrkBf16Args> plain(syrk_bf16_kernel<false, false>, GEMM_THREADS, s), plain64(syrk_bf16_kernel<false, true>, GEMM_THREADS, s),
           half(syrk_bf16_kernel<true, false>, GEMM_THREADS, s), half64(syrk_bf16_kernel<true, true>, GEMM_THREADS, s),
           split(syrk_bf16_kernel<false, true, true>, GEMM_THREADS, s);
-      Batch<GemmArgs> left(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
-          right(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s);
+      Batch<GemmArgs> left(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s),
+          right(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s);
       for (Bucket *bp : todo) {
         Bucket &b = *bp;
         const size_t index = &b - p.buckets.data();
@@ -1656,6 +1664,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           g.a.from_table = 1; g.b.from_table = 1;
           g.desc = desc; g.ptr_table = gs_tab;
           g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
+          scale_factor(b, g, 1);
           DiagFactorArgs df{};
           df.desc = desc; df.g_table = gs_tab; df.a = beta; df.b = alpha; df.m = b.m; df.n = b.n;
           if (b.diagL) {
@@ -1695,9 +1704,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     // two indices swapped, d_k x (pre post).  gram_reduce_kernel adds the ranges up in float64 and applies the moving average.
     for (int mid = 0; mid < 2; ++mid) {
       Batch<PermuteArgs> swaps(permute_12_kernel<GS>, 256, s);
-      Batch<GemmArgs> first(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
-          middle(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s),
-          last(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, FLUSH>, GEMM_THREADS, s);
+      Batch<GemmArgs> first(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s),
+          middle(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>, GEMM_THREADS, s),
+          last(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s);
       Batch<GramNarrowArgs> narrow(gram_narrow_kernel<GS>, 256, s);
       Batch<GramReduceArgs> reduce64(gram_reduce_kernel<double>, 256, s), reduce32(gram_reduce_kernel<float>, 256, s);
       for (Bucket *bp : todo) {
@@ -1710,6 +1719,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         float *sums_r = reinterpret_cast<float *>(sums_m + mn * b.count), *swapped = reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2);
         GemmArgs g{};
         g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
+        scale_factor(b, g, 1);
         if (mid == 0) {
           o->upper_stale[&b - p.buckets.data()] = UPPER_FRESH;
           g.a.from_table = 1; g.b.from_table = 1; g.desc = desc; g.ptr_table = gs_tab;
@@ -1729,6 +1739,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             } else {
               GemmArgs r = g;
               r.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc3); r.ksplit = 0; r.c64 = nullptr;
+              scale_factor(b, r, b.split3);
               r.c = sums_r; r.c_batch_stride = (int64_t)dl * dl; r.ldc = dl;
               r.M = dl; r.N = dl; r.K = (b.m / b.split3) * inner;
               r.alpha = 1.f; r.beta = 0.f; r.alpha_d = 1.0; r.beta_d = 0.0; r.batch = b.count * b.split3;
@@ -1750,6 +1761,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           h.alpha = (float)alpha; h.beta = (float)beta; h.alpha_d = alpha; h.beta_d = beta; h.batch = b.count;
           h.c = reinterpret_cast<float *>(ws + b.off_mid[mid]); h.c_batch_stride = (int64_t)dk * dk; h.ldc = dk;
           h.M = dk; h.N = dk; h.K = pre * post;
+          scale_factor(b, h, 1);
           h.tiles_m = h.tiles_n = (dk + BM - 1) / BM; h.tiles = h.tiles_m * (h.tiles_m + 1) / 2;
           const int sp = split_gram(b, h, sums_m);
           if ((rc = middle.add(h, (int64_t)h.tiles * h.batch))) return rc;
@@ -1869,14 +1881,19 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       // T = Lbar G, then P = T Rbar with partial sums of squares
       Batch<GemmX2Args> tall1(gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>, 256, s), wide1(gemm_f16x2_kernel<128, 64, THREE ? 3 : 1, X2_STORE_SPLIT>, 256, s),
           tall2(gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>, 256, s), wide2(gemm_f16x2_kernel<128, 64, THREE ? 3 : 2, X2_STORE_NORM>, 256, s);
-      Batch<GemmArgs> first(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>, GEMM_THREADS, s),
-          only(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false>, GEMM_THREADS, s),
-          second(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>, GEMM_THREADS, s);
+      const bool fp32 = c.precond_matrix_cores == SHAMPOO_MATRIX_CORES_FP32;
+      Batch<GemmArgs> first(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false, false, true>
+                                 : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>, GEMM_THREADS, s),
+          only(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false, false, true>
+                    : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false>, GEMM_THREADS, s),
+          second(fp32 ? gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false, false, true>
+                      : gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>, GEMM_THREADS, s);
       auto gemm_wgs = [](const GemmArgs &g) { return (int64_t)g.tiles * g.batch; };
       auto x2_wgs = [](const GemmX2Args &g) { return (int64_t)g.tiles_m * g.tiles_n * g.batch; };
       // a block of m x n times its left root, and the other way round
-      auto left_product = [&](const Bucket &b, float *out) {
+      auto left_product = [&](const Bucket &b, float *out, bool result) {
         GemmArgs g{};
+        scale_direction(b, g, true, result);
         // (Lbar symmetric: A(i,k) read as Lbar[k][i], contiguous in i)
         g.a.base = ws + b.off_Linv; g.a.batch_stride = (int64_t)b.m * b.m; g.a.ld = b.m;
         g.b.from_table = 1; g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); g.ptr_table = gd_tab;
@@ -1885,8 +1902,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         g.tiles_m = b.tiles_m; g.tiles_n = b.tiles_n; g.tiles = b.tiles_m * b.tiles_n; g.batch = b.count;
         return g;
       };
-      auto right_product = [&](const Bucket &b, const float *in) {
+      auto right_product = [&](const Bucket &b, const float *in, bool scaled) {
         GemmArgs h{};
+        if (scaled) scale_direction(b, h, false, true);
         h.a.base = in; h.a.batch_stride = (int64_t)b.m * b.n; h.a.ld = b.n;
         h.b.base = ws + b.off_Rinv; h.b.batch_stride = (int64_t)b.n * b.n; h.b.ld = b.n;
         h.c = reinterpret_cast<float *>(ws + b.off_P); h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
@@ -1944,7 +1962,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             if ((rc = (x.tall ? tall1 : wide1).add(g, x2_wgs(g))) || (rc = (x.tall ? tall2 : wide2).add(h, x2_wgs(h)))) return rc;
           } else if (b.t3) {
             // P = G x_1 Lbar_1 x_2 Lbar_2 ... x_w Lbar_w (Sec. 2.3), the first product here
-            GemmArgs g = left_product(b, b.modes == 1 ? P : T);
+            GemmArgs g = left_product(b, b.modes == 1 ? P : T, b.modes == 1);
             if (b.modes == 1) { g.norm_partial = ssh; rc = only.add(g, gemm_wgs(g)); }
             else rc = first.add(g, gemm_wgs(g));
             if (rc) return rc;
@@ -1964,11 +1982,11 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
               ds.dl = dl; ds.out = T; ds.alpha = c1;
               hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
               HIP_TRY(hipGetLastError());
-              const GemmArgs h = right_product(b, T);
+              const GemmArgs h = right_product(b, T, false);
               if ((rc = second.add(h, gemm_wgs(h)))) return rc;
             } else {
               // T = Lbar G, then P = T D_R
-              const GemmArgs g = left_product(b, T);
+              const GemmArgs g = left_product(b, T, true);
               if ((rc = first.add(g, gemm_wgs(g))) || (rc = first.flush())) return rc;
               ds.src = T; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = 1.f;
               hipLaunchKernelGGL(diag_scale_kernel<float>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
@@ -1976,7 +1994,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
               ssh_count[i] = b.geom.chunks;
             }
           } else {
-            const GemmArgs g = left_product(b, T), h = right_product(b, T);
+            const GemmArgs g = left_product(b, T, false), h = right_product(b, T, true);
             if ((rc = first.add(g, gemm_wgs(g))) || (rc = second.add(h, gemm_wgs(h)))) return rc;
           }
         }
@@ -1987,7 +2005,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         std::vector<int> swapped(todo.size(), 0);       // the block is in the second scratch
         for (int mid = 0; mid < 2; ++mid) {
           Batch<PermuteArgs> there(permute_12_kernel<float>, 256, s), back(permute_12_kernel<float>, 256, s);
-          Batch<GemmArgs> products(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>, GEMM_THREADS, s);
+          Batch<GemmArgs> products(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, false, true>
+                                        : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>, GEMM_THREADS, s);
           for (size_t i = 0; i < todo.size(); ++i) {
             const Bucket &b = *todo[i];
             if (!b.t3 || mid + 2 >= b.modes) continue;
@@ -2023,6 +2042,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           q.M = (int)(mn / dl); q.N = dl; q.K = dl; q.alpha = 1.f; q.beta = 0.f;
           q.tiles_m = (q.M + BM - 1) / BM; q.tiles_n = (q.N + BN - 1) / BN; q.tiles = q.tiles_m * q.tiles_n; q.batch = b.count;
           q.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
+          scale_direction(b, q, false, true);
           if ((rc = second.add(q, gemm_wgs(q)))) return rc;
           ssh_count[i] = q.tiles;
         }
@@ -2220,6 +2240,7 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
     if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_R), 0.f, B * (int64_t)b.r_elems(), s))) return fail(rc);
     if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_P), 0.f, B * b.m * b.n, s))) return fail(rc);
     if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_norms), 0.f, B * 2, s))) return fail(rc);
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_gmax), 0.f, B * 2, s))) return fail(rc);
     if (b.t3) {
       for (int k = 0; k + 2 < b.modes; ++k) {
         const int64_t t2 = B * b.td[k + 1] * b.td[k + 1];
