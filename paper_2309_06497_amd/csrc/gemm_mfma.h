@@ -4,15 +4,17 @@
 // One workgroup (256 threads = 4 wavefronts of 64) computes a 128 x 128 tile of
 // C = alpha * A * B (+ beta * C).  Each wavefront owns a 64 x 64 quadrant as
 // 2 x 2 MFMA tiles of 32 x 32; tiles that hold nothing (ragged edges, above the diagonal) are passed over.  Slabs of
-// 32 values of k go through LDS as float32, laid out as they are read from memory ([row][k] or [k][row]: 16-byte writes
-// either way), double-buffered against the global loads of the next slab.  Operands may be float32 or bfloat16 in memory.
+// 32 values of k go through LDS, the loads of the next one in flight meanwhile.  Operands may be float32 or bfloat16 in
+// memory.
 //
-// A product is six v_mfma_f32_32x32x16_bf16 of operands split into three bf16 terms on the way from LDS (bf16_terms.h):
-// 192 cycles for 16 values of k, 512 on the float32 matrix cores, and 44 vector instructions per operand and step for the
-// splitting, which run beside them; a bf16 operand is one term and leaves three products, or one.  The five small
+// A product is six v_mfma_f32_32x32x16_bf16 of operands split into three bf16 terms (bf16_terms.h): 192 cycles for 16
+// values of k, 512 on the float32 matrix cores; a bf16 operand is one term and leaves three products, or one.  The terms are
+// made once, on the way into LDS (22 vector instructions per thread, operand and 4 values; made on the way out, by both
+// wavefronts that read an operand, the vector instructions took longer than the matrix cores).  The five small
 // products have accumulators of their own, so that only h h' is rounded at full size.  FP32 keeps
-// v_mfma_f32_32x32x2_f32 for callers that ask for it.
-// GEMM_FIGURES
+// v_mfma_f32_32x32x2_f32 on float32 slabs for callers that ask for it.
+// 64 symmetric products of 1024 (36 of 64 tiles), operands along k / along rows: 530 / 650 us, 700 on the float32 matrix
+// cores; that is 0.87 PFLOP/s of bf16 products, where gemm_f16x2.h reaches 1.1 on planes made beforehand.
 //
 // The operands of the Shampoo step (Sec. 2.3, 3.1.1 of the paper) map onto it as
 //   L <- beta2 L + (1-beta2) G G^T   A(i,k) = G[i][k]   B(k,j) = G[j][k]   (both k-contiguous)
@@ -31,10 +33,16 @@ namespace shampoo {
 constexpr int BM = 128;
 constexpr int BN = 128;
 constexpr int BK = 32;          // k-slab depth
-constexpr int GEMM_LDK = BK + 4;      // rows of a slab [row][k], and [k][row]: 16-byte aligned, four banks apart
+constexpr int GEMM_LDK = BK + 4;      // FP32, rows of a slab [row][k] and [k][row], floats: 16-byte aligned, four banks apart
 constexpr int GEMM_LDR = BM + 4;
-constexpr int GEMM_SLAB = BM * GEMM_LDK;     // floats; the larger of the two layouts
-static_assert(BK * GEMM_LDR <= GEMM_SLAB, "slab");
+constexpr int GEMM_FLOATS = BM * GEMM_LDK;   // the larger of the two layouts
+// Planes: rows of 32 values of k, 20 words apart; where four rows at a time are written (ROW_CONTIG), every fourth row lies beside
+// the next, and the four groups are 16 banks apart.  The 16 lanes that are served at a time then cover the 64 banks, in
+// 16-byte reads and in 8-byte writes.
+constexpr int GEMM_PK = BK / 2 + 4;
+constexpr int GEMM_PGROUP = BM / 4 * GEMM_PK + 16;
+constexpr int GEMM_PLANE = 4 * GEMM_PGROUP;  // words
+static_assert(BK * GEMM_LDR <= GEMM_FLOATS, "slab");
 constexpr int LOAD_PASSES = BK / 8;          // 128 x BK floats = 256 threads x LOAD_PASSES float4
 constexpr int GEMM_THREADS = 256;
 constexpr int NUM_XCD = 8;
@@ -43,6 +51,12 @@ constexpr int NUM_XCD = 8;
 //   K_CONTIG:   ptr[row * ld + k]     (a row-major matrix used as A, or B given transposed)
 //   ROW_CONTIG: ptr[k * ld + row]     (a row-major matrix used as B, or A given transposed)
 enum { K_CONTIG = 0, ROW_CONTIG = 1 };
+
+// where a row of a plane begins; row + 32 i lies i plane_tile() words further
+template <int ORIENT> __device__ __forceinline__ int plane_row(int row) {
+  return ORIENT == K_CONTIG ? row * GEMM_PK : (row & 3) * GEMM_PGROUP + (row >> 2) * GEMM_PK;
+}
+template <int ORIENT> constexpr int plane_tile() { return ORIENT == K_CONTIG ? 32 * GEMM_PK : 8 * GEMM_PK; }
 
 enum { EPI_STORE = 0, EPI_STORE_NORM = 1, EPI_SYRK = 2 };
 
@@ -167,13 +181,13 @@ struct TileLoader {
         }
       }
     } else {
-      const int kk = k0 + (tid >> 5);
+      const int kk = k0 + 4 * (tid >> 5);        // four values of k
       if (rows_left >= 4) {                      // uniform
 #pragma unroll
         for (int h = 0; h < LOAD_PASSES; ++h) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) r[h][j] = 0.f;
-          if (whole || kk + 8 * h < K) load_u4<T>(ptr + (int64_t)(kk + 8 * h) * ld + lane_row, r[h]);
+          if (whole || kk + h < K) load_u4<T>(ptr + (int64_t)(kk + h) * ld + lane_row, r[h]);
         }
         if (rows_left < BM && (rows_left & 3)) { // uniform
 #pragma unroll
@@ -188,7 +202,7 @@ struct TileLoader {
         for (int h = 0; h < LOAD_PASSES; ++h)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            r[h][j] = (kk + 8 * h < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)(kk + 8 * h) * ld + r4 + j) : 0.f;
+            r[h][j] = (kk + h < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)(kk + h) * ld + r4 + j) : 0.f;
       }
     }
   }
@@ -211,10 +225,10 @@ struct TileLoader {
         for (int h = 0; h < LOAD_PASSES; ++h) r[h][j] *= s;
       }
     } else {
-      const int kk = tid >> 5;
+      const int kk = 4 * (tid >> 5);
 #pragma unroll
       for (int h = 0; h < LOAD_PASSES; ++h) {
-        const int k = k0 + kk + 8 * h;
+        const int k = k0 + kk + h;
         const float s = (k < K) ? kscale[k] : 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) r[h][j] *= s;
@@ -230,16 +244,48 @@ struct TileLoader {
       for (int h = 0; h < LOAD_PASSES; ++h)
         *reinterpret_cast<float4 *>(lds + (row + RPP * h) * GEMM_LDK + kq) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
     } else {
-      const int kk = tid >> 5, r4 = (tid & 31) * 4;
+      const int kk = 4 * (tid >> 5), r4 = (tid & 31) * 4;
 #pragma unroll
       for (int h = 0; h < LOAD_PASSES; ++h)
-        *reinterpret_cast<float4 *>(lds + (kk + 8 * h) * GEMM_LDR + r4) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+        *reinterpret_cast<float4 *>(lds + (kk + h) * GEMM_LDR + r4) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+    }
+  }
+  // the planes of the terms, h first
+  __device__ __forceinline__ void store_terms(uint32_t *lds, int tid) {
+    constexpr bool ONE = sizeof(T) == 2;
+    if (ORIENT == K_CONTIG) {
+      constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;
+      uint32_t *at = lds + (tid / TPR) * GEMM_PK + (tid % TPR) * 2;
+#pragma unroll
+      for (int h = 0; h < LOAD_PASSES; ++h)
+#pragma unroll
+        for (int t = 0; t < (ONE ? 1 : 3); ++t) {
+          const uint32_t x = bf16_round2(r[h][0], r[h][1], !ONE && t < 2), y = bf16_round2(r[h][2], r[h][3], !ONE && t < 2);
+          *reinterpret_cast<uint2 *>(at + t * GEMM_PLANE + RPP * h * GEMM_PK) = make_uint2(x, y);
+        }
+    } else {
+      uint32_t *at = lds + (tid & 31) * GEMM_PK + 2 * (tid >> 5);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < (ONE ? 1 : 3); ++t) {
+          const uint32_t x = bf16_round2(r[0][e], r[1][e], !ONE && t < 2), y = bf16_round2(r[2][e], r[3][e], !ONE && t < 2);
+          *reinterpret_cast<uint2 *>(at + t * GEMM_PLANE + e * GEMM_PGROUP) = make_uint2(x, y);
+        }
     }
   }
 
   // the MFMA operand of 32 rows: row (of the lane), values k ... k + 7 of the slab
   static __device__ __forceinline__ floatx8 operand(const float *lds, int row, int k) {
     return ORIENT == K_CONTIG ? lds_row8<GEMM_LDK>(lds, row, k) : lds_col8<GEMM_LDR>(lds, k, row);
+  }
+  // of 32 rows: tile i behind the lane's address, values k ... k + 7 of a half of the slab that the lane's address names
+  static __device__ __forceinline__ void terms(const uint32_t *lane, int i, int s, Bf16Terms &x) {
+    auto plane = [&](int t) {
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(lane + t * GEMM_PLANE + i * plane_tile<ORIENT>() + 8 * s));
+    };
+    x.h = plane(0);
+    if constexpr (sizeof(T) == 4) { x.l = plane(1); x.m = plane(2); }
   }
 };
 
@@ -272,8 +318,10 @@ __device__ __forceinline__ const T *operand_ptr(const Operand &o, const BlockDes
 template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, bool ACC64 = false, bool FP32 = false>
 __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
   static_assert(!(ACC64 && FP32), "float64 sums: bf16 terms");
-  __shared__ __align__(16) float As[2][GEMM_SLAB];
-  __shared__ __align__(16) float Bs[2][GEMM_SLAB];
+  constexpr int SLAB_A = FP32 ? GEMM_FLOATS : (sizeof(TA) == 2 ? 1 : 3) * GEMM_PLANE, SLAB_B = FP32 ? GEMM_FLOATS : (sizeof(TB) == 2 ? 1 : 3) * GEMM_PLANE;
+  constexpr int STAGES = FP32 ? 2 : 1;           // two workgroups per CU either way
+  __shared__ __align__(16) uint32_t As[STAGES][SLAB_A];
+  __shared__ __align__(16) uint32_t Bs[STAGES][SLAB_B];
   __shared__ float red[4];
 
   int wg;
@@ -355,76 +403,91 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
       if (g.scale_b) lb.multiply(sg);
     }
     if (KSCALE) la.scale(ks, k0, tid);
-    la.store(As[stage], tid);
-    lb.store(Bs[stage], tid);
+    if constexpr (FP32) {
+      la.store(reinterpret_cast<float *>(As[stage]), tid);
+      lb.store(reinterpret_cast<float *>(Bs[stage]), tid);
+    } else {
+      la.store_terms(As[stage], tid);
+      lb.store_terms(Bs[stage], tid);
+    }
   };
   fetch(0);
-  store(0, 0);
-  __syncthreads();
+  if constexpr (FP32) {
+    store(0, 0);
+    __syncthreads();
+  }
 
   const int arow = wm * 64 + (lane & 31);
   const int bcol = wn * 64 + (lane & 31);
   const int khalf = lane >> 5;
+  const uint32_t *lane_a = As[0] + plane_row<AO>(arow) + 4 * khalf, *lane_b = Bs[0] + plane_row<BO>(bcol) + 4 * khalf;
   constexpr bool AONE = sizeof(TA) == 2, BONE = sizeof(TB) == 2;
   for (int kt = 0; kt < nk; ++kt) {
-    const float *as = As[kt & 1], *bs = Bs[kt & 1];
+    if constexpr (!FP32) {
+      if (kt > 0) __syncthreads();       // the slab before has been read
+      store(0, kt * BK);
+      __syncthreads();
+    }
     if (kt + 1 < nk) fetch((kt + 1) * BK);
-    auto operand_a = [&](int i, int s) { return TileLoader<AO, TA>::operand(as, arow + 32 * i, 16 * s + 8 * khalf); };
-    auto operand_b = [&](int j, int s) { return TileLoader<BO, TB>::operand(bs, bcol + 32 * j, 16 * s + 8 * khalf); };
+    auto terms_a = [&](int i, int s, Bf16Terms &x) { TileLoader<AO, TA>::terms(lane_a, i, s, x); };
+    auto terms_b = [&](int j, int s, Bf16Terms &x) { TileLoader<BO, TB>::terms(lane_b, j, s, x); };
     if constexpr (ACC64) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        if (on[i][0] || on[i][1]) {
-          Bf16Terms a[2];
-          bf16_split<AONE>(operand_a(i, 0), a[0]);
-          bf16_split<AONE>(operand_a(i, 1), a[1]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (on[i][j]) {
+            floatx16 c = {};
+            Bf16Terms a, t;
+            terms_a(i, 0, a);
+            terms_b(j, 0, t);
+            const bf16x8 ah = a.h, th = t.h;
+            c = bf16_small_products<AONE, BONE>(a, t, c);
+            terms_a(i, 1, a);
+            terms_b(j, 1, t);
+            c = bf16_small_products<AONE, BONE>(a, t, c);
+            c = bf16_mfma(ah, th, c);
+            c = bf16_mfma(a.h, t.h, c);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc64[i][j][v] += (double)c[v];
+          }
+    } else if constexpr (FP32) {
+#pragma unroll 1
+      for (int s = 0; s < 2; ++s) {
+        const float *as = reinterpret_cast<const float *>(As[kt & 1]), *bs = reinterpret_cast<const float *>(Bs[kt & 1]);
+        floatx8 a[2], t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          a[i] = TileLoader<AO, TA>::operand(as, arow + 32 * i, 16 * s + 8 * khalf);
+          t[i] = TileLoader<BO, TB>::operand(bs, bcol + 32 * i, 16 * s + 8 * khalf);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            if (on[i][j]) acc[i][j] = fp32_products(a[i], t[j], acc[i][j]);
+      }
+      if (kt + 1 < nk) store((kt + 1) & 1, (kt + 1) * BK);
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        Bf16Terms a[2], t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (on[i][0] || on[i][1]) terms_a(i, s, a[i]);
+          if (on[0][i] || on[1][i]) terms_b(i, s, t[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j)
             if (on[i][j]) {
-              floatx16 c = {};
-              Bf16Terms t[2];
-              bf16_split<BONE>(operand_b(j, 0), t[0]);
-              c = bf16_small_products<AONE, BONE>(a[0], t[0], c);
-              bf16_split<BONE>(operand_b(j, 1), t[1]);
-              c = bf16_small_products<AONE, BONE>(a[1], t[1], c);
-              c = bf16_mfma(a[0].h, t[0].h, c);
-              c = bf16_mfma(a[1].h, t[1].h, c);
-#pragma unroll
-              for (int v = 0; v < 16; ++v) acc64[i][j][v] += (double)c[v];
+              rest[i][j] = bf16_small_products<AONE, BONE>(a[i], t[j], rest[i][j]);
+              acc[i][j] = bf16_mfma(a[i].h, t[j].h, acc[i][j]);
             }
-        }
-    } else {
-#pragma unroll 1
-      for (int s = 0; s < 2; ++s) {
-        if constexpr (FP32) {
-          floatx8 a[2], t[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) { a[i] = operand_a(i, s); t[i] = operand_b(i, s); }
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              if (on[i][j]) acc[i][j] = fp32_products(a[i], t[j], acc[i][j]);
-        } else {
-          Bf16Terms a[2], t[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            if (on[i][0] || on[i][1]) bf16_split<AONE>(operand_a(i, s), a[i]);
-            if (on[0][i] || on[1][i]) bf16_split<BONE>(operand_b(i, s), t[i]);
-          }
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              if (on[i][j]) {
-                rest[i][j] = bf16_small_products<AONE, BONE>(a[i], t[j], rest[i][j]);
-                acc[i][j] = bf16_mfma(a[i].h, t[j].h, acc[i][j]);
-              }
-        }
       }
     }
-    if (kt + 1 < nk) store((kt + 1) & 1, (kt + 1) * BK);
-    __syncthreads();
   }
   if constexpr (!ACC64 && !FP32)
 #pragma unroll

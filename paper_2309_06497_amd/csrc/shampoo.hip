@@ -1013,7 +1013,7 @@ int newton_product(const float *A, const float *B, float *C, int n, int cnt, con
   g.tiles_m = g.tiles_n = (n + BM - 1) / BM;
   g.tiles = g.tiles_m * (g.tiles_m + 1) / 2;
   g.batch = cnt;
-  return launch_gemm<ROW_CONTIG, ROW_CONTIG, float, float, EPI_SYRK, false>(g, s);
+  return launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(g, s);     // symmetric: read along k
 }
 
 // X_i = (scale * A_i + eps I)^(-1/p) for a batch of dense n x n matrices.
