@@ -41,6 +41,8 @@ namespace shampoo {
 constexpr int SB = 128;            // largest block edge handled here
 constexpr int SB_HALF = 64;        // the small variant
 constexpr int SB_THREADS = 256;
+constexpr int SB_POINTERS = 224;   // of parameters that travel with the launch
+static_assert(SB_THREADS == EW_THREADS, "chunks of 1-D parameters");
 
 // One block handled by the kernel: where it sits in the caller's tensors and where its state
 // sits in the workspace (byte offsets).  Blocks of all small buckets share one launch.
@@ -66,7 +68,15 @@ struct SmallStepArgs {
   float beta1, gd_scale;         // filter, and its bias correction c1
   int32_t nesterov;
   int32_t fp32;                  // Lbar G Rbar on the float32 matrix cores
+  int32_t n_blocks;              // workgroups behind them: chunks of 1-D parameters
+  DiagArgs diag;
+  // Parameter and gradient pointers of up to SB_POINTERS parameters by value: a step that needs nothing else is one launch
+  // (one 256 x 128 weight and a bias: 18.0 us with a launch for the tables and one for the bias, 15.4 us so)
+  int32_t by_value;
+  void *w_ptr[SB_POINTERS];
+  const void *g_ptr[SB_POINTERS];
 };
+static_assert(sizeof(SmallStepArgs) <= 4096, "kernel arguments");
 
 // sums / maxima over the workgroup in a fixed order; every thread gets the result.  red: 4 floats not in use.
 __device__ __forceinline__ float sb_reduce(float v, float *red, int tid) {
@@ -175,7 +185,7 @@ __device__ __forceinline__ int sb_pairs(int tiles) { return tiles >= 4 ? 4 : til
 __device__ __forceinline__ int sb_singles(int tiles) { return tiles >= 3 ? 2 : 1; }
 
 // GT: element type of the caller's gradients; CAP: no block is larger; FILT: directions from the filtered gradient.
-// grid: one workgroup per entry of g.blocks.
+// grid: one workgroup per entry of g.blocks and per chunk of g.diag.
 template <typename GT, int CAP, bool FILT>
 __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const SmallStepArgs g) {
   constexpr int LD = CAP + 4;
@@ -189,12 +199,19 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
 
   const int slot = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, khalf = lane >> 5;
+  auto w_of = [&](int32_t param) { return global_ptr<float>(g.by_value ? g.w_ptr[param] : g.w_table[param]); };
+  auto g_of = [&](int32_t param) { return global_ptr<const GT>(g.by_value ? g.g_ptr[param] : g.g_table[param]); };
+  if (slot >= g.n_blocks) {
+    const DiagChunk c = g.diag.chunks[slot - g.n_blocks];
+    diag_chunk<GT>(g.diag, c, w_of(c.param), g_of(c.param));
+    return;
+  }
   const SmallBlock sbk = g.blocks[slot];
   const int m = sbk.m, n = sbk.n;
   const BlockDesc d = sbk.d;
   float *norms = reinterpret_cast<float *>(g.ws + sbk.off_norms);
-  const GT *gp = global_ptr<const GT>(g.g_table[d.param]) + d.offset;
-  float *wp = global_ptr<float>(g.w_table[d.param]) + d.offset;
+  const GT *gp = g_of(d.param) + d.offset;
+  float *wp = w_of(d.param) + d.offset;
   float *ap = g.a_state + d.state_offset;
   float *mp = g.m_state ? g.m_state + d.state_offset : nullptr;
   float *fp = FILT ? g.gf_state + d.state_offset : nullptr;

@@ -340,31 +340,50 @@ struct DiagArgs {
   int32_t nesterov;
 };
 
+// One chunk, with the pointers of its parameter.  Four elements of a thread at a time, every load ahead of the stores.
 template <typename GT>
-__global__ __launch_bounds__(EW_THREADS) void diag_kernel(const DiagArgs g) {
-  const DiagChunk c = g.chunks[blockIdx.x];
-  float *w = global_ptr<float>(g.w_table[c.param]) + c.start;
-  const GT *gp = global_ptr<const GT>(g.g_table[c.param]) + c.start;
+__device__ __forceinline__ void diag_chunk(const DiagArgs &g, const DiagChunk &c, float *w, const GT *gp) {
+  constexpr int U = 4;
   float *a = g.a_state + c.state_offset;
   float *m = g.m_state ? g.m_state + c.state_offset : nullptr;
   float *gf = g.gf_state ? g.gf_state + c.state_offset : nullptr;
-  for (int i = threadIdx.x; i < c.len; i += EW_THREADS) {
-    float wv = w[i];
-    float gv = Elem<GT>::load1(gp + i);
-    if (g.wd_l2 != 0.f) gv += g.wd_l2 * wv;
-    const float av = g.a_decay * a[i] + g.a_gain * (gv * gv);
-    a[i] = av;
-    float dv = gv;
-    if (gf) { dv = g.beta1 * gf[i] + (1.f - g.beta1) * gv; gf[i] = dv; }
-    float p = -(g.gd_scale * dv) / (sqrtf(g.a_bc * av) + g.graft_eps);
-    if (g.wd_decoupled != 0.f) p -= g.wd_decoupled * wv;
-    if (m) {
-      const float mv = g.mu * m[i] + p;
-      m[i] = mv;
-      p = g.nesterov ? g.mu * mv + p : mv;
+  w += c.start;
+  gp += c.start;
+  for (int i0 = threadIdx.x; i0 < c.len; i0 += U * EW_THREADS) {
+    float wv[U], gv[U], av[U], mv[U], fv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * EW_THREADS;
+      if (i < c.len) {
+        wv[u] = w[i]; gv[u] = Elem<GT>::load1(gp + i); av[u] = a[i];
+        mv[u] = m ? m[i] : 0.f;
+        fv[u] = gf ? gf[i] : 0.f;
+      }
     }
-    w[i] = wv + g.lr * p;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * EW_THREADS;
+      if (i >= c.len) break;
+      if (g.wd_l2 != 0.f) gv[u] += g.wd_l2 * wv[u];
+      const float an = g.a_decay * av[u] + g.a_gain * (gv[u] * gv[u]);
+      a[i] = an;
+      float dv = gv[u];
+      if (gf) { dv = g.beta1 * fv[u] + (1.f - g.beta1) * gv[u]; gf[i] = dv; }
+      float p = -(g.gd_scale * dv) / (sqrtf(g.a_bc * an) + g.graft_eps);
+      if (g.wd_decoupled != 0.f) p -= g.wd_decoupled * wv[u];
+      if (m) {
+        const float mn = g.mu * mv[u] + p;
+        m[i] = mn;
+        p = g.nesterov ? g.mu * mn + p : mn;
+      }
+      w[i] = wv[u] + g.lr * p;
+    }
   }
+}
+template <typename GT>
+__global__ __launch_bounds__(EW_THREADS) void diag_kernel(const DiagArgs g) {
+  const DiagChunk c = g.chunks[blockIdx.x];
+  diag_chunk<GT>(g, c, global_ptr<float>(g.w_table[c.param]), global_ptr<const GT>(g.g_table[c.param]));
 }
 
 // 2-D parameters, flat chunks: G1 = G + wd W (if g1 != nullptr) and

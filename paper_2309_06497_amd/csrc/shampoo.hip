@@ -1102,6 +1102,7 @@ struct shampoo_opt {
   size_t off_nfail = 0;   // coupled Newton: per-matrix failure flags of one batch (int32)
   std::vector<void *> last_w, last_g;    // the caller's pointers of the last step (what the device tables name)
   AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
+  bool tables_stale = true;              // last_w and last_g have not been sent to the device
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
   std::vector<char> upper_stale;         // per bucket: which part of the factors is out of date (UPPER_*)
   int64_t last_step = -1;
@@ -1361,6 +1362,7 @@ inline bool young_factor(int64_t step, int cols, int dim) { return (step + 1) * 
 // a few microseconds (two copies from pageable memory behind a drained stream before: a step of
 // 512 blocks of 128 x 128 took 482 us, now 168).
 int send_pointer_tables(shampoo_opt *o, hipStream_t s) {
+  if (!o->tables_stale) return SHAMPOO_OK;
   const int np = o->cfg.n_params;
   for (int at = 0; at < np; at += POINTER_SET) {
     PointerSet ps;
@@ -1377,6 +1379,7 @@ int send_pointer_tables(shampoo_opt *o, hipStream_t s) {
     hipLaunchKernelGGL(pointer_table_kernel, dim3(1), dim3(256), 0, s, ps);
     HIP_TRY(hipGetLastError());
   }
+  o->tables_stale = false;
   return SHAMPOO_OK;
 }
 
@@ -1419,6 +1422,21 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
                          ? (float)(1.0 / (1.0 - std::pow((double)c.grafting_beta2, (double)(step + 1)))) : 1.f;
   int rc;
 
+  // Blocks of at most 128 x 128 take the whole step in one workgroup (gradient block
+  // resident in LDS) whenever no refresh separates the factor update from the
+  // preconditioning (l2 weight decay and SGD grafting go stage by stage).
+  const bool small_ok = use_shampoo && !refresh && !o->use_l2 && !sgd && o->n_small > 0;
+  auto fused = [&](const Bucket &b) { return small_ok && b.small(); };
+  // A step of nothing but such blocks and 1-D parameters, of which few enough, brings its pointers along
+  const bool by_value = small_ok && o->n_small == (int64_t)p.blocks.size() && c.n_params <= SB_POINTERS;
+  if (!by_value && (rc = send_pointer_tables(o, s))) return rc;
+  DiagArgs d;
+  d.chunks = reinterpret_cast<const DiagChunk *>(ws + o->off_diag);
+  d.w_table = wtab; d.g_table = gtab; d.a_state = A; d.m_state = M; d.gf_state = Gf;
+  d.graft_eps = c.graft_epsilon; d.mu = c.momentum; d.lr = lr;
+  d.beta1 = c.beta1; d.wd_l2 = wd_l2; d.wd_decoupled = wd_dec; d.nesterov = c.use_nesterov ? 1 : 0;
+  d.gd_scale = c1; d.a_decay = a_decay; d.a_gain = a_gain; d.a_bc = a_bc;
+
   // Tensor parameters (Sec. 2.3): the step works on block-contiguous copies of their gradient
   // and of the parameter itself; the pointer tables on the device name those copies.
   TensorCopySet copies{};
@@ -1457,11 +1475,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     HIP_TRY(hipGetLastError());
   }
 
-  // Blocks of at most 128 x 128 take the whole step in one workgroup (gradient block
-  // resident in LDS) whenever no refresh separates the factor update from the
-  // preconditioning (l2 weight decay and SGD grafting go stage by stage).
-  const bool small_ok = use_shampoo && !refresh && !o->use_l2 && !sgd && o->n_small > 0;
-  auto fused = [&](const Bucket &b) { return small_ok && b.small(); };
   const int64_t n_prep = small_ok ? o->n_prep_rest : (int64_t)p.prep_chunks.size();
   if ((o->use_l2 || o->use_b1) && n_prep > 0) {
     StageTimer t(o, SHAMPOO_STAGE_GRAFT, s);
@@ -1481,7 +1494,11 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     f.nesterov = c.use_nesterov ? 1 : 0;
     f.a_decay = a_decay; f.a_gain = a_gain; f.a_bc = a_bc; f.beta1 = c.beta1; f.gd_scale = c1;
     f.fp32 = c.precond_matrix_cores == SHAMPOO_MATRIX_CORES_FP32 ? 1 : 0;
-    const dim3 grid((unsigned)o->n_small), block(SB_THREADS);
+    f.n_blocks = (int32_t)o->n_small; f.diag = d;
+    f.by_value = by_value ? 1 : 0;
+    if (by_value)
+      for (int i = 0; i < c.n_params; ++i) { f.w_ptr[i] = o->last_w[i]; f.g_ptr[i] = o->last_g[i]; }
+    const dim3 grid((unsigned)(o->n_small + (int64_t)p.diag_chunks.size())), block(SB_THREADS);
     constexpr bool FILT_ONLY = sizeof(GT) == 2 && sizeof(GD) == 4;   // bf16 gradients with float directions are filtered
     if (FILT_ONLY || Gf) {
       if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, true>), grid, block, 0, s, f);
@@ -2105,14 +2122,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     send_copies(true);
     HIP_TRY(hipGetLastError());
   }
-  if (!p.diag_chunks.empty()) {
+  if (!p.diag_chunks.empty() && !small_ok) {
     StageTimer t(o, SHAMPOO_STAGE_DIAG, s);
-    DiagArgs d;
-    d.chunks = reinterpret_cast<const DiagChunk *>(ws + o->off_diag);
-    d.w_table = wtab; d.g_table = gtab; d.a_state = A; d.m_state = M; d.gf_state = Gf;
-    d.graft_eps = c.graft_epsilon; d.mu = c.momentum; d.lr = lr;
-    d.beta1 = c.beta1; d.wd_l2 = wd_l2; d.wd_decoupled = wd_dec; d.nesterov = c.use_nesterov ? 1 : 0;
-    d.gd_scale = c1; d.a_decay = a_decay; d.a_gain = a_gain; d.a_bc = a_bc;
     hipLaunchKernelGGL(diag_kernel<GT>, dim3((unsigned)p.diag_chunks.size()), dim3(EW_THREADS), 0, s, d);
     HIP_TRY(hipGetLastError());
   }
@@ -2309,7 +2320,7 @@ int shampoo_step(shampoo_opt *o, void *const *params, const void *const *grads, 
   if (!std::isfinite(lr)) return SHAMPOO_ERR_HYPER;
   hipStream_t s = static_cast<hipStream_t>(stream);
   HIP_TRY(hipSetDevice(o->cfg.device));
-  // pointer tables: re-sent only when they change
+  // pointer tables: re-sent only when they have changed, by the first step that reads them
   const size_t tab_bytes = (size_t)np * sizeof(void *);
   const bool same = (int)o->last_w.size() == np && std::memcmp(o->last_w.data(), params, tab_bytes) == 0 &&
                     std::memcmp(o->last_g.data(), grads, tab_bytes) == 0;
@@ -2320,7 +2331,7 @@ int shampoo_step(shampoo_opt *o, void *const *params, const void *const *grads, 
     uintptr_t bits = 0;
     for (int i = 0; i < np; ++i) bits |= reinterpret_cast<uintptr_t>(grads[i]);
     o->ptrs_aligned16 = bits % 16 == 0;
-    if (const int rt = send_pointer_tables(o, s)) { o->last_w.clear(); return rt; }
+    o->tables_stale = true;
   }
   int rc;
   if (o->cfg.grad_dtype == SHAMPOO_GRAD_BF16) {
