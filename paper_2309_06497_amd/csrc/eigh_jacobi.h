@@ -28,6 +28,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "group.h"
 #include "gemm_mfma.h"
 
 namespace shampoo {
@@ -481,6 +482,8 @@ struct SmallRootArgs {
   float epsilon, r;
   float scale;           // the root is taken of scale * A (bias correction, Sec. 3.1.1); 1 = off
   const int32_t *only;   // optional [batch]: matrices whose entry is 0 are left alone (x untouched)
+  int32_t batch;
+  __device__ __forceinline__ void globals() { to_global(a, x, lambda, failed, fail_count, only); }
 };
 
 // NT threads per workgroup: 256 while several matrices fit the LDS of a CU (n <= 64); 1024

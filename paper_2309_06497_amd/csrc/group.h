@@ -14,13 +14,13 @@
 
 namespace shampoo {
 
-// entries in a launch: what fits the 4 KB of a kernel's arguments
-template <typename Args> constexpr int group_max() { return std::min<int>(32, (4096 - 16) / ((int)sizeof(Args) + 4) - 1); }
+// entries in a launch: what fits the 4 KB of a kernel's arguments beside RESERVE bytes of others
+template <typename Args, int RESERVE = 0> constexpr int group_max() { return std::min<int>(32, (4096 - 16 - RESERVE) / ((int)sizeof(Args) + 4) - 1); }
 
-template <typename Args> struct Group {
+template <typename Args, int RESERVE = 0> struct Group {
   int32_t count;
-  int32_t first[group_max<Args>()];    // first workgroup of an entry (a multiple of 8: the XCD of a workgroup is its index modulo 8)
-  Args a[group_max<Args>()];
+  int32_t first[group_max<Args, RESERVE>()];    // first workgroup of an entry (a multiple of 8: the XCD of a workgroup is its index modulo 8)
+  Args a[group_max<Args, RESERVE>()];
 };
 
 // The compiler knows that a pointer among a kernel's arguments is one to global memory, but not of one that it finds by an
@@ -38,7 +38,7 @@ template <typename T, typename... Rest> __device__ __forceinline__ void to_globa
 
 // The entry of this workgroup, and its index among the entry's workgroups.  A copy, read once: what stays behind a
 // reference is read again wherever it is used.
-template <typename Args> __device__ __forceinline__ Args group_pick(const Group<Args> &g, int &wg) {
+template <typename Args, int RESERVE> __device__ __forceinline__ Args group_pick(const Group<Args, RESERVE> &g, int &wg) {
   int k = 0;
   while (k + 1 < g.count && (int)blockIdx.x >= g.first[k + 1]) ++k;
   wg = (int)blockIdx.x - g.first[k];

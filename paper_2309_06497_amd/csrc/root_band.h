@@ -32,6 +32,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "gemm_mfma.h"
+#include "group.h"
 #include "lds_dma.h"
 #include "root_rational.h"
 #include "root_tridiag.h"
@@ -77,6 +78,31 @@ struct BandArgs {
   int32_t *dec;                          // [np]: row is coupled to no other
   int32_t *skip;                         // meta->skip != 0, back to back for the products of the way back
 };
+// Matrices of one size in a launch (group.h): several sizes go through the same launches, each at its own panel.
+struct BandJob {
+  BandArgs g;
+  int32_t k, cnt;                        // panel, group of panels or round; number of matrices
+  __device__ __forceinline__ void globals() {
+    to_global(g.a, g.x, g.failed_user, g.fail_count, g.only, g.meta, g.w, g.f, g.vp, g.z, g.y, g.t, g.part, g.vall, g.tall, g.dblk, g.cblk, g.kf, g.gf,
+              g.v1, g.ok, g.dec, g.skip);
+  }
+};
+constexpr int BAND_TABLE_RESERVE = sizeof(RatTable) + 16;      // of a launch's arguments, where the weights go along
+typedef Group<BandJob> BandJobs;
+typedef Group<BandJob, BAND_TABLE_RESERVE> BandTableJobs;
+// the job of a workgroup, the matrix and the workgroup's index among the PER of a matrix
+#define BAND_PICK(PER)                                                     \
+  int wg;                                                                  \
+  const BandJob job = group_pick(grp, wg);                                 \
+  BandArgs g = job.g;                                                      \
+  const int k = job.k, per_ = (PER), b = wg / per_, bx = wg - b * per_;    \
+  (void)k; (void)bx;                                                       \
+  if (b >= job.cnt) return;
+// rows and workgroups of a panel's products
+__host__ __device__ inline int band_left(const BandArgs &g, int k) { return g.np - (k + 1) * BAND; }
+__host__ __device__ inline int band_row_wgs(const BandArgs &g, int k) { const int m = band_left(g, k); return (m + BAND_ROWS - 1) / BAND_ROWS; }
+__host__ __device__ inline int band_col_wgs(const BandArgs &g, int k) { const int m = band_left(g, k); return (m + BAND_COLS - 1) / BAND_COLS; }
+__host__ __device__ inline int band_groups(const BandArgs &g) { return (g.nb - 1 + BAND_GROUP - 1) / BAND_GROUP; }
 // Arrays of the way back, in the memory of kf and gf, which nothing reads any more by then: the work array
 // [np][BAND_PLD] of a group of panels; [T^T; -T M T^T / 2] as a [256][128] matrix; T [groups][128][128].
 __host__ __device__ inline float *band_p(const BandArgs &g) { return reinterpret_cast<float *>(g.kf); }
@@ -106,12 +132,13 @@ __device__ __forceinline__ band_f4 band_mfma(float a, float b, band_f4 c) { retu
 __device__ __forceinline__ int band_row(int lg, int v) { return lg + 4 * v; }   // of element v of a band_d4
 
 // ---------------------------------------------------------------------------
-// W = pad(sym(scale A)); which rows stand alone.  grid (np / 32, batch), 256 threads
+// W = pad(sym(scale A)); which rows stand alone.  workgroups: np / 32 per matrix, 256 threads
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void band_init_kernel(BandArgs g) {
+__global__ __launch_bounds__(256) void band_init_kernel(const BandJobs grp) {
   __shared__ float Xs[BAND][BAND + 1], Ys[BAND][BAND + 1];
   __shared__ int coupled[BAND];
-  const int b = blockIdx.y, br = blockIdx.x, tid = threadIdx.x, r = tid >> 3, c4 = (tid & 7) * 4;
+  BAND_PICK(g.nb)
+  const int br = bx, tid = threadIdx.x, r = tid >> 3, c4 = (tid & 7) * 4;
   const int32_t *only = g.only;
   band_select(g, b);
   if (only && only[b] == 0) {
@@ -156,10 +183,11 @@ __global__ __launch_bounds__(256) void band_init_kernel(BandArgs g) {
 
 // A row that is coupled to no other is an eigenvector by itself: its entry of the result is f of its
 // diagonal entry.  It goes through the reduction, like the padding, with a diagonal entry from inside
-// the spectrum of the rest.  grid (batch), 256 threads
-__global__ __launch_bounds__(256) void band_alone_kernel(BandArgs g) {
+// the spectrum of the rest.  a workgroup of 256 threads per matrix
+__global__ __launch_bounds__(256) void band_alone_kernel(const BandJobs grp) {
   __shared__ double red[2][4];
-  band_select(g, blockIdx.x);
+  BAND_PICK(1)
+  band_select(g, b);
   if (g.meta->skip) return;
   const int tid = threadIdx.x, n = g.n, np = g.np;
   double dmin = 1.0e300, fill = -1.0e300;
@@ -252,10 +280,11 @@ struct BandQrShared {
 };
 
 template <int TT>
-__global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(BandArgs g, const int k) {
+__global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs grp) {
   static_assert(TT % 4 == 0, "registers by fours");
   __shared__ BandQrShared sh;
-  band_select(g, blockIdx.x);
+  BAND_PICK(1)
+  band_select(g, b);
   if (g.meta->skip) return;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, ph = lane >> 4;
   const int r0 = (k + 1) * BAND, m = np - r0;
@@ -409,15 +438,16 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(BandArgs g, co
 // r0 ... np - 1, r0 = 32 (k + 1).
 // ---------------------------------------------------------------------------
 // Z = W[r0:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
-// grid (ceil((np - r0) / 128), batch), 4 wavefronts of 32 rows.  Memory bound (every element of W is
+// Workgroups: ceil((np - r0) / 128) per matrix, 4 wavefronts of 32 rows.  Memory bound (every element of W is
 // read once for 64 multiply-adds); a lane reads 4 consecutive k of its row.
-__global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
+__global__ __launch_bounds__(256) void band_z_kernel(const BandJobs grp) {
   __shared__ double red[4][1024];
-  band_select(g, blockIdx.y);
+  BAND_PICK(band_row_wgs(g, k))
+  band_select(g, b);
   if (g.meta->skip) return;
   const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
+  const int base = r0 + BAND_ROWS * bx + BAND * w;
   band_d4 m1[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -462,20 +492,21 @@ __global__ __launch_bounds__(256) void band_z_kernel(BandArgs g, const int k) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) red[w][(16 * i + band_row(lg, v)) * BAND + 16 * j + li] = m1[i][j][v];
   __syncthreads();
-  for (int e = tid; e < 1024; e += 256) g.part[(int64_t)blockIdx.x * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+  for (int e = tid; e < 1024; e += 256) g.part[(int64_t)bx * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
-// Y = Z T - V (T^T M T) / 2 with M = V^T Z.  grid and threads as above
-__global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
+// Y = Z T - V (T^T M T) / 2 with M = V^T Z.  workgroups as above
+__global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
   __shared__ double M[BAND][BAND + 1], Tm[BAND][BAND + 1], S[BAND][BAND + 1];
-  band_select(g, blockIdx.y);
+  BAND_PICK(band_row_wgs(g, k))
+  band_select(g, b);
   if (g.meta->skip) return;
   const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
+  const int base = r0 + BAND_ROWS * bx + BAND * w;
   for (int e = tid; e < 1024; e += 256) {
     double s = 0.0;
-    for (int q = 0; q < (int)gridDim.x; ++q) s += g.part[(int64_t)q * 1024 + e];
+    for (int q = 0; q < per_; ++q) s += g.part[(int64_t)q * 1024 + e];
     M[e >> 5][e & 31] = s;
     Tm[e >> 5][e & 31] = g.t[e];
   }
@@ -523,18 +554,20 @@ __global__ __launch_bounds__(256) void band_y_kernel(BandArgs g, const int k) {
   }
 }
 
-// W <- W - V Y^T - Y V^T on rows and columns r0 ....  grid (ceil((np - r0) / 128), ceil((np - r0) / 128), batch), 4
+// W <- W - V Y^T - Y V^T on rows and columns r0 ....  workgroups: the square of ceil((np - r0) / 128) per matrix, 4
 // wavefronts of 32 rows, which keep their rows of V and Y in registers and walk along the columns together, 16 at a
 // time.  Memory bound, 3.3 TB/s for 64 matrices of 1024.  Blocks below the diagonal only, with their mirror images stored
 // from the same registers, took 1 % off 16 matrices of 2048 and added 0.4 % to 64 of 1024: not kept.
-__global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int k) {
-  band_select(g, blockIdx.z);
+__global__ __launch_bounds__(256) void band_update_kernel(const BandJobs grp) {
+  BAND_PICK(band_row_wgs(g, k) * band_col_wgs(g, k))
+  const int rows = band_row_wgs(g, k), by = bx / rows;
+  band_select(g, b);
   if (g.meta->skip) return;
   const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = r0 + BAND_ROWS * blockIdx.x + BAND * w;
+  const int base = r0 + BAND_ROWS * (bx - rows * by) + BAND * w;
   if (base >= np) return;
-  const int c0 = r0 + BAND_COLS * blockIdx.y, c1 = min(c0 + BAND_COLS, np);
+  const int c0 = r0 + BAND_COLS * by, c1 = min(c0 + BAND_COLS, np);
   band_d4 va[2][2], ya[2][2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
@@ -576,10 +609,11 @@ __global__ __launch_bounds__(256) void band_update_kernel(BandArgs g, const int 
 // ---------------------------------------------------------------------------
 // The block tridiagonal matrix
 // ---------------------------------------------------------------------------
-// Gershgorin bounds of B.  grid (batch), 256 threads
-__global__ __launch_bounds__(256) void band_bounds_kernel(BandArgs g) {
+// Gershgorin bounds of B.  a workgroup of 256 threads per matrix
+__global__ __launch_bounds__(256) void band_bounds_kernel(const BandJobs grp) {
   __shared__ double red[2][4];
-  band_select(g, blockIdx.x);
+  BAND_PICK(1)
+  band_select(g, b);
   if (g.meta->skip) return;
   const int tid = threadIdx.x, np = g.np;
   double hi = -1.0e300, amax = 0.0;
@@ -696,7 +730,7 @@ struct BandElim {
 // Round `round` of the search for the smallest eigenvalue: wavefront s tells whether B - shift_s is
 // positive definite.  Round 0: a ladder of shifts over all magnitudes; later rounds divide the bracket,
 // where the eigenvalue is negative or so small that float64 resolves it only by itself.
-// grid (BAND_SHIFTS, batch), one wavefront
+// BAND_SHIFTS workgroups per matrix, one wavefront
 __device__ __forceinline__ double band_ladder(int s, double amax) {   // 0, amax 2^-48 ... 2^-3, -amax 2^-55 ... 2
   return s == 0 ? 0.0 : s <= 16 ? ldexp(amax, 3 * s - 51) : -2.0 * ldexp(amax, 4 * (s - 31));
 }
@@ -729,10 +763,11 @@ __device__ __forceinline__ void band_bracket(const BandArgs &g, int round, doubl
     }
   }
 }
-__global__ __launch_bounds__(64) void band_probe_kernel(BandArgs g, const int round) {
+__global__ __launch_bounds__(64) void band_probe_kernel(const BandJobs grp) {
   __shared__ double row[2 * BAND];
-  const int s = blockIdx.x;
-  band_select(g, blockIdx.y);
+  BAND_PICK(BAND_SHIFTS)
+  const int s = bx, round = k;
+  band_select(g, b);
   if (g.meta->skip) return;
   const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
   double sigma;
@@ -755,9 +790,12 @@ __global__ __launch_bounds__(64) void band_probe_kernel(BandArgs g, const int ro
 }
 
 // Range, poles and exceptions of every matrix.  One thread per matrix
-__global__ void band_plan_kernel(BandArgs g, const int batch) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
+__global__ __launch_bounds__(64) void band_plan_kernel(const BandJobs grp) {
+  int wg;
+  const BandJob job = group_pick(grp, wg);
+  BandArgs g = job.g;
+  const int b = wg * 64 + threadIdx.x;
+  if (b >= job.cnt) return;
   int32_t *failed_user = g.failed_user;
   band_select(g, b);
   BandMeta &m = *g.meta;
@@ -785,15 +823,16 @@ __global__ void band_plan_kernel(BandArgs g, const int batch) {
 }
 
 // Eliminates B + sigma_j from the first block to the last, then forms the diagonal blocks of the inverse
-// from the last to the first.  One wavefront per matrix and pole: grid (BAND_SLOTS, batch).  Bound by the
+// from the last to the first.  One wavefront per matrix and pole, BAND_SLOTS workgroups per matrix.  Bound by the
 // latency of 32 pivots per block.  The last slot iterates for the eigenvector that is handled by itself, from just below
 // its eigenvalue: the smallest pole is near zero on the shifted axis, and where lambda_min is positive that is no nearer
 // to it than to the next eigenvalue.
-__global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTable table) {
+__global__ __launch_bounds__(64) void band_factor_kernel(const BandTableJobs grp, const RatTable table) {
   __shared__ double row[2 * BAND];
   __shared__ double z[BAND_MAX_N + BAND];
-  const int pole = blockIdx.x;
-  band_select(g, blockIdx.y);
+  BAND_PICK(BAND_SLOTS)
+  const int pole = bx;
+  band_select(g, b);
   const BandMeta m = *g.meta;
   const bool vector = pole == RAT_MAX_POLES;
   if (m.skip || (vector ? !m.deflate : pole >= m.poles)) return;
@@ -923,15 +962,16 @@ __global__ __launch_bounds__(64) void band_factor_kernel(BandArgs g, const RatTa
 
 // Block row l of F = sum_j w_j (B + sigma_j)^-1: per pole G_{l,i} = -G_{l,i+1} K_i, held transposed, so that
 // a product's result is the next one's operand; the poles are dealt over 8 wavefronts, which meet in
-// LDS once per block.  grid (nb, batch), 512 threads; the longest rows first.
+// LDS once per block.  nb workgroups per matrix, 512 threads; the longest rows first.
 template <int PW>
-__global__ __launch_bounds__(512, 2) void band_rows_kernel(BandArgs g) {
+__global__ __launch_bounds__(512, 2) void band_rows_kernel(const BandJobs grp) {
   __shared__ float red[2][8][1024];
-  band_select(g, blockIdx.y);
+  BAND_PICK(g.nb)
+  band_select(g, b);
   const int poles = g.meta->poles;
   if (g.meta->skip || (poles + 7) / 8 != PW) return;
   const int np = g.np, nb = g.nb, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int l = nb - 1 - blockIdx.x;
+  const int l = nb - 1 - bx;
   double gt[PW][2][2][4];                // [pole][rows 16 h ...][tile of columns][v]
 #pragma unroll
   for (int p = 0; p < PW; ++p) {
@@ -1004,21 +1044,23 @@ __global__ __launch_bounds__(512, 2) void band_rows_kernel(BandArgs g) {
 }
 
 // The part of F along v1 becomes f1:  F <- F - v q^T - q v^T,  q = F v - (v.F v + f1) / 2 v.
-// First kernel: y = F v;  grid (np / 32, batch), 256 threads.  Second: the update; grid (np / 32, batch).
-__global__ __launch_bounds__(256) void band_fv_kernel(BandArgs g) {
-  band_select(g, blockIdx.y);
+// First kernel: y = F v;  workgroups: np / 32 per matrix, 256 threads.  Second: the update; grid (np / 32, batch).
+__global__ __launch_bounds__(256) void band_fv_kernel(const BandJobs grp) {
+  BAND_PICK(g.nb)
+  band_select(g, b);
   if (g.meta->skip || !g.meta->deflate) return;
   const int np = g.np, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int r = blockIdx.x * BAND + w; r < (int)(blockIdx.x + 1) * BAND; r += 4) {
+  for (int r = bx * BAND + w; r < (bx + 1) * BAND; r += 4) {
     double s = 0.0;
     for (int c = lane; c < np; c += 64) s += (double)g.f[(int64_t)r * np + c] * g.v1[c];
     s = wave64_sum(s);
     if (lane == 0) g.z[r] = s;
   }
 }
-__global__ __launch_bounds__(256) void band_deflate_kernel(BandArgs g) {
+__global__ __launch_bounds__(256) void band_deflate_kernel(const BandJobs grp) {
   __shared__ double red[4];
-  band_select(g, blockIdx.y);
+  BAND_PICK(g.nb)
+  band_select(g, b);
   if (g.meta->skip || !g.meta->deflate) return;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   double s = 0.0;
@@ -1027,7 +1069,7 @@ __global__ __launch_bounds__(256) void band_deflate_kernel(BandArgs g) {
   if (lane == 0) red[w] = s;
   __syncthreads();
   const double K = 0.5 * ((red[0] + red[1]) + (red[2] + red[3]) + g.meta->f1);
-  for (int r = blockIdx.x * BAND + w; r < (int)(blockIdx.x + 1) * BAND; r += 4) {
+  for (int r = bx * BAND + w; r < (bx + 1) * BAND; r += 4) {
     const double vr = g.v1[r], qr = g.z[r] - K * vr;
     for (int c = lane; c < np; c += 64) {
       const double vc = g.v1[c], qc = g.z[c] - K * vc;
@@ -1044,13 +1086,14 @@ __global__ __launch_bounds__(256) void band_deflate_kernel(BandArgs g) {
 // 64 matrices of 1024, kernel time summed over four streams: 23.7 ms one panel at a time, 16 ms so (64
 // refreshed factors: 19.5 -> 18.1 ms in all); groups of 4 because T and M of 128 columns still fit LDS.
 // ---------------------------------------------------------------------------
-// T of the groups: T of two neighbours is [T1, -T1 (V1^T V2) T2; 0, T2].  grid (groups, batch), 16
+// T of the groups: T of two neighbours is [T1, -T1 (V1^T V2) T2; 0, T2].  band_groups workgroups per matrix, 16
 // wavefronts that share the rows of the 6 products V_a^T V_b; all groups of all matrices in one launch.
-__global__ __launch_bounds__(1024) void band_group_t_kernel(BandArgs g) {
+__global__ __launch_bounds__(1024) void band_group_t_kernel(const BandJobs grp) {
   __shared__ float red[16][1024], T[BAND_GW][BAND_GW + 1];
-  band_select(g, blockIdx.y);
+  BAND_PICK(band_groups(g))
+  band_select(g, b);
   if (g.meta->skip) return;
-  const int np = g.np, q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
+  const int np = g.np, q = bx, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int panels = min(BAND_GROUP, g.nb - 1 - BAND_GROUP * q);
   band_f4 acc[6][2][2];
 #pragma unroll
@@ -1119,12 +1162,14 @@ __global__ __launch_bounds__(1024) void band_group_t_kernel(BandArgs g) {
   for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x / BAND_GW][x % BAND_GW];
 }
 
-// V of group q into the work array (Y = false), or Y into its second place.  grid (np / 8, batch), 256 threads
+// V of group q into the work array (Y = false), or Y into its second place.  np / 8 workgroups per matrix, 256 threads
 template <bool Y>
-__global__ __launch_bounds__(256) void band_stage_kernel(BandArgs g, const int q) {
-  band_select(g, blockIdx.y);
+__global__ __launch_bounds__(256) void band_stage_kernel(const BandJobs grp) {
+  BAND_PICK(g.np / 8)
+  const int q = k;
+  band_select(g, b);
   if (g.meta->skip) return;
-  const int row = blockIdx.x * 8 + (threadIdx.x >> 5), c = (threadIdx.x & 31) * 4;
+  const int row = bx * 8 + (threadIdx.x >> 5), c = (threadIdx.x & 31) * 4;
   float *p = band_p(g) + (int64_t)row * BAND_PLD;
   if (Y) {
     *reinterpret_cast<float4 *>(p + 2 * BAND_GW + c) = *reinterpret_cast<const float4 *>(p + c);
@@ -1135,12 +1180,14 @@ __global__ __launch_bounds__(256) void band_stage_kernel(BandArgs g, const int q
   }
 }
 
-// M = V^T Z and [T^T; -T M T^T / 2].  grid (batch), 16 wavefronts of 32 x 32 results each; one workgroup per
+// M = V^T Z and [T^T; -T M T^T / 2].  16 wavefronts of 32 x 32 results each; one workgroup per
 // matrix, since the second product needs all of the first (158 us for 32 matrices of 1024 beside 32 others).  On the fp64 matrix cores:
 // float32 sums here cost more accuracy than the roundings of everything else on the way back together, and 135 us.
-__global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
+__global__ __launch_bounds__(1024) void band_s_kernel(const BandJobs grp) {
   __shared__ float M[BAND_GW][BAND_GW + 1], T[BAND_GW][BAND_GW + 1];
-  band_select(g, blockIdx.x);
+  BAND_PICK(1)
+  const int q = k;
+  band_select(g, b);
   if (g.meta->skip) return;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int i0 = 32 * (w >> 2), j0 = 32 * (w & 3);
@@ -1195,17 +1242,17 @@ __global__ __launch_bounds__(1024) void band_s_kernel(BandArgs g, const int q) {
   for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x % BAND_GW][x / BAND_GW];
 }
 
-// x from the lower triangle of F, mirrored; the rows that stand alone.  grid (pairs of 32 x 32 tiles, batch), 256 threads
-__global__ __launch_bounds__(256) void band_out_kernel(BandArgs g) {
+// x from the lower triangle of F, mirrored; the rows that stand alone.  a workgroup of 256 threads per pair of 32 x 32 tiles and matrix
+__global__ __launch_bounds__(256) void band_out_kernel(const BandJobs grp) {
   __shared__ float tile[BAND][BAND + 1];
-  const int b = blockIdx.y;
+  BAND_PICK(g.nb * (g.nb + 1) / 2)
   band_select(g, b);
   if (g.meta->skip) return;
   const int n = g.n, np = g.np, tid = threadIdx.x;
-  int bi = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
-  while ((bi + 1) * (bi + 2) / 2 <= (int)blockIdx.x) ++bi;
-  while (bi * (bi + 1) / 2 > (int)blockIdx.x) --bi;
-  const int bj = blockIdx.x - bi * (bi + 1) / 2;
+  int bi = (int)((sqrtf(8.f * (float)bx + 1.f) - 1.f) * 0.5f);
+  while ((bi + 1) * (bi + 2) / 2 <= bx) ++bi;
+  while (bi * (bi + 1) / 2 > bx) --bi;
+  const int bj = bx - bi * (bi + 1) / 2;
   const int r = tid >> 3, c4 = (tid & 7) * 4;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1227,12 +1274,17 @@ __global__ __launch_bounds__(256) void band_out_kernel(BandArgs g) {
 }
 
 // meta and flags start at zero.  One thread per matrix
-__global__ void band_clear_kernel(BandArgs g, const int batch) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= batch) return;
+__global__ __launch_bounds__(256) void band_clear_kernel(const BandJobs grp) {
+  int wg;
+  const BandJob job = group_pick(grp, wg);
+  BandArgs g = job.g;
+  const int b = wg * 256 + threadIdx.x;
+  if (b >= job.cnt) return;
   band_select(g, b);
   g.meta->skip = 0;
   g.meta->active[0] = g.meta->active[1] = 0;
 }
+
+#undef BAND_PICK
 
 }  // namespace shampoo

@@ -36,6 +36,7 @@ constexpr double TRI_LOWEST = 0x1p-48;       // the widest range of the rational
 // leaves of the next one is rounding, 1e-16 of it, and so on: after some ten of them its square is a denormal number with a
 // few bits, and a reflector made of it is not orthogonal.  1e-100 is far below the rounding of any float32 matrix.
 constexpr double TRI_NO_COLUMN = 1e-200;
+constexpr int TRI_TABLE_RESERVE = sizeof(RatTable) + 16;   // of a launch's arguments, for the weights
 constexpr int TRI_CHUNK = 16;                // columns of F handed from their makers to their owners at a time
 
 // element of another lane of the same 16
@@ -129,14 +130,16 @@ template <int N> struct TriShared {
 
 // N: the largest n; NT threads = 16 lanes along the columns x RG row groups
 template <int N, int NT>
-__global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const SmallRootArgs g, const RatTable table) {
+__global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<SmallRootArgs, TRI_TABLE_RESERVE> grp, const RatTable table) {
   constexpr int RG = NT / 16, RB = N / RG, CB = N / 16;
   constexpr int PQ = RAT_MAX_POLES / 2, PQ_STEP = 6;      // two lanes share a row of F: poles per lane, taken 6 at a time
   static_assert(NT == 2 * N && PQ % PQ_STEP == 0, "two lanes per row");
-  if (g.only && g.only[blockIdx.x] == 0) return;
+  int b;
+  const SmallRootArgs g = group_pick(grp, b);
+  if (b >= g.batch || (g.only && g.only[b] == 0)) return;
   __shared__ __align__(16) TriShared<N> sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & 15, rg = tid >> 4;
-  const int b = blockIdx.x, n = g.n;
+  const int n = g.n;
   const float *a = g.a + (int64_t)b * g.a_stride;
 
   // ---- load (symmetrised), find what is not finite and the rows that stand alone ----

@@ -404,26 +404,29 @@ struct BandLayout {
          off_kf = 0, off_gf = 0, off_v1 = 0, off_ok = 0, off_dec = 0, off_skip = 0, off_meta = 0;
   size_t bytes = 0;
 };
-BandLayout band_layout(int n, int batch) {
+// of `cnt` matrices
+BandLayout band_layout_of(int n, int cnt) {
   BandLayout e;
   if (n > BAND_MAX_N) return e;
   e.np = (n + BAND - 1) / BAND * BAND; e.nb = e.np / BAND;
   const size_t np = e.np, blk = (size_t)e.nb * BAND * BAND, parts = (np + BAND_ROWS - 1) / BAND_ROWS;
-  auto place = [&](size_t chunk) {
-    size_t off = 0;
-    auto take = [&](size_t per) { const size_t at = off; off += align_up(per * chunk); return at; };
-    e.off_w = take(np * np * 8); e.off_vall = take(np * np * 4);
-    e.off_vp = take(np * BAND * 8); e.off_z = take(np * BAND * 8); e.off_y = take(np * BAND * 8);
-    e.off_t = take(BAND * BAND * 8); e.off_part = take(parts * BAND * BAND * 8); e.off_tall = take(blk * 4);
-    e.off_dblk = take(blk * 8); e.off_cblk = take(blk * 8);
-    e.off_kf = take(blk * 8 * BAND_SLOTS); e.off_gf = take(blk * 8 * BAND_SLOTS);
-    e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_skip = take(4); e.off_meta = take(sizeof(BandMeta));
-    e.chunk = (int32_t)chunk;
-    e.bytes = off;
-  };
-  place(1);
-  place(std::max<size_t>(1, std::min<size_t>({(size_t)batch, (size_t)32768, BAND_CHUNK_BYTES / e.bytes})));
+  size_t off = 0;
+  auto take = [&](size_t per) { const size_t at = off; off += align_up(per * (size_t)cnt); return at; };
+  e.off_w = take(np * np * 8); e.off_vall = take(np * np * 4);
+  e.off_vp = take(np * BAND * 8); e.off_z = take(np * BAND * 8); e.off_y = take(np * BAND * 8);
+  e.off_t = take(BAND * BAND * 8); e.off_part = take(parts * BAND * BAND * 8); e.off_tall = take(blk * 4);
+  e.off_dblk = take(blk * 8); e.off_cblk = take(blk * 8);
+  e.off_kf = take(blk * 8 * BAND_SLOTS); e.off_gf = take(blk * 8 * BAND_SLOTS);
+  e.off_v1 = take(np * 8); e.off_ok = take(2 * BAND_SHIFTS * 4); e.off_dec = take(np * 4); e.off_skip = take(4); e.off_meta = take(sizeof(BandMeta));
+  e.chunk = cnt;
+  e.bytes = off;
   return e;
+}
+// of a chunk of the `batch`
+BandLayout band_layout(int n, int batch) {
+  const BandLayout one = band_layout_of(n, 1);
+  if (!one.bytes) return one;
+  return band_layout_of(n, (int)std::max<size_t>(1, std::min<size_t>({(size_t)batch, (size_t)32768, BAND_CHUNK_BYTES / one.bytes})));
 }
 
 struct EigLayout {
@@ -484,8 +487,9 @@ EigLayout eig_layout(int n, int batch, bool band, size_t budget = EIG_CHUNK_BYTE
 
 // One launch of a kernel for the buckets added to it (group.h), or several where they are more than an argument table
 // holds.  Nothing is launched before flush: what the kernel reads may be written by a launch that is still to come.
-template <typename Args> struct Batch {
-  using Kernel = void (*)(const Group<Args>);
+// Extra: further arguments, of RESERVE bytes.
+template <typename Args, int RESERVE = 0, typename... Extra> struct Batch {
+  using Kernel = void (*)(const Group<Args, RESERVE>, Extra...);
   struct Entry { Args args; int64_t workgroups; };
   Kernel kernel; int threads; hipStream_t s;
   std::vector<Entry> entries;
@@ -495,17 +499,17 @@ template <typename Args> struct Batch {
     if (workgroups > 0) entries.push_back(Entry{a, (workgroups + NUM_XCD - 1) / NUM_XCD * NUM_XCD});
     return SHAMPOO_OK;
   }
-  int flush() {
-    Group<Args> g;
+  int flush(const Extra &...extra) {
+    Group<Args, RESERVE> g;
     for (size_t at = 0; at < entries.size();) {
       int64_t total = 0;
       g.count = 0;
-      while (at < entries.size() && g.count < group_max<Args>() && total + entries[at].workgroups <= (int64_t)1 << 30) {
+      while (at < entries.size() && g.count < group_max<Args, RESERVE>() && total + entries[at].workgroups <= (int64_t)1 << 30) {
         g.a[g.count] = entries[at].args;
         g.first[g.count++] = (int32_t)total;
         total += entries[at++].workgroups;
       }
-      hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(threads), 0, s, g);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(threads), 0, s, g, extra...);
       HIP_TRY(hipGetLastError());
     }
     entries.clear();
@@ -740,91 +744,104 @@ struct BlockSolve {
   }
 };
 
-// One sub-chunk of the band reduction: matrices [first, first + cnt) of a chunk, all of its work on one
-// stream.  Enqueued panel by panel, so that the caller can interleave sub-chunks: while one is in a QR
-// factorisation, which uses one CU per matrix, the others' products fill the chip.
+// Band reductions on one stream: matrices of one size or of several, each launch for all of them (the panels, groups and
+// rounds that a size does not have are left out).  Enqueued panel by panel, so
+// that the caller can interleave two of them: while one is in a QR
+// factorisation, which uses one CU per matrix, the other's products fill the chip.
 struct BandSolve {
-  BandArgs g; int cnt; hipStream_t s; const RatTable *table;
-  int begin() {
-    hipLaunchKernelGGL(band_clear_kernel, dim3((cnt + 255) / 256), dim3(256), 0, s, g, cnt);
-    hipLaunchKernelGGL(band_init_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(band_alone_kernel, dim3(cnt), dim3(256), 0, s, g);
-    HIP_TRY(hipGetLastError());
-    return SHAMPOO_OK;
+  std::vector<BandJob> jobs;
+  hipStream_t s;
+  const RatTable *table;
+  using Kernel = void (*)(const BandJobs);
+  // wgs: workgroups of a job, 0 where it takes no part; may set its k
+  template <typename F> int each(Kernel kernel, int threads, F wgs) {
+    Batch<BandJob> x(kernel, threads, s);
+    for (BandJob &j : jobs)
+      if (const int64_t n = wgs(j))
+        if (const int rc = x.add(j, n)) return rc;
+    return x.flush();
   }
-  int forward(int k) {
-    const int m = g.np - (k + 1) * BAND;
-    if (m <= 256) hipLaunchKernelGGL(band_qr_kernel<8>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
-    else if (m <= 512) hipLaunchKernelGGL(band_qr_kernel<16>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
-    else if (m <= 1024) hipLaunchKernelGGL(band_qr_kernel<32>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
-    else hipLaunchKernelGGL(band_qr_kernel<64>, dim3(cnt), dim3(BAND_QR_THREADS), 0, s, g, k);
-    if (m > 0) {
-      const unsigned rb = (m + BAND_ROWS - 1) / BAND_ROWS, cb = (m + BAND_COLS - 1) / BAND_COLS;
-      hipLaunchKernelGGL(band_z_kernel, dim3(rb, cnt), dim3(256), 0, s, g, k);
-      hipLaunchKernelGGL(band_y_kernel, dim3(rb, cnt), dim3(256), 0, s, g, k);
-      hipLaunchKernelGGL(band_update_kernel, dim3(rb, cb, cnt), dim3(256), 0, s, g, k);
-    }
-    HIP_TRY(hipGetLastError());
-    return SHAMPOO_OK;
+  int most(int (*f)(const BandArgs &)) const { int m = 0; for (const BandJob &j : jobs) m = std::max(m, f(j.g)); return m; }
+  int panels() const { return most([](const BandArgs &g) { return (int)g.nb; }); }
+  int groups() const { return most([](const BandArgs &g) { return band_groups(g); }); }
+  int begin() {
+    int rc;
+    if ((rc = each(band_clear_kernel, 256, [](BandJob &j) { return (j.cnt + 255) / 256; }))) return rc;
+    if ((rc = each(band_init_kernel, 256, [](BandJob &j) { return (int64_t)j.g.nb * j.cnt; }))) return rc;
+    return each(band_alone_kernel, 256, [](BandJob &j) { return j.cnt; });
+  }
+  int forward(int p) {
+    int rc, m = 0;
+    for (BandJob &j : jobs) { j.k = p; if (p < j.g.nb) m = std::max(m, band_left(j.g, p)); }
+    const Kernel qr = m <= 256 ? band_qr_kernel<8> : m <= 512 ? band_qr_kernel<16> : m <= 1024 ? band_qr_kernel<32> : band_qr_kernel<64>;
+    if ((rc = each(qr, BAND_QR_THREADS, [&](BandJob &j) { return p < j.g.nb ? j.cnt : 0; }))) return rc;
+    auto rows = [&](BandJob &j) { return p + 1 < j.g.nb ? (int64_t)band_row_wgs(j.g, p) * j.cnt : 0; };
+    if ((rc = each(band_z_kernel, 256, rows)) || (rc = each(band_y_kernel, 256, rows))) return rc;
+    return each(band_update_kernel, 256, [&](BandJob &j) { return rows(j) * (p + 1 < j.g.nb ? band_col_wgs(j.g, p) : 0); });
   }
   int function() {
-    hipLaunchKernelGGL(band_bounds_kernel, dim3(cnt), dim3(256), 0, s, g);
+    int rc;
+    auto one = [](BandJob &j) { return j.cnt; };
+    auto per_block = [](BandJob &j) { return (int64_t)j.g.nb * j.cnt; };
+    if ((rc = each(band_bounds_kernel, 256, one))) return rc;
     for (int round = 0; round < BAND_ROUNDS; ++round)
-      hipLaunchKernelGGL(band_probe_kernel, dim3(BAND_SHIFTS, cnt), dim3(64), 0, s, g, round);
-    hipLaunchKernelGGL(band_plan_kernel, dim3((cnt + 63) / 64), dim3(64), 0, s, g, cnt);
-    hipLaunchKernelGGL(band_factor_kernel, dim3(BAND_SLOTS, cnt), dim3(64), 0, s, g, *table);
-    hipLaunchKernelGGL(band_rows_kernel<2>, dim3(g.nb, cnt), dim3(512), 0, s, g);
-    hipLaunchKernelGGL(band_rows_kernel<3>, dim3(g.nb, cnt), dim3(512), 0, s, g);
-    hipLaunchKernelGGL(band_rows_kernel<4>, dim3(g.nb, cnt), dim3(512), 0, s, g);
-    hipLaunchKernelGGL(band_rows_kernel<5>, dim3(g.nb, cnt), dim3(512), 0, s, g);
-    hipLaunchKernelGGL(band_fv_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(band_deflate_kernel, dim3(g.nb, cnt), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(band_group_t_kernel, dim3(groups(), cnt), dim3(1024), 0, s, g);
-    HIP_TRY(hipGetLastError());
-    return SHAMPOO_OK;
+      if ((rc = each(band_probe_kernel, 64, [&](BandJob &j) { j.k = round; return (int64_t)BAND_SHIFTS * j.cnt; }))) return rc;
+    if ((rc = each(band_plan_kernel, 64, [](BandJob &j) { return (j.cnt + 63) / 64; }))) return rc;
+    Batch<BandJob, BAND_TABLE_RESERVE, const RatTable> factor(band_factor_kernel, 64, s);
+    for (const BandJob &j : jobs) if ((rc = factor.add(j, (int64_t)BAND_SLOTS * j.cnt))) return rc;
+    if ((rc = factor.flush(*table))) return rc;
+    for (const Kernel rows : {band_rows_kernel<2>, band_rows_kernel<3>, band_rows_kernel<4>, band_rows_kernel<5>})
+      if ((rc = each(rows, 512, per_block))) return rc;
+    if ((rc = each(band_fv_kernel, 256, per_block)) || (rc = each(band_deflate_kernel, 256, per_block))) return rc;
+    return each(band_group_t_kernel, 1024, [](BandJob &j) { return (int64_t)band_groups(j.g) * j.cnt; });
   }
-  int groups() const { return (g.nb - 1 + BAND_GROUP - 1) / BAND_GROUP; }
-  int back(int q) {
-    const int np = g.np, r0 = (BAND_GROUP * q + 1) * BAND, tiles = (np + BM - 1) / BM;
-    float *p = band_p(g);
-    const int64_t pstride = band_p_stride(g);
+  // the u-th group of panels from the end
+  int back(int u) {
     // The sums are what these products lose accuracy by: those of 32 values of k go into float64.  Error of
     // the root of a factor of one gradient at n = 160, 256, 1024: 1.4e-6, 1.4e-6, 1.9e-6 with float32 sums but in Z, 4.8e-7,
     // 4.8e-7, 6.2e-7 so; block Jacobi 8.8e-7, 1.0e-6, 3.0e-6.  The update of F moves the root by a tenth of that:
     // float64 where the margin to Jacobi is small.
     int rc;
-    hipLaunchKernelGGL(band_stage_kernel<false>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
-    GemmArgs z{};                        // Z = F V
-    z.a.base = g.f + r0; z.a.batch_stride = (int64_t)np * np * 2; z.a.ld = np;
-    z.b.base = p + (int64_t)r0 * BAND_PLD + BAND_GW; z.b.batch_stride = pstride; z.b.ld = BAND_PLD;
-    z.c = p; z.c_batch_stride = pstride; z.ldc = BAND_PLD;
-    z.M = np; z.N = BAND_GW; z.K = np - r0; z.alpha_d = 1.0; z.skip = g.skip;
-    z.tiles_m = z.tiles = tiles; z.tiles_n = 1; z.batch = cnt;
-    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>(z, s))) return rc;
-    hipLaunchKernelGGL(band_s_kernel, dim3(cnt), dim3(1024), 0, s, g, q);
-    // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them
-    GemmArgs y = z;
-    y.a = Operand{p, pstride, BAND_PLD, 0};
-    y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
-    y.K = 2 * BAND_GW;
-    if ((rc = launch_gemm<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>(y, s))) return rc;
-    hipLaunchKernelGGL(band_stage_kernel<true>, dim3(np / 8, cnt), dim3(256), 0, s, g, q);
-    GemmArgs u = z;                      // F <- F - [Y V] [V Y]^T; V has no rows in front of r0
-    u.a = y.a;
-    u.b = Operand{p + BAND_GW, pstride, BAND_PLD, 0};
-    u.c = g.f; u.c_batch_stride = (int64_t)np * np * 2; u.ldc = np;
-    u.N = np; u.K = 2 * BAND_GW; u.alpha = -1.f; u.beta = 1.f; u.alpha_d = -1.0; u.beta_d = 1.0;
-    u.tiles_n = tiles; u.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; u.tiles = tiles * (tiles + 1) / 2 - u.tile0;
-    if (np <= 512) rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>(u, s);
-    else rc = launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(u, s);
-    if (rc) return rc;
-    HIP_TRY(hipGetLastError());
-    return SHAMPOO_OK;
+    auto takes_part = [&](BandJob &j) { j.k = band_groups(j.g) - 1 - u; return j.k >= 0; };
+    Batch<GemmArgs> zs(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>, GEMM_THREADS, s),
+        ys(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>, GEMM_THREADS, s),
+        us64(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>, GEMM_THREADS, s),
+        us(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>, GEMM_THREADS, s);
+    for (BandJob &j : jobs) {
+      if (!takes_part(j)) continue;
+      const BandArgs &g = j.g;
+      const int np = g.np, r0 = (BAND_GROUP * j.k + 1) * BAND, tiles = (np + BM - 1) / BM;
+      float *p = band_p(g);
+      const int64_t pstride = band_p_stride(g);
+      GemmArgs z{};                        // Z = F V
+      z.a.base = g.f + r0; z.a.batch_stride = (int64_t)np * np * 2; z.a.ld = np;
+      z.b.base = p + (int64_t)r0 * BAND_PLD + BAND_GW; z.b.batch_stride = pstride; z.b.ld = BAND_PLD;
+      z.c = p; z.c_batch_stride = pstride; z.ldc = BAND_PLD;
+      z.M = np; z.N = BAND_GW; z.K = np - r0; z.alpha_d = 1.0; z.skip = g.skip;
+      z.tiles_m = z.tiles = tiles; z.tiles_n = 1; z.batch = j.cnt;
+      if ((rc = zs.add(z, (int64_t)z.tiles * z.batch))) return rc;
+      // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them
+      GemmArgs y = z;
+      y.a = Operand{p, pstride, BAND_PLD, 0};
+      y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
+      y.K = 2 * BAND_GW;
+      if ((rc = ys.add(y, (int64_t)y.tiles * y.batch))) return rc;
+      GemmArgs f = z;                      // F <- F - [Y V] [V Y]^T; V has no rows in front of r0
+      f.a = y.a;
+      f.b = Operand{p + BAND_GW, pstride, BAND_PLD, 0};
+      f.c = g.f; f.c_batch_stride = (int64_t)np * np * 2; f.ldc = np;
+      f.N = np; f.K = 2 * BAND_GW; f.alpha = -1.f; f.beta = 1.f; f.alpha_d = -1.0; f.beta_d = 1.0;
+      f.tiles_n = tiles; f.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; f.tiles = tiles * (tiles + 1) / 2 - f.tile0;
+      if ((rc = (np <= 512 ? us64 : us).add(f, (int64_t)f.tiles * f.batch))) return rc;
+    }
+    auto stage = [&](BandJob &j) { return takes_part(j) ? (int64_t)(j.g.np / 8) * j.cnt : 0; };
+    if ((rc = each(band_stage_kernel<false>, 256, stage)) || (rc = zs.flush())) return rc;
+    if ((rc = each(band_s_kernel, 1024, [&](BandJob &j) { return takes_part(j) ? j.cnt : 0; })) || (rc = ys.flush())) return rc;
+    if ((rc = each(band_stage_kernel<true>, 256, stage)) || (rc = us64.flush())) return rc;
+    return us.flush();
   }
   int finish() {
-    hipLaunchKernelGGL(band_out_kernel, dim3(g.nb * (g.nb + 1) / 2, cnt), dim3(256), 0, s, g);
-    HIP_TRY(hipGetLastError());
-    return SHAMPOO_OK;
+    return each(band_out_kernel, 256, [](BandJob &j) { return (int64_t)(j.g.nb * (j.g.nb + 1) / 2) * j.cnt; });
   }
 };
 
@@ -832,7 +849,7 @@ struct BandSolve {
 // other has products to do.  64 matrices of 1024: 19.4 ms on one stream, 18.1 on two, 18.3 on three, 18.5 on
 // four; 16 of 2048: 43.6, 44.4, 45.3, 45.7; refresh of two transformer layers: 47.1, 44.6, 44.3, 44.7.
 constexpr int BAND_STREAMS = 2;
-static_assert(BAND_STREAMS <= JAC_STREAMS, "helper streams");
+static_assert(BAND_STREAMS < JAC_STREAMS, "helper streams, and one more");
 
 // Forks the helper streams off s and joins them again.
 int aux_fork(AuxStreams *aux, int subs, hipStream_t s) {
@@ -849,47 +866,100 @@ int aux_join(AuxStreams *aux, int subs, hipStream_t s) {
   return SHAMPOO_OK;
 }
 
-int band_root_batched(const float *a, int n, int batch, float eps, float r, float scale, float *x, int32_t *failed_user,
-                      unsigned long long *fail_count, unsigned char *ws, const BandLayout &e, hipStream_t s, AuxStreams *aux,
-                      const int32_t *only, const RatTable &table) {
+// Roots of a batch of dense n x n matrices that the band reduction or the tridiagonal one serves.
+struct RootJob {
+  const float *a; int n, batch; float r, scale; float *x; int32_t *failed_user; const int32_t *only;
+};
+
+// Jobs of one exponent, of any sizes: as many of their matrices at a time as fit into `room` bytes of ws, those
+// in two halves on two streams.  The launches of few matrices leave most of the GPU idle, and every panel of every size is a
+// launch: the two sides of a dozen buckets take one pass here, not one each.  Refresh of three layers of 700 in blocks of 512:
+// 31 ms one size at a time, 5.4 so; two layers of 1300 in blocks of 1024: 100 and 24; one layer of 896 in blocks of 256, where
+// nothing is ragged: 1.9 and 1.5.
+int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *fail_count, unsigned char *ws, size_t room, hipStream_t s,
+               AuxStreams *aux, const RatTable &table) {
   int rc;
-  for (int b0 = 0; b0 < batch; b0 += e.chunk) {
-    const int cb = std::min(e.chunk, batch - b0);
-    const int subs = aux ? std::min(BAND_STREAMS, cb) : 1;
-    if ((rc = aux_fork(aux, subs, s))) return rc;
-    BandArgs base{};
-    base.a = a + (int64_t)b0 * n * n; base.n = n; base.np = e.np; base.nb = e.nb;
-    base.eps = eps; base.r = r; base.scale = scale; base.x = x + (int64_t)b0 * n * n; base.fail_count = fail_count;
-    base.meta = reinterpret_cast<BandMeta *>(ws + e.off_meta);
-    base.w = reinterpret_cast<double *>(ws + e.off_w); base.f = reinterpret_cast<float *>(ws + e.off_w);
-    base.vp = reinterpret_cast<double *>(ws + e.off_vp); base.t = reinterpret_cast<double *>(ws + e.off_t);
-    base.z = reinterpret_cast<double *>(ws + e.off_z); base.y = reinterpret_cast<double *>(ws + e.off_y);
-    base.part = reinterpret_cast<double *>(ws + e.off_part); base.skip = reinterpret_cast<int32_t *>(ws + e.off_skip);
-    base.vall = reinterpret_cast<float *>(ws + e.off_vall); base.tall = reinterpret_cast<float *>(ws + e.off_tall);
-    base.dblk = reinterpret_cast<double *>(ws + e.off_dblk); base.cblk = reinterpret_cast<double *>(ws + e.off_cblk);
-    base.kf = reinterpret_cast<double *>(ws + e.off_kf); base.gf = reinterpret_cast<double *>(ws + e.off_gf);
-    base.v1 = reinterpret_cast<double *>(ws + e.off_v1);
-    base.ok = reinterpret_cast<int32_t *>(ws + e.off_ok); base.dec = reinterpret_cast<int32_t *>(ws + e.off_dec);
+  size_t i = 0;
+  int done = 0;                            // matrices of todo[i]
+  while (i < todo.size()) {
     BandSolve solve[BAND_STREAMS];
-    int first = 0;
-    for (int k = 0; k < subs; ++k) {
-      BandSolve &v = solve[k];
-      v.g = base; v.cnt = cb / subs + (k < cb % subs ? 1 : 0); v.table = &table;
-      v.s = k == 0 ? s : aux->stream[k - 1];
-      band_select(v.g, first);
-      v.g.failed_user = failed_user ? failed_user + b0 + first : nullptr;
-      v.g.only = only ? only + b0 + first : nullptr;
-      first += v.cnt;
+    size_t at = 0;
+    int turn = 0;
+    for (int k = 0; k < BAND_STREAMS; ++k) { solve[k].table = &table; solve[k].s = k == 0 || !aux ? s : aux->stream[k - 1]; }
+    while (i < todo.size()) {
+      const RootJob &j = todo[i];
+      const int left = std::min(j.batch - done, 32768);
+      int cnt = (int)std::min<size_t>(left, (room - at) / band_layout_of(j.n, 1).bytes);
+      while (cnt < left && at + band_layout_of(j.n, cnt + 1).bytes <= room) ++cnt;   // the arrays of a single matrix are padded
+      if (cnt == 0) break;
+      const BandLayout e = band_layout_of(j.n, cnt);
+      BandArgs base{};
+      unsigned char *w = ws + at;
+      base.a = j.a + (int64_t)done * j.n * j.n; base.n = j.n; base.np = e.np; base.nb = e.nb;
+      base.eps = eps; base.r = j.r; base.scale = j.scale; base.x = j.x + (int64_t)done * j.n * j.n; base.fail_count = fail_count;
+      base.meta = reinterpret_cast<BandMeta *>(w + e.off_meta);
+      base.w = reinterpret_cast<double *>(w + e.off_w); base.f = reinterpret_cast<float *>(w + e.off_w);
+      base.vp = reinterpret_cast<double *>(w + e.off_vp); base.t = reinterpret_cast<double *>(w + e.off_t);
+      base.z = reinterpret_cast<double *>(w + e.off_z); base.y = reinterpret_cast<double *>(w + e.off_y);
+      base.part = reinterpret_cast<double *>(w + e.off_part); base.skip = reinterpret_cast<int32_t *>(w + e.off_skip);
+      base.vall = reinterpret_cast<float *>(w + e.off_vall); base.tall = reinterpret_cast<float *>(w + e.off_tall);
+      base.dblk = reinterpret_cast<double *>(w + e.off_dblk); base.cblk = reinterpret_cast<double *>(w + e.off_cblk);
+      base.kf = reinterpret_cast<double *>(w + e.off_kf); base.gf = reinterpret_cast<double *>(w + e.off_gf);
+      base.v1 = reinterpret_cast<double *>(w + e.off_v1);
+      base.ok = reinterpret_cast<int32_t *>(w + e.off_ok); base.dec = reinterpret_cast<int32_t *>(w + e.off_dec);
+      // halves; odd ones out go to either stream in turn
+      const int subs = aux ? BAND_STREAMS : 1;
+      int first = 0;
+      for (int k = 0; k < subs; ++k) {
+        const int part = cnt / subs + ((k + turn) % subs < cnt % subs ? 1 : 0);
+        if (part == 0) continue;
+        BandJob job{base, 0, part};
+        band_select(job.g, first);
+        job.g.failed_user = j.failed_user ? j.failed_user + done + first : nullptr;
+        job.g.only = j.only ? j.only + done + first : nullptr;
+        solve[k].jobs.push_back(job);
+        first += part;
+      }
+      turn += cnt;
+      at += e.bytes;
+      done += cnt;
+      if (done < j.batch) break;           // no room for the rest
+      ++i; done = 0;
     }
-    for (int k = 0; k < subs; ++k) if ((rc = solve[k].begin())) return rc;
-    for (int p = 0; p < e.nb; ++p)
-      for (int k = 0; k < subs; ++k) if ((rc = solve[k].forward(p))) return rc;
-    for (int k = 0; k < subs; ++k) if ((rc = solve[k].function())) return rc;
-    for (int q = solve[0].groups() - 1; q >= 0; --q)
-      for (int k = 0; k < subs; ++k) if ((rc = solve[k].back(q))) return rc;
-    for (int k = 0; k < subs; ++k) if ((rc = solve[k].finish())) return rc;
-    if ((rc = aux_join(aux, subs, s))) return rc;
+    if (at == 0) return SHAMPOO_ERR_WORKSPACE;
+    const int subs = aux && !solve[1].jobs.empty() ? (solve[0].jobs.empty() ? 0 : 2) : 1;
+    BandSolve *v = solve;
+    if (subs == 0) { solve[0].jobs.swap(solve[1].jobs); }
+    const int n_solve = std::max(subs, 1);
+    if ((rc = aux_fork(aux, n_solve, s))) return rc;
+    int panels = 0, groups = 0;
+    for (int k = 0; k < n_solve; ++k) { panels = std::max(panels, v[k].panels()); groups = std::max(groups, v[k].groups()); }
+    for (int k = 0; k < n_solve; ++k) if ((rc = v[k].begin())) return rc;
+    for (int q = 0; q < panels; ++q)
+      for (int k = 0; k < n_solve; ++k) if (q < v[k].panels() && (rc = v[k].forward(q))) return rc;
+    for (int k = 0; k < n_solve; ++k) if ((rc = v[k].function())) return rc;
+    for (int u = 0; u < groups; ++u)
+      for (int k = 0; k < n_solve; ++k) if (u < v[k].groups() && (rc = v[k].back(u))) return rc;
+    for (int k = 0; k < n_solve; ++k) if ((rc = v[k].finish())) return rc;
+    if ((rc = aux_join(aux, n_solve, s))) return rc;
   }
+  return SHAMPOO_OK;
+}
+
+// Roots of up to 128 x 128: one launch for all jobs of a kernel (of one exponent), the largest matrices first.
+int tridiag_roots(std::vector<RootJob> todo, float eps, unsigned long long *fail_count, hipStream_t s, const RatTable &table) {
+  std::stable_sort(todo.begin(), todo.end(), [](const RootJob &x, const RootJob &y) { return x.n > y.n; });
+  using Roots = Batch<SmallRootArgs, TRI_TABLE_RESERVE, const RatTable>;
+  Roots large(rootinv_tridiag_kernel<128, 256>, 256, s), middle(rootinv_tridiag_kernel<64, 128>, 128, s), small(rootinv_tridiag_kernel<32, 64>, 64, s);
+  for (const RootJob &j : todo) {
+    SmallRootArgs g{};
+    g.a = j.a; g.a_stride = (int64_t)j.n * j.n; g.x = j.x; g.x_stride = (int64_t)j.n * j.n;
+    g.failed = j.failed_user; g.fail_count = fail_count; g.n = j.n; g.epsilon = eps; g.r = j.r; g.scale = j.scale; g.only = j.only;
+    g.batch = j.batch;
+    if (const int rc = (j.n > 64 ? large : j.n > 32 ? middle : small).add(g, j.batch)) return rc;
+  }
+  for (Roots *x : {&large, &middle, &small})
+    if (const int rc = x->flush(table)) return rc;
   return SHAMPOO_OK;
 }
 
@@ -903,20 +973,14 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
                          const WarmStart &warm = WarmStart()) {
   if (batch <= 0) return SHAMPOO_OK;
   if (n <= JAC_SMALL_MAX) {
-    SmallRootArgs g;
+    SmallRootArgs g{};
     g.a = a; g.a_stride = (int64_t)n * n;
     g.x = x; g.x_stride = (int64_t)n * n;
     g.lambda = lambda; g.failed = failed_user; g.fail_count = fail_count;
     g.n = n; g.epsilon = eps; g.r = r; g.scale = scale; g.only = only;
     // without eigenvectors where nobody asks for eigenvalues and the exponent has a rational fit
     RatTable table;
-    if (!lambda && rat_table(r, table)) {
-      if (n <= 32) hipLaunchKernelGGL((rootinv_tridiag_kernel<32, 64>), dim3(batch), dim3(64), 0, s, g, table);
-      else if (n <= 64) hipLaunchKernelGGL((rootinv_tridiag_kernel<64, 128>), dim3(batch), dim3(128), 0, s, g, table);
-      else hipLaunchKernelGGL((rootinv_tridiag_kernel<128, 256>), dim3(batch), dim3(256), 0, s, g, table);
-      HIP_TRY(hipGetLastError());
-      return SHAMPOO_OK;
-    }
+    if (!lambda && rat_table(r, table)) return tridiag_roots({RootJob{a, n, batch, r, scale, x, failed_user, only}}, eps, fail_count, s, table);
     const size_t lds = rootinv_small_lds_bytes(n);
     if (n <= 64) {
       HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(rootinv_small_kernel<256>),
@@ -938,7 +1002,7 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
   if (aux && !aux->ready()) aux = nullptr;
   RatTable table;
   if (!lambda && !warm.qt && e.band.bytes && band_serves(n, r) && rat_table(r, table))
-    return band_root_batched(a, n, batch, eps, r, scale, x, failed_user, fail_count, ws, e.band, s, aux, only, table);
+    return band_roots({RootJob{a, n, batch, r, scale, x, failed_user, only}}, eps, fail_count, ws, e.band.bytes, s, aux, table);
   const int n_sub = aux ? JAC_STREAMS : 1;
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {
     const int cb = std::min(e.chunk, batch - b0);
@@ -1093,6 +1157,7 @@ struct shampoo_opt {
   int64_t n_prep_rest = 0; // of plan.prep_chunks, the first ones: parameters with other blocks too
   bool use_l2 = false, use_b1 = false;
   size_t off_A = 0, off_M = 0, off_T = 0, off_wtab = 0, off_gtab = 0, off_diag = 0, off_count = 0, off_eig = 0;
+  size_t eig_bytes = 0;
   std::vector<EigLayout> eig_L, eig_R, eig_mid[2];   // per bucket (eig_mid: the middle dimensions of tensor blocks)
   // tensor parameters: block-contiguous copies of the gradient and the parameter (byte offsets
   // into the workspace, 0 for other parameters), and a second scratch array the size of T
@@ -1133,7 +1198,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   const size_t offG1tab = take((size_t)c->n_params * sizeof(void *));
   const size_t offGftab = take((size_t)c->n_params * sizeof(void *));
   const size_t offPrep = (use_l2 || use_b1) ? take(std::max<size_t>(1, p.prep_chunks.size()) * sizeof(DiagChunk)) : 0;
-  size_t eig_bytes = 0, max_count = 1;
+  size_t eig_bytes = 0, max_count = 1, band_all = 0;
   std::vector<size_t> t_need;
   std::vector<EigLayout> eL, eR, eM[2];
   for (auto &b : p.buckets) {
@@ -1194,7 +1259,11 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     const int em = b.diagL ? 1 : b.m, en = b.diagR ? 1 : b.rdim();
     const bool warm = c->warm_start_roots != 0 && c->root_method == SHAMPOO_ROOT_EIGH && !b.t3;   // tensor blocks start cold
     const float r_exp = b.t3 ? 2.f * c->root_exponent / (float)b.modes : c->root_exponent;
-    auto eig = [&](int n_) { return eig_layout(n_, b.count, !warm && band_serves(n_, r_exp)); };
+    auto eig = [&](int n_) {
+      const EigLayout e = eig_layout(n_, b.count, !warm && band_serves(n_, r_exp));
+      if (e.band.bytes) band_all += band_layout_of(n_, b.count).bytes;
+      return e;
+    };
     eL.push_back(eig(em));
     eR.push_back(eig(en));
     if (warm && eL.back().np > 0) b.off_QtL = take(B * (size_t)eL.back().np * eL.back().np * 4);
@@ -1208,6 +1277,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
                                              std::max(eM[0].back().bytes, eM[1].back().bytes)));
     max_count = std::max(max_count, (size_t)b.count);
   }
+  // roots of all sizes at once where they fit into what one size may take (band_roots)
+  eig_bytes = std::max(eig_bytes, std::min(band_all, BAND_CHUNK_BYTES));
   // Sets of buckets whose scratch fits side by side into what the largest bucket needs, or SET_BYTES
   size_t t_bytes = 0, t2_bytes = 0;
   {
@@ -1250,7 +1321,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     o->off_A = offA; o->off_M = offM; o->off_T = offT;
     o->off_G1 = offG1; o->off_Gf = offGf; o->off_g1tab = offG1tab; o->off_gftab = offGftab; o->off_prep = offPrep;
     o->use_l2 = use_l2; o->use_b1 = use_b1; o->off_wtab = offW; o->off_gtab = offG;
-    o->off_diag = offD; o->off_count = offC; o->off_eig = offE;
+    o->off_diag = offD; o->off_count = offC; o->off_eig = offE; o->eig_bytes = eig_bytes;
     o->off_small = offSmall; o->n_small = n_small; o->small_half = small_half; o->n_prep_rest = p.n_prep_rest;
     o->eig_L = eL; o->eig_R = eR; o->eig_mid[0] = eM[0]; o->eig_mid[1] = eM[1];
     o->upper_stale.assign(o->plan.buckets.size(), 0);
@@ -1803,72 +1874,75 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       w.young = young_factor(step, cols, dim);
       return w;
     };
+    // Roots that need no eigenvectors wait until all of them are known, and are then taken together, by exponent; the others
+    // one batch after the other.
+    std::vector<RootJob> waiting;
+    auto take_root = [&](size_t off_factor, size_t off_root, int dim, int count, float r, const EigLayout &lay, const WarmStart &w) {
+      const float *F = reinterpret_cast<const float *>(ws + off_factor);
+      float *Fi = reinterpret_cast<float *>(ws + off_root);
+      RatTable table;
+      if (!w.qt && rat_table(r, table) && (dim <= JAC_SMALL_MAX || (lay.band.bytes && band_serves(dim, r)))) {
+        waiting.push_back(RootJob{F, dim, count, r, c2, Fi, nullptr, nullptr});
+        return (int)SHAMPOO_OK;
+      }
+      return root_inverse_batched(F, dim, count, c.epsilon, r, c2, Fi, nullptr, nullptr, fail_count, ws + o->off_eig, lay, s, &o->aux, nullptr, w);
+    };
     for (size_t i = 0; i < p.buckets.size(); ++i) {
       auto &b = p.buckets[i];
       if ((rc = complete_factors(o, i, s))) return rc;
-      if (b.whole()) {
-        // diagonal sides: elementwise root; full sides: the eigensolver
-        for (int side = 0; side < 2; ++side) {
-          const bool dg = side == 0 ? b.diagL : b.diagR;
-          const int dim = side == 0 ? b.m : b.n;
-          float *F = reinterpret_cast<float *>(ws + (side == 0 ? b.off_L : b.off_R));
-          float *Fi = reinterpret_cast<float *>(ws + (side == 0 ? b.off_Linv : b.off_Rinv));
-          if (dg) {
-            DiagRootArgs da;
-            da.vec = F; da.out = Fi; da.dim = dim; da.epsilon = c.epsilon; da.r = c.root_exponent; da.scale = c2;
-            da.fail_count = fail_count;
-            hipLaunchKernelGGL(diag_root_kernel, dim3(b.count), dim3(256), 0, s, da);
-            HIP_TRY(hipGetLastError());
-          } else {
-            rc = root_inverse_batched(F, dim, b.count, c.epsilon, c.root_exponent, c2, Fi, nullptr, nullptr, fail_count,
-                                      ws + o->off_eig, side == 0 ? o->eig_L[i] : o->eig_R[i], s, &o->aux, nullptr,
-                                      warm_of(side == 0 ? o->eig_L[i] : o->eig_R[i], side == 0 ? b.off_QtL : b.off_QtR,
-                                              side == 0 ? b.n : b.m, dim));
-            if (rc) return rc;
-          }
-        }
-        continue;
-      }
+      const bool newton = c.root_method == SHAMPOO_ROOT_NEWTON;
       if (b.t3) {
         // one root per dimension, exponent 2 r / w (Sec. 2.3: "root 2w")
         const float rw = 2.f * c.root_exponent / (float)b.modes;
-        int dims[4]; size_t fac[4], inv[4]; const EigLayout *lay[4];
         for (int k = 0; k < b.modes; ++k) {
-          dims[k] = b.td[k];
-          if (k == 0) { fac[k] = b.off_L; inv[k] = b.off_Linv; lay[k] = &o->eig_L[i]; }
-          else if (k == b.modes - 1) { fac[k] = b.off_R; inv[k] = b.off_Rinv; lay[k] = &o->eig_R[i]; }
-          else { fac[k] = b.off_mid[k - 1]; inv[k] = b.off_midinv[k - 1]; lay[k] = &o->eig_mid[k - 1][i]; }
-        }
-        for (int k = 0; k < b.modes; ++k) {
-          if (c.root_method == SHAMPOO_ROOT_NEWTON) {
-            rc = newton_root_guarded(o, reinterpret_cast<float *>(ws + fac[k]), dims[k], b.count, rw, c2,
-                                     reinterpret_cast<float *>(ws + inv[k]), *lay[k], s);
-          } else {
-            rc = root_inverse_batched(reinterpret_cast<float *>(ws + fac[k]), dims[k], b.count, c.epsilon, rw, c2,
-                                      reinterpret_cast<float *>(ws + inv[k]), nullptr, nullptr, fail_count,
-                                      ws + o->off_eig, *lay[k], s, &o->aux);
-          }
+          const bool first = k == 0, last = !first && k == b.modes - 1;
+          const size_t fac = first ? b.off_L : last ? b.off_R : b.off_mid[k - 1], inv = first ? b.off_Linv : last ? b.off_Rinv : b.off_midinv[k - 1];
+          const EigLayout &lay = first ? o->eig_L[i] : last ? o->eig_R[i] : o->eig_mid[k - 1][i];
+          if (newton) rc = newton_root_guarded(o, reinterpret_cast<float *>(ws + fac), b.td[k], b.count, rw, c2, reinterpret_cast<float *>(ws + inv), lay, s);
+          else rc = take_root(fac, inv, b.td[k], b.count, rw, lay, WarmStart());
           if (rc) return rc;
         }
         continue;
       }
-      if (c.root_method == SHAMPOO_ROOT_NEWTON) {
-        rc = newton_root_guarded(o, reinterpret_cast<float *>(ws + b.off_L), b.m, b.count, c.root_exponent, c2,
-                                 reinterpret_cast<float *>(ws + b.off_Linv), o->eig_L[i], s);
+      for (int side = 0; side < 2; ++side) {
+        const size_t fac = side == 0 ? b.off_L : b.off_R, inv = side == 0 ? b.off_Linv : b.off_Rinv;
+        const int dim = side == 0 ? b.m : b.n, cols = side == 0 ? b.n : b.m;
+        const EigLayout &lay = side == 0 ? o->eig_L[i] : o->eig_R[i];
+        if (side == 0 ? b.diagL : b.diagR) {
+          // diagonal sides: elementwise root
+          DiagRootArgs da;
+          da.vec = reinterpret_cast<float *>(ws + fac); da.out = reinterpret_cast<float *>(ws + inv); da.dim = dim; da.epsilon = c.epsilon;
+          da.r = c.root_exponent; da.scale = c2; da.fail_count = fail_count;
+          hipLaunchKernelGGL(diag_root_kernel, dim3(b.count), dim3(256), 0, s, da);
+          HIP_TRY(hipGetLastError());
+          continue;
+        }
+        if (newton && !b.whole())
+          rc = newton_root_guarded(o, reinterpret_cast<float *>(ws + fac), dim, b.count, c.root_exponent, c2, reinterpret_cast<float *>(ws + inv), lay, s);
+        else rc = take_root(fac, inv, dim, b.count, c.root_exponent, lay, warm_of(lay, side == 0 ? b.off_QtL : b.off_QtR, cols, dim));
         if (rc) return rc;
-        rc = newton_root_guarded(o, reinterpret_cast<float *>(ws + b.off_R), b.n, b.count, c.root_exponent, c2,
-                                 reinterpret_cast<float *>(ws + b.off_Rinv), o->eig_R[i], s);
-        if (rc) return rc;
-        continue;
       }
-      rc = root_inverse_batched(reinterpret_cast<float *>(ws + b.off_L), b.m, b.count, c.epsilon, c.root_exponent, c2,
-                                reinterpret_cast<float *>(ws + b.off_Linv), nullptr, nullptr, fail_count,
-                                ws + o->off_eig, o->eig_L[i], s, &o->aux, nullptr, warm_of(o->eig_L[i], b.off_QtL, b.n, b.m));
-      if (rc) return rc;
-      rc = root_inverse_batched(reinterpret_cast<float *>(ws + b.off_R), b.n, b.count, c.epsilon, c.root_exponent, c2,
-                                reinterpret_cast<float *>(ws + b.off_Rinv), nullptr, nullptr, fail_count,
-                                ws + o->off_eig, o->eig_R[i], s, &o->aux, nullptr, warm_of(o->eig_R[i], b.off_QtR, b.m, b.n));
-      if (rc) return rc;
+    }
+    while (!waiting.empty()) {
+      const float r = waiting[0].r;
+      std::vector<RootJob> small, band, rest;
+      for (const RootJob &j : waiting) (j.r != r ? rest : j.n <= JAC_SMALL_MAX ? small : band).push_back(j);
+      RatTable table;
+      if (!rat_table(r, table)) return SHAMPOO_ERR_HYPER;
+      // small matrices beside the large ones, on a stream that those do not use
+      AuxStreams *aux = !band.empty() && o->aux.ready() ? &o->aux : nullptr;
+      const bool beside = aux && !small.empty();
+      if (beside) {
+        HIP_TRY(hipEventRecord(aux->fork, s));
+        HIP_TRY(hipStreamWaitEvent(aux->stream[BAND_STREAMS - 1], aux->fork, 0));
+      }
+      if (!small.empty() && (rc = tridiag_roots(small, c.epsilon, fail_count, beside ? aux->stream[BAND_STREAMS - 1] : s, table))) return rc;
+      if (!band.empty() && (rc = band_roots(band, c.epsilon, fail_count, ws + o->off_eig, o->eig_bytes, s, aux, table))) return rc;
+      if (beside) {
+        HIP_TRY(hipEventRecord(aux->join[BAND_STREAMS - 1], aux->stream[BAND_STREAMS - 1]));
+        HIP_TRY(hipStreamWaitEvent(s, aux->join[BAND_STREAMS - 1], 0));
+      }
+      waiting.swap(rest);
     }
     o->n_refresh++;
     if ((rc = split_roots(o, s))) return rc;

@@ -1,0 +1,42 @@
+"""Roots of buckets of many sizes in one refresh (csrc/group.h): every launch serves all of them, each at its own panel. Against
+the fp64 oracle's roots of the same factors."""
+import numpy as np
+import pytest
+
+from oracle import shampoo_oracle as so
+from paper_2309_06497_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+MATRIX = [(B.GET_L, B.GET_LINV), (B.GET_R, B.GET_RINV)]
+TENSOR = {3: MATRIX + [(B.GET_L2, B.GET_L2INV)], 4: MATRIX + [(B.GET_L2, B.GET_L2INV), (B.GET_L3, B.GET_L3INV)]}
+
+
+# sizes on both sides of the kernels' classes: 32, 64 and 128 in LDS; panels of 256, 512 and 1024 rows
+@pytest.mark.parametrize("shapes,block", [
+    ([(20, 33), (64, 65), (128, 129), (130, 257), (300, 513)], 1024),
+    ([(1056, 40), (161, 1025), (7, 128)], 2048),
+    ([(700, 333)], 256),                                        # four buckets, the full one has two blocks
+    ([(40, 130, 9), (16, 150, 3, 3), (200, 96)], 256),          # exponents 1/6 and 1/8 beside 1/4
+])
+def test_roots_of_a_refresh(shapes, block):
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    opt = B.Shampoo(shapes, block, 0.99, 1e-12, 0.25, 1, 0)
+    w = [torch.zeros(s, device="cuda") for s in shapes]
+    for t in range(3):
+        opt.step(w, [torch.randn(s, device="cuda", generator=gen) * 1e-2 for s in shapes], 0.01, t)
+    table, buckets = opt.plan()
+    assert buckets >= 3 and opt.status()["failed_roots"] == 0
+    count = {}
+    for row in table:
+        p, flags = int(row[0]), int(row[7])
+        k = count[p] = count.get(p, -1) + 1
+        modes = flags >> 4 if flags & 4 else 2
+        for factor, root in TENSOR[modes] if flags & 4 else MATRIX:
+            a, x = opt.get(p, k, factor).cpu().numpy(), opt.get(p, k, root).cpu().numpy()
+            want, _ = so.root_inverse(a, float(np.float32(1e-12)), 0.5 / modes)
+            err = np.linalg.norm(x - want) / np.linalg.norm(want)
+            print(f"    {shapes[p]} block {k} n={a.shape[0]}: {err:.1e}", flush=True)
+            assert np.array_equal(x, x.T) and err <= 1e-5, (p, k, a.shape, err)      # as for one size at a time
