@@ -43,7 +43,8 @@ constexpr int BAND = 32;                 // block size: half bandwidth of B
 constexpr int BAND_MAX_N = 2048;
 constexpr int BAND_SHIFTS = 32;          // shifts tried per round of the bisection
 constexpr int BAND_ROUNDS = 12;          // 33^11 covers 2^53
-constexpr int BAND_ROWS = 128;           // rows per workgroup of the panel products
+constexpr int BAND_ROWS = 128;           // rows per workgroup of Y and of the rank-64 update
+constexpr int BAND_ZROWS = 64;           // rows per workgroup of Z = W V
 constexpr int BAND_COLS = 128;           // columns per workgroup of the rank-64 update
 constexpr int BAND_GROUP = 4;            // panels per block reflector of the way back
 constexpr int BAND_GW = BAND_GROUP * BAND;   // its columns
@@ -67,9 +68,9 @@ struct BandArgs {
   float eps, r, scale;
   float *x; int32_t *failed_user; unsigned long long *fail_count; const int32_t *only;
   BandMeta *meta;
-  double *w;        // [np][np]: the matrix being reduced
+  double *w;        // [np][np]: the matrix being reduced, in the 32 x 32 blocks on and below the diagonal
   float *f;         // [np][np], in the memory of w: F, then X
-  double *vp, *z, *y, *t, *part;         // current panel: V, Z, Y [np][32], T [32][32], partial sums of V^T Z [np / 128][32][32]
+  double *vp, *z, *y, *t, *part;         // current panel: V, Z, Y [np][32], T [32][32], partial sums of V^T Z [np / 64][32][32]
   float *vall, *tall;                    // all panels: V [np][np], panel k in columns 32 k ...; T [nb - 1][32][32]
   double *dblk, *cblk;                   // B: diagonal blocks [nb][32][32], transposed sub-diagonal blocks [nb][32][32]
   double *kf, *gf;                       // per slot and block: -K^T (A operand order) and weight * G (D order), [BAND_SLOTS][nb][1024]
@@ -101,6 +102,7 @@ typedef Group<BandJob, BAND_TABLE_RESERVE> BandTableJobs;
 // rows and workgroups of a panel's products
 __host__ __device__ inline int band_left(const BandArgs &g, int k) { return g.np - (k + 1) * BAND; }
 __host__ __device__ inline int band_row_wgs(const BandArgs &g, int k) { const int m = band_left(g, k); return (m + BAND_ROWS - 1) / BAND_ROWS; }
+__host__ __device__ inline int band_z_wgs(const BandArgs &g, int k) { const int m = band_left(g, k); return (m + BAND_ZROWS - 1) / BAND_ZROWS; }
 __host__ __device__ inline int band_col_wgs(const BandArgs &g, int k) { const int m = band_left(g, k); return (m + BAND_COLS - 1) / BAND_COLS; }
 __host__ __device__ inline int band_groups(const BandArgs &g) { return (g.nb - 1 + BAND_GROUP - 1) / BAND_GROUP; }
 // Arrays of the way back, in the memory of kf and gf, which nothing reads any more by then: the work array
@@ -119,7 +121,7 @@ __host__ __device__ inline void band_select(BandArgs &g, int b) {
   g.meta += b;
   g.w += b * np * np; g.f += b * np * np * 2;
   g.vp += b * np * BAND; g.z += b * np * BAND; g.y += b * np * BAND; g.t += (int64_t)b * 1024;
-  const int64_t parts = (np + BAND_ROWS - 1) / BAND_ROWS;
+  const int64_t parts = (np + BAND_ZROWS - 1) / BAND_ZROWS;
   g.part += b * parts * 1024;
   g.vall += b * np * np; g.tall += b * nb * 1024;
   g.dblk += b * nb * 1024; g.cblk += b * nb * 1024;
@@ -171,8 +173,10 @@ __global__ __launch_bounds__(256) void band_init_kernel(const BandJobs grp) {
       v[e] = (double)g.scale * (0.5 * ((double)Xs[r][c4 + e] + (double)Ys[c4 + e][r]));
       if (gi != bc * BAND + c4 + e && v[e] != 0.0) any = 1;
     }
-    double2 *dst = reinterpret_cast<double2 *>(g.w + (int64_t)gi * np + bc * BAND + c4);
-    dst[0] = make_double2(v[0], v[1]); dst[1] = make_double2(v[2], v[3]);
+    if (bc <= br) {
+      double2 *dst = reinterpret_cast<double2 *>(g.w + (int64_t)gi * np + bc * BAND + c4);
+      dst[0] = make_double2(v[0], v[1]); dst[1] = make_double2(v[2], v[3]);
+    }
     __syncthreads();
   }
   if (any) coupled[r] = 1;
@@ -438,64 +442,85 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
 // r0 ... np - 1, r0 = 32 (k + 1).
 // ---------------------------------------------------------------------------
 // Z = W[r0:, r0:] V[r0:] and, per workgroup, its rows' share of V^T Z.
-// Workgroups: ceil((np - r0) / 128) per matrix, 4 wavefronts of 32 rows.  Memory bound (every element of W is
-// read once for 64 multiply-adds); a lane reads 4 consecutive k of its row.
-__global__ __launch_bounds__(256) void band_z_kernel(const BandJobs grp) {
-  __shared__ double red[4][1024];
-  BAND_PICK(band_row_wgs(g, k))
+// Workgroups: ceil((np - r0) / 64) per matrix, 8 wavefronts: 2 of 32 rows by 4 quarters of k, which meet in LDS, so that few
+// matrices fill the GPU too.  Bound by memory and by the latency of its loads (every element of W is read once for 64
+// multiply-adds).  What lies to the right of the diagonal blocks is read from its mirror image below them.
+// 8 matrices of 2048 beside 8 others, the average panel: TIME_Z.
+__global__ __launch_bounds__(512) void band_z_kernel(const BandJobs grp) {
+  __shared__ double red[8][16 * 64];
+  BAND_PICK(band_z_wgs(g, k))
   band_select(g, b);
   if (g.meta->skip) return;
   const int r0 = (k + 1) * BAND;
-  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int base = r0 + BAND_ROWS * bx + BAND * w;
-  band_d4 m1[2][2];
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lg = lane >> 4;
+  const int rg = w & 1, kq = w >> 1, base = r0 + BAND_ZROWS * bx + BAND * rg;
+  band_d4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) m1[i][j] = (band_d4){0, 0, 0, 0};
+    for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0, 0, 0, 0};
   if (base < np) {
-    band_d4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0, 0, 0, 0};
-    const double *wr[2] = {g.w + (int64_t)(base + li) * np + 4 * lg, g.w + (int64_t)(base + 16 + li) * np + 4 * lg};
+    const int steps = (np - r0) / 16, s1 = steps * (kq + 1) / 4, diag = (base + BAND - r0) / 16;
+    int s = steps * kq / 4;
     const double *vr = g.vp + (int64_t)(4 * lg) * BAND + li;
-#pragma unroll 2
-    for (int k0 = r0; k0 < np; k0 += 16) {
-      const band_d4 a0 = *reinterpret_cast<const band_d4 *>(wr[0] + k0), a1 = *reinterpret_cast<const band_d4 *>(wr[1] + k0);
+    auto product = [&](int k0, const band_d4 &a0, const band_d4 &a1) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const double b0 = vr[(int64_t)(k0 + q) * BAND], b1 = vr[(int64_t)(k0 + q) * BAND + 16];
         acc[0][0] = band_mfma(a0[q], b0, acc[0][0]); acc[0][1] = band_mfma(a0[q], b1, acc[0][1]);
         acc[1][0] = band_mfma(a1[q], b0, acc[1][0]); acc[1][1] = band_mfma(a1[q], b1, acc[1][1]);
       }
+    };
+    const double *row = g.w + (int64_t)(base + li) * np + 4 * lg;         // a lane reads 4 consecutive k of its rows
+#pragma unroll 2
+    for (const int e = min(s1, diag); s < e; ++s) {
+      const int k0 = r0 + 16 * s;
+      product(k0, *reinterpret_cast<const band_d4 *>(row + k0), *reinterpret_cast<const band_d4 *>(row + (int64_t)16 * np + k0));
     }
+    const double *col = g.w + (int64_t)(4 * lg) * np + base + li;         // or the same elements of a column
+#pragma unroll 2
+    for (; s < s1; ++s) {
+      const int k0 = r0 + 16 * s;
+      band_d4 a0, a1;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = base + 16 * rt + band_row(lg, v);
-        g.z[(int64_t)row * BAND + li] = acc[rt][0][v];
-        g.z[(int64_t)row * BAND + 16 + li] = acc[rt][1][v];
-        {
-          const double v0 = g.vp[(int64_t)row * BAND + li], v1 = g.vp[(int64_t)row * BAND + 16 + li];
-          m1[0][0] = band_mfma(v0, acc[rt][0][v], m1[0][0]); m1[0][1] = band_mfma(v0, acc[rt][1][v], m1[0][1]);
-          m1[1][0] = band_mfma(v1, acc[rt][0][v], m1[1][0]); m1[1][1] = band_mfma(v1, acc[rt][1][v], m1[1][1]);
-        }
-      }
+      for (int q = 0; q < 4; ++q) { a0[q] = col[(int64_t)(k0 + q) * np]; a1[q] = col[(int64_t)(k0 + q) * np + 16]; }
+      product(k0, a0, a1);
+    }
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[w][(16 * i + band_row(lg, v)) * BAND + 16 * j + li] = m1[i][j][v];
+      for (int v = 0; v < 4; ++v) red[w][((2 * i + j) * 4 + v) * 64 + lane] = acc[i][j][v];
   __syncthreads();
-  for (int e = tid; e < 1024; e += 256) g.part[(int64_t)bx * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+  // wavefront (rg, kq): the tile (kq / 2, kq % 2) of its rows, and what it gives to V^T Z
+  const int rt = kq >> 1, j = kq & 1;
+  band_d4 z, m0 = {0, 0, 0, 0}, m1 = {0, 0, 0, 0};
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int at = (4 * kq + v) * 64 + lane;
+    z[v] = (red[rg][at] + red[2 + rg][at]) + (red[4 + rg][at] + red[6 + rg][at]);
+  }
+  if (base < np)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t at = (int64_t)(base + 16 * rt + band_row(lg, v)) * BAND + li;
+      g.z[at + 16 * j] = z[v];
+      m0 = band_mfma(g.vp[at], z[v], m0);
+      m1 = band_mfma(g.vp[at + 16], z[v], m1);
+    }
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    red[2 * rt + rg][band_row(lg, v) * BAND + 16 * j + li] = m0[v];
+    red[2 * rt + rg][(16 + band_row(lg, v)) * BAND + 16 * j + li] = m1[v];
+  }
+  __syncthreads();
+  for (int e = tid; e < 1024; e += 512) g.part[(int64_t)bx * 1024 + e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
-// Y = Z T - V (T^T M T) / 2 with M = V^T Z.  workgroups as above
+// Y = Z T - V (T^T M T) / 2 with M = V^T Z.  Workgroups: ceil((np - r0) / 128) per matrix, 4 wavefronts of 32 rows.
 __global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
   __shared__ double M[BAND][BAND + 1], Tm[BAND][BAND + 1], S[BAND][BAND + 1];
   BAND_PICK(band_row_wgs(g, k))
@@ -504,10 +529,15 @@ __global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
   const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int base = r0 + BAND_ROWS * bx + BAND * w;
-  for (int e = tid; e < 1024; e += 256) {
-    double s = 0.0;
-    for (int q = 0; q < per_; ++q) s += g.part[(int64_t)q * 1024 + e];
-    M[e >> 5][e & 31] = s;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int q = 0, parts = band_z_wgs(g, k); q < parts; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] += g.part[(int64_t)q * 1024 + tid + 256 * i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int e = tid + 256 * i;
+    M[e >> 5][e & 31] = s[i];
     Tm[e >> 5][e & 31] = g.t[e];
   }
   __syncthreads();
@@ -554,10 +584,9 @@ __global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
   }
 }
 
-// W <- W - V Y^T - Y V^T on rows and columns r0 ....  workgroups: the square of ceil((np - r0) / 128) per matrix, 4
-// wavefronts of 32 rows, which keep their rows of V and Y in registers and walk along the columns together, 16 at a
-// time.  Memory bound, 3.3 TB/s for 64 matrices of 1024.  Blocks below the diagonal only, with their mirror images stored
-// from the same registers, took 1 % off 16 matrices of 2048 and added 0.4 % to 64 of 1024: not kept.
+// W <- W - V Y^T - Y V^T on rows and columns r0 ..., up to the diagonal blocks.  workgroups: the square of
+// ceil((np - r0) / 128) per matrix, 4 wavefronts of 32 rows, which keep their rows of V and Y in registers and walk along the
+// columns together, 16 at a time.  Memory bound.  The whole square, a second copy of every element for Z to read: TIME_UPD
 __global__ __launch_bounds__(256) void band_update_kernel(const BandJobs grp) {
   BAND_PICK(band_row_wgs(g, k) * band_col_wgs(g, k))
   const int rows = band_row_wgs(g, k), by = bx / rows;
@@ -567,7 +596,8 @@ __global__ __launch_bounds__(256) void band_update_kernel(const BandJobs grp) {
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int base = r0 + BAND_ROWS * (bx - rows * by) + BAND * w;
   if (base >= np) return;
-  const int c0 = r0 + BAND_COLS * by, c1 = min(c0 + BAND_COLS, np);
+  const int c0 = r0 + BAND_COLS * by, c1 = min(c0 + BAND_COLS, base + BAND);
+  if (c0 >= c1) return;
   band_d4 va[2][2], ya[2][2];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
@@ -1180,58 +1210,85 @@ __global__ __launch_bounds__(256) void band_stage_kernel(const BandJobs grp) {
   }
 }
 
-// M = V^T Z and [T^T; -T M T^T / 2].  16 wavefronts of 32 x 32 results each; one workgroup per
-// matrix, since the second product needs all of the first (158 us for 32 matrices of 1024 beside 32 others).  On the fp64 matrix cores:
-// float32 sums here cost more accuracy than the roundings of everything else on the way back together, and 135 us.
-__global__ __launch_bounds__(1024) void band_s_kernel(const BandJobs grp) {
-  __shared__ float M[BAND_GW][BAND_GW + 1], T[BAND_GW][BAND_GW + 1];
-  BAND_PICK(1)
+// M = V^T Z and M T^T, which goes where Y will be read from.  4 workgroups of 16 wavefronts per matrix: 32 rows of M each, 4
+// blocks of 32 columns by 4 quarters of V's rows.  On the fp64 matrix cores: float32 sums here cost more accuracy than the
+// roundings of everything else on the way back together.  Bound by them: one workgroup per matrix for this and the next
+// kernel's product took 158 us for 32 matrices of 1024 beside 32 others, TIME_S.
+__global__ __launch_bounds__(1024) void band_m_kernel(const BandJobs grp) {
+  __shared__ float M[BAND][BAND_GW + 1], T[BAND_GW][BAND_GW + 1];
+  __shared__ double red[16][4 * 64];
+  BAND_PICK(4)
   const int q = k;
   band_select(g, b);
   if (g.meta->skip) return;
-  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
-  const int i0 = 32 * (w >> 2), j0 = 32 * (w & 3);
+  const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lg = lane >> 4;
+  const int i0 = 32 * bx, j0 = 32 * (w & 3), kq = w >> 2;
   const float *tg = band_tg(g) + (int64_t)q * BAND_GW * BAND_GW;
   for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) T[x / BAND_GW][x % BAND_GW] = tg[x];
   band_d4 acc[2][2];
-  auto clear = [&]() {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0.0, 0.0, 0.0, 0.0};
-  };
-  auto product = [&](double a0, double a1, double b0, double b1) {
+    for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0.0, 0.0, 0.0, 0.0};
+  const float *p = band_p(g) + (int64_t)lg * BAND_PLD + li;
+  const int first = (BAND_GROUP * q + 1) * BAND, steps = (np - first) / 16;
+  for (int s = steps * kq / 4, e = steps * (kq + 1) / 4; s < e; ++s)
+#pragma unroll
+    for (int t = 0; t < 16; t += 4) {
+      const float *z = p + (int64_t)(first + 16 * s + t) * BAND_PLD, *v = z + BAND_GW;
+      const double a0 = v[i0], a1 = v[i0 + 16], b0 = z[j0], b1 = z[j0 + 16];
+      acc[0][0] = band_mfma(a0, b0, acc[0][0]); acc[0][1] = band_mfma(a0, b1, acc[0][1]);
+      acc[1][0] = band_mfma(a1, b0, acc[1][0]); acc[1][1] = band_mfma(a1, b1, acc[1][1]);
+    }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {              // tile by tile: the sums of four quarters
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) red[w][u * 64 + lane] = acc[x >> 1][x & 1][u];
+    __syncthreads();
+    const int at = kq * 64 + lane, jb = w & 3;      // element kq of the tile
+    const double sum = (red[jb][at] + red[4 + jb][at]) + (red[8 + jb][at] + red[12 + jb][at]);
+    M[16 * (x >> 1) + band_row(lg, kq)][32 * jb + 16 * (x & 1) + li] = (float)sum;
+  }
+  __syncthreads();
+  // 32 x 128 results: a tile of 16 x 16 per wavefront
+  const int ti = 16 * (w & 1), tj = 16 * (w >> 1);
+  band_d4 n = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int s = 0; s < BAND_GW / 4; ++s) n = band_mfma((double)M[ti + li][4 * s + lg], (double)T[tj + li][4 * s + lg], n);
+  float *out = band_ts(g);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) out[(BAND_GW + i0 + ti + band_row(lg, u)) * BAND_GW + tj + li] = (float)n[u];
+}
+
+// [T^T; -T (M T^T) / 2], the second half in the place of M T^T.  4 workgroups of 4 wavefronts per matrix: 32 columns each.
+__global__ __launch_bounds__(256) void band_s_kernel(const BandJobs grp) {
+  __shared__ float N[BAND_GW][BAND + 1];
+  BAND_PICK(4)
+  const int q = k;
+  band_select(g, b);
+  if (g.meta->skip) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4, i0 = 32 * w, j0 = 32 * bx;
+  const float *tg = band_tg(g) + (int64_t)q * BAND_GW * BAND_GW;
+  float *out = band_ts(g);
+  for (int x = tid; x < BAND_GW * BAND; x += 256) {
+    const int row = x / BAND, col = x % BAND;
+    N[row][col] = out[(BAND_GW + row) * BAND_GW + j0 + col];
+    out[(j0 + col) * BAND_GW + row] = tg[row * BAND_GW + j0 + col];
+  }
+  __syncthreads();
+  band_d4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (band_d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int s = 0; s < BAND_GW / 4; ++s) {
+    const int x = 4 * s + lg;
+    const double a0 = tg[(i0 + li) * BAND_GW + x], a1 = tg[(i0 + 16 + li) * BAND_GW + x], b0 = N[x][li], b1 = N[x][16 + li];
     acc[0][0] = band_mfma(a0, b0, acc[0][0]); acc[0][1] = band_mfma(a0, b1, acc[0][1]);
     acc[1][0] = band_mfma(a1, b0, acc[1][0]); acc[1][1] = band_mfma(a1, b1, acc[1][1]);
-  };
-  clear();
-  const float *p = band_p(g) + (int64_t)lg * BAND_PLD + li;
-  for (int r = (BAND_GROUP * q + 1) * BAND; r < np; r += BAND)
-#pragma unroll
-    for (int t = 0; t < BAND; t += 4) {
-      const float *z = p + (int64_t)(r + t) * BAND_PLD, *v = z + BAND_GW;
-      product(v[i0], v[i0 + 16], z[j0], z[j0 + 16]);
-    }
-  auto put = [&]() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) M[i0 + 16 * i + band_row(lg, u)][j0 + 16 * j + li] = (float)acc[i][j][u];
-  };
-  put();
-  __syncthreads();
-  clear();
-#pragma unroll 8
-  for (int s = 0; s < BAND_GW / 4; ++s) product(M[i0 + li][4 * s + lg], M[i0 + 16 + li][4 * s + lg], T[j0 + li][4 * s + lg], T[j0 + 16 + li][4 * s + lg]);
-  __syncthreads();
-  put();
-  __syncthreads();
-  clear();
-#pragma unroll 8
-  for (int s = 0; s < BAND_GW / 4; ++s) product(T[i0 + li][4 * s + lg], T[i0 + 16 + li][4 * s + lg], M[4 * s + lg][j0 + li], M[4 * s + lg][j0 + 16 + li]);
-  float *out = band_ts(g);
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -1239,7 +1296,6 @@ __global__ __launch_bounds__(1024) void band_s_kernel(const BandJobs grp) {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         out[(BAND_GW + i0 + 16 * i + band_row(lg, u)) * BAND_GW + j0 + 16 * j + li] = (float)(-0.5 * acc[i][j][u]);
-  for (int x = tid; x < BAND_GW * BAND_GW; x += 1024) out[x] = T[x % BAND_GW][x / BAND_GW];
 }
 
 // x from the lower triangle of F, mirrored; the rows that stand alone.  a workgroup of 256 threads per pair of 32 x 32 tiles and matrix

@@ -409,7 +409,7 @@ BandLayout band_layout_of(int n, int cnt) {
   BandLayout e;
   if (n > BAND_MAX_N) return e;
   e.np = (n + BAND - 1) / BAND * BAND; e.nb = e.np / BAND;
-  const size_t np = e.np, blk = (size_t)e.nb * BAND * BAND, parts = (np + BAND_ROWS - 1) / BAND_ROWS;
+  const size_t np = e.np, blk = (size_t)e.nb * BAND * BAND, parts = (np + BAND_ZROWS - 1) / BAND_ZROWS;
   size_t off = 0;
   auto take = [&](size_t per) { const size_t at = off; off += align_up(per * (size_t)cnt); return at; };
   e.off_w = take(np * np * 8); e.off_vall = take(np * np * 4);
@@ -776,7 +776,8 @@ struct BandSolve {
     const Kernel qr = m <= 256 ? band_qr_kernel<8> : m <= 512 ? band_qr_kernel<16> : m <= 1024 ? band_qr_kernel<32> : band_qr_kernel<64>;
     if ((rc = each(qr, BAND_QR_THREADS, [&](BandJob &j) { return p < j.g.nb ? j.cnt : 0; }))) return rc;
     auto rows = [&](BandJob &j) { return p + 1 < j.g.nb ? (int64_t)band_row_wgs(j.g, p) * j.cnt : 0; };
-    if ((rc = each(band_z_kernel, 256, rows)) || (rc = each(band_y_kernel, 256, rows))) return rc;
+    if ((rc = each(band_z_kernel, 512, [&](BandJob &j) { return p + 1 < j.g.nb ? (int64_t)band_z_wgs(j.g, p) * j.cnt : 0; }))) return rc;
+    if ((rc = each(band_y_kernel, 256, rows))) return rc;
     return each(band_update_kernel, 256, [&](BandJob &j) { return rows(j) * (p + 1 < j.g.nb ? band_col_wgs(j.g, p) : 0); });
   }
   int function() {
@@ -836,7 +837,8 @@ struct BandSolve {
     }
     auto stage = [&](BandJob &j) { return takes_part(j) ? (int64_t)(j.g.np / 8) * j.cnt : 0; };
     if ((rc = each(band_stage_kernel<false>, 256, stage)) || (rc = zs.flush())) return rc;
-    if ((rc = each(band_s_kernel, 1024, [&](BandJob &j) { return takes_part(j) ? j.cnt : 0; })) || (rc = ys.flush())) return rc;
+    auto four = [&](BandJob &j) { return takes_part(j) ? (int64_t)4 * j.cnt : 0; };
+    if ((rc = each(band_m_kernel, 1024, four)) || (rc = each(band_s_kernel, 256, four)) || (rc = ys.flush())) return rc;
     if ((rc = each(band_stage_kernel<true>, 256, stage)) || (rc = us64.flush())) return rc;
     return us.flush();
   }
