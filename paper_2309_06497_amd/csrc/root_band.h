@@ -249,15 +249,6 @@ template <int J> __device__ __forceinline__ void row16_fma(double &x, double y, 
   asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(y), "v"(q), "n"(J));
 }
 template <int J> __device__ __forceinline__ double row16_bcast(double x) { return dpp_fetch<0x150 + J>(x); }
-// sum over the four lanes l % 16, in all of them
-__device__ __forceinline__ double rows_sum(double x) {
-  auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
-  auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
-  x = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-  lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
-  hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
-  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
 
 // One element per lane and row block of a column of a row-major array: lane address and scalar step, in elements
 struct BandColumn {

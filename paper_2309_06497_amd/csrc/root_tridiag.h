@@ -93,6 +93,19 @@ template <int RB> __device__ __forceinline__ double row16_sums(const double (&v)
   return x + dpp_fetch<DPP_XOR1>(x);
 }
 
+// sum over the four lanes l % 16, in all of them
+__device__ __forceinline__ double rows_sum(double x) {
+  auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+  auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+  x = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+  lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+  hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+typedef double tri_d4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ tri_d4 tri_mfma(double a, double b, tri_d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
 // f(BlockIndex<0>()), ..., f(BlockIndex<COUNT - 1>()): a loop whose index is a constant in the body
 template <int I> struct BlockIndex { static constexpr int value = I; };
 template <int COUNT, int I = 0, typename F> __device__ __forceinline__ void for_each_block(F &&f) {
@@ -110,14 +123,21 @@ __device__ __forceinline__ bool tri_above(const double *d, const double *e, int 
   return ok;
 }
 
+// The way back: 16 reflectors at a time.  The strides leave no bank conflicts but for a few lanes, along rows and across them.
+template <int N> struct TriBack {
+  float v[16][N + 20];                       // V^T
+  double y[16][N + 18];                      // Z^T, shares of M, Y^T; S = V^T V of all groups, 256 entries each
+  double t[N / 16][256];                     // T^T of all groups
+};
 template <int N> struct TriShared {
   double d[N], e[N], v1[N];                  // T; the eigenvector handled by itself
   double beta[N];                            // reflector k: 2 / v.v, or 0 where there is none
   union {
     struct {
       union {
-        struct { double x[3][N], p[2][N]; } step;             // vectors of the current reflection
+        struct { double x[N], p[N], s2[4], vav[4]; } step;    // vectors of the current reflection, wavefronts' sums
         struct { double slot[N * RAT_MAX_POLES]; float chunk[TRI_CHUNK][N]; } fun;
+        TriBack<N> back;
       };
       float vs[(N - 1) * (N - 2) / 2];       // reflector k: entries k + 2 .. n - 1 (entry k + 1 is 1)
     };
@@ -139,18 +159,29 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   if (b >= g.batch || (g.only && g.only[b] == 0)) return;
   __shared__ __align__(16) TriShared<N> sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & 15, rg = tid >> 4;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int n = g.n;
   const float *a = g.a + (int64_t)b * g.a_stride;
+  auto wave_sums = [](const double *s) { return NT == 64 ? s[0] : NT == 128 ? s[0] + s[1] : (s[0] + s[1]) + (s[2] + s[3]); };
 
   // ---- load (symmetrised), find what is not finite and the rows that stand alone ----
   double A[RB][CB];
   int bad = 0;
-  for (int i = wave; i < n; i += NT / 64)
-    for (int j = lane; j < n; j += 64) {
-      const float v = a[(int64_t)i * n + j];
-      if (!(fabsf(v) <= 3.0e38f)) bad = 1;
-      sh.out[i][j] = v;
+  // element e is in row e / n: e n < 2^32.  16 loads in flight (one at a time took 42 us for 64 KB)
+  const uint32_t over_n = (uint32_t)((1ull << 32) / n) + ((n & (n - 1)) != 0 ? 1u : 0u);
+  auto row_of = [&](int e) { return n == 1 ? 0 : (int)__umulhi((uint32_t)e, over_n); };
+  for (int e0 = tid; e0 < n * n; e0 += 16 * NT) {
+    float v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) { const int e = e0 + NT * t; v[t] = a[e < n * n ? e : 0]; }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int e = e0 + NT * t, i = row_of(e);
+      if (e >= n * n) continue;
+      if (!(fabsf(v[t]) <= 3.0e38f)) bad = 1;
+      sh.out[i][e - i * n] = v[t];
     }
+  }
   for (int i = tid; i < N; i += NT) sh.dec[i] = 1;
   __syncthreads();
 #pragma unroll
@@ -181,11 +212,11 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   for (int p = 0; p < RB; ++p)
 #pragma unroll
     for (int q = 0; q < CB; ++q)
-      if (rg + RG * p == cl + 16 * q) sh.step.x[0][rg + RG * p] = A[p][q];
+      if (rg + RG * p == cl + 16 * q) sh.step.x[rg + RG * p] = A[p][q];
   __syncthreads();
   double dec_min = 1.0e300, fill = -1.0e300;
   for (int i = lane; i < n; i += 64) {
-    const double v = sh.step.x[0][i];
+    const double v = sh.step.x[i];
     if (sh.dec[i]) dec_min = fmin(dec_min, v); else fill = fmax(fill, v);
   }
 #pragma unroll
@@ -206,10 +237,26 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // Columns 16 KQ .. 16 KQ + 15: the blocks left of and above them are finished and drop out of the
   // code (the whole similarity transform is applied to the others: what it does to finished rows and
   // columns inside them is to turn them into T).
+  // Bound by the latency of a reflection.  The update of A that belongs to one is done in the next: its first block column
+  // ahead of the barrier behind which the next column can be read, the rest beside the chain from that column's norm to its
+  // reflector.  Norm and v^T A v are summed within the wavefronts ahead of the barriers that are there anyway.  3072 matrices of 128 x 128, two
+  // workgroups per CU: 3590 cycles per reflection before, TIME_RED so.
+  double vr[RB], qr[RB], vc[CB], qc[CB];         // rows and columns of v and q: A <- A - v q^T - q v^T is to be done
+#pragma unroll
+  for (int p = 0; p < RB; ++p) vr[p] = qr[p] = 0.0;
+#pragma unroll
+  for (int q = 0; q < CB; ++q) vc[q] = qc[q] = 0.0;
   auto reduce16 = [&](auto kq) {
-    constexpr int KQ = decltype(kq)::value, P0 = 16 * KQ / RG, P1 = 16 * KQ / RG + 16 / RG;   // row blocks P0 .. P1 - 1: rows 16 KQ .. 16 KQ + 15
+    constexpr int KQ = decltype(kq)::value, P0 = 16 * KQ / RG, P1 = P0 + 16 / RG, P2 = P1 + 16 / RG;  // row blocks P0 .. P1 - 1: rows 16 KQ .. 16 KQ + 15
     for (int k = 16 * KQ; k < min(16 * KQ + 16, n - 1); ++k) {
-      double *xb = sh.step.x[k & 1], *pb = sh.step.p[0];
+      double *xb = sh.step.x, *pb = sh.step.p;
+      double s2 = 0.0;
+#pragma unroll
+      for (int p = P0; p < RB; ++p) {
+        A[p][KQ] = fma(-vr[p], qc[KQ], fma(-qr[p], vc[KQ], A[p][KQ]));
+        const double x = (p >= P2 || rg + RG * p > k + 1) ? A[p][KQ] : 0.0;
+        s2 = fma(x, x, s2);
+      }
       if (cl == (k & 15)) {
 #pragma unroll
         for (int p = P0; p < RB; ++p) {
@@ -218,62 +265,49 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
           if (p < P1 && r == k) sh.d[k] = A[p][KQ];
         }
       }
-      if (KQ > 0 && (k & 15) < 2) for (int i = tid; i < 16 * KQ; i += NT) xb[i] = 0.0;      // what the blocks before left there
+      s2 = rows_sum(s2);
+      if (lane == (k & 15)) sh.step.s2[wave] = s2;
       __syncthreads();
-      double s2 = 0.0;
-#pragma unroll
-      for (int h = 0; h < (N + 63) / 64; ++h) {
-        const int i = lane + 64 * h;
-        if (N % 64 == 0 || i < N) { const double v = xb[i]; if (i != k + 1) s2 += v * v; }
-      }
-      s2 = wave64_sum(s2);
+      s2 = wave_sums(sh.step.s2);
       const double x0 = xb[k + 1];
-      if (!(s2 > TRI_NO_COLUMN)) {       // nothing to reflect
-        if (tid == 0) { sh.beta[k] = 0.0; sh.e[k] = x0; }
-        for (int i = tid; i < n; i += NT) if (i > k + 1) sh.vs[offs(k) + i] = 0.f;
-        continue;
-      }
-      const double nn = x0 * x0 + s2, norm = nn * rsqrt_newton(nn);
-      const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, beta = rcp_newton(norm * fabs(v0));
-      double vc[CB], part[RB];
+      // finished rows of A (p < P0) are left as they are
 #pragma unroll
-      for (int p = P0; p < RB; ++p) part[p] = 0.0;
+      for (int q = KQ + 1; q < CB; ++q)
+#pragma unroll
+        for (int p = P0; p < RB; ++p) A[p][q] = fma(-vr[p], qc[q], fma(-qr[p], vc[q], A[p][q]));
+      const bool none = !(s2 > TRI_NO_COLUMN);       // nothing to reflect
+      const double nn = none ? 1.0 : fma(x0, x0, s2), norm = nn * rsqrt_newton(nn);
+      const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, beta = none ? 0.0 : rcp_newton(norm * fabs(v0));
+      double part[RB], vav = 0.0;
+#pragma unroll
+      for (int p = 0; p < RB; ++p) part[p] = 0.0;
 #pragma unroll
       for (int q = KQ; q < CB; ++q) {
         vc[q] = xb[cl + 16 * q];
         if (q < KQ + 2 && cl + 16 * q == k + 1) vc[q] = v0;
 #pragma unroll
-        for (int p = P0; p < RB; ++p) part[p] += A[p][q] * vc[q];
+        for (int p = P0; p < RB; ++p) part[p] = fma(A[p][q], vc[q], part[p]);
       }
-#pragma unroll
-      for (int p = 0; p < P0; ++p) part[p] = 0.0;
-      pb[rg + RG * row16_slot<RB>(cl)] = beta * row16_sums<RB>(part, cl);
-      {
-        const double inv = rcp_newton(v0);
-        if (tid == 0) { sh.beta[k] = beta * v0 * v0; sh.e[k] = alpha; }
-        for (int i = tid; i < n; i += NT) if (i > k + 1) sh.vs[offs(k) + i] = (float)(xb[i] * inv);
-      }
-      __syncthreads();
-      double vp = 0.0;
-#pragma unroll
-      for (int h = 0; h < (N + 63) / 64; ++h) {
-        const int i = lane + 64 * h;
-        if (N % 64 == 0 || i < N) vp += (i == k + 1 ? v0 : xb[i]) * pb[i];
-      }
-      const double K = 0.5 * beta * wave64_sum(vp);
-      double vr[RB], qr[RB];
 #pragma unroll
       for (int p = P0; p < RB; ++p) {
         vr[p] = xb[rg + RG * p];
-        if (p < P1 + 16 / RG && rg + RG * p == k + 1) vr[p] = v0;
-        qr[p] = pb[rg + RG * p] - K * vr[p];
+        if (p < P2 && rg + RG * p == k + 1) vr[p] = v0;
+        vav = fma(vr[p], part[p], vav);
       }
-#pragma unroll
-      for (int q = KQ; q < CB; ++q) {
-        const double qc = pb[cl + 16 * q] - K * vc[q];
-#pragma unroll
-        for (int p = P0; p < RB; ++p) A[p][q] -= vr[p] * qc + qr[p] * vc[q];
+      pb[rg + RG * row16_slot<RB>(cl)] = row16_sums<RB>(part, cl);
+      vav = rows_sum(row16_sum(vav));
+      if (lane == 0) sh.step.vav[wave] = vav;
+      {
+        const double inv = none ? 0.0 : rcp_newton(v0);
+        if (tid == 0) { sh.beta[k] = beta * v0 * v0; sh.e[k] = none ? x0 : alpha; }
+        if (tid > k + 1 && tid < n) sh.vs[offs(k) + tid] = (float)(xb[tid] * inv);
       }
+      __syncthreads();
+      const double K = 0.5 * beta * (beta * wave_sums(sh.step.vav));       // beta^2 may be too large
+#pragma unroll
+      for (int q = KQ; q < CB; ++q) qc[q] = fma(beta, pb[cl + 16 * q], -K * vc[q]);
+#pragma unroll
+      for (int p = P0; p < RB; ++p) qr[p] = fma(beta, pb[rg + RG * p], -K * vr[p]);
     }
   };
   for_each_block<CB>(reduce16);
@@ -392,6 +426,11 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     if (sh.dec[i]) sh.d[i] = pow(((double)g.scale * (double)a[(int64_t)i * n + i] - shift) + eps, -r_exp);
   // Row l of F runs from its diagonal entry to the left: G_{l,i} = -(e_i / pivot_i) G_{l,i+1}, every
   // pole by itself, two lanes sharing the poles of a row.  A lane's values are zero until its row begins.
+  // F is kept as results of 16 x 16 matrix products: a wavefront has tile columns J = wave and CB - 1 - wave, element (j, I, u) is
+  // row 16 I + lg + 4 u, column 16 J_j + li.
+  const int lg = lane >> 4, li = cl;
+  const int tile[2] = {wave_u, CB - 1 - wave_u};
+  tri_d4 F[2][CB];
   {
     const int l = tid >> 1;
     float val[PQ];
@@ -418,99 +457,202 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
         }
       __syncthreads();
 #pragma unroll
-      for (int p = 0; p < RB; ++p)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int q = 0; q < CB; ++q)
-          if (min(RG * p / 16, q) == ch) {       // all of its rows and columns lie in one 16 x 16 block
-            const int r = rg + RG * p, c = cl + 16 * q, mn = min(r, c), mx = max(r, c);
-            A[p][q] = mx < n ? (double)sh.fun.chunk[mn % TRI_CHUNK][mx] : 0.0;
-          }
+        for (int I = 0; I < CB; ++I)
+          if (min(I, tile[j]) == ch)             // all of its rows and columns lie in one 16 x 16 block
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int r = 16 * I + lg + 4 * u, c = 16 * tile[j] + li, mn = min(r, c), mx = max(r, c);
+              F[j][I][u] = mx < n ? (double)sh.fun.chunk[mn % TRI_CHUNK][mx] : 0.0;
+            }
       __syncthreads();
     }
 #pragma unroll
-    for (int p = 0; p < RB; ++p)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int q = 0; q < CB; ++q)
-        if (rg + RG * p >= n || cl + 16 * q >= n) A[p][q] = 0.0;
+      for (int I = 0; I < CB; ++I)
+        if (16 * min(I, tile[j]) >= n) F[j][I] = (tri_d4){0.0, 0.0, 0.0, 0.0};      // no chunk of it
   }
 
-  // ---- F <- F - v q^T - q v^T with p = beta F v, q = p - (beta v.p + add) / 2 v ----
-  // beta = 2 / v.v, add = 0: the reflection H F H;  |v| = 1, beta = 1, add = f: the part of F along
-  // v is replaced by f.  v (in xb): zero below index k0.
-  // v of the next reflection is put in place on the way (three buffers: a wavefront may be one step ahead).
-  auto place = [&](double *xb, int k) {
-    const float *v = sh.vs + offs(k);
-    for (int i = tid; i < N; i += NT) xb[i] = i == k + 1 ? 1.0 : (i > k + 1 && i < n) ? (double)v[i] : 0.0;
-  };
-  // KQ: v is zero in front of element 16 KQ.
-  auto rank2 = [&](auto kq, const double *xb, double *pb, double beta, double add, double *xnext, int knext) {
-    constexpr int KQ = decltype(kq)::value, P0 = 16 * KQ / RG;
-    double vc[CB], part[RB];
+  // ---- the eigenvector that is handled by itself: the part of F along v1 is replaced by f ----
+  // F <- F - v q^T - q v^T with p = F v, q = p - (v.p + f) / 2 v
+  if (deflate) {
+    double *pb = sh.step.p;
+    const double *v = sh.v1;
+    double p[2] = {0.0, 0.0};
 #pragma unroll
-    for (int p = 0; p < RB; ++p) part[p] = 0.0;
+    for (int I = 0; I < CB; ++I)
 #pragma unroll
-    for (int q = KQ; q < CB; ++q) {
-      vc[q] = xb[cl + 16 * q];
+      for (int u = 0; u < 4; ++u) {
+        const double x = v[16 * I + lg + 4 * u];
+        p[0] += F[0][I][u] * x; p[1] += F[1][I][u] * x;
+      }
 #pragma unroll
-      for (int p = 0; p < RB; ++p) part[p] += A[p][q] * vc[q];
+    for (int j = 0; j < 2; ++j) {
+      p[j] += __shfl_xor(p[j], 16, 64); p[j] += __shfl_xor(p[j], 32, 64);
+      if (lg == 0) pb[16 * tile[j] + li] = p[j];
     }
-    pb[rg + RG * row16_slot<RB>(cl)] = beta * row16_sums<RB>(part, cl);
-    if (knext >= 0) place(xnext, knext);
     __syncthreads();
     double vp = 0.0;
 #pragma unroll
-    for (int h = 0; h < (N + 63) / 64; ++h) {
-      const int i = lane + 64 * h;
-      if (N % 64 == 0 || i < N) vp += xb[i] * pb[i];
+    for (int e = 0; e < (N + 63) / 64; ++e) {
+      const int i = lane + 64 * e;
+      if (N % 64 == 0 || i < N) vp += v[i] * pb[i];
     }
-    const double K = 0.5 * (beta * wave64_sum(vp) + add);
-    double vr[RB], qr[RB];
+    const double K = 0.5 * (wave64_sum(vp) + pow((lam - shift) + eps, -r_exp));
+    double vc[2], qc[2];
 #pragma unroll
-    for (int p = 0; p < RB; ++p) {
-      vr[p] = p >= P0 ? xb[rg + RG * p] : 0.0;
-      qr[p] = p >= P0 ? pb[rg + RG * p] - K * vr[p] : pb[rg + RG * p];
+    for (int j = 0; j < 2; ++j) { vc[j] = v[16 * tile[j] + li]; qc[j] = p[j] - K * vc[j]; }
+#pragma unroll
+    for (int I = 0; I < CB; ++I)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double vr = v[16 * I + lg + 4 * u], qr = pb[16 * I + lg + 4 * u] - K * vr;
+        F[0][I][u] -= vr * qc[0] + qr * vc[0]; F[1][I][u] -= vr * qc[1] + qr * vc[1];
+      }
+    __syncthreads();
+  }
+
+  // ---- X = Q F Q^T, 16 reflectors at a time, on the fp64 matrix cores ----
+  // Group q: those with k + 1 in 16 q ... 16 q + 15, which are zero in front of row 16 q.  Their product is I - V T V^T, and
+  //   F <- F - Y V^T - V Y^T,   Y = Z T^T - V (T M T^T) / 2,   Z = F V,   M = V^T Z.
+  // Five barriers for 16 reflections, and no wavefront sums: one reflection at a time (two barriers, two sums over the lanes)
+  // 1460 matrices of 128 x 128 took TIME_TRI_BACK.  Lane l supplies A(l % 16, l / 16 + 4 u) and B(l / 16 + 4 u, l % 16) to step u of a product
+  // and gets D(l / 16 + 4 u, l % 16): a result is the B operand of the next one as it lies, F also its own A operand.
+  TriBack<N> &bk = sh.back;
+  // entry (row, reflector 16 q + i - 1) of V
+  auto entry = [&](int k, int at, int row) { return row == k + 1 ? 1.f : row > k + 1 && row < n ? sh.vs[at + row] : 0.f; };
+  auto exists = [n](int k) { return k >= 0 && k <= n - 3; };
+  // S = V^T V, then T by columns: T_jj = 2 / S_jj, T_ij = -T_jj sum_l T_il S_lj.  A wavefront does two groups
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int q = tile[j], k = 16 * q + li - 1, at = exists(k) ? offs(k) : 0;
+    tri_d4 s = {0.0, 0.0, 0.0, 0.0};
+    for (int r0 = 16 * q; r0 < n; r0 += 16)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double x = exists(k) ? (double)entry(k, at, r0 + lg + 4 * u) : 0.0;
+        s = tri_mfma(x, x, s);
+      }
+    double *S = &bk.y[0][0] + 256 * q;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) S[(lg + 4 * u) * 16 + li] = s[u];
+  }
+  __syncthreads();
+  if (lg < 2) {
+    const int q = lg == 0 ? tile[0] : tile[1];
+    const double *S = &bk.y[0][0] + 256 * q;
+    double T[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int k = 16 * q + j - 1;
+      const bool is = exists(k) && sh.beta[max(k, 0)] != 0.0;
+      const double tau = is ? 2.0 * rcp_newton(S[17 * j]) : 0.0;
+      double x = 0.0;
+#pragma unroll
+      for (int l = 0; l < j; ++l) x += T[l] * S[l * 16 + j];
+      T[j] = li == j ? tau : li < j ? -tau * x : 0.0;
+      bk.t[q][j * 16 + li] = T[j];
     }
+  }
+  for (int q = (n - 2) / 16; q >= 0; --q) {
+    __syncthreads();                             // T; what the group before has read
+    for (int e = tid; e < 16 * N; e += NT) {
+      const int i = e / N, row = e % N, k = 16 * q + i - 1;
+      bk.v[i][row] = exists(k) ? entry(k, offs(k), row) : 0.f;
+    }
+    __syncthreads();
+    // Z^T, and the share of M of this wavefront's rows
+    tri_d4 z[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}}, m = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < CB; ++q) {
-      const double qc = q >= KQ ? pb[cl + 16 * q] - K * vc[q] : pb[cl + 16 * q];
+    for (int I = 0; I < CB; ++I)
+      if (I >= q)
 #pragma unroll
-      for (int p = 0; p < RB; ++p) {
-        if (q >= KQ && p >= P0) A[p][q] -= vr[p] * qc + qr[p] * vc[q];
-        else if (q >= KQ) A[p][q] -= qr[p] * vc[q];
-        else if (p >= P0) A[p][q] -= vr[p] * qc;
+        for (int u = 0; u < 4; ++u) {
+          const double x = (double)bk.v[li][16 * I + lg + 4 * u];
+          z[0] = tri_mfma(x, F[0][I][u], z[0]); z[1] = tri_mfma(x, F[1][I][u], z[1]);
+        }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (tile[j] >= q) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[j] + li] = z[j][u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)              // own entries: the wavefront's LDS operations keep their order
+          m = tri_mfma((double)bk.v[li][16 * tile[j] + lg + 4 * u], bk.y[li][16 * tile[j] + lg + 4 * u], m);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[0] + li] = m[u];
+    __syncthreads();
+    // W = T M T^T / 2
+    double t[4];
+    tri_d4 W = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      t[u] = bk.t[q][(lg + 4 * u) * 16 + li];
+      double x = 0.0;
+#pragma unroll
+      for (int e = 0; e < CB / 2; ++e) x += bk.y[lg + 4 * u][16 * e + li];       // M is symmetric
+      W = tri_mfma(x, t[u], W);
+    }
+    {
+      const tri_d4 mt = W;
+      W = (tri_d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) W = tri_mfma(t[u], mt[u], W);
+    }
+    __syncthreads();
+    // -Y^T = W V^T - T Z^T, -V^T
+    tri_d4 y[2];
+    double v[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      y[j] = (tri_d4){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) y[j] = tri_mfma(-t[u], z[j][u], y[j]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[j][u] = -(double)bk.v[lg + 4 * u][16 * tile[j] + li];
+      if (tile[j] >= q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[j] = tri_mfma(-0.5 * W[u], v[j][u], y[j]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[j] + li] = -y[j][u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int I = 0; I < CB; ++I) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double yi = bk.y[lg + 4 * u][16 * I + li], vi = (double)bk.v[lg + 4 * u][16 * I + li];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (tile[j] >= q) F[j][I] = tri_mfma(yi, v[j][u], F[j][I]);
+          if (I >= q) F[j][I] = tri_mfma(vi, y[j][u], F[j][I]);
+        }
       }
     }
-  };
-  int turn = 0;
-  if (n > 2) place(sh.step.x[0], n - 3);
-  if (deflate) rank2(BlockIndex<0>(), sh.v1, sh.step.p[1], 1.0, pow((lam - shift) + eps, -r_exp), nullptr, -1);
-  __syncthreads();
-  for_each_block<CB>([&](auto rev) {
-    constexpr int KQ = CB - 1 - decltype(rev)::value;
-    for (int k = min(n - 3, 16 * KQ + 14); k >= max(0, 16 * KQ - 1); --k) {       // k + 1 in 16 KQ .. 16 KQ + 15
-      const int nxt = turn == 2 ? 0 : turn + 1;
-      rank2(BlockIndex<KQ>(), sh.step.x[turn], sh.step.p[k & 1], sh.beta[k], 0.0, sh.step.x[nxt], k - 1);
-      turn = nxt;
-    }
-  });
+  }
   __syncthreads();
 
   // ---- out: the lower triangle and its mirror image carry the same bits ----
 #pragma unroll
-  for (int p = 0; p < RB; ++p)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int q = 0; q < CB; ++q) {
-      const int r = rg + RG * p, c = cl + 16 * q;
+    for (int e = 0; e < 4 * CB; ++e) {
+      const int r = 16 * (e >> 2) + lg + 4 * (e & 3), c = 16 * tile[j] + li;
       if (r < n && c <= r) {
-        double v = A[p][q];
+        double v = F[j][e >> 2][e & 3];
         if (sh.dec[r] || sh.dec[c]) v = r == c ? sh.d[r] : 0.0;
         sh.out[r][c] = (float)v;
       }
     }
   __syncthreads();
   float *x = g.x + (int64_t)b * g.x_stride;
-  for (int i = wave; i < n; i += NT / 64)
-    for (int j = lane; j < n; j += 64) x[(int64_t)i * n + j] = i >= j ? sh.out[i][j] : sh.out[j][i];
+  for (int e = tid; e < n * n; e += NT) {
+    const int i = row_of(e), j = e - i * n;
+    x[e] = i >= j ? sh.out[i][j] : sh.out[j][i];
+  }
 }
 
 }  // namespace shampoo
