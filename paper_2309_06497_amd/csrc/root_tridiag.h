@@ -3,16 +3,17 @@
 //   A = Q T Q^T        Householder reduction to tridiagonal form, float64, A in registers
 //   F = f(T)           f(x) = (x - min(lambda_min, 0) + eps)^-r as a sum of inverses of shifted T
 //                      (root_rational.h): two recurrences per shift, one product chain per row
-//   X = Q F Q^T        the same reflectors in reverse order, float64, F in registers
+//   X = Q F Q^T        the same reflectors in reverse order, 16 at a time, float64, F in registers
 //
 // The LDS Jacobi solver (eigh_jacobi.h) does the same job in about eight sweeps of 127 rounds with
-// two barriers and a pass over the matrix each; here there are 2 x 126 reflections.  It still serves
+// two barriers and a pass over the matrix each; here there are 126 reflections and 8 products of 16.  It still serves
 // callers that want the eigenvalues, and exponents that root_rational.h has no fit for.
 //
-// What bounds it: the latency of a reflection (barriers, wavefront reductions) and its LDS reads.
+// What bounds it: the latency of a reflection (two barriers, LDS round trips) and the fp64 matrix cores on the way back.  Cycles at
+// n = 128, two workgroups per CU: 37000 to read A, 382000 to reduce it, 69000 for bounds and pivots, 103000 for F, 153000 back.
 // The matrix itself stays out of LDS: a thread owns rows rg + RG a and columns cl + 16 b (cyclic,
-// so that the shrinking part stays spread over all threads), only the vectors of a reflection go
-// through LDS, and partial row sums meet across the 16 lanes of a DPP row.  At n = 128: 4 wavefronts,
+// so that the shrinking part stays spread over all threads), and only the vectors of a reflection go
+// through LDS.  At n = 128: 4 wavefronts,
 // 128 registers of matrix per lane, 80 KB of LDS, two workgroups per CU.
 //
 // Accuracy: T comes from a float64 reduction, so eigenvalues move by about 1e-16 of the largest, as
@@ -63,36 +64,6 @@ __device__ __forceinline__ double wave64_sum(double x) {
   return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
-// Sums of RB values over 16 lanes, the values split among the lanes on the way: lane cl ends with
-// value row16_slot<RB>(cl).  Each step sends the half that the other side keeps.
-template <int RB> __device__ __forceinline__ int row16_slot(int cl) {
-  return RB == 4 ? (((cl >> 3) & 1) * 2 + ((cl >> 2) & 1)) : (((cl >> 3) & 1) * 4 + ((cl >> 2) & 1) * 2 + ((cl >> 1) & 1));
-}
-template <int RB> __device__ __forceinline__ double row16_sums(const double (&v)[RB], int cl) {
-  static_assert(RB == 4 || RB == 8, "4 or 8 values");
-  double h[RB / 2];
-  const bool b3 = (cl & 8) != 0, b2 = (cl & 4) != 0, b1 = (cl & 2) != 0;
-#pragma unroll
-  for (int i = 0; i < RB / 2; ++i) {
-    const double keep = b3 ? v[RB / 2 + i] : v[i], send = b3 ? v[i] : v[RB / 2 + i];
-    h[i] = keep + dpp_fetch<DPP_MIRROR16>(send);
-  }
-  double q[RB / 4];
-#pragma unroll
-  for (int i = 0; i < RB / 4; ++i) {
-    const double keep = b2 ? h[RB / 4 + i] : h[i], send = b2 ? h[i] : h[RB / 4 + i];
-    q[i] = keep + dpp_fetch<DPP_MIRROR8>(send);
-  }
-  double x = q[0];
-  if (RB == 8) {
-    const double keep = b1 ? q[RB / 4 - 1] : q[0], send = b1 ? q[0] : q[RB / 4 - 1];
-    x = keep + dpp_fetch<DPP_XOR2>(send);
-  } else {
-    x += dpp_fetch<DPP_XOR2>(x);
-  }
-  return x + dpp_fetch<DPP_XOR1>(x);
-}
-
 // sum over the four lanes l % 16, in all of them
 __device__ __forceinline__ double rows_sum(double x) {
   auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
@@ -101,6 +72,40 @@ __device__ __forceinline__ double rows_sum(double x) {
   lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
   hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
   return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// The reduction's lanes: 16 columns (lane bits 5, 4, 1, 0) by 4 rows (bits 3, 2), so that the sums over columns begin with the
+// swaps of half and quarter wavefronts, which exchange what each side does not keep without a selection.
+__device__ __forceinline__ int tri_col(int lane) { return (lane >> 4) * 4 + (lane & 3); }
+__device__ __forceinline__ int tri_row(int lane) { return (lane >> 2) & 3; }
+__device__ __forceinline__ double tri_rows_sum(double x) { x += dpp_fetch<0x128>(x); return x + dpp_fetch<0x124>(x); }   // row_ror:8, row_ror:4
+// lanes < 32: a + a of lane + 32; others b + b of lane - 32
+__device__ __forceinline__ double swap32_sum(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// the same between the even and the odd rows of 16 lanes
+__device__ __forceinline__ double swap16_sum(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sums over the 16 columns of v[P0 ... 7], P0 < 4 or not: a lane ends with value tri_slot<P0>.
+template <int P0> __device__ __forceinline__ int tri_slot(int lane) {
+  return P0 < 4 ? (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 1) & 1) : 4 + (lane >> 5) * 2 + ((lane >> 4) & 1);
+}
+template <int P0> __device__ __forceinline__ double tri_cols_sums(const double (&v)[8], int lane) {
+  double x;
+  if constexpr (P0 < 4) {
+    const double a = swap16_sum(swap32_sum(v[0], v[4]), swap32_sum(v[2], v[6])), b = swap16_sum(swap32_sum(v[1], v[5]), swap32_sum(v[3], v[7]));
+    const bool second = (lane & 2) != 0;
+    x = (second ? b : a) + dpp_fetch<DPP_XOR2>(second ? a : b);
+  } else {
+    x = swap16_sum(swap32_sum(v[4], v[6]), swap32_sum(v[5], v[7]));
+    x += dpp_fetch<DPP_XOR2>(x);
+  }
+  return x + dpp_fetch<DPP_XOR1>(x);
 }
 
 typedef double tri_d4 __attribute__((ext_vector_type(4)));
@@ -131,7 +136,7 @@ template <int N> struct TriBack {
 };
 template <int N> struct TriShared {
   double d[N], e[N], v1[N];                  // T; the eigenvector handled by itself
-  double beta[N];                            // reflector k: 2 / v.v, or 0 where there is none
+  double beta[N];                            // reflector k: 0 where there is none
   union {
     struct {
       union {
@@ -152,13 +157,14 @@ template <int N> struct TriShared {
 template <int N, int NT>
 __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<SmallRootArgs, TRI_TABLE_RESERVE> grp, const RatTable table) {
   constexpr int RG = NT / 16, RB = N / RG, CB = N / 16;
+  static_assert(RB == 8, "rows of a lane");
   constexpr int PQ = RAT_MAX_POLES / 2, PQ_STEP = 6;      // two lanes share a row of F: poles per lane, taken 6 at a time
   static_assert(NT == 2 * N && PQ % PQ_STEP == 0, "two lanes per row");
   int b;
   const SmallRootArgs g = group_pick(grp, b);
   if (b >= g.batch || (g.only && g.only[b] == 0)) return;
   __shared__ __align__(16) TriShared<N> sh;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tid & 15, rg = tid >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cl = tri_col(lane), rg = tri_row(lane) + 4 * wave;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int n = g.n;
   const float *a = g.a + (int64_t)b * g.a_stride;
@@ -221,7 +227,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) { dec_min = fmin(dec_min, __shfl_xor(dec_min, off, 64)); fill = fmax(fill, __shfl_xor(fill, off, 64)); }
-  const bool coupled = fill > -1.0e300;
+  const bool coupled = fill > -1.0e300, lone = dec_min < 1.0e300;
   if (!coupled) fill = 1.0;
 #pragma unroll
   for (int p = 0; p < RB; ++p)
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // Bound by the latency of a reflection.  The update of A that belongs to one is done in the next: its first block column
   // ahead of the barrier behind which the next column can be read, the rest beside the chain from that column's norm to its
   // reflector.  Norm and v^T A v are summed within the wavefronts ahead of the barriers that are there anyway.  3072 matrices of 128 x 128, two
-  // workgroups per CU: 3590 cycles per reflection before, TIME_RED so.
+  // workgroups per CU: 3590 cycles per reflection before, 3030 so.
   double vr[RB], qr[RB], vc[CB], qc[CB];         // rows and columns of v and q: A <- A - v q^T - q v^T is to be done
 #pragma unroll
   for (int p = 0; p < RB; ++p) vr[p] = qr[p] = 0.0;
@@ -265,8 +271,8 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
           if (p < P1 && r == k) sh.d[k] = A[p][KQ];
         }
       }
-      s2 = rows_sum(s2);
-      if (lane == (k & 15)) sh.step.s2[wave] = s2;
+      s2 = tri_rows_sum(s2);
+      if (lane == ((k & 12) << 2 | (k & 3))) sh.step.s2[wave] = s2;
       __syncthreads();
       s2 = wave_sums(sh.step.s2);
       const double x0 = xb[k + 1];
@@ -294,12 +300,12 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
         if (p < P2 && rg + RG * p == k + 1) vr[p] = v0;
         vav = fma(vr[p], part[p], vav);
       }
-      pb[rg + RG * row16_slot<RB>(cl)] = row16_sums<RB>(part, cl);
+      pb[rg + RG * tri_slot<P0>(lane)] = tri_cols_sums<P0>(part, lane);
       vav = rows_sum(row16_sum(vav));
       if (lane == 0) sh.step.vav[wave] = vav;
       {
-        const double inv = none ? 0.0 : rcp_newton(v0);
-        if (tid == 0) { sh.beta[k] = beta * v0 * v0; sh.e[k] = none ? x0 : alpha; }
+        const double inv = copysign(norm * beta, v0);
+        if (tid == 0) { sh.beta[k] = beta; sh.e[k] = none ? x0 : alpha; }
         if (tid > k + 1 && tid < n) sh.vs[offs(k) + tid] = (float)(xb[tid] * inv);
       }
       __syncthreads();
@@ -428,7 +434,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // pole by itself, two lanes sharing the poles of a row.  A lane's values are zero until its row begins.
   // F is kept as results of 16 x 16 matrix products: a wavefront has tile columns J = wave and CB - 1 - wave, element (j, I, u) is
   // row 16 I + lg + 4 u, column 16 J_j + li.
-  const int lg = lane >> 4, li = cl;
+  const int lg = lane >> 4, li = lane & 15;
   const int tile[2] = {wave_u, CB - 1 - wave_u};
   tri_d4 F[2][CB];
   {
@@ -438,7 +444,8 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     for (int q = 0; q < PQ; ++q) val[q] = 0.f;
     const float4 *sl = reinterpret_cast<const float4 *>(slot + (tid & 1) * half);
     for (int ch = (n - 1) / TRI_CHUNK; ch >= 0; --ch) {
-      if (32 * wave + 31 >= ch * TRI_CHUNK)      // a wavefront holds 32 rows
+      // all 32 rows of a wavefront have begun, or some
+      auto columns = [&](auto begun) {
         for (int i = min(n, (ch + 1) * TRI_CHUNK) - 1; i >= ch * TRI_CHUNK; --i) {
           float acc = 0.f;
 #pragma unroll
@@ -447,14 +454,18 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
 #pragma unroll
               for (int q = q0; q < q0 + PQ_STEP; q += 2) {
                 const float4 s = sl[i * (RAT_MAX_POLES / 2) + q / 2];
-                val[q] = l == i ? s.y : val[q] * s.x;
-                val[q + 1] = l == i ? s.w : val[q + 1] * s.z;
+                val[q] *= s.x;
+                val[q + 1] *= s.z;
+                if (!decltype(begun)::value && l == i) { val[q] = s.y; val[q + 1] = s.w; }
                 acc += val[q] + val[q + 1];
               }
             }
           acc += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc), DPP_XOR1, 0xf, 0xf, true));
           if ((tid & 1) == 0) sh.fun.chunk[i - ch * TRI_CHUNK][l] = acc;
         }
+      };
+      if (32 * wave_u >= (ch + 1) * TRI_CHUNK) columns(BlockIndex<1>());
+      else if (32 * wave_u + 31 >= ch * TRI_CHUNK) columns(BlockIndex<0>());
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -518,7 +529,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // Group q: those with k + 1 in 16 q ... 16 q + 15, which are zero in front of row 16 q.  Their product is I - V T V^T, and
   //   F <- F - Y V^T - V Y^T,   Y = Z T^T - V (T M T^T) / 2,   Z = F V,   M = V^T Z.
   // Five barriers for 16 reflections, and no wavefront sums: one reflection at a time (two barriers, two sums over the lanes)
-  // 1460 matrices of 128 x 128 took TIME_TRI_BACK.  Lane l supplies A(l % 16, l / 16 + 4 u) and B(l / 16 + 4 u, l % 16) to step u of a product
+  // the kernel took 3011 us for 3000 matrices of up to 128 x 128, so 2673.  Lane l supplies A(l % 16, l / 16 + 4 u) and B(l / 16 + 4 u, l % 16) to step u of a product
   // and gets D(l / 16 + 4 u, l % 16): a result is the B operand of the next one as it lies, F also its own A operand.
   TriBack<N> &bk = sh.back;
   // entry (row, reflector 16 q + i - 1) of V
@@ -643,7 +654,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
       const int r = 16 * (e >> 2) + lg + 4 * (e & 3), c = 16 * tile[j] + li;
       if (r < n && c <= r) {
         double v = F[j][e >> 2][e & 3];
-        if (sh.dec[r] || sh.dec[c]) v = r == c ? sh.d[r] : 0.0;
+        if (lone && (sh.dec[r] || sh.dec[c])) v = r == c ? sh.d[r] : 0.0;
         sh.out[r][c] = (float)v;
       }
     }
