@@ -2,8 +2,8 @@
 // alignment; the products on planes made beforehand are gemm_f16x2.h and syrk_bf16.h).
 //
 // One workgroup (256 threads = 4 wavefronts of 64) computes a 128 x 128 tile of
-// C = alpha * A * B (+ beta * C).  Each wavefront owns a 64 x 64 quadrant as
-// 2 x 2 MFMA tiles of 32 x 32; tiles that hold nothing (ragged edges, above the diagonal) are passed over.  Slabs of
+// C = alpha * A * B (+ beta * C), or a 64 x 64 one (TILE) where there are few of those.  Each wavefront owns a quadrant as
+// 2 x 2 MFMA tiles of 32 x 32, or one; tiles that hold nothing (ragged edges, above the diagonal) are passed over.  Slabs of
 // 32 values of k go through LDS, the loads of the next one in flight meanwhile.  Operands may be float32 or bfloat16 in
 // memory.
 //
@@ -34,16 +34,17 @@ constexpr int BM = 128;
 constexpr int BN = 128;
 constexpr int BK = 32;          // k-slab depth
 constexpr int GEMM_LDK = BK + 4;      // FP32, rows of a slab [row][k] and [k][row], floats: 16-byte aligned, four banks apart
-constexpr int GEMM_LDR = BM + 4;
-constexpr int GEMM_FLOATS = BM * GEMM_LDK;   // the larger of the two layouts
+constexpr int GEMM_SMALL = 64;        // the smaller tile
 // Planes: rows of 32 values of k, 20 words apart; where four rows at a time are written (ROW_CONTIG), every fourth row lies beside
 // the next, and the four groups are 16 banks apart.  The 16 lanes that are served at a time then cover the 64 banks, in
 // 16-byte reads and in 8-byte writes.
 constexpr int GEMM_PK = BK / 2 + 4;
-constexpr int GEMM_PGROUP = BM / 4 * GEMM_PK + 16;
-constexpr int GEMM_PLANE = 4 * GEMM_PGROUP;  // words
-static_assert(BK * GEMM_LDR <= GEMM_FLOATS, "slab");
-constexpr int LOAD_PASSES = BK / 8;          // 128 x BK floats = 256 threads x LOAD_PASSES float4
+template <int ROWS> struct GemmSlab {
+  static constexpr int LDR = ROWS + 4, FLOATS = ROWS * GEMM_LDK;   // FLOATS: the larger of the two layouts
+  static constexpr int PGROUP = ROWS / 4 * GEMM_PK + 16, PLANE = 4 * PGROUP;   // words
+  static constexpr int PASSES = ROWS * BK / 1024;                  // ROWS x BK floats = 256 threads x PASSES float4
+  static_assert(BK * LDR <= FLOATS && ROWS * GEMM_PK <= PLANE, "slab");
+};
 constexpr int GEMM_THREADS = 256;
 constexpr int NUM_XCD = 8;
 
@@ -53,8 +54,8 @@ constexpr int NUM_XCD = 8;
 enum { K_CONTIG = 0, ROW_CONTIG = 1 };
 
 // where a row of a plane begins; row + 32 i lies i plane_tile() words further
-template <int ORIENT> __device__ __forceinline__ int plane_row(int row) {
-  return ORIENT == K_CONTIG ? row * GEMM_PK : (row & 3) * GEMM_PGROUP + (row >> 2) * GEMM_PK;
+template <int ORIENT, int ROWS> __device__ __forceinline__ int plane_row(int row) {
+  return ORIENT == K_CONTIG ? row * GEMM_PK : (row & 3) * GemmSlab<ROWS>::PGROUP + (row >> 2) * GEMM_PK;
 }
 template <int ORIENT> constexpr int plane_tile() { return ORIENT == K_CONTIG ? 32 * GEMM_PK : 8 * GEMM_PK; }
 
@@ -148,19 +149,21 @@ __device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reint
 // and later writes it into LDS as [row][k] (K_CONTIG) or [k][row].  Whatever is read lies inside the matrix: rows past its
 // last one read that again (what they reach is never stored), values of k past the end are zero, and of four rows that
 // cross the end the last four of the matrix are read and moved into place.
-template <int ORIENT, typename T>
+template <int ORIENT, typename T, int ROWS>
 struct TileLoader {
+  typedef GemmSlab<ROWS> S;
+  static constexpr int PASSES = S::PASSES, QUADS = ROWS / 4;   // QUADS threads side by side along the rows, PASSES values of k each
   const T *ptr;     // operand origin for this batch entry, already offset to the tile's first row
   int ld;
   int rows_left;    // valid rows from the tile's first row
   int K;
   int lane_row;     // ROW_CONTIG: the first of the four rows that are read
   int back;         // ROW_CONTIG: how far they lie in front of their place
-  float r[LOAD_PASSES][4];
+  float r[PASSES][4];
 
   __device__ __forceinline__ void init(const T *p, int ld_, int rows_left_, int K_, int tid) {
     ptr = p; ld = ld_; rows_left = rows_left_; K = K_;
-    const int r4 = (tid & 31) * 4;
+    const int r4 = (tid % QUADS) * 4;
     lane_row = min(r4, max(rows_left - 4, 0));
     back = r4 < rows_left ? r4 - lane_row : 0;
   }
@@ -171,7 +174,7 @@ struct TileLoader {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;   // threads per row, rows per pass
       const int row = tid / TPR, kq = k0 + (tid % TPR) * 4;
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h) {
+      for (int h = 0; h < PASSES; ++h) {
         const T *p = ptr + (int64_t)min(row + RPP * h, rows_left - 1) * ld + kq;
         if (whole) {
           load_u4<T>(p, r[h]);
@@ -181,25 +184,25 @@ struct TileLoader {
         }
       }
     } else {
-      const int kk = k0 + 4 * (tid >> 5);        // four values of k
+      const int kk = k0 + PASSES * (tid / QUADS);        // PASSES values of k
       if (rows_left >= 4) {                      // uniform
 #pragma unroll
-        for (int h = 0; h < LOAD_PASSES; ++h) {
+        for (int h = 0; h < PASSES; ++h) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) r[h][j] = 0.f;
           if (whole || kk + h < K) load_u4<T>(ptr + (int64_t)(kk + h) * ld + lane_row, r[h]);
         }
-        if (rows_left < BM && (rows_left & 3)) { // uniform
+        if (rows_left < ROWS && (rows_left & 3)) { // uniform
 #pragma unroll
-          for (int h = 0; h < LOAD_PASSES; ++h) {
+          for (int h = 0; h < PASSES; ++h) {
             if (back & 1) { r[h][0] = r[h][1]; r[h][1] = r[h][2]; r[h][2] = r[h][3]; }
             if (back & 2) { r[h][0] = r[h][2]; r[h][1] = r[h][3]; }
           }
         }
       } else {
-        const int r4 = (tid & 31) * 4;
+        const int r4 = (tid % QUADS) * 4;
 #pragma unroll
-        for (int h = 0; h < LOAD_PASSES; ++h)
+        for (int h = 0; h < PASSES; ++h)
 #pragma unroll
           for (int j = 0; j < 4; ++j)
             r[h][j] = (kk + h < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)(kk + h) * ld + r4 + j) : 0.f;
@@ -209,7 +212,7 @@ struct TileLoader {
 
   __device__ __forceinline__ void multiply(float s) {
 #pragma unroll
-    for (int h = 0; h < LOAD_PASSES; ++h)
+    for (int h = 0; h < PASSES; ++h)
 #pragma unroll
       for (int j = 0; j < 4; ++j) r[h][j] *= s;
   }
@@ -222,12 +225,12 @@ struct TileLoader {
       for (int j = 0; j < 4; ++j) {
         const float s = (k0 + kq + j < K) ? kscale[k0 + kq + j] : 0.f;
 #pragma unroll
-        for (int h = 0; h < LOAD_PASSES; ++h) r[h][j] *= s;
+        for (int h = 0; h < PASSES; ++h) r[h][j] *= s;
       }
     } else {
-      const int kk = 4 * (tid >> 5);
+      const int kk = PASSES * (tid / QUADS);
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h) {
+      for (int h = 0; h < PASSES; ++h) {
         const int k = k0 + kk + h;
         const float s = (k < K) ? kscale[k] : 0.f;
 #pragma unroll
@@ -241,13 +244,13 @@ struct TileLoader {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;
       const int row = tid / TPR, kq = (tid % TPR) * 4;
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h)
+      for (int h = 0; h < PASSES; ++h)
         *reinterpret_cast<float4 *>(lds + (row + RPP * h) * GEMM_LDK + kq) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
     } else {
-      const int kk = 4 * (tid >> 5), r4 = (tid & 31) * 4;
+      const int kk = PASSES * (tid / QUADS), r4 = (tid % QUADS) * 4;
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h)
-        *reinterpret_cast<float4 *>(lds + (kk + h) * GEMM_LDR + r4) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+      for (int h = 0; h < PASSES; ++h)
+        *reinterpret_cast<float4 *>(lds + (kk + h) * S::LDR + r4) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
     }
   }
   // the planes of the terms, h first
@@ -257,32 +260,37 @@ struct TileLoader {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;
       uint32_t *at = lds + (tid / TPR) * GEMM_PK + (tid % TPR) * 2;
 #pragma unroll
-      for (int h = 0; h < LOAD_PASSES; ++h)
+      for (int h = 0; h < PASSES; ++h)
 #pragma unroll
         for (int t = 0; t < (ONE ? 1 : 3); ++t) {
           const uint32_t x = bf16_round2(r[h][0], r[h][1], !ONE && t < 2), y = bf16_round2(r[h][2], r[h][3], !ONE && t < 2);
-          *reinterpret_cast<uint2 *>(at + t * GEMM_PLANE + RPP * h * GEMM_PK) = make_uint2(x, y);
+          *reinterpret_cast<uint2 *>(at + t * S::PLANE + RPP * h * GEMM_PK) = make_uint2(x, y);
         }
     } else {
-      uint32_t *at = lds + (tid & 31) * GEMM_PK + 2 * (tid >> 5);
+      uint32_t *at = lds + (tid % QUADS) * GEMM_PK + PASSES / 2 * (tid / QUADS);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int t = 0; t < (ONE ? 1 : 3); ++t) {
-          const uint32_t x = bf16_round2(r[0][e], r[1][e], !ONE && t < 2), y = bf16_round2(r[2][e], r[3][e], !ONE && t < 2);
-          *reinterpret_cast<uint2 *>(at + t * GEMM_PLANE + e * GEMM_PGROUP) = make_uint2(x, y);
+          const uint32_t x = bf16_round2(r[0][e], r[1][e], !ONE && t < 2);
+          if constexpr (PASSES == 4) {
+            const uint32_t y = bf16_round2(r[2][e], r[3][e], !ONE && t < 2);
+            *reinterpret_cast<uint2 *>(at + t * S::PLANE + e * S::PGROUP) = make_uint2(x, y);
+          } else {
+            at[t * S::PLANE + e * S::PGROUP] = x;
+          }
         }
     }
   }
 
   // the MFMA operand of 32 rows: row (of the lane), values k ... k + 7 of the slab
   static __device__ __forceinline__ floatx8 operand(const float *lds, int row, int k) {
-    return ORIENT == K_CONTIG ? lds_row8<GEMM_LDK>(lds, row, k) : lds_col8<GEMM_LDR>(lds, k, row);
+    return ORIENT == K_CONTIG ? lds_row8<GEMM_LDK>(lds, row, k) : lds_col8<S::LDR>(lds, k, row);
   }
   // of 32 rows: tile i behind the lane's address, values k ... k + 7 of a half of the slab that the lane's address names
   static __device__ __forceinline__ void terms(const uint32_t *lane, int i, int s, Bf16Terms &x) {
     auto plane = [&](int t) {
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(lane + t * GEMM_PLANE + i * plane_tile<ORIENT>() + 8 * s));
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(lane + t * S::PLANE + i * plane_tile<ORIENT>() + 8 * s));
     };
     x.h = plane(0);
     if constexpr (sizeof(T) == 4) { x.l = plane(1); x.m = plane(2); }
@@ -315,11 +323,15 @@ __device__ __forceinline__ const T *operand_ptr(const Operand &o, const BlockDes
 // factor updates: the first root refresh sees L = G G^T of a single gradient,
 // whose condition number is the square of G's, and a plain float32 running sum
 // over k would perturb its small eigenvalues by more than the parity budget.
-template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, bool ACC64 = false, bool FP32 = false>
-__global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
+template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, bool ACC64 = false, bool FP32 = false, int TILE = BM>
+__global__ __launch_bounds__(GEMM_THREADS, TILE == BM ? 2 : 4) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
   static_assert(!(ACC64 && FP32), "float64 sums: bf16 terms");
-  constexpr int SLAB_A = FP32 ? GEMM_FLOATS : (sizeof(TA) == 2 ? 1 : 3) * GEMM_PLANE, SLAB_B = FP32 ? GEMM_FLOATS : (sizeof(TB) == 2 ? 1 : 3) * GEMM_PLANE;
-  constexpr int STAGES = FP32 ? 2 : 1;           // two workgroups per CU either way
+  typedef GemmSlab<TILE> S;
+  typedef TileLoader<AO, TA, TILE> LoadA;
+  typedef TileLoader<BO, TB, TILE> LoadB;
+  constexpr int WT = TILE / 64, HALF = TILE / 2;      // a wavefront has WT x WT tiles of 32 x 32
+  constexpr int SLAB_A = FP32 ? S::FLOATS : (sizeof(TA) == 2 ? 1 : 3) * S::PLANE, SLAB_B = FP32 ? S::FLOATS : (sizeof(TB) == 2 ? 1 : 3) * S::PLANE;
+  constexpr int STAGES = FP32 ? 2 : 1;           // two workgroups per CU either way, four of the smaller tile
   __shared__ __align__(16) uint32_t As[STAGES][SLAB_A];
   __shared__ __align__(16) uint32_t Bs[STAGES][SLAB_B];
   __shared__ float red[4];
@@ -349,7 +361,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int row0 = ti * BM, col0 = tj * BN;
+  const int row0 = ti * TILE, col0 = tj * TILE;
 
   int lda, ldb, entry = b, K = g.K, kfirst = 0;
   if (EPI == EPI_SYRK && g.ksplit > 1) {
@@ -363,28 +375,28 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
     pa += AO == K_CONTIG ? (int64_t)kfirst : (int64_t)kfirst * lda;
     pb += BO == K_CONTIG ? (int64_t)kfirst : (int64_t)kfirst * ldb;
   }
-  TileLoader<AO, TA> la;
-  TileLoader<BO, TB> lb;
+  LoadA la;
+  LoadB lb;
   la.init(pa + (AO == K_CONTIG ? (int64_t)row0 * lda : (int64_t)row0), lda, g.M - row0, K, tid);
   lb.init(pb + (BO == K_CONTIG ? (int64_t)col0 * ldb : (int64_t)col0), ldb, g.N - col0, K, tid);
   const float *ks = KSCALE ? g.kscale + (int64_t)b * g.kscale_stride : nullptr;
   const float sg = g.gmax ? range_scale(g.gmax[entry / g.gmax_per]) : 1.f;
-  // which of this wavefront's 2 x 2 tiles hold part of the result
-  bool on[2][2];
+  // which of this wavefront's tiles hold part of the result
+  bool on[WT][WT];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < WT; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int r = wm * 64 + 32 * i, c = wn * 64 + 32 * j;
+    for (int j = 0; j < WT; ++j) {
+      const int r = wm * HALF + 32 * i, c = wn * HALF + 32 * j;
       on[i][j] = row0 + r < g.M && col0 + c < g.N && !(EPI == EPI_SYRK && ti == tj && c > r);
     }
 
-  floatx16 acc[2][2], rest[ACC64 || FP32 ? 1 : 2][ACC64 || FP32 ? 1 : 2];
-  double acc64[ACC64 ? 2 : 1][ACC64 ? 2 : 1][ACC64 ? 16 : 1];
+  floatx16 acc[WT][WT], rest[ACC64 || FP32 ? 1 : WT][ACC64 || FP32 ? 1 : WT];
+  double acc64[ACC64 ? WT : 1][ACC64 ? WT : 1][ACC64 ? 16 : 1];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < WT; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < WT; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         acc[i][j][v] = 0.f;
@@ -417,10 +429,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
     __syncthreads();
   }
 
-  const int arow = wm * 64 + (lane & 31);
-  const int bcol = wn * 64 + (lane & 31);
+  const int arow = wm * HALF + (lane & 31);
+  const int bcol = wn * HALF + (lane & 31);
   const int khalf = lane >> 5;
-  const uint32_t *lane_a = As[0] + plane_row<AO>(arow) + 4 * khalf, *lane_b = Bs[0] + plane_row<BO>(bcol) + 4 * khalf;
+  const uint32_t *lane_a = As[0] + plane_row<AO, TILE>(arow) + 4 * khalf, *lane_b = Bs[0] + plane_row<BO, TILE>(bcol) + 4 * khalf;
   constexpr bool AONE = sizeof(TA) == 2, BONE = sizeof(TB) == 2;
   for (int kt = 0; kt < nk; ++kt) {
     if constexpr (!FP32) {
@@ -429,13 +441,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
       __syncthreads();
     }
     if (kt + 1 < nk) fetch((kt + 1) * BK);
-    auto terms_a = [&](int i, int s, Bf16Terms &x) { TileLoader<AO, TA>::terms(lane_a, i, s, x); };
-    auto terms_b = [&](int j, int s, Bf16Terms &x) { TileLoader<BO, TB>::terms(lane_b, j, s, x); };
+    auto terms_a = [&](int i, int s, Bf16Terms &x) { LoadA::terms(lane_a, i, s, x); };
+    auto terms_b = [&](int j, int s, Bf16Terms &x) { LoadB::terms(lane_b, j, s, x); };
     if constexpr (ACC64) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < WT; ++j)
           if (on[i][j]) {
             floatx16 c = {};
             Bf16Terms a, t;
@@ -455,16 +467,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
 #pragma unroll 1
       for (int s = 0; s < 2; ++s) {
         const float *as = reinterpret_cast<const float *>(As[kt & 1]), *bs = reinterpret_cast<const float *>(Bs[kt & 1]);
-        floatx8 a[2], t[2];
+        floatx8 a[WT], t[WT];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          a[i] = TileLoader<AO, TA>::operand(as, arow + 32 * i, 16 * s + 8 * khalf);
-          t[i] = TileLoader<BO, TB>::operand(bs, bcol + 32 * i, 16 * s + 8 * khalf);
+        for (int i = 0; i < WT; ++i) {
+          a[i] = LoadA::operand(as, arow + 32 * i, 16 * s + 8 * khalf);
+          t[i] = LoadB::operand(bs, bcol + 32 * i, 16 * s + 8 * khalf);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < WT; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < WT; ++j)
             if (on[i][j]) acc[i][j] = fp32_products(a[i], t[j], acc[i][j]);
       }
       if (kt + 1 < nk) store((kt + 1) & 1, (kt + 1) * BK);
@@ -472,16 +484,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
     } else {
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        Bf16Terms a[2], t[2];
+        Bf16Terms a[WT], t[WT];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          if (on[i][0] || on[i][1]) terms_a(i, s, a[i]);
-          if (on[0][i] || on[1][i]) terms_b(i, s, t[i]);
+        for (int i = 0; i < WT; ++i) {
+          if (on[i][0] || on[i][WT - 1]) terms_a(i, s, a[i]);
+          if (on[0][i] || on[WT - 1][i]) terms_b(i, s, t[i]);
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < WT; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < WT; ++j)
             if (on[i][j]) {
               rest[i][j] = bf16_small_products<AONE, BONE>(a[i], t[j], rest[i][j]);
               acc[i][j] = bf16_mfma(a[i].h, t[j].h, acc[i][j]);
@@ -491,9 +503,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
   }
   if constexpr (!ACC64 && !FP32)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < WT; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] += rest[i][j][v];
   // s is up to 2^120, its square in float64
@@ -503,15 +515,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
   const float alpha = g.unscale ? g.alpha * inv_s : g.alpha;
 
   // ---- epilogue.  Accumulator element v of MFMA tile (mi, ni) is
-  //      row = wm*64 + mi*32 + 8*(v/4) + 4*(lane/32) + v%4, col = wn*64 + ni*32 + lane%32.
+  //      row = wm*HALF + mi*32 + 8*(v/4) + 4*(lane/32) + v%4, col = wn*HALF + ni*32 + lane%32.
   float *c = g.c + (int64_t)b * g.c_batch_stride;
   const int ldc = g.ldc;
   float ss = 0.f;
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+  for (int mi = 0; mi < WT; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int j = col0 + wn * 64 + ni * 32 + (lane & 31);
+    for (int ni = 0; ni < WT; ++ni) {
+      const int j = col0 + wn * HALF + ni * 32 + (lane & 31);
       // EPI_SYRK with a nonzero beta: the 16 old values of an MFMA tile are requested before
       // its first store.  The mirrored stores may alias later loads, so interleaved they
       // would cost one memory round trip per element instead of one per tile.
@@ -520,13 +532,13 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void gemm_mfma_kernel(const Group<
         const bool need = ACC64 ? (g.beta_d != 0.0 && g.ksplit <= 1) : (g.beta != 0.f);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int i = row0 + wm * 64 + mi * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+          const int i = row0 + wm * HALF + mi * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
           old[EPI == EPI_SYRK ? v : 0] = (need && i < g.M && j <= i) ? c[(int64_t)i * ldc + j] : 0.f;
         }
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int ibase = row0 + wm * 64 + mi * 32 + 8 * q + 4 * (lane >> 5);
+        const int ibase = row0 + wm * HALF + mi * 32 + 8 * q + 4 * (lane >> 5);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int i = ibase + e;

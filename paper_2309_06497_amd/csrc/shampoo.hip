@@ -517,6 +517,50 @@ template <typename Args, int RESERVE = 0, typename... Extra> struct Batch {
   }
 };
 
+// Products of several buckets with gemm_mfma_kernel, in tiles of 128 x 128 or of 64 x 64.  Sets the counts of tiles, and those of
+// the partial sums of squares that the caller wants to know.
+// The smaller tile reads and splits its operands twice as often, but has four workgroups on a CU instead of two and four times as
+// many: it is taken where the larger would leave half of the GPU's 512 places empty or fill them but once or twice, and where
+// k is so short that a tile is little but its latency.  Step, large and small tiles: one layer of 331 in blocks of 1024 (float32) 418 and
+// 223 us, of 526 in blocks of 512 301 and 215, one matrix of 191 144 and 82; two layers of 900, where the
+// products have 576 tiles, 1225 and 1100, with those of 2048 in small tiles too 1190; ResNet-50 with convolution tensors, products
+// over 128 of 6200 tiles, 893 and 843.
+constexpr int64_t GEMM_FEW_TILES = 1024;
+constexpr int GEMM_SHORT_K = 128;
+struct GemmKernels { Batch<GemmArgs>::Kernel large, small; };
+template <int AO, int BO, typename TA, typename TB, int EPI, bool ACC64 = false, bool FP32 = false> constexpr GemmKernels gemm_kernels() {
+  return {gemm_mfma_kernel<AO, BO, TA, TB, EPI, false, ACC64, FP32>, gemm_mfma_kernel<AO, BO, TA, TB, EPI, false, ACC64, FP32, GEMM_SMALL>};
+}
+template <int EPI> struct GemmBatch {
+  struct Entry { GemmArgs g; int *parts; int first_row; };
+  GemmKernels kernels; hipStream_t s;
+  std::vector<Entry> entries;
+  GemmBatch(GemmKernels k, hipStream_t s_) : kernels(k), s(s_) {}
+  // first_row (EPI_SYRK): the rows in front of it may stay as they are
+  void add(const GemmArgs &g, int *parts = nullptr, int first_row = 0) { entries.push_back(Entry{g, parts, first_row}); }
+  static void tile(Entry &e, int size) {
+    GemmArgs &g = e.g;
+    const int skipped = e.first_row / size;
+    g.tiles_m = (g.M + size - 1) / size; g.tiles_n = (g.N + size - 1) / size;
+    g.tile0 = skipped * (skipped + 1) / 2;
+    g.tiles = EPI == EPI_SYRK ? g.tiles_m * (g.tiles_m + 1) / 2 - g.tile0 : g.tiles_m * g.tiles_n;
+  }
+  int flush() {
+    int64_t total = 0;
+    int k = 0;
+    for (Entry &e : entries) { tile(e, BM); total += (int64_t)e.g.tiles * e.g.batch; k = std::max(k, e.g.K); }
+    const bool small = total <= GEMM_FEW_TILES || k <= GEMM_SHORT_K;
+    Batch<GemmArgs> x(small ? kernels.small : kernels.large, GEMM_THREADS, s);
+    for (Entry &e : entries) {
+      if (small) tile(e, GEMM_SMALL);
+      if (e.parts) *e.parts = e.g.tiles;
+      if (const int rc = x.add(e.g, (int64_t)e.g.tiles * e.g.batch)) return rc;
+    }
+    entries.clear();
+    return x.flush();
+  }
+};
+
 template <int AO, int BO, typename TA, typename TB, int EPI, bool KS, bool ACC64 = false>
 int launch_gemm(const GemmArgs &g, hipStream_t s) {
   Batch<GemmArgs> one(gemm_mfma_kernel<AO, BO, TA, TB, EPI, KS, ACC64>, GEMM_THREADS, s);
@@ -804,10 +848,9 @@ struct BandSolve {
     // float64 where the margin to Jacobi is small.
     int rc;
     auto takes_part = [&](BandJob &j) { j.k = band_groups(j.g) - 1 - u; return j.k >= 0; };
-    Batch<GemmArgs> zs(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>, GEMM_THREADS, s),
-        ys(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>, GEMM_THREADS, s),
-        us64(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>, GEMM_THREADS, s),
-        us(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>, GEMM_THREADS, s);
+    GemmBatch<EPI_STORE> zs(gemm_kernels<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, true>(), s);
+    Batch<GemmArgs> ys(gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>, GEMM_THREADS, s);
+    GemmBatch<EPI_SYRK> us64(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, true>(), s), us(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);
     for (BandJob &j : jobs) {
       if (!takes_part(j)) continue;
       const BandArgs &g = j.g;
@@ -820,8 +863,9 @@ struct BandSolve {
       z.c = p; z.c_batch_stride = pstride; z.ldc = BAND_PLD;
       z.M = np; z.N = BAND_GW; z.K = np - r0; z.alpha_d = 1.0; z.skip = g.skip;
       z.tiles_m = z.tiles = tiles; z.tiles_n = 1; z.batch = j.cnt;
-      if ((rc = zs.add(z, (int64_t)z.tiles * z.batch))) return rc;
-      // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them
+      zs.add(z);
+      // Y = [Z V] [T^T; -T M T^T / 2], over Z: a workgroup stores only rows that no other reads, after it has read them (tiles as
+      // wide as Z)
       GemmArgs y = z;
       y.a = Operand{p, pstride, BAND_PLD, 0};
       y.b = Operand{band_ts(g), pstride, BAND_GW, 0};
@@ -832,8 +876,7 @@ struct BandSolve {
       f.b = Operand{p + BAND_GW, pstride, BAND_PLD, 0};
       f.c = g.f; f.c_batch_stride = (int64_t)np * np * 2; f.ldc = np;
       f.N = np; f.K = 2 * BAND_GW; f.alpha = -1.f; f.beta = 1.f; f.alpha_d = -1.0; f.beta_d = 1.0;
-      f.tiles_n = tiles; f.tile0 = (r0 / BM) * (r0 / BM + 1) / 2; f.tiles = tiles * (tiles + 1) / 2 - f.tile0;
-      if ((rc = (np <= 512 ? us64 : us).add(f, (int64_t)f.tiles * f.batch))) return rc;
+      (np <= 512 ? us64 : us).add(f, nullptr, r0);
     }
     auto stage = [&](BandJob &j) { return takes_part(j) ? (int64_t)(j.g.np / 8) * j.cnt : 0; };
     if ((rc = each(band_stage_kernel<false>, 256, stage)) || (rc = zs.flush())) return rc;
@@ -1076,10 +1119,10 @@ int newton_product(const float *A, const float *B, float *C, int n, int cnt, con
   g.c = C; g.c_batch_stride = (int64_t)n * n; g.ldc = n;
   g.M = n; g.N = n; g.K = n; g.alpha = 1.f; g.beta = 0.f;
   g.skip = done;
-  g.tiles_m = g.tiles_n = (n + BM - 1) / BM;
-  g.tiles = g.tiles_m * (g.tiles_m + 1) / 2;
   g.batch = cnt;
-  return launch_gemm<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false>(g, s);     // symmetric: read along k
+  GemmBatch<EPI_SYRK> product(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);     // symmetric: read along k
+  product.add(g);
+  return product.flush();
 }
 
 // X_i = (scale * A_i + eps I)^(-1/p) for a batch of dense n x n matrices.
@@ -1239,8 +1282,9 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_sgp = take(B * b.geom.chunks * 4);
     // partial sums of ||P_shampoo||^2: one per tile of the last product (tensor blocks: the
     // (d2 d1) x d3 product of the third dimension) or per chunk of an elementwise pass
-    size_t ssh_parts = std::max<size_t>((size_t)b.tiles_m * b.tiles_n, (size_t)b.geom.chunks);
-    if (b.t3) ssh_parts = std::max(ssh_parts, (size_t)((m * n / b.dlast() + BM - 1) / BM) * ((b.dlast() + BN - 1) / BN));
+    auto parts = [](size_t rows, size_t cols) { return ((rows + GEMM_SMALL - 1) / GEMM_SMALL) * ((cols + GEMM_SMALL - 1) / GEMM_SMALL); };
+    size_t ssh_parts = std::max(parts(m, n), (size_t)b.geom.chunks);
+    if (b.t3) ssh_parts = std::max(ssh_parts, parts(m * n / b.dlast(), b.dlast()));
     b.off_sshp = take(B * ssh_parts * 4);
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
@@ -1698,8 +1742,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       Batch<SyrkBf16Args> plain(syrk_bf16_kernel<false, false>, GEMM_THREADS, s), plain64(syrk_bf16_kernel<false, true>, GEMM_THREADS, s),
           half(syrk_bf16_kernel<true, false>, GEMM_THREADS, s), half64(syrk_bf16_kernel<true, true>, GEMM_THREADS, s),
           split(syrk_bf16_kernel<false, true, true>, GEMM_THREADS, s);
-      Batch<GemmArgs> left(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s),
-          right(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s);
+      GemmBatch<EPI_SYRK> left(gemm_kernels<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, true>(), s),
+          right(gemm_kernels<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, true>(), s);
       for (Bucket *bp : todo) {
         Bucket &b = *bp;
         const size_t index = &b - p.buckets.data();
@@ -1767,7 +1811,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
             g.M = b.m; g.N = b.m; g.K = b.n;
             g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
-            if ((rc = left.add(g, (int64_t)g.tiles * g.batch))) return rc;
+            left.add(g);
           }
           if (b.diagR) {
             // r_j <- beta r_j + alpha sum_i G_ij^2, rows cut into segments whose partial sums go through T
@@ -1781,7 +1825,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             g.c = reinterpret_cast<float *>(ws + b.off_R); g.c_batch_stride = (int64_t)b.n * b.n; g.ldc = b.n;
             g.M = b.n; g.N = b.n; g.K = b.m;
             g.tiles_m = g.tiles_n = b.tiles_n; g.tiles = b.tiles_n * (b.tiles_n + 1) / 2;
-            if ((rc = right.add(g, (int64_t)g.tiles * g.batch))) return rc;
+            right.add(g);
           }
         }
       }
@@ -1794,9 +1838,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     // two indices swapped, d_k x (pre post).  gram_reduce_kernel adds the ranges up in float64 and applies the moving average.
     for (int mid = 0; mid < 2; ++mid) {
       Batch<PermuteArgs> swaps(permute_12_kernel<GS>, 256, s);
-      Batch<GemmArgs> first(gemm_mfma_kernel<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s),
-          middle(gemm_mfma_kernel<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, false, true>, GEMM_THREADS, s),
-          last(gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, false, true>, GEMM_THREADS, s);
+      GemmBatch<EPI_SYRK> first(gemm_kernels<K_CONTIG, K_CONTIG, GS, GS, EPI_SYRK, true>(), s),
+          middle(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK, true>(), s),
+          last(gemm_kernels<ROW_CONTIG, ROW_CONTIG, GS, GS, EPI_SYRK, true>(), s);
       Batch<GramNarrowArgs> narrow(gram_narrow_kernel<GS>, 256, s);
       Batch<GramReduceArgs> reduce64(gram_reduce_kernel<double>, 256, s), reduce32(gram_reduce_kernel<float>, 256, s);
       for (Bucket *bp : todo) {
@@ -1817,7 +1861,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           g.M = b.m; g.N = b.m; g.K = b.n;
           g.tiles_m = g.tiles_n = b.tiles_m; g.tiles = b.tiles_m * (b.tiles_m + 1) / 2;
           const int sp = split_gram(b, g, sums_l);
-          if ((rc = first.add(g, (int64_t)g.tiles * g.batch))) return rc;
+          first.add(g);
           if (sp > 1 && (rc = reduce_gram(reduce64, sums_l, b.off_L, b.m, sp, b.count))) return rc;
           if (b.modes >= 3) {
             const int dl = b.dlast(), inner = b.n / dl;
@@ -1834,7 +1878,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
               r.M = dl; r.N = dl; r.K = (b.m / b.split3) * inner;
               r.alpha = 1.f; r.beta = 0.f; r.alpha_d = 1.0; r.beta_d = 0.0; r.batch = b.count * b.split3;
               r.tiles_m = r.tiles_n = (dl + BM - 1) / BM; r.tiles = r.tiles_m * (r.tiles_m + 1) / 2;
-              if ((rc = last.add(r, (int64_t)r.tiles * r.batch))) return rc;
+              last.add(r);
             }
             if ((rc = reduce_gram(reduce32, sums_r, b.off_R, dl, b.split3, b.count))) return rc;
           }
@@ -1854,7 +1898,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           scale_factor(b, h, 1);
           h.tiles_m = h.tiles_n = (dk + BM - 1) / BM; h.tiles = h.tiles_m * (h.tiles_m + 1) / 2;
           const int sp = split_gram(b, h, sums_m);
-          if ((rc = middle.add(h, (int64_t)h.tiles * h.batch))) return rc;
+          middle.add(h);
           if (sp > 1 && (rc = reduce_gram(reduce64, sums_m, b.off_mid[mid], dk, sp, b.count))) return rc;
         }
       }
@@ -1975,13 +2019,12 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       Batch<GemmX2Args> tall1(gemm_f16x2_kernel<256, 128, 1, X2_STORE_SPLIT>, 256, s), wide1(gemm_f16x2_kernel<128, 64, THREE ? 3 : 1, X2_STORE_SPLIT>, 256, s),
           tall2(gemm_f16x2_kernel<256, 128, 2, X2_STORE_NORM>, 256, s), wide2(gemm_f16x2_kernel<128, 64, THREE ? 3 : 2, X2_STORE_NORM>, 256, s);
       const bool fp32 = c.precond_matrix_cores == SHAMPOO_MATRIX_CORES_FP32;
-      Batch<GemmArgs> first(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false, false, true>
-                                 : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false>, GEMM_THREADS, s),
-          only(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false, false, true>
-                    : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false>, GEMM_THREADS, s),
-          second(fp32 ? gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false, false, true>
-                      : gemm_mfma_kernel<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false>, GEMM_THREADS, s);
-      auto gemm_wgs = [](const GemmArgs &g) { return (int64_t)g.tiles * g.batch; };
+      GemmBatch<EPI_STORE> first(fp32 ? gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE, false, true>()
+                                      : gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE>(), s);
+      GemmBatch<EPI_STORE_NORM> only(fp32 ? gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM, false, true>()
+                                          : gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, GD, EPI_STORE_NORM>(), s),
+          second(fp32 ? gemm_kernels<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false, true>()
+                      : gemm_kernels<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM>(), s);
       auto x2_wgs = [](const GemmX2Args &g) { return (int64_t)g.tiles_m * g.tiles_n * g.batch; };
       // a block of m x n times its left root, and the other way round
       auto left_product = [&](const Bucket &b, float *out, bool result) {
@@ -1992,7 +2035,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         g.b.from_table = 1; g.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); g.ptr_table = gd_tab;
         g.c = out; g.c_batch_stride = (int64_t)b.m * b.n; g.ldc = b.n;
         g.M = b.m; g.N = b.n; g.K = b.m; g.alpha = c1; g.beta = 0.f;
-        g.tiles_m = b.tiles_m; g.tiles_n = b.tiles_n; g.tiles = b.tiles_m * b.tiles_n; g.batch = b.count;
+        g.batch = b.count;
         return g;
       };
       auto right_product = [&](const Bucket &b, const float *in, bool scaled) {
@@ -2002,7 +2045,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         h.b.base = ws + b.off_Rinv; h.b.batch_stride = (int64_t)b.n * b.n; h.b.ld = b.n;
         h.c = reinterpret_cast<float *>(ws + b.off_P); h.c_batch_stride = (int64_t)b.m * b.n; h.ldc = b.n;
         h.M = b.m; h.N = b.n; h.K = b.n; h.alpha = 1.f; h.beta = 0.f;
-        h.tiles_m = b.tiles_m; h.tiles_n = b.tiles_n; h.tiles = b.tiles_m * b.tiles_n; h.batch = b.count;
+        h.batch = b.count;
         h.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
         return h;
       };
@@ -2045,7 +2088,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         for (size_t i = 0; i < todo.size(); ++i) {
           const Bucket &b = *todo[i];
           float *T = bucket_t(b), *P = reinterpret_cast<float *>(ws + b.off_P), *ssh = reinterpret_cast<float *>(ws + b.off_sshp);
-          ssh_count[i] = b.tiles_m * b.tiles_n;
           if (on_planes(b)) {
             const X2Shape x = x2_shape(b);
             ssh_count[i] = x.tm * x.tn;
@@ -2056,9 +2098,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           } else if (b.t3) {
             // P = G x_1 Lbar_1 x_2 Lbar_2 ... x_w Lbar_w (Sec. 2.3), the first product here
             GemmArgs g = left_product(b, b.modes == 1 ? P : T, b.modes == 1);
-            if (b.modes == 1) { g.norm_partial = ssh; rc = only.add(g, gemm_wgs(g)); }
-            else rc = first.add(g, gemm_wgs(g));
-            if (rc) return rc;
+            if (b.modes == 1) { g.norm_partial = ssh; only.add(g, &ssh_count[i]); }
+            else first.add(g);
           } else if (b.whole()) {
             // diagonal Shampoo: a diagonalised side scales rows / columns instead of multiplying
             DiagScaleArgs ds{};
@@ -2075,20 +2116,19 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
               ds.dl = dl; ds.out = T; ds.alpha = c1;
               hipLaunchKernelGGL(diag_scale_kernel<GD>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
               HIP_TRY(hipGetLastError());
-              const GemmArgs h = right_product(b, T, false);
-              if ((rc = second.add(h, gemm_wgs(h)))) return rc;
+              second.add(right_product(b, T, false), &ssh_count[i]);
             } else {
               // T = Lbar G, then P = T D_R
-              const GemmArgs g = left_product(b, T, true);
-              if ((rc = first.add(g, gemm_wgs(g))) || (rc = first.flush())) return rc;
+              first.add(left_product(b, T, true));
+              if ((rc = first.flush())) return rc;
               ds.src = T; ds.dr = dr; ds.out = P; ds.norm_partial = ssh; ds.alpha = 1.f;
               hipLaunchKernelGGL(diag_scale_kernel<float>, dim3(ew_grid), dim3(EW_THREADS), 0, s, ds);
               HIP_TRY(hipGetLastError());
               ssh_count[i] = b.geom.chunks;
             }
           } else {
-            const GemmArgs g = left_product(b, T, false), h = right_product(b, T, true);
-            if ((rc = first.add(g, gemm_wgs(g))) || (rc = second.add(h, gemm_wgs(h)))) return rc;
+            first.add(left_product(b, T, false));
+            second.add(right_product(b, T, true), &ssh_count[i]);
           }
         }
         if ((rc = tall1.flush()) || (rc = wide1.flush()) || (rc = first.flush()) || (rc = only.flush())) return rc;
@@ -2098,8 +2138,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         std::vector<int> swapped(todo.size(), 0);       // the block is in the second scratch
         for (int mid = 0; mid < 2; ++mid) {
           Batch<PermuteArgs> there(permute_12_kernel<float>, 256, s), back(permute_12_kernel<float>, 256, s);
-          Batch<GemmArgs> products(fp32 ? gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, false, true>
-                                        : gemm_mfma_kernel<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false>, GEMM_THREADS, s);
+          GemmBatch<EPI_STORE> products(fp32 ? gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE, false, true>()
+                                             : gemm_kernels<ROW_CONTIG, ROW_CONTIG, float, float, EPI_STORE>(), s);
           for (size_t i = 0; i < todo.size(); ++i) {
             const Bucket &b = *todo[i];
             if (!b.t3 || mid + 2 >= b.modes) continue;
@@ -2115,8 +2155,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             h.b.base = other; h.b.batch_stride = mn; h.b.ld = pre * post;
             h.c = cur; h.c_batch_stride = mn; h.ldc = pre * post;
             h.M = dk; h.N = pre * post; h.K = dk; h.alpha = 1.f; h.beta = 0.f;
-            h.tiles_m = (h.M + BM - 1) / BM; h.tiles_n = (h.N + BN - 1) / BN; h.tiles = h.tiles_m * h.tiles_n; h.batch = b.count;
-            if ((rc = products.add(h, gemm_wgs(h)))) return rc;
+            h.batch = b.count;
+            products.add(h);
             pm.d1 = dk; pm.d2 = pre;
             if ((rc = back.add(pm, (int64_t)pm.chunks * b.count))) return rc;
             swapped[i] ^= 1;
@@ -2133,11 +2173,10 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           q.b.base = ws + b.off_Rinv; q.b.batch_stride = (int64_t)dl * dl; q.b.ld = dl;
           q.c = reinterpret_cast<float *>(ws + b.off_P); q.c_batch_stride = mn; q.ldc = dl;
           q.M = (int)(mn / dl); q.N = dl; q.K = dl; q.alpha = 1.f; q.beta = 0.f;
-          q.tiles_m = (q.M + BM - 1) / BM; q.tiles_n = (q.N + BN - 1) / BN; q.tiles = q.tiles_m * q.tiles_n; q.batch = b.count;
+          q.batch = b.count;
           q.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
           scale_direction(b, q, false, true);
-          if ((rc = second.add(q, gemm_wgs(q)))) return rc;
-          ssh_count[i] = q.tiles;
+          second.add(q, &ssh_count[i]);
         }
       }
       {
