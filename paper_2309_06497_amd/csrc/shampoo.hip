@@ -1285,6 +1285,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     auto parts = [](size_t rows, size_t cols) { return ((rows + GEMM_SMALL - 1) / GEMM_SMALL) * ((cols + GEMM_SMALL - 1) / GEMM_SMALL); };
     size_t ssh_parts = std::max(parts(m, n), (size_t)b.geom.chunks);
     if (b.t3) ssh_parts = std::max(ssh_parts, parts(m * n / b.dlast(), b.dlast()));
+    if (b.t3 && b.modes >= 3) ssh_parts = std::max(ssh_parts, (size_t)narrow_tiles(m * n / b.dlast() / b.td[b.modes - 2], b.td[b.modes - 2]));
     b.off_sshp = take(B * ssh_parts * 4);
     b.off_scale = take(B * 4);
     b.off_norms = take(B * 8);
@@ -2026,6 +2027,12 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           second(fp32 ? gemm_kernels<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM, false, true>()
                       : gemm_kernels<K_CONTIG, ROW_CONTIG, float, float, EPI_STORE_NORM>(), s);
       auto x2_wgs = [](const GemmX2Args &g) { return (int64_t)g.tiles_m * g.tiles_n * g.batch; };
+      // the last dimension of a tensor block, where a matrix product would be mostly padding
+      auto narrow = [&](const Bucket &b) { return b.t3 && b.modes >= 3 && b.dlast() <= NARROW_MAX && !fp32; };
+      int widest = 1;                      // one launch for all of them
+      for (const Bucket *b : todo) if (narrow(*b)) widest = std::max(widest, (int)b->dlast());
+      Batch<NarrowProductArgs> narrow_products(widest <= 4 ? product_narrow_kernel<1> : widest <= 8 ? product_narrow_kernel<2>
+                                               : widest <= 12 ? product_narrow_kernel<3> : product_narrow_kernel<4>, 256, s);
       // a block of m x n times its left root, and the other way round
       auto left_product = [&](const Bucket &b, float *out, bool result) {
         GemmArgs g{};
@@ -2157,6 +2164,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             h.M = dk; h.N = pre * post; h.K = dk; h.alpha = 1.f; h.beta = 0.f;
             h.batch = b.count;
             products.add(h);
+            if (narrow(b) && mid + 3 == b.modes) continue;      // the last product swaps back
             pm.d1 = dk; pm.d2 = pre;
             if ((rc = back.add(pm, (int64_t)pm.chunks * b.count))) return rc;
             swapped[i] ^= 1;
@@ -2168,6 +2176,17 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           if (!b.t3 || b.modes == 1) continue;
           const int dl = b.dlast();
           const int64_t mn = (int64_t)b.m * b.n;
+          if (narrow(b)) {
+            NarrowProductArgs na;
+            na.src = swapped[i] ? reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2) : bucket_t(b);
+            na.root = reinterpret_cast<const float *>(ws + b.off_Rinv); na.dst = reinterpret_cast<float *>(ws + b.off_P);
+            na.norm_partial = reinterpret_cast<float *>(ws + b.off_sshp);
+            na.gmax = reinterpret_cast<const float *>(ws + b.off_gmax) + b.count;
+            na.d = dl; na.d2 = b.td[b.modes - 2]; na.d1 = (int)(mn / dl / na.d2); na.blocks = b.count;
+            na.tiles2 = (na.d2 + NARROW_T2 - 1) / NARROW_T2; na.tiles = ssh_count[i] = narrow_tiles(na.d1, na.d2);
+            if ((rc = narrow_products.add(na, (int64_t)na.tiles * b.count))) return rc;
+            continue;
+          }
           GemmArgs q{};
           q.a.base = swapped[i] ? reinterpret_cast<float *>(ws + o->off_T2 + b.off_t2) : bucket_t(b); q.a.batch_stride = mn; q.a.ld = dl;
           q.b.base = ws + b.off_Rinv; q.b.batch_stride = (int64_t)dl * dl; q.b.ld = dl;
@@ -2181,7 +2200,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       }
       {
         StageTimer t(o, SHAMPOO_STAGE_PRECOND2, s);
-        if ((rc = tall2.flush()) || (rc = wide2.flush()) || (rc = second.flush())) return rc;
+        if ((rc = tall2.flush()) || (rc = wide2.flush()) || (rc = second.flush()) || (rc = narrow_products.flush())) return rc;
       }
       // planes of more blocks than the scratch has room for: in passes
       if (THREE)

@@ -106,6 +106,94 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const Group<PermuteArgs
   }
 }
 
+struct NarrowProductArgs {
+  const float *src;             // [slot][d2][d1][d]: the block with its two other indices swapped
+  const float *root;            // [slot][d][d]
+  float *dst;                   // [slot][d1][d2][d]
+  float *norm_partial;          // [slot][tiles]
+  const float *gmax;            // the result is divided by range_scale of the block's
+  int32_t d1, d2, d, tiles2, tiles, blocks;   // tiles2: tiles along d2
+  __device__ __forceinline__ void globals() { to_global(src, root, dst, norm_partial, gmax); }
+};
+constexpr int NARROW_MAX = 16, NARROW_T1 = 32, NARROW_T2 = 16;    // d; a workgroup's share of the other two
+inline int narrow_tiles(int64_t d1, int64_t d2) { return (int)((d1 + NARROW_T1 - 1) / NARROW_T1 * ((d2 + NARROW_T2 - 1) / NARROW_T2)); }
+
+// dst[i1][i2] = src[i2][i1] root: the last product of a tensor block with a last dimension of d <= 16, and the swap that
+// takes the block back to its own order.  Plain float32 multiply-adds: with d = 9 a tile of the GEMM is 93 % padding.  Bound by memory: chunks of 32 d and
+// 16 d values in and out, the exchange in LDS.  The blocks of ResNet-50 (most of them 128 x 128 x 9): 133 us for the GEMM and 34 for the swap before,
+// 28 so.  d <= 4 D4.  Workgroups: tiles x blocks.
+template <int D4>
+__global__ __launch_bounds__(256) void product_narrow_kernel(const Group<NarrowProductArgs> grp) {
+  constexpr int T1 = NARROW_T1, T2 = NARROW_T2, LD = 4 * D4 + 1;
+  __shared__ float x[T1 * T2 * LD];
+  __shared__ __align__(16) float root[NARROW_MAX][4 * D4];        // transposed
+  __shared__ float red[4];
+  int wg;
+  const NarrowProductArgs g = group_pick(grp, wg);
+  const int slot = wg / g.tiles, tile = wg - slot * g.tiles;
+  if (slot >= g.blocks) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), d = g.d;
+  const int t1 = tile / g.tiles2, i1 = t1 * T1, i2 = (tile - t1 * g.tiles2) * T2, n1 = min(T1, g.d1 - i1), n2 = min(T2, g.d2 - i2);
+  const int64_t block = (int64_t)slot * g.d1 * g.d2 * d;
+  const uint32_t over_d = (65536 + d - 1) / d;                    // e / d for e < 32 d <= 512
+  for (int e = tid; e < d * 4 * D4; e += 256) {
+    const int j = e / (4 * D4), k = e - j * (4 * D4);
+    root[j][k] = k < d ? g.root[(int64_t)slot * d * d + k * d + j] : 0.f;
+  }
+  float in[T2 / 4][T1 * 4 * D4 / 64];                             // all loads in flight
+#pragma unroll
+  for (int q = 0; q < T2 / 4; ++q) {
+    const int r2 = wave + 4 * q;
+    const float *row = g.src + block + ((int64_t)(i2 + min(r2, n2 - 1)) * g.d1 + i1) * d;
+#pragma unroll
+    for (int t = 0; t < T1 * 4 * D4 / 64; ++t) in[q][t] = row[min(lane + 64 * t, n1 * d - 1)];
+  }
+#pragma unroll
+  for (int q = 0; q < T2 / 4; ++q)
+#pragma unroll
+    for (int t = 0; t < T1 * 4 * D4 / 64; ++t) {
+      const int e = lane + 64 * t, r1 = (int)((uint32_t)e * over_d >> 16), r2 = wave + 4 * q;
+      if (e < n1 * d) x[(r1 * T2 + r2) * LD + e - r1 * d] = in[q][t];
+    }
+  __syncthreads();
+  const float inv = 1.f / range_scale(g.gmax[slot]);
+  float ss = 0.f;
+#pragma unroll
+  for (int q = 0; q < T1 * T2 / 256; ++q) {
+    const int row = tid + 256 * q;
+    if (row / T2 >= n1 || row % T2 >= n2) continue;
+    float *own = x + row * LD, v[4 * D4];
+#pragma unroll
+    for (int k = 0; k < 4 * D4; ++k) v[k] = k < d ? own[k] : 0.f;
+    for (int j = 0; j < d; ++j) {
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4 * D4; k += 4) {
+        const float4 r = *reinterpret_cast<const float4 *>(&root[j][k]);
+        s = fmaf(v[k], r.x, s); s = fmaf(v[k + 1], r.y, s); s = fmaf(v[k + 2], r.z, s); s = fmaf(v[k + 3], r.w, s);
+      }
+      s *= inv;
+      own[j] = s;
+      ss = fmaf(s, s, ss);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+  if (lane == 0) red[wave] = ss;
+  __syncthreads();
+  if (tid == 0) g.norm_partial[(int64_t)slot * g.tiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
+#pragma unroll
+  for (int q = 0; q < T1 / 4; ++q) {
+    const int r1 = wave + 4 * q;
+    float *out = g.dst + block + ((int64_t)(i1 + r1) * g.d2 + i2) * d;
+    if (r1 < n1)
+      for (int e = lane; e < n2 * d; e += 64) {
+        const int r2 = (int)((uint32_t)e * over_d >> 16);
+        out[e] = x[(r1 * T2 + r2) * LD + e - r2 * d];
+      }
+  }
+}
+
 struct GramReduceArgs {
   const void *partial;    // [slot][splits][d][d]
   float *factor;          // [slot][d][d]
