@@ -53,6 +53,7 @@ struct EwArgs {
 template <typename GT>
 __device__ __forceinline__ void load_g4(const GT *g, bool vec, int valid, float v[4]) {
   if (vec) { Elem<GT>::load4(g, v); return; }
+  if (valid == 4) { load_u4<GT>(g, *reinterpret_cast<float (*)[4]>(v)); return; }
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = e < valid ? Elem<GT>::load1(g + e) : 0.f;
 }
@@ -68,15 +69,30 @@ __device__ __forceinline__ void nt_store4(float *p, const float4 &v) {
   __builtin_nontemporal_store(x, reinterpret_cast<ew_floatx4 *>(p));
 }
 __device__ __forceinline__ void load_f4(const float *p, bool vec, int valid, float v[4]) {
-  if (vec) { Elem<float>::load4(p, v); return; }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = e < valid ? p[e] : 0.f;
+  load_g4<float>(p, vec, valid, v);
 }
 __device__ __forceinline__ void store_f4(float *p, bool vec, int valid, const float v[4]) {
   if (vec) { *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]); return; }
+  if (valid == 4) { store_u4(p, *reinterpret_cast<const float (*)[4]>(v)); return; }
 #pragma unroll
   for (int e = 0; e < 4; ++e) if (e < valid) p[e] = v[e];
 }
+
+// The quads of four columns that a thread has, row by row, from (i, j) on: U of them at a time, so that their loads are in flight
+// together whether they lie in one row or in several.
+template <int V> struct BoolConst { static constexpr int value = V; };
+template <int U> struct QuadWalk {
+  int i[U], j[U];
+  int row, col;
+  __device__ __forceinline__ void next(int first_col, int n, int col_step, int row_step) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      i[u] = row; j[u] = col;
+      col += col_step;
+      if (col >= n) { col = first_col; row += row_step; }
+    }
+  }
+};
 
 // workgroups of a bucket: chunks * blocks, chunk index fastest.
 // GS / GD: element types of the state-source and direction-source gradients.
@@ -100,39 +116,43 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
   const int r0 = chunk * g.geom.rows_per_wg;
   const int r1 = min(r0 + g.geom.rows_per_wg, g.m);
   float ss = 0.f, gmax = 0.f, smax = 0.f;
-  if (vec && g.same_src && !g.sgd_graft) {
-    // The common case, four column passes at a time, every load requested before the first store.
-    constexpr int U = 4;
-    const int step = 4 << lx;
-    for (int i = r0 + ty; i < r1; i += ny)
-      for (int j0 = tx * 4; j0 < n; j0 += U * step) {
-        float gq[U][4];
-        float4 av[U];
+  if (g.same_src && !g.sgd_graft) {
+    // The common case, four quads at a time, every load requested before the first store.
+    auto graft = [&](auto aligned) {
+      constexpr bool VEC = decltype(aligned)::value != 0;
+      constexpr int U = 4;
+      QuadWalk<U> at;
+      at.row = r0 + ty; at.col = tx * 4;
+      while (at.row < r1 && at.col < n) {
+        at.next(tx * 4, n, 4 << lx, ny);
+        float gq[U][4], av[U][4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = j0 + u * step;
-          if (j < n) {
-            Elem<GD>::load4(dp + (int64_t)i * ld + j, gq[u]);
-            av[u] = nt_load4(ap + (int64_t)i * ld + j);
+        for (int u = 0; u < U; ++u)
+          if (at.i[u] < r1) {
+            const int64_t e = (int64_t)at.i[u] * ld + at.j[u];
+            load_g4<GD>(dp + e, VEC, min(4, n - at.j[u]), gq[u]);
+            if constexpr (VEC) { const float4 x = nt_load4(ap + e); av[u][0] = x.x; av[u][1] = x.y; av[u][2] = x.z; av[u][3] = x.w; }
+            else load_f4(ap + e, false, min(4, n - at.j[u]), av[u]);
           }
-        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = j0 + u * step;
-          if (j < n) {
-            float a4[4] = {av[u].x, av[u].y, av[u].z, av[u].w};
+        for (int u = 0; u < U; ++u)
+          if (at.i[u] < r1) {
+            const int valid = min(4, n - at.j[u]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float gv = gq[u][e];
               gmax = fmaxf(gmax, fabsf(gv));
-              a4[e] = g.a_decay * a4[e] + g.a_gain * (gv * gv);
-              const float pg = (gv * g.gd_scale) / (sqrtf(g.a_bc * a4[e]) + g.graft_eps);
-              ss += pg * pg;
+              av[u][e] = g.a_decay * av[u][e] + g.a_gain * (gv * gv);
+              const float pg = (gv * g.gd_scale) / (sqrtf(g.a_bc * av[u][e]) + g.graft_eps);
+              if (VEC || e < valid) ss += pg * pg;
             }
-            nt_store4(ap + (int64_t)i * ld + j, make_float4(a4[0], a4[1], a4[2], a4[3]));
+            float *to = ap + (int64_t)at.i[u] * ld + at.j[u];
+            if constexpr (VEC) nt_store4(to, make_float4(av[u][0], av[u][1], av[u][2], av[u][3]));
+            else store_f4(to, false, valid, av[u]);
           }
-        }
       }
+    };
+    if (vec) graft(BoolConst<1>()); else graft(BoolConst<0>());
   } else
   for (int i = r0 + ty; i < r1; i += ny)
     for (int j = tx * 4; j < n; j += 4 << lx) {
@@ -239,42 +259,51 @@ __global__ __launch_bounds__(EW_THREADS) void update_kernel(const Group<EwArgs> 
   const int r1 = min(r0 + g.geom.rows_per_wg, g.m);
   const float sc = g.graft_only ? 0.f : g.scale[slot];
   if (chunk == 0 && tid < 2) g.gmax[tid * g.blocks + slot] = 0.f;      // read by all products of the step by now
-  if (vec && !g.graft_only && mp) {
-    // The common case, four column passes at a time: all twelve 16-byte loads of a thread are
+  if (!g.graft_only && mp) {
+    // The common case, four quads at a time: all twelve 16-byte loads of a thread are
     // requested before the first store (a store between two loads would make the second one
     // wait: the compiler cannot tell that M, W and P do not overlap).
-    constexpr int U = 4;
-    const int step = 4 << lx;
-    for (int i = r0 + ty; i < r1; i += ny)
-      for (int j0 = tx * 4; j0 < n; j0 += U * step) {
-        float4 pv[U], wv[U], mv[U];
+    auto update = [&](auto aligned) {
+      constexpr bool VEC = decltype(aligned)::value != 0;
+      constexpr int U = 4;
+      QuadWalk<U> at;
+      at.row = r0 + ty; at.col = tx * 4;
+      while (at.row < r1 && at.col < n) {
+        at.next(tx * 4, n, 4 << lx, ny);
+        float pv[U][4], wv[U][4], mv[U][4];
+        auto get = [&](const float *p, int u, float (&v)[4]) {
+          if constexpr (VEC) { const float4 x = nt_load4(p); v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; }
+          else load_f4(p, false, min(4, n - at.j[u]), v);
+        };
+        auto put = [&](float *p, int u, const float (&v)[4]) {
+          if constexpr (VEC) nt_store4(p, make_float4(v[0], v[1], v[2], v[3]));
+          else store_f4(p, false, min(4, n - at.j[u]), v);
+        };
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = j0 + u * step;
-          if (j < n) {
-            pv[u] = nt_load4(pp + (int64_t)i * n + j);
-            wv[u] = nt_load4(wp + (int64_t)i * ld + j);
-            mv[u] = nt_load4(mp + (int64_t)i * ld + j);
+        for (int u = 0; u < U; ++u)
+          if (at.i[u] < r1) {
+            const int64_t e = (int64_t)at.i[u] * ld + at.j[u];
+            get(pp + (int64_t)at.i[u] * n + at.j[u], u, pv[u]);
+            get(wp + e, u, wv[u]);
+            get(mp + e, u, mv[u]);
           }
-        }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int j = j0 + u * step;
-          if (j < n) {
-            float p4[4] = {pv[u].x * sc, pv[u].y * sc, pv[u].z * sc, pv[u].w * sc};
-            float w4[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
-            float m4[4] = {mv[u].x, mv[u].y, mv[u].z, mv[u].w};
+        for (int u = 0; u < U; ++u)
+          if (at.i[u] < r1) {
+            const int64_t at_e = (int64_t)at.i[u] * ld + at.j[u];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              if (g.wd_decoupled != 0.f) p4[e] -= g.wd_decoupled * w4[e];
-              m4[e] = g.mu * m4[e] + p4[e];
-              w4[e] += g.lr * (g.nesterov ? g.mu * m4[e] + p4[e] : m4[e]);
+              float p = pv[u][e] * sc;
+              if (g.wd_decoupled != 0.f) p -= g.wd_decoupled * wv[u][e];
+              mv[u][e] = g.mu * mv[u][e] + p;
+              wv[u][e] += g.lr * (g.nesterov ? g.mu * mv[u][e] + p : mv[u][e]);
             }
-            nt_store4(mp + (int64_t)i * ld + j, make_float4(m4[0], m4[1], m4[2], m4[3]));
-            nt_store4(wp + (int64_t)i * ld + j, make_float4(w4[0], w4[1], w4[2], w4[3]));
+            put(mp + at_e, u, mv[u]);
+            put(wp + at_e, u, wv[u]);
           }
-        }
       }
+    };
+    if (vec) update(BoolConst<1>()); else update(BoolConst<0>());
     return;
   }
   for (int i = r0 + ty; i < r1; i += ny)

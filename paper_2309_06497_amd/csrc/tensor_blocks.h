@@ -37,6 +37,7 @@ constexpr int TENSOR_COPY_SET = 40;
 struct TensorCopySet { TensorCopyArgs t[TENSOR_COPY_SET]; int32_t count; };
 static_assert(sizeof(TensorCopySet) <= 4096, "kernel arguments");
 
+constexpr int COPY_U = 4;
 // Block index = ((k1 * k2n + k2) * k3n + k3) * k4n + k4.  All pieces before the last one of a
 // dimension are full, so the offset of a block inside the copy is
 // s1 D2 D3 D4 + d1 s2 D3 D4 + d1 d2 s3 D4 + d1 d2 d3 s4.
@@ -55,12 +56,24 @@ __device__ __forceinline__ void tensor_copy(const TensorCopyArgs &g, uint32_t wg
   T *copy = static_cast<T *>(g.copy) + voff;
   const uint32_t e4 = (uint32_t)d4, e3 = (uint32_t)d3, e2 = (uint32_t)d2, n = (uint32_t)(d1 * d2 * d3 * d4);
   const int64_t l3 = g.D4, l2 = g.D3 * l3, l1 = g.D2 * l2;
-  for (uint32_t e = chunk * 256 + threadIdx.x; e < n; e += (uint32_t)g.chunks * 256) {
-    uint32_t r = e;
-    const uint32_t q4 = r / e4, i4 = r - q4 * e4, q3 = q4 / e3, i3 = q4 - q3 * e3, i1 = q3 / e2, i2 = q3 - i1 * e2;
-    const int64_t at = i1 * l1 + i2 * l2 + i3 * l3 + i4;
-    if (SCATTER) tensor[at] = copy[e];
-    else copy[e] = tensor[at];
+  const uint32_t step = (uint32_t)g.chunks * 256;
+  for (uint32_t e0 = chunk * 256 + threadIdx.x; e0 < n; e0 += COPY_U * step) {     // several loads in flight
+    int64_t at[COPY_U];
+    T v[COPY_U];
+#pragma unroll
+    for (int u = 0; u < COPY_U; ++u) {
+      const uint32_t e = min(e0 + u * step, n - 1);
+      const uint32_t q4 = e / e4, i4 = e - q4 * e4, q3 = q4 / e3, i3 = q4 - q3 * e3, i1 = q3 / e2, i2 = q3 - i1 * e2;
+      at[u] = i1 * l1 + i2 * l2 + i3 * l3 + i4;
+      v[u] = SCATTER ? copy[e] : tensor[at[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < COPY_U; ++u) {
+      const uint32_t e = e0 + u * step;
+      if (e >= n) continue;
+      if (SCATTER) tensor[at[u]] = v[u];
+      else copy[e] = v[u];
+    }
   }
 }
 template <bool SCATTER>
@@ -99,10 +112,19 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const Group<PermuteArgs
   const float *fin = g.src ? g.src + (int64_t)slot * n : nullptr;
   float *out = g.dst + (int64_t)slot * n;
   const uint32_t d1 = g.d1, d2 = g.d2, d3 = g.d3;   // 32-bit divisions: a block has less than 2^31 elements
-  for (uint32_t e = chunk * 256 + threadIdx.x; e < n; e += g.chunks * 256) {
-    const uint32_t q = e / d3, i3 = e - q * d3, i1 = q / d2, i2 = q - i1 * d2;
-    const float v = fin ? fin[e] : Elem<T>::load1(tin + e);
-    out[(i2 * d1 + i1) * d3 + i3] = v;
+  const uint32_t step = g.chunks * 256;
+  for (uint32_t e0 = chunk * 256 + threadIdx.x; e0 < n; e0 += COPY_U * step) {
+    float v[COPY_U];
+#pragma unroll
+    for (int u = 0; u < COPY_U; ++u) {
+      const uint32_t e = min(e0 + u * step, n - 1);
+      v[u] = fin ? fin[e] : Elem<T>::load1(tin + e);
+    }
+#pragma unroll
+    for (int u = 0; u < COPY_U; ++u) {
+      const uint32_t e = e0 + u * step, q = e / d3, i3 = e - q * d3, i1 = q / d2, i2 = q - i1 * d2;
+      if (e < n) out[(i2 * d1 + i1) * d3 + i3] = v[u];
+    }
   }
 }
 
@@ -256,7 +278,15 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const Group<GramReduce
   if (slot >= g.blocks || e >= dd) return;
   const T *p = static_cast<const T *>(g.partial) + (int64_t)slot * g.splits * dd + e;
   double acc = 0.0;
-  for (int s = 0; s < g.splits; ++s) acc += (double)p[(int64_t)s * dd];
+  int s = 0;
+  for (; s + 8 <= g.splits; s += 8) {            // eight loads in flight, summed in order
+    T v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)(s + u) * dd];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc += (double)v[u];
+  }
+  for (; s < g.splits; ++s) acc += (double)p[(int64_t)s * dd];
   float *f = g.factor + (int64_t)slot * dd + e;
   *f = (float)(g.beta * (double)*f + g.alpha * acc);
 }
