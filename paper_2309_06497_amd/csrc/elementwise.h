@@ -127,13 +127,12 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
         at.next(tx * 4, n, 4 << lx, ny);
         float gq[U][4], av[U][4];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (at.i[u] < r1) {
-            const int64_t e = (int64_t)at.i[u] * ld + at.j[u];
-            load_g4<GD>(dp + e, VEC, min(4, n - at.j[u]), gq[u]);
-            if constexpr (VEC) { const float4 x = nt_load4(ap + e); av[u][0] = x.x; av[u][1] = x.y; av[u][2] = x.z; av[u][3] = x.w; }
-            else load_f4(ap + e, false, min(4, n - at.j[u]), av[u]);
-          }
+        for (int u = 0; u < U; ++u) {                 // rows past the end: the last one again, loads without a branch
+          const int64_t e = (int64_t)min(at.i[u], r1 - 1) * ld + at.j[u];
+          load_g4<GD>(dp + e, VEC, min(4, n - at.j[u]), gq[u]);
+          if constexpr (VEC) { const float4 x = nt_load4(ap + e); av[u][0] = x.x; av[u][1] = x.y; av[u][2] = x.z; av[u][3] = x.w; }
+          else load_f4(ap + e, false, min(4, n - at.j[u]), av[u]);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (at.i[u] < r1) {
@@ -280,13 +279,13 @@ __global__ __launch_bounds__(EW_THREADS) void update_kernel(const Group<EwArgs> 
           else store_f4(p, false, min(4, n - at.j[u]), v);
         };
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (at.i[u] < r1) {
-            const int64_t e = (int64_t)at.i[u] * ld + at.j[u];
-            get(pp + (int64_t)at.i[u] * n + at.j[u], u, pv[u]);
-            get(wp + e, u, wv[u]);
-            get(mp + e, u, mv[u]);
-          }
+        for (int u = 0; u < U; ++u) {                 // rows past the end: the last one again, loads without a branch
+          const int i = min(at.i[u], r1 - 1);
+          const int64_t e = (int64_t)i * ld + at.j[u];
+          get(pp + (int64_t)i * n + at.j[u], u, pv[u]);
+          get(wp + e, u, wv[u]);
+          get(mp + e, u, mv[u]);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (at.i[u] < r1) {
