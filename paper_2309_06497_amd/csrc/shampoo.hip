@@ -527,6 +527,9 @@ template <typename Args, int RESERVE = 0, typename... Extra> struct Batch {
 // over 128 of 6200 tiles, 893 and 843.
 constexpr int64_t GEMM_FEW_TILES = 1024;
 constexpr int GEMM_SHORT_K = 128;
+
+constexpr int64_t OVERLAP_STAGED = 4 << 20;
+
 struct GemmKernels { Batch<GemmArgs>::Kernel large, small; };
 template <int AO, int BO, typename TA, typename TB, int EPI, bool ACC64 = false, bool FP32 = false> constexpr GemmKernels gemm_kernels() {
   return {gemm_mfma_kernel<AO, BO, TA, TB, EPI, false, ACC64, FP32>, gemm_mfma_kernel<AO, BO, TA, TB, EPI, false, ACC64, FP32, GEMM_SMALL>};
@@ -1602,8 +1605,23 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     hipLaunchKernelGGL(prep_kernel<GT>, dim3((unsigned)n_prep), dim3(EW_THREADS), 0, s, pa);
     HIP_TRY(hipGetLastError());
   }
+  // The small blocks' kernel beside the stages of the others.  The fork and the join cost the host some 15 us, which shows
+  // where the launches of the stages take as long as their kernels: not below 4e6 elements in the stages.  Step one after the other and so:
+  // ResNet-50 in blocks of 256, 101 parameters, 283 and 241 us; one layer of 640 in blocks of 512 183 and 144; ResNet-50 with
+  // convolution tensors, 101 and 161 parameters, 234 and 205, 695 and 682; its first 14 (0.2e6 elements) 104 and 130.
+  int64_t staged = 0;
+  if (small_ok) for (const Bucket &b : p.buckets) if (!b.small()) staged += (int64_t)b.m * b.n * b.count;
+  bool beside = staged >= OVERLAP_STAGED && !o->timing;
+  if (beside && o->aux.state == 0) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;       // streams are created outside of a capture
+    HIP_TRY(hipStreamIsCapturing(s, &capture));
+    beside = capture == hipStreamCaptureStatusNone;
+  }
+  beside = beside && o->aux.ready();
+  if (beside && (rc = aux_fork(&o->aux, 2, s))) return rc;
   if (small_ok) {
     StageTimer t(o, SHAMPOO_STAGE_FUSED, s);
+    const hipStream_t own = beside ? o->aux.stream[0] : s;
     SmallStepArgs f;
     f.blocks = reinterpret_cast<const SmallBlock *>(ws + o->off_small); f.ws = ws;
     f.w_table = wtab; f.g_table = gtab; f.a_state = A; f.m_state = M; f.gf_state = Gf;
@@ -1619,11 +1637,11 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     const dim3 grid((unsigned)(o->n_small + (int64_t)p.diag_chunks.size())), block(SB_THREADS);
     constexpr bool FILT_ONLY = sizeof(GT) == 2 && sizeof(GD) == 4;   // bf16 gradients with float directions are filtered
     if (FILT_ONLY || Gf) {
-      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, true>), grid, block, 0, s, f);
-      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, true>), grid, block, 0, s, f);
+      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, true>), grid, block, 0, own, f);
+      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, true>), grid, block, 0, own, f);
     } else {
-      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, false>), grid, block, 0, s, f);
-      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, false>), grid, block, 0, s, f);
+      if (o->small_half) hipLaunchKernelGGL((block_step_small_kernel<GT, SB_HALF, false>), grid, block, 0, own, f);
+      else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, false>), grid, block, 0, own, f);
     }
     HIP_TRY(hipGetLastError());
     for (size_t i = 0; i < p.buckets.size(); ++i) if (p.buckets[i].small()) o->upper_stale[i] = UPPER_HALF_STALE;
@@ -2261,7 +2279,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     hipLaunchKernelGGL(diag_kernel<GT>, dim3((unsigned)p.diag_chunks.size()), dim3(EW_THREADS), 0, s, d);
     HIP_TRY(hipGetLastError());
   }
-  return SHAMPOO_OK;
+  return beside ? aux_join(&o->aux, 2, s) : (int)SHAMPOO_OK;
 }
 
 }  // namespace
