@@ -452,6 +452,16 @@ __global__ __launch_bounds__(256) void pointer_table_kernel(const PointerSet p) 
   if (i < p.count) { p.w_table[i] = p.w[i]; p.g_table[i] = p.g[i]; }
 }
 
+struct ClearArgs {
+  float *p; int32_t n;
+  __device__ __forceinline__ void globals() { to_global(p); }
+};
+__global__ __launch_bounds__(256) void clear_kernel(const Group<ClearArgs> grp) {
+  int wg;
+  const ClearArgs g = group_pick(grp, wg);
+  const int i = wg * 256 + threadIdx.x;
+  if (i < g.n) g.p[i] = 0.f;
+}
 __global__ __launch_bounds__(256) void fill_kernel(float *p, float v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = v;

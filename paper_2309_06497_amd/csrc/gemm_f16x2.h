@@ -107,15 +107,24 @@ __device__ __forceinline__ void split2h(float x, uint16_t &h, uint16_t &l) {
 }
 
 // stats[2 b] = max |x_ij|, stats[2 b + 1] = max_i sum_j |x_ij| of the n x n matrix b.
-// grid (batch, parts of the rows), 256 threads; stats start at zero (values are not negative, so that their
+// Workgroups: parts of the rows x matrices, 256 threads; stats start at zero (values are not negative, so that their
 // bits order like integers and the result does not depend on the order).  One workgroup per matrix read the 192
 // roots of two transformer layers at 0.45 TB/s, 1.7 ms of a refresh.
-__global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float *stats, int n) {
+struct MatrixStatsArgs {
+  const float *x; float *stats;
+  int32_t n, parts, count;
+  __device__ __forceinline__ void globals() { to_global(x, stats); }
+};
+__global__ __launch_bounds__(256) void matrix_stats_kernel(const Group<MatrixStatsArgs> grp) {
   __shared__ float red[8];
-  const float *p = x + (int64_t)blockIdx.x * n * n;
+  int wg;
+  const MatrixStatsArgs g = group_pick(grp, wg);
+  const int b = wg / g.parts, part = wg - b * g.parts, n = g.n;
+  if (b >= g.count) return;
+  const float *p = g.x + (int64_t)b * n * n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float mx = 0.f, rs = 0.f;
-  for (int i = 4 * blockIdx.y + wave; i < n; i += 4 * gridDim.y) {
+  for (int i = 4 * part + wave; i < n; i += 4 * g.parts) {
     float sum = 0.f;
     for (int j = lane; j < n; j += 64) {
       const float v = fabsf(p[(int64_t)i * n + j]);
@@ -131,20 +140,30 @@ __global__ __launch_bounds__(256) void matrix_stats_kernel(const float *x, float
   if (lane == 0) { red[wave] = mx; red[4 + wave] = rs; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int *out = reinterpret_cast<int *>(stats + 2 * blockIdx.x);
+    int *out = reinterpret_cast<int *>(g.stats + 2 * b);
     atomicMax(out, __float_as_int(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
     atomicMax(out + 1, __float_as_int(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]))));
   }
 }
 
 // out[plane][i] = the two fp16 or three bf16 terms of s_b in[i], s_b = pow2_scale_f16(stats[2 b]) for the
-// matrix b that element i belongs to; per, its elements, is a multiple of 64.  grid (ceil(per / 1024), batch), 256 threads.
+// matrix b that element i belongs to; per, its elements, is a multiple of 64.  Workgroups: ceil(per / 1024) x matrices, 256 threads.
+struct SplitRootsArgs {
+  const float *in, *stats; uint16_t *out;
+  int64_t per;
+  int32_t pieces, count;        // ceil(per / 1024), matrices
+  __device__ __forceinline__ void globals() { to_global(in, stats, out); }
+};
 template <bool THREE>
-__global__ __launch_bounds__(256) void split_roots_kernel(const float *in, const float *stats, uint16_t *out, int64_t per, int64_t count) {
-  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, i = blockIdx.y * per + e;
-  if (e >= per) return;
-  const float sc = pow2_scale_f16(stats[2 * blockIdx.y]);
-  const float4 x = *reinterpret_cast<const float4 *>(in + i);
+__global__ __launch_bounds__(256) void split_roots_kernel(const Group<SplitRootsArgs> grp) {
+  int wg;
+  const SplitRootsArgs g = group_pick(grp, wg);
+  const int b = wg / g.pieces;
+  const int64_t e = ((int64_t)(wg - b * g.pieces) * 256 + threadIdx.x) * 4, i = b * g.per + e, count = g.count * g.per;
+  if (b >= g.count || e >= g.per) return;
+  const float sc = pow2_scale_f16(g.stats[2 * b]);
+  const float4 x = *reinterpret_cast<const float4 *>(g.in + i);
+  uint16_t *out = g.out;
   if constexpr (THREE) {
     uint16_t q[4][3];
     split3b(x.x * sc, q[0]); split3b(x.y * sc, q[1]); split3b(x.z * sc, q[2]); split3b(x.w * sc, q[3]);

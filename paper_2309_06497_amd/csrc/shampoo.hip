@@ -1398,25 +1398,27 @@ struct StageTimer {
 // Re-splits the roots of every bucket that keeps them as planes (after create and after
 // every refresh).
 int split_roots(shampoo_opt *o, hipStream_t s) {
+  int rc;
+  Batch<ClearArgs> clears(clear_kernel, 256, s);
+  Batch<MatrixStatsArgs> stats(matrix_stats_kernel, 256, s);
+  Batch<SplitRootsArgs> two(split_roots_kernel<false>, 256, s), three(split_roots_kernel<true>, 256, s);
   for (auto &b : o->plan.buckets) {
     if (!b.planes) continue;
-    const float *Li = reinterpret_cast<const float *>(o->ws + b.off_Linv), *Ri = reinterpret_cast<const float *>(o->ws + b.off_Rinv);
-    float *stat_l = reinterpret_cast<float *>(o->ws + b.off_stat_l), *stat_r = reinterpret_cast<float *>(o->ws + b.off_stat_r);
     for (int side = 0; side < 2; ++side) {
       const int n = side == 0 ? b.m : b.n;
-      const float *x = side == 0 ? Li : Ri;
-      float *stat = side == 0 ? stat_l : stat_r;
+      const float *x = reinterpret_cast<const float *>(o->ws + (side == 0 ? b.off_Linv : b.off_Rinv));
+      float *stat = reinterpret_cast<float *>(o->ws + (side == 0 ? b.off_stat_l : b.off_stat_r));
       const int64_t per = (int64_t)n * n;
-      if (const int rc = launch_fill(stat, 0.f, 2 * (int64_t)b.count, s)) return rc;
-      hipLaunchKernelGGL(matrix_stats_kernel, dim3(b.count, std::max(1, std::min(32, n / 32))), dim3(256), 0, s, x, stat, n);
-      uint16_t *out = reinterpret_cast<uint16_t *>(o->ws + (side == 0 ? b.off_Linvp : b.off_Rinvp));
-      const dim3 grid((unsigned)((per + 1023) / 1024), b.count);
-      if (b.three) hipLaunchKernelGGL(split_roots_kernel<true>, grid, dim3(256), 0, s, x, stat, out, per, (int64_t)b.count * per);
-      else hipLaunchKernelGGL(split_roots_kernel<false>, grid, dim3(256), 0, s, x, stat, out, per, (int64_t)b.count * per);
+      const MatrixStatsArgs ms{x, stat, n, std::max(1, std::min(32, n / 32)), b.count};
+      const SplitRootsArgs sr{x, stat, reinterpret_cast<uint16_t *>(o->ws + (side == 0 ? b.off_Linvp : b.off_Rinvp)), per,
+                              (int32_t)((per + 1023) / 1024), b.count};
+      if ((rc = clears.add(ClearArgs{stat, 2 * b.count}, (2 * (int64_t)b.count + 255) / 256)) ||
+          (rc = stats.add(ms, (int64_t)ms.parts * b.count)) || (rc = (b.three ? three : two).add(sr, (int64_t)sr.pieces * b.count)))
+        return rc;
     }
-    HIP_TRY(hipGetLastError());
   }
-  return SHAMPOO_OK;
+  if ((rc = clears.flush()) || (rc = stats.flush()) || (rc = two.flush())) return rc;
+  return three.flush();
 }
 
 // Coupled Newton with the guard of Sec. 3.2.3.  The paper retries a failed root computation in
@@ -1450,7 +1452,7 @@ int newton_root_guarded(shampoo_opt *o, const float *F, int dim, int count, floa
 // The bf16 factor update writes only the tiles on and below the diagonal of tiles, the step of a small block in one
 // workgroup only the lower triangle; whoever needs the whole symmetric factor (the refresh, the state query) completes
 // it first.
-int complete_factors(shampoo_opt *o, size_t bucket, hipStream_t s) {
+int complete_factors(shampoo_opt *o, size_t bucket, Batch<MirrorArgs> &mirrors) {
   if (o->upper_stale[bucket] == UPPER_FRESH) return SHAMPOO_OK;
   const Bucket &b = o->plan.buckets[bucket];
   const int dims[2] = {(int)b.m, (int)b.n};
@@ -1459,12 +1461,16 @@ int complete_factors(shampoo_opt *o, size_t bucket, hipStream_t s) {
     const int n = dims[side], pieces = (n + 31) / 32;
     const int all = o->upper_stale[bucket] == UPPER_HALF_STALE ? 1 : 0;
     if (n <= (all ? 1 : BM)) continue;   // a single tile: nothing above the diagonal of tiles
-    hipLaunchKernelGGL(mirror_upper_tiles_kernel, dim3(pieces, pieces, b.count), dim3(256), 0, s,
-                       reinterpret_cast<float *>(o->ws + offs[side]), (int64_t)n * n, n, all);
+    const MirrorArgs g{reinterpret_cast<float *>(o->ws + offs[side]), n, all, pieces, b.count};
+    if (const int rc = mirrors.add(g, (int64_t)pieces * pieces * b.count)) return rc;
   }
-  HIP_TRY(hipGetLastError());
   o->upper_stale[bucket] = UPPER_FRESH;
   return SHAMPOO_OK;
+}
+int complete_factors(shampoo_opt *o, size_t bucket, hipStream_t s) {
+  Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
+  const int rc = complete_factors(o, bucket, mirrors);
+  return rc ? rc : mirrors.flush();
 }
 
 // A factor of dimension `dim` that has so far summed (step + 1) gradients of `cols` columns
@@ -1952,9 +1958,11 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       }
       return root_inverse_batched(F, dim, count, c.epsilon, r, c2, Fi, nullptr, nullptr, fail_count, ws + o->off_eig, lay, s, &o->aux, nullptr, w);
     };
+    Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
+    for (size_t i = 0; i < p.buckets.size(); ++i) if ((rc = complete_factors(o, i, mirrors))) return rc;
+    if ((rc = mirrors.flush())) return rc;
     for (size_t i = 0; i < p.buckets.size(); ++i) {
       auto &b = p.buckets[i];
-      if ((rc = complete_factors(o, i, s))) return rc;
       const bool newton = c.root_method == SHAMPOO_ROOT_NEWTON;
       if (b.t3) {
         // one root per dimension, exponent 2 r / w (Sec. 2.3: "root 2w")

@@ -308,12 +308,21 @@ __global__ __launch_bounds__(GEMM_THREADS, ACC64 ? 2 : 3) void syrk_bf16_kernel(
 
 // C[i][j] = C[j][i] for every element whose tile (of BM x BM) lies above the diagonal of tiles, or, `all`, for every
 // element above the diagonal: completes a factor that syrk_bf16_kernel, or block_step_small_kernel, has updated.
-// grid (ceil(n / 32), ceil(n / 32), batch), 256 threads; a 32 x 32 piece never straddles two tiles.
-__global__ __launch_bounds__(256) void mirror_upper_tiles_kernel(float *c, int64_t batch_stride, int n, int all) {
+// Workgroups: ceil(n / 32) x ceil(n / 32) x matrices, 256 threads; a 32 x 32 piece never straddles two tiles.
+struct MirrorArgs {
+  float *c;
+  int32_t n, all, pieces, count;   // ceil(n / 32), matrices
+  __device__ __forceinline__ void globals() { to_global(c); }
+};
+__global__ __launch_bounds__(256) void mirror_upper_tiles_kernel(const Group<MirrorArgs> grp) {
   __shared__ float t[32][33];
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;     // destination piece (i0, j0)
-  if (all ? i0 > j0 : i0 / BM >= j0 / BM) return;
-  float *m = c + (int64_t)blockIdx.z * batch_stride;
+  int wg;
+  const MirrorArgs g = group_pick(grp, wg);
+  const int row = wg / g.pieces, b = row / g.pieces, n = g.n;
+  if (b >= g.count) return;
+  const int i0 = (row - b * g.pieces) * 32, j0 = (wg - row * g.pieces) * 32;     // destination piece (i0, j0)
+  if (g.all ? i0 > j0 : i0 / BM >= j0 / BM) return;
+  float *m = g.c + (int64_t)b * n * n;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
   for (int r = ty; r < 32; r += 8) {
