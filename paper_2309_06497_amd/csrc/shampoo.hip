@@ -395,9 +395,9 @@ bool band_serves(int n, float r) {
 }
 
 // Workspace of the band reduction for chunks of matrices: 33 MB for one of 1024, of which 20 are the eliminations
-// of all poles; 128 of them fit.  Block Jacobi takes half of it.  The refresh of 24 transformer layers (2304 matrices of 1024):
-// 550 ms, 592 in chunks of 3 GiB.
-constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30;
+// of all poles; 256 of them fit, 3 % of the GPU's memory.  The chains of panels and pivots do not take longer for more matrices: refresh of two
+// transformer layers (192 matrices of 1024) 33.0 ms in chunks of 4 GiB, 30.0 in one.
+constexpr size_t BAND_CHUNK_BYTES = (size_t)8 << 30;
 struct BandLayout {
   int32_t np = 0, nb = 0, chunk = 0;
   size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
@@ -893,10 +893,11 @@ struct BandSolve {
   }
 };
 
-// Sub-chunks on streams of their own: while one is in the chain of a panel's columns or of the pivots, the
-// other has products to do.  64 matrices of 1024: 19.4 ms on one stream, 18.1 on two, 18.3 on three, 18.5 on
-// four; 16 of 2048: 43.6, 44.4, 45.3, 45.7; refresh of two transformer layers: 47.1, 44.6, 44.3, 44.7.
-constexpr int BAND_STREAMS = 2;
+// Parts on streams of their own: while one is in the chain of a panel's columns or of the pivots, the
+// others have products to do.  On two and on three streams: 64 matrices of 1024 12.8 and 12.4 ms, refresh of two layers of 1300
+// 20.7 and 20.2, of two transformer layers (192 matrices of 1024) 30.7 and 30.0; 16 of 2048 26.9 and 27.1, 8 of 172 0.80 and 0.87.
+constexpr int BAND_STREAMS = 3;
+constexpr int64_t BAND_MANY = 32;        // matrices from which on there are three
 static_assert(BAND_STREAMS < JAC_STREAMS, "helper streams, and one more");
 
 // Forks the helper streams off s and joins them again.
@@ -920,7 +921,7 @@ struct RootJob {
 };
 
 // Jobs of one exponent, of any sizes: as many of their matrices at a time as fit into `room` bytes of ws, those
-// in two halves on two streams.  The launches of few matrices leave most of the GPU idle, and every panel of every size is a
+// in equal parts on two or three streams.  The launches of few matrices leave most of the GPU idle, and every panel of every size is a
 // launch: the two sides of a dozen buckets take one pass here, not one each.  Refresh of three layers of 700 in blocks of 512:
 // 31 ms one size at a time, 5.4 so; two layers of 1300 in blocks of 1024: 100 and 24; one layer of 896 in blocks of 256, where
 // nothing is ragged: 1.9 and 1.5.
@@ -929,11 +930,13 @@ int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *
   int rc;
   size_t i = 0;
   int done = 0;                            // matrices of todo[i]
+  int64_t left_over = 0;
+  for (const RootJob &j : todo) left_over += j.batch;
   while (i < todo.size()) {
     BandSolve solve[BAND_STREAMS];
     size_t at = 0;
     int turn = 0;
-    for (int k = 0; k < BAND_STREAMS; ++k) { solve[k].table = &table; solve[k].s = k == 0 || !aux ? s : aux->stream[k - 1]; }
+    const int subs = !aux ? 1 : left_over >= BAND_MANY ? BAND_STREAMS : 2;
     while (i < todo.size()) {
       const RootJob &j = todo[i];
       const int left = std::min(j.batch - done, 32768);
@@ -955,8 +958,7 @@ int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *
       base.kf = reinterpret_cast<double *>(w + e.off_kf); base.gf = reinterpret_cast<double *>(w + e.off_gf);
       base.v1 = reinterpret_cast<double *>(w + e.off_v1);
       base.ok = reinterpret_cast<int32_t *>(w + e.off_ok); base.dec = reinterpret_cast<int32_t *>(w + e.off_dec);
-      // halves; odd ones out go to either stream in turn
-      const int subs = aux ? BAND_STREAMS : 1;
+      // in equal parts; odd ones out go to the streams in turn
       int first = 0;
       for (int k = 0; k < subs; ++k) {
         const int part = cnt / subs + ((k + turn) % subs < cnt % subs ? 1 : 0);
@@ -968,17 +970,23 @@ int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *
         solve[k].jobs.push_back(job);
         first += part;
       }
-      turn += cnt;
+      turn += subs - cnt % subs;
+      left_over -= cnt;
       at += e.bytes;
       done += cnt;
       if (done < j.batch) break;           // no room for the rest
       ++i; done = 0;
     }
     if (at == 0) return SHAMPOO_ERR_WORKSPACE;
-    const int subs = aux && !solve[1].jobs.empty() ? (solve[0].jobs.empty() ? 0 : 2) : 1;
+    int n_solve = 0;                       // the parts that have matrices, in front
+    for (int k = 0; k < subs; ++k)
+      if (!solve[k].jobs.empty()) {
+        if (k != n_solve) solve[n_solve].jobs.swap(solve[k].jobs);
+        solve[n_solve].table = &table;
+        solve[n_solve].s = n_solve == 0 ? s : aux->stream[n_solve - 1];
+        ++n_solve;
+      }
     BandSolve *v = solve;
-    if (subs == 0) { solve[0].jobs.swap(solve[1].jobs); }
-    const int n_solve = std::max(subs, 1);
     if ((rc = aux_fork(aux, n_solve, s))) return rc;
     int panels = 0, groups = 0;
     for (int k = 0; k < n_solve; ++k) { panels = std::max(panels, v[k].panels()); groups = std::max(groups, v[k].groups()); }
