@@ -394,10 +394,11 @@ bool band_serves(int n, float r) {
   return n > JAC_SMALL_MAX && n <= BAND_MAX_N && !(r > 0.4f && n <= 224) && rat_table(r, table);
 }
 
-// Workspace of the band reduction for chunks of matrices: 33 MB for one of 1024, of which 20 are the eliminations
-// of all poles; 256 of them fit, 3 % of the GPU's memory.  The chains of panels and pivots do not take longer for more matrices: refresh of two
-// transformer layers (192 matrices of 1024) 33.0 ms in chunks of 4 GiB, 30.0 in one.
-constexpr size_t BAND_CHUNK_BYTES = (size_t)8 << 30;
+// Workspace of the band reduction: 33 MB for a matrix of 1024, of which 20 are the eliminations of all poles.  Chunks of one size take up to
+// BAND_CHUNK_BYTES (128 of 1024), the pass over all sizes of a refresh up to BAND_PASS_BYTES, 2 % of the GPU's memory: the chains
+// of panels and pivots do not take longer for more matrices.  Refresh of two transformer layers (192 matrices of 1024) 33.0 ms
+// in passes of 4 GiB, 30.0 in one.
+constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30, BAND_PASS_BYTES = (size_t)6 << 30;
 struct BandLayout {
   int32_t np = 0, nb = 0, chunk = 0;
   size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
@@ -1335,8 +1336,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
                                              std::max(eM[0].back().bytes, eM[1].back().bytes)));
     max_count = std::max(max_count, (size_t)b.count);
   }
-  // roots of all sizes at once where they fit into what one size may take (band_roots)
-  eig_bytes = std::max(eig_bytes, std::min(band_all, BAND_CHUNK_BYTES));
+  // roots of all sizes at once (band_roots)
+  eig_bytes = std::max(eig_bytes, std::min(band_all, BAND_PASS_BYTES));
   // Sets of buckets whose scratch fits side by side into what the largest bucket needs, or SET_BYTES
   size_t t_bytes = 0, t2_bytes = 0;
   {
