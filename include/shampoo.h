@@ -122,8 +122,9 @@ typedef struct {
                              below 2^-16 of a block's largest keep absolute, not relative,
                              accuracy).  Float32 or filtered gradients, more than 128 rows and columns:
                              three bf16 planes each, all 24 bits of every element, six products;
-                             the factor updates of float32 gradients take the same planes.
-                             SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA          */
+                             the factor updates of float32 gradients take the same planes.  All other
+                             blocks: the same three terms, split on the way into the kernels.
+                             SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA for Lbar G Rbar */
   int32_t warm_start_roots; /* != 0: the eigendecomposition of a refresh starts from the eigenvectors of
                              the previous one (Sec. 3.2.1, 4.3: between refreshes a factor changes
                              little) instead of from the identity: W = Q^T L Q is formed (float64
@@ -159,8 +160,8 @@ int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap,
                  int64_t *n_blocks, int64_t *n_buckets);
 
 /* Bytes of device workspace shampoo_create needs for cfg; 0 if cfg is invalid.  Beside the state (factors, roots,
- * A, M, the last direction) it holds scratch of the size of the largest bucket, scratch of the root refresh (at most
- * about 4 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66), and for blocks
+ * A, M, the last direction) it holds scratch of the size of the largest bucket or of several up to 2 GiB, scratch of the root refresh (at most
+ * about 6.25 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66), and for blocks
  * whose products run on the 16-bit matrix cores a second copy of the roots: 4 bytes per element, 6 for float32
  * directions, whose planes take up to 2 GiB more. */
 size_t shampoo_workspace_bytes(const shampoo_config *cfg);
