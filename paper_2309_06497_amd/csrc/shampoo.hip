@@ -1203,8 +1203,6 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
 // ---------------------------------------------------------------------------
 // The optimizer object
 // ---------------------------------------------------------------------------
-enum : char { UPPER_FRESH = 0, UPPER_TILES_STALE = 1, UPPER_HALF_STALE = 2 };   // the tiles above the diagonal of tiles; all above the diagonal
-
 struct shampoo_opt {
   shampoo_config cfg;
   std::vector<int32_t> ndim;
@@ -1231,7 +1229,9 @@ struct shampoo_opt {
   AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
   bool tables_stale = true;              // last_w and last_g have not been sent to the device
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
-  std::vector<char> upper_stale;         // per bucket: which part of the factors is out of date (UPPER_*)
+  std::vector<char> upper_stale;         // per bucket: the last factor update left out the tiles above the diagonal of tiles
+  std::vector<char> half_stale;          // per bucket: a step in one workgroup per block has left out all above the diagonal, and may do so
+                                         // again in the replay of a graph, of which the host learns nothing: never reset
   int64_t last_step = -1;
   int64_t n_refresh = 0;
   bool timing = false;
@@ -1389,6 +1389,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     o->off_small = offSmall; o->n_small = n_small; o->small_half = small_half; o->n_prep_rest = p.n_prep_rest;
     o->eig_L = eL; o->eig_R = eR; o->eig_mid[0] = eM[0]; o->eig_mid[1] = eM[1];
     o->upper_stale.assign(o->plan.buckets.size(), 0);
+    o->half_stale.assign(o->plan.buckets.size(), 0);
     o->off_nfail = offNf;
     o->off_T2 = offT2; o->off_Gb = offGb; o->off_Wb = offWb; o->has_tensor = has_tensor;
   }
@@ -1465,26 +1466,19 @@ int newton_root_guarded(shampoo_opt *o, const float *F, int dim, int count, floa
 
 // The bf16 factor update writes only the tiles on and below the diagonal of tiles, the step of a small block in one
 // workgroup only the lower triangle; whoever needs the whole symmetric factor (the refresh, the state query) completes
-// it first.
-int complete_factors(shampoo_opt *o, size_t bucket, Batch<MirrorArgs> &mirrors) {
-  if (o->upper_stale[bucket] == UPPER_FRESH) return SHAMPOO_OK;
+// it first.  half: all above the diagonal.
+int complete_factors(shampoo_opt *o, size_t bucket, bool half, Batch<MirrorArgs> &mirrors) {
+  if (!half && !o->upper_stale[bucket]) return SHAMPOO_OK;
   const Bucket &b = o->plan.buckets[bucket];
   const int dims[2] = {(int)b.m, (int)b.n};
   const size_t offs[2] = {b.off_L, b.off_R};
   for (int side = 0; side < 2; ++side) {
     const int n = dims[side], pieces = (n + 31) / 32;
-    const int all = o->upper_stale[bucket] == UPPER_HALF_STALE ? 1 : 0;
-    if (n <= (all ? 1 : BM)) continue;   // a single tile: nothing above the diagonal of tiles
-    const MirrorArgs g{reinterpret_cast<float *>(o->ws + offs[side]), n, all, pieces, b.count};
+    if (n <= (half ? 1 : BM)) continue;  // a single tile: nothing above the diagonal of tiles
+    const MirrorArgs g{reinterpret_cast<float *>(o->ws + offs[side]), n, half ? 1 : 0, pieces, b.count};
     if (const int rc = mirrors.add(g, (int64_t)pieces * pieces * b.count)) return rc;
   }
-  o->upper_stale[bucket] = UPPER_FRESH;
   return SHAMPOO_OK;
-}
-int complete_factors(shampoo_opt *o, size_t bucket, hipStream_t s) {
-  Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
-  const int rc = complete_factors(o, bucket, mirrors);
-  return rc ? rc : mirrors.flush();
 }
 
 // A factor of dimension `dim` that has so far summed (step + 1) gradients of `cols` columns
@@ -1664,7 +1658,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       else hipLaunchKernelGGL((block_step_small_kernel<GT, SB, false>), grid, block, 0, own, f);
     }
     HIP_TRY(hipGetLastError());
-    for (size_t i = 0; i < p.buckets.size(); ++i) if (p.buckets[i].small()) o->upper_stale[i] = UPPER_HALF_STALE;
+    for (size_t i = 0; i < p.buckets.size(); ++i) if (p.buckets[i].small()) o->half_stale[i] = 1;
   }
   // ---- stage by stage.  Buckets are independent of one another, so that each stage is one launch for all of them
   // (group.h); those of a set have their own parts of the scratch T, and sets follow one another.
@@ -1778,6 +1772,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     }
     // both factors of matrix blocks
     {
+      Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
       Batch<SyrkBf16Args> plain(syrk_bf16_kernel<false, false>, GEMM_THREADS, s), plain64(syrk_bf16_kernel<false, true>, GEMM_THREADS, s),
           half(syrk_bf16_kernel<true, false>, GEMM_THREADS, s), half64(syrk_bf16_kernel<true, true>, GEMM_THREADS, s),
           split(syrk_bf16_kernel<false, true, true>, GEMM_THREADS, s);
@@ -1789,9 +1784,10 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         const BlockDesc *desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc);
         const int path = factor_path(b);
         if (path == F_BF16) {
-          // the kernel reads and writes the tiles on and below the diagonal, those on it whole
-          if (o->upper_stale[index] == UPPER_HALF_STALE && (rc = complete_factors(o, index, s))) return rc;
-          o->upper_stale[index] = UPPER_TILES_STALE;
+          // the kernel reads and writes the tiles on and below the diagonal, those on it whole (refresh: this step may be the
+          // one that a graph repeats between others)
+          if (b.small() && !o->use_l2 && !sgd && (refresh || o->half_stale[index]) && (rc = complete_factors(o, index, true, mirrors))) return rc;
+          o->upper_stale[index] = 1;
           const bool x2 = sizeof(GD) == 2 && b.planes;
           SyrkBf16Args sa{};
           sa.desc = desc; sa.ptr_table = gs_tab; sa.alpha = alpha; sa.beta = beta; sa.batch = b.count;
@@ -1809,7 +1805,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           if ((rc = (x2 ? (young ? half64 : half) : (young ? plain64 : plain)).add(sa, syrk_wgs(sa)))) return rc;
         } else if (path == F_SPLIT) {
           // float32 gradients: both factors from three bf16 planes, of as many blocks at a time as T has room for
-          o->upper_stale[index] = UPPER_TILES_STALE;
+          o->upper_stale[index] = 1;
           for (int b0 = 0; b0 < b.count; b0 += b.plane_chunk) {
             const int cnt = std::min(b.plane_chunk, b.count - b0);
             const BlockPlanesArgs bp = planes_of(b, b0, cnt, true);
@@ -1832,7 +1828,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             if (b.plane_chunk < b.count && (rc = split.flush())) return rc;
           }
         } else if (!b.t3) {
-          o->upper_stale[index] = UPPER_FRESH;   // these kernels read the lower triangle and write both
+          o->upper_stale[index] = 0;   // these kernels read the lower triangle and write both
           GemmArgs g{};
           g.a.from_table = 1; g.b.from_table = 1;
           g.desc = desc; g.ptr_table = gs_tab;
@@ -1868,6 +1864,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           }
         }
       }
+      if ((rc = mirrors.flush())) return rc;
       for (Batch<SyrkBf16Args> *x : {&plain, &plain64, &half, &half64, &split}) if ((rc = x->flush())) return rc;
       if ((rc = left.flush()) || (rc = right.flush())) return rc;
     }
@@ -1894,7 +1891,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
         scale_factor(b, g, 1);
         if (mid == 0) {
-          o->upper_stale[&b - p.buckets.data()] = UPPER_FRESH;
+          o->upper_stale[&b - p.buckets.data()] = 0;
           g.a.from_table = 1; g.b.from_table = 1; g.desc = desc; g.ptr_table = gs_tab;
           g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
           g.M = b.m; g.N = b.m; g.K = b.n;
@@ -1973,7 +1970,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       return root_inverse_batched(F, dim, count, c.epsilon, r, c2, Fi, nullptr, nullptr, fail_count, ws + o->off_eig, lay, s, &o->aux, nullptr, w);
     };
     Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
-    for (size_t i = 0; i < p.buckets.size(); ++i) if ((rc = complete_factors(o, i, mirrors))) return rc;
+    for (size_t i = 0; i < p.buckets.size(); ++i) if ((rc = complete_factors(o, i, false, mirrors))) return rc;
     if ((rc = mirrors.flush())) return rc;
     for (size_t i = 0; i < p.buckets.size(); ++i) {
       auto &b = p.buckets[i];
@@ -2549,8 +2546,9 @@ int shampoo_get(shampoo_opt *o, int32_t param, int32_t block, int32_t which, voi
   switch (which) {
     case SHAMPOO_GET_L:
     case SHAMPOO_GET_R: {
-      const int rcf = complete_factors(o, (size_t)b.bucket, s);
-      if (rcf) return rcf;
+      Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
+      int rcf = complete_factors(o, (size_t)b.bucket, o->half_stale[b.bucket], mirrors);
+      if (rcf || (rcf = mirrors.flush())) return rcf;
       need = (which == SHAMPOO_GET_L ? bk.l_elems() : bk.r_elems()) * 4;
       src = ws + (which == SHAMPOO_GET_L ? bk.off_L : bk.off_R) + (size_t)b.slot * need;
       break;

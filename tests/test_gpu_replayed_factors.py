@@ -1,0 +1,57 @@
+"""Factors of small blocks, whose upper triangles are completed on request: the same after replays of a captured step, of which
+the host learns nothing, as after eager ones, in the state query and in the next refresh."""
+import pytest
+
+from paper_2309_06497_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+SHAPE, REPLAYS = (96, 128), 3
+
+
+def run(bf16, graph):
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    opt = B.Shampoo([SHAPE], 128, 0.99, 1e-6, 0.25, 100, 0, momentum=0.9, grad_dtype=B.GRAD_BF16 if bf16 else B.GRAD_F32)
+    w = [torch.zeros(SHAPE, device="cuda")]
+    g = [torch.empty(SHAPE, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32)]
+    out, t, replay = [], 1000, None
+
+    def step():
+        nonlocal t
+        g[0].copy_(torch.randn(SHAPE, device="cuda", generator=gen))
+        if replay is not None and t % 100 != 0:
+            replay.replay()
+        else:
+            opt.step(w, g, 0.01, t)
+        torch.cuda.synchronize()
+        t += 1
+
+    step()                                # a refresh
+    step()
+    if graph:
+        replay = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(replay):
+            opt.step(w, g, 0.01, t)
+    for _ in range(2):
+        for _ in range(2):                # asked for, stepped on, asked for again
+            for _ in range(REPLAYS):
+                step()
+            out += [opt.get(0, 0, which).clone() for which in (B.GET_L, B.GET_R)]
+        t = t // 100 * 100 + 100
+        step()                            # the refresh after them, eagerly
+        out += [opt.get(0, 0, which).clone() for which in (B.GET_LINV, B.GET_RINV)]
+        for _ in range(REPLAYS):
+            step()
+        out += [opt.get(0, 0, which).clone() for which in (B.GET_L, B.GET_R)]
+    return out + w
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_replays_leave_what_eager_steps_leave(bf16):
+    import torch
+    want, got = run(bf16, False), run(bf16, True)
+    assert all(torch.equal(x, x.t()) for x in want[:4])
+    for k, (x, y) in enumerate(zip(want, got)):
+        assert torch.equal(x, y), k
