@@ -43,7 +43,7 @@ enum {
   SHAMPOO_ERR_HYPER = -3,     /* hyper-parameter out of range                     */
   SHAMPOO_ERR_WORKSPACE = -4, /* workspace NULL, misaligned or too small          */
   SHAMPOO_ERR_STEP = -5,      /* step not strictly increasing                     */
-  SHAMPOO_ERR_HIP = -6,       /* a HIP runtime call failed                        */
+  SHAMPOO_ERR_HIP = -6,       /* a HIP runtime call failed, or host memory ran out */
   SHAMPOO_ERR_UNSUPPORTED = -7 /* size outside what the kernels support           */
 };
 

@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <tuple>
 #include <new>
@@ -2306,9 +2307,10 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // extern "C" boundary
 // ---------------------------------------------------------------------------
+// No entry point throws: host memory that runs out is the only exception there is, and an error like a launch that fails.
 extern "C" {
 
-int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap, int64_t *n_blocks, int64_t *n_buckets) {
+int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap, int64_t *n_blocks, int64_t *n_buckets) try {
   const int rc = check_config(cfg);
   if (rc) return rc;
   if (cap < 0 || (cap > 0 && !table)) return SHAMPOO_ERR_NULL;
@@ -2327,49 +2329,50 @@ int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap, int64_t
     row[8] = b.s3; row[9] = b.d3; row[10] = b.s4; row[11] = b.d4;
   }
   return SHAMPOO_OK;
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
-size_t shampoo_workspace_bytes(const shampoo_config *cfg) {
+size_t shampoo_workspace_bytes(const shampoo_config *cfg) try {
   if (check_config(cfg)) return 0;
   Plan p;
   make_plan(cfg, p);
   if (check_plan(p)) return 0;
   return layout(cfg, p, nullptr);
+} catch (const std::exception &) {
+  return 0;
 }
 
 int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_bytes, void *stream,
-                   shampoo_opt **out) {
+                   shampoo_opt **out) try {
   if (!out) return SHAMPOO_ERR_NULL;
   *out = nullptr;
   int rc = check_config(cfg);
   if (rc) return rc;
-  shampoo_opt *o = new (std::nothrow) shampoo_opt();
-  if (!o) return SHAMPOO_ERR_HIP;
+  std::unique_ptr<shampoo_opt> own(new shampoo_opt());
+  shampoo_opt *o = own.get();
   o->cfg = *cfg;
   o->ndim.assign(cfg->ndim, cfg->ndim + cfg->n_params);
   o->shape.assign(cfg->shape, cfg->shape + (size_t)SHAMPOO_MAX_NDIM * cfg->n_params);
   o->cfg.ndim = o->ndim.data();
   o->cfg.shape = o->shape.data();
   make_plan(&o->cfg, o->plan);
-  if ((rc = check_plan(o->plan))) { delete o; return rc; }
+  if ((rc = check_plan(o->plan))) return rc;
   const size_t need = layout(&o->cfg, o->plan, o);
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % ALIGN) != 0 || workspace_bytes < need) {
-    delete o;
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) % ALIGN) != 0 || workspace_bytes < need)
     return SHAMPOO_ERR_WORKSPACE;
-  }
   o->ws = static_cast<unsigned char *>(workspace);
   o->ws_bytes = workspace_bytes;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  auto fail = [&](int code) { delete o; return code; };
-  if (hipSetDevice(cfg->device) != hipSuccess) return fail(SHAMPOO_ERR_HIP);
+  if (hipSetDevice(cfg->device) != hipSuccess) return SHAMPOO_ERR_HIP;
   Plan &p = o->plan;
   // state: A = M = 0, L = R = 0, roots = I
-  if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_A), 0.f, p.total_elems, s))) return fail(rc);
+  if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_A), 0.f, p.total_elems, s))) return rc;
   if (cfg->momentum > 0.f)
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_M), 0.f, p.total_elems, s))) return fail(rc);
-  if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_count), 0.f, 16, s))) return fail(rc);
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_M), 0.f, p.total_elems, s))) return rc;
+  if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_count), 0.f, 16, s))) return rc;
   if (o->use_b1)
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_Gf), 0.f, p.total_elems, s))) return fail(rc);
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + o->off_Gf), 0.f, p.total_elems, s))) return rc;
   {
     // pointer tables of the library-owned gradient buffers (same layout as A / M)
     std::vector<void *> t1(cfg->n_params), t2(cfg->n_params);
@@ -2379,12 +2382,12 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
     }
     if (hipMemcpyAsync(o->ws + o->off_g1tab, t1.data(), t1.size() * sizeof(void *), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(o->ws + o->off_gftab, t2.data(), t2.size() * sizeof(void *), hipMemcpyHostToDevice, s) != hipSuccess)
-      return fail(SHAMPOO_ERR_HIP);
+      return SHAMPOO_ERR_HIP;
     if ((o->use_l2 || o->use_b1) && !p.prep_chunks.empty())
       if (hipMemcpyAsync(o->ws + o->off_prep, p.prep_chunks.data(), p.prep_chunks.size() * sizeof(DiagChunk),
                          hipMemcpyHostToDevice, s) != hipSuccess)
-        return fail(SHAMPOO_ERR_HIP);
-    if (hipStreamSynchronize(s) != hipSuccess) return fail(SHAMPOO_ERR_HIP);   // t1, t2 go out of scope
+        return SHAMPOO_ERR_HIP;
+    if (hipStreamSynchronize(s) != hipSuccess) return SHAMPOO_ERR_HIP;   // t1, t2 go out of scope
   }
   std::vector<std::vector<BlockDesc>> descs(p.buckets.size()), descs3(p.buckets.size());
   for (size_t i = 0; i < p.buckets.size(); ++i) {
@@ -2418,36 +2421,36 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
   for (size_t i = 0; i < p.buckets.size(); ++i) {
     Bucket &b = p.buckets[i];
     const int64_t B = b.count;
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_L), 0.f, B * (int64_t)b.l_elems(), s))) return fail(rc);
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_R), 0.f, B * (int64_t)b.r_elems(), s))) return fail(rc);
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_P), 0.f, B * b.m * b.n, s))) return fail(rc);
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_norms), 0.f, B * 2, s))) return fail(rc);
-    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_gmax), 0.f, B * 2, s))) return fail(rc);
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_L), 0.f, B * (int64_t)b.l_elems(), s))) return rc;
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_R), 0.f, B * (int64_t)b.r_elems(), s))) return rc;
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_P), 0.f, B * b.m * b.n, s))) return rc;
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_norms), 0.f, B * 2, s))) return rc;
+    if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_gmax), 0.f, B * 2, s))) return rc;
     if (b.t3) {
       for (int k = 0; k + 2 < b.modes; ++k) {
         const int64_t t2 = B * b.td[k + 1] * b.td[k + 1];
-        if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_mid[k]), 0.f, t2, s))) return fail(rc);
+        if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_mid[k]), 0.f, t2, s))) return rc;
         hipLaunchKernelGGL(eye_kernel, dim3((unsigned)((t2 + 255) / 256)), dim3(256), 0, s,
                            reinterpret_cast<float *>(o->ws + b.off_midinv[k]), b.td[k + 1], t2);
       }
       if (hipMemcpyAsync(o->ws + b.off_desc3, descs3[i].data(), descs3[i].size() * sizeof(BlockDesc),
                          hipMemcpyHostToDevice, s) != hipSuccess)
-        return fail(SHAMPOO_ERR_HIP);
+        return SHAMPOO_ERR_HIP;
     }
     // roots start as the identity (a diagonalised side: the vector of ones)
     const int64_t tl = B * b.m * b.m, tr = B * (int64_t)b.rdim() * b.rdim();
-    if (b.diagL) { if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_Linv), 1.f, B * b.m, s))) return fail(rc); }
+    if (b.diagL) { if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_Linv), 1.f, B * b.m, s))) return rc; }
     else hipLaunchKernelGGL(eye_kernel, dim3((unsigned)((tl + 255) / 256)), dim3(256), 0, s,
                             reinterpret_cast<float *>(o->ws + b.off_Linv), b.m, tl);
-    if (b.diagR) { if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_Rinv), 1.f, B * b.n, s))) return fail(rc); }
+    if (b.diagR) { if ((rc = launch_fill(reinterpret_cast<float *>(o->ws + b.off_Rinv), 1.f, B * b.n, s))) return rc; }
     else hipLaunchKernelGGL(eye_kernel, dim3((unsigned)((tr + 255) / 256)), dim3(256), 0, s,
                             reinterpret_cast<float *>(o->ws + b.off_Rinv), b.rdim(), tr);
-    if (hipGetLastError() != hipSuccess) return fail(SHAMPOO_ERR_HIP);
+    if (hipGetLastError() != hipSuccess) return SHAMPOO_ERR_HIP;
     if (hipMemcpyAsync(o->ws + b.off_desc, descs[i].data(), descs[i].size() * sizeof(BlockDesc),
                        hipMemcpyHostToDevice, s) != hipSuccess)
-      return fail(SHAMPOO_ERR_HIP);
+      return SHAMPOO_ERR_HIP;
   }
-  if ((rc = split_roots(o, s))) return fail(rc);
+  if ((rc = split_roots(o, s))) return rc;
   if (o->n_small > 0) {
     // largest blocks first, so that the tail of the launch is made of the cheapest workgroups
     std::vector<SmallBlock> small;
@@ -2470,19 +2473,21 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
       return (int64_t)x.m * x.n > (int64_t)y.m * y.n;
     });
     if (hipMemcpy(o->ws + o->off_small, small.data(), small.size() * sizeof(SmallBlock), hipMemcpyHostToDevice) != hipSuccess)
-      return fail(SHAMPOO_ERR_HIP);
+      return SHAMPOO_ERR_HIP;
   }
   if (!p.diag_chunks.empty())
     if (hipMemcpyAsync(o->ws + o->off_diag, p.diag_chunks.data(), p.diag_chunks.size() * sizeof(DiagChunk),
                        hipMemcpyHostToDevice, s) != hipSuccess)
-      return fail(SHAMPOO_ERR_HIP);
-  if (hipStreamSynchronize(s) != hipSuccess) return fail(SHAMPOO_ERR_HIP);
-  *out = o;
+      return SHAMPOO_ERR_HIP;
+  if (hipStreamSynchronize(s) != hipSuccess) return SHAMPOO_ERR_HIP;
+  *out = own.release();
   return SHAMPOO_OK;
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 int shampoo_step(shampoo_opt *o, void *const *params, const void *const *grads, float lr, int64_t step,
-                 void *stream) {
+                 void *stream) try {
   if (!o || !params || !grads) return SHAMPOO_ERR_NULL;
   const int np = o->cfg.n_params;
   for (int i = 0; i < np; ++i)
@@ -2516,10 +2521,12 @@ int shampoo_step(shampoo_opt *o, void *const *params, const void *const *grads, 
   // counter then stays where it was, so the error is not masked by SHAMPOO_ERR_STEP on a retry.
   if (rc == SHAMPOO_OK) o->last_step = step;
   return rc;
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 int shampoo_get(shampoo_opt *o, int32_t param, int32_t block, int32_t which, void *dst, size_t bytes,
-                void *stream) {
+                void *stream) try {
   if (!o || !dst) return SHAMPOO_ERR_NULL;
   if (param < 0 || param >= o->cfg.n_params) return SHAMPOO_ERR_SHAPE;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -2592,6 +2599,8 @@ int shampoo_get(shampoo_opt *o, int32_t param, int32_t block, int32_t which, voi
   if (bytes != need) return SHAMPOO_ERR_SHAPE;
   HIP_TRY(hipMemcpyAsync(dst, src, need, hipMemcpyDeviceToDevice, s));
   return SHAMPOO_OK;
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 int shampoo_status(shampoo_opt *o, void *stream, int64_t *n_refreshes, int64_t *n_failed_roots) {
@@ -2647,7 +2656,7 @@ size_t shampoo_root_inverse_workspace_bytes(int32_t n, int32_t batch) {
 }
 
 int shampoo_root_inverse(const float *a, int32_t n, int32_t batch, float epsilon, float r, float *x,
-                         float *lambda, int32_t *failed, void *workspace, size_t workspace_bytes, void *stream) {
+                         float *lambda, int32_t *failed, void *workspace, size_t workspace_bytes, void *stream) try {
   if (!a || !x) return SHAMPOO_ERR_NULL;
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > MAX_BLOCK_SIZE) return SHAMPOO_ERR_UNSUPPORTED;
@@ -2670,6 +2679,8 @@ int shampoo_root_inverse(const float *a, int32_t n, int32_t batch, float epsilon
   std::lock_guard<std::mutex> lock(per_device[dev].mutex);
   return root_inverse_batched(a, n, batch, epsilon, r, 1.f, x, lambda, failed, nullptr,
                               static_cast<unsigned char *>(workspace), e, s, &per_device[dev].aux);
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 size_t shampoo_root_inverse_warm_workspace_bytes(int32_t n, int32_t batch) {
@@ -2679,7 +2690,7 @@ size_t shampoo_root_inverse_warm_workspace_bytes(int32_t n, int32_t batch) {
 
 int shampoo_root_inverse_warm(const float *a, int32_t n, int32_t batch, float epsilon, float r, float *x,
                               float *lambda, int32_t *failed, float *qt, int32_t start, int32_t *sweeps,
-                              void *workspace, size_t workspace_bytes, void *stream) {
+                              void *workspace, size_t workspace_bytes, void *stream) try {
   if (!a || !x || !qt) return SHAMPOO_ERR_NULL;
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > MAX_BLOCK_SIZE || n <= JAC_SMALL_MAX) return SHAMPOO_ERR_UNSUPPORTED;
@@ -2703,10 +2714,12 @@ int shampoo_root_inverse_warm(const float *a, int32_t n, int32_t batch, float ep
   std::lock_guard<std::mutex> lock(per_device[dev].mutex);
   return root_inverse_batched(a, n, batch, epsilon, r, 1.f, x, lambda, failed, nullptr,
                               static_cast<unsigned char *>(workspace), e, s, &per_device[dev].aux, nullptr, w);
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 int shampoo_root_inverse_static(const float *a, int32_t n, int32_t batch, float epsilon, float r, float *x,
-                                float *lambda, int32_t *failed, void *stream) {
+                                float *lambda, int32_t *failed, void *stream) try {
   if (!a || !x) return SHAMPOO_ERR_NULL;
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > SHAMPOO_STATIC_MAX_N) return SHAMPOO_ERR_UNSUPPORTED;
@@ -2735,6 +2748,8 @@ int shampoo_root_inverse_static(const float *a, int32_t n, int32_t batch, float 
   }
   // everything on the caller's stream: no helper streams are created on this path
   return root_inverse_batched(a, n, batch, epsilon, r, 1.f, x, lambda, failed, nullptr, ws, e, s, nullptr);
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 size_t shampoo_root_inverse_newton_workspace_bytes(int32_t n, int32_t batch) {
@@ -2744,7 +2759,7 @@ size_t shampoo_root_inverse_newton_workspace_bytes(int32_t n, int32_t batch) {
 
 int shampoo_root_inverse_newton(const float *a, int32_t n, int32_t batch, float epsilon, int32_t p, float tolerance,
                                 int32_t max_iterations, float *x, int32_t *iterations, int32_t *failed,
-                                void *workspace, size_t workspace_bytes, void *stream) {
+                                void *workspace, size_t workspace_bytes, void *stream) try {
   if (!a || !x) return SHAMPOO_ERR_NULL;
   if (n < 1 || batch < 1) return SHAMPOO_ERR_SHAPE;
   if (n > MAX_BLOCK_SIZE || !newton_p_supported(p)) return SHAMPOO_ERR_UNSUPPORTED;
@@ -2756,6 +2771,8 @@ int shampoo_root_inverse_newton(const float *a, int32_t n, int32_t batch, float 
     return SHAMPOO_ERR_WORKSPACE;
   return newton_root_batched(a, n, batch, epsilon, p, 1.f, tolerance, max_iterations, x, iterations, failed, nullptr,
                              static_cast<unsigned char *>(workspace), e, static_cast<hipStream_t>(stream));
+} catch (const std::exception &) {
+  return SHAMPOO_ERR_HIP;
 }
 
 int shampoo_jacobi_pair(int32_t s, int32_t halves, int32_t round, int32_t k, int32_t *p, int32_t *q) {
@@ -2779,7 +2796,7 @@ const char *shampoo_strerror(int code) {
     case SHAMPOO_ERR_HYPER: return "hyper-parameter out of range";
     case SHAMPOO_ERR_WORKSPACE: return "workspace NULL, misaligned or too small";
     case SHAMPOO_ERR_STEP: return "step must be non-negative and strictly increasing";
-    case SHAMPOO_ERR_HIP: return "a HIP runtime call failed";
+    case SHAMPOO_ERR_HIP: return "a HIP runtime call failed or host memory ran out";
     case SHAMPOO_ERR_UNSUPPORTED: return "size outside the supported range";
     default: return "unknown error code";
   }
