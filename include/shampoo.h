@@ -200,7 +200,8 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
  * grads:  host array [n_params] of device pointers, float32 or bfloat16 per
  *         grad_dtype, same shapes; read only.
  * Asynchronous on `stream` (except refresh steps under SHAMPOO_ROOT_NEWTON, see
- * root_method).
+ * root_method).  Recorded into a graph (stream capture), a step keeps the pointers, lr and step number that it was
+ * given: replays work on those tensors, whatever eager steps come between them.
  * With bf16 gradients the factor update of the first steps, while a factor has summed fewer than
  * four times as many gradient columns as it has rows, adds up in float64 (the later ones in the
  * float32 accumulators of the matrix cores): a root taken from such a young factor weights its

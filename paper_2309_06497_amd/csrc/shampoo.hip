@@ -1228,7 +1228,8 @@ struct shampoo_opt {
   size_t off_nfail = 0;   // coupled Newton: per-matrix failure flags of one batch (int32)
   std::vector<void *> last_w, last_g;    // the caller's pointers of the last step (what the device tables name)
   AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
-  bool tables_stale = true;              // last_w and last_g have not been sent to the device
+  bool tables_stale = true;              // last_w and last_g may not be what the device's tables hold
+  bool tables_recorded = false;          // a graph holds a launch that writes them
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
   std::vector<char> upper_stale;         // per bucket: the last factor update left out the tiles above the diagonal of tiles
   std::vector<char> half_stale;          // per bucket: a step in one workgroup per block has left out all above the diagonal, and may do so
@@ -1492,13 +1493,24 @@ constexpr int64_t WARM_RESTART_PERIOD = 16;
 
 inline bool young_factor(int64_t step, int cols, int dim) { return (step + 1) * (int64_t)cols < 4 * (int64_t)dim; }
 
+// Whether what is enqueued on s goes into a graph.  A query that fails (another capture may forbid it) counts as one that does.
+bool recording(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // The device's tables of parameter and gradient pointers.  The pointers travel as kernel
 // arguments: nothing on the host has to outlive the call, so the stream is not waited for, and
 // a training loop whose gradients come in other buffers every step pays one or two launches of
 // a few microseconds (two copies from pageable memory behind a drained stream before: a step of
 // 512 blocks of 128 x 128 took 482 us, now 168).
+// A launch recorded into a graph writes in every replay and not now, and the host learns of no replay: a recorded step always
+// brings its pointers, and from then on every eager one does.
 int send_pointer_tables(shampoo_opt *o, hipStream_t s) {
-  if (!o->tables_stale) return SHAMPOO_OK;
+  const bool record = recording(s);
+  if (!o->tables_stale && !record) return SHAMPOO_OK;
   const int np = o->cfg.n_params;
   for (int at = 0; at < np; at += POINTER_SET) {
     PointerSet ps;
@@ -1515,7 +1527,8 @@ int send_pointer_tables(shampoo_opt *o, hipStream_t s) {
     hipLaunchKernelGGL(pointer_table_kernel, dim3(1), dim3(256), 0, s, ps);
     HIP_TRY(hipGetLastError());
   }
-  o->tables_stale = false;
+  o->tables_recorded = o->tables_recorded || record;
+  o->tables_stale = o->tables_recorded;
   return SHAMPOO_OK;
 }
 
@@ -1628,9 +1641,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   if (small_ok) for (const Bucket &b : p.buckets) if (!b.small()) staged += (int64_t)b.m * b.n * b.count;
   bool beside = staged >= OVERLAP_STAGED && !o->timing;
   if (beside && o->aux.state == 0) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;       // streams are created outside of a capture
-    HIP_TRY(hipStreamIsCapturing(s, &capture));
-    beside = capture == hipStreamCaptureStatusNone;
+    beside = !recording(s);              // streams are created outside of a capture
   }
   beside = beside && o->aux.ready();
   if (beside && (rc = aux_fork(&o->aux, 2, s))) return rc;
