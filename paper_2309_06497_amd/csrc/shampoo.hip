@@ -902,20 +902,28 @@ constexpr int BAND_STREAMS = 3;
 constexpr int64_t BAND_MANY = 32;        // matrices from which on there are three
 static_assert(BAND_STREAMS < JAC_STREAMS, "helper streams, and one more");
 
-// Forks the helper streams off s and joins them again.
-int aux_fork(AuxStreams *aux, int subs, hipStream_t s) {
-  if (subs <= 1) return SHAMPOO_OK;
-  HIP_TRY(hipEventRecord(aux->fork, s));
-  for (int k = 1; k < subs; ++k) HIP_TRY(hipStreamWaitEvent(aux->stream[k - 1], aux->fork, 0));
-  return SHAMPOO_OK;
-}
-int aux_join(AuxStreams *aux, int subs, hipStream_t s) {
-  for (int k = 1; k < subs; ++k) {
-    HIP_TRY(hipEventRecord(aux->join[k - 1], aux->stream[k - 1]));
-    HIP_TRY(hipStreamWaitEvent(s, aux->join[k - 1], 0));
+// Helper streams forked off s, and joined to it again on every way out, also where a call fails or host memory runs out: whatever a
+// call returns, s waits for all that the call has enqueued.
+struct Fork {
+  AuxStreams *aux = nullptr; int first = 0, last = 0; hipStream_t s = nullptr;      // streams first ... last - 1 are forked
+  Fork() = default;
+  Fork(const Fork &) = delete;
+  Fork &operator=(const Fork &) = delete;
+  int begin(AuxStreams *a, int from, int to, hipStream_t stream) {
+    aux = a; first = last = from; s = stream;
+    if (from >= to) return SHAMPOO_OK;
+    HIP_TRY(hipEventRecord(aux->fork, s));
+    for (; last < to; ++last) HIP_TRY(hipStreamWaitEvent(aux->stream[last], aux->fork, 0));
+    return SHAMPOO_OK;
   }
-  return SHAMPOO_OK;
-}
+  int join() {
+    int rc = SHAMPOO_OK;
+    for (; first < last; ++first)
+      if (hipEventRecord(aux->join[first], aux->stream[first]) != hipSuccess || hipStreamWaitEvent(s, aux->join[first], 0) != hipSuccess) rc = SHAMPOO_ERR_HIP;
+    return rc;
+  }
+  ~Fork() { (void)join(); }
+};
 
 // Roots of a batch of dense n x n matrices that the band reduction or the tridiagonal one serves.
 struct RootJob {
@@ -994,7 +1002,8 @@ int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *
         ++n_solve;
       }
     BandSolve *v = solve;
-    if ((rc = aux_fork(aux, n_solve, s))) return rc;
+    Fork fork;
+    if ((rc = fork.begin(aux, 0, n_solve - 1, s))) return rc;
     int panels = 0, groups = 0;
     for (int k = 0; k < n_solve; ++k) { panels = std::max(panels, v[k].panels()); groups = std::max(groups, v[k].groups()); }
     for (int k = 0; k < n_solve; ++k) if ((rc = v[k].begin())) return rc;
@@ -1004,7 +1013,7 @@ int band_roots(const std::vector<RootJob> &todo, float eps, unsigned long long *
     for (int u = 0; u < groups; ++u)
       for (int k = 0; k < n_solve; ++k) if (u < v[k].groups() && (rc = v[k].back(u))) return rc;
     for (int k = 0; k < n_solve; ++k) if ((rc = v[k].finish())) return rc;
-    if ((rc = aux_join(aux, n_solve, s))) return rc;
+    if ((rc = fork.join())) return rc;
   }
   return SHAMPOO_OK;
 }
@@ -1070,7 +1079,8 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {
     const int cb = std::min(e.chunk, batch - b0);
     const int subs = std::min(n_sub, cb);
-    if (const int rc = aux_fork(aux, subs, s)) return rc;
+    Fork fork;
+    if (const int rc = fork.begin(aux, 0, subs - 1, s)) return rc;
     BlockSolve solve[JAC_STREAMS];
     int first = 0;
     for (int k = 0; k < subs; ++k) {
@@ -1093,7 +1103,7 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
         if (const int rc = solve[k].sweep()) return rc;
     for (int k = 0; k < subs; ++k)
       if (const int rc = solve[k].finish()) return rc;
-    if (const int rc = aux_join(aux, subs, s)) return rc;
+    if (const int rc = fork.join()) return rc;
   }
   return SHAMPOO_OK;
 }
@@ -1644,7 +1654,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     beside = !recording(s);              // streams are created outside of a capture
   }
   beside = beside && o->aux.ready();
-  if (beside && (rc = aux_fork(&o->aux, 2, s))) return rc;
+  Fork helper;
+  if (beside && (rc = helper.begin(&o->aux, 0, 1, s))) return rc;
   if (small_ok) {
     StageTimer t(o, SHAMPOO_STAGE_FUSED, s);
     const hipStream_t own = beside ? o->aux.stream[0] : s;
@@ -2027,17 +2038,12 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
       if (!rat_table(r, table)) return SHAMPOO_ERR_HYPER;
       // small matrices beside the large ones, on a stream that those do not use
       AuxStreams *aux = !band.empty() && o->aux.ready() ? &o->aux : nullptr;
-      const bool beside = aux && !small.empty();
-      if (beside) {
-        HIP_TRY(hipEventRecord(aux->fork, s));
-        HIP_TRY(hipStreamWaitEvent(aux->stream[BAND_STREAMS - 1], aux->fork, 0));
-      }
-      if (!small.empty() && (rc = tridiag_roots(small, c.epsilon, fail_count, beside ? aux->stream[BAND_STREAMS - 1] : s, table))) return rc;
+      const bool apart = aux && !small.empty();
+      Fork fork;
+      if (apart && (rc = fork.begin(aux, BAND_STREAMS - 1, BAND_STREAMS, s))) return rc;
+      if (!small.empty() && (rc = tridiag_roots(small, c.epsilon, fail_count, apart ? aux->stream[BAND_STREAMS - 1] : s, table))) return rc;
       if (!band.empty() && (rc = band_roots(band, c.epsilon, fail_count, ws + o->off_eig, o->eig_bytes, s, aux, table))) return rc;
-      if (beside) {
-        HIP_TRY(hipEventRecord(aux->join[BAND_STREAMS - 1], aux->stream[BAND_STREAMS - 1]));
-        HIP_TRY(hipStreamWaitEvent(s, aux->join[BAND_STREAMS - 1], 0));
-      }
+      if ((rc = fork.join())) return rc;
       waiting.swap(rest);
     }
     o->n_refresh++;
@@ -2310,7 +2316,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     hipLaunchKernelGGL(diag_kernel<GT>, dim3((unsigned)p.diag_chunks.size()), dim3(EW_THREADS), 0, s, d);
     HIP_TRY(hipGetLastError());
   }
-  return beside ? aux_join(&o->aux, 2, s) : (int)SHAMPOO_OK;
+  return helper.join();
 }
 
 }  // namespace

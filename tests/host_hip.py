@@ -22,6 +22,7 @@ Entry entries[1 << 16];
 int64_t count = 0, fail_at = -1, calls = 0, allocations = 0, alloc_fail_at = -1, peek = 0;
 bool capturing = false, counting = false;
 int last = 0;
+char failed = ' ';       // what the failing call was
 intptr_t next_handle = 16;
 Entry *add(char what, const void *stream) {
   Entry *e = &entries[count < (1 << 16) ? count++ : (1 << 16) - 1];
@@ -29,11 +30,12 @@ Entry *add(char what, const void *stream) {
   e->what = what; e->stream = stream;
   return e;
 }
-int result() { const int rc = fail_at >= 0 && calls++ == fail_at ? 719 : 0; if (rc) last = rc; return rc; }
+int result() { const int rc = fail_at >= 0 && calls++ == fail_at ? 719 : 0; if (rc) { last = rc; failed = count ? entries[count - 1].what : '?'; } return rc; }
 }
 extern "C" {
 // the test's side
-void fake_reset(int64_t fail, int64_t alloc_fail, int cap) { count = 0; calls = 0; allocations = 0; fail_at = fail; alloc_fail_at = alloc_fail; capturing = cap != 0; last = 0; }
+void fake_reset(int64_t fail, int64_t alloc_fail, int cap) { count = 0; calls = 0; allocations = 0; fail_at = fail; alloc_fail_at = alloc_fail; capturing = cap != 0; last = 0; failed = ' '; }
+int fake_failed() { return failed; }
 void fake_count_allocations(int on) { counting = on != 0; }
 void fake_peek(int64_t word) { peek = word; }
 int64_t fake_entries(Entry **e) { *e = entries; return count; }
@@ -101,6 +103,26 @@ def entries():
 def launches(name=""):
     return [e for e in entries() if e.what == b"K" and name.encode() in e.name]
 STREAM = 7 << 20                      # the caller's
+def failing(call, limit=1 << 20):
+    # the call with its first request to the runtime failing, its second one, and so on until it succeeds: what failed, and the code
+    for k in range(limit):
+        reset(fail=k)
+        rc = call()
+        if fake.fake_calls() <= k:
+            assert rc == 0, rc
+            return
+        yield chr(fake.fake_failed()), rc
+def out_of_memory(call, limit=1 << 20):
+    # the same for allocations of host memory
+    for k in range(limit):
+        reset(alloc_fail=k)
+        fake.fake_count_allocations(1)
+        rc = call()
+        fake.fake_count_allocations(0)
+        if fake.fake_allocations() <= k:
+            assert rc == 0, rc
+            return
+        yield rc
 class Opt:
     # memory of the device is never touched: addresses that nothing lies at
     def __init__(self, shapes, block, freq=100, start=0, **kw):
@@ -114,6 +136,8 @@ class Opt:
     def step(self, t, where=1, skew=0):
         w, g = self.pointers(where), self.pointers(where + 1, skew)
         return L.shampoo_step(self.handle, w, g, 0.01, t, ctypes.c_void_p(STREAM))
+    def timing(self, on):
+        assert L.shampoo_set_timing(self.handle, int(on)) == 0
     def get(self, param, block, which, nbytes):
         return L.shampoo_get(self.handle, param, block, which, ctypes.c_void_p(1 << 39), nbytes, ctypes.c_void_p(STREAM))
 def unjoined():

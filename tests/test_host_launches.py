@@ -37,3 +37,41 @@ for t, where, capturing in ((0, 1, 0), (1, 1, 0), (2, 1, 1), (3, 3, 0), (4, 3, 0
     print(len(launches("pointer_table_kernel")))
 """)
     assert out[:5] == ["1", "0", "1", "1", "1"], out
+
+
+# Helper streams are forked off the caller's stream and joined to it.  Whatever fails in between, and wherever host memory runs out, the
+# caller's stream waits for what is under way: memory that the caller frees after the error is not in use.  (A failing record or
+# wait cannot be made up for.)
+@pytest.mark.parametrize("what,call", [
+    # small blocks beside the stages of large ones
+    ("step", "o = Opt([(2124, 2048)] + [(96, 128)] * 40, 1024); o.step(0)\ncall = lambda: o.step(1)"),
+    # band reductions on three streams, small roots on another
+    ("refresh", "o = Opt([(160, 200)] * 40 + [(96, 128)], 256, freq=1); o.step(0)\ncall = lambda: o.step(1)"),
+    # the Jacobi solver (no rational sum for this exponent)
+    ("jacobi", """
+ws = L.shampoo_root_inverse_workspace_bytes(130, 5)
+call = lambda: L.shampoo_root_inverse(ctypes.c_void_p(1 << 36), 130, 5, 1e-12, 1.0, ctypes.c_void_p(1 << 37), None, None, ctypes.c_void_p(1 << 40), ws,
+                                      ctypes.c_void_p(STREAM))
+"""),
+], ids=["step", "refresh", "jacobi"])
+def test_a_call_that_fails_leaves_nothing_beside_the_callers_stream(lib, what, call):
+    out = host_hip.run(lib, "reset()\n" + call + r"""
+reset()
+assert call() == 0 and unjoined() == []
+assert any(e.stream not in (None, STREAM) for e in launches())       # there is something to join
+bad, n, t = {"code": 0, "unjoined": 0}, 0, 1
+def again():
+    global t
+    t += 1
+    return call() if WHAT == "jacobi" else o.step(t)
+for failed, rc in failing(again):
+    n += 1
+    bad["code"] += rc != -6
+    bad["unjoined"] += failed not in "RW" and len(unjoined()) > 0
+for rc in out_of_memory(again):
+    n += 1
+    bad["code"] += rc not in (0, -6)        # 0: a sort that did without its buffer
+    bad["unjoined"] += len(unjoined()) > 0
+print(n > 20, bad)
+""".replace("WHAT", repr(what)))
+    assert out[0] == "True {'code': 0, 'unjoined': 0}", out
