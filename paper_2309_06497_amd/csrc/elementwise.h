@@ -33,7 +33,8 @@ struct EwArgs {
   const float *p;                // [slot][m][n] Shampoo directions
   float *sg_partial;             // [slot][chunks]
   float *gmax_partial;           // graft_kernel: [slot][chunks] max |G| of the chunk, direction gradients (nullptr: not wanted)
-  float *gmax;                   // [2][blocks]: largest element of state and direction gradients; zero between steps
+  float *gmax;                   // [2][blocks]: largest element of state and direction gradients; zero between steps (graft_kernel: nullptr
+                                 // where no product wants it)
   const float *scale;            // [slot]
   int32_t m, n, blocks;
   EwGeom geom;
@@ -197,9 +198,11 @@ __global__ __launch_bounds__(EW_THREADS) void graft_kernel(const Group<EwArgs> g
     gmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     smax = g.same_src ? gmax : fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
     if (g.gmax_partial) g.gmax_partial[(int64_t)slot * g.geom.chunks + chunk] = gmax;
-    // not negative, so that their bits order like integers and the result does not depend on the order
-    atomicMax(reinterpret_cast<int *>(g.gmax + slot), __float_as_int(smax));
-    atomicMax(reinterpret_cast<int *>(g.gmax + g.blocks + slot), __float_as_int(gmax));
+    if (g.gmax) {
+      // not negative, so that their bits order like integers and the result does not depend on the order
+      atomicMax(reinterpret_cast<int *>(g.gmax + slot), __float_as_int(smax));
+      atomicMax(reinterpret_cast<int *>(g.gmax + g.blocks + slot), __float_as_int(gmax));
+    }
   }
 }
 

@@ -1738,6 +1738,10 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     if (sizeof(GS) == 4 && b.split_factor && use_shampoo && o->ptrs_aligned16) return F_SPLIT;
     return F_F32;
   };
+  auto on_planes = [&](const Bucket &b) { return !b.t3 && !b.whole() && b.planes && o->ptrs_aligned16; };
+  // products that split their operands on the way into LDS: they scale by the largest element of a block, which grafting finds.  Not for
+  // others: its maxima over a block's workgroups, two atomics each on the same words, took 15 of 39 us (12 blocks of 1024)
+  auto scaled_inside = [&](const Bucket &b) { return factor_path(b) == F_F32 || (use_shampoo && !on_planes(b)); };
   auto fill_ew = [&](EwArgs &e, const Bucket &b) {
     e.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
     e.m = b.m; e.n = b.n; e.blocks = b.count; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
@@ -1764,6 +1768,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         e.sg_partial = reinterpret_cast<float *>(ws + b->off_sgp);
         e.same_src = (gs_tab == gd_tab) ? 1 : 0;
         if (b->planes) e.gmax_partial = reinterpret_cast<float *>(ws + b->off_gmaxp);
+        if (!scaled_inside(*b)) e.gmax = nullptr;
         if ((rc = graft.add(e, (int64_t)b->geom.chunks * b->count))) return rc;
       }
       if ((rc = graft.flush())) return rc;
@@ -2054,7 +2059,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     if (todo.empty()) continue;
     std::vector<int> ssh_count(todo.size());
     if (use_shampoo) {
-      auto on_planes = [&](const Bucket &b) { return !b.t3 && !b.whole() && b.planes && o->ptrs_aligned16; };
       constexpr bool THREE = sizeof(GD) == 4;
       {
         StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
