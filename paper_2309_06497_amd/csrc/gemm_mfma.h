@@ -149,7 +149,8 @@ __device__ __forceinline__ void store_u4(float *p, const float (&v)[4]) { *reint
 // and later writes it into LDS as [row][k] (K_CONTIG) or [k][row].  Whatever is read lies inside the matrix: rows past its
 // last one read that again (what they reach is never stored), values of k past the end are zero, and of four rows that
 // cross the end the last four of the matrix are read and moved into place.
-template <int ORIENT, typename T, int ROWS>
+// BITS (bf16 operands): fetched as they lie, two elements to a word, and made floats by unpack().
+template <int ORIENT, typename T, int ROWS, bool BITS = false>
 struct TileLoader {
   typedef GemmSlab<ROWS> S;
   static constexpr int PASSES = S::PASSES, QUADS = ROWS / 4;   // QUADS threads side by side along the rows, PASSES values of k each
@@ -169,6 +170,7 @@ struct TileLoader {
   }
 
   __device__ __forceinline__ void fetch(int k0, int tid) {
+    if constexpr (BITS) { fetch_bits(k0, tid); return; }
     const bool whole = k0 + BK <= K;             // uniform
     if (ORIENT == K_CONTIG) {
       constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;   // threads per row, rows per pass
@@ -207,6 +209,56 @@ struct TileLoader {
           for (int j = 0; j < 4; ++j)
             r[h][j] = (kk + h < K && r4 + j < rows_left) ? Elem<T>::load1(ptr + (int64_t)(kk + h) * ld + r4 + j) : 0.f;
       }
+    }
+  }
+
+  // Values that are converted here are waited for here, ahead of the products that are to hide the loads, which the float32 matrix
+  // cores take long over: T = Lbar G of 96 bf16 blocks of 1024 there 2356 us so, 1943 with the bits.
+  __device__ __forceinline__ void fetch_bits(int k0, int tid) {
+    typedef uint32_t pair __attribute__((ext_vector_type(2)));
+    const bool whole = k0 + BK <= K;             // uniform
+    auto put = [&](int h, uint32_t x, uint32_t y) { r[h][0] = __uint_as_float(x); r[h][1] = __uint_as_float(y); };
+    auto four = [&](int h, const T *p) { const pair x = __builtin_bit_cast(pair, *reinterpret_cast<const ushort4u *>(p)); put(h, x[0], x[1]); };
+    auto some = [&](int h, const T *p, auto exists) {
+      uint32_t x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = exists(j) ? p[j] : 0;
+      put(h, x[0] | x[1] << 16, x[2] | x[3] << 16);
+    };
+    if (ORIENT == K_CONTIG) {
+      constexpr int TPR = BK / 4, RPP = GEMM_THREADS / TPR;
+      const int row = tid / TPR, kq = k0 + (tid % TPR) * 4;
+#pragma unroll
+      for (int h = 0; h < PASSES; ++h) {
+        const T *p = ptr + (int64_t)min(row + RPP * h, rows_left - 1) * ld + kq;
+        if (whole) four(h, p); else some(h, p, [&](int j) { return kq + j < K; });
+      }
+    } else {
+      const int kk = k0 + PASSES * (tid / QUADS), r4 = (tid % QUADS) * 4;
+#pragma unroll
+      for (int h = 0; h < PASSES; ++h) {
+        const T *p = ptr + (int64_t)(kk + h) * ld;
+        if (rows_left < 4) some(h, p + r4, [&](int j) { return kk + h < K && r4 + j < rows_left; });
+        else if (whole) four(h, p + lane_row);
+        else { put(h, 0, 0); if (kk + h < K) four(h, p + lane_row); }
+      }
+    }
+  }
+  // once behind a fetch, ahead of all that works on the values
+  __device__ __forceinline__ void unpack() {
+    if constexpr (BITS) {
+#pragma unroll
+      for (int h = 0; h < PASSES; ++h) {
+        const uint32_t x = __float_as_uint(r[h][0]), y = __float_as_uint(r[h][1]);
+        r[h][0] = __uint_as_float(x << 16); r[h][1] = __uint_as_float(x & 0xffff0000u);
+        r[h][2] = __uint_as_float(y << 16); r[h][3] = __uint_as_float(y & 0xffff0000u);
+      }
+      if (ORIENT == ROW_CONTIG && rows_left >= 4 && rows_left < ROWS && (rows_left & 3)) // uniform
+#pragma unroll
+        for (int h = 0; h < PASSES; ++h) {
+          if (back & 1) { r[h][0] = r[h][1]; r[h][1] = r[h][2]; r[h][2] = r[h][3]; }
+          if (back & 2) { r[h][0] = r[h][2]; r[h][1] = r[h][3]; }
+        }
     }
   }
 
@@ -327,8 +379,8 @@ template <int AO, int BO, typename TA, typename TB, int EPI, bool KSCALE, bool A
 __global__ __launch_bounds__(GEMM_THREADS, TILE == BM ? 2 : 4) void gemm_mfma_kernel(const Group<GemmArgs> grp) {
   static_assert(!(ACC64 && FP32), "float64 sums: bf16 terms");
   typedef GemmSlab<TILE> S;
-  typedef TileLoader<AO, TA, TILE> LoadA;
-  typedef TileLoader<BO, TB, TILE> LoadB;
+  typedef TileLoader<AO, TA, TILE, FP32 && sizeof(TA) == 2> LoadA;
+  typedef TileLoader<BO, TB, TILE, FP32 && sizeof(TB) == 2> LoadB;
   constexpr int WT = TILE / 64, HALF = TILE / 2;      // a wavefront has WT x WT tiles of 32 x 32
   constexpr int SLAB_A = FP32 ? S::FLOATS : (sizeof(TA) == 2 ? 1 : 3) * S::PLANE, SLAB_B = FP32 ? S::FLOATS : (sizeof(TB) == 2 ? 1 : 3) * S::PLANE;
   constexpr int STAGES = FP32 ? 2 : 1;           // two workgroups per CU either way, four of the smaller tile
@@ -410,6 +462,8 @@ __global__ __launch_bounds__(GEMM_THREADS, TILE == BM ? 2 : 4) void gemm_mfma_ke
     lb.fetch(k0, tid);
   };
   auto store = [&](int stage, int k0) {
+    if constexpr (FP32 && sizeof(TA) == 2) la.unpack();
+    if constexpr (FP32 && sizeof(TB) == 2) lb.unpack();
     if (sg != 1.f) {                     // uniform
       if (g.scale_a) la.multiply(sg);
       if (g.scale_b) lb.multiply(sg);

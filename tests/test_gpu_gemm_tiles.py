@@ -40,3 +40,25 @@ def test_both_tiles(m, n, grad, cores):
     errors = rel(get(B.GET_L), L), rel(get(B.GET_R), R), rel(get(B.GET_PSH), P)
     print("    %d x %d %s: L %.1e R %.1e P %.1e" % (m, n, grad, *errors), flush=True)
     assert errors[0] <= 2 * 6e-8 and errors[1] <= 2 * 6e-8 and errors[2] <= 2e-6, errors
+
+
+# bf16 gradients that the float32 matrix cores read, at an even and an odd address: four columns at a time, the last four again where three
+# or fewer are left (131 and 255 columns), one by one where there are no four (2, 3); k short of a slab, and one more than a slab
+@pytest.mark.parametrize("m,n", [(129, 131), (32, 255), (33, 130), (259, 3), (40, 2), (5, 64)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_bf16_gradients_on_the_float32_matrix_cores(m, n, skew):
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m * n + skew)
+    # epsilon of the size of the factor's eigenvalues: with 1e-6 the null space of R of one 32 x 255 gradient has 31 in the root where
+    # the rest has 0.8, and what cancels there left 31 / 0.8 sqrt(255) 6e-8 = 4e-5 at worst (7e-6 measured)
+    opt = B.Shampoo([(m, n)], 512, 0.99, 1.0, 0.25, 1, 0, grad_dtype=B.GRAD_BF16, precond_matrix_cores=B.MATRIX_CORES_FP32,
+                    grafting_type=B.GRAFT_SGD)               # stage by stage at any size
+    g = torch.empty(m * n + 8, device="cuda", dtype=torch.bfloat16)[skew:skew + m * n].view(m, n)
+    g.copy_(torch.randn(m, n, device="cuda", generator=gen))
+    opt.step([torch.zeros(m, n, device="cuda")], [g], 0.01, 0)
+    get = lambda which: opt.get(0, 0, which).double()
+    P = get(B.GET_LINV) @ g.double() @ get(B.GET_RINV)
+    err = float((get(B.GET_PSH) - P).norm() / P.norm())
+    print("    %d x %d: %.1e" % (m, n, err), flush=True)
+    assert err <= 2e-6                                       # two sums of up to 259 values: 2 sqrt(259) 6e-8
