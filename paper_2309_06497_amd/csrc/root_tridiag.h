@@ -532,6 +532,10 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // the kernel took 3011 us for 3000 matrices of up to 128 x 128, so 2673.  Lane l supplies A(l % 16, l / 16 + 4 u) and B(l / 16 + 4 u, l % 16) to step u of a product
   // and gets D(l / 16 + 4 u, l % 16): a result is the B operand of the next one as it lies, F also its own A operand.
   TriBack<N> &bk = sh.back;
+  // Of the smallest variant, whose matrices may have one tile or a few reflectors, what there is none of is left out (uniform):
+  // 512 matrices of 2, 4, 8 and 16: 17.8, 21.1, 27.3 and 39.9 us with all of it, 13.2, 18.2, 24.7 and 38.1 so.
+  auto there = [n](int I) { return N > 32 || 16 * I < n; };      // row or column of tiles
+  const int reflectors = N > 32 ? N : n - 2;
   // entry (row, reflector 16 q + i - 1) of V
   auto entry = [&](int k, int at, int row) { return row == k + 1 ? 1.f : row > k + 1 && row < n ? sh.vs[at + row] : 0.f; };
   auto exists = [n](int k) { return k >= 0 && k <= n - 3; };
@@ -539,6 +543,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int q = tile[j], k = 16 * q + li - 1, at = exists(k) ? offs(k) : 0;
+    if (!there(q)) continue;
     tri_d4 s = {0.0, 0.0, 0.0, 0.0};
     for (int r0 = 16 * q; r0 < n; r0 += 16)
 #pragma unroll
@@ -557,6 +562,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     double T[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
+      if (j > reflectors) { T[j] = 0.0; bk.t[q][j * 16 + li] = 0.0; continue; }      // (those of the second tile are fewer)
       const int k = 16 * q + j - 1;
       const bool is = exists(k) && sh.beta[max(k, 0)] != 0.0;
       const double tau = is ? 2.0 * rcp_newton(S[17 * j]) : 0.0;
@@ -567,7 +573,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
       bk.t[q][j * 16 + li] = T[j];
     }
   }
-  for (int q = (n - 2) / 16; q >= 0; --q) {
+  for (int q = reflectors > 0 ? (n - 2) / 16 : -1; q >= 0; --q) {
     __syncthreads();                             // T; what the group before has read
     for (int e = tid; e < 16 * N; e += NT) {
       const int i = e / N, row = e % N, k = 16 * q + i - 1;
@@ -578,15 +584,16 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     tri_d4 z[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}}, m = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int I = 0; I < CB; ++I)
-      if (I >= q)
+      if (I >= q && there(I))
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const double x = (double)bk.v[li][16 * I + lg + 4 * u];
-          z[0] = tri_mfma(x, F[0][I][u], z[0]); z[1] = tri_mfma(x, F[1][I][u], z[1]);
+          z[0] = tri_mfma(x, F[0][I][u], z[0]);
+          if (there(tile[1])) z[1] = tri_mfma(x, F[1][I][u], z[1]);
         }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      if (tile[j] >= q) {
+      if (tile[j] >= q && there(tile[j])) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[j] + li] = z[j][u];
 #pragma unroll
@@ -619,6 +626,7 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     double v[2][4];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      if (!there(tile[j])) continue;
       y[j] = (tri_d4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int u = 0; u < 4; ++u) y[j] = tri_mfma(-t[u], z[j][u], y[j]);
@@ -633,11 +641,13 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     __syncthreads();
 #pragma unroll
     for (int I = 0; I < CB; ++I) {
+      if (!there(I)) continue;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const double yi = bk.y[lg + 4 * u][16 * I + li], vi = (double)bk.v[lg + 4 * u][16 * I + li];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
+          if (!there(tile[j])) continue;
           if (tile[j] >= q) F[j][I] = tri_mfma(yi, v[j][u], F[j][I]);
           if (I >= q) F[j][I] = tri_mfma(vi, y[j][u], F[j][I]);
         }

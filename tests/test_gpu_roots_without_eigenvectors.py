@@ -50,6 +50,12 @@ def test_small_sizes(n):
     check(n, 0.25)
 
 
+# no reflector, one, fewer than a tile of 16 holds, as many, one more
+@pytest.mark.parametrize("n", [4, 5, 8, 14, 15, 16, 18, 19])
+def test_sizes_around_one_tile(n):
+    check(n, 0.25)
+
+
 @pytest.mark.parametrize("n", [129, 160, 161, 255, 288, 544, 1056])
 def test_band_sizes(n):
     check(n, 0.25)
