@@ -1236,7 +1236,7 @@ struct shampoo_opt {
   size_t off_T2 = 0;
   bool has_tensor = false;
   size_t off_nfail = 0;   // coupled Newton: per-matrix failure flags of one batch (int32)
-  std::vector<void *> last_w, last_g;    // the caller's pointers of the last step (what the device tables name)
+  std::vector<void *> last_w, last_g;    // [n_params] the caller's pointers of the last step; null before the first
   AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
   bool tables_stale = true;              // last_w and last_g may not be what the device's tables hold
   bool tables_recorded = false;          // a graph holds a launch that writes them
@@ -1411,6 +1411,8 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
 struct StageTimer {
   shampoo_opt *o; int stage; hipStream_t s; bool on; hipEvent_t a{};
   StageTimer(shampoo_opt *o_, int st, hipStream_t s_) : o(o_), stage(st), s(s_), on(o_->timing) {
+    // room for the interval now: nothing may throw on the way out
+    if (on && o->intervals[st].size() == o->intervals[st].capacity()) o->intervals[st].reserve(std::max<size_t>(16, 2 * o->intervals[st].size()));
     if (on) { if (hipEventCreate(&a) != hipSuccess) { on = false; return; } (void)hipEventRecord(a, s); }
   }
   ~StageTimer() {
@@ -2377,6 +2379,8 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
   o->shape.assign(cfg->shape, cfg->shape + (size_t)SHAMPOO_MAX_NDIM * cfg->n_params);
   o->cfg.ndim = o->ndim.data();
   o->cfg.shape = o->shape.data();
+  o->last_w.assign(cfg->n_params, nullptr);
+  o->last_g.assign(cfg->n_params, nullptr);
   make_plan(&o->cfg, o->plan);
   if ((rc = check_plan(o->plan))) return rc;
   const size_t need = layout(&o->cfg, o->plan, o);
@@ -2519,11 +2523,9 @@ int shampoo_step(shampoo_opt *o, void *const *params, const void *const *grads, 
   HIP_TRY(hipSetDevice(o->cfg.device));
   // pointer tables: re-sent only when they have changed, by the first step that reads them
   const size_t tab_bytes = (size_t)np * sizeof(void *);
-  const bool same = (int)o->last_w.size() == np && std::memcmp(o->last_w.data(), params, tab_bytes) == 0 &&
-                    std::memcmp(o->last_g.data(), grads, tab_bytes) == 0;
+  const bool same = std::memcmp(o->last_w.data(), params, tab_bytes) == 0 && std::memcmp(o->last_g.data(), grads, tab_bytes) == 0;
   if (!same) {
-    o->last_w.assign(params, params + np);
-    o->last_g.resize(np);
+    std::memcpy(o->last_w.data(), params, tab_bytes);
     std::memcpy(o->last_g.data(), grads, tab_bytes);
     uintptr_t bits = 0;
     for (int i = 0; i < np; ++i) bits |= reinterpret_cast<uintptr_t>(grads[i]);

@@ -75,3 +75,38 @@ for rc in out_of_memory(again):
 print(n > 20, bad)
 """.replace("WHAT", repr(what)))
     assert out[0] == "True {'code': 0, 'unjoined': 0}", out
+
+
+@pytest.mark.parametrize("timing", [0, 1])
+def test_a_first_step_that_runs_out_of_host_memory_can_be_taken_again(lib, timing):
+    """Wherever the memory runs out: an error code, and the same call succeeds afterwards with what it sends to the GPU complete."""
+    out = host_hip.run(lib, r"""
+def fresh():
+    global o
+    reset()
+    o = Opt([(300, 128), (40,), (20, 30, 9)], 256)
+    o.timing(TIMING)
+def first(k):
+    reset(alloc_fail=k)
+    fake.fake_count_allocations(1)
+    rc = o.step(0)
+    fake.fake_count_allocations(0)
+    return rc, fake.fake_allocations()
+fresh()
+rc, allocations = first(-1)
+want = [(e.name, e.a) for e in launches()]
+assert rc == 0 and allocations > 5
+bad = 0
+for k in range(allocations):
+    fresh()
+    rc, _ = first(k)
+    assert rc in (0, -6)
+    if rc == 0:
+        continue
+    rc, _ = first(-1)
+    got = [(e.name, e.a) for e in launches()]
+    # the tables may have gone before the memory ran out
+    bad += rc != 0 or [x for x in got if b"pointer_table" not in x[0]] != [x for x in want if b"pointer_table" not in x[0]]
+print("ok", bad)
+""".replace("TIMING", str(timing)))
+    assert out[0] == "ok 0", out
