@@ -1480,18 +1480,18 @@ int newton_root_guarded(shampoo_opt *o, const float *F, int dim, int count, floa
 
 // The bf16 factor update writes only the tiles on and below the diagonal of tiles, the step of a small block in one
 // workgroup only the lower triangle; whoever needs the whole symmetric factor (the refresh, the state query) completes
-// it first.  half: all above the diagonal.
-int complete_factors(shampoo_opt *o, size_t bucket, bool half, Batch<MirrorArgs> &mirrors) {
+// it first.  half: all above the diagonal.  One side (0: L, 1: R) of `count` blocks of a bucket from slot `first` on.
+int complete_factor(shampoo_opt *o, size_t bucket, int side, int first, int count, bool half, Batch<MirrorArgs> &mirrors) {
   if (!half && !o->upper_stale[bucket]) return SHAMPOO_OK;
   const Bucket &b = o->plan.buckets[bucket];
-  const int dims[2] = {(int)b.m, (int)b.n};
-  const size_t offs[2] = {b.off_L, b.off_R};
-  for (int side = 0; side < 2; ++side) {
-    const int n = dims[side], pieces = (n + 31) / 32;
-    if (n <= (half ? 1 : BM)) continue;  // a single tile: nothing above the diagonal of tiles
-    const MirrorArgs g{reinterpret_cast<float *>(o->ws + offs[side]), n, half ? 1 : 0, pieces, b.count};
-    if (const int rc = mirrors.add(g, (int64_t)pieces * pieces * b.count)) return rc;
-  }
+  const int n = side == 0 ? b.m : b.n, pieces = (n + 31) / 32;
+  if (n <= (half ? 1 : BM)) return SHAMPOO_OK;        // a single tile: nothing above the diagonal of tiles
+  float *c = reinterpret_cast<float *>(o->ws + (side == 0 ? b.off_L : b.off_R)) + (int64_t)first * n * n;
+  return mirrors.add(MirrorArgs{c, n, half ? 1 : 0, pieces, count}, (int64_t)pieces * pieces * count);
+}
+int complete_factors(shampoo_opt *o, size_t bucket, bool half, Batch<MirrorArgs> &mirrors) {
+  for (int side = 0; side < 2; ++side)
+    if (const int rc = complete_factor(o, bucket, side, 0, o->plan.buckets[bucket].count, half, mirrors)) return rc;
   return SHAMPOO_OK;
 }
 
@@ -2577,7 +2577,8 @@ int shampoo_get(shampoo_opt *o, int32_t param, int32_t block, int32_t which, voi
     case SHAMPOO_GET_L:
     case SHAMPOO_GET_R: {
       Batch<MirrorArgs> mirrors(mirror_upper_tiles_kernel, 256, s);
-      int rcf = complete_factors(o, (size_t)b.bucket, o->half_stale[b.bucket], mirrors);
+      // of this block alone: a program that reads all factors asks for one after the other
+      int rcf = complete_factor(o, (size_t)b.bucket, which == SHAMPOO_GET_L ? 0 : 1, b.slot, 1, o->half_stale[b.bucket], mirrors);
       if (rcf || (rcf = mirrors.flush())) return rcf;
       need = (which == SHAMPOO_GET_L ? bk.l_elems() : bk.r_elems()) * 4;
       src = ws + (which == SHAMPOO_GET_L ? bk.off_L : bk.off_R) + (size_t)b.slot * need;

@@ -110,3 +110,22 @@ for k in range(allocations):
 print("ok", bad)
 """.replace("TIMING", str(timing)))
     assert out[0] == "ok 0", out
+
+
+def test_a_state_query_completes_the_one_factor_that_it_returns(lib):
+    """Upper triangles (small blocks) and tiles above the diagonal are written on request: of one matrix, not of its bucket."""
+    out = host_hip.run(lib, r"""
+for shapes, block, n in (([(96, 128)] * 50, 128, 128), ([(2048, 2048)] * 3, 1024, 1024)):
+    o = Opt(shapes, block, grad_dtype=B.GRAD_BF16)
+    for t in (0, 1):
+        assert o.step(t) == 0
+    for which in (B.GET_L, B.GET_R):
+        dim = 96 if n == 128 and which == B.GET_L else n
+        reset()
+        assert o.get(1, 0, which, dim * dim * 4) == 0
+        print([e.a for e in launches("mirror")], (-(-dim // 32)) ** 2)
+    reset()
+    assert o.get(1, 0, B.GET_LINV, (96 if n == 128 else n) ** 2 * 4) == 0
+    print(len(launches()))
+""")
+    assert out[:6] == ["[16] 9", "[16] 16", "0", "[1024] 1024", "[1024] 1024", "0"], out
