@@ -1241,9 +1241,9 @@ struct shampoo_opt {
   bool tables_stale = true;              // last_w and last_g may not be what the device's tables hold
   bool tables_recorded = false;          // a graph holds a launch that writes them
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
-  std::vector<char> upper_stale;         // per bucket: the last factor update left out the tiles above the diagonal of tiles
-  std::vector<char> half_stale;          // per bucket: a step in one workgroup per block has left out all above the diagonal, and may do so
-                                         // again in the replay of a graph, of which the host learns nothing: never reset
+  // per bucket: a factor update has left out the tiles above the diagonal of tiles, a step in one workgroup per block all above the
+  // diagonal.  Either may do so again in the replay of a graph, of which the host learns nothing: never reset
+  std::vector<char> upper_stale, half_stale;
   int64_t last_step = -1;
   int64_t n_refresh = 0;
   bool timing = false;
@@ -1858,8 +1858,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             if (b.plane_chunk < b.count && (rc = split.flush())) return rc;
           }
         } else if (!b.t3) {
-          o->upper_stale[index] = 0;   // these kernels read the lower triangle and write both
-          GemmArgs g{};
+          GemmArgs g{};                // these kernels read the lower triangle and write both
           g.a.from_table = 1; g.b.from_table = 1;
           g.desc = desc; g.ptr_table = gs_tab;
           g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
@@ -1921,7 +1920,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         g.alpha = (float)alpha; g.beta = (float)beta; g.alpha_d = alpha; g.beta_d = beta; g.batch = b.count;
         scale_factor(b, g, 1);
         if (mid == 0) {
-          o->upper_stale[&b - p.buckets.data()] = 0;
           g.a.from_table = 1; g.b.from_table = 1; g.desc = desc; g.ptr_table = gs_tab;
           g.c = reinterpret_cast<float *>(ws + b.off_L); g.c_batch_stride = (int64_t)b.m * b.m; g.ldc = b.m;
           g.M = b.m; g.N = b.m; g.K = b.n;

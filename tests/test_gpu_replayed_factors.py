@@ -55,3 +55,43 @@ def test_replays_leave_what_eager_steps_leave(bf16):
     assert all(torch.equal(x, x.t()) for x in want[:4])
     for k, (x, y) in enumerate(zip(want, got)):
         assert torch.equal(x, y), k
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_upper_tiles_after_a_step_that_wrote_them_itself(bf16):
+    """A recorded step whose factor update leaves out the tiles above the diagonal, an eager one from unaligned gradients, which writes
+    them, and a replay: the state query completes what the replay has left."""
+    import torch
+
+    def steps(graph):
+        shape, n = (264, 264), 264 * 264
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(13)
+        opt = B.Shampoo([shape], 264, 0.99, 1e-6, 0.25, 100, 0, grad_dtype=B.GRAD_BF16 if bf16 else B.GRAD_F32)
+        w, buf = [torch.zeros(shape, device="cuda")], torch.empty(n + 8, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32)
+        aligned, skewed = [buf[:n].view(shape)], [buf[1:n + 1].view(shape)]
+
+        def fill(g):
+            g[0].copy_(torch.randn(shape, device="cuda", generator=gen))
+        fill(aligned)
+        opt.step(w, aligned, 0.01, 1001)
+        torch.cuda.synchronize()
+        if graph:
+            replay = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(replay):
+                opt.step(w, aligned, 0.01, 1002)
+        out = []
+        for t in (1003, 1005, 1007):
+            fill(skewed)
+            opt.step(w, skewed, 0.01, t)
+            fill(aligned)
+            if graph:
+                replay.replay()
+            else:
+                opt.step(w, aligned, 0.01, t + 1)
+            torch.cuda.synchronize()
+            out += [opt.get(0, 0, which).clone() for which in (B.GET_L, B.GET_R)]
+        return out
+
+    for x, y in zip(steps(False), steps(True)):
+        assert torch.equal(x, x.t()) and torch.equal(x, y)

@@ -129,3 +129,21 @@ for shapes, block, n in (([(96, 128)] * 50, 128, 128), ([(2048, 2048)] * 3, 1024
     print(len(launches()))
 """)
     assert out[:6] == ["[16] 9", "[16] 16", "0", "[1024] 1024", "[1024] 1024", "0"], out
+
+
+def test_upper_tiles_stay_marked(lib):
+    """A replay of a step that leaves them out may come behind any other: once one has been enqueued they are always completed."""
+    out = host_hip.run(lib, r"""
+o = Opt([(264, 264)], 264, grad_dtype=B.GRAD_BF16)
+def mirrors():
+    reset()
+    assert o.get(0, 0, B.GET_L, 264 * 264 * 4) == 0
+    return len(launches("mirror"))
+assert o.step(1, skew=2) == 0
+print(mirrors())                       # unaligned gradients: that update writes all of the factor
+assert o.step(2) == 0
+print(mirrors())
+assert o.step(3, skew=2) == 0
+print(mirrors())
+""")
+    assert out[:3] == ["0", "1", "1"], out
