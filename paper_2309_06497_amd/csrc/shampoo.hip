@@ -12,6 +12,7 @@
 #include <mutex>
 #include <tuple>
 #include <new>
+#include <optional>
 #include <utility>
 #include <vector>
 
@@ -1410,6 +1411,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
 
 struct StageTimer {
   shampoo_opt *o; int stage; hipStream_t s; bool on; hipEvent_t a{};
+  StageTimer(const StageTimer &) = delete;
   StageTimer(shampoo_opt *o_, int st, hipStream_t s_) : o(o_), stage(st), s(s_), on(o_->timing) {
     // room for the interval now: nothing may throw on the way out
     if (on && o->intervals[st].size() == o->intervals[st].capacity()) o->intervals[st].reserve(std::max<size_t>(16, 2 * o->intervals[st].size()));
@@ -2060,8 +2062,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
     std::vector<int> ssh_count(todo.size());
     if (use_shampoo) {
       constexpr bool THREE = sizeof(GD) == 4;
+      std::optional<StageTimer> timer(std::in_place, o, SHAMPOO_STAGE_PRECOND, s);      // one interval, of all up to the second product
       {
-        StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
         // on a refresh the roots, and with them their scales, have just changed; filtered gradients have not been scaled yet
         Batch<X2ScaleArgs> scales(x2_scales_kernel, 64, s);
         Batch<BlockPlanesArgs> planes(block_planes_kernel, 256, s);
@@ -2150,7 +2152,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         h.tiles_m = x.tm; h.tiles_n = x.tn; h.batch = cnt;
       };
       {
-        StageTimer t(o, SHAMPOO_STAGE_PRECOND, s);
         for (size_t i = 0; i < todo.size(); ++i) {
           const Bucket &b = *todo[i];
           float *T = bucket_t(b), *P = reinterpret_cast<float *>(ws + b.off_P), *ssh = reinterpret_cast<float *>(ws + b.off_sshp);
@@ -2257,6 +2258,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
           second.add(q, &ssh_count[i]);
         }
       }
+      timer.reset();
       {
         StageTimer t(o, SHAMPOO_STAGE_PRECOND2, s);
         if ((rc = tall2.flush()) || (rc = wide2.flush()) || (rc = second.flush()) || (rc = narrow_products.flush())) return rc;

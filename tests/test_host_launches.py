@@ -147,3 +147,20 @@ assert o.step(3, skew=2) == 0
 print(mirrors())
 """)
     assert out[:3] == ["0", "1", "1"], out
+
+
+@pytest.mark.parametrize("grad", ["GRAD_F32", "GRAD_BF16"])
+def test_a_stage_of_a_step_is_one_interval(lib, grad):
+    """Time per interval is time per step for parameters that are worked on together, as the benchmark takes it to be."""
+    out = host_hip.run(lib, r"""
+o = Opt([(300, 520), (40,)], 264, grad_dtype=B.GRAD)
+o.timing(1)
+for t in range(1, 4):
+    assert o.step(t) == 0
+o.timing(0)
+for stage in (0, 1, 3, 4, 5, 7):
+    ms, n = ctypes.c_double(), i64()
+    assert L.shampoo_get_timing(o.handle, stage, ctypes.byref(ms), ctypes.byref(n)) == 0
+    print(n.value)
+""".replace("B.GRAD", "B." + grad))
+    assert out[:6] == ["3"] * 6, out
