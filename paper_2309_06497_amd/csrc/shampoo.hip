@@ -583,7 +583,7 @@ int launch_fill(float *p, float v, int64_t n, hipStream_t s) {
 
 constexpr int JAC_STREAMS = 4;   // sub-chunks of the block solver that run concurrently
 
-// Helper streams (default priority) and fork / join events of the block solver.
+// Helper streams (default priority) and fork / join events of root refreshes and of steps of small and larger blocks.
 struct AuxStreams {
   hipStream_t stream[JAC_STREAMS - 1] = {};
   hipEvent_t fork = nullptr, join[JAC_STREAMS - 1] = {};
@@ -596,7 +596,7 @@ struct AuxStreams {
         if (hipStreamCreateWithFlags(&stream[i], hipStreamNonBlocking) != hipSuccess) { stream[i] = nullptr; state = -1; }
         else if (hipEventCreateWithFlags(&join[i], hipEventDisableTiming) != hipSuccess) { join[i] = nullptr; state = -1; }
       }
-      if (state == -1) release();
+      if (state == -1) { release(); (void)hipGetLastError(); }
     }
     return state == 1;
   }
@@ -1238,7 +1238,8 @@ struct shampoo_opt {
   bool has_tensor = false;
   size_t off_nfail = 0;   // coupled Newton: per-matrix failure flags of one batch (int32)
   std::vector<void *> last_w, last_g;    // [n_params] the caller's pointers of the last step; null before the first
-  AuxStreams aux;                        // helper streams of the block solver, created at the first large refresh
+  AuxStreams aux;                        // helper streams, made by shampoo_create where steps or refreshes can use them
+  bool overlap = false;                  // the stages of the larger blocks are worth a stream of their own for the small ones
   bool tables_stale = true;              // last_w and last_g may not be what the device's tables hold
   bool tables_recorded = false;          // a graph holds a launch that writes them
   bool ptrs_aligned16 = false;           // every gradient pointer is 16-byte aligned
@@ -1651,13 +1652,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   // where the launches of the stages take as long as their kernels: not below 4e6 elements in the stages.  Step one after the other and so:
   // ResNet-50 in blocks of 256, 101 parameters, 283 and 241 us; one layer of 640 in blocks of 512 183 and 144; ResNet-50 with
   // convolution tensors, 101 and 161 parameters, 234 and 205, 695 and 682; its first 14 (0.2e6 elements) 104 and 130.
-  int64_t staged = 0;
-  if (small_ok) for (const Bucket &b : p.buckets) if (!b.small()) staged += (int64_t)b.m * b.n * b.count;
-  bool beside = staged >= OVERLAP_STAGED && !o->timing;
-  if (beside && o->aux.state == 0) {
-    beside = !recording(s);              // streams are created outside of a capture
-  }
-  beside = beside && o->aux.ready();
+  const bool beside = small_ok && o->overlap && !o->timing && o->aux.state == 1;
   Fork helper;
   if (beside && (rc = helper.begin(&o->aux, 0, 1, s))) return rc;
   if (small_ok) {
@@ -2505,6 +2500,16 @@ int shampoo_create(const shampoo_config *cfg, void *workspace, size_t workspace_
                        hipMemcpyHostToDevice, s) != hipSuccess)
       return SHAMPOO_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return SHAMPOO_ERR_HIP;
+  // Helper streams now and not by the first step that wants them: a millisecond there, and a step that is recorded first would stay
+  // without them in every replay.
+  int64_t staged = 0;
+  bool large = false;
+  for (const Bucket &b : p.buckets) {
+    if (!b.small()) staged += (int64_t)b.m * b.n * b.count;
+    large = large || (!b.diagL && b.m > JAC_SMALL_MAX) || (!b.diagR && b.rdim() > JAC_SMALL_MAX) || (b.t3 && std::max(b.td[1], b.td[2]) > JAC_SMALL_MAX);
+  }
+  o->overlap = o->n_small > 0 && staged >= OVERLAP_STAGED;
+  if (o->overlap || large) (void)o->aux.ready();
   *out = own.release();
   return SHAMPOO_OK;
 } catch (const std::exception &) {

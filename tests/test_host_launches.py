@@ -164,3 +164,23 @@ for stage in (0, 1, 3, 4, 5, 7):
     print(n.value)
 """.replace("B.GRAD", "B." + grad))
     assert out[:6] == ["3"] * 6, out
+
+
+@pytest.mark.parametrize("shapes", ["[(2124, 2048)] + [(96, 128)] * 40", "[(160, 200)] * 40 + [(96, 128)]", "[(40, 150, 9)]"])
+def test_helper_streams_are_there_before_the_first_step(lib, shapes):
+    """Neither a step nor a refresh makes streams, and one that is recorded first uses them like any other."""
+    out = host_hip.run(lib, r"""
+def run(capturing):
+    reset()
+    o = Opt(SHAPES, 1024, freq=2)
+    seen = []
+    for t in (0, 1):
+        reset(capturing=capturing)
+        assert o.step(t) == 0
+        assert not [e for e in entries() if e.what in b"SE"], t
+        seen.append(sorted((e.name, e.a, e.stream != STREAM) for e in launches() if b"pointer_table" not in e.name))
+    return seen
+a, b = run(0), run(1)
+print(a == b, any(x[2] for step in a for x in step))
+""".replace("SHAPES", shapes))
+    assert out[0] == "True True", out
