@@ -249,12 +249,13 @@ __global__ __launch_bounds__(SB_THREADS, 2) void block_step_small_kernel(const S
         load_u4<float>(ap + first + (int64_t)(RPP * u) * ld, av[u]);
       }
     }
+    wavefront_order();                           // repeated elements: read by both lanes before either stores them
 #pragma unroll
     for (int u = 0; u < GV; ++u)
       if (mine && vi + RPP * u < m) {
         float fv[4];
         const int64_t at = first + (int64_t)(RPP * u) * ld;
-        if constexpr (FILT) load_u4<float>(fp + at, fv);
+        if constexpr (FILT) { load_u4<float>(fp + at, fv); wavefront_order(); }
 #pragma unroll
         for (int e = 0; e < 4; ++e) element(gv[u][e], fv[e], av[u][e], e >= back);
         if constexpr (FILT) { if (sbk.filter) store_u4(fp + at, fv); }

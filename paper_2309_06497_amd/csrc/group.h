@@ -36,6 +36,13 @@ template <typename T> __device__ __forceinline__ T *global_ptr(const void *p) {
 }
 template <typename T, typename... Rest> __device__ __forceinline__ void to_global(T *&p, Rest *&...rest) { to_global(p); to_global(rest...); }
 
+// Between accesses to memory by lanes of one wavefront that depend on one another: the memory keeps their order by itself, the compiler must.
+// No instruction.
+__device__ __forceinline__ void wavefront_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // The entry of this workgroup, and its index among the entry's workgroups.  A copy, read once: what stays behind a
 // reference is read again wherever it is used.
 template <typename Args, int RESERVE> __device__ __forceinline__ Args group_pick(const Group<Args, RESERVE> &g, int &wg) {

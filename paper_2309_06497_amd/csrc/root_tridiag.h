@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "eigh_jacobi.h"      // SmallRootArgs, rcp_newton
+#include "group.h"
 #include "root_rational.h"
 
 namespace shampoo {
@@ -596,10 +597,12 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
       if (tile[j] >= q && there(tile[j])) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[j] + li] = z[j][u];
+        wavefront_order();                       // entries that other lanes of the wavefront have just written
 #pragma unroll
-        for (int u = 0; u < 4; ++u)              // own entries: the wavefront's LDS operations keep their order
+        for (int u = 0; u < 4; ++u)
           m = tri_mfma((double)bk.v[li][16 * tile[j] + lg + 4 * u], bk.y[li][16 * tile[j] + lg + 4 * u], m);
       }
+    wavefront_order();                           // and read
 #pragma unroll
     for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[0] + li] = m[u];
     __syncthreads();
