@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 
 from paper_2309_06497_amd import binding as B
+from paper_2309_06497_amd import workloads as wl
+from test_gpu_parity import Pair
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +88,34 @@ def test_factors_are_whole_where_the_next_step_needs_them(bf16):
     root = (Q * (lam - min(lam[0], 0.0) + f32(1e-10)) ** -0.25) @ Q.T
     got = opt.get(0, 0, B.GET_LINV).double().cpu().numpy()
     assert np.linalg.norm(got - root) <= 1e-5 * np.linalg.norm(root)      # the bar of a root
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_filtered_parameter_of_small_and_larger_blocks(bf16):
+    """200 x 200 in blocks of 150: the filter of the whole parameter is updated ahead of the stages of its larger blocks, and only read
+    by the one workgroup of its 50 x 50 block, which updates that of the parameter beside it.  Bars of test_gpu_parity.py."""
+    shapes = [(200, 200), (96, 64), (50,)]
+    p = Pair(shapes, 150, 0.99, 3, eps=1e-6, bf16=bf16, beta1=0.9, bias_correction=True)
+    for t in range(6):
+        p.step(wl.gaussian_grads(shapes, 83, t, 1e-2), 0.01, t)
+        p.check(t)
+
+
+@pytest.mark.parametrize("count", [224, 225])
+def test_as_many_parameters_as_a_launch_carries_pointers_of(count):
+    """And one more, which takes them from the tables: the same bits as in two optimizers of half as many, whose buffers take turns too."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(31)
+    shapes = [(24, 20), (7,), (5, 33)] * (count // 3) + [(40, 8)] * (count % 3)
+    draw = lambda: [torch.randn(s, device="cuda", generator=gen) for s in shapes]
+    w, g = [draw() for _ in range(2)], [draw() for _ in range(2)]
+    v = [[x.clone() for x in ws] for ws in w]
+    make = lambda s: B.Shampoo(s, 64, 0.99, 1e-6, 0.25, 100, 0, momentum=0.9)
+    half = count // 2
+    whole, parts = make(shapes), (make(shapes[:half]), make(shapes[half:]))
+    for t in range(5):                    # the first one takes the roots; the others bring their pointers along or not
+        whole.step(w[t % 2], g[t % 2], 0.01, t)
+        parts[0].step(v[t % 2][:half], g[t % 2][:half], 0.01, t)
+        parts[1].step(v[t % 2][half:], g[t % 2][half:], 0.01, t)
+    assert all(torch.equal(x, y) for a, b in zip(w, v) for x, y in zip(a, b))

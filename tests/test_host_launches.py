@@ -27,6 +27,18 @@ print(sends(600, 5), sends(700, 5))
     assert out[:5] == ["1 0 0", "1", "1", "1 1", "1 1"], out
 
 
+def test_pointers_that_fit_a_launch_travel_with_it(lib):
+    out = host_hip.run(lib, r"""
+for count in (224, 225):
+    o = Opt([(24, 20), (7,)] * (count // 2) + [(9,)] * (count % 2), 64)
+    assert o.step(1, 1) == 0
+    reset()
+    assert o.step(2, 3) == 0
+    print(len(launches("pointer_table_kernel")), len(launches()))
+""")
+    assert out[:2] == ["0 1", "1 2"], out
+
+
 def test_a_recorded_step_brings_its_pointers(lib):
     """Replays work on the tensors that the step was recorded with, whichever steps come between them."""
     out = host_hip.run(lib, r"""
