@@ -397,10 +397,8 @@ bool band_serves(int n, float r) {
 }
 
 // Workspace of the band reduction: 33 MB for a matrix of 1024, of which 20 are the eliminations of all poles.  Chunks of one size take up to
-// BAND_CHUNK_BYTES (128 of 1024), the pass over all sizes of a refresh up to BAND_PASS_BYTES, 2 % of the GPU's memory: the chains
-// of panels and pivots do not take longer for more matrices.  Refresh of two transformer layers (192 matrices of 1024) 33.0 ms
-// in passes of 4 GiB, 30.0 in one.
-constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30, BAND_PASS_BYTES = (size_t)25 << 28;
+// BAND_CHUNK_BYTES (128 of 1024), the pass over all sizes of a refresh up to band_pass_bytes().
+constexpr size_t BAND_CHUNK_BYTES = (size_t)4 << 30;
 struct BandLayout {
   int32_t np = 0, nb = 0, chunk = 0;
   size_t off_w = 0, off_vall = 0, off_vp = 0, off_z = 0, off_y = 0, off_t = 0, off_part = 0, off_tall = 0, off_dblk = 0, off_cblk = 0,
@@ -425,6 +423,11 @@ BandLayout band_layout_of(int n, int cnt) {
   e.bytes = off;
   return e;
 }
+// A panel is one workgroup per matrix, and its chain of columns does not take longer for more matrices while there is a CU for each of
+// them: a matrix of 1024 for every CU, 8 GiB, which is 3 % of the GPU's memory.  Refreshes in passes of 4, 8 and 16 GiB: 128
+// matrices of 1024 23.4, 20.7, 20.7 ms; 256 of them 43.9, 38.4, 38.5; 800 132, 122, 117; 48 of 2048 56.2, 46.2, 47.1; 96 102, 94.0, 85.6; 512 of
+// 512 18.4 in all; 250 of 1024 and 250 of 700 65.3, 60.9, 58.6.
+size_t band_pass_bytes() { return band_layout_of(1024, 256).bytes; }
 // of a chunk of the `batch`
 BandLayout band_layout(int n, int batch) {
   const BandLayout one = band_layout_of(n, 1);
@@ -1356,7 +1359,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     max_count = std::max(max_count, (size_t)b.count);
   }
   // roots of all sizes at once (band_roots)
-  eig_bytes = std::max(eig_bytes, std::min(band_all, BAND_PASS_BYTES));
+  eig_bytes = std::max(eig_bytes, std::min(band_all, band_pass_bytes()));
   // Sets of buckets whose scratch fits side by side into what the largest bucket needs, or SET_BYTES
   size_t t_bytes = 0, t2_bytes = 0;
   {

@@ -40,3 +40,24 @@ def test_roots_of_a_refresh(shapes, block):
             err = np.linalg.norm(x - want) / np.linalg.norm(want)
             print(f"    {shapes[p]} block {k} n={a.shape[0]}: {err:.1e}", flush=True)
             assert np.array_equal(x, x.T) and err <= 1e-5, (p, k, a.shape, err)      # as for one size at a time
+
+
+def test_more_matrices_than_the_scratch_has_room_for():
+    """190 matrices of 1024 and as many of 700 in one refresh, in two passes of equal size: some of the larger ones, then the rest of them
+    and all of the smaller ones.  Against the roots of the same factors, one size at a time."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    m, n, count = 1024, 700, 190
+    opt = B.Shampoo([(m, n)] * count, m, 0.99, 1e-12, 0.25, 1, 2)
+    w = [torch.zeros(m, n, device="cuda") for _ in range(count)]
+    for t in range(3):
+        opt.step(w, [torch.randn(m, n, device="cuda", generator=gen) * 1e-2 for _ in range(count)], 0.01, t)
+    assert opt.status() == {"refreshes": 1, "failed_roots": 0}
+    for factor, root in MATRIX:
+        a, x = (torch.stack([opt.get(p, 0, which) for p in range(count)]) for which in (factor, root))
+        want = B.shampoo_root_inverse(a, 1e-12, 0.25)
+        err = (x - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)
+        print(f"    n={a.shape[1]}: {float(err.max()):.1e}", flush=True)
+        assert float(err.max()) <= 2e-5      # both within the 1e-5 of test_roots_of_a_refresh
+    opt.destroy()

@@ -196,3 +196,16 @@ a, b = run(0), run(1)
 print(a == b, any(x[2] for step in a for x in step))
 """.replace("SHAPES", shapes))
     assert out[0] == "True True", out
+
+
+def test_roots_of_a_refresh_take_equal_passes(lib):
+    """One pass over up to a matrix of 1024 for every CU, then two of the same size, each on three streams."""
+    out = host_hip.run(lib, r"""
+for count in (96, 128, 129, 200):
+    o = Opt([(1024, 1024)] * count, 1024, freq=1)
+    reset()
+    assert o.step(1) == 0
+    sides = [e.a for e in launches("band_alone")]
+    print(len(sides), max(sides) - min(sides) <= 8, sum(sides) >= 2 * count)
+""")
+    assert out[:4] == ["3 True True", "3 True True", "6 True True", "6 True True"], out
