@@ -161,7 +161,8 @@ int shampoo_plan(const shampoo_config *cfg, int64_t *table, int64_t cap,
 
 /* Bytes of device workspace shampoo_create needs for cfg; 0 if cfg is invalid.  Beside the state (factors, roots,
  * A, M, the last direction) it holds scratch of the size of the largest bucket or of several up to 2 GiB, scratch of the root refresh (at most
- * about 8 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66), and for blocks
+ * about 8 GiB; half of what it would otherwise be with warm_start_roots and for exponents above 0.66; the same memory, where no
+ * planes of float32 gradients wait for the end of a refresh), and for blocks
  * whose products run on the 16-bit matrix cores a second copy of the roots: 4 bytes per element, 6 for float32
  * directions, whose planes take up to 2 GiB more. */
 size_t shampoo_workspace_bytes(const shampoo_config *cfg);

@@ -94,7 +94,7 @@ struct Bucket {
   // three: float32 directions, from three bf16 planes of every operand; split_factor: of float32 gradients that feed the
   // factors too, which then take the planes of the block both ways round.  Planes of a block live in T, of
   // plane_chunk blocks at a time: cols, the transpose, and behind it rows, the block as it lies, or T = Lbar G
-  bool three = false, split_factor = false;
+  bool three = false, split_factor = false, cols_wait = false;   // cols_wait: the factor update's cols serve the products too
   int32_t plane_chunk = 0;
   size_t off_gmax = 0;            // [2][count]: largest |element| of a block's gradients (factors, directions), zero between steps
   size_t off_t = 0, off_t2 = 0;   // this bucket's part of the scratch arrays T and T2
@@ -1376,7 +1376,14 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     }
     p.n_sets = p.buckets.empty() ? 0 : set + 1;
   }
-  const size_t offT = take(t_bytes);
+  // Planes of the transposes wait in T for the products; otherwise nothing does while the roots are taken, whose scratch
+  // is then the same memory
+  bool t_waits = false;
+  for (auto &b : p.buckets) {
+    b.cols_wait = p.n_sets == 1 && b.three && b.split_factor && b.plane_chunk == b.count;
+    t_waits = t_waits || b.cols_wait;
+  }
+  const size_t offT = take(t_waits ? t_bytes : std::max(t_bytes, eig_bytes));
   const size_t offT2 = t2_bytes ? take(t2_bytes) : 0;
   std::vector<size_t> offGb(c->n_params, 0), offWb(c->n_params, 0);
   bool has_tensor = false;
@@ -1397,7 +1404,7 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
   const size_t offSmall = take(std::max<size_t>(1, (size_t)n_small) * sizeof(SmallBlock));
   const size_t offC = take(64);
   const size_t offNf = take(max_count * 4);
-  const size_t offE = take(eig_bytes);
+  const size_t offE = t_waits ? take(eig_bytes) : offT;
   if (o) {
     o->off_A = offA; o->off_M = offM; o->off_T = offT;
     o->off_G1 = offG1; o->off_Gf = offGf; o->off_g1tab = offG1tab; o->off_gftab = offGftab; o->off_prep = offPrep;
@@ -1971,7 +1978,6 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         return rc;
     }
   }
-  const bool cols_in_t = p.n_sets == 1;     // planes of the transposes that the factor update has made are still there
   if (refresh) {
     StageTimer t(o, SHAMPOO_STAGE_ROOT, s);
     // Warm start: from the eigenvectors of the previous refresh, except at the first refresh and
@@ -2070,7 +2076,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         if ((rc = scales.flush())) return rc;
         if (THREE)
           for (Bucket *b : todo)
-            if (on_planes(*b) && b->plane_chunk == b->count && !(b->split_factor && cols_in_t) &&
+            if (on_planes(*b) && b->plane_chunk == b->count && !b->cols_wait &&
                 (rc = planes.add(planes_of(*b, 0, b->count, false), planes_wgs(*b, b->count))))
               return rc;
         if ((rc = planes.flush())) return rc;
