@@ -1749,8 +1749,9 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   };
   auto on_planes = [&](const Bucket &b) { return !b.t3 && !b.whole() && b.planes && o->ptrs_aligned16; };
   // products that split their operands on the way into LDS: they scale by the largest element of a block, which grafting finds.  Not for
-  // others: its maxima over a block's workgroups, two atomics each on the same words, took 15 of 39 us (12 blocks of 1024)
-  auto scaled_inside = [&](const Bucket &b) { return factor_path(b) == F_F32 || (use_shampoo && !on_planes(b)); };
+  // others: its maxima over a block's workgroups, two atomics each on the same words, took 15 of 39 us (12 blocks of 1024), 24 of 58
+  // (two bf16 parameters of 3000 x 3000, both factors diagonal: no product at all)
+  auto scaled_inside = [&](const Bucket &b) { return !(b.diagL && b.diagR) && (factor_path(b) == F_F32 || (use_shampoo && !on_planes(b))); };
   auto fill_ew = [&](EwArgs &e, const Bucket &b) {
     e.desc = reinterpret_cast<const BlockDesc *>(ws + b.off_desc); e.w_table = wtab; e.g_table = gs_tab; e.gd_table = gd_tab; e.a_state = A; e.m_state = M;
     e.m = b.m; e.n = b.n; e.blocks = b.count; e.geom = b.geom; e.graft_eps = c.graft_epsilon; e.mu = c.momentum; e.lr = lr;
