@@ -44,12 +44,14 @@ __device__ __forceinline__ void wavefront_order() {
 }
 
 // The entry of this workgroup, and its index among the entry's workgroups.  A copy, read once: what stays behind a
-// reference is read again wherever it is used.
+// reference is read again wherever it is used.  The first entry is requested together with the count, so that a launch for one
+// bucket starts after one round trip.
 template <typename Args, int RESERVE> __device__ __forceinline__ Args group_pick(const Group<Args, RESERVE> &g, int &wg) {
+  Args a = g.a[0];
   int k = 0;
   while (k + 1 < g.count && (int)blockIdx.x >= g.first[k + 1]) ++k;
-  wg = (int)blockIdx.x - g.first[k];
-  Args a = g.a[k];
+  if (k > 0) a = g.a[k];
+  wg = (int)blockIdx.x - (k > 0 ? g.first[k] : 0);
   a.globals();
   return a;
 }
