@@ -533,48 +533,64 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
   // the kernel took 3011 us for 3000 matrices of up to 128 x 128, so 2673.  Lane l supplies A(l % 16, l / 16 + 4 u) and B(l / 16 + 4 u, l % 16) to step u of a product
   // and gets D(l / 16 + 4 u, l % 16): a result is the B operand of the next one as it lies, F also its own A operand.
   TriBack<N> &bk = sh.back;
-  // Of the smallest variant, whose matrices may have one tile or a few reflectors, what there is none of is left out (uniform):
-  // 512 matrices of 2, 4, 8 and 16: 17.8, 21.1, 27.3 and 39.9 us with all of it, 13.2, 18.2, 24.7 and 38.1 so.
-  auto there = [n](int I) { return N > 32 || 16 * I < n; };      // row or column of tiles
-  const int reflectors = N > 32 ? N : n - 2;
   // entry (row, reflector 16 q + i - 1) of V
   auto entry = [&](int k, int at, int row) { return row == k + 1 ? 1.f : row > k + 1 && row < n ? sh.vs[at + row] : 0.f; };
   auto exists = [n](int k) { return k >= 0 && k <= n - 3; };
-  // S = V^T V, then T by columns: T_jj = 2 / S_jj, T_ij = -T_jj sum_l T_il S_lj.  A wavefront does two groups
+  // A matrix of one tile, in the smallest variant: one reflection at a time, F in 4 registers of the one wavefront and nothing in
+  // LDS but the reflectors.  F <- F - v q^T - q v^T with q = tau p - tau^2 (v.p) / 2 v, p = F v, tau = 2 / v.v.  512 matrices of 4, 8, 12 and 16: 21.1,
+  // 27.3, 33.6 and 40.0 us by groups of 16, 15.5, 23.3, 31.5 and 39.8 so.
+  const bool one_tile = N == 32 && n <= 16;
+  if (one_tile) {
+    for (int k = n - 3; k >= 0; --k) {
+      if (sh.beta[k] == 0.0) continue;
+      const int at = offs(k);
+      const double vc = (double)entry(k, at, li);
+      double vr[4], pr[4], p = 0.0;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int q = tile[j], k = 16 * q + li - 1, at = exists(k) ? offs(k) : 0;
-    if (!there(q)) continue;
-    tri_d4 s = {0.0, 0.0, 0.0, 0.0};
-    for (int r0 = 16 * q; r0 < n; r0 += 16)
+      for (int u = 0; u < 4; ++u) { vr[u] = (double)entry(k, at, lg + 4 * u); p = fma(F[0][0][u], vr[u], p); }
+      const double tau = 2.0 * rcp_newton(row16_sum(vc * vc));
+      p = rows_sum(p);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double x = exists(k) ? (double)entry(k, at, r0 + lg + 4 * u) : 0.0;
-        s = tri_mfma(x, x, s);
+      for (int u = 0; u < 4; ++u) pr[u] = __shfl(p, lg + 4 * u, 64);
+      const double K = 0.5 * tau * row16_sum(vc * p), q = tau * (p - K * vc);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) F[0][0][u] -= vr[u] * q + tau * (pr[u] - K * vr[u]) * vc;
+    }
+  } else {
+    // S = V^T V, then T by columns: T_jj = 2 / S_jj, T_ij = -T_jj sum_l T_il S_lj.  A wavefront does two groups
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int q = tile[j], k = 16 * q + li - 1, at = exists(k) ? offs(k) : 0;
+      tri_d4 s = {0.0, 0.0, 0.0, 0.0};
+      for (int r0 = 16 * q; r0 < n; r0 += 16)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double x = exists(k) ? (double)entry(k, at, r0 + lg + 4 * u) : 0.0;
+          s = tri_mfma(x, x, s);
+        }
+      double *S = &bk.y[0][0] + 256 * q;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) S[(lg + 4 * u) * 16 + li] = s[u];
+    }
+    __syncthreads();
+    if (lg < 2) {
+      const int q = lg == 0 ? tile[0] : tile[1];
+      const double *S = &bk.y[0][0] + 256 * q;
+      double T[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int k = 16 * q + j - 1;
+        const bool is = exists(k) && sh.beta[max(k, 0)] != 0.0;
+        const double tau = is ? 2.0 * rcp_newton(S[17 * j]) : 0.0;
+        double x = 0.0;
+#pragma unroll
+        for (int l = 0; l < j; ++l) x += T[l] * S[l * 16 + j];
+        T[j] = li == j ? tau : li < j ? -tau * x : 0.0;
+        bk.t[q][j * 16 + li] = T[j];
       }
-    double *S = &bk.y[0][0] + 256 * q;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) S[(lg + 4 * u) * 16 + li] = s[u];
-  }
-  __syncthreads();
-  if (lg < 2) {
-    const int q = lg == 0 ? tile[0] : tile[1];
-    const double *S = &bk.y[0][0] + 256 * q;
-    double T[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      if (j > reflectors) { T[j] = 0.0; bk.t[q][j * 16 + li] = 0.0; continue; }      // (those of the second tile are fewer)
-      const int k = 16 * q + j - 1;
-      const bool is = exists(k) && sh.beta[max(k, 0)] != 0.0;
-      const double tau = is ? 2.0 * rcp_newton(S[17 * j]) : 0.0;
-      double x = 0.0;
-#pragma unroll
-      for (int l = 0; l < j; ++l) x += T[l] * S[l * 16 + j];
-      T[j] = li == j ? tau : li < j ? -tau * x : 0.0;
-      bk.t[q][j * 16 + li] = T[j];
     }
   }
-  for (int q = reflectors > 0 ? (n - 2) / 16 : -1; q >= 0; --q) {
+  for (int q = one_tile ? -1 : (n - 2) / 16; q >= 0; --q) {
     __syncthreads();                             // T; what the group before has read
     for (int e = tid; e < 16 * N; e += NT) {
       const int i = e / N, row = e % N, k = 16 * q + i - 1;
@@ -585,16 +601,15 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     tri_d4 z[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}}, m = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int I = 0; I < CB; ++I)
-      if (I >= q && there(I))
+      if (I >= q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const double x = (double)bk.v[li][16 * I + lg + 4 * u];
-          z[0] = tri_mfma(x, F[0][I][u], z[0]);
-          if (there(tile[1])) z[1] = tri_mfma(x, F[1][I][u], z[1]);
+          z[0] = tri_mfma(x, F[0][I][u], z[0]); z[1] = tri_mfma(x, F[1][I][u], z[1]);
         }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      if (tile[j] >= q && there(tile[j])) {
+      if (tile[j] >= q) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) bk.y[lg + 4 * u][16 * tile[j] + li] = z[j][u];
         wavefront_order();                       // entries that other lanes of the wavefront have just written
@@ -629,7 +644,6 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     double v[2][4];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      if (!there(tile[j])) continue;
       y[j] = (tri_d4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int u = 0; u < 4; ++u) y[j] = tri_mfma(-t[u], z[j][u], y[j]);
@@ -644,13 +658,11 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
     __syncthreads();
 #pragma unroll
     for (int I = 0; I < CB; ++I) {
-      if (!there(I)) continue;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const double yi = bk.y[lg + 4 * u][16 * I + li], vi = (double)bk.v[lg + 4 * u][16 * I + li];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          if (!there(tile[j])) continue;
           if (tile[j] >= q) F[j][I] = tri_mfma(yi, v[j][u], F[j][I]);
           if (I >= q) F[j][I] = tri_mfma(vi, y[j][u], F[j][I]);
         }
