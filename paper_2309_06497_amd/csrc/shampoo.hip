@@ -1143,8 +1143,8 @@ NewtonLayout newton_layout(int n, int batch) {
 // p must be 1, 2, 4 or 8: T^p is formed by repeated squaring
 inline bool newton_p_supported(int p) { return p == 1 || p == 2 || p == 4 || p == 8; }
 
-// C = A B on the lower tiles, mirrored (A, B symmetric and commuting), for the matrices not yet done
-int newton_product(const float *A, const float *B, float *C, int n, int cnt, const int32_t *done, hipStream_t s) {
+// C = A B on the lower tiles, mirrored (A, B symmetric and commuting), for the matrices not yet done; launched by flush.
+void newton_product(GemmBatch<EPI_SYRK> &to, const float *A, const float *B, float *C, int n, int cnt, const int32_t *done) {
   GemmArgs g{};
   g.a.base = A; g.a.batch_stride = (int64_t)n * n; g.a.ld = n; g.a.from_table = 0;
   g.b.base = B; g.b.batch_stride = (int64_t)n * n; g.b.ld = n; g.b.from_table = 0;
@@ -1152,9 +1152,7 @@ int newton_product(const float *A, const float *B, float *C, int n, int cnt, con
   g.M = n; g.N = n; g.K = n; g.alpha = 1.f; g.beta = 0.f;
   g.skip = done;
   g.batch = cnt;
-  GemmBatch<EPI_SYRK> product(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);     // symmetric: read along k
-  product.add(g);
-  return product.flush();
+  to.add(g);
 }
 
 // X_i = (scale * A_i + eps I)^(-1/p) for a batch of dense n x n matrices.
@@ -1197,16 +1195,20 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
       hipLaunchKernelGGL(newton_finish_kernel, dim3((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb), dim3(256), 0, s, fa);
       HIP_TRY(hipGetLastError());
       if (k == max_iter) break;
-      // T^p by repeated squaring, X' = X T, M' = T^p M
+      // T^p by repeated squaring, X' = X T, M' = T^p M.  X T goes along with the first of the others: of small matrices a
+      // launch is what an iteration costs (one of 33 x 33: 2.74 ms in seven launches an iteration, 2.38 in six).
+      GemmBatch<EPI_SYRK> products(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);     // symmetric: read along k
+      newton_product(products, X, T, X2, n, cb, g.done);
       const float *Tp = T;
       float *sq[2] = {Pa, Pb};
       int w = 0;
       for (int q = 1; q < p; q *= 2) {
-        if ((rc = newton_product(Tp, Tp, sq[w], n, cb, g.done, s))) return rc;
+        newton_product(products, Tp, Tp, sq[w], n, cb, g.done);
+        if ((rc = products.flush())) return rc;
         Tp = sq[w]; w ^= 1;
       }
-      if ((rc = newton_product(X, T, X2, n, cb, g.done, s))) return rc;
-      if ((rc = newton_product(Tp, M, M2, n, cb, g.done, s))) return rc;
+      newton_product(products, Tp, M, M2, n, cb, g.done);
+      if ((rc = products.flush())) return rc;
       std::swap(M, M2); std::swap(X, X2);
     }
   }

@@ -209,3 +209,18 @@ for count in (96, 128, 129, 200):
     print(len(sides), max(sides) - min(sides) <= 8, sum(sides) >= 2 * count)
 """)
     assert out[:4] == ["3 True True", "3 True True", "6 True True", "6 True True"], out
+
+
+@pytest.mark.parametrize("p,launches", [(1, 1), (2, 2), (4, 3), (8, 4)])
+def test_products_of_a_newton_iteration(lib, p, launches):
+    """X T goes along with the first of the others, whose squares and last product need one another."""
+    out = host_hip.run(lib, r"""
+ws = L.shampoo_root_inverse_newton_workspace_bytes(40, 3)
+def call(iterations):
+    reset()
+    assert L.shampoo_root_inverse_newton(ctypes.c_void_p(1 << 36), 40, 3, ctypes.c_float(1e-6), P, ctypes.c_float(1e-6), iterations, ctypes.c_void_p(1 << 37), None,
+                                         None, ctypes.c_void_p(1 << 40), ws, ctypes.c_void_p(STREAM)) == 0
+    return len(launches("gemm_mfma_kernel"))
+print(call(1), call(7))
+""".replace("P,", "%d," % p, 1))
+    assert out[0] == "%d %d" % (launches, 7 * launches), out
