@@ -66,11 +66,12 @@ PEAK_F16_MFMA_TFLOPS = 2500.0
 TRAFFIC_BYTES = {"transformer": 14.43e9 + 4.83e9}
 # the same for the single-workgroup block-step kernel on the ResNet-50 shapes:
 # profiles/resnet50_b128_hbm_traffic_pmc.md
-FUSED_TRAFFIC_BYTES = {"resnet50": 0.849e9 + 0.631e9}
+FUSED_TRAFFIC_BYTES = {"resnet50": 0.762e9 + 0.518e9}
 # and for P = T Rbar on the fp16 matrix cores (two-plane operands) of the transformer workload:
 # profiles/transformer_b1024_hbm_traffic_pmc.md
 X2_TRAFFIC_BYTES = {"transformer": 9.66e9 + 4.83e9}
 PEAK_HBM_GBS = 8000.0
+FP32_PRODUCT = "gemm_mfma_kernel<0, 1, float, float, 1, false, false, true, 128> (P = T Rbar, fp32 MFMA)"
 TILE = 128
 
 
@@ -106,12 +107,12 @@ def flop_counts(table):
 
 def fused_bytes(table, gsz):
     """Algorithmic HBM bytes per step of the blocks that take the single-workgroup kernel
-    (m, n <= 128): G once, L and R read + written, Lbar and Rbar read, A, M, W read + written."""
+    (m, n <= 128): G once, one triangle of L and R read + written and of Lbar and Rbar read, A, M, W read + written."""
     total = 0.0
     for row in table:
         m, n = float(row[3]), float(row[4])
         if m <= 128 and n <= 128:
-            total += (gsz + 24.0) * m * n + 12.0 * (m * m + n * n)
+            total += (gsz + 24.0) * m * n + 6.0 * (m * (m + 1) + n * (n + 1))
     return total
 
 
@@ -199,7 +200,7 @@ def rootstress(args):
     ms = sum(timed) / len(timed)
     out = {"metric": "root_inverse_ms", "value": ms, "unit": "ms", "n_gpus": 1, "steps": len(timed),
            "warmup": max(args.warmup, 1), "ms_per_step": ms, "higher_is_better": False, "scaling": "weak",
-           "vs_baseline": None, "dtype": "f32 in / out, f32 + f64 sweeps", "data": "synthetic",
+           "vs_baseline": None, "dtype": "f32 in / out, f64 reduction", "data": "synthetic",
            "config": {"workload": "root-inverse stress: 256 matrices of 2048 x 2048, rank 64 + 1e-6 I, eps 1e-12, exponent 1/4"},
            "ms_per_matrix": ms / batch, "failed_roots": int(failed.sum())}
     if not args.no_cpu_baseline:
@@ -367,7 +368,7 @@ def main():
         roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS,
                     "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
                     "traffic": TRAFFIC_BYTES.get(args.workload) if default_shape else None,
-                    "kernel": "gemm_mfma_kernel<0, 1, float, float, 1, false, 0> (P = T Rbar, fp32 MFMA)",
+                    "kernel": FP32_PRODUCT,
                     "matrix_core_dtype": "f32", "first_product_launch_ms": first_ms,
                     "launch_ms": launch_ms, "flops_per_launch": gemm_flops_per_launch}
     fused_ms, fused_launches = stages["fused"]
@@ -390,12 +391,13 @@ def main():
         "higher_is_better": False,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 state and accumulation, operands of the preconditioning products as two fp16 planes" if x2 else "f32",
+        "dtype": ("f32 state and accumulation, operands of the preconditioning products as two fp16 planes" if x2 else
+                  "f32" if args.fp32_matrix_cores else "f32 state and accumulation, operands of the products as three bf16 terms"),
         "data": "synthetic",
         "config": {"workload": wk["label"], "params": n_elems, "blocks": int(len(table)),
                    "buckets": int(n_buckets), "block_size": wk["block"], "precondition_frequency": f,
                    "grad_dtype": "bf16" if wk["bf16"] else "f32", "root_method": args.root_method,
-                   "precond_matrix_cores": "f32" if (args.fp32_matrix_cores or not wk["bf16"]) else "f16x2",
+                   "precond_matrix_cores": "f32" if args.fp32_matrix_cores else "f16x2" if wk["bf16"] else "bf16x3",
                    "first_refresh_at_step": t_first},
         "refresh_ms": refresh_ms,
         "first_step_ms": first_step_ms,
@@ -405,9 +407,9 @@ def main():
         "stage_ms_per_step": st_ms,
         "roofline": roofline,
         "stage_roofline": {
-            # bf16 gradients: G G^T runs on the bf16 matrix cores (exact products, float32 / float64
-            # accumulation); the figure is algorithmic flops per second, comparable to the float32 peak
-            "factor": {"bound": "mfma", "matrix_core_dtype": "bf16" if wk["bf16"] else "f32",
+            # G G^T runs on the bf16 matrix cores (bf16 gradients: exact products, float32 / float64 accumulation; float32
+            # ones: six products of three terms); the figure is algorithmic flops per second, comparable to the float32 peak
+            "factor": {"bound": "mfma", "matrix_core_dtype": "bf16",
                        "tflops_algorithmic": alg_f / (st_ms["factor"] * 1e-3) / 1e12 if st_ms["factor"] else 0,
                        "tflops_executed": exe_f / (st_ms["factor"] * 1e-3) / 1e12 if st_ms["factor"] else 0},
             "precond": {"bound": "mfma", "tflops": alg_p / (st_ms["precond"] * 1e-3) / 1e12 if st_ms["precond"] else 0},
@@ -451,7 +453,7 @@ def secondary_fp32(B, torch, wk, shapes, params, pool, alg_p2, steps):
     return {"ms_per_step": ms, "steps": n, "roots": "identity (no refresh in this second run)",
             "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                          "frac": tf / PEAK_FP32_MFMA_TFLOPS, "launch_ms": launch_ms,
-                         "kernel": "gemm_mfma_kernel<0, 1, float, float, 1, false, 0> (P = T Rbar, fp32 MFMA)"},
+                         "kernel": FP32_PRODUCT},
             "command": "python bench.py --fp32-matrix-cores"}
 
 

@@ -124,7 +124,9 @@ typedef struct {
                              three bf16 planes each, all 24 bits of every element, six products;
                              the factor updates of float32 gradients take the same planes.  All other
                              blocks: the same three terms, split on the way into the kernels.
-                             SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA for Lbar G Rbar */
+                             SHAMPOO_MATRIX_CORES_FP32: always the float32 MFMA for Lbar G Rbar; the factor
+                             updates are as under AUTO where no planes are kept: bf16 gradients as they
+                             are, float32 ones as three bf16 terms, sums of 32 products in float64 */
   int32_t warm_start_roots; /* != 0: the eigendecomposition of a refresh starts from the eigenvectors of
                              the previous one (Sec. 3.2.1, 4.3: between refreshes a factor changes
                              little) instead of from the identity: W = Q^T L Q is formed (float64

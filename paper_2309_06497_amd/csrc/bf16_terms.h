@@ -67,7 +67,10 @@ template <int LD> __device__ __forceinline__ floatx8 lds_col8(const float *Gs, i
   return x;
 }
 // A power of two that brings a largest element outside 2^-40 ... 2^40 to 0.5 ... 1, so that neither the small terms nor their
-// products underflow; otherwise 1.
+// products underflow; otherwise 1.  For products with gradients, whose size is the caller's.  The others go without: elements below about
+// 2^-110 of theirs lose the third term, which is 2^-16 of the element.  Newton's iterates are around 1, or around the
+// root itself; F on the way back of a root is f of the spectrum; the second product of diagonal Shampoo takes D G, and where that is so
+// small, the norm of the direction, a sum of squares in float32, is zero for any root below 1e10, and with it the step.
 __device__ __forceinline__ float range_scale(float largest) {
   if (!(largest > 0.f) || !(largest < 3.4e38f) || (largest >= 0x1p-40f && largest <= 0x1p40f)) return 1.f;
   int e;

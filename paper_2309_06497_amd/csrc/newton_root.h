@@ -8,7 +8,7 @@
 // matrix on the device (`done` flags, which the GEMM launches take as their skip list), so
 // a refresh needs no host synchronisation.
 //
-// Arithmetic is float32 (MFMA with float32 accumulation).  ||M_k - I||_inf cannot fall below
+// Arithmetic is float32: operands as three bf16 terms, products summed in float32 (gemm_mfma.h).  ||M_k - I||_inf cannot fall below
 // about n * 2^-24 * (a few) in that arithmetic, so besides the paper's test the iteration of
 // a matrix also ends when the norm, once below 0.1 (quadratic regime), fails to halve.
 #pragma once

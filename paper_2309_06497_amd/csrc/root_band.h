@@ -1066,7 +1066,7 @@ __global__ __launch_bounds__(512, 2) void band_rows_kernel(const BandJobs grp) {
 }
 
 // The part of F along v1 becomes f1:  F <- F - v q^T - q v^T,  q = F v - (v.F v + f1) / 2 v.
-// First kernel: y = F v;  workgroups: np / 32 per matrix, 256 threads.  Second: the update; grid (np / 32, batch).
+// First kernel: y = F v;  workgroups: np / 32 per matrix, 256 threads.  Second: the update, by as many.
 __global__ __launch_bounds__(256) void band_fv_kernel(const BandJobs grp) {
   BAND_PICK(g.nb)
   band_select(g, b);

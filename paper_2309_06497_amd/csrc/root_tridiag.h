@@ -3,7 +3,7 @@
 //   A = Q T Q^T        Householder reduction to tridiagonal form, float64, A in registers
 //   F = f(T)           f(x) = (x - min(lambda_min, 0) + eps)^-r as a sum of inverses of shifted T
 //                      (root_rational.h): two recurrences per shift, one product chain per row
-//   X = Q F Q^T        the same reflectors in reverse order, 16 at a time, float64, F in registers
+//   X = Q F Q^T        the same reflectors in reverse order, 16 at a time (up to n = 16 one by one), float64, F in registers
 //
 // The LDS Jacobi solver (eigh_jacobi.h) does the same job in about eight sweeps of 127 rounds with
 // two barriers and a pass over the matrix each; here there are 126 reflections and 8 products of 16.  It still serves

@@ -1298,9 +1298,10 @@ size_t layout(const shampoo_config *c, Plan &p, shampoo_opt *o) {
     b.off_P = take(B * m * n * 4);
     // the preconditioning products run on the fp16 matrix cores from operands kept split in two
     // scaled fp16 planes, float32 directions on the bf16 ones from three planes.  These also have to be split in every
-    // step, and blocks of one 128-wide tile leave half of the 256-wide one idle: they keep the float32 matrix cores there.
-    // Both products of 2^25 elements in blocks of 1024, 512, 256, 192 and 144: 1.28, 0.68, 0.38, 0.51 and 0.65 ms on the float32
-    // matrix cores, 0.70, 0.43, 0.32, 0.40 and 0.66 so; just above 256 columns, 0.81 and 0.83 (264 x 264).
+    // step, and blocks of one 128-wide tile leave half of the 256-wide one idle: their terms are made on the way into LDS.
+    // Factors and both products of 2^25 float32 elements in blocks of 1024, 512, 256 and 192: 1.61, 1.01, 0.74 and 0.99 ms with the terms made
+    // there, 1.42, 0.87, 0.69 and 0.87 on planes.  Just above a multiple of the tile the planes lose by their padding (144: 1.18 and
+    // 1.38, 264: 1.16 and 1.56, 392: 1.19 and 1.44), which the line does not take into account.
     const bool dir32 = c->grad_dtype != SHAMPOO_GRAD_BF16 || use_l2 || use_b1;
     b.planes = b.bf16_mfma && c->precond_matrix_cores != SHAMPOO_MATRIX_CORES_FP32 && (!dir32 || (b.m > BM && b.n > BN));
     b.three = b.planes && dir32;
@@ -1742,7 +1743,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
   auto planes_wgs = [](const Bucket &b, int cnt) { return (int64_t)((b.n + 63) / 64) * ((b.m + 63) / 64) * cnt; };
   auto syrk_wgs = [](const SyrkBf16Args &g) { return (int64_t)g.tiles * g.batch; };
   auto tensor_chunks = [](const Bucket &b) { return (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, ((int64_t)b.m * b.n + 2047) / 2048)); };
-  // how a bucket's factors are updated: fp16 / bf16 matrix cores, three bf16 planes, float32 matrix cores
+  // how a bucket's factors are updated: fp16 / bf16 matrix cores, three bf16 planes, three bf16 terms made on the way into LDS
   enum { F_BF16, F_SPLIT, F_F32 };
   auto factor_path = [&](const Bucket &b) {
     if (sizeof(GS) == 2 && b.bf16_mfma && o->ptrs_aligned16) return F_BF16;
