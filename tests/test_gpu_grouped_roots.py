@@ -61,3 +61,25 @@ def test_more_matrices_than_the_scratch_has_room_for():
         print(f"    n={a.shape[1]}: {float(err.max()):.1e}", flush=True)
         assert float(err.max()) <= 2e-5      # both within the 1e-5 of test_roots_of_a_refresh
     opt.destroy()
+
+
+@pytest.mark.parametrize("shapes", [[(1024, 704)] * 40, [(1024, 704)] * 150 + [(1024, 1024)] * 110], ids=["planes wait", "two sets of buckets"])
+def test_directions_of_a_refresh(shapes):
+    """Float32 gradients: the planes that the factor update has made either wait beside the scratch of the roots, or are made again in the
+    memory that it has used."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(13)
+    opt = B.Shampoo(shapes, 1024, 0.99, 1e-12, 0.25, 1, 2)
+    w = [torch.zeros(s, device="cuda") for s in shapes]
+    for t in range(4):
+        g = [torch.randn(s, device="cuda", generator=gen) * 1e-2 for s in shapes]
+        opt.step(w, g, 0.01, t)
+    assert opt.status() == {"refreshes": 2, "failed_roots": 0}
+    for p in (0, len(shapes) // 2, len(shapes) - 1):
+        want = opt.get(p, 0, B.GET_LINV).double() @ g[p].double() @ opt.get(p, 0, B.GET_RINV).double()
+        err = float((opt.get(p, 0, B.GET_PSH).double() - want).norm() / want.norm())
+        print(f"    {shapes[p]}: {err:.1e}", flush=True)
+        # two sums of 32 roundings to float32 each, 6e-8 sqrt(64) at random, by the norms of |Lbar| |G| |Rbar|, which is at most some ten times that of the product here
+        assert err <= 5e-6, (p, err)
+    opt.destroy()
