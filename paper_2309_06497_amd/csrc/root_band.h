@@ -671,12 +671,18 @@ __device__ __forceinline__ int band_d_index(int r, int c) { return ((((r >> 4) *
 // by 32 pivots of the sweep operator on [M R^T; R S].  S is eliminated pivot by pivot (the stable
 // Cholesky way); formed as a product with M^-1 it would lose the condition number of M in accuracy,
 // which for a pivot block with a few large eigenvalues and many tiny ones is everything.
-// row: 64 doubles of LDS.  Returns whether all pivots were positive.
+// Bound by the latency of a pivot: its row goes through LDS (64 doubles) and its reciprocal is a chain of its own.  So a pivot
+// first updates the row of the next one, sends it and requests it; the rest of its update runs meanwhile, the next reciprocal
+// in the second half of it, and the next block's D and R are requested half way through this one.
+// 16 matrices of 2048, a launch of 256 chains of 64 blocks beside another: 615 us without that, 385 so; a lone chain of 32 blocks 278 and
+// 157 us.  Two wavefronts per SIMD instead of three (248 registers) cost less than that gains also where thousands of chains run.
+// Returns whether all pivots were positive.
 // INVERSE = false: only that answer and S.  The rows that pivots have left behind are not turned into an inverse,
-// and of the symmetric M and S only the three tiles on and above the diagonal are kept up: 32 instead of 48
-// multiply-adds per lane and pivot; bisection of 16 matrices of 2048 11.3 -> 8.8 ms of kernel time, their roots 44.2 -> 42.8.
+// and of the symmetric M and S only the three tiles on and above the diagonal are kept up: 27 instead of 48
+// multiply-adds per lane and pivot.
 struct BandElim {
-  double M[2][2][4], K[2][2][4], S[2][2][4];
+  double M[2][2][4], K[2][2][4], S[2][2][4], nk[2][2][4], ns[2][2][4];   // nk, ns: R^T and D_i+1 of the block to come
+  struct Row { double p, c[2], k[2], f[2][4], h[2][4]; };                // a pivot, and its row of [M K] by columns and by rows
   static __device__ __forceinline__ void load(double (&x)[2][2][4], const double *d, int li, int lg) {
     const double *p = d + lg * BAND + li;
 #pragma unroll
@@ -686,65 +692,118 @@ struct BandElim {
 #pragma unroll
         for (int v = 0; v < 4; ++v) x[ti][tj][v] = p[(16 * ti + 4 * v) * BAND + 16 * tj];
   }
-  __device__ __forceinline__ void begin(const double *d, int li, int lg) { load(S, d, li, lg); }
-  // d, rt: D_i+1 and R^T, row-major; last: there is no next block
-  template <bool INVERSE = true>
-  __device__ __forceinline__ bool step(const double *d, const double *rt, bool last, double sigma, double tiny, double *row, int li, int lg) {
+  // d, rt: D and R^T of all nb blocks, row-major
+  __device__ __forceinline__ void begin(const double *d, const double *rt, int nb, int li, int lg) {
+    load(ns, d, li, lg);
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
       for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) M[ti][tj][v] = S[ti][tj][v] + (ti == tj && lg + 4 * v == li ? sigma : 0.0);
-    if (!last) { load(K, rt, li, lg); load(S, d, li, lg); }
-    bool ok = true;
+        for (int v = 0; v < 4; ++v) { S[ti][tj][v] = ns[ti][tj][v]; nk[ti][tj][v] = 0.0; }
+    request(d, rt, 0, nb, li, lg);
+  }
+  __device__ __forceinline__ void request(const double *d, const double *rt, int i, int nb, int li, int lg) {
+    if (i + 1 < nb) { load(nk, rt + (int64_t)i * 1024, li, lg); load(ns, d + (int64_t)(i + 1) * 1024, li, lg); }
+  }
+  // Row PV through LDS.  What a pivot does not need any more is not sent: its wavefront's accesses to LDS keep their order.
+  template <bool INVERSE, int PV> __device__ __forceinline__ void fetch(double *row, Row &r, int li, int lg) {
+    constexpr int ti = PV / 16, v = PV % 16 / 4, t0 = INVERSE ? 0 : ti;
+    wavefront_order();
+    if (lg == PV % 4) {
+      if (t0 == 0) row[li] = M[ti][0][v];
+      row[16 + li] = M[ti][1][v];
+      row[32 + li] = K[ti][0][v]; row[48 + li] = K[ti][1][v];
+    }
+    wavefront_order();
+    r.p = row[PV];
+    r.c[0] = t0 == 0 ? row[li] : 0.0; r.c[1] = row[16 + li];
+    r.k[0] = row[32 + li]; r.k[1] = row[48 + li];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (t >= t0) r.f[t][u] = row[16 * t + lg + 4 * u];
+        r.h[t][u] = row[32 + 16 * t + lg + 4 * u];
+      }
+  }
+  // Formed here: moved to where it is used next, an update would keep its operands alive until then.
+  static __device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+  // 1 / pivot, with a floor under it
+  static __device__ __forceinline__ double inverse(double p, double tiny, bool &ok) {
+    if (!(p > 0.0)) ok = false;
+    if (!(p > tiny)) p = tiny;
+    return rcp_newton(p);
+  }
+  template <bool INVERSE = true>
+  __device__ __forceinline__ bool step(const double *d, const double *rt, int i, int nb, double sigma, double tiny, double *row, int li, int lg) {
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-#pragma unroll 1
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const int p = 16 * ti + 4 * v + r4;
-          const int t0 = INVERSE ? 0 : ti;   // tiles of rows in front of it are done with
-          if (lg == r4) {
-            if (t0 == 0) row[li] = M[ti][0][v];
-            row[16 + li] = M[ti][1][v];
-            row[32 + li] = K[ti][0][v]; row[48 + li] = K[ti][1][v];
-          }
-          __syncthreads();
-          double pv = row[p];
-          if (!(pv > 0.0)) ok = false;
-          if (!(pv > tiny)) pv = tiny;
-          const double inv = rcp_newton(pv);
-          const double c0 = t0 == 0 ? row[li] : 0.0, c1 = row[16 + li], k0 = row[32 + li], k1 = row[48 + li];
-          double f[2][4], h[2][4];
+      for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
-          for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { f[t][u] = t >= t0 ? row[16 * t + lg + 4 * u] * inv : 0.0; h[t][u] = row[32 + 16 * t + lg + 4 * u] * inv; }
-          __syncthreads();
-          const bool mine = li == 4 * v + r4;
-#pragma unroll
-          for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              if (t >= t0) {
-                if (INVERSE || t == 0) M[t][0][u] -= f[t][u] * c0;
-                M[t][1][u] -= f[t][u] * c1;
-                if (INVERSE && mine) M[t][ti][u] = f[t][u];
-                K[t][0][u] -= f[t][u] * k0;
-                K[t][1][u] -= f[t][u] * k1;
-              }
-              if (INVERSE || t == 0) S[t][0][u] -= h[t][u] * k0;
-              S[t][1][u] -= h[t][u] * k1;
-            }
-          if (INVERSE && lg == r4) {
-            M[ti][0][v] = c0 * inv; M[ti][1][v] = c1 * inv;
-            if (mine) M[ti][ti][v] = -inv;
-            K[ti][0][v] = k0 * inv; K[ti][1][v] = k1 * inv;
-          }
+        for (int v = 0; v < 4; ++v) {
+          M[ti][tj][v] = S[ti][tj][v] + (ti == tj && lg + 4 * v == li ? sigma : 0.0);
+          K[ti][tj][v] = nk[ti][tj][v];
+          S[ti][tj][v] = ns[ti][tj][v];
         }
+    bool ok = true;
+    Row cur;
+    fetch<INVERSE, 0>(row, cur, li, lg);
+    double inv = inverse(cur.p, tiny, ok);
+    for_each_block<32>([&](auto pc) {
+      constexpr int PV = decltype(pc)::value, ti = PV / 16, v = PV % 16 / 4, t0 = INVERSE ? 0 : ti;
+      constexpr int NT = (PV + 1) / 16, NV = (PV + 1) % 16 / 4;            // where the next pivot's row is
+      const double c0 = t0 == 0 ? cur.c[0] * inv : 0.0, c1 = cur.c[1] * inv, k0 = cur.k[0] * inv, k1 = cur.k[1] * inv;
+      const bool mine = li == PV % 16;
+      // of the pivot's own column remains its row times 1 / pivot
+      const double m0 = INVERSE && ti == 0 && mine ? -inv : c0, m1 = INVERSE && ti == 1 && mine ? -inv : c1;
+      auto update_mk = [&](int t, int u) {
+        if (t < t0 || (!INVERSE && t == ti && u < v)) return;              // rows in front of the pivot are done with
+        if (INVERSE) M[t][ti][u] = mine ? 0.0 : M[t][ti][u];
+        if (INVERSE || t == 0) M[t][0][u] -= cur.f[t][u] * m0;
+        M[t][1][u] -= cur.f[t][u] * m1;
+        K[t][0][u] -= cur.f[t][u] * k0;
+        K[t][1][u] -= cur.f[t][u] * k1;
+        if (INVERSE || t == 0) pin(M[t][0][u]);
+        pin(M[t][1][u]); pin(K[t][0][u]); pin(K[t][1][u]);
+      };
+      auto update_s = [&](int t, int u) {
+        if (INVERSE || t == 0) S[t][0][u] -= cur.h[t][u] * k0;
+        S[t][1][u] -= cur.h[t][u] * k1;
+        if (INVERSE || t == 0) pin(S[t][0][u]);
+        pin(S[t][1][u]);
+      };
+      // the pivot's own row; one that shares its registers with the next pivot's has to be settled first
+      auto own = [&]() {
+        if (!INVERSE) return;
+        const bool row = lg == PV % 4;
+        M[ti][0][v] = row ? (ti == 0 && mine ? -inv : c0) : M[ti][0][v];
+        M[ti][1][v] = row ? (ti == 1 && mine ? -inv : c1) : M[ti][1][v];
+        K[ti][0][v] = row ? k0 : K[ti][0][v];
+        K[ti][1][v] = row ? k1 : K[ti][1][v];
+      };
+      Row next = cur;
+      if constexpr (PV < 31) {
+        update_mk(NT, NV);
+        if (NT == ti && NV == v) own();
+        fetch<INVERSE, PV + 1>(row, next, li, lg);
+        __builtin_amdgcn_sched_barrier(0);
       }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) if (!(PV < 31 && t == NT && u == NV)) update_mk(t, u);
+      if (!(PV < 31 && NT == ti && NV == v)) own();
+      if constexpr (PV < 31) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) update_s(t, u);
+      if constexpr (PV < 31) inv = inverse(next.p, tiny, ok);
+      if constexpr (PV == 15) request(d, rt, i + 1, nb, li, lg);
+      cur = next;
+    });
     return ok;
   }
 };
@@ -805,9 +864,8 @@ __global__ __launch_bounds__(64) void band_probe_kernel(const BandJobs grp) {
   }
   BandElim e;
   bool ok = true;
-  e.begin(g.dblk, li, lg);
-  for (int i = 0; i < g.nb && ok; ++i)
-    ok = e.step<false>(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == g.nb, -sigma, 1.0e-290, row, li, lg);
+  e.begin(g.dblk, g.cblk, g.nb, li, lg);
+  for (int i = 0; i < g.nb && ok; ++i) ok = e.step<false>(g.dblk, g.cblk, i, g.nb, -sigma, 1.0e-290, row, li, lg);
   if (lane == 0) g.ok[(round & 1) * BAND_SHIFTS + s] = ok ? 1 : 0;
 }
 
@@ -863,9 +921,9 @@ __global__ __launch_bounds__(64) void band_factor_kernel(const BandTableJobs grp
   const double wj = vector ? 0.0 : table.w[rat_offset(m.cls) + pole] * pow(m.low, 1.0 - (double)g.r);
   double *kf = g.kf + (int64_t)pole * nb * 1024, *gf = g.gf + (int64_t)pole * nb * 1024;
   BandElim e;
-  e.begin(g.dblk, li, lg);
+  e.begin(g.dblk, g.cblk, nb, li, lg);
   for (int i = 0; i < nb; ++i) {
-    e.step(g.dblk + (int64_t)(i + 1) * 1024, g.cblk + (int64_t)i * 1024, i + 1 == nb, sigma, 0x1p-60 * m.amax, row, li, lg);
+    e.step(g.dblk, g.cblk, i, nb, sigma, 0x1p-60 * m.amax, row, li, lg);
     double *go = gf + (int64_t)i * 1024;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
