@@ -947,59 +947,79 @@ __global__ __launch_bounds__(64) void band_factor_kernel(const BandTableJobs grp
     const int a = lane & 31, k0 = 16 * (lane >> 5);
     for (int i = lane; i < g.np; i += 64) z[i] = 1.0 + 0.25 * (double)(((unsigned)i * 2654435761u) >> 24) * 0x1p-8;
     __syncthreads();
-    for (int it = 0; it < 5; ++it) {
-      for (int i = 0; i + 1 < nb; ++i) {
-        const double *ko = kf + (int64_t)i * 1024;
-        double s = 0.0;
+    // Chains of 2 nb steps: the next step's entries of K and of the inverse pivots are requested before this one's are used.
+    auto k_to = [&](double (&x)[16], int i) {                    // K_i, for z_i
+      const double *ko = kf + (int64_t)min(i, max(nb - 2, 0)) * 1024;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s += ko[band_a_index(k0 + q, a)] * z[BAND * i + k0 + q];
+      for (int q = 0; q < 16; ++q) x[q] = ko[band_a_index(k0 + q, a)];
+    };
+    auto back_to = [&](double (&x)[16], double (&y)[16], int i) {  // pivot_i^-1, for z_i, and K_i^T, for z_i+1
+      const double *go = gf + (int64_t)max(i, 0) * 1024, *ko = kf + (int64_t)max(min(i, nb - 2), 0) * 1024;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) { x[q] = go[band_d_index(a, k0 + q)]; y[q] = ko[band_a_index(a, k0 + q)]; }
+    };
+    for (int it = 0; it < 5; ++it) {
+      double kx[16], gx[16];
+      k_to(kx, 0);
+      for (int i = 0; i + 1 < nb; ++i) {
+        double next[16], s = 0.0;
+        k_to(next, i + 1);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s += kx[q] * z[BAND * i + k0 + q];
         s += __shfl_xor(s, 32, 64);
         if (lane < 32) z[BAND * (i + 1) + a] += s;
-        __syncthreads();
+        wavefront_order();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) kx[q] = next[q];
       }
       double nrm = 0.0;
+      back_to(gx, kx, nb - 1);
       for (int i = nb - 1; i >= 0; --i) {
-        const double *go = gf + (int64_t)i * 1024, *ko = kf + (int64_t)i * 1024;
-        double s = 0.0;
+        double gn[16], kn[16], s = 0.0;
+        back_to(gn, kn, i - 1);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s += go[band_d_index(a, k0 + q)] * z[BAND * i + k0 + q];
+        for (int q = 0; q < 16; ++q) s += gx[q] * z[BAND * i + k0 + q];
         if (i + 1 < nb) {
 #pragma unroll
-          for (int q = 0; q < 16; ++q) s += ko[band_a_index(a, k0 + q)] * z[BAND * (i + 1) + k0 + q];
+          for (int q = 0; q < 16; ++q) s += kx[q] * z[BAND * (i + 1) + k0 + q];
         }
         s += __shfl_xor(s, 32, 64);
-        __syncthreads();
+        wavefront_order();
         if (lane < 32) z[BAND * i + a] = s;
-        __syncthreads();
+        wavefront_order();
         nrm += lane < 32 ? s * s : 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) { gx[q] = gn[q]; kx[q] = kn[q]; }
       }
       nrm = rsqrt_newton(wave64_sum(nrm));
       for (int i = lane; i < g.np; i += 64) z[i] *= nrm;
-      __syncthreads();
+      wavefront_order();
     }
     for (int i = lane; i < g.np; i += 64) g.v1[i] = z[i];
     return;
   }
-  // G_i = pivot_i^-1 + K_i^T G_i+1 K_i
-  double G[2][2][4];
-  for (int i = nb - 1; i >= 0; --i) {
-    double *go = gf + (int64_t)i * 1024;
-    double P[2][2][4];
+  // G_i = pivot_i^-1 + K_i^T G_i+1 K_i; the next block's operands are requested before the products of this one
+  double G[2][2][4], P[2][2][4], kn[2][2][4];
+  auto get = [&](double (&x)[2][2][4], const double *from) {
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
       for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) P[ti][tj][v] = go[((ti * 2 + tj) * 4 + v) * 64 + lane];
+        for (int v = 0; v < 4; ++v) x[ti][tj][v] = from[((ti * 2 + tj) * 4 + v) * 64 + lane];
+  };
+  get(G, gf + (int64_t)(nb - 1) * 1024);
+  if (nb > 1) { get(P, gf + (int64_t)(nb - 2) * 1024); get(kn, kf + (int64_t)(nb - 2) * 1024); }
+  for (int i = nb - 1; i >= 0; --i) {
     if (i + 1 < nb) {
-      const double *ko = kf + (int64_t)i * 1024;
-      double kn[2][2][4];
+      double p[2][2][4], kk[2][2][4];
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-        for (int tk = 0; tk < 2; ++tk)
+        for (int tj = 0; tj < 2; ++tj)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) kn[ti][tk][v] = ko[((ti * 2 + tk) * 4 + v) * 64 + lane];
+          for (int v = 0; v < 4; ++v) { p[ti][tj][v] = P[ti][tj][v]; kk[ti][tj][v] = kn[ti][tj][v]; }
+      if (i > 0) { get(P, gf + (int64_t)(i - 1) * 1024); get(kn, kf + (int64_t)(i - 1) * 1024); }
       band_d4 H[2][2];
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti)
@@ -1009,28 +1029,22 @@ __global__ __launch_bounds__(64) void band_factor_kernel(const BandTableJobs grp
 #pragma unroll
           for (int tk = 0; tk < 2; ++tk)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) H[ti][tj] = band_mfma(G[tk][ti][v], kn[tj][tk][v], H[ti][tj]);
+            for (int v = 0; v < 4; ++v) H[ti][tj] = band_mfma(G[tk][ti][v], kk[tj][tk][v], H[ti][tj]);
         }
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
         for (int tj = 0; tj < 2; ++tj) {
-          band_d4 acc = {P[ti][tj][0], P[ti][tj][1], P[ti][tj][2], P[ti][tj][3]};
+          band_d4 acc = {p[ti][tj][0], p[ti][tj][1], p[ti][tj][2], p[ti][tj][3]};
 #pragma unroll
           for (int tk = 0; tk < 2; ++tk)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc = band_mfma(kn[ti][tk][v], H[tk][tj][v], acc);
+            for (int v = 0; v < 4; ++v) acc = band_mfma(kk[ti][tk][v], H[tk][tj][v], acc);
 #pragma unroll
           for (int v = 0; v < 4; ++v) G[ti][tj][v] = acc[v];
         }
-    } else {
-#pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) G[ti][tj][v] = P[ti][tj][v];
     }
+    double *go = gf + (int64_t)i * 1024;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
