@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void band_alone_kernel(const BandJobs grp) {
 // stays as it is and becomes the reflector, by one factor, when all 16 are done.  The entries are MFMA operands as they lie.
 // Per column one barrier.  Two wavefronts per SIMD: the panel of 2048 rows takes 128 of 256 registers (four
 // wavefronts with half as many rows each spilled up to 247 of 128).
-// 8 panels of 2048 rows beside 8 others: 287 us before, 118 so; 32 of 1024 rows 152 and 85 us.
+// 8 panels of 2016 rows beside 8 others: 287 us with 16 wavefronts, 126 with 8, 99 with the next reads of V on their way and the first
+// reflectors applied on the matrix cores (44 of the 126 us, 22 of the 99); 32 of 992 rows 152, 90 and 70 us.
 // The other matrices of the batch run beside it, other sub-chunks' products too.
 // ---------------------------------------------------------------------------
 constexpr int BAND_QR_WAVES = 8, BAND_QR_THREADS = 64 * BAND_QR_WAVES;
@@ -250,16 +251,22 @@ template <int J> __device__ __forceinline__ void row16_fma(double &x, double y, 
 }
 template <int J> __device__ __forceinline__ double row16_bcast(double x) { return dpp_fetch<0x150 + J>(x); }
 
-// One element per lane and row block of a column of a row-major array: lane address and scalar step, in elements
+// Elements of a lane in an array of `count` elements: lane address and scalar step.  With a step inside the array, what a lane
+// asks for past its end is read as zero.
 struct BandColumn {
   __amdgpu_buffer_rsrc_t r;
   int lane;
-  __device__ __forceinline__ BandColumn(const void *base, int lane_, int size)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(uniform_ptr(base)), 0, INT32_MAX, 0x00020000)), lane(lane_ * size) {}
+  __device__ __forceinline__ BandColumn(const void *base, int lane_, int count, int size)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(uniform_ptr(base)), 0, count * size, 0x00020000)), lane(lane_ * size) {}
   __device__ __forceinline__ double get(int at) const {
     typedef uint32_t pair __attribute__((ext_vector_type(2)));
     const pair x = __builtin_amdgcn_raw_buffer_load_b64(r, lane, at * 8, 0);
     return __hiloint2double((int)x[1], (int)x[0]);
+  }
+  __device__ __forceinline__ band_d4 get4(int at) const {         // at a multiple of 16 bytes
+    const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, lane, at * 8, 0), y = __builtin_amdgcn_raw_buffer_load_b128(r, lane + 16, at * 8, 0);
+    return (band_d4){__hiloint2double((int)x[1], (int)x[0]), __hiloint2double((int)x[3], (int)x[2]), __hiloint2double((int)y[1], (int)y[0]),
+                     __hiloint2double((int)y[3], (int)y[2])};
   }
   __device__ __forceinline__ void put(int at, double v) const {
     typedef uint32_t pair __attribute__((ext_vector_type(2)));
@@ -288,19 +295,36 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
   const int tt = m / BAND;               // row blocks of 32: np is a multiple
   const int rel0 = 4 * w + ph;           // row of register t: rel0 + 32 t
   // The panel's columns in W, V and all of V: a lane's address, plus a scalar that steps from register to register (64 vector
-  // addresses, held over both halves, cost more registers than the panel)
-  const BandColumn wcol(g.w + (int64_t)r0 * np + k * BAND, rel0 * np + c, 8), vcol(g.vp + (int64_t)r0 * BAND, rel0 * BAND + c, 8),
-      acol(g.vall + (int64_t)r0 * np + k * BAND, rel0 * np + c, 4);
+  // addresses, held over both halves, cost more registers than the panel).  Of V also the rows of four registers as an MFMA
+  // operand (row c of those 16, four columns).
+  const BandColumn wcol(g.w + (int64_t)r0 * np + k * BAND, rel0 * np + c, m * np - k * BAND, 8),
+      vcol(g.vp + (int64_t)r0 * BAND, rel0 * BAND + c, m * BAND, 8), vrow(g.vp + (int64_t)r0 * BAND, ((c >> 2) * BAND + 4 * w + (c & 3)) * BAND + 4 * ph, m * BAND, 8),
+      acol(g.vall + (int64_t)r0 * np + k * BAND, rel0 * np + c, m * np - k * BAND, 4);
   double P[TT];
   int buf = 0;
 
-  // f(t) for the registers that hold rows, four of them in flight at a time (all loads ahead of all uses would take as many
-  // registers again)
-  auto by_fours = [&](auto f) {
-    for_each_block<TT>([&](auto t) {
-      if (decltype(t)::value < tt) f(t);
-      if constexpr (decltype(t)::value % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  // f(batch, what load(batch) returned) for the batches of four registers that hold rows, the next DEPTH batches' loads ahead of it.
+  // With one batch at a time, and none ahead, this kernel spent half of its time here (2048 rows).
+  auto by_fours = [&](auto load, auto f) {
+    constexpr int B = TT / 4, DEPTH = 2;
+    decltype(load(0)) x[DEPTH + 1];
+#pragma unroll
+    for (int q = 0; q < DEPTH; ++q) if (q < B && 4 * q < tt) x[q] = load(q);
+    for_each_block<B>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      if (4 * q < tt) {
+        if constexpr (q + DEPTH < B) if (4 * (q + DEPTH) < tt) x[(q + DEPTH) % (DEPTH + 1)] = load(q + DEPTH);
+        __builtin_amdgcn_sched_barrier(0);
+        f(qc, x[q % (DEPTH + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     });
+  };
+  auto v0_of = [&](int q) {
+    band_d4 x;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = vcol.get(min(4 * q + u, tt - 1) * BAND * BAND);   // rows past the end meet a zero in P
+    return x;
   };
   // sum over the wavefronts of a 16 x 16 tile held as MFMA results: to sum[i][j]
   auto tile_sum = [&](band_d4 acc, double (*sum)[17]) {
@@ -325,19 +349,26 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
     }
     if (h == 1) {                        // the reflectors of the first 16 columns:  C <- C - V0 (T0^T V0^T C)
       band_d4 acc = {0.0, 0.0, 0.0, 0.0};
-      by_fours([&](auto t) { acc = band_mfma(vcol.get(decltype(t)::value * BAND * BAND), P[decltype(t)::value], acc); });
-      tile_sum(acc, sh.s);
-      double e = 0.0;
-      if (tid < 256) for (int l = 0; l <= (tid >> 4); ++l) e += sh.t[0][l][tid >> 4] * sh.s[l][tid & 15];
-      __syncthreads();
-      if (tid < 256) sh.s[tid >> 4][tid & 15] = e;
-      __syncthreads();
-      double sw[16];
+      by_fours(v0_of, [&](auto qc, const band_d4 &v) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sw[i] = -sh.s[i][c];
-      by_fours([&](auto t) {
-        const double v = vcol.get(decltype(t)::value * BAND * BAND);
-        for_each_block<16>([&](auto i) { row16_fma<decltype(i)::value>(P[decltype(t)::value], v, sw[decltype(i)::value]); });
+        for (int u = 0; u < 4; ++u) acc = band_mfma(v[u], P[4 * decltype(qc)::value + u], acc);
+      });
+      tile_sum(acc, sh.s);
+      double sw[4];                      // -T0^T V0^T C, rows 4 ph ...
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        double e = 0.0;
+#pragma unroll 4
+        for (int l = 0; l < 16; ++l) e -= sh.t[0][l][4 * ph + u] * sh.s[l][c];
+        sw[u] = e;
+      }
+      by_fours([&](int q) { return vrow.get4(4 * q * BAND * BAND); }, [&](auto qc, const band_d4 &v) {
+        constexpr int t = 4 * decltype(qc)::value;
+        band_d4 x = {P[t], P[t + 1], P[t + 2], P[t + 3]};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x = band_mfma(v[u], sw[u], x);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) P[t + u] = x[u];
       });
     }
     double mine = 0.0;                   // the factor that makes a reflector of this lane's column
@@ -356,9 +387,11 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
       if (lane < 16) sh.red[buf][w][c] = dot;
       if (rel0 == pr) sh.prow[buf][c] = P[0];
       __syncthreads();
-      double s = 0.0;
+      double part[BAND_QR_WAVES];
 #pragma unroll
-      for (int i = 0; i < BAND_QR_WAVES; ++i) s += sh.red[buf][i][c];
+      for (int i = 0; i < BAND_QR_WAVES; ++i) part[i] = sh.red[buf][i][c];
+      const double s = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
+      static_assert(BAND_QR_WAVES == 8, "sum");
       const double sj = row16_bcast<J>(s), x0 = sh.prow[buf][J], pc = sh.prow[buf][c];
       buf ^= 1;
       double tau = 0.0;
@@ -383,25 +416,31 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
     g.cblk[(int64_t)k * 1024 + (16 * h + c) * BAND + rel0] = rel0 <= 16 * h + c ? P[0] : 0.0;
     P[0] = rel0 > 16 * h + c ? P[0] * mine : rel0 == 16 * h + c ? 1.0 : 0.0;
     band_d4 acc = {0.0, 0.0, 0.0, 0.0}, acc01 = {0.0, 0.0, 0.0, 0.0};
-    by_fours([&](auto tc) {
-      constexpr int t = decltype(tc)::value;
-      const double v = t > 0 ? P[t] * mine : P[0];
-      if (h == 1) acc01 = band_mfma(vcol.get(t * BAND * BAND), v, acc01);
-      acc = band_mfma(v, v, acc);
-      vcol.put(t * BAND * BAND + 16 * h, v);
-      acol.put(t * BAND * np + 16 * h, (float)v);
+    by_fours([&](int q) { return h == 1 ? v0_of(q) : (band_d4){0.0, 0.0, 0.0, 0.0}; }, [&](auto qc, const band_d4 &v0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = 4 * decltype(qc)::value + u;
+        const double v = t > 0 ? P[t] * mine : P[0];
+        if (h == 1) acc01 = band_mfma(v0[u], v, acc01);
+        acc = band_mfma(v, v, acc);
+        if (t < tt) {
+          vcol.put(t * BAND * BAND + 16 * h, v);
+          acol.put(t * BAND * np + 16 * h, (float)v);
+        }
+      }
     });
     tile_sum(acc, sh.s);
     // T of these 16 columns: T[i][j] = -tau_j sum_{i <= l < j} T[i][l] (v_l . v_j); lane i holds row i
     if (w == 0) {
-      double T[16];
+      double T[16], e[16];               // e[j]: the sum so far
+#pragma unroll
+      for (int j = 0; j < 16; ++j) e[j] = 0.0;
       for_each_block<16>([&](auto jc) {
         constexpr int J = decltype(jc)::value;
         const double tj = sh.tau[16 * h + J];
-        double e = 0.0;
+        T[J] = c == J ? tj : c < J ? -tj * e[J] : 0.0;
 #pragma unroll
-        for (int l = 0; l < J; ++l) e += T[l] * sh.s[l][J];
-        T[J] = c == J ? tj : c < J ? -tj * e : 0.0;
+        for (int j = J + 1; j < 16; ++j) e[j] += T[J] * sh.s[J][j];
       });
       if (lane < 16) {
 #pragma unroll
@@ -414,13 +453,16 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
   // T = [T0, -T0 (V0^T V1) T1; 0, T1]
   double e = 0.0;
   const int i = tid >> 4, j = tid & 15;
-  if (tid < 256) for (int l = 0; l <= j; ++l) e += sh.g01[i][l] * sh.t[1][l][j];
+  if (tid < 256)
+#pragma unroll
+    for (int l = 0; l < 16; ++l) e += sh.g01[i][l] * sh.t[1][l][j];      // T: zeros below the diagonal
   __syncthreads();
   if (tid < 256) sh.s[i][j] = e;
   __syncthreads();
   if (tid < 256) {
     e = 0.0;
-    for (int l = i; l < 16; ++l) e -= sh.t[0][i][l] * sh.s[l][j];
+#pragma unroll
+    for (int l = 0; l < 16; ++l) e -= sh.t[0][i][l] * sh.s[l][j];
     double *t = g.t;
     float *ta = g.tall + (int64_t)k * 1024;
     auto put = [&](int row, int col, double v) { t[row * BAND + col] = v; ta[row * BAND + col] = (float)v; };
