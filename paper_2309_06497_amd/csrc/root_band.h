@@ -221,8 +221,9 @@ __global__ __launch_bounds__(256) void band_alone_kernel(const BandJobs grp) {
 // stays as it is and becomes the reflector, by one factor, when all 16 are done.  The entries are MFMA operands as they lie.
 // Per column one barrier.  Two wavefronts per SIMD: the panel of 2048 rows takes 128 of 256 registers (four
 // wavefronts with half as many rows each spilled up to 247 of 128).
-// 8 panels of 2016 rows beside 8 others: 287 us with 16 wavefronts, 126 with 8, 99 with the next reads of V on their way and the first
-// reflectors applied on the matrix cores (44 of the 126 us, 22 of the 99); 32 of 992 rows 152, 90 and 70 us.
+// 8 panels of 2016 rows beside 8 others: 287 us with 16 wavefronts, 126 with 8, 96 with the next reads of V on their way and the first
+// reflectors applied on the matrix cores (44 of the 126 us, 22 of the 96); 32 of 992 rows 152, 90 and 67 us.  With 4
+// wavefronts, one per SIMD, and twice the rows in each, the columns take as long and the reads longer.
 // The other matrices of the batch run beside it, other sub-chunks' products too.
 // ---------------------------------------------------------------------------
 constexpr int BAND_QR_WAVES = 8, BAND_QR_THREADS = 64 * BAND_QR_WAVES;
@@ -396,10 +397,16 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
       buf ^= 1;
       double tau = 0.0;
       if (sj > TRI_NO_COLUMN) {
-        const double nn = sj + x0 * x0, rn = rsqrt_newton(nn), norm = nn * rn;
-        const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, inv = rcp_newton(v0);
-        tau = fabs(v0) * rn;
-        const double wc = c > J ? tau * (s * inv + pc) : 0.0, q = -(inv * wc);
+        // 1 / |v0|, v0 = x0 -+ norm, starts from the estimate of the norm, beside the steps that refine it.  The estimates are good to
+        // 2^-22: two steps reach float64.
+        const double nn = sj + x0 * x0, h2 = 0.5 * nn;
+        double rn = __builtin_amdgcn_rsq(nn), r0 = __builtin_amdgcn_rcp(fabs(x0) + nn * rn);
+        rn = rn * (1.5 - h2 * (rn * rn)); rn = rn * (1.5 - h2 * (rn * rn));
+        const double norm = nn * rn, av = fabs(x0) + norm;
+        r0 = r0 * (2.0 - av * r0); r0 = r0 * (2.0 - av * r0);
+        const double alpha = x0 > 0.0 ? -norm : norm, inv = x0 > 0.0 ? r0 : -r0;
+        tau = av * rn;
+        const double zc = c > J ? s * inv + pc : 0.0, wc = tau * zc, q = (x0 > 0.0 ? -rn : rn) * zc;    // q = -wc / v0
         if (c == J) mine = inv;
         double x = rel0 > pr ? P[0] : 0.0;
         const double x1 = x;
@@ -432,15 +439,15 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
     tile_sum(acc, sh.s);
     // T of these 16 columns: T[i][j] = -tau_j sum_{i <= l < j} T[i][l] (v_l . v_j); lane i holds row i
     if (w == 0) {
-      double T[16], e[16];               // e[j]: the sum so far
+      const double tau_c = sh.tau[16 * h + c];
+      double T[16], e[16], sc[16];       // e[j]: the sum so far; sc[j]: (v_c . v_j)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) e[j] = 0.0;
+      for (int j = 0; j < 16; ++j) { e[j] = 0.0; sc[j] = sh.s[c][j]; }
       for_each_block<16>([&](auto jc) {
         constexpr int J = decltype(jc)::value;
-        const double tj = sh.tau[16 * h + J];
+        const double tj = row16_bcast<J>(tau_c);
         T[J] = c == J ? tj : c < J ? -tj * e[J] : 0.0;
-#pragma unroll
-        for (int j = J + 1; j < 16; ++j) e[j] += T[J] * sh.s[J][j];
+        for_each_block<15 - J>([&](auto d) { constexpr int j = J + 1 + decltype(d)::value; row16_fma<J>(e[j], sc[j], T[J]); });
       });
       if (lane < 16) {
 #pragma unroll
