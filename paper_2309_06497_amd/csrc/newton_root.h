@@ -6,7 +6,10 @@
 // (the SYRK epilogue of the GEMM kernel), 36 of 64 tiles at n = 1024.  The kernels here are
 // the small elementwise / reduction steps around those products; convergence is tracked per
 // matrix on the device (`done` flags, which the GEMM launches take as their skip list), so
-// a refresh needs no host synchronisation.
+// a refresh needs no host synchronisation.  The host enqueues all iterations up to the cap, and most find every matrix done,
+// so launches count: the test on M_k is made by the last workgroup of T_k's launch, a finished matrix is copied out behind the
+// last iteration (nothing writes its X any more), and X_1 = T_0 / c is written beside T_0.  64 matrices of 1024 with six launches an
+// iteration and X_0 T_0 a product 22.8 ms, with four and without it 21.6.
 //
 // Arithmetic is float32: operands as three bf16 terms, products summed in float32 (gemm_mfma.h).  ||M_k - I||_inf cannot fall below
 // about n * 2^-24 * (a few) in that arithmetic, so besides the paper's test the iteration of
@@ -21,8 +24,10 @@ struct NewtonArgs {
   const float *a;        // [batch][n][n] input matrices
   int64_t a_stride;
   float *M, *X, *T;      // [batch][n][n] work matrices
-  double *rowpart;       // [batch][n] row sums of squares of A
-  float *err;            // [batch] ||M - I||_inf of the current iterate (atomic max, cleared by check)
+  float *X1;             // X_1, where the iterate is X_0; otherwise nullptr
+  double *rowpart;       // [batch][ceil(n / 32)] sums of squares of A by block rows
+  float *err;            // [batch] ||M - I||_inf of the current iterate (atomic max, cleared by the test)
+  int32_t *arrived;      // [batch] workgroups whose rows are in err (cleared by the test)
   float *prev;           // [batch] the norm one iteration earlier
   int32_t *done;         // [batch] iteration finished (converged, stalled, capped or failed)
   int32_t *failed;       // [batch] not finite: the caller keeps the previous root
@@ -31,39 +36,92 @@ struct NewtonArgs {
   float epsilon, scale, tol;
 };
 
-// grid (n, batch): row i of A = scale * sym(L) + eps I: sum of squares, non-finite check.
-__global__ __launch_bounds__(256) void newton_rownorm_kernel(const NewtonArgs g) {
+// Block row I of A = scale * sym(L) + eps I from the tiles (I, J) and (J, I), J <= I: f(r, c4, x) has row r of the tile, its columns
+// c4 ... c4 + 3 and their values.  Read along rows; the mirror image goes through LDS.  Read down its columns it took 360 us for the
+// norm and 460 for M_0 and X_0 of 64 matrices of 1024, 100 and 205 so.  256 threads.
+constexpr int NEWTON_TILE = 32;
+// Elements (i, j) ... (i, j + 3) of an n x n matrix, zeros past its edges.  quads: rows are whole 16-byte pieces (the sizes of blocks; a
+// caller's may be any).
+__device__ __forceinline__ void newton_get4(const float *a, int n, bool quads, int i, int j, float (&x)[4]) {
+  const float *p = a + (int64_t)i * n + j;
+  if (quads) {
+    const float4 q = i < n && j < n ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
+    x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = i < n && j + e < n ? p[e] : 0.f;
+}
+__device__ __forceinline__ void newton_put4(float *a, int n, bool quads, int i, int j, const float (&x)[4]) {
+  float *p = a + (int64_t)i * n + j;
+  if (quads) {
+    if (i < n && j < n) *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (i < n && j + e < n) p[e] = x[e];
+}
+__device__ __forceinline__ bool newton_quads(const float *a, int n) { return n % 4 == 0 && reinterpret_cast<uintptr_t>(a) % 16 == 0; }
+
+template <typename F> __device__ __forceinline__ void newton_block_row(const float *a, int n, int I, float scale, float eps, int &bad, F f) {
+  __shared__ float mirror[NEWTON_TILE][NEWTON_TILE + 1];
+  const int r = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4, i = I * NEWTON_TILE + r, mj = I * NEWTON_TILE + c4;
+  const bool quads = newton_quads(a, n);
+  for (int J = 0; J <= I; ++J) {
+    const int j = J * NEWTON_TILE + c4, mi = J * NEWTON_TILE + r;
+    float x[4], y[4];
+    newton_get4(a, n, quads, i, j, x);
+    newton_get4(a, n, quads, mi, mj, y);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (!(fabsf(x[e]) <= 3.0e38f) || !(fabsf(y[e]) <= 3.0e38f)) bad = 1;
+    }
+    __syncthreads();                     // the tile before has been read
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mirror[r][c4 + e] = y[e];
+    __syncthreads();
+    double v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (double)scale * 0.5 * ((double)x[e] + (double)mirror[c4 + e][r]);
+      if (i == j + e) v[e] += (double)eps;
+    }
+    f(J, r, c4, v);
+  }
+}
+
+// grid (ceil(n / 32), batch): a block row's part of the sum of squares, non-finite check.
+__global__ __launch_bounds__(256) void newton_norm_kernel(const NewtonArgs g) {
   __shared__ double red[4];
-  const int i = blockIdx.x, b = blockIdx.y, n = g.n, tid = threadIdx.x;
-  const float *a = g.a + (int64_t)b * g.a_stride;
+  const int I = blockIdx.x, b = blockIdx.y, n = g.n, tid = threadIdx.x;
   double ss = 0.0;
   int bad = 0;
-  for (int j = tid; j < n; j += 256) {
-    const float lo = a[(int64_t)i * n + j], up = a[(int64_t)j * n + i];
-    if (!(fabsf(lo) <= 3.0e38f) || !(fabsf(up) <= 3.0e38f)) bad = 1;
-    double v = (double)g.scale * 0.5 * ((double)lo + (double)up);
-    if (i == j) v += (double)g.epsilon;
-    ss += v * v;
-  }
+  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c4, const double (&v)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (I * NEWTON_TILE + r < n && J * NEWTON_TILE + c4 + e < n) ss += (J < I ? 2.0 : 1.0) * (v[e] * v[e]);
+  });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) { ss += __shfl_xor(ss, off, 64); bad |= __shfl_xor(bad, off, 64); }
   if ((tid & 63) == 0) red[tid >> 6] = ss;
   if (bad && (tid & 63) == 0) atomicOr(&g.failed[b], 1);
   __syncthreads();
-  if (tid == 0) g.rowpart[(int64_t)b * n + i] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (tid == 0) g.rowpart[(int64_t)b * gridDim.x + I] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// grid (n, batch): row i of M_0 = A / c^p and X_0 = I / c; the Frobenius norm is summed from
-// the row parts in a fixed order by every workgroup.
+// grid (ceil(n / 32), batch): block row I of M_0 = A / c^p and X_0 = I / c, up to the diagonal, and its mirror image; the Frobenius norm is
+// summed from the parts in a fixed order by every workgroup.
 __global__ __launch_bounds__(256) void newton_init_kernel(const NewtonArgs g) {
   __shared__ double red[4];
-  const int i = blockIdx.x, b = blockIdx.y, n = g.n, tid = threadIdx.x;
+  __shared__ float tile[NEWTON_TILE][NEWTON_TILE + 1];
+  const int I = blockIdx.x, b = blockIdx.y, n = g.n, tid = threadIdx.x;
   if (g.failed[b]) {
-    if (i == 0 && tid == 0) { g.done[b] = 1; g.iters[b] = 0; }
+    if (I == 0 && tid == 0) { g.done[b] = 1; g.iters[b] = 0; }
     return;
   }
   double ss = 0.0;
-  for (int j = tid; j < n; j += 256) ss += g.rowpart[(int64_t)b * n + j];
+  for (int j = tid; j < (int)gridDim.x; j += 256) ss += g.rowpart[(int64_t)b * gridDim.x + j];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
@@ -73,22 +131,48 @@ __global__ __launch_bounds__(256) void newton_init_kernel(const NewtonArgs g) {
   const bool ok = cp > 0.0 && cp <= 1.0e300;
   const double inv_cp = ok ? 1.0 / cp : 0.0;
   const float inv_c = ok ? (float)pow(cp, -1.0 / (double)g.p) : 0.f;
-  const float *a = g.a + (int64_t)b * g.a_stride;
   float *M = g.M + (int64_t)b * n * n, *X = g.X + (int64_t)b * n * n;
-  for (int j = tid; j < n; j += 256) {
-    double v = (double)g.scale * 0.5 * ((double)a[(int64_t)i * n + j] + (double)a[(int64_t)j * n + i]);
-    if (i == j) v += (double)g.epsilon;
-    M[(int64_t)i * n + j] = (float)(v * inv_cp);
-    X[(int64_t)i * n + j] = (i == j) ? inv_c : 0.f;
-  }
-  if (i == 0 && tid == 0) {
+  const bool quads = newton_quads(M, n) && newton_quads(X, n);
+  int bad = 0;
+  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c4, const double (&v)[4]) {
+    const int i = I * NEWTON_TILE + r, j = J * NEWTON_TILE + c4, mi = J * NEWTON_TILE + r, mj = I * NEWTON_TILE + c4;
+    float x[4], id[4], mirror[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[e] = (float)(v[e] * inv_cp);
+      id[e] = i == j + e ? inv_c : 0.f;
+      tile[r][c4 + e] = x[e];            // its last readers are behind a barrier of the next tile's
+    }
+    newton_put4(M, n, quads, i, j, x);
+    newton_put4(X, n, quads, i, j, id);
+    __syncthreads();
+    if (J == I) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { mirror[e] = tile[c4 + e][r]; id[e] = 0.f; }
+    newton_put4(M, n, quads, mi, mj, mirror);
+    newton_put4(X, n, quads, mi, mj, id);
+  });
+  if (I == 0 && tid == 0) {
     g.done[b] = ok ? 0 : 1;
     if (!ok) g.failed[b] = 1;      // zero or non-finite norm
-    g.iters[b] = 0; g.err[b] = 0.f; g.prev[b] = 3.0e38f;
+    g.iters[b] = 0; g.err[b] = 0.f; g.prev[b] = 3.0e38f; g.arrived[b] = 0;
   }
 }
 
-// T = ((p + 1) I - M) / p and ||M - I||_inf.  grid (ceil(n / NEWTON_ROWS), batch), a wavefront per row at a time.
+// The termination test on M_k (k = g.k), e = ||M_k - I||_inf.  One thread
+__device__ __forceinline__ void newton_check(const NewtonArgs &g, int b, float e) {
+  const float pv = g.prev[b];
+  int stop = 0;
+  if (!(e <= 3.0e38f)) { g.failed[b] = 1; stop = 1; }
+  else if (e < g.tol) stop = 1;                               // the paper's criterion
+  else if (g.k >= g.max_iter) stop = 1;                       // iteration cap
+  else if (pv < 0.1f && e > 0.5f * pv) stop = 1;              // float32 floor reached
+  if (stop) { g.done[b] = 1; g.iters[b] = g.k; }
+  g.prev[b] = e;
+}
+
+// T = ((p + 1) I - M) / p and ||M - I||_inf; the last workgroup of a matrix makes the test.  grid (ceil(n / NEWTON_ROWS), batch), a
+// wavefront per row at a time.
 // The host enqueues all max_iter iterations, and most of them find every matrix done: with a workgroup per row
 // 64 matrices of 1024 cost 60 us for each such launch, now about 5 (root of 64 such matrices: 38.6 -> 32.1 ms).
 constexpr int NEWTON_ROWS = 32;
@@ -99,59 +183,57 @@ __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
   const int last = min((int)(blockIdx.x + 1) * NEWTON_ROWS, n);
   float worst = 0.f;
   for (int i = blockIdx.x * NEWTON_ROWS + w; i < last; i += 4) {
-    const float *M = g.M + ((int64_t)b * n + i) * n;
-    float *T = g.T + ((int64_t)b * n + i) * n;
+    const int64_t row = ((int64_t)b * n + i) * n;
+    const float *M = g.M + row;
+    float *T = g.T + row, *X1 = g.X1 ? g.X1 + row : nullptr;
+    const float inv_c = X1 ? g.X[row + i] : 0.f;
     float rs = 0.f;
 #pragma unroll 4
     for (int j = lane; j < n; j += 64) {
-      const float mv = M[j], id = (i == j) ? 1.f : 0.f;
+      const float mv = M[j], id = (i == j) ? 1.f : 0.f, t = ((pp + 1.f) * id - mv) * inv_p;
       rs += fabsf(mv - id);
-      T[j] = ((pp + 1.f) * id - mv) * inv_p;
+      T[j] = t;
+      if (X1) X1[j] = inv_c * t;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) rs += __shfl_xor(rs, off, 64);
     if (!(rs <= 3.0e38f)) rs = __int_as_float(0x7f800000);   // NaN / inf -> +inf, which orders above everything
     worst = fmaxf(worst, rs);
   }
-  if (lane == 0) atomicMax(reinterpret_cast<int *>(g.err + b), __float_as_int(worst));   // >= 0: int order = float order
-}
-
-// one thread per matrix: the termination test on M_k (k = g.k)
-__global__ __launch_bounds__(256) void newton_check_kernel(const NewtonArgs g, int batch) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= batch || g.done[b]) return;
-  const float e = g.err[b], pv = g.prev[b];
-  int stop = 0;
-  if (!(e <= 3.0e38f)) { g.failed[b] = 1; stop = 1; }
-  else if (e < g.tol) stop = 1;                               // the paper's criterion
-  else if (g.k >= g.max_iter) stop = 1;                       // iteration cap
-  else if (pv < 0.1f && e > 0.5f * pv) stop = 1;              // float32 floor reached
-  if (stop) { g.done[b] = 1; g.iters[b] = g.k; }
-  g.prev[b] = e;
-  g.err[b] = 0.f;
+  // Only the norm passes between workgroups, by atomics: each is waited for ahead of the count.  A fence would write T back from
+  // the caches, 400 us.
+  if (lane == 0) {
+    const int before = atomicMax(reinterpret_cast<int *>(g.err + b), __float_as_int(worst));   // >= 0: int order = float order
+    asm volatile("" :: "v"(before) : "memory");
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && atomicAdd(g.arrived + b, 1) == (int)gridDim.x - 1) {
+    const float e = __int_as_float(atomicExch(reinterpret_cast<int *>(g.err + b), 0));
+    g.arrived[b] = 0;
+    newton_check(g, b, e);
+  }
 }
 
 struct NewtonFinishArgs {
-  const float *X; float *x; int64_t x_stride;
-  const int32_t *done, *failed; int32_t *failed_out; unsigned long long *fail_count;
+  const float *X[2]; float *x; int64_t x_stride;       // X_k of even k and of odd k
+  const int32_t *failed; int32_t *failed_out; unsigned long long *fail_count;
   const int32_t *iters; int32_t *iters_out;
-  int32_t n, k;
+  int32_t n;
 };
 
-// grid (ceil(n / NEWTON_ROWS), batch), launched after the test on M_k: a matrix whose iteration ended at exactly
-// this k copies X_k into the output (unless it failed) and reports its status.
+// grid (ceil(n / NEWTON_ROWS), batch), behind the last iteration: a matrix whose iteration ended at k
+// copies X_k into the output (unless it failed) and reports its status.
 __global__ __launch_bounds__(256) void newton_finish_kernel(const NewtonFinishArgs g) {
   const int b = blockIdx.y, n = g.n, tid = threadIdx.x;
-  if (!g.done[b] || g.iters[b] != g.k) return;
-  const int bad = g.failed[b];
+  const int bad = g.failed[b], k = g.iters[b];
   if (blockIdx.x == 0 && tid == 0) {
     if (g.failed_out) g.failed_out[b] = bad;
-    if (g.iters_out) g.iters_out[b] = g.iters[b];
+    if (g.iters_out) g.iters_out[b] = k;
     if (bad && g.fail_count) atomicAdd(g.fail_count, 1ull);
   }
   if (bad) return;
   const int64_t first = (int64_t)blockIdx.x * NEWTON_ROWS * n, last = min(first + (int64_t)NEWTON_ROWS * n, (int64_t)n * n);
-  const float *X = g.X + (int64_t)b * n * n;
+  const float *X = g.X[k & 1] + (int64_t)b * n * n;
   float *x = g.x + (int64_t)b * g.x_stride;
 #pragma unroll 4
   for (int64_t e = first + tid; e < last; e += 256) x[e] = X[e];

@@ -1118,7 +1118,7 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
 struct NewtonLayout {
   int32_t chunk = 0;
   size_t mat = 0;          // bytes of one n x n float32 matrix (aligned)
-  size_t off_mats = 0, off_rowpart = 0, off_err = 0, off_prev = 0, off_done = 0, off_failed = 0, off_iters = 0;
+  size_t off_mats = 0, off_rowpart = 0, off_err = 0, off_prev = 0, off_done = 0, off_failed = 0, off_iters = 0, off_arrived = 0;
   size_t bytes = 0;
 };
 constexpr int NEWTON_MATS = 7;   // M, M', X, X', T and two buffers for the powers of T
@@ -1130,12 +1130,13 @@ NewtonLayout newton_layout(int n, int batch) {
   e.chunk = (int)std::max<size_t>(1, std::min<size_t>(std::min<size_t>((size_t)std::max(batch, 1), 32768), EIG_CHUNK_BYTES / (NEWTON_MATS * e.mat)));
   size_t off = 0;
   e.off_mats = off; off += (size_t)NEWTON_MATS * e.chunk * e.mat;
-  e.off_rowpart = off; off += align_up((size_t)e.chunk * n * sizeof(double));
+  e.off_rowpart = off; off += align_up((size_t)e.chunk * ((n + NEWTON_TILE - 1) / NEWTON_TILE) * sizeof(double));
   e.off_err = off; off += align_up((size_t)e.chunk * sizeof(float));
   e.off_prev = off; off += align_up((size_t)e.chunk * sizeof(float));
   e.off_done = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.off_failed = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.off_iters = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
+  e.off_arrived = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.bytes = off;
   return e;
 }
@@ -1172,33 +1173,27 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
     g.rowpart = reinterpret_cast<double *>(ws + e.off_rowpart);
     g.err = reinterpret_cast<float *>(ws + e.off_err); g.prev = reinterpret_cast<float *>(ws + e.off_prev);
     g.done = reinterpret_cast<int32_t *>(ws + e.off_done); g.failed = reinterpret_cast<int32_t *>(ws + e.off_failed);
-    g.iters = reinterpret_cast<int32_t *>(ws + e.off_iters);
+    g.iters = reinterpret_cast<int32_t *>(ws + e.off_iters); g.arrived = reinterpret_cast<int32_t *>(ws + e.off_arrived);
     g.n = n; g.p = p; g.max_iter = max_iter; g.epsilon = eps; g.scale = scale; g.tol = tol;
     int rc = launch_fill(reinterpret_cast<float *>(g.failed), 0.f, cb, s);
     if (rc) return rc;
     g.M = M; g.X = X; g.T = T;
-    hipLaunchKernelGGL(newton_rownorm_kernel, dim3(n, cb), dim3(256), 0, s, g);
-    hipLaunchKernelGGL(newton_init_kernel, dim3(n, cb), dim3(256), 0, s, g);
+    NewtonFinishArgs fa{};
+    fa.X[0] = X; fa.X[1] = X2;
+    const dim3 blocks((n + NEWTON_TILE - 1) / NEWTON_TILE, cb), rows((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb);
+    hipLaunchKernelGGL(newton_norm_kernel, blocks, dim3(256), 0, s, g);
+    hipLaunchKernelGGL(newton_init_kernel, blocks, dim3(256), 0, s, g);
     HIP_TRY(hipGetLastError());
     for (int k = 0; k <= max_iter; ++k) {
-      g.k = k; g.M = M; g.X = X; g.T = T;
-      hipLaunchKernelGGL(newton_prep_kernel, dim3((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb), dim3(256), 0, s, g);
-      hipLaunchKernelGGL(newton_check_kernel, dim3((cb + 255) / 256), dim3(256), 0, s, g, cb);
-      HIP_TRY(hipGetLastError());
-      // matrices whose iteration ended at this k hand their X over now: afterwards the X / M
-      // buffers swap roles, and a finished matrix is no longer written by the products
-      NewtonFinishArgs fa;
-      fa.X = X; fa.x = x + (int64_t)b0 * n * n; fa.x_stride = (int64_t)n * n;
-      fa.done = g.done; fa.failed = g.failed; fa.failed_out = failed_user ? failed_user + b0 : nullptr;
-      fa.fail_count = fail_count;
-      fa.iters = g.iters; fa.iters_out = iters_user ? iters_user + b0 : nullptr; fa.n = n; fa.k = k;
-      hipLaunchKernelGGL(newton_finish_kernel, dim3((n + NEWTON_ROWS - 1) / NEWTON_ROWS, cb), dim3(256), 0, s, fa);
+      // the X / M buffers swap roles from one k to the next, and a matrix whose iteration has ended is not written by the products
+      g.k = k; g.M = M; g.X = X; g.X1 = k == 0 ? X2 : nullptr; g.T = T;
+      hipLaunchKernelGGL(newton_prep_kernel, rows, dim3(256), 0, s, g);
       HIP_TRY(hipGetLastError());
       if (k == max_iter) break;
-      // T^p by repeated squaring, X' = X T, M' = T^p M.  X T goes along with the first of the others: of small matrices a
+      // T^p by repeated squaring, X' = X T, M' = T^p M.  X T goes along with the first of the others (X_1 comes from newton_prep_kernel): of small matrices a
       // launch is what an iteration costs (one of 33 x 33: 2.74 ms in seven launches an iteration, 2.38 in six).
       GemmBatch<EPI_SYRK> products(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);     // symmetric: read along k
-      newton_product(products, X, T, X2, n, cb, g.done);
+      if (k > 0) newton_product(products, X, T, X2, n, cb, g.done);
       const float *Tp = T;
       float *sq[2] = {Pa, Pb};
       int w = 0;
@@ -1211,6 +1206,12 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
       if ((rc = products.flush())) return rc;
       std::swap(M, M2); std::swap(X, X2);
     }
+    fa.x = x + (int64_t)b0 * n * n; fa.x_stride = (int64_t)n * n;
+    fa.failed = g.failed; fa.failed_out = failed_user ? failed_user + b0 : nullptr;
+    fa.fail_count = fail_count;
+    fa.iters = g.iters; fa.iters_out = iters_user ? iters_user + b0 : nullptr; fa.n = n;
+    hipLaunchKernelGGL(newton_finish_kernel, rows, dim3(256), 0, s, fa);
+    HIP_TRY(hipGetLastError());
   }
   return SHAMPOO_OK;
 }
