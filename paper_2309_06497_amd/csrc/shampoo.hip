@@ -1962,8 +1962,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
         if (mid + 2 < b.modes) {
           const int pre = mid == 0 ? b.m : b.m * b.td[1], dk = b.td[mid + 1], post = (int)(mn / ((int64_t)pre * dk));
           PermuteArgs pm{};
-          pm.desc = desc; pm.table = gs_tab; pm.dst = swapped; pm.d1 = pre; pm.d2 = dk; pm.d3 = post;
-          pm.chunks = tensor_chunks(b); pm.blocks = b.count;
+          pm.desc = desc; pm.table = gs_tab; pm.dst = swapped; pm.d1 = pre; pm.d2 = dk; pm.d3 = post; pm.blocks = b.count;
+          permute_shape(pm, tensor_chunks(b));
           if ((rc = swaps.add(pm, (int64_t)pm.chunks * b.count))) return rc;
           GemmArgs h{};
           h.a.base = swapped; h.a.batch_stride = mn; h.a.ld = pre * post;
@@ -2224,7 +2224,8 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             const int64_t mn = (int64_t)b.m * b.n;
             const int pre = mid == 0 ? b.m : b.m * b.td[1], dk = b.td[mid + 1], post = (int)(mn / ((int64_t)pre * dk));
             PermuteArgs pm{};
-            pm.src = cur; pm.dst = other; pm.d1 = pre; pm.d2 = dk; pm.d3 = post; pm.chunks = tensor_chunks(b); pm.blocks = b.count;
+            pm.src = cur; pm.dst = other; pm.d1 = pre; pm.d2 = dk; pm.d3 = post; pm.blocks = b.count;
+            permute_shape(pm, tensor_chunks(b));
             if ((rc = there.add(pm, (int64_t)pm.chunks * b.count))) return rc;
             GemmArgs h{};
             h.a.base = ws + b.off_midinv[mid]; h.a.batch_stride = (int64_t)dk * dk; h.a.ld = dk;
@@ -2235,6 +2236,7 @@ int step_impl(shampoo_opt *o, float lr, int64_t step, hipStream_t s) {
             products.add(h);
             if (narrow(b) && mid + 3 == b.modes) continue;      // the last product swaps back
             pm.d1 = dk; pm.d2 = pre;
+            permute_shape(pm, tensor_chunks(b));
             if ((rc = back.add(pm, (int64_t)pm.chunks * b.count))) return rc;
             swapped[i] ^= 1;
           }

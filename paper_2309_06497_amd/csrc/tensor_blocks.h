@@ -93,12 +93,28 @@ struct PermuteArgs {
   float *dst;                   // [slot][d2][d1][d3]
   int32_t d1, d2, d3;
   int32_t chunks, blocks;       // workgroups per block
+  int32_t t1, t2, stride;       // tile of i1 and i2 that goes through LDS and its row there; t1 = 0: none
   __device__ __forceinline__ void globals() { to_global(desc, table, src, dst); }
 };
+constexpr int PERMUTE_TILE = 4608, PERMUTE_LDS = PERMUTE_TILE + 32 * 63;
+// The tile of a swap, and its workgroups; `chunks` of them where there is none.  Runs of t2 d3 elements are read and runs of t1 d3
+// written; with more than 72 values of i3 the runs as they lie are long enough.  A row's place in LDS is d3 behind the one before modulo
+// the 64 banks, so that a run's elements, one from each row in turn, lie in different ones.
+inline void permute_shape(PermuteArgs &g, int chunks) {
+  g.chunks = chunks; g.t1 = 0; g.t2 = 1; g.stride = 0;
+  if (g.d3 > 72) return;
+  g.t1 = 32; g.t2 = 16;
+  while (g.t1 * g.t2 * g.d3 > PERMUTE_TILE) { if (g.t1 > g.t2) g.t1 /= 2; else g.t2 /= 2; }
+  g.stride = g.t2 * g.d3 + ((g.d3 - g.t2 * g.d3) & 63);
+  g.chunks = (g.d1 + g.t1 - 1) / g.t1 * ((g.d2 + g.t2 - 1) / g.t2);
+}
 
-// dst[slot][i2][i1][i3] = in[slot][i1][i2][i3].  Workgroups: chunks x blocks.
+// dst[slot][i2][i1][i3] = in[slot][i1][i2][i3].  Workgroups: chunks x blocks.  Bound by memory.  Element by element, the 36-byte pieces of a
+// 3 x 3 convolution's blocks went to memory by parts of lines: the swaps of ResNet-50's blocks (most of them 128 x 128 x 9, 90 MB
+// read and written) took 95 us, 22 through LDS.
 template <typename T>
 __global__ __launch_bounds__(256) void permute_12_kernel(const Group<PermuteArgs> grp) {
+  __shared__ float tile[PERMUTE_LDS];
   int wg;
   const PermuteArgs g = group_pick(grp, wg);
   const int slot = wg / g.chunks, chunk = wg - slot * g.chunks;
@@ -112,6 +128,36 @@ __global__ __launch_bounds__(256) void permute_12_kernel(const Group<PermuteArgs
   const float *fin = g.src ? g.src + (int64_t)slot * n : nullptr;
   float *out = g.dst + (int64_t)slot * n;
   const uint32_t d1 = g.d1, d2 = g.d2, d3 = g.d3;   // 32-bit divisions: a block has less than 2^31 elements
+  if (g.t1 > 0) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tiles2 = (g.d2 + g.t2 - 1) / g.t2, a = chunk / tiles2, i1 = a * g.t1, i2 = (chunk - a * tiles2) * g.t2;
+    const int n1 = min(g.t1, g.d1 - i1), n2 = min(g.t2, g.d2 - i2), run = n2 * g.d3, pieces = (run + 63) / 64;
+    const uint32_t over = (65536 + pieces - 1) / pieces, over_d = (65536 + d3 - 1) / d3;   // quotients below 2^16 / divisor
+    const int64_t first = ((int64_t)i1 * g.d2 + i2) * g.d3, step = (int64_t)g.d2 * g.d3;
+    for (int q0 = wave; q0 < n1 * pieces; q0 += 4 * 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {                  // eight loads in flight
+        const int q = min(q0 + 4 * u, n1 * pieces - 1), r1 = (int)((uint32_t)q * over >> 16), x = min((q - r1 * pieces) * 64 + lane, run - 1);
+        v[u] = fin ? fin[first + r1 * step + x] : Elem<T>::load1(tin + first + r1 * step + x);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int q = q0 + 4 * u, r1 = (int)((uint32_t)q * over >> 16), x = (q - r1 * pieces) * 64 + lane;
+        if (q < n1 * pieces && x < run) tile[r1 * g.stride + x] = v[u];
+      }
+    }
+    __syncthreads();
+    for (int r2 = wave; r2 < n2; r2 += 4) {
+      float *to = out + ((int64_t)(i2 + r2) * g.d1 + i1) * g.d3;
+#pragma unroll 4
+      for (int y = lane; y < n1 * g.d3; y += 64) {
+        const int r1 = (int)((uint32_t)y * over_d >> 16);
+        to[y] = tile[r1 * g.stride + r2 * g.d3 + y - r1 * g.d3];
+      }
+    }
+    return;
+  }
   const uint32_t step = g.chunks * 256;
   for (uint32_t e0 = chunk * 256 + threadIdx.x; e0 < n; e0 += COPY_U * step) {
     float v[COPY_U];
