@@ -18,7 +18,7 @@ def test_factor_of_the_middle_dimension(shape, post, bf16):
     g = torch.randn(shape, device="cuda", generator=gen)
     if bf16:
         g = g.bfloat16()
-    opt = B.Shampoo([shape], 128, 0.0, 1e-12, 0.25, 1 << 20, 1 << 20, grad_dtype=B.GRAD_BF16 if bf16 else B.GRAD_F32)
+    opt = B.Shampoo([shape], max(shape), 1.0, 1e-12, 0.25, 1 << 20, 1 << 20, grad_dtype=B.GRAD_BF16 if bf16 else B.GRAD_F32)
     opt.step([torch.zeros(shape, device="cuda")], [g], 0.01, 0)
     x = g.double()
     exact = torch.einsum("iaj,ibj->ab", x.cpu(), x.cpu())
@@ -34,7 +34,7 @@ def test_there_and_back(shape):
     import torch
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1)
-    opt = B.Shampoo([shape], 64, 0.99, 1e-12, 0.25, 1, 0)
+    opt = B.Shampoo([shape], max(shape), 0.99, 1e-12, 0.25, 1, 0)
     w = [torch.zeros(shape, device="cuda")]
     for t in range(2):
         g = torch.randn(shape, device="cuda", generator=gen)
