@@ -569,16 +569,36 @@ __global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
   const int r0 = (k + 1) * BAND;
   const int np = g.np, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lg = lane >> 4;
   const int base = r0 + BAND_ROWS * bx + BAND * w;
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int q = 0, parts = band_z_wgs(g, k); q < parts; ++q)
+  // The rows' own operands are requested with the first of the sums, eight of which are in flight: 8 matrices of 2048 beside 8 others, the
+  // average panel, 17 us with four and the operands behind them, 12 so.
+  band_d4 za[2][2], va[2][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] += g.part[(int64_t)q * 1024 + tid + 256 * i];
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t at = (int64_t)(min(base, np - BAND) + 16 * rt + li) * BAND + 16 * h + 4 * lg;
+      za[rt][h] = *reinterpret_cast<const band_d4 *>(g.z + at);
+      va[rt][h] = *reinterpret_cast<const band_d4 *>(g.vp + at);
+    }
+  double tt[4], s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) tt[i] = g.t[tid + 256 * i];
+  for (int q = 0, parts = band_z_wgs(g, k); q < parts; q += 8) {
+    double x[8][4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[u][i] = g.part[(int64_t)min(q + u, parts - 1) * 1024 + tid + 256 * i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] += q + u < parts ? x[u][i] : 0.0;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int e = tid + 256 * i;
     M[e >> 5][e & 31] = s[i];
-    Tm[e >> 5][e & 31] = g.t[e];
+    Tm[e >> 5][e & 31] = tt[i];
   }
   __syncthreads();
   const int ti = 16 * (w >> 1), tj = 16 * (w & 1);
@@ -602,17 +622,14 @@ __global__ __launch_bounds__(256) void band_y_kernel(const BandJobs grp) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) { zt[j] = (band_d4){0, 0, 0, 0}; vs[j] = (band_d4){0, 0, 0, 0}; }
 #pragma unroll
-    for (int kk = 0; kk < BAND; kk += 16) {
-      const int64_t at = (int64_t)(base + 16 * rt + li) * BAND + kk + 4 * lg;
-      const band_d4 za = *reinterpret_cast<const band_d4 *>(g.z + at);
-      const band_d4 va = *reinterpret_cast<const band_d4 *>(g.vp + at);
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int kq = kk + 4 * lg + q;
+        const int kq = 16 * h + 4 * lg + q;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          zt[j] = band_mfma(za[q], Tm[kq][16 * j + li], zt[j]);
-          vs[j] = band_mfma(va[q], S[kq][16 * j + li], vs[j]);
+          zt[j] = band_mfma(za[rt][h][q], Tm[kq][16 * j + li], zt[j]);
+          vs[j] = band_mfma(va[rt][h][q], S[kq][16 * j + li], vs[j]);
         }
       }
     }
