@@ -120,16 +120,12 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
     const int j = col0 + 32 * t + l32;
     at[t] = j < dim && (t == 0 || two) ? (row0 + 4 * khalf) * stride + 4 * j : SB_NOWHERE;
   }
+  // no branch around them, or they would be waited for where it ends
   float old[2][16];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) old[t][v] = 0.f;
-  if (beta != 0.0)
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) old[t][v] = sb_get(f, at[t] + (8 * (v >> 2) + (v & 3)) * stride);
+    for (int v = 0; v < 16; ++v) old[t][v] = sb_get(f, beta != 0.0 ? at[t] + (8 * (v >> 2) + (v & 3)) * stride : SB_NOWHERE);
   double sum[2][16];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
@@ -167,6 +163,11 @@ __device__ __forceinline__ void sb_factor(const float *Gs, float *F, int dim, in
 #pragma unroll
       for (int v = 0; v < 16; ++v) sum[1][v] += (double)acc[1][v];
   }
+  // not converted to float64 before the products: that would wait for them there
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(old[t][v]));
   // of a tile on the diagonal the lower half
   const bool diag[2] = {I == J, I == J + 1};
 #pragma unroll
