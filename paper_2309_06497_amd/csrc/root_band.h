@@ -397,8 +397,7 @@ __global__ __launch_bounds__(BAND_QR_THREADS) void band_qr_kernel(const BandJobs
       buf ^= 1;
       double tau = 0.0;
       if (sj > TRI_NO_COLUMN) {
-        // 1 / |v0|, v0 = x0 -+ norm, starts from the estimate of the norm, beside the steps that refine it.  The estimates are good to
-        // 2^-22: two steps reach float64.
+        // 1 / |v0|, v0 = x0 -+ norm, starts from the estimate of the norm, beside the steps that refine it (as rsqrt_newton and rcp_newton)
         const double nn = sj + x0 * x0, h2 = 0.5 * nn;
         double rn = __builtin_amdgcn_rsq(nn), r0 = __builtin_amdgcn_rcp(fabs(x0) + nn * rn);
         rn = rn * (1.5 - h2 * (rn * rn)); rn = rn * (1.5 - h2 * (rn * rn));

@@ -283,8 +283,13 @@ __global__ __launch_bounds__(NT, 2) void rootinv_tridiag_kernel(const Group<Smal
 #pragma unroll
         for (int p = P0; p < RB; ++p) A[p][q] = fma(-vr[p], qc[q], fma(-qr[p], vc[q], A[p][q]));
       const bool none = !(s2 > TRI_NO_COLUMN);       // nothing to reflect
-      const double nn = none ? 1.0 : fma(x0, x0, s2), norm = nn * rsqrt_newton(nn);
-      const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, beta = none ? 0.0 : rcp_newton(norm * fabs(v0));
+      // 1 / (norm |v0|) starts from the estimate of the norm, beside the steps that refine it (as rsqrt_newton and rcp_newton)
+      const double nn = none ? 1.0 : fma(x0, x0, s2), h = 0.5 * nn;
+      double rn = __builtin_amdgcn_rsq(nn), bi = __builtin_amdgcn_rcp(fma(nn * rn, fabs(x0), nn));
+      rn = rn * (1.5 - h * (rn * rn)); rn = rn * (1.5 - h * (rn * rn));
+      const double norm = nn * rn, nv = fma(norm, fabs(x0), nn);          // norm |v0| = norm (norm + |x0|)
+      bi = bi * (2.0 - nv * bi); bi = bi * (2.0 - nv * bi);
+      const double alpha = x0 > 0.0 ? -norm : norm, v0 = x0 - alpha, beta = none ? 0.0 : bi;
       double part[RB], vav = 0.0;
 #pragma unroll
       for (int p = 0; p < RB; ++p) part[p] = 0.0;
