@@ -1118,7 +1118,7 @@ int root_inverse_batched(const float *a, int n, int batch, float eps, float r, f
 struct NewtonLayout {
   int32_t chunk = 0;
   size_t mat = 0;          // bytes of one n x n float32 matrix (aligned)
-  size_t off_mats = 0, off_rowpart = 0, off_err = 0, off_prev = 0, off_done = 0, off_failed = 0, off_iters = 0, off_arrived = 0;
+  size_t off_mats = 0, off_rowpart = 0, off_err = 0, off_prev = 0, off_done = 0, off_failed = 0, off_iters = 0, off_arrived = 0, off_xdone = 0;
   size_t bytes = 0;
 };
 constexpr int NEWTON_MATS = 7;   // M, M', X, X', T and two buffers for the powers of T
@@ -1137,6 +1137,7 @@ NewtonLayout newton_layout(int n, int batch) {
   e.off_failed = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.off_iters = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.off_arrived = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
+  e.off_xdone = off; off += align_up((size_t)e.chunk * sizeof(int32_t));
   e.bytes = off;
   return e;
 }
@@ -1174,6 +1175,7 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
     g.err = reinterpret_cast<float *>(ws + e.off_err); g.prev = reinterpret_cast<float *>(ws + e.off_prev);
     g.done = reinterpret_cast<int32_t *>(ws + e.off_done); g.failed = reinterpret_cast<int32_t *>(ws + e.off_failed);
     g.iters = reinterpret_cast<int32_t *>(ws + e.off_iters); g.arrived = reinterpret_cast<int32_t *>(ws + e.off_arrived);
+    g.xdone = reinterpret_cast<int32_t *>(ws + e.off_xdone);
     g.n = n; g.p = p; g.max_iter = max_iter; g.epsilon = eps; g.scale = scale; g.tol = tol;
     int rc = launch_fill(reinterpret_cast<float *>(g.failed), 0.f, cb, s);
     if (rc) return rc;
@@ -1193,7 +1195,7 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
       // T^p by repeated squaring, X' = X T, M' = T^p M.  X T goes along with the first of the others (X_1 comes from newton_prep_kernel): of small matrices a
       // launch is what an iteration costs (one of 33 x 33: 2.74 ms in seven launches an iteration, 2.38 in six).
       GemmBatch<EPI_SYRK> products(gemm_kernels<K_CONTIG, K_CONTIG, float, float, EPI_SYRK>(), s);     // symmetric: read along k
-      if (k > 0) newton_product(products, X, T, X2, n, cb, g.done);
+      if (k > 0) newton_product(products, X, T, X2, n, cb, g.xdone);
       const float *Tp = T;
       float *sq[2] = {Pa, Pb};
       int w = 0;

@@ -1,0 +1,39 @@
+"""The last step of the coupled Newton iteration, which does not form the M that would only pass the test:
+||M_{k+1} - I|| <= ||M_k - I||^2 ends an iteration at the k at which the one that forms it ends, in float64 too."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def factors(n, seed):
+    """Four matrices that end at different k: far from and close to a multiple of I."""
+    r = np.random.default_rng(seed)
+    out = np.empty((4, n, n), np.float32)
+    for b, columns in enumerate((2 * n + 1, 4 * n, 64 * n, 4096 * n)):
+        g = r.standard_normal((n, columns)) if n * columns < 1 << 20 else np.sqrt(columns) * np.eye(n)
+        out[b] = (g @ g.T / columns).astype(np.float32)
+        out[b] = 0.5 * (out[b] + out[b].T)
+    return out
+
+
+# n = 2, p = 2: M_0 = 1.06 I, decided at k = 0
+@pytest.mark.parametrize("n,p,tol", [(1, 2, 0.3), (2, 2, 1e-2), (2, 4, 1e-3), (33, 1, 1e-2), (63, 2, 0.5), (64, 4, 1e-2), (65, 8, 1e-3), (129, 4, 1e-3)])
+def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
+    import torch
+    from oracle import shampoo_oracle as so
+    from paper_2309_06497_amd import binding as B
+    f32 = lambda v: float(np.float32(v))
+    a = factors(n, 7 * n + p)
+    dev = torch.from_numpy(a).cuda()
+    want = [so.root_inverse_newton(a[b], f32(1e-3), p, f32(tol), 100) for b in range(4)]
+    caps = {100} | {max(1, k + d) for _, k, _ in want for d in (-1, 0)}     # caps at, and one ahead of, each end
+    for cap in sorted(caps):
+        x, iters, failed = B.shampoo_root_inverse_newton(dev, 1e-3, p, tol, cap, True, True)
+        assert not failed.any()
+        for b in range(4):
+            X, k, _ = so.root_inverse_newton(a[b], f32(1e-3), p, f32(tol), cap)
+            assert int(iters[b]) == k, (cap, b)
+            got = x[b].cpu().numpy()
+            # the same iterates up to float32 products: condition numbers up to 40, n-long sums, at most 10 iterations
+            assert np.linalg.norm(got - X) <= 2e-5 * np.linalg.norm(X), (cap, b)
