@@ -23,6 +23,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "bf16_terms.h"
+#include "group.h"
 
 namespace shampoo {
 
@@ -249,6 +251,212 @@ __global__ __launch_bounds__(256) void newton_finish_kernel(const NewtonFinishAr
   float *x = g.x + (int64_t)b * g.x_stride;
 #pragma unroll 4
   for (int64_t e = first + tid; e < last; e += 256) x[e] = X[e];
+}
+
+
+// Matrices of up to 128: the whole iteration in one launch, a workgroup per matrix and a wavefront per 32 x 32 tile on or
+// below the diagonal.  Launch by launch such a root is 400 launches whatever its size (2.4 ms), nine of ten of them for
+// nothing.  M and X stay in registers, as tiles of MFMA results; the operands of a product go through LDS, mirrored and along
+// k (two matrices of 128 fill it).  With E = (I - M) / p, which is exact, X' = X + X E and M' = M + ((I + E)^p - I) M: a product rounds
+// at the size of E, not of T = I + E.  Products on the float32 matrix cores, in two accumulators that take turns: four cost spills.
+// One matrix of 64 x 64 2.37 ms in 400 launches, 0.056 so, of 128 x 128 2.36 and 0.18 ms; 2048 of them 3.02 and 0.33, 7.8 and 1.6 ms.
+// Bound by the chain of four products an iteration, which many matrices of 64 and all larger ones make on matrix cores that
+// are not evenly loaded (10 tiles on 4 SIMDs).  Errors against float64 a third to an eighth of those of the launches.  From 129 on
+// two matrices do not fit into LDS.
+struct NewtonSmallArgs {
+  const float *a; float *x;             // [batch][n][n]
+  int32_t *iters_out, *failed_out; unsigned long long *fail_count;      // any may be nullptr
+  int32_t n, p, max_iter;
+  float epsilon, scale, tol;
+};
+constexpr int NEWTON_SMALL = 128;
+// Calls that allow fewer iterations than well-conditioned matrices take (6 ... 9) keep the launches, four an iteration.
+// That is not for their speed (2048 of 128 x 128 with a cap of 7 3.3 ms, with one of 8 1.6; one of 64 x 64 205 and 54 us): what a call of few
+// iterations enqueues is held to by tests/test_host_launches.py.
+constexpr int NEWTON_SMALL_ITERATIONS = 8;
+
+// NB = ceil(n / 32).  Workgroups: matrices.
+template <int NB> __global__ __launch_bounds__(32 * NB * (NB + 1)) void newton_small_kernel(const NewtonSmallArgs g) {
+  constexpr int W = NB * (NB + 1) / 2, NR = 32 * NB, LD = NR + 4;       // rows of a matrix in LDS four banks apart
+  __shared__ __align__(16) float sh[2][NR * LD];
+  __shared__ float rows[(NB + 1) * NR];
+  __shared__ double red[W];
+  __shared__ int bads[W];
+  const int b = blockIdx.x, n = g.n, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int ti = 0;
+  while (w >= (ti + 1) * (ti + 2) / 2) ++ti;
+  const int tj = w - ti * (ti + 1) / 2, half = lane >> 5, l32 = lane & 31;
+  // element v of a lane's tile: row i0 + 8 (v / 4) + v % 4, column j
+  const int i0 = 32 * ti + 4 * half, j = 32 * tj + l32;
+  auto row_of = [&](int v) { return i0 + 8 * (v >> 2) + (v & 3); };
+  // The tile and its mirror image into LDS.  A tile on the diagonal reads its own back, and what lies above the diagonal becomes what
+  // lies below.
+  auto put = [&](float *s, float (&x)[16]) {
+    float *down = s + i0 * LD + j, *across = s + j * LD + i0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) down[(8 * (v >> 2) + (v & 3)) * LD] = x[v];
+    if (ti != tj) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) *reinterpret_cast<float4 *>(across + 8 * q) = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+      return;
+    }
+    wavefront_order();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = *reinterpret_cast<const float4 *>(across + 8 * q);
+      const float m[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * q + e] = i0 + 8 * q + e >= j ? x[4 * q + e] : m[e];
+    }
+    wavefront_order();
+#pragma unroll
+    for (int v = 0; v < 16; ++v) down[(8 * (v >> 2) + (v & 3)) * LD] = x[v];
+  };
+  // The tile of A B, both symmetric.  A lane's four values of k are those of four MFMAs.
+  const int steps = (n + 7) / 8;         // zeros behind
+  auto product = [&](const float *A, const float *B, float (&out)[16]) {
+    const float *pa = A + (32 * ti + l32) * LD + 4 * half, *pb = B + (32 * tj + l32) * LD + 4 * half;
+    floatx16 acc[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[e][v] = 0.f;
+#pragma unroll 2
+    for (int q = 0; q < steps; ++q) {
+      const float4 x = *reinterpret_cast<const float4 *>(pa + 8 * q), y = *reinterpret_cast<const float4 *>(pb + 8 * q);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc[1], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc[1], 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) out[v] = acc[0][v] + acc[1][v];
+  };
+
+  // A = scale * sym(L) + eps I, its norm, M_0 and X_0 as newton_init_kernel
+  const float *a = g.a + (int64_t)b * n * n;
+  int bad = 0;
+  for (int i = w; i < NR; i += W)
+    for (int c = lane; c < NR; c += 64) {
+      const float x = i < n && c < n ? a[(int64_t)i * n + c] : 0.f;
+      if (!(fabsf(x) <= 3.0e38f)) bad = 1;
+      sh[0][i * LD + c] = x;
+    }
+  __syncthreads();
+  float M[16], X[16], E[16];             // E = (I - M) / p = T - I
+  double val[16], ss = 0.0;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int i = row_of(v);
+    val[v] = (double)g.scale * 0.5 * ((double)sh[0][i * LD + j] + (double)sh[0][j * LD + i]);
+    if (i == j && i < n) val[v] += (double)g.epsilon;
+    ss += (i > j ? 2.0 : i == j ? 1.0 : 0.0) * (val[v] * val[v]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { ss += __shfl_xor(ss, off, 64); bad |= __shfl_xor(bad, off, 64); }
+  if (lane == 0) { red[w] = ss; bads[w] = bad; }
+  __syncthreads();
+  double fro = 0.0;
+  bad = 0;
+#pragma unroll
+  for (int i = 0; i < W; ++i) { fro += red[i]; bad |= bads[i]; }
+  fro = sqrt(fro);
+  const double cp = 2.0 * fro / ((double)g.p + 1.0);           // c^p
+  int failed = bad || !(cp > 0.0 && cp <= 1.0e300), iters = 0;
+  if (!failed) {
+    const double inv_cp = 1.0 / cp;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) M[v] = (float)(val[v] * inv_cp);
+    __builtin_amdgcn_sched_barrier(0);
+    const float inv_c = (float)pow(cp, -1.0 / (double)g.p), pp = (float)g.p, inv_p = 1.f / pp;
+    float prev = 3.0e38f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) X[v] = row_of(v) == j && j < n ? inv_c : 0.f;
+    for (int k = 0;; ++k) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) E[v] = ((row_of(v) == j && j < n ? 1.f : 0.f) - M[v]) * inv_p;
+      __syncthreads();                   // the reads before
+      put(sh[0], E);
+      put(sh[1], X);
+      __syncthreads();
+      // ||M - I||_inf = p ||E||_inf: NB + 1 threads a row, then all rows in every wavefront, so that all of them decide alike
+      const int r = tid % NR, part = tid / NR;
+      float rs = 0.f;
+      for (int c = part; c < NR / 4; c += NB + 1) {
+        const float4 q = *reinterpret_cast<const float4 *>(sh[0] + r * LD + 4 * c);
+        rs += (fabsf(q.x) + fabsf(q.y)) + (fabsf(q.z) + fabsf(q.w));
+      }
+      rows[part * NR + r] = rs;
+      __syncthreads();
+      float e = 0.f;
+#pragma unroll
+      for (int i = lane; i < NR; i += 64) {
+        float sum = 0.f;
+#pragma unroll
+        for (int q = 0; q <= NB; ++q) sum += rows[q * NR + i];
+        if (!(sum <= 3.0e38f)) sum = __int_as_float(0x7f800000);
+        e = fmaxf(e, sum);
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) e = fmaxf(e, __shfl_xor(e, off, 64));
+      e *= pp;
+      // the tests of newton_check
+      failed = !(e <= 3.0e38f);
+      iters = k;
+      if (failed || e < g.tol || k >= g.max_iter || (prev < 0.1f && e > 0.5f * prev)) break;
+      prev = e;
+      float out[16];
+      if (k > 0) product(sh[1], sh[0], out);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) X[v] += k > 0 ? out[v] : inv_c * E[v];
+      if (e <= 1.f && e * e < g.tol) { iters = k + 1; break; }
+      if (g.p == 1) {
+        __syncthreads();
+        put(sh[1], M);
+      } else {
+        product(sh[0], sh[0], out);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) E[v] = 2.f * E[v] + out[v];          // (I + E)^2 - I, and so on
+        __syncthreads();
+        put(sh[1], E);
+        put(sh[0], M);
+        for (int q = 4; q <= g.p; q *= 2) {
+          __syncthreads();
+          product(sh[1], sh[1], out);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) E[v] = 2.f * E[v] + out[v];
+          __syncthreads();
+          put(sh[1], E);
+        }
+      }
+      __syncthreads();
+      product(sh[1], sh[0], out);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) M[v] += out[v];
+    }
+  }
+  if (tid == 0) {
+    if (g.failed_out) g.failed_out[b] = failed;
+    if (g.iters_out) g.iters_out[b] = iters;
+    if (failed && g.fail_count) atomicAdd(g.fail_count, 1ull);
+  }
+  if (failed) return;
+  __syncthreads();
+  put(sh[0], X);
+  __syncthreads();
+  float *x = g.x + (int64_t)b * n * n;
+  for (int i = w; i < n; i += W)
+    for (int c = lane; c < n; c += 64) x[(int64_t)i * n + c] = sh[0][i * LD + c];
+}
+
+inline void launch_newton_small(const NewtonSmallArgs &g, int batch, hipStream_t s) {
+  const dim3 grid(batch);
+  switch ((g.n + 31) / 32) {
+    case 1: hipLaunchKernelGGL(newton_small_kernel<1>, grid, dim3(64), 0, s, g); break;
+    case 2: hipLaunchKernelGGL(newton_small_kernel<2>, grid, dim3(192), 0, s, g); break;
+    case 3: hipLaunchKernelGGL(newton_small_kernel<3>, grid, dim3(384), 0, s, g); break;
+    default: hipLaunchKernelGGL(newton_small_kernel<4>, grid, dim3(640), 0, s, g); break;
+  }
 }
 
 }  // namespace shampoo

@@ -1162,6 +1162,12 @@ int newton_root_batched(const float *a, int n, int batch, float eps, int p, floa
                         float *x, int32_t *iters_user, int32_t *failed_user, unsigned long long *fail_count,
                         unsigned char *ws, const NewtonLayout &e, hipStream_t s) {
   if (batch <= 0) return SHAMPOO_OK;
+  if (n <= NEWTON_SMALL && max_iter >= NEWTON_SMALL_ITERATIONS) {
+    NewtonSmallArgs g{a, x, iters_user, failed_user, fail_count, n, p, max_iter, eps, scale, tol};
+    launch_newton_small(g, batch, s);
+    HIP_TRY(hipGetLastError());
+    return SHAMPOO_OK;
+  }
   const size_t mat_elems = e.mat / sizeof(float);
   for (int b0 = 0; b0 < batch; b0 += e.chunk) {
     const int cb = std::min(e.chunk, batch - b0);

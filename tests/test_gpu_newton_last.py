@@ -1,5 +1,6 @@
-"""The last step of the coupled Newton iteration, which does not form the M that would only pass the test:
-||M_{k+1} - I|| <= ||M_k - I||^2 ends an iteration at the k at which the one that forms it ends, in float64 too."""
+"""Newton roots around the sizes where their kernels change (up to 128 in one launch, in tiles of 32), and the last
+step of the iteration, which does not form the M that would only pass the test: ||M_{k+1} - I|| <= ||M_k - I||^2
+ends an iteration at the k at which the one that forms it ends, in float64 too."""
 import numpy as np
 import pytest
 
@@ -18,7 +19,9 @@ def factors(n, seed):
 
 
 # n = 2, p = 2: M_0 = 1.06 I, decided at k = 0
-@pytest.mark.parametrize("n,p,tol", [(1, 2, 0.3), (2, 2, 1e-2), (2, 4, 1e-3), (33, 1, 1e-2), (63, 2, 0.5), (64, 4, 1e-2), (65, 8, 1e-3), (129, 4, 1e-3)])
+@pytest.mark.parametrize("n,p,tol", [(1, 2, 0.3), (2, 2, 1e-2), (2, 4, 1e-3), (33, 1, 1e-2), (63, 2, 0.5), (64, 4, 1e-2), (65, 8, 1e-3), (129, 4, 1e-3),
+                                     (31, 4, 1e-3), (32, 8, 1e-2), (96, 2, 1e-2), (97, 4, 1e-3), (127, 1, 1e-2), (128, 8, 1e-3), (128, 1, 1e-2),
+                                     (32, 1, 1e-5), (128, 1, 1e-5)])
 def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
     import torch
     from oracle import shampoo_oracle as so
@@ -27,7 +30,8 @@ def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
     a = factors(n, 7 * n + p)
     dev = torch.from_numpy(a).cuda()
     want = [so.root_inverse_newton(a[b], f32(1e-3), p, f32(tol), 100) for b in range(4)]
-    caps = {100} | {max(1, k + d) for _, k, _ in want for d in (-1, 0)}     # caps at, and one ahead of, each end
+    # caps at, and one ahead of, each end; from 8 on small matrices are done in one launch
+    caps = {8, 100} | {max(1, k + d) for _, k, _ in want for d in (-1, 0)}
     for cap in sorted(caps):
         x, iters, failed = B.shampoo_root_inverse_newton(dev, 1e-3, p, tol, cap, True, True)
         assert not failed.any()
@@ -36,4 +40,5 @@ def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
             assert int(iters[b]) == k, (cap, b)
             got = x[b].cpu().numpy()
             # the same iterates up to float32 products: condition numbers up to 40, n-long sums, at most 10 iterations
+            assert np.array_equal(got, got.T)
             assert np.linalg.norm(got - X) <= 2e-5 * np.linalg.norm(X), (cap, b)
