@@ -186,6 +186,7 @@ __device__ __forceinline__ void newton_check(const NewtonArgs &g, int b, float e
 // wavefront per row at a time.
 // The host enqueues all max_iter iterations, and most of them find every matrix done: with a workgroup per row
 // 64 matrices of 1024 cost 60 us for each such launch, now about 5 (root of 64 such matrices: 38.6 -> 32.1 ms).
+// Otherwise it is bound by memory: 512 MB in 157 us with 4-byte loads, 118 so.
 constexpr int NEWTON_ROWS = 32;
 __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
   const int b = blockIdx.y, n = g.n, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -194,6 +195,7 @@ __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
     return;
   }
   const float pp = (float)g.p, inv_p = 1.f / pp;
+  const bool quads = newton_quads(g.M, n);                   // T and X_1 lie a multiple of 256 bytes further
   const int last = min((int)(blockIdx.x + 1) * NEWTON_ROWS, n);
   float worst = 0.f;
   for (int i = blockIdx.x * NEWTON_ROWS + w; i < last; i += 4) {
@@ -203,11 +205,21 @@ __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
     const float inv_c = X1 ? g.X[row + i] : 0.f;
     float rs = 0.f;
 #pragma unroll 4
-    for (int j = lane; j < n; j += 64) {
-      const float mv = M[j], id = (i == j) ? 1.f : 0.f, t = ((pp + 1.f) * id - mv) * inv_p;
-      rs += fabsf(mv - id);
-      T[j] = t;
-      if (X1) X1[j] = inv_c * t;
+    for (int j = 4 * lane; j < n; j += 256) {
+      float m[4], t[4];
+      newton_get4(M, n, quads, 0, j, m);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float id = i == j + e ? 1.f : 0.f;
+        t[e] = ((pp + 1.f) * id - m[e]) * inv_p;
+        rs += fabsf(m[e] - id);
+      }
+      newton_put4(T, n, quads, 0, j, t);
+      if (X1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] *= inv_c;
+        newton_put4(X1, n, quads, 0, j, t);
+      }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) rs += __shfl_xor(rs, off, 64);
