@@ -281,11 +281,8 @@ struct NewtonSmallArgs {
   int32_t n, p, max_iter;
   float epsilon, scale, tol;
 };
+// A call that allows a single iteration gains too: one matrix of 128 61 -> 37 us, 2048 of them 744 -> 382, 2048 of 32 110 -> 24.
 constexpr int NEWTON_SMALL = 128;
-// Calls that allow fewer iterations than well-conditioned matrices take (6 ... 9) keep the launches, four an iteration.
-// That is not for their speed (2048 of 128 x 128 with a cap of 7 3.3 ms, with one of 8 1.6; one of 64 x 64 205 and 54 us): what a call of few
-// iterations enqueues is held to by tests/test_host_launches.py.
-constexpr int NEWTON_SMALL_ITERATIONS = 8;
 
 // NB = ceil(n / 32).  Workgroups: matrices.
 template <int NB> __global__ __launch_bounds__(32 * NB * (NB + 1)) void newton_small_kernel(const NewtonSmallArgs g) {

@@ -30,7 +30,7 @@ def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
     a = factors(n, 7 * n + p)
     dev = torch.from_numpy(a).cuda()
     want = [so.root_inverse_newton(a[b], f32(1e-3), p, f32(tol), 100) for b in range(4)]
-    # caps at, and one ahead of, each end; from 8 on small matrices are done in one launch
+    # caps at, and one ahead of, each end
     caps = {8, 100} | {max(1, k + d) for _, k, _ in want for d in (-1, 0)}
     for cap in sorted(caps):
         x, iters, failed = B.shampoo_root_inverse_newton(dev, 1e-3, p, tol, cap, True, True)

@@ -215,12 +215,26 @@ for count in (96, 128, 129, 200):
 def test_products_of_a_newton_iteration(lib, p, launches):
     """X T goes along with the first of the others, whose squares and last product need one another."""
     out = host_hip.run(lib, r"""
-ws = L.shampoo_root_inverse_newton_workspace_bytes(40, 3)
+ws = L.shampoo_root_inverse_newton_workspace_bytes(129, 3)
 def call(iterations):
     reset()
-    assert L.shampoo_root_inverse_newton(ctypes.c_void_p(1 << 36), 40, 3, ctypes.c_float(1e-6), P, ctypes.c_float(1e-6), iterations, ctypes.c_void_p(1 << 37), None,
+    assert L.shampoo_root_inverse_newton(ctypes.c_void_p(1 << 36), 129, 3, ctypes.c_float(1e-6), P, ctypes.c_float(1e-6), iterations, ctypes.c_void_p(1 << 37), None,
                                          None, ctypes.c_void_p(1 << 40), ws, ctypes.c_void_p(STREAM)) == 0
     return len(launches("gemm_mfma_kernel"))
 print(call(1), call(7))
 """.replace("P,", "%d," % p, 1))
     assert out[0] == "%d %d" % (launches, 7 * launches), out
+
+
+@pytest.mark.parametrize("n", [1, 40, 128])
+def test_a_small_newton_iteration_is_one_launch(lib, n):
+    """Whatever the cap: the arithmetic of a matrix does not change with the number of iterations that a call allows."""
+    out = host_hip.run(lib, r"""
+ws = L.shampoo_root_inverse_newton_workspace_bytes(N, 3)
+for cap in (1, 7, 8, 1000):
+    reset()
+    assert L.shampoo_root_inverse_newton(ctypes.c_void_p(1 << 36), N, 3, ctypes.c_float(1e-6), 4, ctypes.c_float(1e-6), cap, ctypes.c_void_p(1 << 37), None,
+                                         None, ctypes.c_void_p(1 << 40), ws, ctypes.c_void_p(STREAM)) == 0
+    print(len(entries()), [e.a for e in launches("newton_small_kernel")])
+""".replace("N,", "%d," % n))
+    assert out[:4] == ["1 [3]"] * 4, out
