@@ -1125,6 +1125,7 @@ constexpr int NEWTON_MATS = 7;   // M, M', X, X', T and two buffers for the powe
 
 NewtonLayout newton_layout(int n, int batch) {
   NewtonLayout e;
+  if (n <= NEWTON_SMALL) { e.bytes = ALIGN; return e; }      // newton_small_kernel keeps everything in registers and LDS
   e.mat = align_up((size_t)n * n * sizeof(float));
   // the kernels take the matrix index as grid.y
   e.chunk = (int)std::max<size_t>(1, std::min<size_t>(std::min<size_t>((size_t)std::max(batch, 1), 32768), EIG_CHUNK_BYTES / (NEWTON_MATS * e.mat)));

@@ -86,6 +86,18 @@ def test_workspace_holds_the_state_of_the_memory_rule():
     assert 35e9 < big < 60e9
 
 
+def test_workspace_of_a_newton_iteration():
+    """Seven matrices for each of a chunk where the iteration goes through memory; up to 128 x 128 it does not."""
+    L = B.lib()
+    assert [L.shampoo_root_inverse_newton_workspace_bytes(n, 2048) for n in (1, 33, 128)] == [256] * 3
+    assert L.shampoo_root_inverse_newton_workspace_bytes(129, 2048) >= 7 * 2048 * 129 * 129 * 4
+    # it is asked for all the same, as before
+    ok, a = ctypes.c_void_p(0x100000), ctypes.c_void_p(0x200000)
+    def call(workspace, nbytes):
+        return L.shampoo_root_inverse_newton(a, 40, 3, 1e-6, 4, 1e-6, 10, a, None, None, workspace, nbytes, None)
+    assert call(None, 256) == -4 and call(ctypes.c_void_p(0x100004), 256) == -4 and call(ok, 255) == -4
+
+
 def test_workspace_of_callers_that_need_eigenvectors():
     """The path without eigenvectors needs about twice the scratch of block Jacobi.  Callers that never take it -- warm
     starts, eigenvalues, exponents without a rational fit -- have no room for it."""
