@@ -23,6 +23,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "bf16_terms.h"
 #include "group.h"
 
@@ -45,59 +46,65 @@ struct NewtonArgs {
   float epsilon, scale, tol;
 };
 
-// Block row I of A = scale * sym(L) + eps I from the tiles (I, J) and (J, I), J <= I: f(r, c4, x) has row r of the tile, its columns
-// c4 ... c4 + 3 and their values.  Read along rows; the mirror image goes through LDS.  Read down its columns it took 360 us for the
-// norm and 460 for M_0 and X_0 of 64 matrices of 1024, 100 and 205 so.  256 threads.
 constexpr int NEWTON_TILE = 32;
-// Elements (i, j) ... (i, j + 3) of an n x n matrix, zeros past its edges.  quads: rows are whole 16-byte pieces (the sizes of blocks; a
-// caller's may be any).
-__device__ __forceinline__ void newton_get4(const float *a, int n, bool quads, int i, int j, float (&x)[4]) {
+// Elements (i, j), (i, j + step) ... of an n x n matrix, four of them, zeros past its edges.  step 1 is one 16-byte access, where rows are
+// whole pieces of 16 bytes (the sizes of blocks); a caller's may be any, and then neighbouring lanes take neighbouring elements.  With four
+// in a row of each lane, one by one, newton_prep_kernel took 22 us a launch for 64 matrices of 1023 (mean of all 101 of a call), 16 so.
+__device__ __forceinline__ void newton_get4(const float *a, int n, int step, int i, int j, float (&x)[4]) {
   const float *p = a + (int64_t)i * n + j;
-  if (quads) {
+  if (step == 1) {
     const float4 q = i < n && j < n ? *reinterpret_cast<const float4 *>(p) : make_float4(0.f, 0.f, 0.f, 0.f);
     x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
     return;
   }
 #pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = i < n && j + e < n ? p[e] : 0.f;
+  for (int e = 0; e < 4; ++e) x[e] = i < n && j + step * e < n ? p[step * e] : 0.f;
 }
-__device__ __forceinline__ void newton_put4(float *a, int n, bool quads, int i, int j, const float (&x)[4]) {
+__device__ __forceinline__ void newton_put4(float *a, int n, int step, int i, int j, const float (&x)[4]) {
   float *p = a + (int64_t)i * n + j;
-  if (quads) {
+  if (step == 1) {
     if (i < n && j < n) *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
     return;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (i < n && j + e < n) p[e] = x[e];
+    if (i < n && j + step * e < n) p[step * e] = x[e];
 }
 __device__ __forceinline__ bool newton_quads(const float *a, int n) { return n % 4 == 0 && reinterpret_cast<uintptr_t>(a) % 16 == 0; }
 
+// Block row I of A = scale * sym(L) + eps I from the tiles (I, J) and (J, I), J <= I: f(J, r, c, step, x) has row r of the tile, its columns
+// c, c + step ... and their values (step: a constant, known only at run time it cost newton_init_kernel 30 of 207 us for 64 matrices of 1024).
+// Read along rows; the mirror image goes through LDS.  Read down its columns it took 360 us for the norm and 460 for M_0 and X_0 of 64
+// matrices of 1024, 92 and 207 so; of 1023 380 and 490, 129 and 473 so.  256 threads.
 template <typename F> __device__ __forceinline__ void newton_block_row(const float *a, int n, int I, float scale, float eps, int &bad, F f) {
   __shared__ float mirror[NEWTON_TILE][NEWTON_TILE + 1];
-  const int r = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4, i = I * NEWTON_TILE + r, mj = I * NEWTON_TILE + c4;
-  const bool quads = newton_quads(a, n);
-  for (int J = 0; J <= I; ++J) {
-    const int j = J * NEWTON_TILE + c4, mi = J * NEWTON_TILE + r;
-    float x[4], y[4];
-    newton_get4(a, n, quads, i, j, x);
-    newton_get4(a, n, quads, mi, mj, y);
+  const auto tiles = [&](auto step_) {
+    constexpr int step = decltype(step_)::value;
+    const int r = threadIdx.x >> 3, c = (threadIdx.x & 7) * (step == 1 ? 4 : 1), i = I * NEWTON_TILE + r, mj = I * NEWTON_TILE + c;
+    for (int J = 0; J <= I; ++J) {
+      const int j = J * NEWTON_TILE + c, mi = J * NEWTON_TILE + r;
+      float x[4], y[4];
+      newton_get4(a, n, step, i, j, x);
+      newton_get4(a, n, step, mi, mj, y);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (!(fabsf(x[e]) <= 3.0e38f) || !(fabsf(y[e]) <= 3.0e38f)) bad = 1;
+      for (int e = 0; e < 4; ++e) {
+        if (!(fabsf(x[e]) <= 3.0e38f) || !(fabsf(y[e]) <= 3.0e38f)) bad = 1;
+      }
+      __syncthreads();                   // the tile before has been read
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mirror[r][c + step * e] = y[e];
+      __syncthreads();
+      double v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = (double)scale * 0.5 * ((double)x[e] + (double)mirror[c + step * e][r]);
+        if (i == j + step * e) v[e] += (double)eps;
+      }
+      f(J, r, c, step_, v);
     }
-    __syncthreads();                     // the tile before has been read
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mirror[r][c4 + e] = y[e];
-    __syncthreads();
-    double v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = (double)scale * 0.5 * ((double)x[e] + (double)mirror[c4 + e][r]);
-      if (i == j + e) v[e] += (double)eps;
-    }
-    f(J, r, c4, v);
-  }
+  };
+  if (newton_quads(a, n)) tiles(std::integral_constant<int, 1>{});
+  else tiles(std::integral_constant<int, 8>{});
 }
 
 // grid (ceil(n / 32), batch): a block row's part of the sum of squares, non-finite check.
@@ -106,10 +113,10 @@ __global__ __launch_bounds__(256) void newton_norm_kernel(const NewtonArgs g) {
   const int I = blockIdx.x, b = blockIdx.y, n = g.n, tid = threadIdx.x;
   double ss = 0.0;
   int bad = 0;
-  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c4, const double (&v)[4]) {
+  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c, auto step, const double (&v)[4]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (I * NEWTON_TILE + r < n && J * NEWTON_TILE + c4 + e < n) ss += (J < I ? 2.0 : 1.0) * (v[e] * v[e]);
+      if (I * NEWTON_TILE + r < n && J * NEWTON_TILE + c + step * e < n) ss += (J < I ? 2.0 : 1.0) * (v[e] * v[e]);
   });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) { ss += __shfl_xor(ss, off, 64); bad |= __shfl_xor(bad, off, 64); }
@@ -141,25 +148,25 @@ __global__ __launch_bounds__(256) void newton_init_kernel(const NewtonArgs g) {
   const double inv_cp = ok ? 1.0 / cp : 0.0;
   const float inv_c = ok ? (float)pow(cp, -1.0 / (double)g.p) : 0.f;
   float *M = g.M + (int64_t)b * n * n, *X = g.X + (int64_t)b * n * n;
-  const bool quads = newton_quads(M, n) && newton_quads(X, n);
   int bad = 0;
-  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c4, const double (&v)[4]) {
-    const int i = I * NEWTON_TILE + r, j = J * NEWTON_TILE + c4, mi = J * NEWTON_TILE + r, mj = I * NEWTON_TILE + c4;
+  // M and X start 256-byte aligned: where A's rows are whole pieces of 16 bytes, so are theirs
+  newton_block_row(g.a + (int64_t)b * g.a_stride, n, I, g.scale, g.epsilon, bad, [&](int J, int r, int c, auto step, const double (&v)[4]) {
+    const int i = I * NEWTON_TILE + r, j = J * NEWTON_TILE + c, mi = J * NEWTON_TILE + r, mj = I * NEWTON_TILE + c;
     float x[4], id[4], mirror[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       x[e] = (float)(v[e] * inv_cp);
-      id[e] = i == j + e ? inv_c : 0.f;
-      tile[r][c4 + e] = x[e];            // its last readers are behind a barrier of the next tile's
+      id[e] = i == j + step * e ? inv_c : 0.f;
+      tile[r][c + step * e] = x[e];      // its last readers are behind a barrier of the next tile's
     }
-    newton_put4(M, n, quads, i, j, x);
-    newton_put4(X, n, quads, i, j, id);
+    newton_put4(M, n, step, i, j, x);
+    newton_put4(X, n, step, i, j, id);
     __syncthreads();
     if (J == I) return;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { mirror[e] = tile[c4 + e][r]; id[e] = 0.f; }
-    newton_put4(M, n, quads, mi, mj, mirror);
-    newton_put4(X, n, quads, mi, mj, id);
+    for (int e = 0; e < 4; ++e) { mirror[e] = tile[c + step * e][r]; id[e] = 0.f; }
+    newton_put4(M, n, step, mi, mj, mirror);
+    newton_put4(X, n, step, mi, mj, id);
   });
   if (I == 0 && tid == 0) {
     g.done[b] = g.xdone[b] = ok ? 0 : 1;
@@ -196,6 +203,7 @@ __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
   }
   const float pp = (float)g.p, inv_p = 1.f / pp;
   const bool quads = newton_quads(g.M, n);                   // T and X_1 lie a multiple of 256 bytes further
+  const int c = quads ? 4 * lane : lane, step = quads ? 1 : 64;
   const int last = min((int)(blockIdx.x + 1) * NEWTON_ROWS, n);
   float worst = 0.f;
   for (int i = blockIdx.x * NEWTON_ROWS + w; i < last; i += 4) {
@@ -205,20 +213,20 @@ __global__ __launch_bounds__(256) void newton_prep_kernel(const NewtonArgs g) {
     const float inv_c = X1 ? g.X[row + i] : 0.f;
     float rs = 0.f;
 #pragma unroll 4
-    for (int j = 4 * lane; j < n; j += 256) {
+    for (int j = c; j < n; j += 256) {
       float m[4], t[4];
-      newton_get4(M, n, quads, 0, j, m);
+      newton_get4(M, n, step, 0, j, m);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float id = i == j + e ? 1.f : 0.f;
+        const float id = i == j + step * e ? 1.f : 0.f;
         t[e] = ((pp + 1.f) * id - m[e]) * inv_p;
         rs += fabsf(m[e] - id);
       }
-      newton_put4(T, n, quads, 0, j, t);
+      newton_put4(T, n, step, 0, j, t);
       if (X1) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) t[e] *= inv_c;
-        newton_put4(X1, n, quads, 0, j, t);
+        newton_put4(X1, n, step, 0, j, t);
       }
     }
 #pragma unroll

@@ -42,3 +42,34 @@ def test_ends_where_the_iteration_in_float64_ends(n, p, tol):
             # the same iterates up to float32 products: condition numbers up to 40, n-long sums, at most 10 iterations
             assert np.array_equal(got, got.T)
             assert np.linalg.norm(got - X) <= 2e-5 * np.linalg.norm(X), (cap, b)
+
+
+@pytest.mark.parametrize("n", [130, 131, 132, 160, 516])
+def test_matrices_that_start_anywhere(n):
+    """Rows of whole 16-byte pieces are read as such, all others element by element: the same X, bit for bit, since the sum of squares
+    of these entries (multiples of 1/64 up to 2 and n) is exact in any order."""
+    import ctypes
+    import torch
+    from paper_2309_06497_amd import binding as B
+    r = np.random.default_rng(n)
+    q = r.integers(-128, 129, (2, n, n)) / 64.0
+    a = (np.tril(q) + np.tril(q, -1).transpose(0, 2, 1) + np.floor(4 * np.sqrt(n)) * np.eye(n)).astype(np.float32)
+    room = torch.zeros(a.size + 4, dtype=torch.float32, device="cuda")
+    ws = torch.empty(B.lib().shampoo_root_inverse_newton_workspace_bytes(n, 2), dtype=torch.uint8, device="cuda")
+    got = []
+    for skew in range(4):
+        dev = room[skew:skew + a.size]
+        dev.copy_(torch.from_numpy(a).reshape(-1))
+        out = torch.zeros(a.size + 4, dtype=torch.float32, device="cuda")[3 - skew:][:a.size]
+        iters = torch.zeros(2, dtype=torch.int32, device="cuda")
+        rc = B.lib().shampoo_root_inverse_newton(ctypes.c_void_p(dev.data_ptr()), n, 2, 0.0, 4, 1e-3, 50, ctypes.c_void_p(out.data_ptr()),
+                                                 ctypes.c_void_p(iters.data_ptr()), None, ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+                                                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        got.append((out.cpu().numpy().reshape(2, n, n), iters.tolist()))
+    for x, k in got[1:]:
+        assert k == got[0][1] and np.array_equal(x, got[0][0])
+    lam, v = np.linalg.eigh(a.astype(np.float64))
+    assert lam.min() > 0
+    want = (v * lam[:, None, :] ** -0.25) @ v.transpose(0, 2, 1)
+    assert np.linalg.norm(got[0][0] - want) <= 2e-5 * np.linalg.norm(want)      # as above
