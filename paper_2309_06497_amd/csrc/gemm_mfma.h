@@ -573,8 +573,9 @@ __global__ __launch_bounds__(GEMM_THREADS, TILE == BM ? 2 : 4) void gemm_mfma_ke
   float *c = g.c + (int64_t)b * g.c_batch_stride;
   const int ldc = g.ldc;
   // The mirror image of four rows of a lane is four consecutive columns: one store, in 16-byte aligned rows (64 symmetric products of
-  // 1024: 535 us with four, 520 so)
-  const bool mirror4 = EPI == EPI_SYRK && (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(c) & 15) == 0;
+  // 1024: 535 us with four, 520 so).  Small tiles of bf16 operands that lie along k are kept at their five wavefronts per SIMD instead, which
+  // the four values would make four (200 of 301 rows to 202 of 202: 65 us with, 62 without; along rows 70.5 and 72.5).
+  const bool mirror4 = EPI == EPI_SYRK && (TILE == BM || sizeof(TA) == 4 || AO != K_CONTIG) && (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(c) & 15) == 0;
   float ss = 0.f;
 #pragma unroll
   for (int mi = 0; mi < WT; ++mi)
