@@ -73,3 +73,51 @@ def test_matrices_that_start_anywhere(n):
     assert lam.min() > 0
     want = (v * lam[:, None, :] ** -0.25) @ v.transpose(0, 2, 1)
     assert np.linalg.norm(got[0][0] - want) <= 2e-5 * np.linalg.norm(want)      # as above
+
+
+@pytest.mark.parametrize("n", [17, 64, 128, 129, 200, 513])
+@pytest.mark.parametrize("p", [1, 4])
+def test_tolerance_below_the_floor_of_float32(n, p):
+    """The norm of M_k - I cannot fall below about n 2^-24 times a few: 1e-6 ends an iteration by the square of the norm before, or
+    because the norm no longer halves, a step at most beside the float64 iteration's end and as close to the root."""
+    import torch
+    from oracle import shampoo_oracle as so
+    from paper_2309_06497_amd import binding as B
+    f32 = lambda v: float(np.float32(v))
+    a = factors(n, 5 * n + p)
+    x, iters, failed = B.shampoo_root_inverse_newton(torch.from_numpy(a).cuda(), 1e-3, p, 1e-6, 100, True, True)
+    assert not failed.any()
+    for b in range(4):
+        k = so.root_inverse_newton(a[b], f32(1e-3), p, f32(1e-6), 100)[1]
+        assert abs(int(iters[b]) - k) <= 1, b
+        lam, v = np.linalg.eigh(a[b].astype(np.float64))
+        want = (v * (lam + f32(1e-3)) ** (-1.0 / p)) @ v.T
+        assert np.linalg.norm(x[b].cpu().numpy() - want) <= 2e-5 * np.linalg.norm(want), b      # as above
+
+
+@pytest.mark.parametrize("n", [1, 31, 64, 96, 128, 129, 160])
+def test_matrices_that_fail_beside_others(n):
+    """One launch and many, and each number of tiles: not a number, an infinity, nothing at all, and matrices that are left alone by that."""
+    import ctypes
+    import torch
+    from paper_2309_06497_amd import binding as B
+    a = np.stack([factors(n, n)[0]] * 5)
+    a[0, n - 1, 0] = np.nan                # of one triangle
+    a[1, 0, n - 1] = np.inf
+    a[3] = 0.0                             # epsilon = 0: the norm is zero
+    dev = torch.from_numpy(a).cuda()
+    for cap in (1, 50):
+        x = torch.full((5, n, n), 7.0, device="cuda")
+        iters, failed = torch.full((5,), -1, dtype=torch.int32, device="cuda"), torch.full((5,), -1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(B.lib().shampoo_root_inverse_newton_workspace_bytes(n, 5), dtype=torch.uint8, device="cuda")
+        pointer = lambda t: ctypes.c_void_p(t.data_ptr())
+        rc = B.lib().shampoo_root_inverse_newton(pointer(dev), n, 5, 0.0, 4, 1e-3, cap, pointer(x), pointer(iters), pointer(failed), pointer(ws), ws.numel(),
+                                                 ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        assert failed.tolist() == [1, 1, 0, 1, 0] and [iters[b].item() for b in (0, 1, 3)] == [0, 0, 0]
+        for b in (0, 1, 3):
+            assert bool((x[b] == 7.0).all()), b
+        assert torch.equal(x[2], x[4]) and iters[2] == iters[4]
+    lam, v = np.linalg.eigh(a[2].astype(np.float64))
+    want = (v * lam ** -0.25) @ v.T
+    assert 1 <= int(iters[2]) < 50 and np.linalg.norm(x[2].cpu().numpy() - want) <= 1e-3 * np.linalg.norm(want)     # the tolerance
