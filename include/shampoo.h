@@ -339,7 +339,8 @@ int shampoo_root_inverse_static(const float *a, int32_t n, int32_t batch, float 
  *   X_{k+1} = X_k T_k,  M_{k+1} = T_k^p M_k,  T_k = ((p + 1) I - M_k) / p,
  * ended per matrix at the first k with ||M_k - I||_inf < tolerance, at k = max_iterations,
  * or when the norm has reached the floor of float32 arithmetic (below 0.1 and no longer
- * halving).  M_k itself is not formed where ||M_{k-1} - I||_inf^2 < tolerance, which bounds its norm.
+ * halving).  M_k itself is not formed where ||M_{k-1} - I||_inf^2 < tolerance, which bounds its norm
+ * (in exact arithmetic): the matrix ends at that k.
  * x_i = X_k approximates A_i^(-1/p).
  * a:          device, batch dense row-major symmetric n x n float32 matrices (read only)
  * p:          1, 2, 4 or 8 (else SHAMPOO_ERR_UNSUPPORTED)

@@ -127,8 +127,8 @@ __device__ __host__ __forceinline__ void grouped_pair(int cnt, int group, int r,
 
 // 1 / sqrt(x) and 1 / x for finite x > 0 (x != 0 for the reciprocal) to float64 accuracy: hardware estimate and two Newton
 // steps, each of which squares the relative error.  Over 2^20 values of all magnitudes the estimates are good to 2^-24.2 and 2^-24.4,
-// after one step 2^-47.8 and 2^-48.7, after two 2^-51.8 and 2^-52.2 (a third changes nothing but the length of the chains that
-// eliminations and reflections are).  (h y) y and not h (y y), which is as long: the square of y overflows for subnormal x.
+// after one step 2^-47.8 and 2^-48.7, after two 2^-51.9 and 2^-52.2, which are roundings (a third step of the square root: 2^-52.1, and
+// longer chains in eliminations and reflections).  (h y) y and not h (y y), which is as long: the square of y overflows for subnormal x.
 __device__ __forceinline__ double rsqrt_newton(double x) {
   const double h = 0.5 * x;
   double y = __builtin_amdgcn_rsq(x);

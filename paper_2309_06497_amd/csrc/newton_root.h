@@ -14,8 +14,11 @@
 // The last M_k is not formed where it would only be found close enough to I.  With E = M_k - I,
 //   M_{k+1} - I = (I - E / p)^p (I + E) - I = - (p + 1) / (2 p) E^2 + ...,
 // a polynomial whose coefficients alternate in sign from E^2 on and add up in absolute value to its value at -I, which is 1:
-// ||M_{k+1} - I|| <= ||E||^2 for ||E|| <= 1.  So ||E||^2 < tol is the paper's test on M_{k+1}, one product (X_{k+1} = X_k T_k) for four.
-// 64 matrices of 1024 (9 iterations): 20.8 -> 19.35 ms, with the same number of iterations; errors against float64 as before (9.0e-7 there).
+// ||M_{k+1} - I|| <= ||E||^2 for ||E|| <= 1.  So ||E||^2 < tol is in exact arithmetic the paper's test on M_{k+1}, one product
+// (X_{k+1} = X_k T_k) for four.  A tolerance below the floor of float32 (next paragraph) a formed M_{k+1} might not pass; such a matrix would
+// go on until its norm no longer halves, now it ends at k + 1.
+// 64 matrices of 1024 (9 iterations): 20.8 -> 19.35 ms.  For 129 ... 1024, p of 1 ... 8, condition numbers of 1.6 to above 1e6 and a tolerance of
+// 1e-6 (floor: 1.5e-5 and more) neither a number of iterations changed nor an error against float64 by more than 1 %.
 //
 // Arithmetic is float32: operands as three bf16 terms, products summed in float32 (gemm_mfma.h).  ||M_k - I||_inf cannot fall below
 // about n * 2^-24 * (a few) in that arithmetic, so besides the paper's test the iteration of
@@ -278,10 +281,11 @@ __global__ __launch_bounds__(256) void newton_finish_kernel(const NewtonFinishAr
 // below the diagonal.  Launch by launch such a root is 400 launches whatever its size (2.4 ms), nine of ten of them for
 // nothing.  M and X stay in registers, as tiles of MFMA results; the operands of a product go through LDS, mirrored and along
 // k (two matrices of 128 fill it).  With E = (I - M) / p, which is exact, X' = X + X E and M' = M + ((I + E)^p - I) M: a product rounds
-// at the size of E, not of T = I + E.  Products on the float32 matrix cores, in two accumulators that take turns: four cost spills.
+// at the size of E, not of T = I + E.  Products on the float32 matrix cores, in two accumulators that take turns.  From 97 on ten wavefronts leave
+// 168 registers to each, 35 too few: they spill between the products, not in them (with four accumulators 90; 2048 of 128 2.3 ms, 1.6 so).
 // One matrix of 64 x 64 2.37 ms in 400 launches, 0.056 so, of 128 x 128 2.36 and 0.18 ms; 2048 of them 3.02 and 0.33, 7.8 and 1.6 ms.
 // Bound by the chain of four products an iteration, which many matrices of 64 and all larger ones make on matrix cores that
-// are not evenly loaded (10 tiles on 4 SIMDs).  Errors against float64 a third to an eighth of those of the launches.  From 129 on
+// are not evenly loaded (10 tiles on 4 SIMDs).  Errors against float64 0.14 to 0.77 of those of the launches.  From 129 on
 // two matrices do not fit into LDS.
 struct NewtonSmallArgs {
   const float *a; float *x;             // [batch][n][n]
@@ -338,7 +342,6 @@ template <int NB> __global__ __launch_bounds__(32 * NB * (NB + 1)) void newton_s
     for (int e = 0; e < 2; ++e)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[e][v] = 0.f;
-#pragma unroll 2
     for (int q = 0; q < steps; ++q) {
       const float4 x = *reinterpret_cast<const float4 *>(pa + 8 * q), y = *reinterpret_cast<const float4 *>(pb + 8 * q);
       acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc[0], 0, 0, 0);
